@@ -111,7 +111,10 @@ ftk_status ftk_assign_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K,
  *                 point i only between centroids whose squared distances differ by less than
  *                 2 * detect_coef * B_i; in FTK_FT_STRICT it cannot move it at all.
  *   band_coef   : scores closer than band_coef * B_i are not ordered by the matrix path but
- *                 settled by exact re-evaluation. */
+ *                 settled by exact re-evaluation.
+ * Both describe the fp32 / fp64 matrix kernel of the problem, which is what runs with checksums or
+ * listed faults; an unprotected call may take the scan instead, which settles a wider band of its
+ * own and leaves no error of this form in its distances. */
 ftk_status ftk_ft_thresholds(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft,
                              double *detect_coef /* (host) */, double *band_coef /* (host) */);
 
@@ -127,7 +130,10 @@ ftk_status ftk_plan_padded_rows(ftk_dtype dtype, int64_t N, int32_t D, int32_t K
  *   X [N x D], C [K x D]  in  : read only.
  *   labels [N] int32      out : index of the nearest centroid.
  *   mindist [N] (dtype)   out : squared distance to it, >= 0; may be NULL.  Accuracy: points whose
- *                               decision was settled by exact re-evaluation, and every point of
+ *                               decision was settled by exact re-evaluation, every point of the
+ *                               scan that unprotected calls with enough centroids take (bf16
+ *                               matrix instructions on split operands name the centroid, the
+ *                               distance is evaluated from the rows), and every point of
  *                               the register-resident fp32 kernels (D <= 32; 32 < D <= 128 where
  *                               that kernel is dispatched), get the direct-difference value
  *                               (relative error of a few units in the last place of the
@@ -154,7 +160,9 @@ ftk_status ftk_kmeans_assign(ftk_dtype dtype, const void *X, const void *C, int6
  * ftk_static_scratch_bytes() = 16 MiB per GPU the library runs on, held until the process ends.
  * The call allocates nothing (no hipMalloc / hipFree, no events; the profiling aid below does
  * not apply to it).  A problem whose scratch exceeds the array (roughly N > 4 million points, or
- * K*D beyond a few million) is rejected with FTK_EWORKSPACE and nothing is enqueued.  Every call
+ * K*D beyond a few million) is rejected with FTK_EWORKSPACE and nothing is enqueued; one that fits
+ * only without the buffers of the scan (16 bytes per point and more) runs on the fp32 / fp64 matrix
+ * kernels, whose distances may differ in the last places.  Every call
  * on a GPU shares that GPU's array: calls must be ordered on one stream; calls that overlap on
  * one GPU race.  The buffer keeps the last call's contents; everything that must start at zero
  * is cleared by the call itself. */
@@ -306,7 +314,8 @@ ftk_status ftk_kmeans_fit_fast(ftk_dtype dtype, const void *X, int64_t N, int32_
 ftk_status ftk_seeded_indices(uint64_t seed, int64_t N, int32_t K, int64_t *idx_host);
 
 /* Profiling aid for benchmarks.  While enabled, every ftk_kmeans_assign call brackets its main
- * contraction kernel (not the small norm / refine kernels around it) with a pair of HIP events
+ * contraction kernel (not the small norm / refine kernels around it; on the scan path: the scan with
+ * its preparation and settlement) with a pair of HIP events
  * recorded on the call's stream.  ftk_profile_read waits for all recorded pairs, returns the
  * summed kernel time in milliseconds and the number of launches since the last read (host
  * pointers), and releases the events.  Not thread-safe; creates events, so keep it out of

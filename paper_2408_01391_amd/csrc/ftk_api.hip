@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "ftk_internal.h"
+#include "ftk_scan.h"
 
 namespace ftk {
 
@@ -133,10 +134,21 @@ size_t hcn_entries_max(ftk_dtype dtype, int64_t N, int D, int K)
     return (size_t)ceil_div((int64_t)need, 512) * 512 + 512;
 }
 
+// The scan (ftk_scan.hip) takes the assignments that carry neither checksums nor listed faults; a
+// forced kernel choice goes to the kernel it names.
+static ScanPlan route_scan(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
+{
+    if (ft != FTK_FT_OFF || n_faults > 0 || g_tuning.assign_variant != -1) return ScanPlan{};
+    return plan_scan(dtype, N, D, K);
+}
+
 // The workspace is carved for the larger of the two kernel variants so that its size does not
-// depend on which one the dispatcher picks.
+// depend on which one the dispatcher picks.  The scan's buffers share their bytes with those of the
+// label-sorted update, which no call uses at the same time (the tables of the other update path
+// stay apart: the batched step adds to them between assignments); assign_only: nothing beyond what
+// the assignment touches, the scan's buffers included if `scan`.
 Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft,
-                          bool assign_only)
+                          bool assign_only, bool scan)
 {
     (void)ft;
     const size_t esz = dtype == FTK_F32 ? 4 : 8;
@@ -161,7 +173,11 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
     w.wl_count = (int32_t *)take(4 * sizeof(int32_t));
     w.wl = (int32_t *)take((size_t)N * sizeof(int32_t));
     w.wg_refined = (int32_t *)take(((size_t)N / 64 + 2) * sizeof(int32_t));
-    if (assign_only) {  // the assignment step touches nothing beyond this point
+    const size_t scan_bytes = assign_only && !scan ? 0 : carve_scan(nullptr, plan_scan(dtype, N, D, K)).bytes;
+    w.scan = nullptr;
+    if (assign_only) {  // the assignment step touches nothing beyond its own buffers and the scan's
+        if (p) w.scan = (void *)(p + off);
+        off += scan_bytes;
         w.fx_sums = nullptr;
         w.upd_slab = nullptr;
         w.upd_cslab = nullptr;
@@ -175,7 +191,6 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
         w.total = off;
         return w;
     }
-    w.fx_sums = (int64_t *)take((size_t)K * D * 2 * sizeof(int64_t));  // two limbs per cell
     {   // shared by the two update paths: per-workgroup tables, or two tagged slots per walker
         const size_t slab_cells = (size_t)update_slab_cells_max(N, D, K);
         const size_t slot_cells = (size_t)update_walkers_max(N) * 2 * (size_t)D;
@@ -184,10 +199,14 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
         const size_t slot_tags = (size_t)update_walkers_max(N) * 2;
         w.upd_cslab = (int32_t *)take((slab_counts > slot_tags ? slab_counts : slot_tags) * sizeof(int32_t));
     }
-    w.absmax = (double *)take(2 * sizeof(double));
+    const size_t shared = off;
+    if (p) w.scan = (void *)(p + off);
+    w.fx_sums = (int64_t *)take((size_t)K * D * 2 * sizeof(int64_t));  // two limbs per cell
     w.sort_idx = (int32_t *)take((size_t)N * sizeof(int32_t));
     w.sort_lab = (int32_t *)take((size_t)N * sizeof(int32_t));
     w.sort_cursor = (int32_t *)take(((size_t)K + 1) * sizeof(int32_t));
+    if (off < shared + scan_bytes) off = shared + scan_bytes;
+    w.absmax = (double *)take(2 * sizeof(double));
     w.C_cur = take((size_t)K * D * esz);
     w.mindist = take((size_t)N * esz);
     w.inertia = (double *)take(FIT_MAX_ITERS_IN_WS * sizeof(double));
@@ -267,22 +286,26 @@ static bool g_profile = false;
 static std::vector<std::pair<hipEvent_t, hipEvent_t>> g_profile_events;
 
 static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t st, bool fast = false,
-                              bool allow_profile = true)
+                              bool own_scratch = false, bool allow_scan = true)
 {
     const bool aligned16 = ((uintptr_t)c.X % 16 == 0) && ((uintptr_t)c.C % 16 == 0);
+    const ScanPlan scan = fast || !allow_scan ? ScanPlan{} : route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     AssignPlan p;
-    if (fast) {
+    if (scan.ok) {
+        memset(&p, 0, sizeof(p));
+    } else if (fast) {
         memset(&p, 0, sizeof(p));
         plan_fast(c.N, c.D, c.K, c.ft, p);
     } else {
         p = plan_assign(c.dtype, c.N, c.D, c.K, c.ft, aligned16);
     }
-    // the carve is a prefix of the full one, so the assignment-only layout serves both callers
-    const Workspace w = carve_workspace(workspace, c.dtype, c.N, c.D, c.K, c.ft, !fast);
-    FTK_TRY(launch_centroid_prologue(c, p, w, st));
+    // own_scratch: the assignment's buffers are all there is.  Without the scan's they are a prefix of
+    // the full layout.
+    const Workspace w = carve_workspace(workspace, c.dtype, c.N, c.D, c.K, c.ft, own_scratch || !(fast || scan.ok), scan.ok);
+    if (!scan.ok) FTK_TRY(launch_centroid_prologue(c, p, w, st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     // at most 65536 pending pairs: a caller that enables profiling and never reads stops recording
-    const bool profile = g_profile && allow_profile && g_profile_events.size() < 65536;
+    const bool profile = g_profile && !own_scratch && g_profile_events.size() < 65536;
     if (profile) {
         FTK_TRY_HIP(hipEventCreate(&e0));
         if (hipError_t e = hipEventCreate(&e1); e != hipSuccess) {
@@ -291,7 +314,9 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
         }
         FTK_TRY_HIP(hipEventRecord(e0, st));
     }
-    if (fast)
+    if (scan.ok)
+        FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan), w, st));
+    else if (fast)
         FTK_TRY(launch_assign_fast(c, p, w, st));
     else
         FTK_TRY(launch_assign(c, p, w, st));
@@ -299,6 +324,7 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
         g_profile_events.emplace_back(e0, e1);  // owned by the list from here on
         FTK_TRY_HIP(hipEventRecord(e1, st));
     }
+    if (scan.ok) return FTK_OK;  // no list is left
     const int n_wg = (!fast && c.stats && p.variant == VAR_GENERIC) ? (int)p.workgroups : 0;
     FTK_TRY(launch_refine(c, w, n_wg, st));
     return FTK_OK;
@@ -500,7 +526,10 @@ ftk_status ftk_kmeans_assign_static(ftk_dtype dtype, const void *X, const void *
         return FTK_EINVAL;
     }
     if (stats) FTK_TRY(check_ptr(stats, 8, "stats"));
-    const size_t need = carve_workspace(nullptr, dtype, N, D, K, ft, true).total;
+    // a problem that fits the array only without the scan's buffers runs on the fp32 / fp64 kernels
+    const bool scan = route_scan(dtype, N, D, K, ft, n_faults).ok &&
+                      carve_workspace(nullptr, dtype, N, D, K, ft, true, true).total <= FTK_STATIC_SCRATCH_BYTES;
+    const size_t need = carve_workspace(nullptr, dtype, N, D, K, ft, true, false).total;
     if (need > FTK_STATIC_SCRATCH_BYTES) {
         set_error("problem needs %zu bytes of scratch, the static buffer holds %zu (N=%lld D=%d K=%d): "
                   "use ftk_kmeans_assign with a caller workspace", need, (size_t)FTK_STATIC_SCRATCH_BYTES,
@@ -511,7 +540,7 @@ ftk_status ftk_kmeans_assign_static(ftk_dtype dtype, const void *X, const void *
     void *scratch = nullptr;
     FTK_TRY(static_scratch_of_current_device(&scratch));
     AssignCall c{dtype, X, C, N, D, K, labels, mindist, ft, faults, n_faults, stats};
-    return assign_impl(c, scratch, (hipStream_t)hip_stream, false, false);
+    return assign_impl(c, scratch, (hipStream_t)hip_stream, false, true, scan);
 }
 
 static ftk_status check_fast(ftk_dtype dtype, int D)
@@ -653,13 +682,22 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
     // norms of the centroids once: they do not change inside the iteration
     AssignCall whole{dtype, X, C, batch_rows < N ? batch_rows : N, D, K, labels, mindist, FTK_FT_OFF, nullptr, 0, nullptr};
     AssignPlan pprev = plan_assign(dtype, whole.N, D, K, FTK_FT_OFF, aligned16);
-    FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
+    // the path is chosen for the whole problem, as in the two-call step
+    const ScanPlan scan = route_scan(dtype, N, D, K, FTK_FT_OFF, 0);
+    if (!scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
     for (int64_t b = 0; b < nbatch; ++b) {
         const int64_t r0 = b * batch_rows;
         const int64_t nb = N - r0 < batch_rows ? N - r0 : batch_rows;
         const char *Xb = (const char *)X + (size_t)r0 * D * esz;
         AssignCall c{dtype, Xb, C, nb, D, K, labels + r0, mindist ? (void *)((char *)mindist + (size_t)r0 * esz) : nullptr,
                      FTK_FT_OFF, nullptr, 0, nullptr};
+        if (scan.ok) {
+            Workspace wb = w;
+            wb.wl_count = w.batch_counters + 4 * b;
+            FTK_TRY(launch_scan_assign(c, cut_scan(dtype, nb, D, K), carve_scan(w.scan, scan), wb, st));
+            FTK_TRY(launch_update_batch(dtype, Xb, labels + r0, nb, D, K, x_absmax, w, ub, b == 0, st));
+            continue;
+        }
         AssignPlan p = plan_assign(dtype, nb, D, K, FTK_FT_OFF, aligned16);
         if (p.variant != pprev.variant || p.nkc * p.KC != pprev.nkc * pprev.KC || p.hcn_pad_inf != pprev.hcn_pad_inf) {
             // a shorter last batch may be planned for another kernel, whose padded norm vector differs

@@ -80,6 +80,7 @@ struct Workspace {
     int32_t *wl_count;  // [4]   0: refine work-list length, 1: block counter (small-D / fast kernels)
     int32_t *wl;        // [N]   refine work-list (point indices)
     int32_t *wg_refined;  // [N/64 + 2] points each workgroup of the generic kernel settled in place
+    void *scan;         // buffers of the scan (ftk_scan.h), sharing the update's bytes
     // update
     int64_t *fx_sums;   // [K*D][2] fixed-point sums, two limbs (label-sorted path)
     int64_t *upd_slab;  // [chunks][K*D] per-workgroup fixed-point tables (LDS path), or
@@ -105,7 +106,7 @@ constexpr int MAX_BATCHES = 4096;
 size_t hcn_entries_max(ftk_dtype dtype, int64_t N, int D, int K);
 // assign_only: stop after the assignment step's buffers (a prefix of the full layout)
 Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft,
-                          bool assign_only = false);
+                          bool assign_only = false, bool scan = false);
 // upper bounds of the update step's per-workgroup tables, independent of pointer alignment
 int64_t update_slab_chunks_max(int64_t N);
 int64_t update_slab_cells_max(int64_t N, int D, int K);

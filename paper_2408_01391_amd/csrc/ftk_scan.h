@@ -1,0 +1,50 @@
+// Assignment for the unprotected path: a scan on the bf16 matrix instructions names each point's
+// nearest centroid, further passes settle it exactly (see ftk_scan.hip).
+#pragma once
+
+#include "ftk_internal.h"
+
+namespace ftk {
+
+struct ScanPlan {
+    bool ok;
+    bool triple;        // rows of up to 8 features: three pieces per operand, one 16-value block per tile
+    bool stream;        // rows beyond 128 features: both operands streamed through LDS
+    int nb;             // blocks of 16 features in the centroid image (and of the compiled variant)
+    int tiles, tiles_pad;  // tiles of 32 centroids, and those the image holds (whole chunks)
+    int tpc, nch;       // tiles per staged chunk, chunks
+    int splits, cps;    // workgroups sharing a block of points, chunks each of them sweeps
+    int ct;             // stream: centroid tiles per wave
+    int64_t pblocks;    // blocks of 256 points
+    int64_t rec_reserve;  // records to reserve
+    bool resolve;       // listed points are settled by the scan's own third pass (else refine_kernel)
+    double band_coef;   // scores closer than band_coef * B cannot be ordered by the scan
+};
+
+// what the scan leaves of a point: its best score and centroid, the second-best score, and (written by
+// the settle pass for listed points) the score a centroid needs to be a candidate
+struct ScanRecord {
+    float m1, m2;
+    int32_t j1;
+    float thr;
+};
+
+struct ScanBuffers {
+    uint4 *image;       // [tiles_pad][nb][2][64] centroid pieces in fragment order
+    float *start;       // [tiles_pad][32] accumulator start values -||c||^2/2 (scaled), fragment order
+    float *tile_max;    // [tiles_pad] largest ||c||^2 (scaled) of a tile
+    double *scale;      // [1] the power of two both operands are multiplied by
+    ScanRecord *rec;    // [splits][N]
+    size_t bytes;
+};
+
+// the rule: which problems take this path, and how they are cut up
+ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K);
+// the cut alone, for a batch of a problem that takes this path
+ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K);
+// buffers for the whole problem and for any batch of it
+ScanBuffers carve_scan(void *base, const ScanPlan &whole);
+ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,
+                              hipStream_t st);
+
+}  // namespace ftk

@@ -1,0 +1,1151 @@
+// Assignment without fault tolerance for fp32 and fp64 data, in three passes:
+//
+//   scan    the contraction on the bf16 matrix instructions, both operands split into two bf16 pieces,
+//           fp32 accumulation.  Per point it keeps the best score, its centroid and the second-best
+//           score - nothing else;
+//   settle  the distance to the named centroid in direct-difference form, in the data's own type
+//           (Section 3.1.1), and the decision whether the scan could be trusted: where the two best
+//           scores are closer than the scan's error bound the point is listed;
+//   resolve the listed points: every centroid whose score lies within the bound of the best is
+//           evaluated in double.
+//
+// Results are therefore those of the fp32 / fp64 matrix kernels - labels exact up to the documented
+// ties, distances direct - while the contraction runs on hardware that does 16 (fp32) or 32 (fp64)
+// times as many multiplications a second.
+//
+// Error of a score, in units of u = 2^-24 times B = ||x|| max||c|| + max||c||^2 / 2.  A value is
+// x = x0 + x1 + r with x0 = bf16(x), x1 = bf16(x - x0): |x1| <= 2^-9 |x|, |r| <= 2^-18 |x|, the same
+// for c.  Kept are x0c0 + x0c1 + x1c0; lost are x1c1, r.c and x.r', 2^-18 each: 3 * 64 u = 192 u.  An
+// instruction rounds to within 7 u of what it adds up (measured, pinned by a test): 21 u per block of
+// 16 features.  Rows of up to 8 features leave half of a block empty, which holds the three-piece
+// form (six products, error 2 u) in the same three instructions.
+//
+// Both operands are multiplied by one power of two taken from two centroid rows, so that the scores
+// sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
+// the same (overflow, NaN) is found by the settle pass, whose test such a point cannot pass.
+#include <cmath>
+
+#include "ftk_internal.h"
+#include "ftk_mma.h"
+#include "ftk_scan.h"
+#include "ftk_smalld.h"
+
+namespace ftk {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// rows need no more than element alignment: 16-byte loads from 4- or 8-byte aligned addresses
+typedef float float4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef double double2e __attribute__((ext_vector_type(2), aligned(8)));
+
+constexpr int SC_THREADS = 256;  // resident scan: four waves of two point tiles
+constexpr int SC_PT = 2;
+constexpr int SC_POINTS = 256;   // points per workgroup (both scans)
+constexpr int SS_THREADS = 512;  // streaming scan: eight waves
+constexpr int FRAG_UNITS = 64;   // 16-byte units per fragment: one per lane
+constexpr int SCAN_FILL = 512;     // workgroups that fill the chip (resident scan; the streaming one runs one a unit)
+constexpr int SETTLE_ROWS = 4;   // rows a group of lanes settles at once
+constexpr float SCAN_FLOOR = 7.9e-31f;  // 2^-100: below it scores (of centroids near 1) may have lost digits to underflow
+
+struct ScanArgs {
+    const void *X;
+    const uint4 *image;
+    const float *start;
+    const double *scale;
+    int64_t N;
+    int D;
+    int tiles;   // tiles that hold centroids
+    int tpc;     // tiles per chunk
+    int nch;     // chunks
+    int cps;     // chunks per split
+    int splits;
+    int pblocks;
+    ScanRecord *rec;
+};
+
+// Copies from global memory to LDS without registers: lane i's 16 (4) bytes land at l + 16 (4) * i; l is
+// the same for the whole wave.  Written as assembly because the compiler, which cannot tell the
+// two halves of a double buffer apart, would wait for the copy before the next LDS read; every
+// copy is waited for with wait_loads() before the barrier that hands its buffer over.
+__device__ __forceinline__ void to_lds16(const void *g, void *l)
+{
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(g) : "memory", "m0");
+}
+__device__ __forceinline__ void to_lds4(const void *g, void *l)
+{
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(at), "v"(g) : "memory", "m0");
+}
+
+// wait until all but the youngest N memory loads, and all LDS accesses, are done
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+}
+
+__device__ __forceinline__ void split_pair(const float (&v)[8], uint4 &hi, uint4 &lo)
+{
+    bf16x8 p0, p1;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        p0[e] = (__bf16)v[e];
+        p1[e] = (__bf16)(v[e] - (float)p0[e]);  // the difference is exact
+    }
+    hi = __builtin_bit_cast(uint4, p0);
+    lo = __builtin_bit_cast(uint4, p1);
+}
+
+__device__ __forceinline__ void split_triple(const float (&v)[8], uint4 &a, uint4 &b, uint4 &c)
+{
+    bf16x8 p0, p1, p2;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        p0[e] = (__bf16)v[e];
+        const float r = v[e] - (float)p0[e];
+        p1[e] = (__bf16)r;
+        p2[e] = (__bf16)(r - (float)p1[e]);
+    }
+    a = __builtin_bit_cast(uint4, p0);
+    b = __builtin_bit_cast(uint4, p1);
+    c = __builtin_bit_cast(uint4, p2);
+}
+
+__device__ __forceinline__ uint4 select_units(bool c, const uint4 &a, const uint4 &b)
+{
+    return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
+}
+
+// Four features from `off`, without branches: whole quads by one access clamped into the row, the
+// quad that holds the row's end (RAG: D not a multiple of 4) from `tail`, zero beyond.
+template <typename T>
+struct Quad {
+    T v[4];
+};
+template <typename T>
+__device__ __forceinline__ Quad<T> load_quad(const T *p)
+{
+    Quad<T> q;
+    if constexpr (sizeof(T) == 4) {
+        const float4e f = *reinterpret_cast<const float4e *>(p);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q.v[e] = f[e];
+    } else {
+        const double2e f = *reinterpret_cast<const double2e *>(p);
+        const double2e h = *reinterpret_cast<const double2e *>(p + 2);
+        q.v[0] = f[0];
+        q.v[1] = f[1];
+        q.v[2] = h[0];
+        q.v[3] = h[1];
+    }
+    return q;
+}
+template <typename T, bool RAG>
+struct RowReader {
+    const T *row;
+    int D, Dq;  // features, and those in whole quads
+    T tail[3];
+    __device__ __forceinline__ RowReader(const T *r, int d) : row(r), D(d), Dq(d & ~3)
+    {
+        if constexpr (RAG) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) tail[e] = row[min(Dq + e, D - 1)];
+        }
+    }
+    __device__ __forceinline__ Quad<T> request(int off) const { return load_quad<T>(row + min(off, Dq - 4)); }
+    __device__ __forceinline__ Quad<T> keep(Quad<T> q, int off) const
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            T v = off < Dq ? q.v[e] : T(0);
+            if constexpr (RAG) {
+                if (e < 3) v = (off == Dq && Dq + e < D) ? tail[e < 3 ? e : 0] : v;
+            }
+            q.v[e] = v;
+        }
+        return q;
+    }
+};
+
+// ---- centroids: pieces in fragment order, start values, norms --------------------------------
+// One workgroup per tile of 32 centroids; lane l of a fragment supplies row l % 32 and the 8 features
+// 16b + 8(l/32) of block b (TRI: all 8 features; fragment 0 = (c0 | c1), fragment 1 = (c2 | c0)).
+template <typename T, bool TRI>
+__global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
+                                                              float *tile_max, double *scale, int32_t *wl_count)
+{
+    __shared__ double sh_n[16][32];
+    __shared__ T sh_m[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = (int)blockDim.x >> 6;
+    // the scale: the largest magnitude of rows 0 and K/2 goes to [1, 2)
+    T m = T(0);
+    for (int d = tid; d < D; d += blockDim.x) {
+        const T a = fabs(C[d]), b = fabs(C[(size_t)(K / 2) * D + d]);
+        m = a > m ? a : m;
+        m = b > m ? b : m;
+    }
+#pragma unroll
+    for (int k = 32; k >= 1; k >>= 1) {
+        const T o = __shfl_xor(m, k, 64);
+        m = o > m ? o : m;
+    }
+    if (lane == 0) sh_m[wave] = m;
+    __syncthreads();
+    for (int i = 0; i < nw; ++i) m = sh_m[i] > m ? sh_m[i] : m;
+    int e2 = 0;
+    if (m > T(0) && m < Mma<T>::huge()) e2 = ilogb(m);
+    constexpr int E2 = sizeof(T) == 4 ? 100 : 1000;
+    e2 = e2 > E2 ? E2 : (e2 < -E2 ? -E2 : e2);
+    const T s = (T)ldexp(1.0, -e2);
+    if (blockIdx.x == 0 && tid == 0) {
+        scale[0] = (double)s;
+        wl_count[0] = 0;
+        wl_count[1] = 0;
+    }
+    const int tile = blockIdx.x;
+    const int row = lane & 31, g = lane >> 5;
+    const int j = 32 * tile + row;
+    const T *c = C + (size_t)(j < K ? j : 0) * D;
+    double n = 0.0;
+    for (int b = wave; b < nb; b += nw) {
+        const int f0 = TRI ? 0 : 16 * b + 8 * g;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int d = f0 + e;
+            const T w = (j < K && d < D) ? c[d < D ? d : 0] * s : T(0);
+            n = fma((double)w, (double)w, n);
+            v[e] = (float)w;
+        }
+        uint4 *dst = image + ((size_t)tile * nb + b) * (2 * FRAG_UNITS) + lane;
+        if constexpr (TRI) {
+            uint4 a0, a1, a2;
+            split_triple(v, a0, a1, a2);
+            dst[0] = select_units(g != 0, a1, a0);
+            dst[FRAG_UNITS] = select_units(g != 0, a0, a2);
+        } else {
+            uint4 a0, a1;
+            split_pair(v, a0, a1);
+            dst[0] = a0;
+            dst[FRAG_UNITS] = a1;
+        }
+    }
+    if (!TRI) n += __shfl_xor(n, 32, 64);
+    if (lane < 32) sh_n[wave][lane] = n;
+    __syncthreads();
+    if (tid < 32) {
+        n = 0.0;
+        for (int i = 0; i < nw; ++i) n += sh_n[i][tid];
+        // register r of lane group gg reads row 8(r/4) + 4gg + r%4
+        const int gg = (tid >> 2) & 1, r = 4 * (tid >> 3) + (tid & 3);
+        start[tile * 32 + gg * 16 + r] = 32 * tile + tid < K ? (float)(-0.5 * n) : -__builtin_huge_valf();
+        float f = (float)n;
+#pragma unroll
+        for (int k = 16; k >= 1; k >>= 1) {
+            const float o = __shfl_xor(f, k, 64);
+            f = o > f ? o : f;  // a NaN row never wins and does not count
+        }
+        if (tid == 0) tile_max[tile] = f > 0.f ? f : 0.f;  // tid 0 may hold a NaN of its own
+    }
+}
+
+// ---- bookkeeping of the scans -----------------------------------------------------------------
+// Tile maximum, runner-up tile maximum and the 16 scores of the best tile of one lane: two scores
+// share a v_max3; the copy of the scores is skipped unless some lane of the wave found a better tile.
+struct ScanBest {
+    float m1, m2;
+    int t1;
+    floatx16 s;
+};
+
+__device__ __forceinline__ void scan_best_init(ScanBest &b)
+{
+    b.m1 = b.m2 = Mma<float>::neg_inf();
+    b.t1 = 0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) b.s[r] = Mma<float>::neg_inf();
+}
+
+__device__ __forceinline__ void scan_best_add(ScanBest &b, const floatx16 &acc, int T)
+{
+    float tm = max2f(acc[0], acc[1]);
+#pragma unroll
+    for (int r = 2; r < 16; r += 2) tm = max3f(tm, acc[r], acc[r + 1]);
+    const bool c = tm > b.m1;
+    b.m2 = __builtin_amdgcn_fmed3f(b.m1, b.m2, tm);
+    b.m1 = max2f(b.m1, tm);
+    if (__any(c)) {
+        b.t1 = c ? T : b.t1;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) b.s[r] = c ? acc[r] : b.s[r];
+    }
+}
+
+// best score, its centroid and the second best of a point (both lanes of the pair get them)
+__device__ __forceinline__ void scan_best_finish(const ScanBest &b, int g, float &m1, int &j1, float &m2)
+{
+    int r1 = 0;
+#pragma unroll
+    for (int r = 15; r >= 0; --r) r1 = b.s[r] == b.m1 ? r : r1;
+    float sec = b.m2;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sec = (r != r1 && b.s[r] > sec) ? b.s[r] : sec;
+    const int j = 32 * b.t1 + 8 * (r1 >> 2) + 4 * g + (r1 & 3);
+    const float om1 = __shfl_xor(b.m1, 32, 64), osec = __shfl_xor(sec, 32, 64);
+    const int oj = __shfl_xor(j, 32, 64);
+    const bool mine = b.m1 > om1 || (b.m1 == om1 && j < oj);
+    m1 = mine ? b.m1 : om1;
+    j1 = mine ? j : oj;
+    m2 = mine ? (sec > om1 ? sec : om1) : (osec > b.m1 ? osec : b.m1);
+    if (!(b.m1 == b.m1) || !(om1 == om1)) m2 = __builtin_huge_valf();  // NaN scores: not to be trusted
+}
+
+// ---- scan of rows of up to 128 features ---------------------------------------------------------
+// A wave keeps the pieces of its 2 x 32 points in registers for the whole sweep; the centroid image
+// passes through LDS in chunks of 16 or 32 KB, the next chunk copied (global memory to LDS, no
+// registers) while the current one is multiplied.  Fragments are stored lane by lane, so the copy is
+// linear and the reads are free of bank conflicts.  No settlement code: at 128 features 228 registers,
+// two workgroups of four waves per compute unit that wait at their own barriers.
+template <typename T, int NB, bool TRI, bool RAG>
+__global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_kernel(ScanArgs a)
+{
+    constexpr int TU = NB * 2 * FRAG_UNITS;  // units per tile
+    extern __shared__ __align__(16) uint4 lds4[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g = lane >> 5;
+    const int pb = (int)blockIdx.x / a.splits, split = (int)blockIdx.x % a.splits;
+    const int ch0 = split * a.cps, ch1 = min(ch0 + a.cps, a.nch);
+    const int cu = a.tpc * TU + ((a.tpc + 1) / 2) * 16;  // units of a chunk buffer: fragments, then start values
+    const int64_t p0 = (int64_t)pb * SC_POINTS + wave * (SC_PT * 32);
+
+    auto stage = [&](int ch, uint4 *buf) {
+        const int tile0 = ch * a.tpc;
+        const uint4 *src = a.image + (size_t)tile0 * TU;
+        const int n = a.tpc * TU / FRAG_UNITS;
+        for (int i = wave; i < n; i += SC_THREADS / 64) to_lds16(src + i * FRAG_UNITS + lane, buf + i * FRAG_UNITS);
+        // start values, two tiles a time (the array is padded by one tile)
+        const float *sv = a.start + tile0 * 32;
+        float *dst = reinterpret_cast<float *>(buf + a.tpc * TU);
+        for (int i = wave; 2 * i < a.tpc; i += SC_THREADS / 64) to_lds4(sv + i * 64 + lane, dst + i * 64);
+    };
+    stage(ch0, lds4);
+
+    const T s = (T)a.scale[0];
+    const T *X = reinterpret_cast<const T *>(a.X);
+    constexpr int NP = TRI ? 3 : 2;
+    uint4 b[SC_PT][NB][NP];
+#pragma unroll
+    for (int pt = 0; pt < SC_PT; ++pt) {
+        int64_t p = p0 + pt * 32 + col;
+        if (p >= a.N) p = a.N - 1;
+        const RowReader<T, RAG> row(X + p * a.D, a.D);
+        // all of a row's loads in flight together, unless that takes more registers than there are
+        constexpr int BATCH = sizeof(T) == 8 && NB > 4 ? NB / 2 : NB;
+        auto off = [&](int u) { return TRI ? 4 * u : 16 * (u >> 1) + 8 * g + 4 * (u & 1); };
+        Quad<T> q[2 * BATCH];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (k % BATCH == 0) {
+                if (k) asm volatile("" ::: "memory");
+#pragma unroll
+                for (int u = 0; u < 2 * BATCH; ++u) q[u] = row.request(off(2 * k + u));
+            }
+            float v[8];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const Quad<T> w = row.keep(q[2 * (k % BATCH) + h], off(2 * k + h));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
+            }
+            if constexpr (TRI) {
+                uint4 x0, x1, x2;
+                split_triple(v, x0, x1, x2);
+                b[pt][k][0] = x0;
+                b[pt][k][1] = x1;
+                b[pt][k][2] = select_units(g != 0, x2, x0);
+            } else {
+                split_pair(v, b[pt][k][0], b[pt][k][1]);
+            }
+        }
+    }
+    ScanBest best[SC_PT];
+#pragma unroll
+    for (int pt = 0; pt < SC_PT; ++pt) scan_best_init(best[pt]);
+    wait_loads<0>();
+    __syncthreads();
+
+    int cur = 0;
+    for (int ch = ch0; ch < ch1; ++ch) {
+        uint4 *buf = lds4 + cur * cu;
+        if (ch + 1 < ch1) stage(ch + 1, lds4 + (cur ^ 1) * cu);
+        const int nt = min(a.tpc, a.tiles - ch * a.tpc);
+        const float *hv = reinterpret_cast<const float *>(buf + a.tpc * TU) + g * 16;
+        for (int t = 0; t < nt; ++t) {
+            const uint4 *f = buf + t * TU + lane;
+            floatx16 acc[SC_PT];
+            {
+                floatx16 ci;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const floatx4 h = *reinterpret_cast<const floatx4 *>(hv + t * 32 + 4 * i);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ci[4 * i + e] = h[e];
+                }
+#pragma unroll
+                for (int pt = 0; pt < SC_PT; ++pt) acc[pt] = ci;
+            }
+            // the fragments of block k + 1 are requested before the instructions of block k are issued
+            uint4 n0 = f[0], n1 = f[FRAG_UNITS];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const bf16x8 a0 = __builtin_bit_cast(bf16x8, n0);
+                const bf16x8 a1 = __builtin_bit_cast(bf16x8, n1);
+                if (k + 1 < NB) {
+                    n0 = f[(2 * k + 2) * FRAG_UNITS];
+                    n1 = f[(2 * k + 3) * FRAG_UNITS];
+                }
+                // the products, smallest first; the chains of the two point tiles interleave
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int pt = 0; pt < SC_PT; ++pt) {
+                        const bf16x8 x = __builtin_bit_cast(bf16x8, TRI ? b[pt][k][i == 0 ? NP - 1 : (i == 1 ? 1 : 0)]
+                                                                        : b[pt][k][i == 1 ? 1 : 0]);
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i == 0 ? a1 : a0, x, acc[pt], 0, 0, 0);
+                    }
+            }
+            // keep that order through instruction scheduling, which would sink every read to its use
+            // (at four blocks the second pair of fragments does not fit the registers of three waves)
+            if constexpr (NB != 4) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+                for (int k = 0; k + 1 < NB; ++k) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 3 * SC_PT, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 3 * SC_PT, 0);
+            }
+#pragma unroll
+            for (int pt = 0; pt < SC_PT; ++pt) scan_best_add(best[pt], acc[pt], ch * a.tpc + t);
+        }
+        wait_loads<0>();  // the next chunk has arrived
+        __syncthreads();
+        cur ^= 1;
+    }
+#pragma unroll
+    for (int pt = 0; pt < SC_PT; ++pt) {
+        float m1, m2;
+        int j1;
+        scan_best_finish(best[pt], g, m1, j1, m2);
+        const int64_t p = p0 + pt * 32 + col;
+        if (g == 0 && p < a.N) {
+            a.rec[(int64_t)split * a.N + p] = ScanRecord{m1, m2, j1, 0.f};
+        }
+    }
+}
+
+// ---- scan of longer rows --------------------------------------------------------------------------
+// A workgroup multiplies 256 points by 64 * CT centroids, 32 features at a time through LDS (double
+// buffered, up to 128 KB): the centroid fragments are copied from the image, the rows of X are split
+// on the way - requested two stages ahead, split and stored one stage ahead, in between the matrix
+// instructions.  Wave w takes point tiles 2(w%4) .. +1 and the centroid tiles of half w/4.  The
+// workgroups that share a block of points run side by side on one XCD, so that X comes from memory
+// once whatever K.
+template <typename T, int CT, bool RAG>
+__global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
+{
+    constexpr int TPC = 2 * CT;  // centroid tiles per workgroup
+    constexpr int AU = TPC * 4 * FRAG_UNITS, BU = 8 * 4 * FRAG_UNITS;  // units per stage: centroids, points
+    extern __shared__ __align__(16) uint4 lds4[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g = lane >> 5;
+    // consecutive workgroups go to consecutive XCDs: those of one XCD that follow each other share points
+    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
+    const int ch = slot % a.nch;
+    const int pb = (slot / a.nch) * 8 + xcd;
+    if (pb >= a.pblocks) return;
+    const int D = a.D;
+    const int ns = (D + 31) >> 5;
+    const int nb = 2 * ns;  // blocks per tile of the image
+    const int wp = wave & 3, wc = wave >> 2;
+
+    // the features this thread brings in: 16 of block kb of row `wave * 32 + lane % 32`
+    const int kb = g;
+    int64_t pr = (int64_t)pb * SC_POINTS + wave * 32 + col;
+    if (pr >= a.N) pr = a.N - 1;
+    const T *X = reinterpret_cast<const T *>(a.X);
+    const RowReader<T, RAG> row(X + pr * D, D);
+    const T s = (T)a.scale[0];
+    Quad<T> xq[4];
+    auto request = [&](int st) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) xq[h] = row.request(32 * st + 16 * kb + 4 * h);
+    };
+    auto stage_centroids = [&](int st, uint4 *buf) {
+        if (TPC == 8 || wave < TPC) {
+            const uint4 *src = a.image + (((size_t)(ch * TPC + wave)) * nb + 2 * st) * (2 * FRAG_UNITS) + lane;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) to_lds16(src + i * FRAG_UNITS, buf + (wave * 4 + i) * FRAG_UNITS);
+        }
+    };
+    auto store_half = [&](int st, uint4 *buf, int gg) {  // features 8gg .. 8gg + 7 of the block
+        float v[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const Quad<T> w = row.keep(xq[2 * gg + h], 32 * st + 16 * kb + 8 * gg + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
+        }
+        uint4 hi, lo;
+        split_pair(v, hi, lo);
+        uint4 *dst = buf + AU + (wave * 4 + 2 * kb) * FRAG_UNITS + gg * 32 + col;
+        dst[0] = hi;
+        dst[FRAG_UNITS] = lo;
+    };
+
+    floatx16 acc[CT][SC_PT];
+    const int tile0 = ch * TPC + wc * CT;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const float *hv = a.start + (tile0 + c) * 32 + g * 16;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float h = hv[r];
+#pragma unroll
+            for (int pt = 0; pt < SC_PT; ++pt) acc[c][pt][r] = h;
+        }
+    }
+    request(0);
+    stage_centroids(0, lds4);
+    store_half(0, lds4, 0);
+    store_half(0, lds4, 1);
+    request(min(1, ns - 1));
+    wait_loads<0>();
+    __syncthreads();
+    for (int st = 0; st < ns; ++st) {
+        const uint4 *buf = lds4 + (st & 1) * (AU + BU);
+        uint4 *nxt = lds4 + ((st + 1) & 1) * (AU + BU);
+        // (the last stage repeats itself into the buffer nobody reads: no branch in the loop)
+        stage_centroids(min(st + 1, ns - 1), nxt);
+        const uint4 *af = buf + (wc * CT) * 4 * FRAG_UNITS + lane;
+        const uint4 *bf = buf + AU + (wp * 2) * 4 * FRAG_UNITS + lane;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            bf16x8 x0[SC_PT], x1[SC_PT];
+#pragma unroll
+            for (int pt = 0; pt < SC_PT; ++pt) {
+                x0[pt] = __builtin_bit_cast(bf16x8, bf[(pt * 4 + 2 * k) * FRAG_UNITS]);
+                x1[pt] = __builtin_bit_cast(bf16x8, bf[(pt * 4 + 2 * k + 1) * FRAG_UNITS]);
+            }
+            uint4 n0 = af[(2 * k) * FRAG_UNITS], n1 = af[(2 * k + 1) * FRAG_UNITS];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const bf16x8 a0 = __builtin_bit_cast(bf16x8, n0);
+                const bf16x8 a1 = __builtin_bit_cast(bf16x8, n1);
+                if (c + 1 < CT) {
+                    n0 = af[((c + 1) * 4 + 2 * k) * FRAG_UNITS];
+                    n1 = af[((c + 1) * 4 + 2 * k + 1) * FRAG_UNITS];
+                }
+#pragma unroll
+                for (int pt = 0; pt < SC_PT; ++pt)
+                    acc[c][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, x0[pt], acc[c][pt], 0, 0, 0);
+#pragma unroll
+                for (int pt = 0; pt < SC_PT; ++pt)
+                    acc[c][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x1[pt], acc[c][pt], 0, 0, 0);
+#pragma unroll
+                for (int pt = 0; pt < SC_PT; ++pt)
+                    acc[c][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x0[pt], acc[c][pt], 0, 0, 0);
+            }
+        }
+        store_half(min(st + 1, ns - 1), nxt, 0);
+        store_half(min(st + 1, ns - 1), nxt, 1);
+        // reads two fragments ahead; the rows of the next stage, requested at the end of the last one,
+        // are split between the matrix instructions of the second block (all eight waves would
+        // otherwise do it at once, with the matrix pipes idle)
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+        for (int i = 0; i < 2 * CT; ++i) {
+            if (i + 1 == CT) __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+            else if (i + 1 < 2 * CT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            if (i < CT) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 3 * SC_PT, 0);
+            } else {
+#pragma unroll
+                for (int m = 0; m < 3 * SC_PT; ++m) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 20 / CT, 0);
+                }
+            }
+        }
+        __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
+        request(min(st + 2, ns - 1));
+        wait_loads<sizeof(T) == 4 ? 4 : 8>();  // the centroids have arrived; the rows requested above travel on
+        __syncthreads();
+    }
+    // the records of the two centroid halves meet in LDS
+    float *xm1 = reinterpret_cast<float *>(lds4), *xm2 = xm1 + SC_POINTS;
+    int *xj = reinterpret_cast<int *>(xm2 + SC_POINTS);
+    float m1[SC_PT], m2[SC_PT];
+    int j1[SC_PT];
+#pragma unroll
+    for (int pt = 0; pt < SC_PT; ++pt) {
+        ScanBest best;
+        scan_best_init(best);
+#pragma unroll
+        for (int c = 0; c < CT; ++c) scan_best_add(best, acc[c][pt], tile0 + c);
+        scan_best_finish(best, g, m1[pt], j1[pt], m2[pt]);
+        if (wc == 1 && g == 0) {
+            const int i = (wp * 2 + pt) * 32 + col;
+            xm1[i] = m1[pt];
+            xm2[i] = m2[pt];
+            xj[i] = j1[pt];
+        }
+    }
+    __syncthreads();
+    if (wc == 0 && g == 0) {
+#pragma unroll
+        for (int pt = 0; pt < SC_PT; ++pt) {
+            const int i = (wp * 2 + pt) * 32 + col;
+            const float o1 = xm1[i], o2 = xm2[i];
+            const bool mine = m1[pt] >= o1;
+            const float hi = mine ? m1[pt] : o1, lo = mine ? o1 : m1[pt];
+            const float sec = fmaxf(fmaxf(m2[pt], o2), lo);
+            const int64_t p = (int64_t)pb * SC_POINTS + i;
+            if (p < a.N)
+                a.rec[(int64_t)ch * a.N + p] = ScanRecord{hi, sec, mine ? j1[pt] : xj[i], 0.f};
+        }
+    }
+}
+
+// ---- settle -----------------------------------------------------------------------------------
+// L lanes share a row (row-contiguous 16-byte loads) and take ROWS of them at once: the pass is a
+// chain of latencies - record, then the centroid's row - that only requests in flight can hide.
+// Every workgroup hands its listed points over with one atomic.
+struct SettleArgs {
+    ScanRecord *rec;
+    int splits;
+    const float *tile_max;
+    int tiles;
+    const double *scale;
+    int64_t N;
+    int D, K;
+    float band;
+    int32_t *labels;
+    int32_t *wl, *wl_count;
+};
+
+template <typename T, int L>
+__global__ __launch_bounds__(256) void scan_settle_kernel(const T *X, const T *C, T *mindist, SettleArgs a)
+{
+    constexpr int ROWS = SETTLE_ROWS;
+    constexpr int RPB = 256 / L;  // rows side by side
+    __shared__ float sh_max[4];
+    __shared__ int sh_n, sh_base;
+    __shared__ int32_t sh_list[RPB * ROWS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int sub = tid & (L - 1), grp = tid / L;
+    const int Dq = a.D & ~3;
+    int64_t pp[ROWS];
+    float m1[ROWS], m2[ROWS];
+    int j[ROWS];
+    const T *x[ROWS], *c[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        const int64_t p = ((int64_t)blockIdx.x * ROWS + u) * RPB + grp;
+        pp[u] = p < a.N ? p : a.N - 1;
+        const ScanRecord r = a.rec[pp[u]];
+        m1[u] = r.m1;
+        m2[u] = r.m2;
+        j[u] = r.j1;
+        x[u] = X + pp[u] * a.D;
+    }
+    if (tid == 0) sh_n = 0;
+    float cm = 0.f;
+    for (int i = tid; i < a.tiles; i += 256) cm = fmaxf(cm, a.tile_max[i]);
+#pragma unroll
+    for (int k = 32; k >= 1; k >>= 1) cm = fmaxf(cm, __shfl_xor(cm, k, 64));
+    if (lane == 0) sh_max[tid >> 6] = cm;
+    __syncthreads();
+    const float cmax2 = 1.000001f * fmaxf(fmaxf(sh_max[0], sh_max[1]), fmaxf(sh_max[2], sh_max[3]));
+    const float cmax = sqrtf(cmax2);
+    const T s = (T)a.scale[0];
+    for (int k = 1; k < a.splits; ++k) {
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const ScanRecord o = a.rec[(int64_t)k * a.N + pp[u]];
+            const bool mine = m1[u] >= o.m1;
+            m2[u] = fmaxf(fmaxf(m2[u], o.m2), mine ? o.m1 : m1[u]);
+            m1[u] = mine ? m1[u] : o.m1;
+            j[u] = mine ? j[u] : o.j1;
+        }
+    }
+    T d[ROWS];
+    float xn[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        j[u] = (unsigned)j[u] < (unsigned)a.K ? j[u] : 0;  // padding rows, when no score was a number
+        c[u] = C + (size_t)j[u] * a.D;
+        d[u] = T(0);
+        xn[u] = 0.f;
+    }
+    auto add = [&](int u, T xv, T cv) {
+        const T t = xv - cv;
+        d[u] = fma(t, t, d[u]);
+        const float w = (float)(xv * s);
+        xn[u] = fmaf(w, w, xn[u]);
+    };
+    for (int f = 4 * sub; f < Dq; f += 4 * L) {
+        Quad<T> xv[ROWS], cv[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            xv[u] = load_quad<T>(x[u] + f);
+            cv[u] = load_quad<T>(c[u] + f);
+        }
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) add(u, xv[u].v[e], cv[u].v[e]);
+    }
+    for (int f = Dq + sub; f < a.D; f += L)
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) add(u, x[u][f], c[u][f]);
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+#pragma unroll
+        for (int k = L / 2; k >= 1; k >>= 1) {
+            d[u] += __shfl_xor(d[u], k, 64);
+            xn[u] += __shfl_xor(xn[u], k, 64);
+        }
+        const int64_t p = ((int64_t)blockIdx.x * ROWS + u) * RPB + grp;
+        // 1.0001: the rounding of xn itself
+        const float bound = a.band * (sqrtf(xn[u]) * 1.0001f * cmax + 0.5f * cmax2) + SCAN_FLOOR;
+        if (sub == 0 && p < a.N) {
+            a.labels[p] = j[u];
+            if (mindist) mindist[p] = d[u];
+            if (!(m1[u] - m2[u] > bound)) {
+                sh_list[atomicAdd(&sh_n, 1)] = (int32_t)p;
+                a.rec[p].thr = m1[u] - bound;
+            }
+        }
+    }
+    __syncthreads();
+    const int n = sh_n;
+    if (n == 0) return;
+    if (tid == 0) sh_base = atomicAdd(a.wl_count, n);
+    __syncthreads();
+    for (int i = tid; i < n; i += 256) a.wl[sh_base + i] = sh_list[i];
+}
+
+// ---- resolve the listed points --------------------------------------------------------------------
+// A workgroup repeats the scan for 32 listed points at a time, now noting every centroid whose score
+// comes within the bound of the best, and evaluates those in direct-difference form in double, lowest
+// index on equal distance.  A point with more of them than are noted (or none: scores that are not
+// numbers) is compared with every centroid.  Listed points are few and scattered, so what counts is the
+// time of one group: sixteen waves share its sweep, the points' fragments sit in LDS, the centroids'
+// come straight from the image (L2), eight blocks in flight.
+struct ResolveArgs {
+    const uint4 *image;
+    const float *start;
+    const double *scale;
+    const ScanRecord *rec;
+    int64_t N;
+    int D, K, nb, tiles;
+    int32_t *labels;
+    const int32_t *wl, *wl_count;
+    ftk_ft_stats *stats;
+};
+
+// direct-difference distance in double by the L lanes of a group (every lane gets it)
+template <typename T, int L>
+__device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, int sub)
+{
+    const int Dq = D & ~3;
+    double d = 0.0;
+#pragma unroll 2
+    for (int f = 4 * sub; f < Dq; f += 4 * L) {
+        const Quad<T> xv = load_quad<T>(x + f), cv = load_quad<T>(c + f);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double t = (double)xv.v[e] - (double)cv.v[e];
+            d = fma(t, t, d);
+        }
+    }
+    for (int f = Dq + sub; f < D; f += L) {
+        const double t = (double)x[f] - (double)c[f];
+        d = fma(t, t, d);
+    }
+#pragma unroll
+    for (int k = L / 2; k >= 1; k >>= 1) d += __shfl_xor(d, k, 64);
+    return d;
+}
+
+constexpr int RS_THREADS = 1024, RS_CAP = 8;
+
+template <typename T, bool TRI, int L>
+__global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, const T *C, T *mindist, ResolveArgs a)
+{
+    constexpr int NP = TRI ? 3 : 2;
+    constexpr int GROUPS = RS_THREADS / L;
+    extern __shared__ __align__(16) uint4 lds4[];  // [nb][NP][64] fragments of the 32 points
+    __shared__ int32_t sh_p[32];
+    __shared__ float sh_thr[32];
+    __shared__ int sh_cnt[32];
+    __shared__ int32_t sh_j[32][RS_CAP];
+    __shared__ double sh_d[32][RS_CAP];
+    __shared__ double sh_bd[16];
+    __shared__ int sh_bj[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g = lane >> 5;
+    const int sub = tid & (L - 1), grp = tid / L;
+    const int n = a.wl_count[0];
+    const T s = (T)a.scale[0];
+    if (a.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&a.stats->refined, (unsigned long long)n);
+    for (int first = (int)blockIdx.x * 32; first < n; first += (int)gridDim.x * 32) {
+        const int np = min(32, n - first);
+        __syncthreads();  // the previous group is written out
+        if (tid < 32) {
+            const int32_t p = a.wl[first + min(tid, np - 1)];
+            sh_p[tid] = p;
+            sh_thr[tid] = a.rec[p].thr;
+            sh_cnt[tid] = 0;
+        }
+        const T *row = X + (int64_t)a.wl[first + min(col, np - 1)] * a.D;
+        for (int b = wave; b < a.nb; b += RS_THREADS / 64) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int f = (TRI ? 0 : 16 * b + 8 * g) + e;
+                const T w = row[min(f, a.D - 1)];
+                v[e] = f < a.D ? (float)(w * s) : 0.f;
+            }
+            uint4 *dst = lds4 + b * NP * FRAG_UNITS + lane;
+            if constexpr (TRI) {
+                uint4 x0, x1, x2;
+                split_triple(v, x0, x1, x2);
+                dst[0] = x0;
+                dst[FRAG_UNITS] = x1;
+                dst[2 * FRAG_UNITS] = select_units(g != 0, x2, x0);
+            } else {
+                uint4 x0, x1;
+                split_pair(v, x0, x1);
+                dst[0] = x0;
+                dst[FRAG_UNITS] = x1;
+            }
+        }
+        __syncthreads();
+        const float thr = sh_thr[col];
+        for (int t = wave; t < a.tiles; t += RS_THREADS / 64) {
+            floatx16 acc;
+            const float *hv = a.start + t * 32 + g * 16;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const floatx4 h = *reinterpret_cast<const floatx4 *>(hv + 4 * i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[4 * i + e] = h[e];
+            }
+            const uint4 *f = a.image + (size_t)t * a.nb * (2 * FRAG_UNITS) + lane;
+#pragma unroll 8
+            for (int b = 0; b < a.nb; ++b) {
+                const bf16x8 a0 = __builtin_bit_cast(bf16x8, f[(2 * b) * FRAG_UNITS]);
+                const bf16x8 a1 = __builtin_bit_cast(bf16x8, f[(2 * b + 1) * FRAG_UNITS]);
+                const uint4 *q = lds4 + b * NP * FRAG_UNITS + lane;
+                const bf16x8 x0 = __builtin_bit_cast(bf16x8, q[0]);
+                const bf16x8 x1 = __builtin_bit_cast(bf16x8, q[FRAG_UNITS]);
+                const bf16x8 xs = TRI ? __builtin_bit_cast(bf16x8, q[(NP - 1) * FRAG_UNITS]) : x0;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, xs, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x1, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x0, acc, 0, 0, 0);
+            }
+            float tm = fmaxf(acc[0], acc[1]);
+#pragma unroll
+            for (int r = 2; r < 16; r += 2) tm = max3f(tm, acc[r], acc[r + 1]);
+            if (__any(tm >= thr)) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int j = 32 * t + 8 * (r >> 2) + 4 * g + (r & 3);
+                    if (acc[r] >= thr && j < a.K) {
+                        const int at = atomicAdd(&sh_cnt[col], 1);
+                        if (at < RS_CAP) sh_j[col][at] = j;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        for (int job = grp; job < np * RS_CAP; job += GROUPS) {
+            const int k = job / RS_CAP, at = job % RS_CAP;
+            if (at < sh_cnt[k] && sh_cnt[k] <= RS_CAP) {
+                const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)sh_j[k][at] * a.D, a.D, sub);
+                if (sub == 0) sh_d[k][at] = d;
+            }
+        }
+        __syncthreads();
+        if (tid < np) {
+            const int m = sh_cnt[tid];
+            if (m >= 1 && m <= RS_CAP) {
+                double d = sh_d[tid][0];
+                int j = sh_j[tid][0];
+                for (int i = 1; i < m; ++i) {
+                    const double di = sh_d[tid][i];
+                    const int ji = sh_j[tid][i];
+                    const bool better = di < d || (di == d && ji < j);
+                    d = better ? di : d;
+                    j = better ? ji : j;
+                }
+                a.labels[sh_p[tid]] = j;
+                if (mindist) mindist[sh_p[tid]] = (T)d;
+            }
+        }
+        for (int k = 0; k < np; ++k) {
+            const int m = sh_cnt[k];
+            if (m >= 1 && m <= RS_CAP) continue;
+            const T *x = X + (int64_t)sh_p[k] * a.D;
+            double best = __builtin_huge_val();
+            int bj = 0x7fffffff;
+            for (int j = grp; j < a.K; j += GROUPS) {
+                const double d = group_sqdist<T, L>(x, C + (size_t)j * a.D, a.D, sub);
+                if (d < best || (d == best && j < bj)) {
+                    best = d;
+                    bj = j;
+                }
+            }
+#pragma unroll
+            for (int q = 32; q >= L; q >>= 1) {
+                const double od = __shfl_xor(best, q, 64);
+                const int oj = __shfl_xor(bj, q, 64);
+                const bool take = od < best || (od == best && oj < bj);
+                best = take ? od : best;
+                bj = take ? oj : bj;
+            }
+            __syncthreads();
+            if (lane == 0) {
+                sh_bd[wave] = best;
+                sh_bj[wave] = bj;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                for (int i = 1; i < RS_THREADS / 64; ++i)
+                    if (sh_bd[i] < best || (sh_bd[i] == best && sh_bj[i] < bj)) {
+                        best = sh_bd[i];
+                        bj = sh_bj[i];
+                    }
+                a.labels[sh_p[k]] = bj == 0x7fffffff ? 0 : bj;
+                if (mindist) mindist[sh_p[k]] = (T)best;
+            }
+        }
+    }
+}
+
+// ---- host ----------------------------------------------------------------------------------------
+static int resident_blocks(int D)
+{
+    const int nb = (int)ceil_div(D, 16);
+    return nb <= 4 ? nb : (nb <= 6 ? 6 : 8);
+}
+
+// Where the scan beats the fp32 / fp64 matrix kernels: they read X once, keep it in registers and
+// settle in place, the scan reads it twice in four launches, so it takes enough centroids (or enough
+// points, for their matrix work to outweigh two launches).  Whole calls, matrix kernels against scan:
+//   fp32   K = 32    loses everywhere (0.55 .. 0.85)
+//          K = 100   D = 128: N = 1 000 34 / 28 us, 2 * 10^4 35 / 34, 10^6 333 / 260; D = 16: 2 * 10^4 14 / 19,
+//                    10^6 83 / 57; D = 8: 10^6 45 / 47
+//          K = 256   D = 16: N = 2 * 10^4 25 / 22, 10^6 111 / 69; D = 8: 16 / 19, 10^6 63 / 59
+//          K = 1024  D = 4: N = 2 * 10^4 33 / 24, 2 * 10^5 51 / 46; D = 64: 10^6 1104 / 382
+//   fp64   K = 100   D = 64: N = 2 * 10^5 79 / 65, 2 * 10^4 23 / 32; D = 256: 2 * 10^5 251 / 276
+//          K = 256   D = 32: N = 2 * 10^4 25 / 26, 2 * 10^5 87 / 49; D = 256: 2 * 10^5 494 / 295
+//          K = 1024  D = 4: N = 2 * 10^4 34 / 25; D = 64: 2 * 10^5 518 / 131
+static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    if (D < 4 || K < 96) return false;
+    if (K >= 768) return true;
+    if (dtype == FTK_F32) {
+        if (D < 16) return K >= 512;
+        return K >= 192 || D >= 128 || N >= 100000;
+    }
+    return N >= 100000 && (K >= 192 || D <= 96);
+}
+
+ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    return scan_pays(dtype, N, D, K) ? cut_scan(dtype, N, D, K) : ScanPlan{};
+}
+
+ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    ScanPlan p = {};
+    p.ok = true;
+    p.triple = D <= 8;
+    p.stream = D > 128;
+    p.tiles = (int)ceil_div(K, 32);
+    p.pblocks = ceil_div(N, SC_POINTS);
+    if (p.stream) {
+        p.nb = 2 * (int)ceil_div(D, 32);
+        // whole chunks of up to eight tiles; smaller ones while the chip is not filled
+        int nch = (int)ceil_div(p.tiles, 8);
+        const int most = (int)ceil_div(p.tiles, 2);
+        while (nch < most && p.pblocks * nch < SCAN_FILL / 2) ++nch;
+        p.ct = (int)ceil_div(p.tiles, 2 * nch);
+        p.tpc = 2 * p.ct;
+        p.nch = (int)ceil_div(p.tiles, p.tpc);
+        p.splits = p.nch;
+        p.cps = 1;
+    } else {
+        p.nb = resident_blocks(D);
+        const int chunk = p.nb <= 4 ? 16 * 1024 : 32 * 1024;
+        int tpc = chunk / (p.nb * 2 * FRAG_UNITS * 16);
+        if (tpc > p.tiles) tpc = p.tiles;
+        p.tpc = tpc;
+        p.nch = (int)ceil_div(p.tiles, tpc);
+        // workgroups share a block of points while the chip is not filled
+        int splits = (int)ceil_div(SCAN_FILL, p.pblocks);
+        if (splits > p.nch) splits = p.nch;
+        p.cps = (int)ceil_div(p.nch, splits);
+        p.splits = (int)ceil_div(p.nch, p.cps);
+    }
+    p.tiles_pad = p.nch * p.tpc;
+    p.resolve = p.nb <= 72;  // 32 points' fragments fit in LDS; longer rows go to refine_kernel
+    // A batch of fewer points may be shared by more workgroups than the whole: splits <= SCAN_FILL /
+    // pblocks + 1 wherever there is more than the whole's, so this holds the records of any batch.
+    p.rec_reserve = (int64_t)p.splits * N;
+    if (p.rec_reserve < SCAN_FILL * SC_POINTS + N + SC_POINTS) p.rec_reserve = SCAN_FILL * SC_POINTS + N + SC_POINTS;
+    if (p.rec_reserve > (int64_t)p.tiles * N) p.rec_reserve = (int64_t)p.tiles * N;
+    const double u = Mma<float>::kEps;
+    p.band_coef = 2.0 * ((p.triple ? 4.0 : 196.0) + 21.0 * p.nb + (dtype == FTK_F64 ? 2.0 : 0.0)) * u;
+    return p;
+}
+
+ScanBuffers carve_scan(void *base, const ScanPlan &p)
+{
+    ScanBuffers b = {};
+    if (!p.ok) return b;
+    char *q = (char *)base;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        void *r = q ? (void *)(q + off) : nullptr;
+        off += align_up(bytes, 256);
+        return r;
+    };
+    // whole chunks of whatever size a batch is cut into: at most eight tiles (stream), tpc (resident)
+    const size_t tiles = p.stream ? (size_t)p.tiles + 8 : (size_t)p.tiles_pad;
+    b.image = (uint4 *)take(tiles * p.nb * 2 * FRAG_UNITS * 16);
+    b.start = (float *)take((tiles + 1) * 32 * 4);  // copied two tiles a time
+    b.tile_max = (float *)take(tiles * 4);
+    b.scale = (double *)take(8);
+    b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
+    b.bytes = off;
+    return b;
+}
+
+template <typename T, int NB, bool TRI>
+static void launch_resident(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
+{
+    const dim3 grid((unsigned)(p.pblocks * p.splits)), block(SC_THREADS);
+    const size_t lds = 2 * ((size_t)p.tpc * NB * 2 * FRAG_UNITS + (size_t)((p.tpc + 1) / 2) * 16) * 16;
+    if (a.D % 4)
+        hipLaunchKernelGGL((scan_resident_kernel<T, NB, TRI, true>), grid, block, lds, st, a);
+    else
+        hipLaunchKernelGGL((scan_resident_kernel<T, NB, TRI, false>), grid, block, lds, st, a);
+}
+
+template <typename T, int CT>
+static void launch_stream(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
+{
+    const dim3 grid((unsigned)(ceil_div(p.pblocks, 8) * 8 * p.nch)), block(SS_THREADS);
+    const size_t lds = 2 * (size_t)(2 * CT + 8) * 4 * FRAG_UNITS * 16;
+    if (a.D % 4)
+        hipLaunchKernelGGL((scan_stream_kernel<T, CT, true>), grid, block, lds, st, a);
+    else
+        hipLaunchKernelGGL((scan_stream_kernel<T, CT, false>), grid, block, lds, st, a);
+}
+
+// L lanes per row in both passes
+template <typename T, int L>
+static void launch_settle(const AssignCall &c, const ScanPlan &p, const SettleArgs &s, const ResolveArgs &r, hipStream_t st)
+{
+    const int rows = 256 / L * SETTLE_ROWS;
+    hipLaunchKernelGGL((scan_settle_kernel<T, L>), dim3((unsigned)ceil_div(c.N, rows)), dim3(256), 0, st, (const T *)c.X,
+                       (const T *)c.C, (T *)c.mindist, s);
+    if (!p.resolve) return;
+    const int64_t groups = ceil_div(c.N, 32);
+    const dim3 grid((unsigned)(groups < 512 ? groups : 512)), block(RS_THREADS);
+    if (p.triple)
+        hipLaunchKernelGGL((scan_resolve_kernel<T, true, L>), grid, block, (size_t)3 * FRAG_UNITS * 16, st, (const T *)c.X,
+                           (const T *)c.C, (T *)c.mindist, r);
+    else
+        hipLaunchKernelGGL((scan_resolve_kernel<T, false, L>), grid, block, (size_t)p.nb * 2 * FRAG_UNITS * 16, st,
+                           (const T *)c.X, (const T *)c.C, (T *)c.mindist, r);
+}
+
+template <typename T>
+static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,
+                                hipStream_t st)
+{
+    const dim3 cg((unsigned)p.tiles_pad), cb((unsigned)(p.nb < 16 ? 64 * p.nb : 1024));
+    if (p.triple)
+        hipLaunchKernelGGL((scan_centroids_kernel<T, true>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start,
+                           b.tile_max, b.scale, w.wl_count);
+    else
+        hipLaunchKernelGGL((scan_centroids_kernel<T, false>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start,
+                           b.tile_max, b.scale, w.wl_count);
+    ScanArgs a = {};
+    a.X = c.X;
+    a.image = b.image;
+    a.start = b.start;
+    a.scale = b.scale;
+    a.N = c.N;
+    a.D = c.D;
+    a.tiles = p.tiles;
+    a.tpc = p.tpc;
+    a.nch = p.nch;
+    a.cps = p.cps;
+    a.splits = p.splits;
+    a.pblocks = (int)p.pblocks;
+    a.rec = b.rec;
+    if (p.stream) {
+        switch (p.ct) {
+        case 1: launch_stream<T, 1>(a, p, st); break;
+        case 2: launch_stream<T, 2>(a, p, st); break;
+        case 3: launch_stream<T, 3>(a, p, st); break;
+        default: launch_stream<T, 4>(a, p, st); break;
+        }
+    } else if (p.triple) {
+        launch_resident<T, 1, true>(a, p, st);
+    } else {
+        switch (p.nb) {
+        case 1: launch_resident<T, 1, false>(a, p, st); break;
+        case 2: launch_resident<T, 2, false>(a, p, st); break;
+        case 3: launch_resident<T, 3, false>(a, p, st); break;
+        case 4: launch_resident<T, 4, false>(a, p, st); break;
+        case 6: launch_resident<T, 6, false>(a, p, st); break;
+        default: launch_resident<T, 8, false>(a, p, st); break;
+        }
+    }
+    SettleArgs s;
+    s.rec = b.rec;
+    s.splits = p.splits;
+    s.tile_max = b.tile_max;
+    s.tiles = p.tiles_pad;
+    s.scale = b.scale;
+    s.N = c.N;
+    s.D = c.D;
+    s.K = c.K;
+    s.band = (float)p.band_coef;
+    s.labels = c.labels;
+    s.wl = w.wl;
+    s.wl_count = w.wl_count;
+    const ResolveArgs r = {b.image, b.start, b.scale, b.rec,      c.N,       c.D,
+                           c.K,     p.nb,    p.tiles, c.labels, w.wl, w.wl_count, c.stats};
+    if (c.D <= 12) launch_settle<T, 2>(c, p, s, r, st);
+    else if (c.D <= 24) launch_settle<T, 4>(c, p, s, r, st);
+    else if (c.D <= 128) launch_settle<T, 8>(c, p, s, r, st);
+    else if (c.D <= 512) launch_settle<T, 16>(c, p, s, r, st);
+    else launch_settle<T, 64>(c, p, s, r, st);
+    FTK_TRY_HIP(hipGetLastError());
+    return p.resolve ? FTK_OK : launch_refine(c, w, 0, st);
+}
+
+ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w, hipStream_t st)
+{
+    return c.dtype == FTK_F32 ? launch_scan_t<float>(c, p, b, w, st) : launch_scan_t<double>(c, p, b, w, st);
+}
+
+}  // namespace ftk
