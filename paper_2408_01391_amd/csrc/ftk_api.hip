@@ -173,7 +173,7 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
     w.wl_count = (int32_t *)take(4 * sizeof(int32_t));
     w.wl = (int32_t *)take((size_t)N * sizeof(int32_t));
     w.wg_refined = (int32_t *)take(((size_t)N / 64 + 2) * sizeof(int32_t));
-    const size_t scan_bytes = assign_only && !scan ? 0 : carve_scan(nullptr, plan_scan(dtype, N, D, K)).bytes;
+    const size_t scan_bytes = assign_only && !scan ? 0 : carve_scan(nullptr, plan_scan(dtype, N, D, K), N).bytes;
     w.scan = nullptr;
     if (assign_only) {  // the assignment step touches nothing beyond its own buffers and the scan's
         if (p) w.scan = (void *)(p + off);
@@ -315,7 +315,7 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
         FTK_TRY_HIP(hipEventRecord(e0, st));
     }
     if (scan.ok)
-        FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan), w, st));
+        FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N), w, st));
     else if (fast)
         FTK_TRY(launch_assign_fast(c, p, w, st));
     else
@@ -694,7 +694,7 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
         if (scan.ok) {
             Workspace wb = w;
             wb.wl_count = w.batch_counters + 4 * b;
-            FTK_TRY(launch_scan_assign(c, cut_scan(dtype, nb, D, K), carve_scan(w.scan, scan), wb, st));
+            FTK_TRY(launch_scan_assign(c, cut_scan(dtype, nb, D, K), carve_scan(w.scan, scan, N), wb, st));
             FTK_TRY(launch_update_batch(dtype, Xb, labels + r0, nb, D, K, x_absmax, w, ub, b == 0, st));
             continue;
         }

@@ -21,11 +21,15 @@ struct ScanPlan {
     double band_coef;   // scores closer than band_coef * B cannot be ordered by the scan
 };
 
-// what the scan leaves of a point: its best score and centroid, the second-best score, and (written by
-// the settle pass for listed points) the score a centroid needs to be a candidate
+// what the scan leaves of a point: its best score and centroid, the second-best score
 struct ScanRecord {
     float m1, m2;
     int32_t j1;
+    int32_t unused;
+};
+// a point to resolve, and the score a centroid needs to be a candidate
+struct ScanListed {
+    int32_t point;
     float thr;
 };
 
@@ -35,6 +39,9 @@ struct ScanBuffers {
     float *tile_max;    // [tiles_pad] largest ||c||^2 (scaled) of a tile
     double *scale;      // [1] the power of two both operands are multiplied by
     ScanRecord *rec;    // [splits][N]
+    ScanListed *list;   // points to resolve: lists of equal capacity ...
+    int32_t *list_count;  // ... and a counter each
+    int32_t *tickets;   // [N/32 + 1] workgroups done with a group of listed points
     size_t bytes;
 };
 
@@ -43,7 +50,7 @@ ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // the cut alone, for a batch of a problem that takes this path
 ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // buffers for the whole problem and for any batch of it
-ScanBuffers carve_scan(void *base, const ScanPlan &whole);
+ScanBuffers carve_scan(void *base, const ScanPlan &whole, int64_t N);
 ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,
                               hipStream_t st);
 

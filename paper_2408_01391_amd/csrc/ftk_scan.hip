@@ -43,7 +43,10 @@ constexpr int SC_POINTS = 256;   // points per workgroup (both scans)
 constexpr int SS_THREADS = 512;  // streaming scan: eight waves
 constexpr int FRAG_UNITS = 64;   // 16-byte units per fragment: one per lane
 constexpr int SCAN_FILL = 512;     // workgroups that fill the chip (resident scan; the streaming one runs one a unit)
-constexpr int SETTLE_ROWS = 4;   // rows a group of lanes settles at once
+constexpr int SETTLE_ROWS_MAX = 512;  // rows of a workgroup
+constexpr int settle_rows(size_t element) { return element == 8 ? 2 : 4; }  // rows a group of lanes settles at once
+constexpr int SCAN_LISTS = 64;    // lists of points to resolve, a counter in a line of its own each
+constexpr int LIST_STRIDE = 32;
 constexpr float SCAN_FLOOR = 7.9e-31f;  // 2^-100: below it scores (of centroids near 1) may have lost digits to underflow
 
 struct ScanArgs {
@@ -172,7 +175,7 @@ struct RowReader {
 // 16b + 8(l/32) of block b (TRI: all 8 features; fragment 0 = (c0 | c1), fragment 1 = (c2 | c0)).
 template <typename T, bool TRI>
 __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
-                                                              float *tile_max, double *scale, int32_t *wl_count)
+                                                              float *tile_max, double *scale, int32_t *list_count, int lists)
 {
     __shared__ double sh_n[16][32];
     __shared__ T sh_m[16];
@@ -197,11 +200,8 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     constexpr int E2 = sizeof(T) == 4 ? 100 : 1000;
     e2 = e2 > E2 ? E2 : (e2 < -E2 ? -E2 : e2);
     const T s = (T)ldexp(1.0, -e2);
-    if (blockIdx.x == 0 && tid == 0) {
-        scale[0] = (double)s;
-        wl_count[0] = 0;
-        wl_count[1] = 0;
-    }
+    if (blockIdx.x == 0 && tid == 0) scale[0] = (double)s;
+    if (blockIdx.x == 0 && tid < lists) list_count[tid * LIST_STRIDE] = 0;
     const int tile = blockIdx.x;
     const int row = lane & 31, g = lane >> 5;
     const int j = 32 * tile + row;
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
         scan_best_finish(best[pt], g, m1, j1, m2);
         const int64_t p = p0 + pt * 32 + col;
         if (g == 0 && p < a.N) {
-            a.rec[(int64_t)split * a.N + p] = ScanRecord{m1, m2, j1, 0.f};
+            a.rec[(int64_t)split * a.N + p] = ScanRecord{m1, m2, j1, 0};
         }
     }
 }
@@ -612,15 +612,41 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
             const float sec = fmaxf(fmaxf(m2[pt], o2), lo);
             const int64_t p = (int64_t)pb * SC_POINTS + i;
             if (p < a.N)
-                a.rec[(int64_t)ch * a.N + p] = ScanRecord{hi, sec, mine ? j1[pt] : xj[i], 0.f};
+                a.rec[(int64_t)ch * a.N + p] = ScanRecord{hi, sec, mine ? j1[pt] : xj[i], 0};
         }
     }
+}
+
+// Sum over the L lanes of a group (every lane gets it; the same additions whatever the values).
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int L, typename V>
+__device__ __forceinline__ V group_sum(V v)
+{
+    v += dpp_move<0xB1>(v);                            // lane ^ 1
+    if constexpr (L >= 4) v += dpp_move<0x4E>(v);      // lane ^ 2
+    if constexpr (L >= 8) v += dpp_move<0x141>(v);     // the other four of eight
+    if constexpr (L >= 16) v += dpp_move<0x140>(v);    // the other eight of sixteen
+    if constexpr (L >= 32) v += __shfl_xor(v, 16, 64);
+    if constexpr (L >= 64) v += __shfl_xor(v, 32, 64);
+    return v;
 }
 
 // ---- settle -----------------------------------------------------------------------------------
 // L lanes share a row (row-contiguous 16-byte loads) and take ROWS of them at once: the pass is a
 // chain of latencies - record, then the centroid's row - that only requests in flight can hide.
-// Every workgroup hands its listed points over with one atomic.
+// A workgroup hands its listed points over with one atomic, to one of 64 lists: atomics on one word
+// follow one another at about 10 ns (2^21 x 32, K = 4096: 9 000 workgroups with something to list).
 struct SettleArgs {
     ScanRecord *rec;
     int splits;
@@ -631,35 +657,47 @@ struct SettleArgs {
     int D, K;
     float band;
     int32_t *labels;
-    int32_t *wl, *wl_count;
+    ScanListed *list;  // (point, score a candidate needs), or NULL: the points alone go to wl
+    int32_t *wl, *list_count;
+    int lists, list_cap;
+    int32_t *tickets;   // [N/32 + 1] cleared here for the pass that follows
 };
 
 template <typename T, int L>
-__global__ __launch_bounds__(256) void scan_settle_kernel(const T *X, const T *C, T *mindist, SettleArgs a)
+__global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T *C, T *mindist, SettleArgs a)
 {
-    constexpr int ROWS = SETTLE_ROWS;
+    constexpr int ROWS = settle_rows(sizeof(T));
     constexpr int RPB = 256 / L;  // rows side by side
     __shared__ float sh_max[4];
     __shared__ int sh_n, sh_base;
-    __shared__ int32_t sh_list[RPB * ROWS];
+    __shared__ int32_t sh_lab[RPB * ROWS];   // ~label for listed points
+    __shared__ T sh_dist[RPB * ROWS];
+    __shared__ float sh_thr[RPB * ROWS];
     const int tid = threadIdx.x, lane = tid & 63;
     const int sub = tid & (L - 1), grp = tid / L;
     const int Dq = a.D & ~3;
+    const int64_t first = (int64_t)blockIdx.x * (ROWS * RPB);
     int64_t pp[ROWS];
     float m1[ROWS], m2[ROWS];
     int j[ROWS];
     const T *x[ROWS], *c[ROWS];
+    Quad<T> xv[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
-        const int64_t p = ((int64_t)blockIdx.x * ROWS + u) * RPB + grp;
+        const int64_t p = first + u * RPB + grp;
         pp[u] = p < a.N ? p : a.N - 1;
+        x[u] = X + pp[u] * a.D;
         const ScanRecord r = a.rec[pp[u]];
         m1[u] = r.m1;
         m2[u] = r.m2;
         j[u] = r.j1;
-        x[u] = X + pp[u] * a.D;
     }
+    // the first piece of every row travels with the records
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(x[u] + min(4 * sub, Dq - 4));
     if (tid == 0) sh_n = 0;
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + tid;
+    if (i0 * 32 < a.N) a.tickets[i0] = 0;
     float cm = 0.f;
     for (int i = tid; i < a.tiles; i += 256) cm = fmaxf(cm, a.tile_max[i]);
 #pragma unroll
@@ -688,52 +726,71 @@ __global__ __launch_bounds__(256) void scan_settle_kernel(const T *X, const T *C
         d[u] = T(0);
         xn[u] = 0.f;
     }
-    auto add = [&](int u, T xv, T cv) {
-        const T t = xv - cv;
+    auto add = [&](int u, T xe, T ce) {
+        const T t = xe - ce;
         d[u] = fma(t, t, d[u]);
-        const float w = (float)(xv * s);
+        const float w = (float)(xe * s);
         xn[u] = fmaf(w, w, xn[u]);
     };
-    for (int f = 4 * sub; f < Dq; f += 4 * L) {
-        Quad<T> xv[ROWS], cv[ROWS];
+    for (int f = 4 * sub; f < Dq;) {
+        Quad<T> cv[ROWS];
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-            xv[u] = load_quad<T>(x[u] + f);
-            cv[u] = load_quad<T>(c[u] + f);
-        }
+        for (int u = 0; u < ROWS; ++u) cv[u] = load_quad<T>(c[u] + f);
 #pragma unroll
         for (int u = 0; u < ROWS; ++u)
 #pragma unroll
             for (int e = 0; e < 4; ++e) add(u, xv[u].v[e], cv[u].v[e]);
+        f += 4 * L;
+        if (f < Dq)
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(x[u] + f);
     }
     for (int f = Dq + sub; f < a.D; f += L)
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) add(u, x[u][f], c[u][f]);
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
-#pragma unroll
-        for (int k = L / 2; k >= 1; k >>= 1) {
-            d[u] += __shfl_xor(d[u], k, 64);
-            xn[u] += __shfl_xor(xn[u], k, 64);
-        }
-        const int64_t p = ((int64_t)blockIdx.x * ROWS + u) * RPB + grp;
-        // 1.0001: the rounding of xn itself
-        const float bound = a.band * (sqrtf(xn[u]) * 1.0001f * cmax + 0.5f * cmax2) + SCAN_FLOOR;
-        if (sub == 0 && p < a.N) {
-            a.labels[p] = j[u];
-            if (mindist) mindist[p] = d[u];
-            if (!(m1[u] - m2[u] > bound)) {
-                sh_list[atomicAdd(&sh_n, 1)] = (int32_t)p;
-                a.rec[p].thr = m1[u] - bound;
-            }
+        const T dist = group_sum<L>(d[u]);
+        const float norm = group_sum<L>(xn[u]);
+        // 1.0001: the rounding of the norm itself
+        const float bound = a.band * (sqrtf(norm) * 1.0001f * cmax + 0.5f * cmax2) + SCAN_FLOOR;
+        const bool listed = !(m1[u] - m2[u] > bound);
+        if (sub == 0) {
+            sh_lab[u * RPB + grp] = listed ? ~j[u] : j[u];
+            sh_dist[u * RPB + grp] = dist;
+            sh_thr[u * RPB + grp] = m1[u] - bound;
         }
     }
     __syncthreads();
-    const int n = sh_n;
-    if (n == 0) return;
-    if (tid == 0) sh_base = atomicAdd(a.wl_count, n);
+    // results and the list leave in whole lines
+    int mine[(RPB * ROWS + 255) / 256];
+#pragma unroll
+    for (int k = 0; k < (RPB * ROWS + 255) / 256; ++k) {
+        const int i = k * 256 + tid;
+        const int64_t p = first + i;
+        mine[k] = -1;
+        if (i < RPB * ROWS && p < a.N) {
+            const int v = sh_lab[i];
+            a.labels[p] = v < 0 ? ~v : v;
+            if (mindist) mindist[p] = sh_dist[i];
+            if (v < 0) mine[k] = atomicAdd(&sh_n, 1);
+        }
+    }
     __syncthreads();
-    for (int i = tid; i < n; i += 256) a.wl[sh_base + i] = sh_list[i];
+    if (sh_n == 0) return;
+    const int which = (int)blockIdx.x % a.lists;
+    if (tid == 0) sh_base = atomicAdd(a.list_count + which * LIST_STRIDE, sh_n);
+    __syncthreads();
+    const int64_t at = (int64_t)which * a.list_cap + sh_base;
+#pragma unroll
+    for (int k = 0; k < (RPB * ROWS + 255) / 256; ++k) {
+        if (mine[k] < 0) continue;
+        const int i = k * 256 + tid;
+        if (a.list)
+            a.list[at + mine[k]] = ScanListed{(int32_t)(first + i), sh_thr[i]};
+        else
+            a.wl[at + mine[k]] = (int32_t)(first + i);
+    }
 }
 
 // ---- resolve the listed points --------------------------------------------------------------------
@@ -741,19 +798,32 @@ __global__ __launch_bounds__(256) void scan_settle_kernel(const T *X, const T *C
 // comes within the bound of the best, and evaluates those in direct-difference form in double, lowest
 // index on equal distance.  A point with more of them than are noted (or none: scores that are not
 // numbers) is compared with every centroid.  Listed points are few and scattered, so what counts is the
-// time of one group: sixteen waves share its sweep, the points' fragments sit in LDS, the centroids'
-// come straight from the image (L2), eight blocks in flight.
+// time of one group: eight waves share its sweep, the points' fragments sit in LDS, the centroids'
+// come straight from the image (L2), eight blocks in flight.  That read is what a group waits for (60000 x
+// 1024, K = 1024: 4 MB at 64 bytes a clock, 120 us), so `splits` workgroups share the centroids of one
+// group where the records leave room for their results; the last of them to finish combines these.
 struct ResolveArgs {
     const uint4 *image;
     const float *start;
     const double *scale;
-    const ScanRecord *rec;
+    ScanRecord *rec;
     int64_t N;
-    int D, K, nb, tiles;
+    int D, K, nb, tiles, splits;
     int32_t *labels;
-    const int32_t *wl, *wl_count;
+    const ScanListed *list;
+    const int32_t *list_count;
+    int list_cap;
+    int32_t *tickets;
     ftk_ft_stats *stats;
 };
+
+// result of one workgroup for one point, in the place of its scan record
+struct ResolveSlot {
+    double d;
+    int32_t j;  // -1: no candidate, -2: more than are noted
+    int32_t unused;
+};
+static_assert(sizeof(ResolveSlot) == sizeof(ScanRecord), "layout");
 
 // direct-difference distance in double by the L lanes of a group (every lane gets it)
 template <typename T, int L>
@@ -774,12 +844,10 @@ __device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, in
         const double t = (double)x[f] - (double)c[f];
         d = fma(t, t, d);
     }
-#pragma unroll
-    for (int k = L / 2; k >= 1; k >>= 1) d += __shfl_xor(d, k, 64);
-    return d;
+    return group_sum<L>(d);
 }
 
-constexpr int RS_THREADS = 1024, RS_CAP = 8;
+constexpr int RS_THREADS = 512, RS_CAP = 8;
 
 template <typename T, bool TRI, int L>
 __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, const T *C, T *mindist, ResolveArgs a)
@@ -794,29 +862,57 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     __shared__ double sh_d[32][RS_CAP];
     __shared__ double sh_bd[16];
     __shared__ int sh_bj[16];
+    __shared__ double sh_bd32[32];
+    __shared__ int32_t sh_code[32];
+    __shared__ int sh_last;
+    const int S = a.splits, split = (int)blockIdx.x % S, per = (a.tiles + S - 1) / S;
+    const int tile_end = min(a.tiles, (split + 1) * per);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
     const int sub = tid & (L - 1), grp = tid / L;
-    const int n = a.wl_count[0];
     const T s = (T)a.scale[0];
+    __shared__ int sh_pre[SCAN_LISTS + 1];  // listed points before each list
+    __shared__ int32_t sh_job[32 * RS_CAP];
+    __shared__ int sh_jobs;
+    if (wave == 0) {
+        int v = a.list_count[lane * LIST_STRIDE];
+#pragma unroll
+        for (int k = 1; k < 64; k <<= 1) {
+            const int o = __shfl_up(v, k, 64);
+            v += lane >= k ? o : 0;
+        }
+        sh_pre[lane + 1] = v;
+        if (lane == 0) sh_pre[0] = 0;
+    }
+    __syncthreads();
+    const int n = sh_pre[SCAN_LISTS];
+    auto listed_point = [&](int i) {  // the i-th of all lists
+        int q = 0;
+#pragma unroll
+        for (int k = SCAN_LISTS / 2; k >= 1; k >>= 1) q += sh_pre[q + k] <= i ? k : 0;
+        return a.list[(int64_t)q * a.list_cap + (i - sh_pre[q])];
+    };
     if (a.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&a.stats->refined, (unsigned long long)n);
-    for (int first = (int)blockIdx.x * 32; first < n; first += (int)gridDim.x * 32) {
+    for (int first = (int)blockIdx.x / S * 32; first < n; first += (int)gridDim.x / S * 32) {
         const int np = min(32, n - first);
         __syncthreads();  // the previous group is written out
         if (tid < 32) {
-            const int32_t p = a.wl[first + min(tid, np - 1)];
-            sh_p[tid] = p;
-            sh_thr[tid] = a.rec[p].thr;
+            const ScanListed e = listed_point(first + min(tid, np - 1));
+            sh_p[tid] = e.point;
+            sh_thr[tid] = e.thr;
             sh_cnt[tid] = 0;
         }
-        const T *row = X + (int64_t)a.wl[first + min(col, np - 1)] * a.D;
+        __syncthreads();
+        const RowReader<T, true> row(X + (int64_t)sh_p[col] * a.D, a.D);
+#pragma unroll 2
         for (int b = wave; b < a.nb; b += RS_THREADS / 64) {
+            const int f0 = TRI ? 0 : 16 * b + 8 * g;
+            const Quad<T> q0 = row.keep(row.request(f0), f0), q1 = row.keep(row.request(f0 + 4), f0 + 4);
             float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int f = (TRI ? 0 : 16 * b + 8 * g) + e;
-                const T w = row[min(f, a.D - 1)];
-                v[e] = f < a.D ? (float)(w * s) : 0.f;
+            for (int e = 0; e < 4; ++e) {
+                v[e] = (float)(q0.v[e] * s);
+                v[4 + e] = (float)(q1.v[e] * s);
             }
             uint4 *dst = lds4 + b * NP * FRAG_UNITS + lane;
             if constexpr (TRI) {
@@ -834,20 +930,45 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
         }
         __syncthreads();
         const float thr = sh_thr[col];
-        for (int t = wave; t < a.tiles; t += RS_THREADS / 64) {
-            floatx16 acc;
-            const float *hv = a.start + t * 32 + g * 16;
+        // this wave's tiles, block by block, four blocks and the next tile's start values in flight
+        const int t0 = split * per + wave;
+        const int total = t0 < tile_end ? ((tile_end - t0 - 1) / (RS_THREADS / 64) + 1) * a.nb : 0;
+        uint4 ring[4][2];
+        int lt = t0, lb = 0;  // tile and block of the next request
+        auto request = [&](uint4 (&r)[2]) {
+            const uint4 *f = a.image + ((size_t)min(lt, a.tiles - 1) * a.nb + lb) * (2 * FRAG_UNITS) + lane;
+            r[0] = f[0];
+            r[1] = f[FRAG_UNITS];
+            if (++lb == a.nb) {
+                lb = 0;
+                lt += RS_THREADS / 64;
+            }
+        };
+        floatx16 ci, acc;
+        auto request_start = [&](int t) {
+            const float *hv = a.start + min(t, a.tiles - 1) * 32 + g * 16;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const floatx4 h = *reinterpret_cast<const floatx4 *>(hv + 4 * i);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[4 * i + e] = h[e];
+                for (int e = 0; e < 4; ++e) ci[4 * i + e] = h[e];
             }
-            const uint4 *f = a.image + (size_t)t * a.nb * (2 * FRAG_UNITS) + lane;
-#pragma unroll 8
-            for (int b = 0; b < a.nb; ++b) {
-                const bf16x8 a0 = __builtin_bit_cast(bf16x8, f[(2 * b) * FRAG_UNITS]);
-                const bf16x8 a1 = __builtin_bit_cast(bf16x8, f[(2 * b + 1) * FRAG_UNITS]);
+        };
+        request_start(t0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) request(ring[u]);
+        int t = t0, b = 0;
+        for (int i = 0; i < total; i += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (i + u >= total) break;
+                if (b == 0) {
+                    acc = ci;
+                    request_start(t + RS_THREADS / 64);
+                }
+                const bf16x8 a0 = __builtin_bit_cast(bf16x8, ring[u][0]);
+                const bf16x8 a1 = __builtin_bit_cast(bf16x8, ring[u][1]);
+                request(ring[u]);
                 const uint4 *q = lds4 + b * NP * FRAG_UNITS + lane;
                 const bf16x8 x0 = __builtin_bit_cast(bf16x8, q[0]);
                 const bf16x8 x1 = __builtin_bit_cast(bf16x8, q[FRAG_UNITS]);
@@ -855,49 +976,97 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, xs, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x1, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x0, acc, 0, 0, 0);
-            }
-            float tm = fmaxf(acc[0], acc[1]);
+                if (++b < a.nb) continue;
+                float tm = fmaxf(acc[0], acc[1]);
 #pragma unroll
-            for (int r = 2; r < 16; r += 2) tm = max3f(tm, acc[r], acc[r + 1]);
-            if (__any(tm >= thr)) {
+                for (int r = 2; r < 16; r += 2) tm = max3f(tm, acc[r], acc[r + 1]);
+                if (__any(tm >= thr)) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int j = 32 * t + 8 * (r >> 2) + 4 * g + (r & 3);
-                    if (acc[r] >= thr && j < a.K) {
-                        const int at = atomicAdd(&sh_cnt[col], 1);
-                        if (at < RS_CAP) sh_j[col][at] = j;
+                    for (int r = 0; r < 16; ++r) {
+                        const int j = 32 * t + 8 * (r >> 2) + 4 * g + (r & 3);
+                        if (acc[r] >= thr && j < a.K) {
+                            const int at = atomicAdd(&sh_cnt[col], 1);
+                            if (at < RS_CAP) sh_j[col][at] = j;
+                        }
                     }
                 }
+                b = 0;
+                t += RS_THREADS / 64;
             }
         }
         __syncthreads();
-        for (int job = grp; job < np * RS_CAP; job += GROUPS) {
-            const int k = job / RS_CAP, at = job % RS_CAP;
-            if (at < sh_cnt[k] && sh_cnt[k] <= RS_CAP) {
-                const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)sh_j[k][at] * a.D, a.D, sub);
-                if (sub == 0) sh_d[k][at] = d;
+        if (tid < 64) {  // the candidates as one list of jobs
+            const int m = tid < np ? sh_cnt[tid] : 0;
+            const int mm = m <= RS_CAP ? m : 0;
+            int v = mm;
+#pragma unroll
+            for (int k = 1; k < 32; k <<= 1) {
+                const int o = __shfl_up(v, k, 64);
+                v += lane >= k ? o : 0;
             }
+            for (int i = 0; i < mm; ++i) sh_job[v - mm + i] = tid * RS_CAP + i;
+            if (tid == 31) sh_jobs = v;
+        }
+        __syncthreads();
+        for (int q = grp; q < sh_jobs; q += GROUPS) {
+            const int k = sh_job[q] / RS_CAP, at = sh_job[q] % RS_CAP;
+            const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)sh_j[k][at] * a.D, a.D, sub);
+            if (sub == 0) sh_d[k][at] = d;
         }
         __syncthreads();
         if (tid < np) {
             const int m = sh_cnt[tid];
-            if (m >= 1 && m <= RS_CAP) {
-                double d = sh_d[tid][0];
-                int j = sh_j[tid][0];
-                for (int i = 1; i < m; ++i) {
+            double d = __builtin_huge_val();
+            int j = m > RS_CAP ? -2 : -1;
+            if (m <= RS_CAP)
+                for (int i = 0; i < m; ++i) {
                     const double di = sh_d[tid][i];
                     const int ji = sh_j[tid][i];
-                    const bool better = di < d || (di == d && ji < j);
+                    const bool better = j < 0 || di < d || (di == d && ji < j);
                     d = better ? di : d;
                     j = better ? ji : j;
                 }
-                a.labels[sh_p[tid]] = j;
-                if (mindist) mindist[sh_p[tid]] = (T)d;
+            if (S > 1) {
+                ResolveSlot *slot = reinterpret_cast<ResolveSlot *>(a.rec + (int64_t)split * a.N + sh_p[tid]);
+                // written and read past the caches that other XCDs do not see: a device-wide fence
+                // here would write back a whole L2
+                __hip_atomic_store(&slot->d, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&slot->j, j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            sh_bd32[tid] = d;
+            sh_code[tid] = j;
+        }
+        if (S > 1) {
+            __builtin_amdgcn_s_waitcnt(0);  // the slots are written
+            __syncthreads();
+            if (tid == 0) sh_last = atomicAdd(&a.tickets[first / 32], 1) == S - 1;
+            __syncthreads();
+            if (!sh_last) continue;
+            if (tid < np) {
+                double d = __builtin_huge_val();
+                int j = -1;
+                for (int i = 0; i < S; ++i) {
+                    ResolveSlot *slot = reinterpret_cast<ResolveSlot *>(a.rec + (int64_t)i * a.N + sh_p[tid]);
+                    const double di = __hip_atomic_load(&slot->d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int ji = __hip_atomic_load(&slot->j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (ji == -2 || j == -2) {
+                        j = -2;
+                    } else if (ji >= 0 && (j < 0 || di < d || (di == d && ji < j))) {
+                        d = di;
+                        j = ji;
+                    }
+                }
+                sh_bd32[tid] = d;
+                sh_code[tid] = j;
             }
         }
+        if (tid < np && sh_code[tid] >= 0) {
+            a.labels[sh_p[tid]] = sh_code[tid];
+            if (mindist) mindist[sh_p[tid]] = (T)sh_bd32[tid];
+        }
+        __syncthreads();
         for (int k = 0; k < np; ++k) {
-            const int m = sh_cnt[k];
-            if (m >= 1 && m <= RS_CAP) continue;
+            if (sh_code[k] >= 0) continue;
             const T *x = X + (int64_t)sh_p[k] * a.D;
             double best = __builtin_huge_val();
             int bj = 0x7fffffff;
@@ -1013,7 +1182,7 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     return p;
 }
 
-ScanBuffers carve_scan(void *base, const ScanPlan &p)
+ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
 {
     ScanBuffers b = {};
     if (!p.ok) return b;
@@ -1031,6 +1200,9 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p)
     b.tile_max = (float *)take(tiles * 4);
     b.scale = (double *)take(8);
     b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
+    b.list_count = (int32_t *)take((size_t)SCAN_LISTS * LIST_STRIDE * 4);
+    b.list = (ScanListed *)take(((size_t)N + SCAN_LISTS * SETTLE_ROWS_MAX) * sizeof(ScanListed));
+    b.tickets = (int32_t *)take(((size_t)N / 32 + 1) * 4);
     b.bytes = off;
     return b;
 }
@@ -1059,14 +1231,17 @@ static void launch_stream(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
 
 // L lanes per row in both passes
 template <typename T, int L>
-static void launch_settle(const AssignCall &c, const ScanPlan &p, const SettleArgs &s, const ResolveArgs &r, hipStream_t st)
+static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, ResolveArgs r, hipStream_t st)
 {
-    const int rows = 256 / L * SETTLE_ROWS;
+    const int rows = 256 / L * settle_rows(sizeof(T));
+    static_assert(256 / L * settle_rows(sizeof(T)) <= SETTLE_ROWS_MAX, "list capacity");
+    r.list_cap = s.list_cap = (int)ceil_div(ceil_div(c.N, rows), s.lists) * rows;
     hipLaunchKernelGGL((scan_settle_kernel<T, L>), dim3((unsigned)ceil_div(c.N, rows)), dim3(256), 0, st, (const T *)c.X,
                        (const T *)c.C, (T *)c.mindist, s);
     if (!p.resolve) return;
     const int64_t groups = ceil_div(c.N, 32);
-    const dim3 grid((unsigned)(groups < 512 ? groups : 512)), block(RS_THREADS);
+    const int64_t side = ceil_div(1024, r.splits);  // groups side by side
+    const dim3 grid((unsigned)((groups < side ? groups : side) * r.splits)), block(RS_THREADS);
     if (p.triple)
         hipLaunchKernelGGL((scan_resolve_kernel<T, true, L>), grid, block, (size_t)3 * FRAG_UNITS * 16, st, (const T *)c.X,
                            (const T *)c.C, (T *)c.mindist, r);
@@ -1080,12 +1255,15 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
                                 hipStream_t st)
 {
     const dim3 cg((unsigned)p.tiles_pad), cb((unsigned)(p.nb < 16 ? 64 * p.nb : 1024));
+    // a contiguous list where refine_kernel takes it over
+    int32_t *const counts = p.resolve ? b.list_count : w.wl_count;
+    const int lists = p.resolve ? SCAN_LISTS : 1;
     if (p.triple)
         hipLaunchKernelGGL((scan_centroids_kernel<T, true>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start,
-                           b.tile_max, b.scale, w.wl_count);
+                           b.tile_max, b.scale, counts, lists);
     else
         hipLaunchKernelGGL((scan_centroids_kernel<T, false>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start,
-                           b.tile_max, b.scale, w.wl_count);
+                           b.tile_max, b.scale, counts, lists);
     ScanArgs a = {};
     a.X = c.X;
     a.image = b.image;
@@ -1130,10 +1308,27 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     s.K = c.K;
     s.band = (float)p.band_coef;
     s.labels = c.labels;
+    s.tickets = b.tickets;
+    s.list = p.resolve ? b.list : nullptr;
     s.wl = w.wl;
-    s.wl_count = w.wl_count;
-    const ResolveArgs r = {b.image, b.start, b.scale, b.rec,      c.N,       c.D,
-                           c.K,     p.nb,    p.tiles, c.labels, w.wl, w.wl_count, c.stats};
+    s.list_count = counts;
+    s.lists = lists;
+    ResolveArgs r;
+    r.image = b.image;
+    r.start = b.start;
+    r.scale = b.scale;
+    r.rec = b.rec;
+    r.N = c.N;
+    r.D = c.D;
+    r.K = c.K;
+    r.nb = p.nb;
+    r.tiles = p.tiles;
+    r.splits = p.splits < 16 ? p.splits : 16;
+    r.labels = c.labels;
+    r.list = b.list;
+    r.list_count = b.list_count;
+    r.tickets = b.tickets;
+    r.stats = c.stats;
     if (c.D <= 12) launch_settle<T, 2>(c, p, s, r, st);
     else if (c.D <= 24) launch_settle<T, 4>(c, p, s, r, st);
     else if (c.D <= 128) launch_settle<T, 8>(c, p, s, r, st);
