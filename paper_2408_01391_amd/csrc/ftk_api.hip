@@ -10,6 +10,7 @@
 
 #include "ftk_internal.h"
 #include "ftk_scan.h"
+#include "ftk_small.h"
 
 namespace ftk {
 
@@ -134,12 +135,18 @@ size_t hcn_entries_max(ftk_dtype dtype, int64_t N, int D, int K)
     return (size_t)ceil_div((int64_t)need, 512) * 512 + 512;
 }
 
-// The scan (ftk_scan.hip) takes the assignments that carry neither checksums nor listed faults; a
-// forced kernel choice goes to the kernel it names.
+// Assignments that carry neither checksums nor listed faults: the one-launch kernel (ftk_small.hip) takes
+// the small ones, the scan (ftk_scan.hip) the large ones with enough centroids.  A forced kernel choice
+// goes to the kernel it names.
 static ScanPlan route_scan(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
 {
     if (ft != FTK_FT_OFF || n_faults > 0 || g_tuning.assign_variant != -1) return ScanPlan{};
     return plan_scan(dtype, N, D, K);
+}
+
+static bool route_small(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
+{
+    return ft == FTK_FT_OFF && n_faults == 0 && g_tuning.assign_variant == -1 && small_assign_pays(dtype, N, D, K);
 }
 
 // The workspace is carved for the larger of the two kernel variants so that its size does not
@@ -188,6 +195,7 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
         w.idx = nullptr;
         w.csplit = nullptr;
         w.batch_counters = nullptr;
+        w.small_fit = nullptr;
         w.total = off;
         return w;
     }
@@ -214,6 +222,7 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
     w.idx = (int64_t *)take((size_t)K * sizeof(int64_t));
     w.csplit = take(fast_split_bytes(dtype, D, K));
     w.batch_counters = (int32_t *)take((size_t)4 * MAX_BATCHES * sizeof(int32_t));
+    w.small_fit = take(small_fit_bytes(D, K));
     w.total = off;
     return w;
 }
@@ -289,9 +298,10 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
                               bool own_scratch = false, bool allow_scan = true)
 {
     const bool aligned16 = ((uintptr_t)c.X % 16 == 0) && ((uintptr_t)c.C % 16 == 0);
-    const ScanPlan scan = fast || !allow_scan ? ScanPlan{} : route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
+    const bool small = !fast && route_small(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
+    const ScanPlan scan = fast || small || !allow_scan ? ScanPlan{} : route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     AssignPlan p;
-    if (scan.ok) {
+    if (small || scan.ok) {
         memset(&p, 0, sizeof(p));
     } else if (fast) {
         memset(&p, 0, sizeof(p));
@@ -302,7 +312,7 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
     // own_scratch: the assignment's buffers are all there is.  Without the scan's they are a prefix of
     // the full layout.
     const Workspace w = carve_workspace(workspace, c.dtype, c.N, c.D, c.K, c.ft, own_scratch || !(fast || scan.ok), scan.ok);
-    if (!scan.ok) FTK_TRY(launch_centroid_prologue(c, p, w, st));
+    if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(c, p, w, st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     // at most 65536 pending pairs: a caller that enables profiling and never reads stops recording
     const bool profile = g_profile && !own_scratch && g_profile_events.size() < 65536;
@@ -314,7 +324,9 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
         }
         FTK_TRY_HIP(hipEventRecord(e0, st));
     }
-    if (scan.ok)
+    if (small)
+        FTK_TRY(launch_small_assign(c, st));
+    else if (scan.ok)
         FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N), w, st));
     else if (fast)
         FTK_TRY(launch_assign_fast(c, p, w, st));
@@ -324,7 +336,7 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
         g_profile_events.emplace_back(e0, e1);  // owned by the list from here on
         FTK_TRY_HIP(hipEventRecord(e1, st));
     }
-    if (scan.ok) return FTK_OK;  // no list is left
+    if (small || scan.ok) return FTK_OK;  // no list is left
     const int n_wg = (!fast && c.stats && p.variant == VAR_GENERIC) ? (int)p.workgroups : 0;
     FTK_TRY(launch_refine(c, w, n_wg, st));
     return FTK_OK;
@@ -683,18 +695,22 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
     AssignCall whole{dtype, X, C, batch_rows < N ? batch_rows : N, D, K, labels, mindist, FTK_FT_OFF, nullptr, 0, nullptr};
     AssignPlan pprev = plan_assign(dtype, whole.N, D, K, FTK_FT_OFF, aligned16);
     // the path is chosen for the whole problem, as in the two-call step
-    const ScanPlan scan = route_scan(dtype, N, D, K, FTK_FT_OFF, 0);
-    if (!scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
+    const bool small = route_small(dtype, N, D, K, FTK_FT_OFF, 0);
+    const ScanPlan scan = small ? ScanPlan{} : route_scan(dtype, N, D, K, FTK_FT_OFF, 0);
+    if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
     for (int64_t b = 0; b < nbatch; ++b) {
         const int64_t r0 = b * batch_rows;
         const int64_t nb = N - r0 < batch_rows ? N - r0 : batch_rows;
         const char *Xb = (const char *)X + (size_t)r0 * D * esz;
         AssignCall c{dtype, Xb, C, nb, D, K, labels + r0, mindist ? (void *)((char *)mindist + (size_t)r0 * esz) : nullptr,
                      FTK_FT_OFF, nullptr, 0, nullptr};
-        if (scan.ok) {
+        if (small || scan.ok) {
             Workspace wb = w;
             wb.wl_count = w.batch_counters + 4 * b;
-            FTK_TRY(launch_scan_assign(c, cut_scan(dtype, nb, D, K), carve_scan(w.scan, scan, N), wb, st));
+            if (small)
+                FTK_TRY(launch_small_assign(c, st));
+            else
+                FTK_TRY(launch_scan_assign(c, cut_scan(dtype, nb, D, K), carve_scan(w.scan, scan, N), wb, st));
             FTK_TRY(launch_update_batch(dtype, Xb, labels + r0, nb, D, K, x_absmax, w, ub, b == 0, st));
             continue;
         }
@@ -792,7 +808,12 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
         FTK_TRY(launch_gather_rows(dtype, X, D, w.idx, K, w.C_cur, st));
     }
     FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, w.absmax, st));
-    for (int t = 0; t < iters; ++t) {
+    const bool small = !fast && iters > 0 && ft == FTK_FT_OFF && g_tuning.assign_variant == -1 &&
+                       g_tuning.update_path == -1 && small_fit_pays(dtype, N, D, K);
+    if (small)
+        FTK_TRY(launch_small_fit(dtype, X, N, D, K, iters, w.C_cur, C_out, labels_out, counts_out, w.absmax, w.inertia,
+                                 w.partials, w.small_fit, st));
+    for (int t = 0; !small && t < iters; ++t) {
         AssignCall c{dtype, X, w.C_cur, N, D, K, labels_out, w.mindist, ft, nullptr, 0, stats};
         FTK_TRY(assign_impl(c, workspace, st, fast));
         if (inertia_per_iter)
@@ -800,7 +821,7 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
         FTK_TRY(launch_update(dtype, X, labels_out, N, D, K, w.C_cur, counts_out, w.absmax, w, ft, nullptr, 0,
                               stats, st));
     }
-    FTK_TRY_HIP(hipMemcpyAsync(C_out, w.C_cur, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
+    if (!small) FTK_TRY_HIP(hipMemcpyAsync(C_out, w.C_cur, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
     if (inertia_per_iter && iters > 0) {
         FTK_TRY_HIP(hipMemcpyAsync(inertia_per_iter, w.inertia, (size_t)iters * sizeof(double),
                                    hipMemcpyDeviceToHost, st));

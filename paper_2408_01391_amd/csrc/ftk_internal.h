@@ -99,6 +99,7 @@ struct Workspace {
     // fast (split-bf16) assignment
     void *csplit;       // centroid pieces in LDS image order (fp32 data with D <= 128, else empty)
     int32_t *batch_counters;  // [4 * MAX_BATCHES] work-list counters per batch of the batched step
+    void *small_fit;    // tables of the one-launch Lloyd iteration (ftk_small.h)
     size_t total;
 };
 constexpr int FIT_MAX_ITERS_IN_WS = 4096;

@@ -1117,6 +1117,7 @@ static int resident_blocks(int D)
 //   fp32   K = 32    loses everywhere (0.55 .. 0.85)
 //          K = 100   D = 128: N = 1 000 34 / 28 us, 2 * 10^4 35 / 34, 10^6 333 / 260; D = 16: 2 * 10^4 14 / 19,
 //                    10^6 83 / 57; D = 8: 10^6 45 / 47
+//                    N = 10^5: D = 16 19 / 22, D = 64 35 / 39; K = 200, D = 24 29 / 33
 //          K = 256   D = 16: N = 2 * 10^4 25 / 22, 10^6 111 / 69; D = 8: 16 / 19, 10^6 63 / 59
 //          K = 1024  D = 4: N = 2 * 10^4 33 / 24, 2 * 10^5 51 / 46; D = 64: 10^6 1104 / 382
 //   fp64   K = 100   D = 64: N = 2 * 10^5 79 / 65, 2 * 10^4 23 / 32; D = 256: 2 * 10^5 251 / 276
@@ -1128,9 +1129,9 @@ static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
     if (K >= 768) return true;
     if (dtype == FTK_F32) {
         if (D < 16) return K >= 512;
-        return K >= 192 || D >= 128 || N >= 100000;
+        return K >= 256 || N >= 200000 || (K >= 192 && D >= 32) || D >= 128;
     }
-    return N >= 100000 && (K >= 192 || D <= 96);
+    return K >= 192 ? N >= 100000 : (N >= 200000 && D <= 96);
 }
 
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K)

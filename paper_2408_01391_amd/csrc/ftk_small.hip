@@ -1,0 +1,383 @@
+// Small problems, unprotected: one launch per assignment, one per Lloyd iteration.
+//
+// Below some ten million multiplications an assignment is not bound by any unit but by its launches
+// (norms, matrix kernel, settlement: 17 us for 20 000 x 24 points and 100 centroids, of which the matrix
+// kernel computes for two), and an iteration by its seven (33 us at 4096 x 16, K = 8).  Here the
+// centroids sit in LDS, a point in the registers of the P lanes that share its centroids, and distances
+// are taken in direct-difference form in double (fp64 runs at the fp32 rate on the vector units here):
+// nothing has to be prepared, certified or settled afterwards.
+#include "ftk_internal.h"
+#include "ftk_mma.h"
+#include "ftk_small.h"
+
+namespace ftk {
+
+constexpr int SM_THREADS = 256;
+constexpr int SM_CELLS = 8192;        // most elements of C (LDS)
+constexpr int SM_FIT_CELLS = 4096;    // the same where a table of sums lies beside them
+constexpr int SM_GRID = 512;
+constexpr int SM_LIMB_BITS = 24;
+
+typedef float float4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef double double2e __attribute__((ext_vector_type(2), aligned(8)));
+
+// the update's fixed point (see ftk_update.hip): the same scale and rounding, so the same sums
+__device__ __forceinline__ double small_scale(double absmax, int64_t rows)
+{
+    int L = 11;
+    while (((int64_t)1 << L) < rows) ++L;
+    if (!(absmax > 0.0) || !(absmax < __builtin_huge_val())) return 1.0;
+    return ldexp(1.0, 62 - L - (ilogb(absmax) + 1));
+}
+__device__ __forceinline__ long long small_fixed(double x, double scale)
+{
+    constexpr double MAGIC = 6755399441055744.0;  // 1.5 * 2^52
+    return __double_as_longlong(fma(x, scale, MAGIC)) - __double_as_longlong(MAGIC);
+}
+
+struct SmallArgs {
+    const void *X;
+    const void *C;       // centroids of this assignment, or (FIT, prev given) those before it
+    int64_t N;
+    int D, K, p_log2;
+    int32_t *labels;     // may be NULL
+    void *mindist;       // may be NULL
+    // FIT
+    const unsigned long long *prev;  // sums the centroids are formed from: [K*D] low, [K*D] high, then counts; or NULL
+    unsigned long long *cur, *next;  // this iteration's, and the one to clear for the next
+    void *C_out;         // where workgroup 0 leaves the centroids formed from prev
+    const double *absmax;
+    int64_t scale_rows;
+    const double *partials_prev;     // objective of the previous iteration, by workgroup
+    double *partials, *inertia_prev;
+};
+
+template <typename T>
+__device__ __forceinline__ T small_mean(const unsigned long long *sums, int cells, int i, int n, double inv)
+{
+    const double total = (double)(long long)sums[cells + i] * (double)(1ll << SM_LIMB_BITS) + (double)(long long)sums[i];
+    return (T)((total * inv) / (double)n);
+}
+
+// NQ quads of features, PT points per thread; whole = rows are whole quads
+template <typename T, int NQ, int PT, bool FIT>
+__global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
+{
+    constexpr int E = 16 / sizeof(T);              // elements per LDS read
+    constexpr int SU = (4 * NQ / E) | 1;           // 16-byte units per row: odd, so that rows spread over the banks
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    T *ldsC = reinterpret_cast<T *>(lds_raw);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int D = a.D, K = a.K, cells = K * D;
+    unsigned long long *tab = reinterpret_cast<unsigned long long *>(lds_raw + (size_t)K * SU * 16);
+    int *cnt = reinterpret_cast<int *>(tab + (FIT ? cells : 0));
+    const int P = 1 << a.p_log2, sub = tid & (P - 1);
+    const T *X = reinterpret_cast<const T *>(a.X), *C = reinterpret_cast<const T *>(a.C);
+    T *C_out = reinterpret_cast<T *>(a.C_out);
+
+    double scale = 1.0;
+    if constexpr (FIT) scale = small_scale(*a.absmax, a.scale_rows);
+    const double inv = 1.0 / scale;
+    const int *prev_cnt = reinterpret_cast<const int *>(a.prev + 2 * (size_t)cells);
+    for (int i = tid; i < K * 4 * NQ; i += SM_THREADS) {
+        const int k = i / (4 * NQ), d = i - k * 4 * NQ;
+        T v = T(0);
+        if (d < D) {
+            v = C[k * D + d];
+            if (FIT && a.prev) {
+                const int n = prev_cnt[k];
+                if (n > 0) v = small_mean<T>(a.prev, cells, k * D + d, n, inv);  // an empty cluster keeps its centroid
+                if (blockIdx.x == 0) C_out[k * D + d] = v;
+            }
+        }
+        ldsC[k * (SU * E) + d] = v;
+    }
+    if constexpr (FIT) {
+        for (int i = tid; i < cells; i += SM_THREADS) tab[i] = 0ull;
+        for (int i = tid; i < K; i += SM_THREADS) cnt[i] = 0;
+        int *next = reinterpret_cast<int *>(a.next);
+        for (int64_t i = (int64_t)blockIdx.x * SM_THREADS + tid; i < 4 * (int64_t)cells + K; i += (int64_t)gridDim.x * SM_THREADS)
+            next[i] = 0;
+        if (a.partials_prev && blockIdx.x == 0 && tid < 64) {  // every iteration has the same grid
+            double s = 0.0;
+            for (int i = lane; i < (int)gridDim.x; i += 64) s += a.partials_prev[i];
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
+            if (lane == 0) *a.inertia_prev = s;
+        }
+    }
+    __syncthreads();
+
+    const int per_wg = (SM_THREADS >> a.p_log2) * PT;  // points per workgroup and round
+    double inertia = 0.0;
+    for (int64_t p0 = (int64_t)blockIdx.x * per_wg; p0 < a.N; p0 += (int64_t)gridDim.x * per_wg) {
+        double x[PT][4 * NQ];
+        double best[PT];
+        int bj[PT];
+        bool live[PT];
+        int64_t p[PT];
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            p[t] = p0 + (int64_t)t * (SM_THREADS >> a.p_log2) + (tid >> a.p_log2);
+            live[t] = p[t] < a.N;
+            const T *row = X + (live[t] ? p[t] : a.N - 1) * D;
+            if (D % 4 == 0) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int off = min(4 * q, D - 4);
+                    if constexpr (sizeof(T) == 4) {
+                        const float4e f = *reinterpret_cast<const float4e *>(row + off);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[t][4 * q + e] = 4 * q < D ? (double)f[e] : 0.0;
+                    } else {
+                        const double2e f = *reinterpret_cast<const double2e *>(row + off);
+                        const double2e h = *reinterpret_cast<const double2e *>(row + off + 2);
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            x[t][4 * q + e] = 4 * q < D ? f[e] : 0.0;
+                            x[t][4 * q + 2 + e] = 4 * q < D ? h[e] : 0.0;
+                        }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int d = 0; d < 4 * NQ; ++d) {
+                    const double v = (double)row[min(d, D - 1)];
+                    x[t][d] = d < D ? v : 0.0;
+                }
+            }
+            best[t] = __builtin_huge_val();
+            bj[t] = 0x7fffffff;
+        }
+        for (int j = sub; j < K; j += P) {
+            const T *c = ldsC + j * (SU * E);
+            double d[PT];
+#pragma unroll
+            for (int t = 0; t < PT; ++t) d[t] = 0.0;
+#pragma unroll
+            for (int q = 0; q < 4 * NQ / E; ++q) {
+                const typename Mma<T>::frag_t f = *reinterpret_cast<const typename Mma<T>::frag_t *>(c + q * E);
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const double ce = (double)f[e];
+#pragma unroll
+                    for (int t = 0; t < PT; ++t) {
+                        const double diff = x[t][q * E + e] - ce;
+                        d[t] = fma(diff, diff, d[t]);  // in feature order: equal centroids tie exactly
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < PT; ++t) {
+                const bool better = d[t] < best[t];
+                best[t] = better ? d[t] : best[t];
+                bj[t] = better ? j : bj[t];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            for (int m = 1; m < P; m <<= 1) {
+                const double od = __shfl_xor(best[t], m, 64);
+                const int oj = __shfl_xor(bj[t], m, 64);
+                const bool take = od < best[t] || (od == best[t] && oj < bj[t]);
+                best[t] = take ? od : best[t];
+                bj[t] = take ? oj : bj[t];
+            }
+            const int lab = bj[t] == 0x7fffffff ? 0 : bj[t];  // no distance was a number
+            if (live[t] && sub == 0) {
+                if (a.labels) a.labels[p[t]] = lab;
+                if (a.mindist) reinterpret_cast<T *>(a.mindist)[p[t]] = (T)best[t];
+                if (FIT) {
+                    inertia += (double)(T)best[t];
+                    atomicAdd(&cnt[lab], 1);
+                }
+            }
+            if constexpr (FIT) {
+                if (live[t]) {
+#pragma unroll
+                    for (int d = 0; d < 4 * NQ; ++d)
+                        if ((d & (P - 1)) == sub && d < D)
+                            atomicAdd(&tab[lab * D + d], (unsigned long long)small_fixed(x[t][d], scale));
+                }
+            }
+        }
+    }
+    if constexpr (FIT) {
+        __shared__ double sh_in[SM_THREADS / 64];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) inertia += __shfl_xor(inertia, m, 64);
+        if (lane == 0) sh_in[tid >> 6] = inertia;
+        __syncthreads();
+        if (tid == 0) a.partials[blockIdx.x] = (sh_in[0] + sh_in[1]) + (sh_in[2] + sh_in[3]);
+        // integer sums: the order of these additions does not matter.  fp32: one limb scaled for all of N;
+        // fp64: scaled for this workgroup's rows, so the total needs two
+        for (int i = tid; i < cells; i += SM_THREADS) {
+            const long long v = (long long)tab[i];
+            if (v == 0) continue;
+            if (sizeof(T) == 4) {
+                atomicAdd(a.cur + i, (unsigned long long)v);
+            } else {
+                atomicAdd(a.cur + i, (unsigned long long)(v & ((1ll << SM_LIMB_BITS) - 1)));
+                atomicAdd(a.cur + cells + i, (unsigned long long)(v >> SM_LIMB_BITS));
+            }
+        }
+        int *cur_cnt = reinterpret_cast<int *>(a.cur + 2 * (size_t)cells);
+        for (int i = tid; i < K; i += SM_THREADS)
+            if (cnt[i]) atomicAdd(cur_cnt + i, cnt[i]);
+    }
+}
+
+// centroids, counts and objective of the last iteration
+template <typename T>
+__global__ __launch_bounds__(256) void small_finish_kernel(const unsigned long long *sums, const T *C_prev, T *C_out,
+                                                           int32_t *counts, int D, int K, const double *absmax,
+                                                           int64_t scale_rows, const double *partials, int n_partials,
+                                                           double *inertia)
+{
+    const int cells = K * D, i = blockIdx.x * 256 + threadIdx.x;
+    const int *cnt = reinterpret_cast<const int *>(sums + 2 * (size_t)cells);
+    if (i < cells) {
+        const int n = cnt[i / D];
+        C_out[i] = n > 0 ? small_mean<T>(sums, cells, i, n, 1.0 / small_scale(*absmax, scale_rows)) : C_prev[i];
+    }
+    if (i < K) counts[i] = cnt[i];
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        double s = 0.0;
+        for (int k = threadIdx.x; k < n_partials; k += 64) s += partials[k];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
+        if (threadIdx.x == 0) *inertia = s;
+    }
+}
+
+// ---- host ----------------------------------------------------------------------------------------
+static int small_quads(int D) { return D <= 8 ? 2 : (D <= 16 ? 4 : (D <= 24 ? 6 : (D <= 32 ? 8 : (D <= 48 ? 12 : 16)))); }
+static int small_points(int nq) { return nq <= 8 ? 2 : 1; }
+
+// Where one launch wins: up to about 5 * 10^7 multiplications (whole calls, before / here: fp32 20000 x 24,
+// K = 100 15.6 / 13.9 us; 10^5 x 8, K = 64 14.5 / 10.9; 10^5 x 4, K = 100 15.4 / 15.1; 1000 x 16, K = 32 10.6 / 4.7;
+// fp64 20000 x 32, K = 64 13.4 / 12.9; 10^6 x 8, K = 2 43 / 13).  Rows of more than 32 doubles take one point per
+// thread, and more centroids or points than a few outweigh the launches: 20000 x 64, K = 8 12.4 / 8.1, K = 32
+// 12.7 / 15.8; 10^5 x 45, K = 8 20 / 31.
+static bool small_work(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    const double work = (double)N * K * D;
+    if (dtype == FTK_F64 && D > 32) return work <= 2e7 && N <= 32768;
+    return work <= 5e7;
+}
+
+bool small_assign_pays(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    return D <= 64 && (int64_t)K * small_quads(D) * 4 <= SM_CELLS && small_work(dtype, N, D, K);
+}
+
+bool small_fit_pays(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    return D <= 64 && (int64_t)K * small_quads(D) * 4 <= SM_FIT_CELLS && small_work(dtype, N, D, K);
+}
+
+size_t small_fit_bytes(int D, int K)
+{
+    if (D > 64 || (int64_t)K * small_quads(D) * 4 > SM_FIT_CELLS) return 0;
+    return 3 * align_up(((size_t)2 * K * D) * 8 + (size_t)K * 4, 256) + align_up((size_t)K * D * 8, 256);
+}
+
+// lanes per point: as many as give every compute unit a workgroup, at most one centroid each
+static int small_lanes_log2(int64_t N, int K, int pt, int *grid)
+{
+    int l = 0;
+    while (l < 5 && (2 << l) <= K && ((N << l) / pt) < (int64_t)256 * SM_THREADS) ++l;
+    const int64_t wgs = ceil_div(N, (int64_t)(SM_THREADS >> l) * pt);
+    *grid = (int)(wgs < SM_GRID ? wgs : SM_GRID);
+    return l;
+}
+
+template <typename T, bool FIT>
+static void launch_small_t(const SmallArgs &a, int grid, hipStream_t st)
+{
+    const int nq = small_quads(a.D);
+    const size_t row = (size_t)((4 * nq * sizeof(T) / 16) | 1) * 16;
+    const size_t lds = (size_t)a.K * row + (FIT ? (size_t)a.K * a.D * 8 + (size_t)a.K * 4 : 0);
+    const dim3 g((unsigned)grid), b(SM_THREADS);
+    switch (nq) {
+    case 2: hipLaunchKernelGGL((small_kernel<T, 2, 2, FIT>), g, b, lds, st, a); break;
+    case 4: hipLaunchKernelGGL((small_kernel<T, 4, 2, FIT>), g, b, lds, st, a); break;
+    case 6: hipLaunchKernelGGL((small_kernel<T, 6, 2, FIT>), g, b, lds, st, a); break;
+    case 8: hipLaunchKernelGGL((small_kernel<T, 8, 2, FIT>), g, b, lds, st, a); break;
+    case 12: hipLaunchKernelGGL((small_kernel<T, 12, 1, FIT>), g, b, lds, st, a); break;
+    default: hipLaunchKernelGGL((small_kernel<T, 16, 1, FIT>), g, b, lds, st, a); break;
+    }
+}
+
+ftk_status launch_small_assign(const AssignCall &c, hipStream_t st)
+{
+    SmallArgs a = {};
+    a.X = c.X;
+    a.C = c.C;
+    a.N = c.N;
+    a.D = c.D;
+    a.K = c.K;
+    a.labels = c.labels;
+    a.mindist = c.mindist;
+    int grid;
+    a.p_log2 = small_lanes_log2(c.N, c.K, small_points(small_quads(c.D)), &grid);
+    if (c.dtype == FTK_F32) launch_small_t<float, false>(a, grid, st);
+    else launch_small_t<double, false>(a, grid, st);
+    FTK_TRY_HIP(hipGetLastError());
+    return FTK_OK;
+}
+
+// Iteration t adds into table t % 3 and clears the next one; the centroids of iteration t + 1 are formed
+// from it by every workgroup for itself, in the launch that uses them.
+ftk_status launch_small_fit(ftk_dtype dtype, const void *X, int64_t N, int D, int K, int iters, void *C_cur, void *C_out,
+                            int32_t *labels, int32_t *counts, const double *absmax, double *inertia, double *partials,
+                            void *scratch, hipStream_t st)
+{
+    const size_t cells = (size_t)K * D, esz = dtype == FTK_F32 ? 4 : 8;
+    const size_t table = align_up(2 * cells * 8 + (size_t)K * 4, 256);
+    char *base = (char *)scratch;
+    auto tab = [&](int t) { return reinterpret_cast<unsigned long long *>(base + (size_t)(t % 3) * table); };
+    void *C_alt = base + 3 * table;
+    (void)esz;
+    SmallArgs a = {};
+    a.X = X;
+    a.N = N;
+    a.D = D;
+    a.K = K;
+    const int pt = small_points(small_quads(D));
+    int grid;
+    a.p_log2 = small_lanes_log2(N, K, pt, &grid);
+    const int64_t per_wg = (int64_t)(SM_THREADS >> a.p_log2) * pt;
+    a.scale_rows = dtype == FTK_F32 ? N : ceil_div(ceil_div(N, per_wg), grid) * per_wg;
+    a.absmax = absmax;
+    FTK_TRY(launch_zero_ints(reinterpret_cast<int32_t *>(tab(0)), (int)(4 * cells + K), st));
+    void *C_buf[2] = {C_cur, C_alt};
+    for (int t = 0; t < iters; ++t) {
+        // centroids before the update of iteration t - 1 are in C_buf[(t - 1) & 1]; those after go to the other
+        a.C = t == 0 ? C_buf[0] : C_buf[(t - 1) & 1];
+        a.C_out = C_buf[t & 1];
+        a.prev = t == 0 ? nullptr : tab(t - 1);
+        a.cur = tab(t);
+        a.next = tab(t + 1);
+        a.labels = t == iters - 1 ? labels : nullptr;  // those of the last assignment are what is asked for
+        a.partials = partials + (t & 1) * SM_GRID;
+        a.partials_prev = t == 0 ? nullptr : partials + ((t - 1) & 1) * SM_GRID;
+        a.inertia_prev = t == 0 ? nullptr : inertia + t - 1;
+        if (dtype == FTK_F32) launch_small_t<float, true>(a, grid, st);
+        else launch_small_t<double, true>(a, grid, st);
+    }
+    const dim3 g((unsigned)ceil_div((int64_t)cells > K ? (int64_t)cells : K, 256));
+    const int last = iters - 1;
+    if (dtype == FTK_F32)
+        hipLaunchKernelGGL((small_finish_kernel<float>), g, dim3(256), 0, st, tab(last), (const float *)C_buf[last & 1],
+                           (float *)C_out, counts, D, K, absmax, a.scale_rows, partials + (last & 1) * SM_GRID, grid,
+                           inertia + last);
+    else
+        hipLaunchKernelGGL((small_finish_kernel<double>), g, dim3(256), 0, st, tab(last), (const double *)C_buf[last & 1],
+                           (double *)C_out, counts, D, K, absmax, a.scale_rows, partials + (last & 1) * SM_GRID, grid,
+                           inertia + last);
+    FTK_TRY_HIP(hipGetLastError());
+    return FTK_OK;
+}
+
+}  // namespace ftk
