@@ -199,13 +199,19 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
         w.total = off;
         return w;
     }
-    {   // shared by the two update paths: per-workgroup tables, or two tagged slots per walker
+    {   // shared by the update paths: per-workgroup tables, or two tagged slots per walker
+        int64_t bucket_counts = 0;
+        const size_t bucket_cells = (size_t)update_bucket_cells(dtype, N, D, K, &bucket_counts);
         const size_t slab_cells = (size_t)update_slab_cells_max(N, D, K);
         const size_t slot_cells = (size_t)update_walkers_max(N) * 2 * (size_t)D;
-        w.upd_slab = (int64_t *)take((slab_cells > slot_cells ? slab_cells : slot_cells) * sizeof(int64_t));
+        size_t most = slab_cells > slot_cells ? slab_cells : slot_cells;
+        if (bucket_cells > most) most = bucket_cells;
+        w.upd_slab = (int64_t *)take(most * sizeof(int64_t));
         const size_t slab_counts = (size_t)update_slab_chunks_max(N) * K;
         const size_t slot_tags = (size_t)update_walkers_max(N) * 2;
-        w.upd_cslab = (int32_t *)take((slab_counts > slot_tags ? slab_counts : slot_tags) * sizeof(int32_t));
+        most = slab_counts > slot_tags ? slab_counts : slot_tags;
+        if ((size_t)bucket_counts > most) most = (size_t)bucket_counts;
+        w.upd_cslab = (int32_t *)take(most * sizeof(int32_t));
     }
     const size_t shared = off;
     if (p) w.scan = (void *)(p + off);

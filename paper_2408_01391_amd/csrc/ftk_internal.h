@@ -112,6 +112,7 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
 int64_t update_slab_chunks_max(int64_t N);
 int64_t update_slab_cells_max(int64_t N, int D, int K);
 int64_t update_walkers_max(int64_t N);
+int64_t update_bucket_cells(ftk_dtype dtype, int64_t N, int D, int K, int64_t *counts);
 
 // ---- launches (each returns after enqueueing on `st`) ------------------------------------
 struct AssignCall {

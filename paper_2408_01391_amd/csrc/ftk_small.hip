@@ -16,6 +16,8 @@ constexpr int SM_THREADS = 256;
 constexpr int SM_CELLS = 8192;        // most elements of C (LDS)
 constexpr int SM_FIT_CELLS = 4096;    // the same where a table of sums lies beside them
 constexpr int SM_GRID = 512;
+constexpr int SM_FILL = 256;          // workgroups to aim at: more lanes per point than that fills cost time (20000 x 24,
+                                      // K = 100: 13.4 us; aiming at 1024: 15.4)
 constexpr int SM_LIMB_BITS = 24;
 
 typedef float float4e __attribute__((ext_vector_type(4), aligned(4)));
@@ -286,7 +288,7 @@ size_t small_fit_bytes(int D, int K)
 static int small_lanes_log2(int64_t N, int K, int pt, int *grid)
 {
     int l = 0;
-    while (l < 5 && (2 << l) <= K && ((N << l) / pt) < (int64_t)256 * SM_THREADS) ++l;
+    while (l < 5 && (2 << l) <= K && ((N << l) / pt) < (int64_t)SM_FILL * SM_THREADS) ++l;
     const int64_t wgs = ceil_div(N, (int64_t)(SM_THREADS >> l) * pt);
     *grid = (int)(wgs < SM_GRID ? wgs : SM_GRID);
     return l;

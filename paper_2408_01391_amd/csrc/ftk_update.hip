@@ -893,6 +893,302 @@ __global__ __launch_bounds__(SF_CELLS * SF_GROUPS) void sorted_finalize_kernel(
     }
 }
 
+// ======================= bucketed tables (fp32, unprotected) ==================================
+// The label sort above costs 105 of 180 us at 2^21 x 32, K = 4096: a scattered 4-byte write per point
+// and array, three passes over the labels, a scan.  A full sort is more than the reduction needs: here
+// points are only split into buckets of Kb consecutive clusters whose table fits 32 KB of LDS; the points,
+// bucket after bucket, are shared out evenly among the workgroups - whatever the distribution of the
+// labels - and added up in LDS tables as on the first path, which reads each row of X exactly once
+// whatever K.
+//
+// bucket_split_kernel: a workgroup orders its BK_POINTS points by bucket in LDS and writes them, one
+// word each (cluster within the bucket, point within the source), with the bucket boundaries.
+constexpr int BK_POINTS = 8192;    // points per source workgroup (13 bits of an entry)
+constexpr int BK_THREADS = 1024;
+constexpr int BK_CELLS = 4096;     // cells of a bucket's table: two workgroups per compute unit
+constexpr int BK_MAX = 1024;       // buckets
+constexpr int BK_SOURCES = 4096;   // source workgroups
+constexpr int BK_WGS = 512;        // workgroups that add up: two per compute unit
+
+struct BucketPlan {
+    bool ok;
+    int Kb, buckets, sources, wgs, tx_log2;
+};
+
+__global__ __launch_bounds__(BK_THREADS) void bucket_split_kernel(const int32_t *labels, int64_t N, int K, int Kb,
+                                                                  int buckets, uint32_t *entries, int32_t *bounds,
+                                                                  int32_t *totals)
+{
+    constexpr int PER = BK_POINTS / BK_THREADS;
+    __shared__ int cnt[BK_MAX];
+    __shared__ int wsum[BK_THREADS / 64];
+    __shared__ uint32_t out[BK_POINTS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t base = (int64_t)blockIdx.x * BK_POINTS;
+    int lab[PER], rank[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int64_t p = base + i * BK_THREADS + tid;
+        lab[i] = p < N ? labels[p] : -1;
+    }
+    cnt[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        rank[i] = -1;
+        if ((unsigned)lab[i] < (unsigned)K) rank[i] = atomicAdd(&cnt[lab[i] / Kb], 1);
+    }
+    __syncthreads();
+    // exclusive prefix over the buckets, one per thread
+    const int c = cnt[tid];
+    int v = c;
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+        const int o = __shfl_up(v, k, 64);
+        v += lane >= k ? o : 0;
+    }
+    if (lane == 63) wsum[wave] = v;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < wave; ++w) before += wsum[w];
+    const int start = before + v - c;
+    cnt[tid] = start;
+    int32_t *bound = bounds + (int64_t)blockIdx.x * (buckets + 1);
+    if (tid <= buckets) bound[tid] = start;  // buckets < BK_MAX
+    if (c) atomicAdd(totals + tid, c);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        if (rank[i] >= 0) {
+            const int b = lab[i] / Kb;
+            out[cnt[b] + rank[i]] = (uint32_t)(lab[i] - b * Kb) << 13 | (uint32_t)(i * BK_THREADS + tid);
+        }
+    __syncthreads();
+    for (int i = tid; i < BK_POINTS && base + i < N; i += BK_THREADS) entries[base + i] = out[i];
+}
+
+// inclusive prefix of one value per thread (1024 threads); `wsum` is scratch
+__device__ __forceinline__ int block_prefix(int v, int *wsum)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+        const int o = __shfl_up(v, k, 64);
+        v += lane >= k ? o : 0;
+    }
+    __syncthreads();
+    if (lane == 63) wsum[wave] = v;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) v += wsum[w];
+    return v;
+}
+
+// Every bucket gets workgroups for its share of the points, at most `share` each: first workgroup and
+// number of them for the bucket workgroup `wg` belongs to.  All 1024 threads take part.
+struct BucketShare {
+    int bucket, index, wgs, points;  // index among the bucket's workgroups
+};
+__device__ __forceinline__ int bucket_wgs(int points, int share) { return (points + share - 1) / share; }
+__device__ __forceinline__ BucketShare bucket_share(const int32_t *totals, const BucketPlan &b, int wg, int *first_wg, int *wsum)
+{
+    const int tid = threadIdx.x;
+    const int own = tid < b.buckets ? totals[tid] : 0;
+    block_prefix(own, wsum);
+    int total = 0;
+    for (int w = 0; w < BK_THREADS / 64; ++w) total += wsum[w];
+    __syncthreads();
+    const int share = max(1, (total + b.wgs - 1) / b.wgs);
+    const int m = bucket_wgs(own, share);
+    const int upto = block_prefix(m, wsum);
+    first_wg[tid] = upto - m;
+    __shared__ BucketShare sh;
+    if (tid == 0) sh.bucket = -1;
+    __syncthreads();
+    if (wg >= upto - m && wg < upto) sh = BucketShare{tid, wg - (upto - m), m, own};
+    __syncthreads();
+    return sh;
+}
+
+// One workgroup's part of a bucket: table in LDS, then slot `blockIdx.x` of the slabs.  TX lanes share a
+// row; UNR rows per thread in flight, the entries of the next ones on their way.
+__global__ __launch_bounds__(BK_THREADS) void bucket_accumulate_kernel(
+    const float *X, const uint32_t *entries, const int32_t *bounds, const int32_t *totals, int64_t N, int D, int K,
+    BucketPlan b, const double *absmax_p, long long *slabs, int32_t *cslabs)
+{
+    constexpr int E = 4;
+    constexpr int UNR = 4;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    unsigned long long *cell = reinterpret_cast<unsigned long long *>(lds_raw);
+    const int Dp = D + 1;  // see update_accumulate_kernel
+    int *cnt = reinterpret_cast<int *>(cell + (size_t)b.Kb * Dp);
+    int *pre = cnt + b.Kb;               // [sources + 1] points of the bucket before each source
+    int *from = pre + b.sources + 1;     // [sources]     where a source's points of the bucket begin
+    __shared__ int first_wg[BK_MAX];
+    __shared__ int wsum[BK_THREADS / 64];
+    const int tid = threadIdx.x;
+    const BucketShare me = bucket_share(totals, b, (int)blockIdx.x, first_wg, wsum);
+    if (me.bucket < 0) return;
+    const int part = (me.points + me.wgs - 1) / me.wgs;
+    const int lo = me.index * part, hi = min(lo + part, me.points);
+    for (int i = tid; i < b.Kb * Dp; i += BK_THREADS) cell[i] = 0ull;
+    for (int i = tid; i < b.Kb; i += BK_THREADS) cnt[i] = 0;
+    if (tid == 0) pre[0] = 0;
+    int carry = 0;
+    for (int s0 = 0; s0 < b.sources; s0 += BK_THREADS) {
+        const int s = s0 + tid;
+        int m = 0;
+        if (s < b.sources) {
+            const int32_t *p = bounds + (int64_t)s * (b.buckets + 1) + me.bucket;
+            from[s] = p[0];
+            m = p[1] - p[0];
+        }
+        m = block_prefix(m, wsum) + carry;
+        if (s < b.sources) pre[s + 1] = m;
+        __syncthreads();
+        carry = pre[min(s0 + BK_THREADS, b.sources)];
+    }
+    const double scale = fixed_point_scale(*absmax_p, N);
+    const int TX = 1 << b.tx_log2, TY = BK_THREADS >> b.tx_log2;
+    const int tx = tid & (TX - 1), ty = tid >> b.tx_log2;
+    const int ppr = D / E;
+    // the sources this workgroup's points come from: the last whose points begin at or before i
+    auto source_of = [&](int i, int q, int span) {
+        int top = 1;
+        while (top < span) top <<= 1;
+        for (int k = top >> 1; k >= 1; k >>= 1) {
+            const int r = q + k;
+            if (r < b.sources && pre[r] <= i) q = r;
+        }
+        return q;
+    };
+    const int q_lo = source_of(lo, 0, b.sources), q_hi = hi > lo ? source_of(hi - 1, 0, b.sources) : q_lo;
+    auto fetch = [&](int i0, uint32_t (&e)[UNR], int (&q)[UNR]) {
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int i = min(i0 + u * TY, hi - 1);
+            q[u] = source_of(i, q_lo, q_hi - q_lo + 1);
+            e[u] = entries[(int64_t)q[u] * BK_POINTS + from[q[u]] + (i - pre[q[u]])];
+        }
+    };
+    uint32_t e[UNR];
+    int q[UNR];
+    if (lo + ty < hi) fetch(lo + ty, e, q);
+    for (int i0 = lo + ty; i0 < hi; i0 += TY * UNR) {
+        int lab[UNR];
+        const float *row[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            lab[u] = i0 + u * TY < hi ? (int)(e[u] >> 13) : -1;
+            row[u] = X + ((int64_t)q[u] * BK_POINTS + (e[u] & (BK_POINTS - 1))) * D;
+        }
+        floatx4 f[UNR];
+        const int p0 = min(tx, ppr - 1);
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) f[u] = *reinterpret_cast<const floatx4 *>(row[u] + p0 * E);
+        if (i0 + TY * UNR < hi) fetch(i0 + TY * UNR, e, q);
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+            if (lab[u] >= 0 && tx == 0) atomicAdd(&cnt[lab[u]], 1);
+        for (int pc = tx; pc < ppr; pc += TX) {
+            if (pc != tx) {
+#pragma unroll
+                for (int u = 0; u < UNR; ++u) f[u] = *reinterpret_cast<const floatx4 *>(row[u] + pc * E);
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                if (lab[u] < 0) continue;
+                unsigned long long *dst = cell + (size_t)lab[u] * Dp + pc * E;
+#pragma unroll
+                for (int k = 0; k < E; ++k) atomicAdd(dst + k, (unsigned long long)to_fixed((double)f[u][k], scale));
+            }
+        }
+    }
+    __syncthreads();
+    long long *slab = slabs + (int64_t)blockIdx.x * ((int64_t)b.Kb * D);
+    for (int i = tid; i < b.Kb * D; i += BK_THREADS) {
+        const int k = i / D, d = i - k * D;
+        slab[i] = (long long)cell[k * Dp + d];
+    }
+    for (int i = tid; i < b.Kb; i += BK_THREADS) cslabs[(int64_t)blockIdx.x * b.Kb + i] = cnt[i];
+}
+
+// Sums of a bucket's tables and the averaging pass (as update_reduce_finalize_kernel): blockIdx.x = bucket,
+// BF_CELLS of its cells, BF_GROUPS thread groups that take every BF_GROUPS-th table.
+constexpr int BF_CELLS = 256, BF_GROUPS = BK_THREADS / BF_CELLS;
+__global__ __launch_bounds__(BK_THREADS) void bucket_finalize_kernel(
+    const long long *slabs, const int32_t *cslabs, const int32_t *totals, int64_t N, int D, int K, BucketPlan b,
+    const double *absmax_p, float *C, int32_t *counts)
+{
+    __shared__ int first_wg[BK_MAX];
+    __shared__ int wsum[BK_THREADS / 64];
+    __shared__ long long sh[BF_GROUPS][BF_CELLS];
+    __shared__ int shc[BF_GROUPS][BF_CELLS];
+    const int tid = threadIdx.x, bk = blockIdx.x;
+    bucket_share(totals, b, -1, first_wg, wsum);
+    const int w0 = first_wg[bk], w1 = bk + 1 < BK_MAX ? first_wg[bk + 1] : w0 + 1;
+    const int ci = tid % BF_CELLS, grp = tid / BF_CELLS;
+    const int i = (int)blockIdx.y * BF_CELLS + ci;
+    const int k0 = bk * b.Kb, kn = min(b.Kb, K - k0);
+    const bool on = i < kn * D;
+    const int k = on ? i / D : 0;
+    long long v = 0;
+    int c = 0;
+    if (on) {
+#pragma unroll 8
+        for (int w = w0 + grp; w < w1; w += BF_GROUPS) {
+            v += slabs[(int64_t)w * ((int64_t)b.Kb * D) + i];
+            c += cslabs[(int64_t)w * b.Kb + k];
+        }
+    }
+    sh[grp][ci] = v;
+    shc[grp][ci] = c;
+    __syncthreads();
+    if (grp == 0 && on) {
+#pragma unroll
+        for (int g = 1; g < BF_GROUPS; ++g) {
+            v += sh[g][ci];
+            c += shc[g][ci];
+        }
+        if (i - k * D == 0) counts[k0 + k] = c;
+        int detected = 0;
+        if (c > 0)
+            C[(int64_t)k0 * D + i] = fixed_point_mean<float, false>(0, v, 1.0 / fixed_point_scale(*absmax_p, N), c, &detected);
+    }
+}
+
+// Rows of whole quads (read by 16-byte pieces) that the other paths do not serve as well (whole calls,
+// before / here): D = 32, K = 4096: N = 2^21 174 / 98 us, labels crowded into few clusters 199 / 120, all in one
+// 398 / 133; D = 64, K = 1000, N = 70000 46 / 38; D = 128, K = 512, N = 500000 91 / 88.  Longer rows hide the sort
+// once X leaves the memory-side cache: D = 256: 10^5, K = 4000 101 / 80, 10^6, K = 300 233 / 283.  Against the
+// LDS tables with many slices: D = 12, K = 3000, N = 10^6 76 / 56, but D = 8, K = 4096 41 / 49.
+static bool bucket_pays(int64_t N, int D)
+{
+    return D % 4 == 0 && D >= 12 && (D <= 128 || (D <= 256 && (double)N * D * 4 < 268435456.0));
+}
+
+static BucketPlan plan_bucket(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    BucketPlan b = {};
+    if (dtype != FTK_F32 || !bucket_pays(N, D)) return b;
+    b.Kb = BK_CELLS / D < K ? BK_CELLS / D : K;
+    b.buckets = (int)ceil_div(K, b.Kb);
+    const int64_t sources = ceil_div(N, BK_POINTS);
+    if (b.buckets >= BK_MAX || sources > BK_SOURCES) return b;
+    b.sources = (int)sources;
+    b.wgs = BK_WGS;  // shares; rounding up adds at most one workgroup per bucket
+    while ((1 << b.tx_log2) < D / 4 && b.tx_log2 < 6) ++b.tx_log2;
+    b.ok = sources * (b.buckets + 1) <= N;  // the boundaries take the place of the sorted labels
+    return b;
+}
+// cells and counts of all slots (0: not this path)
+int64_t update_bucket_cells(ftk_dtype dtype, int64_t N, int D, int K, int64_t *counts)
+{
+    const BucketPlan b = plan_bucket(dtype, N, D, K);
+    const int64_t slots = b.ok ? (int64_t)b.wgs + b.buckets : 0;
+    *counts = slots * b.Kb;
+    return slots * b.Kb * D;
+}
+
 // Launch geometry of the pass that accumulates the sums (the one faults are injected into).
 struct UpdateLaunch {
     bool sorted_path;
@@ -971,7 +1267,22 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
     fa.n_faults = n_faults;
     fa.mode = (int)ft_mode;
     fa.stats = stats;
-    if (L.sorted_path) {
+    const BucketPlan bp = plan_bucket(dtype, N, D, K);
+    if (bp.ok && u.aligned && !dmr && n_faults == 0 && g_tuning.update_path < 0 &&
+        (L.sorted_path || (u.nks >= 4 && N >= 65536))) {
+        uint32_t *entries = reinterpret_cast<uint32_t *>(w.sort_idx);
+        long long *slabs = reinterpret_cast<long long *>(w.upd_slab);
+        int32_t *bounds = w.sort_lab, *totals = w.sort_cursor;
+        FTK_TRY(launch_zero_ints(totals, bp.buckets, st));
+        hipLaunchKernelGGL(bucket_split_kernel, dim3(bp.sources), dim3(BK_THREADS), 0, st, labels, N, K, bp.Kb, bp.buckets,
+                           entries, bounds, totals);
+        const size_t lds = (size_t)bp.Kb * (D + 1) * 8 + ((size_t)bp.Kb + 2 * bp.sources + 1) * 4;
+        hipLaunchKernelGGL(bucket_accumulate_kernel, dim3(bp.wgs + bp.buckets), dim3(BK_THREADS), lds, st, (const float *)X, entries,
+                           bounds, totals, N, D, K, bp, absmax, slabs, w.upd_cslab);
+        hipLaunchKernelGGL(bucket_finalize_kernel, dim3(bp.buckets, (unsigned)ceil_div(bp.Kb * D, BF_CELLS)),
+                           dim3(BK_THREADS), 0, st, slabs, w.upd_cslab, totals, N, D, K, bp, absmax, (float *)C,
+                           counts);
+    } else if (L.sorted_path) {
         {
             const int blocks = (int)(ceil_div(cells, 256) < 1024 ? ceil_div(cells, 256) : 1024);
             hipLaunchKernelGGL(update_zero_kernel, dim3(blocks), dim3(256), 0, st, sums, 2 * cells, counts, K);
