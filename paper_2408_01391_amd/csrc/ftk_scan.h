@@ -8,7 +8,7 @@ namespace ftk {
 
 struct ScanPlan {
     bool ok;
-    bool triple;        // rows of up to 8 features: three pieces per operand, one 16-value block per tile
+    int form;           // layout of a block (ScanForm)
     bool stream;        // rows beyond 128 features: both operands streamed through LDS
     int nb;             // blocks of 16 features in the centroid image (and of the compiled variant)
     int tiles, tiles_pad;  // tiles of 32 centroids, and those the image holds (whole chunks)

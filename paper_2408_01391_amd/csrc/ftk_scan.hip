@@ -18,7 +18,9 @@
 // for c.  Kept are x0c0 + x0c1 + x1c0; lost are x1c1, r.c and x.r', 2^-18 each: 3 * 64 u = 192 u.  An
 // instruction rounds to within 7 u of what it adds up (measured, pinned by a test): 21 u per block of
 // 16 features.  Rows of up to 8 features leave half of a block empty, which holds the three-piece
-// form (six products, error 2 u) in the same three instructions.
+// form (six products, error 2 u) in the same three instructions; rows of up to 16 take that form in six,
+// because short rows in many clusters have norms far above their distances and the wider band lists
+// too many of them (10^6 x 16 in a box of 200, K = 200: a tenth of the points).
 //
 // Both operands are multiplied by one power of two taken from two centroid rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
@@ -48,6 +50,15 @@ constexpr int settle_rows(size_t element) { return element == 8 ? 2 : 4; }  // r
 constexpr int SCAN_LISTS = 64;    // lists of points to resolve, a counter in a line of its own each
 constexpr int LIST_STRIDE = 32;
 constexpr float SCAN_FLOOR = 7.9e-31f;  // 2^-100: below it scores (of centroids near 1) may have lost digits to underflow
+
+// how a block of the contraction is laid out
+enum ScanForm : int {
+    FORM_PAIR = 0,    // 16 features, two pieces: fragments c0, c1 against x0, x1; c1x0 + c0x1 + c0x0
+    FORM_OCTET = 1,   // 8 features, three pieces: fragments (c0 | c1), (c2 | c0) against (x0 | x0), (x1 | x1), (x0 | x2)
+    FORM_TRIPLE = 2   // 16 features, three pieces: c0, c1, c2 against x0, x1, x2; the six largest products
+};
+static constexpr int form_frags(int form) { return form == FORM_TRIPLE ? 3 : 2; }   // centroid fragments per block
+static constexpr int form_pieces(int form) { return form == FORM_PAIR ? 2 : 3; }    // point fragments per block
 
 struct ScanArgs {
     const void *X;
@@ -172,8 +183,8 @@ struct RowReader {
 
 // ---- centroids: pieces in fragment order, start values, norms --------------------------------
 // One workgroup per tile of 32 centroids; lane l of a fragment supplies row l % 32 and the 8 features
-// 16b + 8(l/32) of block b (TRI: all 8 features; fragment 0 = (c0 | c1), fragment 1 = (c2 | c0)).
-template <typename T, bool TRI>
+// 16b + 8(l/32) of block b (FORM_OCTET: all 8 features).
+template <typename T, int FORM>
 __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
                                                               float *tile_max, double *scale, int32_t *list_count, int lists)
 {
@@ -208,7 +219,7 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     const T *c = C + (size_t)(j < K ? j : 0) * D;
     double n = 0.0;
     for (int b = wave; b < nb; b += nw) {
-        const int f0 = TRI ? 0 : 16 * b + 8 * g;
+        const int f0 = FORM == FORM_OCTET ? 0 : 16 * b + 8 * g;
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -217,12 +228,18 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
             n = fma((double)w, (double)w, n);
             v[e] = (float)w;
         }
-        uint4 *dst = image + ((size_t)tile * nb + b) * (2 * FRAG_UNITS) + lane;
-        if constexpr (TRI) {
+        uint4 *dst = image + ((size_t)tile * nb + b) * (form_frags(FORM) * FRAG_UNITS) + lane;
+        if constexpr (FORM != FORM_PAIR) {
             uint4 a0, a1, a2;
             split_triple(v, a0, a1, a2);
-            dst[0] = select_units(g != 0, a1, a0);
-            dst[FRAG_UNITS] = select_units(g != 0, a0, a2);
+            if constexpr (FORM == FORM_OCTET) {
+                dst[0] = select_units(g != 0, a1, a0);
+                dst[FRAG_UNITS] = select_units(g != 0, a0, a2);
+            } else {
+                dst[0] = a0;
+                dst[FRAG_UNITS] = a1;
+                dst[2 * FRAG_UNITS] = a2;
+            }
         } else {
             uint4 a0, a1;
             split_pair(v, a0, a1);
@@ -230,7 +247,7 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
             dst[FRAG_UNITS] = a1;
         }
     }
-    if (!TRI) n += __shfl_xor(n, 32, 64);
+    if (FORM != FORM_OCTET) n += __shfl_xor(n, 32, 64);
     if (lane < 32) sh_n[wave][lane] = n;
     __syncthreads();
     if (tid < 32) {
@@ -306,10 +323,11 @@ __device__ __forceinline__ void scan_best_finish(const ScanBest &b, int g, float
 // registers) while the current one is multiplied.  Fragments are stored lane by lane, so the copy is
 // linear and the reads are free of bank conflicts.  No settlement code: at 128 features 228 registers,
 // two workgroups of four waves per compute unit that wait at their own barriers.
-template <typename T, int NB, bool TRI, bool RAG>
+template <typename T, int NB, int FORM, bool RAG>
 __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_kernel(ScanArgs a)
 {
-    constexpr int TU = NB * 2 * FRAG_UNITS;  // units per tile
+    constexpr int FR = form_frags(FORM);
+    constexpr int TU = NB * FR * FRAG_UNITS;  // units per tile
     extern __shared__ __align__(16) uint4 lds4[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
@@ -332,7 +350,7 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
 
     const T s = (T)a.scale[0];
     const T *X = reinterpret_cast<const T *>(a.X);
-    constexpr int NP = TRI ? 3 : 2;
+    constexpr int NP = form_pieces(FORM);
     uint4 b[SC_PT][NB][NP];
 #pragma unroll
     for (int pt = 0; pt < SC_PT; ++pt) {
@@ -341,7 +359,7 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
         const RowReader<T, RAG> row(X + p * a.D, a.D);
         // all of a row's loads in flight together, unless that takes more registers than there are
         constexpr int BATCH = sizeof(T) == 8 && NB > 4 ? NB / 2 : NB;
-        auto off = [&](int u) { return TRI ? 4 * u : 16 * (u >> 1) + 8 * g + 4 * (u & 1); };
+        auto off = [&](int u) { return FORM == FORM_OCTET ? 4 * u : 16 * (u >> 1) + 8 * g + 4 * (u & 1); };
         Quad<T> q[2 * BATCH];
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
@@ -357,12 +375,12 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
             }
-            if constexpr (TRI) {
+            if constexpr (FORM != FORM_PAIR) {
                 uint4 x0, x1, x2;
                 split_triple(v, x0, x1, x2);
                 b[pt][k][0] = x0;
                 b[pt][k][1] = x1;
-                b[pt][k][2] = select_units(g != 0, x2, x0);
+                b[pt][k][2] = FORM == FORM_TRIPLE ? x2 : select_units(g != 0, x2, x0);
             } else {
                 split_pair(v, b[pt][k][0], b[pt][k][1]);
             }
@@ -395,28 +413,34 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
                 for (int pt = 0; pt < SC_PT; ++pt) acc[pt] = ci;
             }
             // the fragments of block k + 1 are requested before the instructions of block k are issued
-            uint4 n0 = f[0], n1 = f[FRAG_UNITS];
+            uint4 n[FR];
+#pragma unroll
+            for (int i = 0; i < FR; ++i) n[i] = f[i * FRAG_UNITS];
 #pragma unroll
             for (int k = 0; k < NB; ++k) {
-                const bf16x8 a0 = __builtin_bit_cast(bf16x8, n0);
-                const bf16x8 a1 = __builtin_bit_cast(bf16x8, n1);
+                bf16x8 af[FR];
+#pragma unroll
+                for (int i = 0; i < FR; ++i) af[i] = __builtin_bit_cast(bf16x8, n[i]);
                 if (k + 1 < NB) {
-                    n0 = f[(2 * k + 2) * FRAG_UNITS];
-                    n1 = f[(2 * k + 3) * FRAG_UNITS];
+#pragma unroll
+                    for (int i = 0; i < FR; ++i) n[i] = f[((k + 1) * FR + i) * FRAG_UNITS];
                 }
-                // the products, smallest first; the chains of the two point tiles interleave
+                // (centroid, point) fragments of the products, smallest first; the chains of the two
+                // point tiles interleave
+                constexpr int NM = FORM == FORM_TRIPLE ? 6 : 3;
+                constexpr int PROD[6][2] = {{FORM == FORM_TRIPLE ? 2 : 1, FORM == FORM_OCTET ? 2 : 0},
+                                            {FORM == FORM_TRIPLE ? 1 : 0, 1}, {0, FORM == FORM_TRIPLE ? 2 : 0},
+                                            {1, 0}, {0, 1}, {0, 0}};
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
+                for (int i = 0; i < NM; ++i)
 #pragma unroll
-                    for (int pt = 0; pt < SC_PT; ++pt) {
-                        const bf16x8 x = __builtin_bit_cast(bf16x8, TRI ? b[pt][k][i == 0 ? NP - 1 : (i == 1 ? 1 : 0)]
-                                                                        : b[pt][k][i == 1 ? 1 : 0]);
-                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i == 0 ? a1 : a0, x, acc[pt], 0, 0, 0);
-                    }
+                    for (int pt = 0; pt < SC_PT; ++pt)
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            af[PROD[i][0]], __builtin_bit_cast(bf16x8, b[pt][k][PROD[i][1]]), acc[pt], 0, 0, 0);
             }
             // keep that order through instruction scheduling, which would sink every read to its use
             // (at four blocks the second pair of fragments does not fit the registers of three waves)
-            if constexpr (NB != 4) {
+            if constexpr (NB != 4 && FORM != FORM_TRIPLE) {
                 __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
                 for (int k = 0; k + 1 < NB; ++k) {
@@ -849,10 +873,10 @@ __device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, in
 
 constexpr int RS_THREADS = 512, RS_CAP = 8;
 
-template <typename T, bool TRI, int L>
+template <typename T, int FORM, int L>
 __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, const T *C, T *mindist, ResolveArgs a)
 {
-    constexpr int NP = TRI ? 3 : 2;
+    constexpr int NP = form_pieces(FORM), FR = form_frags(FORM);
     constexpr int GROUPS = RS_THREADS / L;
     extern __shared__ __align__(16) uint4 lds4[];  // [nb][NP][64] fragments of the 32 points
     __shared__ int32_t sh_p[32];
@@ -906,7 +930,7 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
         const RowReader<T, true> row(X + (int64_t)sh_p[col] * a.D, a.D);
 #pragma unroll 2
         for (int b = wave; b < a.nb; b += RS_THREADS / 64) {
-            const int f0 = TRI ? 0 : 16 * b + 8 * g;
+            const int f0 = FORM == FORM_OCTET ? 0 : 16 * b + 8 * g;
             const Quad<T> q0 = row.keep(row.request(f0), f0), q1 = row.keep(row.request(f0 + 4), f0 + 4);
             float v[8];
 #pragma unroll
@@ -915,12 +939,12 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
                 v[4 + e] = (float)(q1.v[e] * s);
             }
             uint4 *dst = lds4 + b * NP * FRAG_UNITS + lane;
-            if constexpr (TRI) {
+            if constexpr (FORM != FORM_PAIR) {
                 uint4 x0, x1, x2;
                 split_triple(v, x0, x1, x2);
                 dst[0] = x0;
                 dst[FRAG_UNITS] = x1;
-                dst[2 * FRAG_UNITS] = select_units(g != 0, x2, x0);
+                dst[2 * FRAG_UNITS] = FORM == FORM_TRIPLE ? x2 : select_units(g != 0, x2, x0);
             } else {
                 uint4 x0, x1;
                 split_pair(v, x0, x1);
@@ -933,12 +957,12 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
         // this wave's tiles, block by block, four blocks and the next tile's start values in flight
         const int t0 = split * per + wave;
         const int total = t0 < tile_end ? ((tile_end - t0 - 1) / (RS_THREADS / 64) + 1) * a.nb : 0;
-        uint4 ring[4][2];
+        uint4 ring[4][FR];
         int lt = t0, lb = 0;  // tile and block of the next request
-        auto request = [&](uint4 (&r)[2]) {
-            const uint4 *f = a.image + ((size_t)min(lt, a.tiles - 1) * a.nb + lb) * (2 * FRAG_UNITS) + lane;
-            r[0] = f[0];
-            r[1] = f[FRAG_UNITS];
+        auto request = [&](uint4 (&r)[FR]) {
+            const uint4 *f = a.image + ((size_t)min(lt, a.tiles - 1) * a.nb + lb) * (FR * FRAG_UNITS) + lane;
+#pragma unroll
+            for (int i = 0; i < FR; ++i) r[i] = f[i * FRAG_UNITS];
             if (++lb == a.nb) {
                 lb = 0;
                 lt += RS_THREADS / 64;
@@ -968,12 +992,20 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
                 }
                 const bf16x8 a0 = __builtin_bit_cast(bf16x8, ring[u][0]);
                 const bf16x8 a1 = __builtin_bit_cast(bf16x8, ring[u][1]);
+                const bf16x8 a2 = __builtin_bit_cast(bf16x8, ring[u][FR - 1]);
                 request(ring[u]);
                 const uint4 *q = lds4 + b * NP * FRAG_UNITS + lane;
                 const bf16x8 x0 = __builtin_bit_cast(bf16x8, q[0]);
                 const bf16x8 x1 = __builtin_bit_cast(bf16x8, q[FRAG_UNITS]);
-                const bf16x8 xs = TRI ? __builtin_bit_cast(bf16x8, q[(NP - 1) * FRAG_UNITS]) : x0;
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, xs, acc, 0, 0, 0);
+                const bf16x8 x2 = __builtin_bit_cast(bf16x8, q[(NP - 1) * FRAG_UNITS]);
+                if constexpr (FORM == FORM_TRIPLE) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, x0, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, x1, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x2, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, x0, acc, 0, 0, 0);
+                } else {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, FORM == FORM_OCTET ? x2 : x0, acc, 0, 0, 0);
+                }
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x1, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x0, acc, 0, 0, 0);
                 if (++b < a.nb) continue;
@@ -1128,7 +1160,7 @@ static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
     if (D < 4 || K < 96) return false;
     if (K >= 768) return true;
     if (dtype == FTK_F32) {
-        if (D < 16) return K >= 512;
+        if (D <= 8) return K >= 512;
         return K >= 256 || N >= 200000 || (K >= 192 && D >= 32) || D >= 128;
     }
     return K >= 192 ? N >= 100000 : (N >= 200000 && D <= 96);
@@ -1143,7 +1175,7 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
 {
     ScanPlan p = {};
     p.ok = true;
-    p.triple = D <= 8;
+    p.form = D <= 8 ? FORM_OCTET : (D <= 16 ? FORM_TRIPLE : FORM_PAIR);
     p.stream = D > 128;
     p.tiles = (int)ceil_div(K, 32);
     p.pblocks = ceil_div(N, SC_POINTS);
@@ -1161,7 +1193,7 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     } else {
         p.nb = resident_blocks(D);
         const int chunk = p.nb <= 4 ? 16 * 1024 : 32 * 1024;
-        int tpc = chunk / (p.nb * 2 * FRAG_UNITS * 16);
+        int tpc = chunk / (p.nb * form_frags(p.form) * FRAG_UNITS * 16);
         if (tpc > p.tiles) tpc = p.tiles;
         p.tpc = tpc;
         p.nch = (int)ceil_div(p.tiles, tpc);
@@ -1179,7 +1211,8 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     if (p.rec_reserve < SCAN_FILL * SC_POINTS + N + SC_POINTS) p.rec_reserve = SCAN_FILL * SC_POINTS + N + SC_POINTS;
     if (p.rec_reserve > (int64_t)p.tiles * N) p.rec_reserve = (int64_t)p.tiles * N;
     const double u = Mma<float>::kEps;
-    p.band_coef = 2.0 * ((p.triple ? 4.0 : 196.0) + 21.0 * p.nb + (dtype == FTK_F64 ? 2.0 : 0.0)) * u;
+    p.band_coef = 2.0 * ((p.form == FORM_PAIR ? 196.0 : 4.0) + (p.form == FORM_TRIPLE ? 42.0 : 21.0) * p.nb +
+                         (dtype == FTK_F64 ? 2.0 : 0.0)) * u;
     return p;
 }
 
@@ -1196,7 +1229,7 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
     };
     // whole chunks of whatever size a batch is cut into: at most eight tiles (stream), tpc (resident)
     const size_t tiles = p.stream ? (size_t)p.tiles + 8 : (size_t)p.tiles_pad;
-    b.image = (uint4 *)take(tiles * p.nb * 2 * FRAG_UNITS * 16);
+    b.image = (uint4 *)take(tiles * p.nb * form_frags(p.form) * FRAG_UNITS * 16);
     b.start = (float *)take((tiles + 1) * 32 * 4);  // copied two tiles a time
     b.tile_max = (float *)take(tiles * 4);
     b.scale = (double *)take(8);
@@ -1208,15 +1241,15 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
     return b;
 }
 
-template <typename T, int NB, bool TRI>
+template <typename T, int NB, int FORM>
 static void launch_resident(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
 {
     const dim3 grid((unsigned)(p.pblocks * p.splits)), block(SC_THREADS);
-    const size_t lds = 2 * ((size_t)p.tpc * NB * 2 * FRAG_UNITS + (size_t)((p.tpc + 1) / 2) * 16) * 16;
+    const size_t lds = 2 * ((size_t)p.tpc * NB * form_frags(FORM) * FRAG_UNITS + (size_t)((p.tpc + 1) / 2) * 16) * 16;
     if (a.D % 4)
-        hipLaunchKernelGGL((scan_resident_kernel<T, NB, TRI, true>), grid, block, lds, st, a);
+        hipLaunchKernelGGL((scan_resident_kernel<T, NB, FORM, true>), grid, block, lds, st, a);
     else
-        hipLaunchKernelGGL((scan_resident_kernel<T, NB, TRI, false>), grid, block, lds, st, a);
+        hipLaunchKernelGGL((scan_resident_kernel<T, NB, FORM, false>), grid, block, lds, st, a);
 }
 
 template <typename T, int CT>
@@ -1243,12 +1276,19 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
     const int64_t groups = ceil_div(c.N, 32);
     const int64_t side = ceil_div(1024, r.splits);  // groups side by side
     const dim3 grid((unsigned)((groups < side ? groups : side) * r.splits)), block(RS_THREADS);
-    if (p.triple)
-        hipLaunchKernelGGL((scan_resolve_kernel<T, true, L>), grid, block, (size_t)3 * FRAG_UNITS * 16, st, (const T *)c.X,
-                           (const T *)c.C, (T *)c.mindist, r);
-    else
-        hipLaunchKernelGGL((scan_resolve_kernel<T, false, L>), grid, block, (size_t)p.nb * 2 * FRAG_UNITS * 16, st,
-                           (const T *)c.X, (const T *)c.C, (T *)c.mindist, r);
+#define FTK_LAUNCH_RESOLVE(F)                                                                                        \
+    hipLaunchKernelGGL((scan_resolve_kernel<T, F, L>), grid, block, (size_t)p.nb * form_pieces(F) * FRAG_UNITS * 16, \
+                       st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, r)
+    if constexpr (L <= 2) {
+        if (p.form == FORM_OCTET) FTK_LAUNCH_RESOLVE(FORM_OCTET);
+        else FTK_LAUNCH_RESOLVE(FORM_TRIPLE);
+    } else if constexpr (L == 4) {
+        if (p.form == FORM_TRIPLE) FTK_LAUNCH_RESOLVE(FORM_TRIPLE);
+        else FTK_LAUNCH_RESOLVE(FORM_PAIR);
+    } else {
+        FTK_LAUNCH_RESOLVE(FORM_PAIR);
+    }
+#undef FTK_LAUNCH_RESOLVE
 }
 
 template <typename T>
@@ -1259,12 +1299,13 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     // a contiguous list where refine_kernel takes it over
     int32_t *const counts = p.resolve ? b.list_count : w.wl_count;
     const int lists = p.resolve ? SCAN_LISTS : 1;
-    if (p.triple)
-        hipLaunchKernelGGL((scan_centroids_kernel<T, true>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start,
-                           b.tile_max, b.scale, counts, lists);
-    else
-        hipLaunchKernelGGL((scan_centroids_kernel<T, false>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start,
-                           b.tile_max, b.scale, counts, lists);
+#define FTK_LAUNCH_CENTROIDS(F)                                                                                       \
+    hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start, \
+                       b.tile_max, b.scale, counts, lists)
+    if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
+    else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE);
+    else FTK_LAUNCH_CENTROIDS(FORM_PAIR);
+#undef FTK_LAUNCH_CENTROIDS
     ScanArgs a = {};
     a.X = c.X;
     a.image = b.image;
@@ -1286,16 +1327,17 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
         case 3: launch_stream<T, 3>(a, p, st); break;
         default: launch_stream<T, 4>(a, p, st); break;
         }
-    } else if (p.triple) {
-        launch_resident<T, 1, true>(a, p, st);
+    } else if (p.form == FORM_OCTET) {
+        launch_resident<T, 1, FORM_OCTET>(a, p, st);
+    } else if (p.form == FORM_TRIPLE) {
+        launch_resident<T, 1, FORM_TRIPLE>(a, p, st);
     } else {
         switch (p.nb) {
-        case 1: launch_resident<T, 1, false>(a, p, st); break;
-        case 2: launch_resident<T, 2, false>(a, p, st); break;
-        case 3: launch_resident<T, 3, false>(a, p, st); break;
-        case 4: launch_resident<T, 4, false>(a, p, st); break;
-        case 6: launch_resident<T, 6, false>(a, p, st); break;
-        default: launch_resident<T, 8, false>(a, p, st); break;
+        case 2: launch_resident<T, 2, FORM_PAIR>(a, p, st); break;
+        case 3: launch_resident<T, 3, FORM_PAIR>(a, p, st); break;
+        case 4: launch_resident<T, 4, FORM_PAIR>(a, p, st); break;
+        case 6: launch_resident<T, 6, FORM_PAIR>(a, p, st); break;
+        default: launch_resident<T, 8, FORM_PAIR>(a, p, st); break;
         }
     }
     SettleArgs s;
