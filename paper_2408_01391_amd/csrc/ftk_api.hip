@@ -149,6 +149,25 @@ static bool route_small(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft
     return ft == FTK_FT_OFF && n_faults == 0 && g_tuning.assign_variant == -1 && small_assign_pays(dtype, N, D, K);
 }
 
+// The reduced-precision entry point without checksums or faults: its own kernels where nothing else that
+// returns direct-difference distances is faster (whole calls, its own kernel / the other): rows of 9 .. 32
+// features scan at any K (1.5 * 10^6 x 32, K = 64 330 / 95 us, K = 512 516 / 194), wider ones from K = 512 (2 * 10^5 x
+// 128 217 / 125; K = 192 92 / 80, but 64 features 42 / 46 at K = 96).  Rows of up to 8: the fp32 kernel up to 512
+// centroids (2 * 10^5 x 8, K = 64 31 / 19), beyond that the scan while there are few points (20000, K = 4096 106 /
+// 45; 1.5 * 10^6, K = 1024 163 / 195).
+enum FastRoute { FAST_OWN, FAST_SMALL, FAST_FP32, FAST_SCAN };
+static FastRoute route_fast(int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
+{
+    if (ft != FTK_FT_OFF || n_faults > 0 || g_tuning.assign_variant != -1) return FAST_OWN;
+    if (small_assign_pays(FTK_F32, N, D, K)) return FAST_SMALL;
+    if (D <= 8) return K <= 512 ? FAST_FP32 : (N < 100000 ? FAST_SCAN : FAST_OWN);
+    return D <= 32 || K >= 512 ? FAST_SCAN : FAST_OWN;
+}
+static bool fast_may_scan(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    return fast_supported(dtype, D) && route_fast(N, D, K, FTK_FT_OFF, 0) == FAST_SCAN;
+}
+
 // The workspace is carved for the larger of the two kernel variants so that its size does not
 // depend on which one the dispatcher picks.  The scan's buffers share their bytes with those of the
 // label-sorted update, which no call uses at the same time (the tables of the other update path
@@ -180,7 +199,9 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
     w.wl_count = (int32_t *)take(4 * sizeof(int32_t));
     w.wl = (int32_t *)take((size_t)N * sizeof(int32_t));
     w.wg_refined = (int32_t *)take(((size_t)N / 64 + 2) * sizeof(int32_t));
-    const size_t scan_bytes = assign_only && !scan ? 0 : carve_scan(nullptr, plan_scan(dtype, N, D, K), N).bytes;
+    const bool may_scan = plan_scan(dtype, N, D, K).ok || (!assign_only && fast_may_scan(dtype, N, D, K));
+    const size_t scan_bytes =
+        (assign_only && !scan) || !may_scan ? 0 : carve_scan(nullptr, cut_scan(dtype, N, D, K), N).bytes;
     w.scan = nullptr;
     if (assign_only) {  // the assignment step touches nothing beyond its own buffers and the scan's
         if (p) w.scan = (void *)(p + off);
@@ -304,8 +325,17 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
                               bool own_scratch = false, bool allow_scan = true)
 {
     const bool aligned16 = ((uintptr_t)c.X % 16 == 0) && ((uintptr_t)c.C % 16 == 0);
-    const bool small = !fast && route_small(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
-    const ScanPlan scan = fast || small || !allow_scan ? ScanPlan{} : route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
+    FastRoute froute = FAST_OWN;
+    if (fast) {
+        froute = route_fast(c.N, c.D, c.K, c.ft, c.n_faults);
+        if (froute == FAST_FP32) fast = false;  // the register-resident kernel of short rows
+    }
+    const bool small = fast ? froute == FAST_SMALL : froute == FAST_OWN && route_small(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
+    ScanPlan scan = {};
+    if (froute == FAST_SCAN)
+        scan = cut_scan(c.dtype, c.N, c.D, c.K);
+    else if (!fast && froute == FAST_OWN && !small && allow_scan)
+        scan = route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     AssignPlan p;
     if (small || scan.ok) {
         memset(&p, 0, sizeof(p));
