@@ -157,11 +157,11 @@ __global__ __launch_bounds__(256) void split2_centroids_kernel(const float *C, i
 // STREAM (every tile resident, no faults listed): one point tile per unit, and the rows of a wave's
 // next unit are requested before the sweep of the current one, so that the first of the two
 // memory phases of a unit passes under matrix work instead of in front of it.
-template <int NH, bool FT, bool WHOLE, bool STREAM>
+template <int NH, bool FT, bool WHOLE, bool STREAM, int PTS = fw_pt(NH)>
 __global__ __launch_bounds__(FW_WAVES * 64, FW_WAVES / 4) void assign_fast_wide_kernel(FastArgs a)
 {
     constexpr int THREADS = FW_WAVES * 64;
-    constexpr int PT = STREAM ? 1 : fw_pt(NH);
+    constexpr int PT = STREAM ? 1 : PTS;
     using M = Mma<float>;
     using G = TileGeom<FT>;
     constexpr int SU = fw_row_units(NH);
@@ -195,8 +195,9 @@ __global__ __launch_bounds__(FW_WAVES * 64, FW_WAVES / 4) void assign_fast_wide_
     for (int i = tid; i < SMALLD_LIST_CAP; i += THREADS) sh_wl[i] = -1;
     if (tid == 0) sh_wlcnt = 0;
 
-    // stage tiles [ch*tpc, (ch+1)*tpc): a copy of the prepared image (eight 16-byte loads in flight
-    // per thread, clamped instead of guarded) plus the accumulator start values.
+    // stage tiles [ch*tpc, (ch+1)*tpc): a copy of the prepared image, straight to LDS (through registers
+    // it took eight 16-byte loads a thread, which the compiler passed through scratch memory), plus the
+    // accumulator start values.
     // Threads t0 .. t0 + nthr - 1 of the workgroup take part.
     auto stage_chunk = [&](int ch, int t0, int nthr) {
         const int tile0 = ch * a.tpc;
@@ -205,14 +206,8 @@ __global__ __launch_bounds__(FW_WAVES * 64, FW_WAVES / 4) void assign_fast_wide_
         const uint4 *src = a.csplit + (size_t)tile0 * TU;
         const int n = ntile * TU;
         if (ts >= 0) {
-            for (int base = ts; base < n; base += 8 * nthr) {
-                uint4 f[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) f[u] = src[min(base + u * nthr, n - 1)];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (base + u * nthr < n) ldsC[base + u * nthr] = f[u];
-            }
+            for (int i = (ts >> 6) * 64; i < n; i += nthr)
+                if (i + lane < n) to_lds16(src + i + lane, ldsC + i);
             for (int idx = ts; idx < ntile * 32; idx += nthr) {
                 const int tl = idx >> 5, gg = (idx >> 4) & 1, r = idx & 15;
                 const int T = tile0 + tl;
@@ -228,6 +223,7 @@ __global__ __launch_bounds__(FW_WAVES * 64, FW_WAVES / 4) void assign_fast_wide_
                 }
                 ldsH[idx] = h;
             }
+            wait_loads<0>();  // the copy has landed before the barrier that follows
         }
     };
     // With every tile resident the (only) chunk is staged inside the first unit of work and the two
@@ -753,7 +749,23 @@ static void launch_fast_wide_t(const FastArgs &a, const AssignPlan &p, hipStream
         b.nblocks = (int)blocks;
         grid = (int)(blocks < 256 ? blocks : 256);
     }
+    // checksummed tiles staged in chunks, no faults listed: one point tile per unit as well
+    const bool narrow = FT && !stream && a.n_faults == 0;
+    if (narrow) {
+        const int64_t blocks = ceil_div(a.N, (int64_t)FW_WAVES * 32);
+        b.nblocks = (int)blocks;
+        grid = (int)(blocks < 256 ? blocks : 256);
+    }
     const dim3 g((unsigned)grid), t(FW_WAVES * 64);
+    if constexpr (FT) {
+        if (narrow) {
+            if (a.D == 16 * NH)
+                hipLaunchKernelGGL((assign_fast_wide_kernel<NH, FT, true, false, 1>), g, t, p.lds_bytes, st, b);
+            else
+                hipLaunchKernelGGL((assign_fast_wide_kernel<NH, FT, false, false, 1>), g, t, p.lds_bytes, st, b);
+            return;
+        }
+    }
     if (a.D == 16 * NH) {
         if (stream) hipLaunchKernelGGL((assign_fast_wide_kernel<NH, FT, true, true>), g, t, p.lds_bytes, st, b);
         else hipLaunchKernelGGL((assign_fast_wide_kernel<NH, FT, true, false>), g, t, p.lds_bytes, st, b);

@@ -191,4 +191,26 @@ __device__ __forceinline__ float shfl_xor_t(float v, int m) { return __shfl_xor(
 __device__ __forceinline__ double shfl_xor_t(double v, int m) { return __shfl_xor(v, m, 64); }
 __device__ __forceinline__ int shfl_xor_t(int v, int m) { return __shfl_xor(v, m, 64); }
 
+// Copies from global memory to LDS without registers: lane i's 16 (4) bytes land at l + 16 (4) * i; l is
+// the same for the whole wave.  Written as assembly because the compiler, which cannot tell the
+// two halves of a double buffer apart, would wait for the copy before the next LDS read; every
+// copy is waited for with wait_loads() before the barrier that hands its buffer over.
+__device__ __forceinline__ void to_lds16(const void *g, void *l)
+{
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(g) : "memory", "m0");
+}
+__device__ __forceinline__ void to_lds4(const void *g, void *l)
+{
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)l);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(at), "v"(g) : "memory", "m0");
+}
+
+// wait until all but the youngest N memory loads, and all LDS accesses, are done
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+}
+
 }  // namespace ftk

@@ -76,28 +76,6 @@ struct ScanArgs {
     ScanRecord *rec;
 };
 
-// Copies from global memory to LDS without registers: lane i's 16 (4) bytes land at l + 16 (4) * i; l is
-// the same for the whole wave.  Written as assembly because the compiler, which cannot tell the
-// two halves of a double buffer apart, would wait for the copy before the next LDS read; every
-// copy is waited for with wait_loads() before the barrier that hands its buffer over.
-__device__ __forceinline__ void to_lds16(const void *g, void *l)
-{
-    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)l);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(g) : "memory", "m0");
-}
-__device__ __forceinline__ void to_lds4(const void *g, void *l)
-{
-    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)l);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(at), "v"(g) : "memory", "m0");
-}
-
-// wait until all but the youngest N memory loads, and all LDS accesses, are done
-template <int N>
-__device__ __forceinline__ void wait_loads()
-{
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
-}
-
 __device__ __forceinline__ void split_pair(const float (&v)[8], uint4 &hi, uint4 &lo)
 {
     bf16x8 p0, p1;
@@ -217,14 +195,17 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     const int row = lane & 31, g = lane >> 5;
     const int j = 32 * tile + row;
     const T *c = C + (size_t)(j < K ? j : 0) * D;
+    const RowReader<T, true> reader(c, D);
     double n = 0.0;
+#pragma unroll 2
     for (int b = wave; b < nb; b += nw) {
         const int f0 = FORM == FORM_OCTET ? 0 : 16 * b + 8 * g;
+        const Quad<T> q0 = reader.request(f0), q1 = reader.request(f0 + 4);
+        const Quad<T> k0 = reader.keep(q0, f0), k1 = reader.keep(q1, f0 + 4);
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int d = f0 + e;
-            const T w = (j < K && d < D) ? c[d < D ? d : 0] * s : T(0);
+            const T w = j < K ? (e < 4 ? k0.v[e & 3] : k1.v[e & 3]) * s : T(0);
             n = fma((double)w, (double)w, n);
             v[e] = (float)w;
         }
