@@ -814,6 +814,7 @@ struct ResolveArgs {
     ScanRecord *rec;
     int64_t N;
     int D, K, nb, tiles, splits;
+    int side;           // workgroups that run side by side
     int32_t *labels;
     const ScanListed *list;
     const int32_t *list_count;
@@ -870,8 +871,6 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     __shared__ double sh_bd32[32];
     __shared__ int32_t sh_code[32];
     __shared__ int sh_last;
-    const int S = a.splits, split = (int)blockIdx.x % S, per = (a.tiles + S - 1) / S;
-    const int tile_end = min(a.tiles, (split + 1) * per);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
     const int sub = tid & (L - 1), grp = tid / L;
@@ -891,6 +890,10 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     }
     __syncthreads();
     const int n = sh_pre[SCAN_LISTS];
+    // workgroups per group: no more than run side by side
+    const int S = max(1, min(a.splits, a.side / max(1, (n + 31) / 32)));
+    const int split = (int)blockIdx.x % S, per = (a.tiles + S - 1) / S;
+    const int tile_end = min(a.tiles, (split + 1) * per);
     auto listed_point = [&](int i) {  // the i-th of all lists
         int q = 0;
 #pragma unroll
@@ -898,6 +901,7 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
         return a.list[(int64_t)q * a.list_cap + (i - sh_pre[q])];
     };
     if (a.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&a.stats->refined, (unsigned long long)n);
+    if ((int)blockIdx.x / S >= (int)gridDim.x / S) return;  // a remainder of the grid
     for (int first = (int)blockIdx.x / S * 32; first < n; first += (int)gridDim.x / S * 32) {
         const int np = min(32, n - first);
         __syncthreads();  // the previous group is written out
@@ -1255,8 +1259,9 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
                        (const T *)c.C, (T *)c.mindist, s);
     if (!p.resolve) return;
     const int64_t groups = ceil_div(c.N, 32);
-    const int64_t side = ceil_div(1024, r.splits);  // groups side by side
-    const dim3 grid((unsigned)((groups < side ? groups : side) * r.splits)), block(RS_THREADS);
+    // any share of a group among 1 .. splits workgroups divides the grid's work: see the kernel
+    const int64_t most = groups * r.splits;
+    const dim3 grid((unsigned)(most < 1024 ? most : 1024)), block(RS_THREADS);
 #define FTK_LAUNCH_RESOLVE(F)                                                                                        \
     hipLaunchKernelGGL((scan_resolve_kernel<T, F, L>), grid, block, (size_t)p.nb * form_pieces(F) * FRAG_UNITS * 16, \
                        st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, r)
@@ -1348,6 +1353,7 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     r.nb = p.nb;
     r.tiles = p.tiles;
     r.splits = p.splits < 16 ? p.splits : 16;
+    r.side = p.nb > 40 ? 256 : 512;  // the fragments of 32 points: one workgroup per compute unit beyond 80 KB
     r.labels = c.labels;
     r.list = b.list;
     r.list_count = b.list_count;
