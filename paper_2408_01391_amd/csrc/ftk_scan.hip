@@ -22,7 +22,7 @@
 // because short rows in many clusters have norms far above their distances and the wider band lists
 // too many of them (10^6 x 16 in a box of 200, K = 200: a tenth of the points).
 //
-// Both operands are multiplied by one power of two taken from two centroid rows, so that the scores
+// Both operands are multiplied by one power of two taken from four centroid rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
 // the same (overflow, NaN) is found by the settle pass, whose test such a point cannot pass.
 #include <cmath>
@@ -169,12 +169,14 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     __shared__ double sh_n[16][32];
     __shared__ T sh_m[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = (int)blockDim.x >> 6;
-    // the scale: the largest magnitude of rows 0 and K/2 goes to [1, 2)
+    // the scale: the largest magnitude of four rows goes to [1, 2)
     T m = T(0);
     for (int d = tid; d < D; d += blockDim.x) {
-        const T a = fabs(C[d]), b = fabs(C[(size_t)(K / 2) * D + d]);
-        m = a > m ? a : m;
-        m = b > m ? b : m;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const T a = fabs(C[(size_t)((int64_t)K * q / 4) * D + d]);
+            m = a > m ? a : m;
+        }
     }
 #pragma unroll
     for (int k = 32; k >= 1; k >>= 1) {
@@ -452,8 +454,7 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
 // ---- scan of longer rows --------------------------------------------------------------------------
 // A workgroup multiplies 256 points by 64 * CT centroids, 32 features at a time through LDS (double
 // buffered, up to 128 KB): the centroid fragments are copied from the image, the rows of X are split
-// on the way - requested two stages ahead, split and stored one stage ahead, in between the matrix
-// instructions.  Wave w takes point tiles 2(w%4) .. +1 and the centroid tiles of half w/4.  The
+// on the way - requested two stages ahead, split and stored one stage ahead.  Wave w takes point tiles 2(w%4) .. +1 and the centroid tiles of half w/4.  The
 // workgroups that share a block of points run side by side on one XCD, so that X comes from memory
 // once whatever K.
 template <typename T, int CT, bool RAG>
@@ -564,25 +565,20 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
         }
         store_half(min(st + 1, ns - 1), nxt, 0);
         store_half(min(st + 1, ns - 1), nxt, 1);
-        // reads two fragments ahead; the rows of the next stage, requested at the end of the last one,
-        // are split between the matrix instructions of the second block (all eight waves would
-        // otherwise do it at once, with the matrix pipes idle)
-        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+        // fp32: reads two fragments ahead of the matrix instructions, the split after them - the rows requested
+        // at the end of the last stage are then there, and the other wave of the SIMD fills its time.  (Spread
+        // between the second block's instructions it waited for the rows: 60000 x 1024, K = 1024 461 us a call
+        // against 437.)  fp64 rows take the registers the read-ahead needs: left to the compiler, 295 against 274
+        // at 10^5 x 256, K = 1024.
+        if constexpr (sizeof(T) == 4) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
-        for (int i = 0; i < 2 * CT; ++i) {
-            if (i + 1 == CT) __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-            else if (i + 1 < 2 * CT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            if (i < CT) {
+            for (int i = 0; i < 2 * CT; ++i) {
+                if (i + 1 == CT) __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+                else if (i + 1 < 2 * CT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
                 __builtin_amdgcn_sched_group_barrier(0x008, 3 * SC_PT, 0);
-            } else {
-#pragma unroll
-                for (int m = 0; m < 3 * SC_PT; ++m) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 20 / CT, 0);
-                }
             }
         }
-        __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
         request(min(st + 2, ns - 1));
         wait_loads<sizeof(T) == 4 ? 4 : 8>();  // the centroids have arrived; the rows requested above travel on
         __syncthreads();
@@ -902,8 +898,8 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     };
     if (a.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&a.stats->refined, (unsigned long long)n);
     if ((int)blockIdx.x / S >= (int)gridDim.x / S) return;  // a remainder of the grid
-    for (int first = (int)blockIdx.x / S * 32; first < n; first += (int)gridDim.x / S * 32) {
-        const int np = min(32, n - first);
+    for (int64_t at = (int64_t)((int)blockIdx.x / S) * 32; at < n; at += (int64_t)((int)gridDim.x / S) * 32) {
+        const int first = (int)at, np = min(32, n - first);
         __syncthreads();  // the previous group is written out
         if (tid < 32) {
             const ScanListed e = listed_point(first + min(tid, np - 1));
@@ -1143,6 +1139,8 @@ static int resident_blocks(int D)
 static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     if (D < 4 || K < 96) return false;
+    // the streaming scan leaves a record per point and 256 centroids: no more than four times the bytes of X
+    if (D > 128 && ceil_div(K, 256) * (int64_t)sizeof(ScanRecord) > 4 * (int64_t)D * (dtype == FTK_F32 ? 4 : 8)) return false;
     if (K >= 768) return true;
     if (dtype == FTK_F32) {
         if (D <= 8) return K >= 512;
