@@ -513,6 +513,9 @@ def main():
             "frac_whole_call": a["frac_mfma_call"] if mfma_bound else None,
             "call_ms": a["call_ms"],
             "frac_hbm_algorithmic": a["frac_hbm_kernel"],
+            "note": "2*N*D*K over the matrix peak of the data's type; with FT off the contraction may run as a "
+                    "scan on the bf16 matrix instructions (3 or 6 products a multiplication, kernel_ms = scan with its "
+                    "preparation and settlement), so the ratio can pass 1; the checksummed legs run the fp32 / fp64 kernels",
         },
         "configs": configs,
     }
