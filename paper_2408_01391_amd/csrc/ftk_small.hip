@@ -335,12 +335,11 @@ ftk_status launch_small_fit(ftk_dtype dtype, const void *X, int64_t N, int D, in
                             int32_t *labels, int32_t *counts, const double *absmax, double *inertia, double *partials,
                             void *scratch, hipStream_t st)
 {
-    const size_t cells = (size_t)K * D, esz = dtype == FTK_F32 ? 4 : 8;
+    const size_t cells = (size_t)K * D;
     const size_t table = align_up(2 * cells * 8 + (size_t)K * 4, 256);
     char *base = (char *)scratch;
     auto tab = [&](int t) { return reinterpret_cast<unsigned long long *>(base + (size_t)(t % 3) * table); };
     void *C_alt = base + 3 * table;
-    (void)esz;
     SmallArgs a = {};
     a.X = X;
     a.N = N;
