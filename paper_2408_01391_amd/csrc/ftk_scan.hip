@@ -1136,16 +1136,24 @@ static int resident_blocks(int D)
 //   fp64   K = 100   D = 64: N = 2 * 10^5 79 / 65, 2 * 10^4 23 / 32; D = 256: 2 * 10^5 251 / 276
 //          K = 256   D = 32: N = 2 * 10^4 25 / 26, 2 * 10^5 87 / 49; D = 256: 2 * 10^5 494 / 295
 //          K = 1024  D = 4: N = 2 * 10^4 34 / 25; D = 64: 2 * 10^5 518 / 131
+//          small N: 1400 x 447, K = 528 418 / 71; 5000 x 64, K = 256 34 / 30; 20000 x 32, K = 500 43 / 32, but
+//          20000 x 128, K = 256 55 / 59
+//   fp32 rows that are not whole 16-byte pieces, which the matrix kernel loads element by element:
+//          60000 x 867, K = 20 424 / 119; 60000 x 111, K = 8 35 / 33; 6000 x 337, K = 8 150 / 41;
+//          4 * 10^5 x 45, K = 50 70 / 52, but 60000 x 45, K = 20 21 / 24
 static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
-    if (D < 4 || K < 96) return false;
+    if (D < 4 || K < 8) return false;
     // the streaming scan leaves a record per point and 256 centroids: no more than four times the bytes of X
     if (D > 128 && ceil_div(K, 256) * (int64_t)sizeof(ScanRecord) > 4 * (int64_t)D * (dtype == FTK_F32 ? 4 : 8)) return false;
     if (K >= 768) return true;
+    if (dtype == FTK_F32 && D % 4 != 0 && (D >= 96 || (D > 16 && N >= 300000 && K >= 32))) return true;
+    if (K < 96) return false;
     if (dtype == FTK_F32) {
         if (D <= 8) return K >= 512;
         return K >= 256 || N >= 200000 || (K >= 192 && D >= 32) || D >= 128;
     }
+    if ((K >= 256 && D >= 64 && (D > 128 || N <= 5000)) || (K >= 384 && D >= 64) || (K >= 448 && D >= 32)) return true;
     return K >= 192 ? N >= 100000 : (N >= 200000 && D <= 96);
 }
 

@@ -55,6 +55,13 @@ def test_scan_matches_oracle_at_the_edges(N, D, K, dtype):
     check_direct(X, C, dtype)
 
 
+@pytest.mark.parametrize("N,D,K", [(700, 97, 8), (1001, 111, 33), (300, 337, 9), (513, 867, 20), (300001, 21, 32)])
+def test_scan_of_ragged_rows_with_few_centroids(N, D, K):
+    print("scan ragged", N, D, K, flush=True)
+    X, C = blobs(N + D + K, N, D, K, "f32")
+    check_direct(X, C, "f32")
+
+
 @pytest.mark.parametrize("dtype,scale", [("f32", 1e-15), ("f32", 1e15), ("f64", 1e-120), ("f64", 1e120), ("f64", 1e-25)])
 @pytest.mark.parametrize("D", [6, 48, 200])
 def test_scan_at_scales_far_from_one(D, dtype, scale):
