@@ -5,14 +5,14 @@
 // keeps the labels exact: the error bound below is certified and points whose best scores fall
 // inside it are settled by exact re-evaluation.
 //
-// Split: x ~ x0 + x1 with x0 = bf16(x), x1 = bf16(x - x0) - 16 significant bits, error at most
-// 2^-18 |x| (each piece rounds to nearest at 8 significant bits: 2^-9 of what it rounds) - and the same
-// for the centroids; all four piece products are kept,
-//     x.c ~ x0c0 + x0c1 + x1c0 + x1c1                (off by at most 2^-17 |x_d c_d| each feature).
+// Split: x ~ x0 + x1 with x0 = bf16(x), x1 = bf16(x - x0), and the same for the centroids.  A piece rounds
+// to nearest at 8 significant bits: off by up to 2^-8 of what it rounds, and by half a unit of its binade,
+// so |x - x0| <= 2^-8 |x| and |x - x0 - x1| <= 2^-17 |x|.  All four piece products are kept,
+//     x.c ~ x0c0 + x0c1 + x1c0 + x1c1                (off by at most 2^-16 |x_d c_d| each feature).
 // Why two pieces here and three for narrow rows: the rounding bound of the instructions themselves
 // grows with their number (7 u of the magnitude each, u = 2^-24), and at 128 features the
-// three-piece form (6 products per feature: 680 u) is certified no tighter than this
-// one (4 products: 720 u) while it needs half as many instructions again, LDS rows half as long
+// three-piece form (6 products per feature: 680 u) is certified only 1.4 times tighter than this
+// one (4 products: 968 u) while it needs half as many instructions again, LDS rows half as long
 // again (256 centroids of 128 features would no longer fit a compute unit), and half as many
 // point registers again.
 //
@@ -695,10 +695,10 @@ static double fw_ft_coef(int D)
 }
 static constexpr double FW_TRUNC_COEF = 1.001 * 15.0 / 65536.0;  // ||delta|| <= 2^-16 * 15 max ||c||
 
-// Scores closer than this cannot be ordered.  Two scores, each: both operands reduced to two pieces (2^-17 +
-// 2^-36 of the magnitude: 129 u; a budget of 512 u listed twice the points at 500000 x 64, K = 1000 in strict
-// mode), 4*nh instructions at 7 u, and 4 u for the fp32 evaluation of the magnitude itself.
-static double fw_band(int nh) { return 2.0 * (129.0 + 28.0 * nh + 4.0) * Mma<float>::kEps; }
+// Scores closer than this cannot be ordered.  Two scores, each: both operands reduced to two pieces (2^-17 of
+// the magnitude each: 256 u), 4*nh instructions at 7 u, and 4 u for the fp32 evaluation of the magnitude
+// itself.
+static double fw_band(int nh) { return 2.0 * (256.0 + 28.0 * nh + 4.0) * Mma<float>::kEps; }
 
 void plan_fast_wide(int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p)
 {
@@ -730,8 +730,8 @@ void plan_fast_wide(int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p)
     p.lds_bytes = (size_t)tpc * tile_bytes;
     p.ft_coef = fw_ft_coef(D);
     p.ft_trunc_coef = FT ? FW_TRUNC_COEF : 0.0;
-    // what ftk_fast_plan reports, an upper bound of fw_band(): it budgets 2^-15 of the magnitude for the
-    // reduction to two pieces
+    // what ftk_fast_plan reports, an upper bound of fw_band(): it budgets 2^-15 of the magnitude (512 u) for
+    // the reduction to two pieces
     p.band_coef = 2.0 * (512.0 + 28.0 * nh + 4.0) * Mma<float>::kEps;
 }
 

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2408_01391_amd import binding as ftk, synth
+from tests.bf16_operands import FIRST, adversarial
 from tests.gpu_util import DEV, check_assign, check_moved_labels_within_detection_threshold, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -231,3 +232,12 @@ def test_fast_nonfinite_points_do_not_disturb_the_others(D):
         lab, _, _ = _run(Xb, C, mode)
         assert lab.min() >= 0 and lab.max() < K
         assert np.array_equal(lab[keep], lab_clean[keep])
+
+
+@pytest.mark.parametrize("mode", [ftk.FT_OFF, ftk.FT_DETECT, ftk.FT_STRICT])
+@pytest.mark.parametrize("D", [36, 48, 64, 128])
+def test_worst_operands_of_two_pieces_are_settled(D, mode):
+    # more candidates than the kernel compares by itself, in fp32: those are settled in double
+    X, C = adversarial(D, 200, 1 / 64, four_products=True, copies=(61, 91, 121, 151))
+    labels, _, _ = _run(X, C, mode)
+    assert np.all(labels == FIRST)
