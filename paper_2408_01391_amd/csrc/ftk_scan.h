@@ -18,7 +18,6 @@ struct ScanPlan {
     int64_t pblocks;    // blocks of 256 points
     int64_t rec_reserve;  // records to reserve
     bool resolve;       // listed points are settled by the scan's own third pass (else refine_kernel)
-    double band_coef;   // scores closer than band_coef * B cannot be ordered by the scan
 };
 
 // what the scan leaves of a point: its best score and centroid, the second-best score
@@ -36,7 +35,7 @@ struct ScanListed {
 struct ScanBuffers {
     uint4 *image;       // [tiles_pad][nb][2][64] centroid pieces in fragment order
     float *start;       // [tiles_pad][32] accumulator start values -||c||^2/2 (scaled), fragment order
-    float *tile_max;    // [tiles_pad] largest ||c||^2 (scaled) of a tile
+    float4 *tile_stat;  // [tiles_pad] largest ||c||^2 (scaled), ||c1||^2 / ||c||^2, ||r_c||^2 / ||c||^2 of a tile
     double *scale;      // [1] the power of two both operands are multiplied by
     ScanRecord *rec;    // [splits][N]
     ScanListed *list;   // points to resolve: lists of equal capacity ...

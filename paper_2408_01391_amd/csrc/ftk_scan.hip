@@ -13,14 +13,20 @@
 // ties, distances direct - while the contraction runs on hardware that does 16 (fp32) or 32 (fp64)
 // times as many multiplications a second.
 //
-// Error of a score, in units of u = 2^-24 times B = ||x|| max||c|| + max||c||^2 / 2.  A value is
-// x = x0 + x1 + r with x0 = bf16(x), x1 = bf16(x - x0): |x1| <= 2^-9 |x|, |r| <= 2^-18 |x|, the same
-// for c.  Kept are x0c0 + x0c1 + x1c0; lost are x1c1, r.c and x.r', 2^-18 each: 3 * 64 u = 192 u.  An
-// instruction rounds to within 7 u of what it adds up (measured, pinned by a test): 21 u per block of
-// 16 features.  Rows of up to 8 features leave half of a block empty, which holds the three-piece
-// form (six products, error 2 u) in the same three instructions; rows of up to 16 take that form in six,
-// because short rows in many clusters have norms far above their distances and the wider band lists
-// too many of them (10^6 x 16 in a box of 200, K = 200: a tenth of the points).
+// Error of a score.  A value is x = x0 + x1 + r with x0 = bf16(x), x1 = bf16(x - x0), the same for c.  A
+// piece rounds to nearest at 8 significant bits: |x1| up to 2^-8 |x|, |r| up to 2^-17 |x|.  Kept are
+// x0c0 + x0c1 + x1c0; lost are x1c1, r.c and x.r', by Cauchy-Schwarz at most
+//     ||x1|| ||c1|| + ||r_x|| ||c|| + ||x|| ||r_c||.
+// That is up to 512 u of ||x|| ||c|| (u = 2^-24) where every feature sits at a midpoint of the rounding.  The
+// largest ratios ||c1|| / ||c|| and ||r_c|| / ||c|| are measured by the preparation, which leaves 280 u on data at
+// large.  (Norms of the points' pieces measured by the settle pass as well would leave 130 u, but cost it more
+// than the points they save: 300007 x 45, K = 333 70.8 us a call against 66, 2^18 x 128, K = 256 103 against 97.)
+// An instruction rounds to within 7 u of what it adds up (measured, pinned by a test), at most
+// ||x|| ||c|| + ||c||^2 / 2: 21 u per block of 16 features.  Rows of up to 8 features leave half of a block
+// empty, which holds the three-piece form (six products; 24 bits in three pieces, what is lost is 2 u) in
+// the same three instructions; rows of up to 16 take that form in six, because short rows in many clusters
+// have norms far above their distances and the wider band lists too many of them (10^6 x 16 in a box of
+// 200, K = 200: a tenth of the points).
 //
 // Both operands are multiplied by one power of two taken from four centroid rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
@@ -103,6 +109,15 @@ __device__ __forceinline__ void split_triple(const float (&v)[8], uint4 &a, uint
     c = __builtin_bit_cast(uint4, p2);
 }
 
+// squared norms of what two pieces leave of a value: the second piece, and what neither holds
+__device__ __forceinline__ void add_lost(float v, float &n1, float &nr)
+{
+    const float d = v - (float)(__bf16)v;
+    const float p = (float)(__bf16)d, r = d - p;
+    n1 = fmaf(p, p, n1);
+    nr = fmaf(r, r, nr);
+}
+
 __device__ __forceinline__ uint4 select_units(bool c, const uint4 &a, const uint4 &b)
 {
     return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
@@ -164,9 +179,10 @@ struct RowReader {
 // 16b + 8(l/32) of block b (FORM_OCTET: all 8 features).
 template <typename T, int FORM>
 __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
-                                                              float *tile_max, double *scale, int32_t *list_count, int lists)
+                                                              float4 *tile_stat, double *scale, int32_t *list_count, int lists)
 {
     __shared__ double sh_n[16][32];
+    __shared__ float sh_n1[16][32], sh_nr[16][32];  // squared norms of the second pieces and of the residuals
     __shared__ T sh_m[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = (int)blockDim.x >> 6;
     // the scale: the largest magnitude of four rows goes to [1, 2)
@@ -199,6 +215,7 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     const T *c = C + (size_t)(j < K ? j : 0) * D;
     const RowReader<T, true> reader(c, D);
     double n = 0.0;
+    float n1 = 0.f, nr = 0.f;
 #pragma unroll 2
     for (int b = wave; b < nb; b += nw) {
         const int f0 = FORM == FORM_OCTET ? 0 : 16 * b + 8 * g;
@@ -228,24 +245,42 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
             split_pair(v, a0, a1);
             dst[0] = a0;
             dst[FRAG_UNITS] = a1;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) add_lost(v[e], n1, nr);
         }
     }
     if (FORM != FORM_OCTET) n += __shfl_xor(n, 32, 64);
-    if (lane < 32) sh_n[wave][lane] = n;
+    if (FORM == FORM_PAIR) {
+        n1 += __shfl_xor(n1, 32, 64);
+        nr += __shfl_xor(nr, 32, 64);
+    }
+    if (lane < 32) {
+        sh_n[wave][lane] = n;
+        sh_n1[wave][lane] = n1;
+        sh_nr[wave][lane] = nr;
+    }
     __syncthreads();
     if (tid < 32) {
         n = 0.0;
-        for (int i = 0; i < nw; ++i) n += sh_n[i][tid];
+        n1 = nr = 0.f;
+        for (int i = 0; i < nw; ++i) {
+            n += sh_n[i][tid];
+            n1 += sh_n1[i][tid];
+            nr += sh_nr[i][tid];
+        }
         // register r of lane group gg reads row 8(r/4) + 4gg + r%4
         const int gg = (tid >> 2) & 1, r = 4 * (tid >> 3) + (tid & 3);
         start[tile * 32 + gg * 16 + r] = 32 * tile + tid < K ? (float)(-0.5 * n) : -__builtin_huge_valf();
-        float f = (float)n;
+        // (a NaN row never wins and does not count)
+        float f = n > 0.0 ? (float)n : 0.f;
+        float q1 = n > 0.0 ? (float)((double)n1 / n) : 0.f, qr = n > 0.0 ? (float)((double)nr / n) : 0.f;
 #pragma unroll
         for (int k = 16; k >= 1; k >>= 1) {
-            const float o = __shfl_xor(f, k, 64);
-            f = o > f ? o : f;  // a NaN row never wins and does not count
+            f = fmaxf(f, __shfl_xor(f, k, 64));
+            q1 = fmaxf(q1, __shfl_xor(q1, k, 64));
+            qr = fmaxf(qr, __shfl_xor(qr, k, 64));
         }
-        if (tid == 0) tile_max[tile] = f > 0.f ? f : 0.f;  // tid 0 may hold a NaN of its own
+        if (tid == 0) tile_stat[tile] = make_float4(f, q1, qr, 0.f);
     }
 }
 
@@ -651,12 +686,13 @@ __device__ __forceinline__ V group_sum(V v)
 struct SettleArgs {
     ScanRecord *rec;
     int splits;
-    const float *tile_max;
+    const float4 *tile_stat;
     int tiles;
     const double *scale;
     int64_t N;
     int D, K;
-    float band;
+    float psi, lost;    // rounding of a score; what is lost of ||x|| ||c|| whatever the centroids
+    float slack, tiny;  // of the measured norms: their own rounding, and what underflow takes from them
     int32_t *labels;
     ScanListed *list;  // (point, score a candidate needs), or NULL: the points alone go to wl
     int32_t *wl, *list_count;
@@ -669,7 +705,7 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
 {
     constexpr int ROWS = settle_rows(sizeof(T));
     constexpr int RPB = 256 / L;  // rows side by side
-    __shared__ float sh_max[4];
+    __shared__ float sh_max[4][3];
     __shared__ int sh_n, sh_base;
     __shared__ int32_t sh_lab[RPB * ROWS];   // ~label for listed points
     __shared__ T sh_dist[RPB * ROWS];
@@ -699,14 +735,25 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
     if (tid == 0) sh_n = 0;
     const int64_t i0 = (int64_t)blockIdx.x * 256 + tid;
     if (i0 * 32 < a.N) a.tickets[i0] = 0;
-    float cm = 0.f;
-    for (int i = tid; i < a.tiles; i += 256) cm = fmaxf(cm, a.tile_max[i]);
+    float cm[3] = {0.f, 0.f, 0.f};
+    for (int i = tid; i < a.tiles; i += 256) {
+        const float4 t = a.tile_stat[i];
+        cm[0] = fmaxf(cm[0], t.x);
+        cm[1] = fmaxf(cm[1], t.y);
+        cm[2] = fmaxf(cm[2], t.z);
+    }
 #pragma unroll
-    for (int k = 32; k >= 1; k >>= 1) cm = fmaxf(cm, __shfl_xor(cm, k, 64));
-    if (lane == 0) sh_max[tid >> 6] = cm;
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int k = 32; k >= 1; k >>= 1) cm[q] = fmaxf(cm[q], __shfl_xor(cm[q], k, 64));
+        if (lane == 0) sh_max[tid >> 6][q] = cm[q];
+    }
     __syncthreads();
-    const float cmax2 = 1.000001f * fmaxf(fmaxf(sh_max[0], sh_max[1]), fmaxf(sh_max[2], sh_max[3]));
-    const float cmax = sqrtf(cmax2);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) cm[q] = fmaxf(fmaxf(sh_max[0][q], sh_max[1][q]), fmaxf(sh_max[2][q], sh_max[3][q]));
+    const float cmax = 1.000001f * sqrtf(cm[0]) + a.tiny;
+    // a score of centroid c is off by at most per_x ||x|| ||c|| + psi ||c||^2 / 2; ||x1|| <= 2^-8 ||x||
+    const float per_x = a.psi + a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
     const T s = (T)a.scale[0];
     for (int k = 1; k < a.splits; ++k) {
 #pragma unroll
@@ -752,9 +799,8 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         const T dist = group_sum<L>(d[u]);
-        const float norm = group_sum<L>(xn[u]);
-        // 1.0001: the rounding of the norm itself
-        const float bound = a.band * (sqrtf(norm) * 1.0001f * cmax + 0.5f * cmax2) + SCAN_FLOOR;
+        const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + a.tiny;
+        const float bound = 1.00001f * (2.f * per_x * norm + a.psi * cmax) * cmax + SCAN_FLOOR;
         const bool listed = !(m1[u] - m2[u] > bound);
         if (sub == 0) {
             sh_lab[u * RPB + grp] = listed ? ~j[u] : j[u];
@@ -1201,9 +1247,6 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     p.rec_reserve = (int64_t)p.splits * N;
     if (p.rec_reserve < SCAN_FILL * SC_POINTS + N + SC_POINTS) p.rec_reserve = SCAN_FILL * SC_POINTS + N + SC_POINTS;
     if (p.rec_reserve > (int64_t)p.tiles * N) p.rec_reserve = (int64_t)p.tiles * N;
-    const double u = Mma<float>::kEps;
-    p.band_coef = 2.0 * ((p.form == FORM_PAIR ? 196.0 : 4.0) + (p.form == FORM_TRIPLE ? 42.0 : 21.0) * p.nb +
-                         (dtype == FTK_F64 ? 2.0 : 0.0)) * u;
     return p;
 }
 
@@ -1222,7 +1265,7 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
     const size_t tiles = p.stream ? (size_t)p.tiles + 8 : (size_t)p.tiles_pad;
     b.image = (uint4 *)take(tiles * p.nb * form_frags(p.form) * FRAG_UNITS * 16);
     b.start = (float *)take((tiles + 1) * 32 * 4);  // copied two tiles a time
-    b.tile_max = (float *)take(tiles * 4);
+    b.tile_stat = (float4 *)take(tiles * sizeof(float4));
     b.scale = (double *)take(8);
     b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
     b.list_count = (int32_t *)take((size_t)SCAN_LISTS * LIST_STRIDE * 4);
@@ -1293,7 +1336,7 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     const int lists = p.resolve ? SCAN_LISTS : 1;
 #define FTK_LAUNCH_CENTROIDS(F)                                                                                       \
     hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start, \
-                       b.tile_max, b.scale, counts, lists)
+                       b.tile_stat, b.scale, counts, lists)
     if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
     else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE);
     else FTK_LAUNCH_CENTROIDS(FORM_PAIR);
@@ -1335,13 +1378,18 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     SettleArgs s;
     s.rec = b.rec;
     s.splits = p.splits;
-    s.tile_max = b.tile_max;
+    s.tile_stat = b.tile_stat;
     s.tiles = p.tiles_pad;
     s.scale = b.scale;
     s.N = c.N;
     s.D = c.D;
     s.K = c.K;
-    s.band = (float)p.band_coef;
+    // instructions; 4 u for the start value, the comparison and the bound itself; 2 u for operands rounded to fp32
+    const double u = Mma<float>::kEps;
+    s.psi = (float)(((p.form == FORM_TRIPLE ? 42.0 : 21.0) * 1.01 * p.nb + 6.0) * u);  // 1.01: pieces add up to more than the value
+    s.lost = (float)(p.form == FORM_PAIR ? 128.0 * u : 2.0 * u);  // ||r_x|| <= 2^-17 ||x||; three pieces hold 24 bits
+    s.slack = (float)(1.0001 + c.D * u);
+    s.tiny = (float)(std::sqrt((double)c.D) * 0x1p-73);  // squares below 2^-149 are lost
     s.labels = c.labels;
     s.tickets = b.tickets;
     s.list = p.resolve ? b.list : nullptr;

@@ -1,0 +1,45 @@
+"""The error bounds of the unprotected scan, on operands that reach them and on data that stretches
+them: labels are the exact arg-min, whatever two bf16 pieces lose, overflow or leave out of proportion."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2408_01391_amd import binding as ftk
+from tests.bf16_operands import FIRST, adversarial
+from tests.gpu_util import check_assign, to_dev
+
+pytestmark = pytest.mark.gpu
+
+NP = {"f32": np.float32, "f64": np.float64}
+
+
+def run(X, C, **kw):
+    labels, mind = ftk.kmeans_assign(to_dev(X), to_dev(C), **kw)
+    torch.cuda.synchronize()
+    return labels.cpu().numpy(), mind.cpu().numpy()
+
+
+@pytest.mark.parametrize("moved", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("D", [20, 32, 33, 64, 100, 128, 160])
+def test_worst_operands_of_two_pieces_are_settled(D, dtype, moved):
+    print("scan bound", D, dtype, moved, flush=True)
+    X, C = adversarial(D, 800, 1 / 32, moved=moved)
+    labels, _ = run(X.astype(NP[dtype]), C.astype(NP[dtype]))
+    assert np.all(labels == FIRST)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("D,nudge", [(20, 0.001), (32, 0.008), (32, 0.001), (64, 0.001), (128, 0.001)])
+def test_points_next_to_a_centroid_with_all_features_at_a_midpoint(D, nudge, dtype):
+    """Distances far below the norms: the wrong centroid is thousands of times farther."""
+    K = 800
+    X = np.full((64, D), 1 + 2.0 ** -8 - 2.0 ** -16, NP[dtype])
+    C = np.zeros((K, D), NP[dtype])
+    C[K // 2:] = -1
+    C[5] = 1 + 2.0 ** -8 - (2.0 ** -17 + 2.0 ** -22)
+    C[9] = 1 + 2.0 ** -8 + (2.0 ** -17 + 2.0 ** -22)
+    C[9, 0] += nudge
+    labels, mind = run(X, C)
+    check_assign(X, C, labels, mind)
+    assert np.all(labels == 5)
