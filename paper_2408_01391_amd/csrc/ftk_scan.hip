@@ -30,7 +30,7 @@
 //
 // Both operands are multiplied by one power of two taken from four centroid rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
-// the same (overflow, NaN) is found by the settle pass, whose test such a point cannot pass.
+// the same (overflow, NaN) is found by the settle pass, and such a point is compared with every centroid.
 #include <cmath>
 
 #include "ftk_internal.h"
@@ -801,11 +801,14 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
         const T dist = group_sum<L>(d[u]);
         const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + a.tiny;
         const float bound = 1.00001f * (2.f * per_x * norm + a.psi * cmax) * cmax + SCAN_FLOOR;
-        const bool listed = !(m1[u] - m2[u] > bound);
+        // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on
+        // the way to a sum that is not): a threshold that is not a number makes every centroid a candidate.
+        const bool sound = (norm + cmax) * cmax < 1e38f;
+        const bool listed = !sound || !(m1[u] - m2[u] > bound);
         if (sub == 0) {
             sh_lab[u * RPB + grp] = listed ? ~j[u] : j[u];
             sh_dist[u * RPB + grp] = dist;
-            sh_thr[u * RPB + grp] = m1[u] - bound;
+            sh_thr[u * RPB + grp] = sound ? m1[u] - bound : __builtin_nanf("");
         }
     }
     __syncthreads();

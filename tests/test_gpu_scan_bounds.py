@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import cpu as oracle
 from paper_2408_01391_amd import binding as ftk
 from tests.bf16_operands import FIRST, adversarial
 from tests.gpu_util import check_assign, to_dev
@@ -43,3 +44,19 @@ def test_points_next_to_a_centroid_with_all_features_at_a_midpoint(D, nudge, dty
     labels, mind = run(X, C)
     check_assign(X, C, labels, mind)
     assert np.all(labels == 5)
+
+
+@pytest.mark.parametrize("D,K,dtype", [(97, 8, "f32"), (97, 800, "f32"), (40, 768, "f64"), (12, 800, "f32"), (200, 800, "f64")])
+def test_centroids_of_mixed_magnitude_meet_every_candidate(D, K, dtype):
+    """Rows whose scaled norms overflow fp32 beside rows that look tiny: no score may be trusted, and the
+    few that are numbers are not all there is."""
+    rng = np.random.default_rng(D)
+    C = rng.normal(size=(K, D)) * 1e-10
+    big = np.arange(K) % 8 if K > 8 else np.arange(K) % 2
+    C[big % 2 == 1] *= 1e20 if dtype == "f32" else 1e35
+    X = np.concatenate([1.01 * C[1:2], 0.99 * C[3:4], C[2:3], 1.5 * C[5:6]])
+    X, C = X.astype(NP[dtype]), C.astype(NP[dtype])
+    labels, mind = run(X, C)
+    ref = oracle.assign(X, C)
+    assert np.array_equal(labels, ref[0])
+    assert np.allclose(mind, ref[1], rtol=1e-5)
