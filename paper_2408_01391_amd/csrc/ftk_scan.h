@@ -34,9 +34,9 @@ struct ScanListed {
 
 struct ScanBuffers {
     uint4 *image;       // [tiles_pad][nb][2][64] centroid pieces in fragment order
-    float *start;       // [tiles_pad][32] accumulator start values -||c||^2/2 (scaled), fragment order
+    float *start;       // [tiles_pad][32] accumulator start values -||c||^2/2 - r.c (c less the reference r, scaled), fragment order
     float4 *tile_stat;  // [tiles_pad] largest ||c||^2 (scaled), ||c1||^2 / ||c||^2, ||r_c||^2 / ||c||^2 of a tile
-    double *scale;      // [1] the power of two both operands are multiplied by
+    double *scale;      // [2] the power of two both operands are multiplied by; length of the (scaled) reference
     ScanRecord *rec;    // [splits][N]
     ScanListed *list;   // points to resolve: lists of equal capacity ...
     int32_t *list_count;  // ... and a counter each

@@ -28,7 +28,16 @@
 // have norms far above their distances and the wider band lists too many of them (10^6 x 16 in a box of
 // 200, K = 200: a tenth of the points).
 //
-// Both operands are multiplied by one power of two taken from four centroid rows, so that the scores
+// All of this is in proportion to ||x|| ||c||, the distances are not: of data far from the origin every
+// point would have to be settled (2^18 x 32 at 1000, spread 5, K = 1024: 6.2 ms, against 88 us at the origin).
+// Distances do not change when everything moves, so a vector r, the trimmed mean of eight centroid rows, is
+// taken off the centroids (in the data's type, before the split) where these rows say that it shortens them:
+//     x.c - ||c||^2 / 2 = x.(c - r) - (r.(c - r) + ||c - r||^2 / 2) + a term without c,
+// and the start value makes up for it.  The bound is then in proportion to (||x|| + ||r||) ||c - r||.  (Taken off
+// the points as well it would be ||x - r|| ||c - r||, but their share of it costs the streaming scan 3 (fp32) to
+// 20 % (fp64) on any data, and matters for offsets of more than about 10^4 spreads only.)
+//
+// Both operands are multiplied by one power of two taken from the same rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
 // the same (overflow, NaN) is found by the settle pass, and such a point is compared with every centroid.
 #include <cmath>
@@ -176,45 +185,102 @@ struct RowReader {
 
 // ---- centroids: pieces in fragment order, start values, norms --------------------------------
 // One workgroup per tile of 32 centroids; lane l of a fragment supplies row l % 32 and the 8 features
-// 16b + 8(l/32) of block b (FORM_OCTET: all 8 features).
+// 16b + 8(l/32) of block b (FORM_OCTET: all 8 features).  Each of them forms the reference r and the scale for
+// itself, from the same rows by the same instructions; r stays in LDS (REF_BYTES; longer rows go without).
+constexpr int REF_ROWS = 8;
+constexpr size_t REF_BYTES = 64 * 1024;
 template <typename T, int FORM>
 __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
-                                                              float4 *tile_stat, double *scale, int32_t *list_count, int lists)
+                                                              float4 *tile_stat, double *scale, int32_t *list_count, int lists,
+                                                              int has_ref)
 {
-    __shared__ double sh_n[16][32];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    T *const ref = reinterpret_cast<T *>(lds_raw);  // [16 nb]
+    __shared__ double sh_n[16][32], sh_rc[16][32];
     __shared__ float sh_n1[16][32], sh_nr[16][32];  // squared norms of the second pieces and of the residuals
-    __shared__ T sh_m[16];
+    __shared__ T sh_m[16][2];
+    __shared__ double sh_s[16][3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = (int)blockDim.x >> 6;
-    // the scale: the largest magnitude of four rows goes to [1, 2)
-    T m = T(0);
+    T m = T(0), whole = T(0);  // largest magnitude of the rows less the reference, and of the rows
+    double off = 0.0, square = 0.0, rr = 0.0;  // their sums of squares without each feature's largest, and ||r||^2
     for (int d = tid; d < D; d += blockDim.x) {
+        T c[REF_ROWS], sum = T(0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const T a = fabs(C[(size_t)((int64_t)K * q / 4) * D + d]);
-            m = a > m ? a : m;
+        for (int q = 0; q < REF_ROWS; ++q) c[q] = C[(size_t)((int64_t)K * q / REF_ROWS) * D + d];
+        // without the smallest and the largest, so that one far centroid does not move it
+        T lo = c[0], hi = c[0];
+#pragma unroll
+        for (int q = 0; q < REF_ROWS; ++q) {
+            sum += c[q] * T(1.0 / REF_ROWS);
+            lo = c[q] < lo ? c[q] : lo;
+            hi = c[q] > hi ? c[q] : hi;
         }
+        T r = ((sum - lo * T(1.0 / REF_ROWS)) - hi * T(1.0 / REF_ROWS)) * T((double)REF_ROWS / (REF_ROWS - 2));
+        if (!(fabs(r) < Mma<T>::huge())) r = T(0);
+        T md = T(0), wd = T(0);
+#pragma unroll
+        for (int q = 0; q < REF_ROWS; ++q) {
+            const T a = fabs(c[q] - r), w = fabs(c[q]);
+            md = a > md ? a : md;
+            wd = w > wd ? w : wd;
+            off = fma((double)a, (double)a, off);
+            square = fma((double)w, (double)w, square);
+        }
+        off = fma(-(double)md, (double)md, off);
+        square = fma(-(double)wd, (double)wd, square);
+        rr = fma((double)r, (double)r, rr);
+        m = md > m ? md : m;
+        whole = wd > whole ? wd : whole;
+        if (has_ref) ref[d] = r;
     }
+    if (has_ref)
+        for (int d = D + tid; d < 16 * nb; d += blockDim.x) ref[d] = T(0);
 #pragma unroll
     for (int k = 32; k >= 1; k >>= 1) {
-        const T o = __shfl_xor(m, k, 64);
+        const T o = __shfl_xor(m, k, 64), w = __shfl_xor(whole, k, 64);
         m = o > m ? o : m;
+        whole = w > whole ? w : whole;
+        off += __shfl_xor(off, k, 64);
+        square += __shfl_xor(square, k, 64);
+        rr += __shfl_xor(rr, k, 64);
     }
-    if (lane == 0) sh_m[wave] = m;
+    if (lane == 0) {
+        sh_m[wave][0] = m;
+        sh_m[wave][1] = whole;
+        sh_s[wave][0] = off;
+        sh_s[wave][1] = square;
+        sh_s[wave][2] = rr;
+    }
     __syncthreads();
-    for (int i = 0; i < nw; ++i) m = sh_m[i] > m ? sh_m[i] : m;
+    off = square = rr = 0.0;
+    for (int i = 0; i < nw; ++i) {
+        m = sh_m[i][0] > m ? sh_m[i][0] : m;
+        whole = sh_m[i][1] > whole ? sh_m[i][1] : whole;
+        off += sh_s[i][0];
+        square += sh_s[i][1];
+        rr += sh_s[i][2];
+    }
+    // The reference is taken where it halves the squared norms at least: of data about the origin it is
+    // a random vector.  The scale: the largest magnitude goes to [1, 2) - that of the rows themselves where
+    // they are all the same.
+    const bool moved = has_ref && off < 0.5 * square;
+    if (!moved || !(m > T(0))) m = whole;
     int e2 = 0;
     if (m > T(0) && m < Mma<T>::huge()) e2 = ilogb(m);
     constexpr int E2 = sizeof(T) == 4 ? 100 : 1000;
     e2 = e2 > E2 ? E2 : (e2 < -E2 ? -E2 : e2);
     const T s = (T)ldexp(1.0, -e2);
-    if (blockIdx.x == 0 && tid == 0) scale[0] = (double)s;
+    if (blockIdx.x == 0 && tid == 0) {
+        scale[0] = (double)s;
+        scale[1] = moved ? sqrt(rr) * (double)s : 0.0;
+    }
     if (blockIdx.x == 0 && tid < lists) list_count[tid * LIST_STRIDE] = 0;
     const int tile = blockIdx.x;
     const int row = lane & 31, g = lane >> 5;
     const int j = 32 * tile + row;
     const T *c = C + (size_t)(j < K ? j : 0) * D;
     const RowReader<T, true> reader(c, D);
-    double n = 0.0;
+    double n = 0.0, rc = 0.0;
     float n1 = 0.f, nr = 0.f;
 #pragma unroll 2
     for (int b = wave; b < nb; b += nw) {
@@ -224,8 +290,10 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const T w = j < K ? (e < 4 ? k0.v[e & 3] : k1.v[e & 3]) * s : T(0);
+            const T r = moved ? ref[f0 + e] : T(0);
+            const T w = j < K ? ((e < 4 ? k0.v[e & 3] : k1.v[e & 3]) - r) * s : T(0);
             n = fma((double)w, (double)w, n);
+            rc = fma((double)w, (double)r, rc);
             v[e] = (float)w;
         }
         uint4 *dst = image + ((size_t)tile * nb + b) * (form_frags(FORM) * FRAG_UNITS) + lane;
@@ -249,28 +317,33 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
             for (int e = 0; e < 8; ++e) add_lost(v[e], n1, nr);
         }
     }
-    if (FORM != FORM_OCTET) n += __shfl_xor(n, 32, 64);
+    if (FORM != FORM_OCTET) {
+        n += __shfl_xor(n, 32, 64);
+        rc += __shfl_xor(rc, 32, 64);
+    }
     if (FORM == FORM_PAIR) {
         n1 += __shfl_xor(n1, 32, 64);
         nr += __shfl_xor(nr, 32, 64);
     }
     if (lane < 32) {
         sh_n[wave][lane] = n;
+        sh_rc[wave][lane] = rc;
         sh_n1[wave][lane] = n1;
         sh_nr[wave][lane] = nr;
     }
     __syncthreads();
     if (tid < 32) {
-        n = 0.0;
+        n = rc = 0.0;
         n1 = nr = 0.f;
         for (int i = 0; i < nw; ++i) {
             n += sh_n[i][tid];
+            rc += sh_rc[i][tid];
             n1 += sh_n1[i][tid];
             nr += sh_nr[i][tid];
         }
         // register r of lane group gg reads row 8(r/4) + 4gg + r%4
         const int gg = (tid >> 2) & 1, r = 4 * (tid >> 3) + (tid & 3);
-        start[tile * 32 + gg * 16 + r] = 32 * tile + tid < K ? (float)(-0.5 * n) : -__builtin_huge_valf();
+        start[tile * 32 + gg * 16 + r] = 32 * tile + tid < K ? (float)(-0.5 * n - rc * (double)s) : -__builtin_huge_valf();
         // (a NaN row never wins and does not count)
         float f = n > 0.0 ? (float)n : 0.f;
         float q1 = n > 0.0 ? (float)((double)n1 / n) : 0.f, qr = n > 0.0 ? (float)((double)nr / n) : 0.f;
@@ -752,9 +825,10 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
 #pragma unroll
     for (int q = 0; q < 3; ++q) cm[q] = fmaxf(fmaxf(sh_max[0][q], sh_max[1][q]), fmaxf(sh_max[2][q], sh_max[3][q]));
     const float cmax = 1.000001f * sqrtf(cm[0]) + a.tiny;
-    // a score of centroid c is off by at most per_x ||x|| ||c|| + psi ||c||^2 / 2; ||x1|| <= 2^-8 ||x||
-    const float per_x = a.psi + a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
+    // a score of centroid c is off by at most (lost ||x|| + psi (||x|| + ||r||)) ||c|| + psi ||c||^2 / 2; ||x1|| <= 2^-8 ||x||
+    const float lost = a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
     const T s = (T)a.scale[0];
+    const float ref = 1.000001f * (float)a.scale[1] + a.tiny;  // ||r||
     for (int k = 1; k < a.splits; ++k) {
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
@@ -800,10 +874,11 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
     for (int u = 0; u < ROWS; ++u) {
         const T dist = group_sum<L>(d[u]);
         const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + a.tiny;
-        const float bound = 1.00001f * (2.f * per_x * norm + a.psi * cmax) * cmax + SCAN_FLOOR;
+        const float per_c = lost * norm + a.psi * (norm + ref);
+        const float bound = 1.00001f * (2.f * per_c + a.psi * cmax) * cmax + SCAN_FLOOR;
         // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on
         // the way to a sum that is not): a threshold that is not a number makes every centroid a candidate.
-        const bool sound = (norm + cmax) * cmax < 1e38f;
+        const bool sound = (norm + ref + cmax) * cmax < 1e38f;
         const bool listed = !sound || !(m1[u] - m2[u] > bound);
         if (sub == 0) {
             sh_lab[u * RPB + grp] = listed ? ~j[u] : j[u];
@@ -1269,7 +1344,7 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
     b.image = (uint4 *)take(tiles * p.nb * form_frags(p.form) * FRAG_UNITS * 16);
     b.start = (float *)take((tiles + 1) * 32 * 4);  // copied two tiles a time
     b.tile_stat = (float4 *)take(tiles * sizeof(float4));
-    b.scale = (double *)take(8);
+    b.scale = (double *)take(16);
     b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
     b.list_count = (int32_t *)take((size_t)SCAN_LISTS * LIST_STRIDE * 4);
     b.list = (ScanListed *)take(((size_t)N + SCAN_LISTS * SETTLE_ROWS_MAX) * sizeof(ScanListed));
@@ -1337,9 +1412,11 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     // a contiguous list where refine_kernel takes it over
     int32_t *const counts = p.resolve ? b.list_count : w.wl_count;
     const int lists = p.resolve ? SCAN_LISTS : 1;
+    const size_t ref_bytes = (size_t)p.nb * 16 * sizeof(T);
+    const bool has_ref = ref_bytes <= REF_BYTES;
 #define FTK_LAUNCH_CENTROIDS(F)                                                                                       \
-    hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, 0, st, (const T *)c.C, c.D, c.K, p.nb, b.image, b.start, \
-                       b.tile_stat, b.scale, counts, lists)
+    hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, has_ref ? ref_bytes : 0, st, (const T *)c.C, c.D, c.K, p.nb, \
+                       b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref)
     if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
     else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE);
     else FTK_LAUNCH_CENTROIDS(FORM_PAIR);
@@ -1387,7 +1464,7 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     s.N = c.N;
     s.D = c.D;
     s.K = c.K;
-    // instructions; 4 u for the start value, the comparison and the bound itself; 2 u for operands rounded to fp32
+    // instructions; 4 u for the start value, the comparison and the bound itself; 2 u for the rounding of the two operands
     const double u = Mma<float>::kEps;
     s.psi = (float)(((p.form == FORM_TRIPLE ? 42.0 : 21.0) * 1.01 * p.nb + 6.0) * u);  // 1.01: pieces add up to more than the value
     s.lost = (float)(p.form == FORM_PAIR ? 128.0 * u : 2.0 * u);  // ||r_x|| <= 2^-17 ||x||; three pieces hold 24 bits

@@ -60,3 +60,29 @@ def test_centroids_of_mixed_magnitude_meet_every_candidate(D, K, dtype):
     ref = oracle.assign(X, C)
     assert np.array_equal(labels, ref[0])
     assert np.allclose(mind, ref[1], rtol=1e-5)
+
+
+def offset_blobs(seed, N, D, K, offset, dtype):
+    rng = np.random.default_rng(seed)
+    C = rng.normal(size=(K, D)) * 5
+    X = C[rng.integers(0, K, N)] + rng.normal(size=(N, D))
+    return (X + offset).astype(NP[dtype]), (C + offset).astype(NP[dtype])
+
+
+def refined(X, C):
+    stats = ftk.new_stats("cuda:0")
+    labels, mind = run(X, C, stats=stats)
+    check_assign(X, C, labels, mind)
+    return ftk.stats_dict(stats)["refined"]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("D", [8, 16, 32, 128, 200])
+def test_an_offset_of_all_data_lists_no_more_points(D, dtype):
+    """Distances do not change when everything moves, so neither may what cannot be decided."""
+    N, K = 20000, 1024
+    at_origin = refined(*offset_blobs(D, N, D, K, 0.0, dtype))
+    for offset in (100.0, 1000.0):
+        n = refined(*offset_blobs(D, N, D, K, offset, dtype))
+        print("listed", D, dtype, offset, at_origin, n, flush=True)
+        assert n <= 2 * at_origin + N // 50
