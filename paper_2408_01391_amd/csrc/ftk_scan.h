@@ -34,7 +34,8 @@ struct ScanListed {
 
 struct ScanBuffers {
     uint4 *image;       // [tiles_pad][nb][2][64] centroid pieces in fragment order
-    float *start;       // [tiles_pad][32] accumulator start values -||c||^2/2 - r.c (c less the reference r, scaled), fragment order
+    float *start;       // [tiles_pad][32] accumulator start values -||c||^2/2 - r.c (c less the reference r, scaled), raised, fragment order
+    float *norm;        // [tiles_pad][32] ||c|| (scaled)
     float4 *tile_stat;  // [tiles_pad] largest ||c||^2 (scaled), ||c1||^2 / ||c||^2, ||r_c||^2 / ||c||^2 of a tile
     double *scale;      // [2] the power of two both operands are multiplied by; length of the (scaled) reference
     ScanRecord *rec;    // [splits][N]

@@ -37,6 +37,12 @@
 // the points as well it would be ||x - r|| ||c - r||, but their share of it costs the streaming scan 3 (fp32) to
 // 20 % (fp64) on any data, and matters for offsets of more than about 10^4 spreads only.)
 //
+// One far centroid must not widen the band of all points either (2^18 x 8, K = 1024, one centroid 100 times
+// farther out than the others: 3 % of the points listed).  With e(c) = A ||c|| + psi ||c||^2 / 2 the error of the
+// score of centroid c, start values are raised by lift ||c||^2, lift > psi / 2: the score of any c is then at most
+//     A ||c|| + (psi / 2 - lift) ||c||^2 <= A^2 / (4 lift - 2 psi)
+// too low, whatever its norm, and that of the named centroid at most A ||c|| + (psi / 2 + lift) ||c||^2 too high.
+//
 // Both operands are multiplied by one power of two taken from the same rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
 // the same (overflow, NaN) is found by the settle pass, and such a point is compared with every centroid.
@@ -192,7 +198,7 @@ constexpr size_t REF_BYTES = 64 * 1024;
 template <typename T, int FORM>
 __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
                                                               float4 *tile_stat, double *scale, int32_t *list_count, int lists,
-                                                              int has_ref)
+                                                              int has_ref, float *norm, double lift)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     T *const ref = reinterpret_cast<T *>(lds_raw);  // [16 nb]
@@ -343,7 +349,9 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
         }
         // register r of lane group gg reads row 8(r/4) + 4gg + r%4
         const int gg = (tid >> 2) & 1, r = 4 * (tid >> 3) + (tid & 3);
-        start[tile * 32 + gg * 16 + r] = 32 * tile + tid < K ? (float)(-0.5 * n - rc * (double)s) : -__builtin_huge_valf();
+        start[tile * 32 + gg * 16 + r] =
+            32 * tile + tid < K ? (float)((lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
+        norm[tile * 32 + tid] = (float)sqrt(n);
         // (a NaN row never wins and does not count)
         float f = n > 0.0 ? (float)n : 0.f;
         float q1 = n > 0.0 ? (float)((double)n1 / n) : 0.f, qr = n > 0.0 ? (float)((double)nr / n) : 0.f;
@@ -765,6 +773,8 @@ struct SettleArgs {
     int64_t N;
     int D, K;
     float psi, lost;    // rounding of a score; what is lost of ||x|| ||c|| whatever the centroids
+    float lift;         // by which multiple of ||c||^2 the scores were raised
+    const float *norm;  // ||c||
     float slack, tiny;  // of the measured norms: their own rounding, and what underflow takes from them
     int32_t *labels;
     ScanListed *list;  // (point, score a candidate needs), or NULL: the points alone go to wl
@@ -825,7 +835,7 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
 #pragma unroll
     for (int q = 0; q < 3; ++q) cm[q] = fmaxf(fmaxf(sh_max[0][q], sh_max[1][q]), fmaxf(sh_max[2][q], sh_max[3][q]));
     const float cmax = 1.000001f * sqrtf(cm[0]) + a.tiny;
-    // a score of centroid c is off by at most (lost ||x|| + psi (||x|| + ||r||)) ||c|| + psi ||c||^2 / 2; ||x1|| <= 2^-8 ||x||
+    // a score of centroid c is off by at most A ||c|| + psi ||c||^2 / 2, A = lost ||x|| + psi (||x|| + ||r||); ||x1|| <= 2^-8 ||x||
     const float lost = a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
     const T s = (T)a.scale[0];
     const float ref = 1.000001f * (float)a.scale[1] + a.tiny;  // ||r||
@@ -840,11 +850,12 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
         }
     }
     T d[ROWS];
-    float xn[ROWS];
+    float xn[ROWS], cn[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         j[u] = (unsigned)j[u] < (unsigned)a.K ? j[u] : 0;  // padding rows, when no score was a number
         c[u] = C + (size_t)j[u] * a.D;
+        cn[u] = a.norm[j[u]];
         d[u] = T(0);
         xn[u] = 0.f;
     }
@@ -874,8 +885,9 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
     for (int u = 0; u < ROWS; ++u) {
         const T dist = group_sum<L>(d[u]);
         const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + a.tiny;
-        const float per_c = lost * norm + a.psi * (norm + ref);
-        const float bound = 1.00001f * (2.f * per_c + a.psi * cmax) * cmax + SCAN_FLOOR;
+        const float A = lost * norm + a.psi * (norm + ref), B = a.lift - 0.5f * a.psi;
+        const float c1 = 1.000001f * cn[u] + a.tiny, t = fminf(A / (2.f * B), cmax);  // the norm most too low
+        const float bound = 1.00001f * ((A - B * t) * t + A * a.tiny + (A + (a.lift + 0.5f * a.psi) * c1) * c1) + SCAN_FLOOR;
         // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on
         // the way to a sum that is not): a threshold that is not a number makes every centroid a candidate.
         const bool sound = (norm + ref + cmax) * cmax < 1e38f;
@@ -1344,6 +1356,7 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
     b.image = (uint4 *)take(tiles * p.nb * form_frags(p.form) * FRAG_UNITS * 16);
     b.start = (float *)take((tiles + 1) * 32 * 4);  // copied two tiles a time
     b.tile_stat = (float4 *)take(tiles * sizeof(float4));
+    b.norm = (float *)take(tiles * 32 * 4);
     b.scale = (double *)take(16);
     b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
     b.list_count = (int32_t *)take((size_t)SCAN_LISTS * LIST_STRIDE * 4);
@@ -1412,11 +1425,17 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     // a contiguous list where refine_kernel takes it over
     int32_t *const counts = p.resolve ? b.list_count : w.wl_count;
     const int lists = p.resolve ? SCAN_LISTS : 1;
+    // rounding of a score: instructions (1.01: pieces add up to more than the value); 4 u for the start value, the
+    // comparison and the bound itself; 2 u for the rounding of the two operands
+    const double u = Mma<float>::kEps;
+    const double psi = ((p.form == FORM_TRIPLE ? 42.0 : 21.0) * 1.01 * p.nb + 6.0) * u;
+    // half of what A comes to for ||x|| = 1 makes the two parts of the bound smallest where ||c|| = 1 as well
+    const double lift = 0.5 * ((p.form == FORM_PAIR ? 280.0 : 2.0) * u + psi) + 0.5 * psi;
     const size_t ref_bytes = (size_t)p.nb * 16 * sizeof(T);
     const bool has_ref = ref_bytes <= REF_BYTES;
 #define FTK_LAUNCH_CENTROIDS(F)                                                                                       \
     hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, has_ref ? ref_bytes : 0, st, (const T *)c.C, c.D, c.K, p.nb, \
-                       b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref)
+                       b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref, b.norm, lift)
     if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
     else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE);
     else FTK_LAUNCH_CENTROIDS(FORM_PAIR);
@@ -1464,9 +1483,9 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     s.N = c.N;
     s.D = c.D;
     s.K = c.K;
-    // instructions; 4 u for the start value, the comparison and the bound itself; 2 u for the rounding of the two operands
-    const double u = Mma<float>::kEps;
-    s.psi = (float)(((p.form == FORM_TRIPLE ? 42.0 : 21.0) * 1.01 * p.nb + 6.0) * u);  // 1.01: pieces add up to more than the value
+    s.psi = (float)psi;
+    s.lift = (float)lift;
+    s.norm = b.norm;
     s.lost = (float)(p.form == FORM_PAIR ? 128.0 * u : 2.0 * u);  // ||r_x|| <= 2^-17 ||x||; three pieces hold 24 bits
     s.slack = (float)(1.0001 + c.D * u);
     s.tiny = (float)(std::sqrt((double)c.D) * 0x1p-73);  // squares below 2^-149 are lost

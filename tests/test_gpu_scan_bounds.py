@@ -86,3 +86,16 @@ def test_an_offset_of_all_data_lists_no_more_points(D, dtype):
         n = refined(*offset_blobs(D, N, D, K, offset, dtype))
         print("listed", D, dtype, offset, at_origin, n, flush=True)
         assert n <= 2 * at_origin + N // 50
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("at", [0, 517])
+@pytest.mark.parametrize("D", [8, 32, 128, 200])
+def test_one_far_centroid_lists_no_more_points(D, at, dtype):
+    N, K = 20000, 1024
+    X, C = offset_blobs(D, N, D, K, 0.0, dtype)
+    near = refined(X, C)
+    C[at] *= 100
+    n = refined(X, C)
+    print("listed", D, dtype, at, near, n, flush=True)
+    assert n <= 2 * near + N // 50
