@@ -47,6 +47,7 @@
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
 // the same (overflow, NaN) is found by the settle pass, and such a point is compared with every centroid.
 #include <cmath>
+#include <type_traits>
 
 #include "ftk_internal.h"
 #include "ftk_mma.h"
@@ -985,7 +986,203 @@ __device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, in
     return group_sum<L>(d);
 }
 
-constexpr int RS_THREADS = 512, RS_CAP = 8;
+// the same for P points against one centroid, whose elements are read once
+template <typename T, int L, int P>
+__device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *c, int D, int sub, double (&d)[P])
+{
+    const int Dq = D & ~3;
+#pragma unroll
+    for (int i = 0; i < P; ++i) d[i] = 0.0;
+    for (int f = 4 * sub; f < Dq; f += 4 * L) {
+        const Quad<T> cv = load_quad<T>(c + f);
+        Quad<T> xv[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) xv[i] = load_quad<T>(x[i] + f);
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double t = (double)xv[i].v[e] - (double)cv.v[e];
+                d[i] = fma(t, t, d[i]);
+            }
+    }
+    for (int f = Dq + sub; f < D; f += L)
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const double t = (double)x[i][f] - (double)c[f];
+            d[i] = fma(t, t, d[i]);
+        }
+#pragma unroll
+    for (int i = 0; i < P; ++i) d[i] = group_sum<L>(d[i]);
+}
+
+constexpr int RS_THREADS = 512, RS_WAVES = RS_THREADS / 64, RS_CAP = 8;
+
+// ---- points with more candidates than are noted -----------------------------------------------------
+// Data in several groups far from each other, or with one feature that dominates, leave a point every
+// centroid of its group within the bound.  The bound of the data's own type may still tell them apart (fp64:
+// nearly always), so up to 32 such points meet all centroids on the fp32 / fp64 matrix instructions first:
+// best score, its centroid and the runner-up as the matrix kernels find them, from fragments read straight from
+// memory (L2).  Two groups at +-1000, spread 5, K = 1024, every point listed with some 500 candidates, a call with
+// all of them compared in double / here: fp64 2^18 x 32 6291 / 1040 us, 60000 x 512 15592 / 2508; fp32 2^18 x 32
+// 6155 / 1254.  (The matrix kernels alone take 346, 1133 and 271 us of such data; of data in one piece 346, 1139
+// and 188 us against 91, 315 and 93.)
+// Wave w takes pairs of centroid tiles; what it finds goes to sh.*[w].
+template <typename T>
+struct NativeShared {
+    T m1[RS_WAVES][32], m2[RS_WAVES][32];
+    int j1[RS_WAVES][32];
+    double cmax2[RS_WAVES], xn[32];
+};
+
+// E elements of a row from feature d0 by one access clamped into the row: those below d0 belong to another
+// lane's fragment and count as zero here, and so does all of a fragment beyond D
+template <typename T>
+__device__ __forceinline__ typename Mma<T>::frag_t native_frag(const T *row, int d0, int D)
+{
+    constexpr int E = Mma<T>::E;
+    const int off = min(d0, D - E);
+    typename Mma<T>::frag_t f;
+    if constexpr (sizeof(T) == 4) f = *reinterpret_cast<const float4e *>(row + off);
+    else f = *reinterpret_cast<const double2e *>(row + off);
+#pragma unroll
+    for (int e = 0; e < E; ++e) f[e] = off + e >= d0 ? f[e] : T(0);
+    return f;
+}
+
+template <typename T>
+__device__ __forceinline__ void native_sweep(const T *X, const T *C, int D, int K, const int32_t *points, const int *left,
+                                             int nleft, NativeShared<T> &sh)
+{
+    using M = Mma<T>;
+    constexpr int E = M::E, TM = M::TM, NT = 32 / M::TN, CT = 2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane % TM, g = lane / TM;
+    const int nq = (D + 7) >> 3;
+    const T *x[NT];
+    T m1[NT], m2[NT];
+    int j1[NT];
+    double xn[NT], cmax2 = 0.0;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        x[nt] = X + (int64_t)points[left[min(nt * M::TN + row, nleft - 1)]] * D;
+        m1[nt] = m2[nt] = M::neg_inf();
+        j1[nt] = 0;
+    }
+    for (int j0 = wave * CT * TM; j0 < K; j0 += RS_WAVES * CT * TM) {
+        const T *c[CT];
+        typename M::acc_t acc[CT][NT];
+        double cn[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            c[ct] = C + (size_t)min(j0 + ct * TM + row, K - 1) * D;
+            cn[ct] = 0.0;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int r = 0; r < M::R; ++r) acc[ct][nt][r] = T(0);
+        }
+        typename M::frag_t xf[NT], cf[CT], xg[NT], cg[CT];
+        auto request = [&](int q) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) xg[nt] = native_frag<T>(x[nt], 8 * q + E * g, D);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) cg[ct] = native_frag<T>(c[ct], 8 * q + E * g, D);
+        };
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) xn[nt] = 0.0;
+        request(0);
+        for (int q = 0; q < nq; ++q) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) xf[nt] = xg[nt];
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) cf[ct] = cg[ct];
+            request(min(q + 1, nq - 1));
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) acc[ct][nt] = M::mma(cf[ct][e], xf[nt][e], acc[ct][nt]);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) cn[ct] = fma((double)cf[ct][e], (double)cf[ct][e], cn[ct]);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) xn[nt] = fma((double)xf[nt][e], (double)xf[nt][e], xn[nt]);
+            }
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+            for (int k = TM; k < 64; k <<= 1) cn[ct] += __shfl_xor(cn[ct], k, 64);
+            cmax2 = cn[ct] > cmax2 ? cn[ct] : cmax2;  // (rows beyond K repeat the last one)
+#pragma unroll
+            for (int r = 0; r < M::R; ++r) {
+                const T h = (T)(0.5 * __shfl(cn[ct], M::row(r, g), 64));
+                const int j = j0 + ct * TM + M::row(r, g);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const T v = j < K ? acc[ct][nt][r] - h : M::neg_inf();
+                    const bool better = v > m1[nt];  // (a score that is not a number counts for nothing)
+                    const T low = better ? m1[nt] : v;
+                    m2[nt] = low > m2[nt] ? low : m2[nt];
+                    m1[nt] = better ? v : m1[nt];
+                    j1[nt] = better ? j : j1[nt];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+        for (int k = TM; k < 64; k <<= 1) {
+            const T o1 = __shfl_xor(m1[nt], k, 64), o2 = __shfl_xor(m2[nt], k, 64);
+            const int oj = __shfl_xor(j1[nt], k, 64);
+            const bool other = o1 > m1[nt];
+            const T low = other ? m1[nt] : o1;
+            m2[nt] = o2 > m2[nt] ? o2 : m2[nt];
+            m2[nt] = low > m2[nt] ? low : m2[nt];
+            m1[nt] = other ? o1 : m1[nt];
+            j1[nt] = other ? oj : j1[nt];
+            xn[nt] += __shfl_xor(xn[nt], k, 64);
+        }
+        if (g == 0) {
+            sh.m1[wave][nt * M::TN + row] = m1[nt];
+            sh.m2[wave][nt * M::TN + row] = m2[nt];
+            sh.j1[wave][nt * M::TN + row] = j1[nt];
+            if (wave == 0) sh.xn[nt * M::TN + row] = xn[nt];
+        }
+    }
+#pragma unroll
+    for (int k = 1; k < TM; k <<= 1) {
+        const double o = __shfl_xor(cmax2, k, 64);
+        cmax2 = o > cmax2 ? o : cmax2;
+    }
+    if (lane == 0) sh.cmax2[wave] = cmax2;
+}
+
+// the centroid of point i, or -1 where its scores do not tell (a NaN or an infinity among them: the bound does not hold)
+template <typename T>
+__device__ __forceinline__ int native_verdict(const NativeShared<T> &sh, int i, int D)
+{
+    T m1 = sh.m1[0][i], m2 = sh.m2[0][i];
+    int j1 = sh.j1[0][i];
+    double cmax2 = sh.cmax2[0];
+    for (int w = 1; w < RS_WAVES; ++w) {
+        const T o1 = sh.m1[w][i], o2 = sh.m2[w][i];
+        const bool other = o1 > m1;
+        const T low = other ? m1 : o1;
+        m2 = o2 > m2 ? o2 : m2;
+        m2 = low > m2 ? low : m2;
+        m1 = other ? o1 : m1;
+        j1 = other ? sh.j1[w][i] : j1;
+        cmax2 = sh.cmax2[w] > cmax2 ? sh.cmax2[w] : cmax2;
+    }
+    // the band of the matrix kernels (see ftk_assign_generic.hip): D products and the sum's start, each rounded
+    const double big = sqrt(sh.xn[i] * cmax2) + 0.5 * cmax2;
+    const double band = 2.0 * (double)(((D + 7) & ~7) + 4) * Mma<T>::kEps * big;
+    const bool sound = big < 0.25 * (sizeof(T) == 4 ? 3e38 : 1e308);
+    return sound && (double)m1 - (double)m2 > band ? j1 : -1;
+}
 
 template <typename T, int FORM, int L>
 __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, const T *C, T *mindist, ResolveArgs a)
@@ -998,8 +1195,10 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     __shared__ int sh_cnt[32];
     __shared__ int32_t sh_j[32][RS_CAP];
     __shared__ double sh_d[32][RS_CAP];
-    __shared__ double sh_bd[16];
-    __shared__ int sh_bj[16];
+    __shared__ double sh_bd[4][RS_WAVES];
+    __shared__ int sh_bj[4][RS_WAVES];
+    __shared__ int sh_left[32], sh_nleft;  // points that no list of candidates settled
+    __shared__ NativeShared<T> sh_native;
     __shared__ double sh_bd32[32];
     __shared__ int32_t sh_code[32];
     __shared__ int sh_last;
@@ -1214,41 +1413,91 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
             if (mindist) mindist[sh_p[tid]] = (T)sh_bd32[tid];
         }
         __syncthreads();
-        for (int k = 0; k < np; ++k) {
-            if (sh_code[k] >= 0) continue;
-            const T *x = X + (int64_t)sh_p[k] * a.D;
-            double best = __builtin_huge_val();
-            int bj = 0x7fffffff;
+        auto collect = [&] {
+            if (tid < 64) {
+                const bool open = tid < np && sh_code[tid] < 0;
+                const unsigned long long m = __ballot(open);
+                if (open) sh_left[__popcll(m & ((1ull << tid) - 1ull))] = tid;
+                if (tid == 0) sh_nleft = __popcll(m);
+            }
+            __syncthreads();
+        };
+        collect();
+        // (a single point meets all centroids faster below)
+        if (const int nleft = sh_nleft; nleft > 1) {
+            native_sweep<T>(X, C, a.D, a.K, sh_p, sh_left, nleft, sh_native);
+            __syncthreads();
+            if (tid < nleft) {
+                const int j = native_verdict<T>(sh_native, tid, a.D);
+                if (j >= 0) a.labels[sh_p[sh_left[tid]]] = j;
+                sh_code[sh_left[tid]] = j;
+            }
+            __syncthreads();
+            if (mindist)
+                for (int q = grp; q < nleft; q += GROUPS) {
+                    const int k = sh_left[q], j = sh_code[k];
+                    if (j < 0) continue;
+                    const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)j * a.D, a.D, sub);
+                    if (sub == 0) mindist[sh_p[k]] = (T)d;
+                }
+            __syncthreads();
+            collect();
+        }
+        // what is left: every centroid in double, up to four points at a time
+        auto compare_all = [&](auto count, int k0) {
+            constexpr int P = decltype(count)::value;
+            const T *x[P];
+            double best[P];
+            int bj[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                x[i] = X + (int64_t)sh_p[sh_left[min(k0 + i, sh_nleft - 1)]] * a.D;
+                best[i] = __builtin_huge_val();
+                bj[i] = 0x7fffffff;
+            }
             for (int j = grp; j < a.K; j += GROUPS) {
-                const double d = group_sqdist<T, L>(x, C + (size_t)j * a.D, a.D, sub);
-                if (d < best || (d == best && j < bj)) {
-                    best = d;
-                    bj = j;
+                double d[P];
+                group_sqdists<T, L, P>(x, C + (size_t)j * a.D, a.D, sub, d);
+#pragma unroll
+                for (int i = 0; i < P; ++i)
+                    if (d[i] < best[i]) {  // j increases: the first of equal ones stays
+                        best[i] = d[i];
+                        bj[i] = j;
+                    }
+            }
+            __syncthreads();  // the results of the points before these have been read
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+#pragma unroll
+                for (int q = 32; q >= L; q >>= 1) {
+                    const double od = __shfl_xor(best[i], q, 64);
+                    const int oj = __shfl_xor(bj[i], q, 64);
+                    const bool take = od < best[i] || (od == best[i] && oj < bj[i]);
+                    best[i] = take ? od : best[i];
+                    bj[i] = take ? oj : bj[i];
+                }
+                if (lane == 0) {
+                    sh_bd[i][wave] = best[i];
+                    sh_bj[i][wave] = bj[i];
                 }
             }
-#pragma unroll
-            for (int q = 32; q >= L; q >>= 1) {
-                const double od = __shfl_xor(best, q, 64);
-                const int oj = __shfl_xor(bj, q, 64);
-                const bool take = od < best || (od == best && oj < bj);
-                best = take ? od : best;
-                bj = take ? oj : bj;
-            }
             __syncthreads();
-            if (lane == 0) {
-                sh_bd[wave] = best;
-                sh_bj[wave] = bj;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                for (int i = 1; i < RS_THREADS / 64; ++i)
-                    if (sh_bd[i] < best || (sh_bd[i] == best && sh_bj[i] < bj)) {
-                        best = sh_bd[i];
-                        bj = sh_bj[i];
+            if (tid < P && k0 + tid < sh_nleft) {
+                double d = sh_bd[tid][0];
+                int j = sh_bj[tid][0];
+                for (int w = 1; w < RS_WAVES; ++w)
+                    if (sh_bd[tid][w] < d || (sh_bd[tid][w] == d && sh_bj[tid][w] < j)) {
+                        d = sh_bd[tid][w];
+                        j = sh_bj[tid][w];
                     }
-                a.labels[sh_p[k]] = bj == 0x7fffffff ? 0 : bj;
-                if (mindist) mindist[sh_p[k]] = (T)best;
+                const int32_t p = sh_p[sh_left[k0 + tid]];
+                a.labels[p] = j == 0x7fffffff ? 0 : j;
+                if (mindist) mindist[p] = (T)d;
             }
+        };
+        for (int k0 = 0; k0 < sh_nleft; k0 += 4) {
+            if (sh_nleft - k0 == 1) compare_all(std::integral_constant<int, 1>{}, k0);
+            else compare_all(std::integral_constant<int, 4>{}, k0);
         }
     }
 }

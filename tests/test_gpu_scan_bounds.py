@@ -99,3 +99,32 @@ def test_one_far_centroid_lists_no_more_points(D, at, dtype):
     n = refined(X, C)
     print("listed", D, dtype, at, near, n, flush=True)
     assert n <= 2 * near + N // 50
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("N,D,K", [(300, 4, 800), (40000, 9, 900), (2000, 17, 777), (40, 45, 800), (20000, 64, 1000),
+                                   (700, 131, 800), (33, 513, 1500)])
+@pytest.mark.parametrize("kind", ["groups", "one feature", "groups with copies"])
+def test_points_with_many_candidates(N, D, K, dtype, kind):
+    """More centroids within the scan's bound than it notes: settled on the fp32 / fp64 matrix instructions
+    where their bound tells them apart, else (equal centroids among them) by comparison with all."""
+    print("many candidates", N, D, K, dtype, kind, flush=True)
+    rng = np.random.default_rng(N + D)
+    C = rng.normal(size=(K, D)) * 5
+    X = C[rng.integers(0, K, N)] + rng.normal(size=(N, D))
+    if kind == "one feature":
+        X[:, 0] *= 1e4
+        C[:, 0] *= 1e4
+    else:
+        X += np.where(rng.random(N) < 0.5, 3000.0, -3000.0)[:, None]
+        C += np.where(np.arange(K) % 2 == 0, 3000.0, -3000.0)[:, None]
+    if kind == "groups with copies":
+        C[K - 40:] = C[:40]
+        X[:20] = C[K - 20:]
+    X, C = X.astype(NP[dtype]), C.astype(NP[dtype])
+    labels, mind = run(X, C)
+    ref = oracle.assign(X, C)
+    check_assign(X, C, labels, mind, ref=ref)
+    # distances of this path are direct: D differences, squares and sums, each rounded
+    eps = 2.0 ** -24 if dtype == "f32" else 2.0 ** -53
+    assert np.all(np.abs(mind.astype(np.float64) - ref[1]) <= 2 * (D + 4) * eps * ref[1] + 1e-5 * ref[1] * (labels != ref[0]))
