@@ -96,7 +96,9 @@ typedef struct {
     uint32_t workgroups, waves_per_workgroup, tiles_per_wave, regs_per_tile, lanes, bits;
 } ftk_geometry;
 
-/* Bytes of workspace sufficient for any of the three calls below on this problem. */
+/* Bytes of workspace sufficient for any of the three calls below on this problem.  FTK_FT_OFF asks for
+ * more than the protected modes, for buffers of faster paths that only unprotected calls take; such a
+ * call also accepts a workspace of a protected mode's size, and then runs without them. */
 size_t ftk_workspace_bytes(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft);
 
 ftk_status ftk_assign_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft,

@@ -156,36 +156,43 @@ static bool route_small(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft
 // centroids (2 * 10^5 x 8, K = 64 31 / 19), beyond that the scan while there are few points (20000, K = 4096 106 /
 // 45; 1.5 * 10^6, K = 1024 163 / 195).
 enum FastRoute { FAST_OWN, FAST_SMALL, FAST_FP32, FAST_SCAN };
-static FastRoute route_fast(int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
+static FastRoute fast_rule(int64_t N, int D, int K)
 {
-    if (ft != FTK_FT_OFF || n_faults > 0 || g_tuning.assign_variant != -1) return FAST_OWN;
     if (small_assign_pays(FTK_F32, N, D, K)) return FAST_SMALL;
     if (D <= 8) return K <= 512 ? FAST_FP32 : (N < 100000 ? FAST_SCAN : FAST_OWN);
     return D <= 32 || K >= 512 ? FAST_SCAN : FAST_OWN;
 }
-static bool fast_may_scan(ftk_dtype dtype, int64_t N, int D, int K)
+static FastRoute route_fast(int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
 {
-    return fast_supported(dtype, D) && route_fast(N, D, K, FTK_FT_OFF, 0) == FAST_SCAN;
+    if (ft != FTK_FT_OFF || n_faults > 0 || g_tuning.assign_variant != -1) return FAST_OWN;
+    return fast_rule(N, D, K);
+}
+
+// bytes of the scan's buffers for the plain or the reduced-precision entry point, whatever kernel is forced
+static size_t scan_bytes(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    if (!plan_scan(dtype, N, D, K).ok && !(fast_supported(dtype, D) && fast_rule(N, D, K) == FAST_SCAN)) return 0;
+    return carve_scan(nullptr, cut_scan(dtype, N, D, K), N).bytes;
 }
 
 // The workspace is carved for the larger of the two kernel variants so that its size does not
-// depend on which one the dispatcher picks.  The scan's buffers share their bytes with those of the
-// label-sorted update, which no call uses at the same time (the tables of the other update path
-// stay apart: the batched step adds to them between assignments); assign_only: nothing beyond what
-// the assignment touches, the scan's buffers included if `scan`.
-Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft,
-                          bool assign_only, bool scan)
+// depend on which one the dispatcher picks.  `total` serves every call in every mode.  Calls without
+// fault tolerance have faster paths with larger buffers - the scan, the bucketed update, the one-launch
+// fit - which take them where the workspace has room (`unprotected` bytes): protected calls do not pay
+// for them, and a workspace sized for a protected mode serves an unprotected call on the other paths.
+// None of the three runs while another one or the label sort does, so they share the sort's bytes (the tables of
+// the other update path stay apart: the batched step adds to them between assignments).
+Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, int D, int K)
 {
-    (void)ft;
     const size_t esz = dtype == FTK_F32 ? 4 : 8;
     const size_t D8 = (size_t)ceil_div(D, 8) * 8;
     const size_t Kpad = hcn_entries_max(dtype, N, D, K);        // padded rows of the widest plan
     const size_t ntiles = Kpad / 8;                             // generous: checksum rows per lane group
     char *p = (char *)base;
     size_t off = 0;
-    auto take = [&](size_t bytes) {
+    auto take = [&](size_t n) {
         void *r = p ? (void *)(p + off) : nullptr;
-        off += align_up(bytes, 256);
+        off += align_up(n, 256);
         return r;
     };
     Workspace w;
@@ -199,48 +206,15 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
     w.wl_count = (int32_t *)take(4 * sizeof(int32_t));
     w.wl = (int32_t *)take((size_t)N * sizeof(int32_t));
     w.wg_refined = (int32_t *)take(((size_t)N / 64 + 2) * sizeof(int32_t));
-    const bool may_scan = plan_scan(dtype, N, D, K).ok || (!assign_only && fast_may_scan(dtype, N, D, K));
-    const size_t scan_bytes =
-        (assign_only && !scan) || !may_scan ? 0 : carve_scan(nullptr, cut_scan(dtype, N, D, K), N).bytes;
-    w.scan = nullptr;
-    if (assign_only) {  // the assignment step touches nothing beyond its own buffers and the scan's
-        if (p) w.scan = (void *)(p + off);
-        off += scan_bytes;
-        w.fx_sums = nullptr;
-        w.upd_slab = nullptr;
-        w.upd_cslab = nullptr;
-        w.absmax = nullptr;
-        w.sort_idx = w.sort_lab = w.sort_cursor = nullptr;
-        w.C_cur = w.mindist = nullptr;
-        w.inertia = w.partials = nullptr;
-        w.idx = nullptr;
-        w.csplit = nullptr;
-        w.batch_counters = nullptr;
-        w.small_fit = nullptr;
-        w.total = off;
-        return w;
-    }
+    w.assign = off;
     {   // shared by the update paths: per-workgroup tables, or two tagged slots per walker
-        int64_t bucket_counts = 0;
-        const size_t bucket_cells = (size_t)update_bucket_cells(dtype, N, D, K, &bucket_counts);
         const size_t slab_cells = (size_t)update_slab_cells_max(N, D, K);
         const size_t slot_cells = (size_t)update_walkers_max(N) * 2 * (size_t)D;
-        size_t most = slab_cells > slot_cells ? slab_cells : slot_cells;
-        if (bucket_cells > most) most = bucket_cells;
-        w.upd_slab = (int64_t *)take(most * sizeof(int64_t));
+        w.upd_slab = (int64_t *)take((slab_cells > slot_cells ? slab_cells : slot_cells) * sizeof(int64_t));
         const size_t slab_counts = (size_t)update_slab_chunks_max(N) * K;
         const size_t slot_tags = (size_t)update_walkers_max(N) * 2;
-        most = slab_counts > slot_tags ? slab_counts : slot_tags;
-        if ((size_t)bucket_counts > most) most = (size_t)bucket_counts;
-        w.upd_cslab = (int32_t *)take(most * sizeof(int32_t));
+        w.upd_cslab = (int32_t *)take((slab_counts > slot_tags ? slab_counts : slot_tags) * sizeof(int32_t));
     }
-    const size_t shared = off;
-    if (p) w.scan = (void *)(p + off);
-    w.fx_sums = (int64_t *)take((size_t)K * D * 2 * sizeof(int64_t));  // two limbs per cell
-    w.sort_idx = (int32_t *)take((size_t)N * sizeof(int32_t));
-    w.sort_lab = (int32_t *)take((size_t)N * sizeof(int32_t));
-    w.sort_cursor = (int32_t *)take(((size_t)K + 1) * sizeof(int32_t));
-    if (off < shared + scan_bytes) off = shared + scan_bytes;
     w.absmax = (double *)take(2 * sizeof(double));
     w.C_cur = take((size_t)K * D * esz);
     w.mindist = take((size_t)N * esz);
@@ -249,8 +223,22 @@ Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, 
     w.idx = (int64_t *)take((size_t)K * sizeof(int64_t));
     w.csplit = take(fast_split_bytes(dtype, D, K));
     w.batch_counters = (int32_t *)take((size_t)4 * MAX_BATCHES * sizeof(int32_t));
-    w.small_fit = take(small_fit_bytes(D, K));
+    const size_t shared = off;
+    w.fx_sums = (int64_t *)take((size_t)K * D * 2 * sizeof(int64_t));  // two limbs per cell
+    w.sort_idx = (int32_t *)take((size_t)N * sizeof(int32_t));
+    w.sort_lab = (int32_t *)take((size_t)N * sizeof(int32_t));
+    w.sort_cursor = (int32_t *)take(((size_t)K + 1) * sizeof(int32_t));
     w.total = off;
+    int64_t bucket_counts = 0;  // (the buckets use the sort's arrays and its own tables behind them)
+    const int64_t bucket_cells = update_bucket_cells(dtype, N, D, K, &bucket_counts);
+    w.bucket_slab = (int64_t *)take((size_t)bucket_cells * sizeof(int64_t));
+    w.bucket_cslab = (int32_t *)take((size_t)bucket_counts * sizeof(int32_t));
+    w.unprotected = off;
+    for (size_t n : {scan_bytes(dtype, N, D, K), small_fit_bytes(D, K)})
+        if (w.unprotected < shared + n) w.unprotected = shared + n;
+    w.scan = w.small_fit = nullptr;
+    w.room = p && bytes >= w.unprotected;
+    if (w.room) w.scan = w.small_fit = (void *)(p + shared);
     return w;
 }
 
@@ -321,20 +309,22 @@ static ftk_status check_device()
 static bool g_profile = false;
 static std::vector<std::pair<hipEvent_t, hipEvent_t>> g_profile_events;
 
-static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t st, bool fast = false,
-                              bool own_scratch = false, bool allow_scan = true)
+// own_scratch: `w` holds the assignment's buffers alone (and w.scan, if there is room)
+static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream_t st, bool fast = false,
+                              bool own_scratch = false)
 {
     const bool aligned16 = ((uintptr_t)c.X % 16 == 0) && ((uintptr_t)c.C % 16 == 0);
     FastRoute froute = FAST_OWN;
     if (fast) {
         froute = route_fast(c.N, c.D, c.K, c.ft, c.n_faults);
+        if (froute == FAST_SCAN && !w.scan) froute = FAST_OWN;
         if (froute == FAST_FP32) fast = false;  // the register-resident kernel of short rows
     }
     const bool small = fast ? froute == FAST_SMALL : froute == FAST_OWN && route_small(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     ScanPlan scan = {};
     if (froute == FAST_SCAN)
         scan = cut_scan(c.dtype, c.N, c.D, c.K);
-    else if (!fast && froute == FAST_OWN && !small && allow_scan)
+    else if (!fast && froute == FAST_OWN && !small && w.scan)
         scan = route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     AssignPlan p;
     if (small || scan.ok) {
@@ -345,9 +335,6 @@ static ftk_status assign_impl(const AssignCall &c, void *workspace, hipStream_t 
     } else {
         p = plan_assign(c.dtype, c.N, c.D, c.K, c.ft, aligned16);
     }
-    // own_scratch: the assignment's buffers are all there is.  Without the scan's they are a prefix of
-    // the full layout.
-    const Workspace w = carve_workspace(workspace, c.dtype, c.N, c.D, c.K, c.ft, own_scratch || !(fast || scan.ok), scan.ok);
     if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(c, p, w, st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     // at most 65536 pending pairs: a caller that enables profiling and never reads stops recording
@@ -465,7 +452,8 @@ const char *ftk_version(void) { return "ftkmeans 0.1 (gfx950)"; }
 size_t ftk_workspace_bytes(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft)
 {
     if (check_problem(dtype, N, D, K, ft) != FTK_OK) return 0;
-    return carve_workspace(nullptr, dtype, N, D, K, ft).total;
+    const Workspace w = carve_workspace(nullptr, 0, dtype, N, D, K);
+    return ft == FTK_FT_OFF ? w.unprotected : w.total;
 }
 
 ftk_status ftk_assign_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft,
@@ -550,10 +538,11 @@ ftk_status ftk_kmeans_assign(ftk_dtype dtype, const void *X, const void *C, int6
         return FTK_EINVAL;
     }
     if (stats) FTK_TRY(check_ptr(stats, 8, "stats"));
-    FTK_TRY(check_workspace(workspace, workspace_bytes, ftk_workspace_bytes(dtype, N, D, K, ft)));
+    const Workspace w = carve_workspace(workspace, workspace_bytes, dtype, N, D, K);
+    FTK_TRY(check_workspace(workspace, workspace_bytes, w.total));
     FTK_TRY(check_device());
     AssignCall c{dtype, X, C, N, D, K, labels, mindist, ft, faults, n_faults, stats};
-    return assign_impl(c, workspace, (hipStream_t)hip_stream);
+    return assign_impl(c, w, (hipStream_t)hip_stream);
 }
 
 size_t ftk_static_scratch_bytes(void) { return FTK_STATIC_SCRATCH_BYTES; }
@@ -574,10 +563,7 @@ ftk_status ftk_kmeans_assign_static(ftk_dtype dtype, const void *X, const void *
         return FTK_EINVAL;
     }
     if (stats) FTK_TRY(check_ptr(stats, 8, "stats"));
-    // a problem that fits the array only without the scan's buffers runs on the fp32 / fp64 kernels
-    const bool scan = route_scan(dtype, N, D, K, ft, n_faults).ok &&
-                      carve_workspace(nullptr, dtype, N, D, K, ft, true, true).total <= FTK_STATIC_SCRATCH_BYTES;
-    const size_t need = carve_workspace(nullptr, dtype, N, D, K, ft, true, false).total;
+    const size_t need = carve_workspace(nullptr, 0, dtype, N, D, K).assign;
     if (need > FTK_STATIC_SCRATCH_BYTES) {
         set_error("problem needs %zu bytes of scratch, the static buffer holds %zu (N=%lld D=%d K=%d): "
                   "use ftk_kmeans_assign with a caller workspace", need, (size_t)FTK_STATIC_SCRATCH_BYTES,
@@ -587,8 +573,12 @@ ftk_status ftk_kmeans_assign_static(ftk_dtype dtype, const void *X, const void *
     FTK_TRY(check_device());
     void *scratch = nullptr;
     FTK_TRY(static_scratch_of_current_device(&scratch));
+    // the assignment's buffers are a prefix of the layout, the scan's follow them here; a problem that fits the
+    // array only without those runs on the fp32 / fp64 kernels
+    Workspace w = carve_workspace(scratch, 0, dtype, N, D, K);
+    if (need + scan_bytes(dtype, N, D, K) <= FTK_STATIC_SCRATCH_BYTES) w.scan = (char *)scratch + need;
     AssignCall c{dtype, X, C, N, D, K, labels, mindist, ft, faults, n_faults, stats};
-    return assign_impl(c, scratch, (hipStream_t)hip_stream, false, true, scan);
+    return assign_impl(c, w, (hipStream_t)hip_stream, false, true);
 }
 
 static ftk_status check_fast(ftk_dtype dtype, int D)
@@ -617,10 +607,11 @@ ftk_status ftk_kmeans_assign_fast(ftk_dtype dtype, const void *X, const void *C,
         set_error("n_faults=%d with faults=%p", n_faults, (const void *)faults);
         return FTK_EINVAL;
     }
-    FTK_TRY(check_workspace(workspace, workspace_bytes, ftk_workspace_bytes(dtype, N, D, K, ft)));
+    const Workspace w = carve_workspace(workspace, workspace_bytes, dtype, N, D, K);
+    FTK_TRY(check_workspace(workspace, workspace_bytes, w.total));
     FTK_TRY(check_device());
     AssignCall c{dtype, X, C, N, D, K, labels, mindist, ft, faults, n_faults, stats};
-    return assign_impl(c, workspace, (hipStream_t)hip_stream, true);
+    return assign_impl(c, w, (hipStream_t)hip_stream, true);
 }
 
 ftk_status ftk_fast_plan(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft, ftk_geometry *geometry,
@@ -678,10 +669,10 @@ ftk_status ftk_kmeans_update_ft(ftk_dtype dtype, const void *X, const int32_t *l
         return FTK_EINVAL;
     }
     if (stats) FTK_TRY(check_ptr(stats, 8, "stats"));
-    FTK_TRY(check_workspace(workspace, workspace_bytes, ftk_workspace_bytes(dtype, N, D, K, ft)));
+    const Workspace w = carve_workspace(workspace, workspace_bytes, dtype, N, D, K);
+    FTK_TRY(check_workspace(workspace, workspace_bytes, w.total));
     FTK_TRY(check_device());
     hipStream_t st = (hipStream_t)hip_stream;
-    const Workspace w = carve_workspace(workspace, dtype, N, D, K, ft);
     if (!x_absmax) {
         FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, w.absmax, st));
         x_absmax = w.absmax;
@@ -714,10 +705,10 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
                   batch_rows < 1 ? 0ll : (long long)ceil_div(N, batch_rows), MAX_BATCHES);
         return FTK_EINVAL;
     }
-    FTK_TRY(check_workspace(workspace, workspace_bytes, ftk_workspace_bytes(dtype, N, D, K, FTK_FT_OFF)));
+    const Workspace w = carve_workspace(workspace, workspace_bytes, dtype, N, D, K);
+    FTK_TRY(check_workspace(workspace, workspace_bytes, w.total));
     FTK_TRY(check_device());
     hipStream_t st = (hipStream_t)hip_stream;
-    const Workspace w = carve_workspace(workspace, dtype, N, D, K, FTK_FT_OFF);
     // whole rows of 16 bytes keep every batch as aligned as X itself
     const bool aligned16 = ((uintptr_t)X % 16 == 0) && ((uintptr_t)C % 16 == 0) && ((size_t)D * esz) % 16 == 0;
     const BatchedUpdatePlan ub = plan_update_batched(dtype, aligned16 ? X : (const void *)1, N, batch_rows, D, K);
@@ -732,7 +723,7 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
     AssignPlan pprev = plan_assign(dtype, whole.N, D, K, FTK_FT_OFF, aligned16);
     // the path is chosen for the whole problem, as in the two-call step
     const bool small = route_small(dtype, N, D, K, FTK_FT_OFF, 0);
-    const ScanPlan scan = small ? ScanPlan{} : route_scan(dtype, N, D, K, FTK_FT_OFF, 0);
+    const ScanPlan scan = small || !w.scan ? ScanPlan{} : route_scan(dtype, N, D, K, FTK_FT_OFF, 0);
     if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
     for (int64_t b = 0; b < nbatch; ++b) {
         const int64_t r0 = b * batch_rows;
@@ -829,10 +820,10 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
         set_error("seeded initialisation needs K <= N (N=%lld K=%d)", (long long)N, K);
         return FTK_EINVAL;
     }
-    FTK_TRY(check_workspace(workspace, workspace_bytes, ftk_workspace_bytes(dtype, N, D, K, ft)));
+    const Workspace w = carve_workspace(workspace, workspace_bytes, dtype, N, D, K);
+    FTK_TRY(check_workspace(workspace, workspace_bytes, w.total));
     FTK_TRY(check_device());
     hipStream_t st = (hipStream_t)hip_stream;
-    const Workspace w = carve_workspace(workspace, dtype, N, D, K, ft);
 
     if (C_init) {
         FTK_TRY_HIP(hipMemcpyAsync(w.C_cur, C_init, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
@@ -844,14 +835,14 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
         FTK_TRY(launch_gather_rows(dtype, X, D, w.idx, K, w.C_cur, st));
     }
     FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, w.absmax, st));
-    const bool small = !fast && iters > 0 && ft == FTK_FT_OFF && g_tuning.assign_variant == -1 &&
+    const bool small = !fast && w.small_fit && iters > 0 && ft == FTK_FT_OFF && g_tuning.assign_variant == -1 &&
                        g_tuning.update_path == -1 && small_fit_pays(dtype, N, D, K);
     if (small)
         FTK_TRY(launch_small_fit(dtype, X, N, D, K, iters, w.C_cur, C_out, labels_out, counts_out, w.absmax, w.inertia,
                                  w.partials, w.small_fit, st));
     for (int t = 0; !small && t < iters; ++t) {
         AssignCall c{dtype, X, w.C_cur, N, D, K, labels_out, w.mindist, ft, nullptr, 0, stats};
-        FTK_TRY(assign_impl(c, workspace, st, fast));
+        FTK_TRY(assign_impl(c, w, st, fast));
         if (inertia_per_iter)
             FTK_TRY(launch_sum_to_double(dtype, w.mindist, N, w.partials, w.inertia + t, st));
         FTK_TRY(launch_update(dtype, X, labels_out, N, D, K, w.C_cur, counts_out, w.absmax, w, ft, nullptr, 0,

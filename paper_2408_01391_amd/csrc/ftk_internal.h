@@ -80,7 +80,7 @@ struct Workspace {
     int32_t *wl_count;  // [4]   0: refine work-list length, 1: block counter (small-D / fast kernels)
     int32_t *wl;        // [N]   refine work-list (point indices)
     int32_t *wg_refined;  // [N/64 + 2] points each workgroup of the generic kernel settled in place
-    void *scan;         // buffers of the scan (ftk_scan.h), sharing the update's bytes
+    size_t assign;      // bytes up to here: all that an assignment without the scan touches
     // update
     int64_t *fx_sums;   // [K*D][2] fixed-point sums, two limbs (label-sorted path)
     int64_t *upd_slab;  // [chunks][K*D] per-workgroup fixed-point tables (LDS path), or
@@ -99,15 +99,20 @@ struct Workspace {
     // fast (split-bf16) assignment
     void *csplit;       // centroid pieces in LDS image order (fp32 data with D <= 128, else empty)
     int32_t *batch_counters;  // [4 * MAX_BATCHES] work-list counters per batch of the batched step
+    size_t total;       // bytes that serve every call
+    // faster paths of unprotected calls, in the bytes of the label sort and beyond: NULL / unused without room
+    void *scan;         // buffers of the scan (ftk_scan.h)
+    int64_t *bucket_slab;   // [workgroups][clusters of a bucket * D] tables of the bucketed update
+    int32_t *bucket_cslab;  // [workgroups][clusters of a bucket]
     void *small_fit;    // tables of the one-launch Lloyd iteration (ftk_small.h)
-    size_t total;
+    size_t unprotected; // bytes with all of them
+    bool room;
 };
 constexpr int FIT_MAX_ITERS_IN_WS = 4096;
 constexpr int MAX_BATCHES = 4096;
 size_t hcn_entries_max(ftk_dtype dtype, int64_t N, int D, int K);
-// assign_only: stop after the assignment step's buffers (a prefix of the full layout)
-Workspace carve_workspace(void *base, ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft,
-                          bool assign_only = false, bool scan = false);
+// `bytes`: what the caller gave, which decides whether there is room for the unprotected paths
+Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, int D, int K);
 // upper bounds of the update step's per-workgroup tables, independent of pointer alignment
 int64_t update_slab_chunks_max(int64_t N);
 int64_t update_slab_cells_max(int64_t N, int D, int K);

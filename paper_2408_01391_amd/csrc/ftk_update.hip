@@ -1268,19 +1268,19 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
     fa.mode = (int)ft_mode;
     fa.stats = stats;
     const BucketPlan bp = plan_bucket(dtype, N, D, K);
-    if (bp.ok && u.aligned && !dmr && n_faults == 0 && g_tuning.update_path < 0 &&
+    if (bp.ok && w.room && u.aligned && !dmr && n_faults == 0 && g_tuning.update_path < 0 &&
         (L.sorted_path || (u.nks >= 4 && N >= 65536))) {
         uint32_t *entries = reinterpret_cast<uint32_t *>(w.sort_idx);
-        long long *slabs = reinterpret_cast<long long *>(w.upd_slab);
+        long long *slabs = reinterpret_cast<long long *>(w.bucket_slab);
         int32_t *bounds = w.sort_lab, *totals = w.sort_cursor;
         FTK_TRY(launch_zero_ints(totals, bp.buckets, st));
         hipLaunchKernelGGL(bucket_split_kernel, dim3(bp.sources), dim3(BK_THREADS), 0, st, labels, N, K, bp.Kb, bp.buckets,
                            entries, bounds, totals);
         const size_t lds = (size_t)bp.Kb * (D + 1) * 8 + ((size_t)bp.Kb + 2 * bp.sources + 1) * 4;
         hipLaunchKernelGGL(bucket_accumulate_kernel, dim3(bp.wgs + bp.buckets), dim3(BK_THREADS), lds, st, (const float *)X, entries,
-                           bounds, totals, N, D, K, bp, absmax, slabs, w.upd_cslab);
+                           bounds, totals, N, D, K, bp, absmax, slabs, w.bucket_cslab);
         hipLaunchKernelGGL(bucket_finalize_kernel, dim3(bp.buckets, (unsigned)ceil_div(bp.Kb * D, BF_CELLS)),
-                           dim3(BK_THREADS), 0, st, slabs, w.upd_cslab, totals, N, D, K, bp, absmax, (float *)C,
+                           dim3(BK_THREADS), 0, st, slabs, w.bucket_cslab, totals, N, D, K, bp, absmax, (float *)C,
                            counts);
     } else if (L.sorted_path) {
         {

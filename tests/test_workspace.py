@@ -1,0 +1,61 @@
+"""Workspace sizes (host only) and what runs in a workspace of each size."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import cpu as oracle
+from paper_2408_01391_amd import binding as ftk
+
+MB = 1 << 20
+
+
+@pytest.fixture(autouse=True)
+def _restore_rules():
+    if not ftk._LIB_PATH.exists():
+        pytest.skip("libftkmeans.so not built")
+    yield
+    ftk.tuning_override(-1, -1, -1)
+
+
+@pytest.mark.parametrize("dtype,N,D,K,most", [(ftk.F32, 1 << 21, 256, 16384, 280 * MB), (ftk.F64, 1 << 20, 512, 8192, 280 * MB),
+                                              (ftk.F32, 1 << 20, 130, 2048, 60 * MB), (ftk.F32, 2000, 32, 900, 9 * MB)])
+def test_protected_calls_do_not_reserve_what_only_unprotected_ones_use(dtype, N, D, K, most):
+    sizes = [ftk.workspace_bytes(dtype, N, D, K, m) for m in (ftk.FT_OFF, ftk.FT_DETECT, ftk.FT_CORRECT, ftk.FT_STRICT)]
+    assert sizes[1] == sizes[2] == sizes[3] <= min(most, sizes[0])
+
+
+@pytest.mark.parametrize("dtype,N,D,K", [(ftk.F32, 1 << 20, 16, 64), (ftk.F32, 1 << 20, 32, 300), (ftk.F32, 5000, 8, 4096),
+                                         (ftk.F64, 1 << 20, 64, 1024), (ftk.F32, 4096, 16, 8)])
+def test_size_does_not_depend_on_a_forced_kernel(dtype, N, D, K):
+    for mode in (ftk.FT_OFF, ftk.FT_STRICT):
+        ftk.tuning_override(-1, -1, -1)
+        size = ftk.workspace_bytes(dtype, N, D, K, mode)
+        for forced in ((0, 1, 0), (1, 8, 1)):
+            ftk.tuning_override(*forced)
+            assert ftk.workspace_bytes(dtype, N, D, K, mode) == size
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 70000, 32, 3000), ("f64", 5000, 40, 800), ("f32", 4096, 16, 8), ("f32", 3000, 200, 800)])
+def test_unprotected_calls_in_a_workspace_of_a_protected_mode(dtype, N, D, K):
+    """Accepted, with the results of the other paths; bytes beyond the size given stay untouched."""
+    np_t = np.float32 if dtype == "f32" else np.float64
+    rng = np.random.default_rng(N)
+    C = (rng.normal(size=(K, D)) * 5).astype(np_t)
+    X = (C[rng.integers(0, K, N)] + rng.normal(size=(N, D))).astype(np_t)
+    Xd, Cd = torch.from_numpy(X).cuda(), torch.from_numpy(C).cuda()
+    size = ftk.workspace_bytes(ftk.F32 if dtype == "f32" else ftk.F64, N, D, K, ftk.FT_STRICT)
+    whole = torch.full((size + MB,), 0x5a, dtype=torch.uint8, device="cuda")
+    start = -whole.data_ptr() % 256
+    ws = whole[start:start + size]
+    ref = oracle.assign(X, C)
+    calls = [ftk.kmeans_assign] + ([ftk.kmeans_assign_fast] if dtype == "f32" and D <= 128 else [])
+    for call in calls:
+        labels, _ = call(Xd, Cd, workspace=ws)
+        assert np.array_equal(labels.cpu().numpy(), ref[0])
+    C_new = Cd.clone()
+    _, counts = ftk.kmeans_update(Xd, labels, C_new, workspace=ws)
+    assert np.array_equal(counts.cpu().numpy(), np.bincount(ref[0], minlength=K))
+    out = ftk.kmeans_fit(Xd, K, 1, C_init=Cd, workspace=ws)
+    assert torch.equal(out["C"], C_new) and torch.equal(out["labels"], labels)
+    assert bool((whole[start + size:] == 0x5a).all()) and bool((whole[:start] == 0x5a).all())
