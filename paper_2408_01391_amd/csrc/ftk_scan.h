@@ -16,6 +16,7 @@ struct ScanPlan {
     int splits, cps;    // workgroups sharing a block of points, chunks each of them sweeps
     int ct;             // stream: centroid tiles per wave
     int64_t pblocks;    // blocks of 256 points
+    int64_t batch;      // points of a launch: the rest of this is cut for those
     int64_t rec_reserve;  // records to reserve
     bool resolve;       // listed points are settled by the scan's own third pass (else refine_kernel)
 };
@@ -47,7 +48,7 @@ struct ScanBuffers {
 
 // the rule: which problems take this path, and how they are cut up
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K);
-// the cut alone, for a batch of a problem that takes this path
+// the cut alone, for part of a problem that takes this path
 ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // buffers for the whole problem and for any batch of it
 ScanBuffers carve_scan(void *base, const ScanPlan &whole, int64_t N);

@@ -1547,10 +1547,17 @@ ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K)
     return scan_pays(dtype, N, D, K) ? cut_scan(dtype, N, D, K) : ScanPlan{};
 }
 
-ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
+// A launch handles points whose records fit SCAN_RECORDS; more points follow in further launches.  Without that the
+// records of the streaming scan grow with N K (2^21 x 256, K = 16384: 2.1 GB) and so does its grid, beyond the 2^32
+// threads of a launch.  16 thousand workgroups at least stay in a launch.
+constexpr int64_t SCAN_RECORDS = (int64_t)1 << 22;  // 64 MB
+constexpr int64_t SCAN_BATCH_STEP = 2048;           // points: whole rounds of the streaming scan's XCD order
+
+static ScanPlan cut_launch(ftk_dtype dtype, int64_t N, int D, int K)
 {
     ScanPlan p = {};
     p.ok = true;
+    p.batch = N;
     p.form = D <= 8 ? FORM_OCTET : (D <= 16 ? FORM_TRIPLE : FORM_PAIR);
     p.stream = D > 128;
     p.tiles = (int)ceil_div(K, 32);
@@ -1581,10 +1588,24 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     }
     p.tiles_pad = p.nch * p.tpc;
     p.resolve = p.nb <= 72;  // 32 points' fragments fit in LDS; longer rows go to refine_kernel
-    // A batch of fewer points may be shared by more workgroups than the whole: splits <= SCAN_FILL /
-    // pblocks + 1 wherever there is more than the whole's, so this holds the records of any batch.
-    p.rec_reserve = (int64_t)p.splits * N;
-    if (p.rec_reserve < SCAN_FILL * SC_POINTS + N + SC_POINTS) p.rec_reserve = SCAN_FILL * SC_POINTS + N + SC_POINTS;
+    return p;
+}
+
+ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    ScanPlan p = cut_launch(dtype, N, D, K);
+    const int64_t most = SCAN_RECORDS / p.splits / SCAN_BATCH_STEP * SCAN_BATCH_STEP;
+    const int64_t batch_max = most > SCAN_BATCH_STEP ? most : SCAN_BATCH_STEP;
+    const int64_t splits = p.splits;
+    if (N > batch_max) {  // launches of equal size
+        const int64_t n = ceil_div(N, batch_max);
+        p = cut_launch(dtype, ceil_div(ceil_div(N, n), SCAN_BATCH_STEP) * SCAN_BATCH_STEP, D, K);
+    }
+    // What the points or any part of them may need: fewer points may be shared by more workgroups than the whole,
+    // but splits <= SCAN_FILL / pblocks + 1 wherever there is more than the whole's.
+    const int64_t fill = (int64_t)SCAN_FILL * SC_POINTS;
+    p.rec_reserve = splits * (N < batch_max ? N : batch_max);
+    if (p.rec_reserve < fill + (N < fill ? N : fill) + SC_POINTS) p.rec_reserve = fill + (N < fill ? N : fill) + SC_POINTS;
     if (p.rec_reserve > (int64_t)p.tiles * N) p.rec_reserve = (int64_t)p.tiles * N;
     return p;
 }
@@ -1609,8 +1630,9 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
     b.scale = (double *)take(16);
     b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
     b.list_count = (int32_t *)take((size_t)SCAN_LISTS * LIST_STRIDE * 4);
-    b.list = (ScanListed *)take(((size_t)N + SCAN_LISTS * SETTLE_ROWS_MAX) * sizeof(ScanListed));
-    b.tickets = (int32_t *)take(((size_t)N / 32 + 1) * 4);
+    const size_t points = N < SCAN_RECORDS ? N : SCAN_RECORDS;  // of a launch
+    b.list = (ScanListed *)take((points + SCAN_LISTS * SETTLE_ROWS_MAX) * sizeof(ScanListed));
+    b.tickets = (int32_t *)take((points / 32 + 1) * 4);
     b.bytes = off;
     return b;
 }
@@ -1666,11 +1688,12 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
 #undef FTK_LAUNCH_RESOLVE
 }
 
+// tiles: those of the image to prepare (0: they are)
 template <typename T>
-static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,
+static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w, int tiles,
                                 hipStream_t st)
 {
-    const dim3 cg((unsigned)p.tiles_pad), cb((unsigned)(p.nb < 16 ? 64 * p.nb : 1024));
+    const dim3 cg((unsigned)tiles), cb((unsigned)(p.nb < 16 ? 64 * p.nb : 1024));
     // a contiguous list where refine_kernel takes it over
     int32_t *const counts = p.resolve ? b.list_count : w.wl_count;
     const int lists = p.resolve ? SCAN_LISTS : 1;
@@ -1685,7 +1708,8 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
 #define FTK_LAUNCH_CENTROIDS(F)                                                                                       \
     hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, has_ref ? ref_bytes : 0, st, (const T *)c.C, c.D, c.K, p.nb, \
                        b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref, b.norm, lift)
-    if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
+    if (tiles == 0) FTK_TRY(launch_zero_ints(counts, (lists - 1) * LIST_STRIDE + 1, st));  // the preparation does that
+    else if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
     else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE);
     else FTK_LAUNCH_CENTROIDS(FORM_PAIR);
 #undef FTK_LAUNCH_CENTROIDS
@@ -1772,7 +1796,22 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
 
 ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w, hipStream_t st)
 {
-    return c.dtype == FTK_F32 ? launch_scan_t<float>(c, p, b, w, st) : launch_scan_t<double>(c, p, b, w, st);
+    const size_t esz = c.dtype == FTK_F32 ? 4 : 8;
+    const int64_t rest = c.N % p.batch;
+    ScanPlan last = rest ? cut_scan(c.dtype, rest, c.D, c.K) : p;  // fewer points may be cut into smaller chunks
+    int tiles = p.tiles_pad > last.tiles_pad ? p.tiles_pad : last.tiles_pad;
+    for (int64_t r0 = 0; r0 < c.N; r0 += p.batch) {
+        AssignCall part = c;
+        part.N = c.N - r0 < p.batch ? c.N - r0 : p.batch;
+        part.X = (const char *)c.X + (size_t)r0 * c.D * esz;
+        part.labels = c.labels + r0;
+        if (c.mindist) part.mindist = (char *)c.mindist + (size_t)r0 * esz;
+        const ScanPlan &cut = part.N < p.batch ? last : p;
+        FTK_TRY(c.dtype == FTK_F32 ? launch_scan_t<float>(part, cut, b, w, tiles, st)
+                                   : launch_scan_t<double>(part, cut, b, w, tiles, st));
+        tiles = 0;
+    }
+    return FTK_OK;
 }
 
 }  // namespace ftk

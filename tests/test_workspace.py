@@ -59,3 +59,36 @@ def test_unprotected_calls_in_a_workspace_of_a_protected_mode(dtype, N, D, K):
     out = ftk.kmeans_fit(Xd, K, 1, C_init=Cd, workspace=ws)
     assert torch.equal(out["C"], C_new) and torch.equal(out["labels"], labels)
     assert bool((whole[start + size:] == 0x5a).all()) and bool((whole[:start] == 0x5a).all())
+
+
+@pytest.mark.parametrize("dtype,N,D,K", [(ftk.F32, 1 << 21, 256, 16384), (ftk.F64, 1 << 20, 512, 8192), (ftk.F32, 1 << 24, 132, 33000)])
+def test_records_of_the_scan_do_not_grow_with_points_times_centroids(dtype, N, D, K):
+    """64 MB of records, 8 bytes a listed point, a copy of the centroids, the tables of the bucketed update."""
+    more = ftk.workspace_bytes(dtype, N, D, K, ftk.FT_OFF) - ftk.workspace_bytes(dtype, N, D, K, ftk.FT_STRICT)
+    assert more <= 256 * MB
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 4300001, 4, 768), ("f32", 70001, 132, 20000), ("f64", 30011, 1160, 40000)])
+def test_scan_in_several_launches(dtype, N, D, K):
+    """More points than one launch has records for: rows on both sides of the launches' ends, and points to
+    settle (equal centroids) in each of them."""
+    print("several launches", dtype, N, D, K, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    t = torch.float32 if dtype == "f32" else torch.float64
+    C = torch.randn(K, D, generator=gen, device="cuda", dtype=t) * 5
+    C[K - 100:] = C[:100]
+    pick = torch.randint(K, (N,), generator=gen, device="cuda")
+    pick[::97] = K - 1 - (pick[::97] % 100)
+    X = torch.randn(N, D, generator=gen, device="cuda", dtype=t) * 0.1 + C[pick]
+    stats = ftk.new_stats("cuda:0")
+    labels, mind = ftk.kmeans_assign(X, C, stats=stats)
+    torch.cuda.synchronize()
+    assert ftk.stats_dict(stats)["refined"] >= N // 97
+    rows = torch.unique(torch.cat([torch.arange(0, N, max(1, N // 150)), torch.arange(0, N - 4, 2048)[:: max(1, N // 2048 // 60)] + 1,
+                                   torch.arange(N - 20, N), torch.arange(0, N, 97)[:: max(1, N // 97 // 60)]]))
+    Xr, Cn = X[rows.cuda()].cpu().numpy(), C.cpu().numpy()
+    ref = oracle.assign(Xr, Cn)
+    assert np.array_equal(labels.cpu().numpy()[rows], ref[0])
+    err = np.abs(mind.cpu().numpy()[rows].astype(np.float64) - ref[1])
+    assert np.all(err <= 2 * (D + 4) * (2.0 ** -24 if dtype == "f32" else 2.0 ** -53) * ref[1])
