@@ -86,7 +86,8 @@ typedef struct {
                                 produces it                                               */
     uint64_t refined;        /* points whose best scores were closer than the rounding-
                                 error bound and were re-evaluated exactly by the refine
-                                kernel                                                    */
+                                kernel (none in small unprotected calls, which evaluate
+                                every distance exactly)                                   */
     uint64_t max_residual_ppm; /* largest fault-free checksum residual seen, in millionths
                                 of the detection threshold (maximised, not added)        */
 } ftk_ft_stats;
@@ -317,7 +318,7 @@ ftk_status ftk_seeded_indices(uint64_t seed, int64_t N, int32_t K, int64_t *idx_
 
 /* Profiling aid for benchmarks.  While enabled, every ftk_kmeans_assign call brackets its main
  * contraction kernel (not the small norm / refine kernels around it; on the scan path: the scan with
- * its preparation and settlement) with a pair of HIP events
+ * its preparation and settlement; in a small unprotected fit: the one launch of an iteration) with a pair of HIP events
  * recorded on the call's stream.  ftk_profile_read waits for all recorded pairs, returns the
  * summed kernel time in milliseconds and the number of launches since the last read (host
  * pointers), and releases the events.  Not thread-safe; creates events, so keep it out of

@@ -309,6 +309,28 @@ static ftk_status check_device()
 static bool g_profile = false;
 static std::vector<std::pair<hipEvent_t, hipEvent_t>> g_profile_events;
 
+ftk_status profile_begin(ProfileMark &m, hipStream_t st)
+{
+    m = ProfileMark{};
+    // at most 65536 pending pairs: a caller that enables profiling and never reads stops recording
+    if (!g_profile || g_profile_events.size() >= 65536) return FTK_OK;
+    FTK_TRY_HIP(hipEventCreate(&m.from));
+    if (hipError_t e = hipEventCreate(&m.to); e != hipSuccess) {
+        (void)hipEventDestroy(m.from);
+        return hip_failed(e, "hipEventCreate");
+    }
+    FTK_TRY_HIP(hipEventRecord(m.from, st));
+    return FTK_OK;
+}
+
+ftk_status profile_end(const ProfileMark &m, hipStream_t st)
+{
+    if (!m.to) return FTK_OK;
+    g_profile_events.emplace_back(m.from, m.to);  // owned by the list from here on
+    FTK_TRY_HIP(hipEventRecord(m.to, st));
+    return FTK_OK;
+}
+
 // own_scratch: `w` holds the assignment's buffers alone (and w.scan, if there is room)
 static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream_t st, bool fast = false,
                               bool own_scratch = false)
@@ -336,17 +358,8 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
         p = plan_assign(c.dtype, c.N, c.D, c.K, c.ft, aligned16);
     }
     if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(c, p, w, st));
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    // at most 65536 pending pairs: a caller that enables profiling and never reads stops recording
-    const bool profile = g_profile && !own_scratch && g_profile_events.size() < 65536;
-    if (profile) {
-        FTK_TRY_HIP(hipEventCreate(&e0));
-        if (hipError_t e = hipEventCreate(&e1); e != hipSuccess) {
-            (void)hipEventDestroy(e0);
-            return hip_failed(e, "hipEventCreate");
-        }
-        FTK_TRY_HIP(hipEventRecord(e0, st));
-    }
+    ProfileMark mark = {};
+    if (!own_scratch) FTK_TRY(profile_begin(mark, st));
     if (small)
         FTK_TRY(launch_small_assign(c, st));
     else if (scan.ok)
@@ -355,10 +368,7 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
         FTK_TRY(launch_assign_fast(c, p, w, st));
     else
         FTK_TRY(launch_assign(c, p, w, st));
-    if (profile) {
-        g_profile_events.emplace_back(e0, e1);  // owned by the list from here on
-        FTK_TRY_HIP(hipEventRecord(e1, st));
-    }
+    FTK_TRY(profile_end(mark, st));
     if (small || scan.ok) return FTK_OK;  // no list is left
     const int n_wg = (!fast && c.stats && p.variant == VAR_GENERIC) ? (int)p.workgroups : 0;
     FTK_TRY(launch_refine(c, w, n_wg, st));

@@ -119,6 +119,13 @@ int64_t update_slab_cells_max(int64_t N, int D, int K);
 int64_t update_walkers_max(int64_t N);
 int64_t update_bucket_cells(ftk_dtype dtype, int64_t N, int D, int K, int64_t *counts);
 
+// Events around the kernels that ftk_profile_read sums up (null while profiling is off).
+struct ProfileMark {
+    hipEvent_t from, to;
+};
+ftk_status profile_begin(ProfileMark &m, hipStream_t st);
+ftk_status profile_end(const ProfileMark &m, hipStream_t st);
+
 // ---- launches (each returns after enqueueing on `st`) ------------------------------------
 struct AssignCall {
     ftk_dtype dtype;

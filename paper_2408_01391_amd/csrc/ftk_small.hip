@@ -364,8 +364,11 @@ ftk_status launch_small_fit(ftk_dtype dtype, const void *X, int64_t N, int D, in
         a.partials = partials + (t & 1) * SM_GRID;
         a.partials_prev = t == 0 ? nullptr : partials + ((t - 1) & 1) * SM_GRID;
         a.inertia_prev = t == 0 ? nullptr : inertia + t - 1;
+        ProfileMark mark;
+        FTK_TRY(profile_begin(mark, st));
         if (dtype == FTK_F32) launch_small_t<float, true>(a, grid, st);
         else launch_small_t<double, true>(a, grid, st);
+        FTK_TRY(profile_end(mark, st));
     }
     const dim3 g((unsigned)ceil_div((int64_t)cells > K ? (int64_t)cells : K, 256));
     const int last = iters - 1;

@@ -72,3 +72,17 @@ def test_small_fit_keeps_an_empty_cluster_and_repeats_itself():
     b = ftk.kmeans_fit(to_dev(X), 5, 4, C_init=to_dev(C0))
     assert int(a["counts"][4]) == 0 and np.array_equal(a["C"][4].cpu().numpy(), C0[4])
     assert torch.equal(a["C"], b["C"]) and torch.equal(a["labels"], b["labels"])
+
+
+@pytest.mark.parametrize("N,D,K", [(4096, 16, 8), (30000, 17, 300)])
+def test_fits_of_either_kind_are_profiled_once_an_iteration(N, D, K):
+    X, _ = synth.random_problem(2, N, D, K, "f32")
+    Xd, C0 = to_dev(X), to_dev(X[:K])
+    ftk.profile_enable(True)
+    try:
+        ftk.profile_read()
+        ftk.kmeans_fit(Xd, K, 5, C_init=C0)
+        ms, launches = ftk.profile_read()
+    finally:
+        ftk.profile_enable(False)
+    assert launches == 5 and ms > 0.0
