@@ -946,7 +946,8 @@ struct ResolveArgs {
     const double *scale;
     ScanRecord *rec;
     int64_t N;
-    int D, K, nb, tiles, splits;
+    int D, K, tiles, splits;
+    int nb;             // blocks of a row, 0 where the fragments of 32 points do not fit LDS
     int side;           // workgroups that run side by side
     int32_t *labels;
     const ScanListed *list;
@@ -986,34 +987,44 @@ __device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, in
     return group_sum<L>(d);
 }
 
-// the same for P points against one centroid, whose elements are read once
-template <typename T, int L, int P>
-__device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *c, int D, int sub, double (&d)[P])
+// the same for P points against R centroids, whose elements are read once
+template <typename T, int L, int P, int R>
+__device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *const (&c)[R], int D, int sub, double (&d)[P][R])
 {
     const int Dq = D & ~3;
 #pragma unroll
-    for (int i = 0; i < P; ++i) d[i] = 0.0;
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int r = 0; r < R; ++r) d[i][r] = 0.0;
+#pragma unroll 2
     for (int f = 4 * sub; f < Dq; f += 4 * L) {
-        const Quad<T> cv = load_quad<T>(c + f);
-        Quad<T> xv[P];
+        Quad<T> xv[P], cv[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) cv[r] = load_quad<T>(c[r] + f);
 #pragma unroll
         for (int i = 0; i < P; ++i) xv[i] = load_quad<T>(x[i] + f);
 #pragma unroll
         for (int i = 0; i < P; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double t = (double)xv[i].v[e] - (double)cv.v[e];
-                d[i] = fma(t, t, d[i]);
-            }
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double t = (double)xv[i].v[e] - (double)cv[r].v[e];
+                    d[i][r] = fma(t, t, d[i][r]);
+                }
     }
     for (int f = Dq + sub; f < D; f += L)
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            const double t = (double)x[i][f] - (double)c[f];
-            d[i] = fma(t, t, d[i]);
-        }
+        for (int i = 0; i < P; ++i)
 #pragma unroll
-    for (int i = 0; i < P; ++i) d[i] = group_sum<L>(d[i]);
+            for (int r = 0; r < R; ++r) {
+                const double t = (double)x[i][f] - (double)c[r][f];
+                d[i][r] = fma(t, t, d[i][r]);
+            }
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int r = 0; r < R; ++r) d[i][r] = group_sum<L>(d[i][r]);
 }
 
 constexpr int RS_THREADS = 512, RS_WAVES = RS_THREADS / 64, RS_CAP = 8;
@@ -1233,14 +1244,16 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     };
     if (a.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&a.stats->refined, (unsigned long long)n);
     if ((int)blockIdx.x / S >= (int)gridDim.x / S) return;  // a remainder of the grid
-    for (int64_t at = (int64_t)((int)blockIdx.x / S) * 32; at < n; at += (int64_t)((int)gridDim.x / S) * 32) {
-        const int first = (int)at, np = min(32, n - first);
+    // points per group: 32, or fewer of the rows that meet all centroids right away, while that leaves workgroups idle
+    const int per_group = a.nb ? 32 : max(1, min(32, (n + a.side - 1) / a.side));
+    for (int64_t at = (int64_t)((int)blockIdx.x / S) * per_group; at < n; at += (int64_t)((int)gridDim.x / S) * per_group) {
+        const int first = (int)at, np = min(per_group, n - first);
         __syncthreads();  // the previous group is written out
         if (tid < 32) {
             const ScanListed e = listed_point(first + min(tid, np - 1));
             sh_p[tid] = e.point;
             sh_thr[tid] = e.thr;
-            sh_cnt[tid] = 0;
+            sh_cnt[tid] = a.nb ? 0 : RS_CAP + 1;  // rows too long for that: all centroids
         }
         __syncthreads();
         const RowReader<T, true> row(X + (int64_t)sh_p[col] * a.D, a.D);
@@ -1423,8 +1436,11 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
             __syncthreads();
         };
         collect();
-        // (a single point meets all centroids faster below)
-        if (const int nleft = sh_nleft; nleft > 1) {
+        // A few points meet all centroids faster below: one, or of rows beyond 1152 features up to eight (7382 x 2419,
+        // K = 289, 7 points a group 580 us a call against 592; 20000 x 2000, K = 256, 14 points 853 against 664).
+        // Of long fp32 rows the matrix instructions can tell little more than the scan: their band is
+        // 3 (D + 4) u of the norms squared, the scan's some (560 + 4 D) u.
+        if (const int nleft = sh_nleft; nleft > (a.nb ? 1 : 8) && (sizeof(T) == 8 || a.D <= 256)) {
             native_sweep<T>(X, C, a.D, a.K, sh_p, sh_left, nleft, sh_native);
             __syncthreads();
             if (tid < nleft) {
@@ -1444,8 +1460,8 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
             collect();
         }
         // what is left: every centroid in double, up to four points at a time
-        auto compare_all = [&](auto count, int k0) {
-            constexpr int P = decltype(count)::value;
+        auto compare_all = [&](auto count, auto rows, int k0) {
+            constexpr int P = decltype(count)::value, R = decltype(rows)::value;  // R centroids at once: loads in flight
             const T *x[P];
             double best[P];
             int bj[P];
@@ -1455,14 +1471,21 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
                 best[i] = __builtin_huge_val();
                 bj[i] = 0x7fffffff;
             }
-            for (int j = grp; j < a.K; j += GROUPS) {
-                double d[P];
-                group_sqdists<T, L, P>(x, C + (size_t)j * a.D, a.D, sub, d);
+            for (int j0 = grp; j0 < a.K; j0 += R * GROUPS) {
+                const T *c[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) c[r] = C + (size_t)min(j0 + r * GROUPS, a.K - 1) * a.D;
+                double d[P][R];
+                group_sqdists<T, L, P, R>(x, c, a.D, sub, d);
 #pragma unroll
                 for (int i = 0; i < P; ++i)
-                    if (d[i] < best[i]) {  // j increases: the first of equal ones stays
-                        best[i] = d[i];
-                        bj[i] = j;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const int j = j0 + r * GROUPS;
+                        if (j < a.K && d[i][r] < best[i]) {  // j increases: the first of equal ones stays
+                            best[i] = d[i][r];
+                            bj[i] = j;
+                        }
                     }
             }
             __syncthreads();  // the results of the points before these have been read
@@ -1496,8 +1519,8 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
             }
         };
         for (int k0 = 0; k0 < sh_nleft; k0 += 4) {
-            if (sh_nleft - k0 == 1) compare_all(std::integral_constant<int, 1>{}, k0);
-            else compare_all(std::integral_constant<int, 4>{}, k0);
+            if (sh_nleft - k0 == 1) compare_all(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, k0);
+            else compare_all(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}, k0);
         }
     }
 }
@@ -1587,7 +1610,11 @@ static ScanPlan cut_launch(ftk_dtype dtype, int64_t N, int D, int K)
         p.splits = (int)ceil_div(p.nch, p.cps);
     }
     p.tiles_pad = p.nch * p.tpc;
-    p.resolve = p.nb <= 72;  // 32 points' fragments fit in LDS; longer rows go to refine_kernel
+    // 32 points' fragments fit in LDS.  Of longer rows fp64 points go straight to the fp64 matrix instructions, which
+    // tell what the scan cannot; those of fp32 can little more on such rows, and refine_kernel takes fewer points
+    // better (all centroids in double; uniform data of 7382 x 2419, K = 289: fp64 580 us against 1668 by
+    // refine_kernel and 691 by the fp64 matrix kernel, fp32 2000 x 1300, K = 4000 13.5 ms against 0.9).
+    p.resolve = p.nb <= 72 || dtype == FTK_F64;
     return p;
 }
 
@@ -1671,10 +1698,10 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
     if (!p.resolve) return;
     const int64_t groups = ceil_div(c.N, 32);
     // any share of a group among 1 .. splits workgroups divides the grid's work: see the kernel
-    const int64_t most = groups * r.splits;
+    const int64_t most = r.nb ? groups * r.splits : c.N;
     const dim3 grid((unsigned)(most < 1024 ? most : 1024)), block(RS_THREADS);
 #define FTK_LAUNCH_RESOLVE(F)                                                                                        \
-    hipLaunchKernelGGL((scan_resolve_kernel<T, F, L>), grid, block, (size_t)p.nb * form_pieces(F) * FRAG_UNITS * 16, \
+    hipLaunchKernelGGL((scan_resolve_kernel<T, F, L>), grid, block, (size_t)r.nb * form_pieces(F) * FRAG_UNITS * 16, \
                        st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, r)
     if constexpr (L <= 2) {
         if (p.form == FORM_OCTET) FTK_LAUNCH_RESOLVE(FORM_OCTET);
@@ -1776,9 +1803,9 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     r.N = c.N;
     r.D = c.D;
     r.K = c.K;
-    r.nb = p.nb;
+    r.nb = p.nb <= 72 ? p.nb : 0;
     r.tiles = p.tiles;
-    r.splits = p.splits < 16 ? p.splits : 16;
+    r.splits = r.nb ? (p.splits < 16 ? p.splits : 16) : 1;
     r.side = p.nb > 40 ? 256 : 512;  // the fragments of 32 points: one workgroup per compute unit beyond 80 KB
     r.labels = c.labels;
     r.list = b.list;

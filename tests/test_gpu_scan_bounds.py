@@ -103,7 +103,8 @@ def test_one_far_centroid_lists_no_more_points(D, at, dtype):
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("N,D,K", [(300, 4, 800), (40000, 9, 900), (2000, 17, 777), (40, 45, 800), (20000, 64, 1000),
-                                   (700, 131, 800), (33, 513, 1500)])
+                                   (700, 131, 800), (33, 513, 1500),
+                                   (12000, 1160, 300), (90, 1201, 800)])
 @pytest.mark.parametrize("kind", ["groups", "one feature", "groups with copies"])
 def test_points_with_many_candidates(N, D, K, dtype, kind):
     """More centroids within the scan's bound than it notes: settled on the fp32 / fp64 matrix instructions
