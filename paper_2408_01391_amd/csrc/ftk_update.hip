@@ -23,6 +23,8 @@
 namespace ftk {
 
 constexpr int UPD_CELLS = 8192;  // int64 cells per workgroup slice (64 KB)
+constexpr size_t UPD_LDS = 152 * 1024;  // most of a compute unit's 160 KB for a slice's padded rows and member counts
+constexpr size_t upd_lds(int Ks, int Ds) { return (size_t)Ks * (Ds + 1) * 8 + (size_t)Ks * 4; }
 constexpr int UPD_TARGET_WGS = 256;  // one 1024-thread workgroup per CU: every extra table is one more slab to write and re-read
 constexpr int UPD_THREADS = 1024;  // threads per workgroup of the LDS path: many waves per 64 KB table hide the HBM latency
 
@@ -58,7 +60,7 @@ static UpdatePlan plan_update(ftk_dtype dtype, const void *X, int64_t N, int D, 
     const int E = dtype == FTK_F32 ? 4 : 2;
     u.aligned = (D % E == 0) && ((uintptr_t)X % 16 == 0);
     const int line = dtype == FTK_F32 ? 32 : 16;  // features per 128-byte line
-    if ((int64_t)K * D <= UPD_CELLS) {
+    if ((int64_t)K * D <= UPD_CELLS && upd_lds(K, D) <= UPD_LDS) {
         u.Ks = K;
         u.Ds = D;
     } else {
@@ -69,6 +71,8 @@ static UpdatePlan plan_update(ftk_dtype dtype, const void *X, int64_t N, int D, 
         if (ds < 1) ds = 1;
         u.Ds = ds;
         int ks = UPD_CELLS / ds;
+        // (one feature: the pad doubles the rows, and 8192 of them with their counts would not fit)
+        if (upd_lds(ks, ds) > UPD_LDS) ks = (int)(UPD_LDS / upd_lds(1, ds));
         u.Ks = ks < K ? (ks < 1 ? 1 : ks) : K;
     }
     u.nds = (int)ceil_div(D, u.Ds);
@@ -1338,7 +1342,7 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
             set_error("internal: update tables exceed the workspace bound (chunks %d)", u.chunks);
             return FTK_EINVAL;
         }
-        const size_t lds = (size_t)u.Ks * (u.Ds + 1) * 8 + (size_t)u.Ks * 4;
+        const size_t lds = upd_lds(u.Ks, u.Ds);
         dim3 grid(u.chunks, u.nds * u.nks), block(UPD_THREADS);
         long long *slabs = reinterpret_cast<long long *>(w.upd_slab);
         const int64_t scale_rows = dtype == FTK_F64 ? u.rows_per_chunk : N;
@@ -1400,7 +1404,7 @@ ftk_status launch_update_batch(ftk_dtype dtype, const void *Xb, const int32_t *l
                                const double *absmax, const Workspace &w, const BatchedUpdatePlan &b, bool first,
                                hipStream_t st)
 {
-    const size_t lds = (size_t)b.Ks * (b.Ds + 1) * 8 + (size_t)b.Ks * 4;
+    const size_t lds = upd_lds(b.Ks, b.Ds);
     dim3 grid(b.chunks, b.nds * b.nks), block(UPD_THREADS);
     long long *slabs = reinterpret_cast<long long *>(w.upd_slab);
     const int64_t rows_per_chunk = ceil_div(nb, b.chunks);

@@ -66,3 +66,24 @@ def test_bucketed_update_skips_labels_out_of_range():
     C_o, n_o = oracle.update(X[keep], labels[keep], C)
     assert np.array_equal(counts, n_o)
     check_centroids(C_g, C_o)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("N,D,K", [(2530, 1, 7782), (2530, 1, 7783), (300, 1, 8192), (70000, 1, 12797), (7, 1, 8541), (900, 2, 8192)])
+def test_update_of_one_feature_with_many_clusters(N, D, K, dtype):
+    """A table row of one feature and its pad, times 8192 clusters with their counts, is more LDS than there is."""
+    rng = np.random.default_rng(N + K)
+    print("one feature", N, D, K, dtype.__name__, flush=True)
+    X = rng.normal(size=(N, D)).astype(dtype)
+    labels = rng.integers(0, K, N).astype(np.int32)
+    labels[0] = K - 1
+    C = rng.normal(size=(K, D)).astype(dtype)
+    C_o, n_o = oracle.update(X, labels, C)
+    C_g, counts = update(X, labels, C)
+    assert np.array_equal(counts, n_o)
+    check_centroids(C_g, C_o)
+    Cd = to_dev(C).clone()
+    lab, _, cnt = ftk.kmeans_step_batched(to_dev(X), Cd, max(1, N // 3))
+    C_s, n_s = oracle.update(X, lab.cpu().numpy(), C)
+    assert np.array_equal(cnt.cpu().numpy(), n_s)
+    check_centroids(Cd.cpu().numpy(), C_s)
