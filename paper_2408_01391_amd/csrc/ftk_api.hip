@@ -153,13 +153,16 @@ static bool route_small(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft
 // returns direct-difference distances is faster (whole calls, its own kernel / the other): rows of 9 .. 32
 // features scan at any K (1.5 * 10^6 x 32, K = 64 330 / 95 us, K = 512 516 / 194), wider ones from K = 512 (2 * 10^5 x
 // 128 217 / 125; K = 192 92 / 80, but 64 features 42 / 46 at K = 96).  Rows of up to 8: the fp32 kernel up to 512
-// centroids (2 * 10^5 x 8, K = 64 31 / 19), beyond that the scan while there are few points (20000, K = 4096 106 /
-// 45; 1.5 * 10^6, K = 1024 163 / 195).
+// centroids (2 * 10^5 x 8, K = 64 31 / 19), beyond that, while there are few points, the scan where it is faster than that
+// kernel (20000, K = 4096 106 / 45; 97801 x 4, K = 758: own 30.7, scan 35.0, fp32 28.4; 1.5 * 10^6, K = 1024 163 / 195).
 enum FastRoute { FAST_OWN, FAST_SMALL, FAST_FP32, FAST_SCAN };
 static FastRoute fast_rule(int64_t N, int D, int K)
 {
     if (small_assign_pays(FTK_F32, N, D, K)) return FAST_SMALL;
-    if (D <= 8) return K <= 512 ? FAST_FP32 : (N < 100000 ? FAST_SCAN : FAST_OWN);
+    if (D <= 8) {
+        if (K <= 512) return FAST_FP32;
+        return N >= 100000 ? FAST_OWN : (plan_scan(FTK_F32, N, D, K).ok ? FAST_SCAN : FAST_FP32);
+    }
     return D <= 32 || K >= 512 ? FAST_SCAN : FAST_OWN;
 }
 static FastRoute route_fast(int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)

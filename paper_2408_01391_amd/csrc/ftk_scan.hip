@@ -1532,37 +1532,58 @@ static int resident_blocks(int D)
     return nb <= 4 ? nb : (nb <= 6 ? 6 : 8);
 }
 
-// Where the scan beats the fp32 / fp64 matrix kernels: they read X once, keep it in registers and
-// settle in place, the scan reads it twice in four launches, so it takes enough centroids (or enough
-// points, for their matrix work to outweigh two launches).  Whole calls, matrix kernels against scan:
-//   fp32   K = 32    loses everywhere (0.55 .. 0.85)
-//          K = 100   D = 128: N = 1 000 34 / 28 us, 2 * 10^4 35 / 34, 10^6 333 / 260; D = 16: 2 * 10^4 14 / 19,
-//                    10^6 83 / 57; D = 8: 10^6 45 / 47
-//                    N = 10^5: D = 16 19 / 22, D = 64 35 / 39; K = 200, D = 24 29 / 33
-//          K = 256   D = 16: N = 2 * 10^4 25 / 22, 10^6 111 / 69; D = 8: 16 / 19, 10^6 63 / 59
-//          K = 1024  D = 4: N = 2 * 10^4 33 / 24, 2 * 10^5 51 / 46; D = 64: 10^6 1104 / 382
-//   fp64   K = 100   D = 64: N = 2 * 10^5 79 / 65, 2 * 10^4 23 / 32; D = 256: 2 * 10^5 251 / 276
-//          K = 256   D = 32: N = 2 * 10^4 25 / 26, 2 * 10^5 87 / 49; D = 256: 2 * 10^5 494 / 295
-//          K = 1024  D = 4: N = 2 * 10^4 34 / 25; D = 64: 2 * 10^5 518 / 131
-//          small N: 1400 x 447, K = 528 418 / 71; 5000 x 64, K = 256 34 / 30; 20000 x 32, K = 500 43 / 32, but
-//          20000 x 128, K = 256 55 / 59
-//   fp32 rows that are not whole 16-byte pieces, which the matrix kernel loads element by element:
-//          60000 x 867, K = 20 424 / 119; 60000 x 111, K = 8 35 / 33; 6000 x 337, K = 8 150 / 41;
-//          4 * 10^5 x 45, K = 50 70 / 52, but 60000 x 45, K = 20 21 / 24
+// From how many centroids on the scan beats the fp32 / fp64 matrix kernels.  They read X once, keep it in
+// registers and settle in place; the scan reads it twice in four launches but multiplies 16 (32) times as fast, so
+// what counts is the matrix work, and how it lies on the chip:
+//   few points (up to 36 000): neither fills it.  A matrix kernel's time is one workgroup's sweep over K, the scan
+//                cuts the sweep up; long rows make the sweep longer, so the line falls with D.
+//   around 60 000: the matrix kernels fill it once, the scan's launches show, and the line is highest.
+//   from 110 000 (450 000) on: both fill it; launches do not count, and the line is where the matrix work
+//                exceeds the second read of X.
+// fp64 falls lower than fp32 as its matrix instructions are half as fast.  Measured on 2487 calls (15 widths of 4 ..
+// 1024, 14 counts of 8 .. 2048, 7 numbers of points of 300 .. 10^6, blobs and uniform data), matrix kernel / scan, just
+// below and on the line, us:
+//   fp32  D = 128  N = 1500 K = 64 20.2 / 23.7, 96 26.3 / 24.4; N = 60000 K = 128 28.8 / 34.5, 256 47.2 / 38.6;
+//                  N = 200000 K = 64 50.3 / 57.5, 96 71.0 / 61.2
+//         D = 16   N = 20000 K = 512 31.5 / 23.6; N = 60000 K = 256 21.8 / 21.9, 512 31.6 / 25.1; N = 10^6 K = 64 43.5 / 51.5, 96 69.0 / 56.4
+//         D = 4    N = 60000 K = 512 22.8 / 28.4, 1024 33.4 / 32.2; N = 10^6 K = 256 61.1 / 62.2, 512 96.1 / 88.0
+//   fp64  D = 32   N = 20000 K = 192 21.2 / 22.0, 384 33.4 / 23.1; N = 60000 K = 128 22.3 / 23.2, 256 34.5 / 27.3; N = 200000 K = 64 34.0 / 37.6,
+//                  96 47.1 / 38.7
+//         D = 256  N = 6000 K = 128 52.9 / 44.9, 256 96.3 / 46.7; N = 60000 K = 96 76.7 / 83.0, 192 119.2 / 95.1
+static int scan_from(ftk_dtype dtype, int64_t N, int D)
+{
+    static const int from[2][5][6] = {
+        // D < 8, 8, .. 16, .. 48, .. 128, beyond
+        {{768, 512, 256, 160, 96, 48},       // fp32: N < 9 000
+         {768, 512, 320, 176, 160, 80},      //       N < 36 000
+         {1024, 640, 448, 256, 224, 144},    //       N < 110 000
+         {768, 640, 160, 96, 96, 96},        //       N < 450 000
+         {384, 384, 96, 72, 72, 96}},        //       more
+        {{512, 512, 384, 160, 160, 144},     // fp64
+         {512, 512, 384, 288, 272, 160},
+         {512, 512, 320, 192, 224, 160},
+         {96, 96, 96, 96, 96, 144},
+         {48, 48, 48, 72, 80, 144}}};
+    const int d = D < 8 ? 0 : (D == 8 ? 1 : (D <= 16 ? 2 : (D <= 48 ? 3 : (D <= 128 ? 4 : 5))));
+    const int n = N < 9000 ? 0 : (N < 36000 ? 1 : (N < 110000 ? 2 : (N < 450000 ? 3 : 4)));
+    int k = from[dtype == FTK_F32 ? 0 : 1][n][d];
+    // fp32 rows that are not whole 16-byte pieces, which the matrix kernels load element by element: 60000 x 867, K = 20
+    // 424 / 119; 60000 x 111, K = 8 35 / 33; 6000 x 337, K = 8 150 / 41; 4 * 10^5 x 45, K = 50 70 / 52; 200000 x 45, K = 48
+    // 38.5 / 34.5; 200000 x 6, K = 192 33.1 / 28.3; 60000 x 45, K = 192 31.0 / 28.3
+    if (dtype == FTK_F32 && D % 4 != 0) {
+        if (D >= 96) k = 8;
+        else if (n >= 3) k = d == 0 ? 192 : (d == 2 ? 96 : (N >= 300000 ? 32 : 48));
+        else if (n == 2 && d == 3) k = 192;
+    }
+    return k;
+}
+
 static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     if (D < 4 || K < 8) return false;
     // the streaming scan leaves a record per point and 256 centroids: no more than four times the bytes of X
     if (D > 128 && ceil_div(K, 256) * (int64_t)sizeof(ScanRecord) > 4 * (int64_t)D * (dtype == FTK_F32 ? 4 : 8)) return false;
-    if (K >= 768) return true;
-    if (dtype == FTK_F32 && D % 4 != 0 && (D >= 96 || (D > 16 && N >= 300000 && K >= 32))) return true;
-    if (K < 96) return false;
-    if (dtype == FTK_F32) {
-        if (D <= 8) return K >= 512;
-        return K >= 256 || N >= 200000 || (K >= 192 && D >= 32) || D >= 128;
-    }
-    if ((K >= 256 && D >= 64 && (D > 128 || N <= 5000)) || (K >= 384 && D >= 64) || (K >= 448 && D >= 32)) return true;
-    return K >= 192 ? N >= 100000 : (N >= 200000 && D <= 96);
+    return K >= scan_from(dtype, N, D);
 }
 
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K)

@@ -129,3 +129,16 @@ def test_points_with_many_candidates(N, D, K, dtype, kind):
     # distances of this path are direct: D differences, squares and sums, each rounded
     eps = 2.0 ** -24 if dtype == "f32" else 2.0 ** -53
     assert np.all(np.abs(mind.astype(np.float64) - ref[1]) <= 2 * (D + 4) * eps * ref[1] + 1e-5 * ref[1] * (labels != ref[0]))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("N,D,K", [(200003, 4, 769), (60001, 4, 1025), (8999, 8, 1100), (9001, 24, 400), (36001, 64, 230),
+                                   (110001, 16, 170), (1201, 200, 150)])
+def test_scan_on_both_sides_of_its_rule(N, D, K, dtype):
+    """Calls just beyond the lines from which the scan takes over, whatever kernel runs on the near side."""
+    print("rule", N, D, K, dtype, flush=True)
+    for n, k in ((N, K), (N - 3, K - 20)):
+        X, C = offset_blobs(N + D, n, D, k, 3.0, dtype)
+        labels, mind = run(X, C)
+        rows = np.arange(0, n, max(1, n // 4000))
+        check_assign(X, C, labels, mind, rows=rows)
