@@ -190,6 +190,42 @@ struct RowReader {
     }
 };
 
+// Sum over the L lanes of a group (every lane gets it; the same additions whatever the values).
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int L, typename V>
+__device__ __forceinline__ V group_sum(V v)
+{
+    v += dpp_move<0xB1>(v);                            // lane ^ 1
+    if constexpr (L >= 4) v += dpp_move<0x4E>(v);      // lane ^ 2
+    if constexpr (L >= 8) v += dpp_move<0x141>(v);     // the other four of eight
+    if constexpr (L >= 16) v += dpp_move<0x140>(v);    // the other eight of sixteen
+    if constexpr (L >= 32) v += __shfl_xor(v, 16, 64);
+    if constexpr (L >= 64) v += __shfl_xor(v, 32, 64);
+    return v;
+}
+// the largest of 64 lanes, but for those that are not numbers
+template <typename V>
+__device__ __forceinline__ V wave_max(V v)
+{
+    v = fmax(v, dpp_move<0xB1>(v));
+    v = fmax(v, dpp_move<0x4E>(v));
+    v = fmax(v, dpp_move<0x141>(v));
+    v = fmax(v, dpp_move<0x140>(v));
+    v = fmax(v, __shfl_xor(v, 16, 64));
+    return fmax(v, __shfl_xor(v, 32, 64));
+}
+
 // ---- centroids: pieces in fragment order, start values, norms --------------------------------
 // One workgroup per tile of 32 centroids; lane l of a fragment supplies row l % 32 and the 8 features
 // 16b + 8(l/32) of block b (FORM_OCTET: all 8 features).  Each of them forms the reference r and the scale for
@@ -206,10 +242,10 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     __shared__ double sh_n[16][32], sh_rc[16][32];
     __shared__ float sh_n1[16][32], sh_nr[16][32];  // squared norms of the second pieces and of the residuals
     __shared__ T sh_m[16][2];
-    __shared__ double sh_s[16][3];
+    __shared__ double sh_s[16][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = (int)blockDim.x >> 6;
     T m = T(0), whole = T(0);  // largest magnitude of the rows less the reference, and of the rows
-    double off = 0.0, square = 0.0, rr = 0.0;  // their sums of squares without each feature's largest, and ||r||^2
+    double gain = 0.0, rr = 0.0;  // half the rows' sum of squares less that of what is left of them, and ||r||^2
     for (int d = tid; d < D; d += blockDim.x) {
         T c[REF_ROWS], sum = T(0);
 #pragma unroll
@@ -230,11 +266,12 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
             const T a = fabs(c[q] - r), w = fabs(c[q]);
             md = a > md ? a : md;
             wd = w > wd ? w : wd;
-            off = fma((double)a, (double)a, off);
-            square = fma((double)w, (double)w, square);
+            gain = fma(0.5 * (double)w, (double)w, gain);
+            gain = fma(-(double)a, (double)a, gain);
         }
-        off = fma(-(double)md, (double)md, off);
-        square = fma(-(double)wd, (double)wd, square);
+        // (each feature's largest left out of both)
+        gain = fma(-0.5 * (double)wd, (double)wd, gain);
+        gain = fma((double)md, (double)md, gain);
         rr = fma((double)r, (double)r, rr);
         m = md > m ? md : m;
         whole = wd > whole ? wd : whole;
@@ -242,35 +279,28 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     }
     if (has_ref)
         for (int d = D + tid; d < 16 * nb; d += blockDim.x) ref[d] = T(0);
-#pragma unroll
-    for (int k = 32; k >= 1; k >>= 1) {
-        const T o = __shfl_xor(m, k, 64), w = __shfl_xor(whole, k, 64);
-        m = o > m ? o : m;
-        whole = w > whole ? w : whole;
-        off += __shfl_xor(off, k, 64);
-        square += __shfl_xor(square, k, 64);
-        rr += __shfl_xor(rr, k, 64);
-    }
+    m = wave_max(m);
+    whole = wave_max(whole);
+    gain = group_sum<64>(gain);
+    if (blockIdx.x == 0) rr = group_sum<64>(rr);  // the only one to write it
     if (lane == 0) {
         sh_m[wave][0] = m;
         sh_m[wave][1] = whole;
-        sh_s[wave][0] = off;
-        sh_s[wave][1] = square;
-        sh_s[wave][2] = rr;
+        sh_s[wave][0] = gain;
+        sh_s[wave][1] = rr;
     }
     __syncthreads();
-    off = square = rr = 0.0;
+    gain = rr = 0.0;
     for (int i = 0; i < nw; ++i) {
         m = sh_m[i][0] > m ? sh_m[i][0] : m;
         whole = sh_m[i][1] > whole ? sh_m[i][1] : whole;
-        off += sh_s[i][0];
-        square += sh_s[i][1];
-        rr += sh_s[i][2];
+        gain += sh_s[i][0];
+        rr += sh_s[i][1];
     }
     // The reference is taken where it halves the squared norms at least: of data about the origin it is
     // a random vector.  The scale: the largest magnitude goes to [1, 2) - that of the rows themselves where
     // they are all the same.
-    const bool moved = has_ref && off < 0.5 * square;
+    const bool moved = has_ref && gain > 0.0;
     if (!moved || !(m > T(0))) m = whole;
     int e2 = 0;
     if (m > T(0) && m < Mma<T>::huge()) e2 = ilogb(m);
@@ -352,7 +382,7 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
         const int gg = (tid >> 2) & 1, r = 4 * (tid >> 3) + (tid & 3);
         start[tile * 32 + gg * 16 + r] =
             32 * tile + tid < K ? (float)((lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
-        norm[tile * 32 + tid] = (float)sqrt(n);
+        norm[tile * 32 + tid] = sqrtf((float)n);
         // (a NaN row never wins and does not count)
         float f = n > 0.0 ? (float)n : 0.f;
         float q1 = n > 0.0 ? (float)((double)n1 / n) : 0.f, qr = n > 0.0 ? (float)((double)nr / n) : 0.f;
@@ -735,31 +765,6 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
     }
 }
 
-// Sum over the L lanes of a group (every lane gets it; the same additions whatever the values).
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-template <int L, typename V>
-__device__ __forceinline__ V group_sum(V v)
-{
-    v += dpp_move<0xB1>(v);                            // lane ^ 1
-    if constexpr (L >= 4) v += dpp_move<0x4E>(v);      // lane ^ 2
-    if constexpr (L >= 8) v += dpp_move<0x141>(v);     // the other four of eight
-    if constexpr (L >= 16) v += dpp_move<0x140>(v);    // the other eight of sixteen
-    if constexpr (L >= 32) v += __shfl_xor(v, 16, 64);
-    if constexpr (L >= 64) v += __shfl_xor(v, 32, 64);
-    return v;
-}
-
 // ---- settle -----------------------------------------------------------------------------------
 // L lanes share a row (row-contiguous 16-byte loads) and take ROWS of them at once: the pass is a
 // chain of latencies - record, then the centroid's row - that only requests in flight can hide.
@@ -828,8 +833,7 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-#pragma unroll
-        for (int k = 32; k >= 1; k >>= 1) cm[q] = fmaxf(cm[q], __shfl_xor(cm[q], k, 64));
+        cm[q] = wave_max(cm[q]);
         if (lane == 0) sh_max[tid >> 6][q] = cm[q];
     }
     __syncthreads();
