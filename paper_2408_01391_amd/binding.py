@@ -146,9 +146,15 @@ def workspace_bytes(dtype_code: int, N: int, D: int, K: int, ft_mode: int = FT_O
     return n
 
 
-def new_workspace(X: torch.Tensor, K: int, ft_mode: int = FT_CORRECT) -> torch.Tensor:
-    n = workspace_bytes(_dtype_code(X), X.shape[0], X.shape[1], K, ft_mode)
+def _mode_workspace(X: torch.Tensor, K: int, *modes: int) -> torch.Tensor:
+    n = max(workspace_bytes(_dtype_code(X), X.shape[0], X.shape[1], K, m) for m in modes)
     return torch.empty(n + 256, dtype=torch.uint8, device=X.device)
+
+
+def new_workspace(X: torch.Tensor, K: int, ft_mode: int = FT_CORRECT) -> torch.Tensor:
+    """A workspace for calls of ``ft_mode`` and, at their full speed, for unprotected ones beside them (a
+    protected mode alone needs no more than ``workspace_bytes`` reports for it)."""
+    return _mode_workspace(X, K, ft_mode, FT_OFF)
 
 
 def _ws_args(ws: torch.Tensor):
@@ -190,7 +196,7 @@ def kmeans_assign(X, C, labels=None, mindist=None, ft_mode=FT_OFF, faults=None, 
     if mindist is None and want_mindist:
         mindist = torch.empty(N, dtype=X.dtype, device=X.device)
     if workspace is None:
-        workspace = new_workspace(X, K, ft_mode)
+        workspace = _mode_workspace(X, K, ft_mode)
     wp, wn = _ws_args(workspace)
     nf = 0 if faults is None else faults.shape[0]
     _check(load().ftk_kmeans_assign(_dtype_code(X), X.data_ptr(), C.data_ptr(), N, D, K,
@@ -240,7 +246,7 @@ def kmeans_assign_fast(X, C, labels=None, mindist=None, workspace=None, want_min
     if mindist is None and want_mindist:
         mindist = torch.empty(N, dtype=X.dtype, device=X.device)
     if workspace is None:
-        workspace = new_workspace(X, K, ft_mode)
+        workspace = _mode_workspace(X, K, ft_mode)
     wp, wn = _ws_args(workspace)
     nf = 0 if faults is None else faults.shape[0]
     _check(load().ftk_kmeans_assign_fast(_dtype_code(X), X.data_ptr(), C.data_ptr(), N, D, K,
@@ -348,7 +354,7 @@ def kmeans_fit(X, K, iters, seed=0, C_init=None, ft_mode=FT_OFF, stats=None, wor
     counts = torch.empty(K, dtype=torch.int32, device=X.device)
     inertia = np.zeros(iters, dtype=np.float64) if want_inertia else None
     if workspace is None:
-        workspace = new_workspace(X, K, ft_mode)
+        workspace = _mode_workspace(X, K, ft_mode)
     wp, wn = _ws_args(workspace)
     if fast:
         _check(load().ftk_kmeans_fit_fast(_dtype_code(X), X.data_ptr(), N, D, K, iters, seed & (2**64 - 1),

@@ -68,6 +68,14 @@ def test_records_of_the_scan_do_not_grow_with_points_times_centroids(dtype, N, D
     assert more <= 256 * MB
 
 
+def test_new_workspace_serves_unprotected_calls_at_full_speed():
+    X = torch.empty(4000, 40, dtype=torch.float64)
+    size = ftk.workspace_bytes(ftk.F64, 4000, 40, 900, ftk.FT_OFF)
+    assert size > ftk.workspace_bytes(ftk.F64, 4000, 40, 900, ftk.FT_STRICT)
+    for mode in (ftk.FT_OFF, ftk.FT_CORRECT, ftk.FT_STRICT):
+        assert ftk.new_workspace(X, 900, mode).numel() >= size
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,N,D,K", [("f32", 4300001, 4, 768), ("f32", 70001, 132, 20000), ("f64", 30011, 1160, 40000)])
 def test_scan_in_several_launches(dtype, N, D, K):
