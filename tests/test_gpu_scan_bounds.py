@@ -88,6 +88,12 @@ def test_an_offset_of_all_data_lists_no_more_points(D, dtype):
         assert n <= 2 * at_origin + N // 50
 
 
+@pytest.mark.parametrize("dtype,N,D,K", [("f64", 60, 8192, 300), ("f64", 60, 8193, 300), ("f32", 60, 16385, 300), ("f32", 40, 1100, 9000)])
+def test_longest_rows_with_a_reference_and_beyond(dtype, N, D, K):
+    labels, mind = run(*(data := offset_blobs(D, N, D, K, 50.0, dtype)))
+    check_assign(*data, labels, mind)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("at", [0, 517])
 @pytest.mark.parametrize("D", [8, 32, 128, 200])

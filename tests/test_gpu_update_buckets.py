@@ -87,3 +87,30 @@ def test_update_of_one_feature_with_many_clusters(N, D, K, dtype):
     C_s, n_s = oracle.update(X, lab.cpu().numpy(), C)
     assert np.array_equal(cnt.cpu().numpy(), n_s)
     check_centroids(Cd.cpu().numpy(), C_s)
+
+
+# beside the shapes above, of which those with 4 and 8 features do not take this path: its shortest rows, and more
+# sources than the workgroup that adds up has threads
+@pytest.mark.parametrize("N,D,K", [(66001, 12, 8191), (70001, 16, 8192), (8400001, 12, 3001), (16800000, 16, 2100)])
+def test_bucketed_update_of_short_rows_and_of_many_sources(N, D, K):
+    print("bucketed update", N, D, K, flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    X = torch.randn(N, D, generator=gen, device=DEV) * 3 + 1
+    labels = (torch.rand(N, generator=gen, device=DEV) ** 2 * K).to(torch.int32)
+    C = torch.randn(K, D, generator=gen, device=DEV)
+    ws = ftk.new_workspace(X, K)
+    results = []
+    for path in (-1, 1):
+        ftk.tuning_override(-1, -1, path)
+        C_new = C.clone()
+        _, counts = ftk.kmeans_update(X, labels, C_new, workspace=ws)
+        results.append((C_new, counts))
+    torch.cuda.synchronize()
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+    n = torch.bincount(labels.long(), minlength=K)
+    assert torch.equal(n, results[0][1].long())
+    sums = torch.zeros(K, D, dtype=torch.float64, device=DEV)
+    for r in range(0, N, 1 << 20):
+        sums.index_add_(0, labels[r:r + (1 << 20)].long(), X[r:r + (1 << 20)].double())
+    means = torch.where(n[:, None] > 0, sums / n.clamp(min=1)[:, None], C.double())
+    check_centroids(results[0][0].cpu().numpy(), means.float().cpu().numpy())
