@@ -27,7 +27,7 @@ struct ScanRecord {
     int32_t j1;
     int32_t unused;
 };
-// a point to resolve, and the score a centroid needs to be a candidate
+// a point to resolve, and the score a centroid needs to be a candidate (not a number: every centroid is one)
 struct ScanListed {
     int32_t point;
     float thr;

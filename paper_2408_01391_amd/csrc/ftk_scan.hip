@@ -7,7 +7,8 @@
 //           (Section 3.1.1), and the decision whether the scan could be trusted: where the two best
 //           scores are closer than the scan's error bound the point is listed;
 //   resolve the listed points: every centroid whose score lies within the bound of the best is
-//           evaluated in double.
+//           evaluated in double; where there are many of those, all centroids on the matrix instructions
+//           of the data's type, and what these cannot tell apart in double.
 //
 // Results are therefore those of the fp32 / fp64 matrix kernels - labels exact up to the documented
 // ties, distances direct - while the contraction runs on hardware that does 16 (fp32) or 32 (fp64)
@@ -939,7 +940,7 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
 // A workgroup repeats the scan for 32 listed points at a time, now noting every centroid whose score
 // comes within the bound of the best, and evaluates those in direct-difference form in double, lowest
 // index on equal distance.  A point with more of them than are noted (or none: scores that are not
-// numbers) is compared with every centroid.  Listed points are few and scattered, so what counts is the
+// numbers) meets every centroid: see native_sweep(), then in double.  Listed points are few and scattered, so what counts is the
 // time of one group: eight waves share its sweep, the points' fragments sit in LDS, the centroids'
 // come straight from the image (L2), eight blocks in flight.  That read is what a group waits for (60000 x
 // 1024, K = 1024: 4 MB at 64 bytes a clock, 120 us), so `splits` workgroups share the centroids of one
