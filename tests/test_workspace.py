@@ -100,3 +100,40 @@ def test_scan_in_several_launches(dtype, N, D, K):
     assert np.array_equal(labels.cpu().numpy()[rows], ref[0])
     err = np.abs(mind.cpu().numpy()[rows].astype(np.float64) - ref[1])
     assert np.all(err <= 2 * (D + 4) * (2.0 ** -24 if dtype == "f32" else 2.0 ** -53) * ref[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 30001, 32, 3000), ("f64", 20001, 40, 900), ("f32", 1500, 16, 1024),
+                                         ("f32", 4300001, 4, 768), ("f64", 3001, 1160, 2000)])
+def test_captured_assignment_replays_on_new_contents(dtype, N, D, K):
+    """A recorded unprotected assignment (one launch of the scan and several, points that it lists: equal
+    centroids) against the eager call on what the operands hold at each replay."""
+    print("replay", dtype, N, D, K, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    t = torch.float32 if dtype == "f32" else torch.float64
+    X, C = torch.empty(N, D, device="cuda", dtype=t), torch.empty(K, D, device="cuda", dtype=t)
+
+    def fill():
+        C.normal_(generator=gen).mul_(5)
+        C[K - 100:] = C[:100]
+        pick = torch.randint(K, (N,), generator=gen, device="cuda")
+        X.normal_(generator=gen).mul_(0.1).add_(C[pick])
+
+    fill()
+    ws = ftk.new_workspace(X, K, ftk.FT_OFF)
+    labels = torch.empty(N, device="cuda", dtype=torch.int32)
+    mind = torch.empty(N, device="cuda", dtype=t)
+    ftk.kmeans_assign(X, C, labels, mind, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ftk.kmeans_assign(X, C, labels, mind, workspace=ws)
+    for _ in range(4):
+        fill()
+        want = ftk.kmeans_assign(X, C)
+        labels.fill_(-1)
+        mind.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(labels, want[0]) and torch.equal(mind, want[1])
+        assert int(labels.max()) < K - 100
