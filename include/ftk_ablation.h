@@ -69,6 +69,8 @@ int ftk_abl_fused_alu_assign(int dtype, const void *X, const void *C, int64_t N,
  * rounds, which only measurement tells. */
 int ftk_abl_mfma_bf16(const uint16_t *A, const uint16_t *B, const float *C, float *D, int32_t tiles,
                       void *hip_stream);
+/* The same for v_mfma_f32_32x32x16_f16 (A and B as fp16 bit patterns), which the unprotected scan uses. */
+int ftk_abl_mfma_f16(const uint16_t *A, const uint16_t *B, const float *C, float *D, int32_t tiles, void *hip_stream);
 
 /* The same for the instructions of the main path: v_mfma_f32_32x32x2_f32 (A [tiles][32][2],
  * B [tiles][2][32], C and D [tiles][32][32]) and v_mfma_f64_16x16x4_f64 (A [tiles][16][4],

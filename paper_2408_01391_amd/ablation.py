@@ -15,7 +15,7 @@ _lib = None
 
 EXPORTS = ("ftk_abl_naive_assign", "ftk_abl_gemm_workspace_bytes", "ftk_abl_gemm_assign",
            "ftk_abl_fused_alu_workspace_bytes", "ftk_abl_fused_alu_assign", "ftk_abl_mfma_bf16",
-           "ftk_abl_mfma_f32", "ftk_abl_mfma_f64", "ftk_abl_last_error")
+           "ftk_abl_mfma_f16", "ftk_abl_mfma_f32", "ftk_abl_mfma_f64", "ftk_abl_last_error")
 
 
 def load():
@@ -37,8 +37,9 @@ def load():
     L.ftk_abl_fused_alu_workspace_bytes.restype = sz
     L.ftk_abl_fused_alu_assign.argtypes = [i32, vp, vp, i64, i32, i32, vp, vp, i32, vp, sz, vp]
     L.ftk_abl_fused_alu_assign.restype = i32
-    L.ftk_abl_mfma_bf16.argtypes = [vp, vp, vp, vp, i32, vp]
-    L.ftk_abl_mfma_bf16.restype = i32
+    for fn in (L.ftk_abl_mfma_bf16, L.ftk_abl_mfma_f16):
+        fn.argtypes = [vp, vp, vp, vp, i32, vp]
+        fn.restype = i32
     for fn in (L.ftk_abl_mfma_f32, L.ftk_abl_mfma_f64):
         fn.argtypes = [vp, vp, vp, vp, i32, vp]
         fn.restype = i32
@@ -110,17 +111,26 @@ def fused_alu_assign(X, C, variant, labels=None, mindist=None, workspace=None):
     return labels, mindist
 
 
-def mfma_bf16(A_bits, B_bits, C):
-    """D = A B + C by one bf16 matrix instruction per 32x32x16 problem.  A_bits [T,32,16] and B_bits
-    [T,16,32] are int16 tensors holding bf16 bit patterns, C [T,32,32] float32."""
+def _mfma_16bit(fn, A_bits, B_bits, C):
     assert A_bits.is_cuda and A_bits.dtype == torch.int16 and A_bits.is_contiguous() and A_bits.shape[1:] == (32, 16)
     assert B_bits.dtype == torch.int16 and B_bits.is_contiguous() and B_bits.shape[1:] == (16, 32)
     assert C.dtype == torch.float32 and C.is_contiguous() and C.shape[1:] == (32, 32)
     T = A_bits.shape[0]
     assert B_bits.shape[0] == T and C.shape[0] == T
     D = torch.empty_like(C)
-    _check(load().ftk_abl_mfma_bf16(A_bits.data_ptr(), B_bits.data_ptr(), C.data_ptr(), D.data_ptr(), T, _stream()))
+    _check(fn(A_bits.data_ptr(), B_bits.data_ptr(), C.data_ptr(), D.data_ptr(), T, _stream()))
     return D
+
+
+def mfma_bf16(A_bits, B_bits, C):
+    """D = A B + C by one bf16 matrix instruction per 32x32x16 problem.  A_bits [T,32,16] and B_bits
+    [T,16,32] are int16 tensors holding bf16 bit patterns, C [T,32,32] float32."""
+    return _mfma_16bit(load().ftk_abl_mfma_bf16, A_bits, B_bits, C)
+
+
+def mfma_f16(A_bits, B_bits, C):
+    """The same by one fp16 matrix instruction, A_bits and B_bits holding fp16 bit patterns."""
+    return _mfma_16bit(load().ftk_abl_mfma_f16, A_bits, B_bits, C)
 
 
 def mfma_plain(A, B, C):

@@ -4,6 +4,7 @@
 
 #include <cstdarg>
 #include <cstdio>
+#include <type_traits>
 
 #include "ftk_ablation.h"
 
@@ -298,24 +299,28 @@ int fused_alu_t(const void *X, const void *C, int64_t N, int32_t D, int32_t K, i
 // instruction's rounding behaviour - which the fast assignment's error bound is built on and no
 // document states - against the exact sums.
 typedef __bf16 abl_bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 abl_f16x8 __attribute__((ext_vector_type(8)));
 typedef float abl_floatx16 __attribute__((ext_vector_type(16)));
-__global__ __launch_bounds__(64) void abl_mfma_bf16_kernel(const uint16_t *A, const uint16_t *B, const float *C, float *Dout)
+template <typename V>  // abl_bf16x8, or abl_f16x8 for v_mfma_f32_32x32x16_f16, laid out the same
+__global__ __launch_bounds__(64) void abl_mfma_16bit_kernel(const uint16_t *A, const uint16_t *B, const float *C, float *Dout)
 {
+    using E = std::conditional_t<std::is_same_v<V, abl_bf16x8>, __bf16, _Float16>;
     const int lane = threadIdx.x, col = lane & 31, g = lane >> 5;
     const size_t t = blockIdx.x;
     const uint16_t *a = A + t * 32 * 16, *b = B + t * 16 * 32;
     const float *c = C + t * 32 * 32;
     float *d = Dout + t * 32 * 32;
-    abl_bf16x8 av, bv;
+    V av, bv;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        av[e] = __builtin_bit_cast(__bf16, a[col * 16 + 8 * g + e]);
-        bv[e] = __builtin_bit_cast(__bf16, b[(8 * g + e) * 32 + col]);
+        av[e] = __builtin_bit_cast(E, a[col * 16 + 8 * g + e]);
+        bv[e] = __builtin_bit_cast(E, b[(8 * g + e) * 32 + col]);
     }
     abl_floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = c[(8 * (r / 4) + 4 * g + r % 4) * 32 + col];
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
+    if constexpr (std::is_same_v<V, abl_bf16x8>) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
+    else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc, 0, 0, 0);
 #pragma unroll
     for (int r = 0; r < 16; ++r) d[(8 * (r / 4) + 4 * g + r % 4) * 32 + col] = acc[r];
 }
@@ -477,18 +482,33 @@ int ftk_abl_fused_alu_assign(int dtype, const void *X, const void *C, int64_t N,
                       : fused_alu_t<double>(X, C, N, D, K, labels, mindist, variant, (char *)workspace, st);
 }
 
-int ftk_abl_mfma_bf16(const uint16_t *A, const uint16_t *B, const float *C, float *D, int32_t tiles, void *hip_stream)
+}  // extern "C"
+
+template <typename V>
+static int mfma_16bit(const uint16_t *A, const uint16_t *B, const float *C, float *D, int32_t tiles, void *hip_stream)
 {
     if (!A || !B || !C || !D || tiles <= 0) {
         set_err("invalid argument");
         return 1;
     }
-    hipLaunchKernelGGL(abl_mfma_bf16_kernel, dim3((unsigned)tiles), dim3(64), 0, (hipStream_t)hip_stream, A, B, C, D);
+    hipLaunchKernelGGL((abl_mfma_16bit_kernel<V>), dim3((unsigned)tiles), dim3(64), 0, (hipStream_t)hip_stream, A, B, C, D);
     if (hipGetLastError() != hipSuccess) {
         set_err("kernel launch failed");
         return 4;
     }
     return 0;
+}
+
+extern "C" {
+
+int ftk_abl_mfma_bf16(const uint16_t *A, const uint16_t *B, const float *C, float *D, int32_t tiles, void *hip_stream)
+{
+    return mfma_16bit<abl_bf16x8>(A, B, C, D, tiles, hip_stream);
+}
+
+int ftk_abl_mfma_f16(const uint16_t *A, const uint16_t *B, const float *C, float *D, int32_t tiles, void *hip_stream)
+{
+    return mfma_16bit<abl_f16x8>(A, B, C, D, tiles, hip_stream);
 }
 
 int ftk_abl_mfma_f32(const float *A, const float *B, const float *C, float *D, int32_t tiles, void *hip_stream)
