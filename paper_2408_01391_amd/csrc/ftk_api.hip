@@ -171,11 +171,20 @@ static FastRoute route_fast(int64_t N, int D, int K, ftk_ft_mode ft, int n_fault
     return fast_rule(N, D, K);
 }
 
-// bytes of the scan's buffers for the plain or the reduced-precision entry point, whatever kernel is forced
-static size_t scan_bytes(ftk_dtype dtype, int64_t N, int D, int K)
+// bytes of the scan's buffers for the plain or the reduced-precision entry point, whatever kernel is forced;
+// half: with those of its fp16 pieces, without which it runs as well
+static size_t scan_bytes(ftk_dtype dtype, int64_t N, int D, int K, bool half)
 {
     if (!plan_scan(dtype, N, D, K).ok && !(fast_supported(dtype, D) && fast_rule(N, D, K) == FAST_SCAN)) return 0;
-    return carve_scan(nullptr, cut_scan(dtype, N, D, K), N).bytes;
+    ScanPlan p = cut_scan(dtype, N, D, K);
+    p.half = p.half && half;
+    return carve_scan(nullptr, p, N, D).bytes;
+}
+
+static ScanPlan fit_scan(ScanPlan p, const Workspace &w, int64_t N, int D)
+{
+    p.half = p.half && carve_scan(nullptr, p, N, D).bytes <= w.scan_bytes;
+    return p;
 }
 
 // The workspace is carved for the larger of the two kernel variants so that its size does not
@@ -236,12 +245,18 @@ Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, 
     const int64_t bucket_cells = update_bucket_cells(dtype, N, D, K, &bucket_counts);
     w.bucket_slab = (int64_t *)take((size_t)bucket_cells * sizeof(int64_t));
     w.bucket_cslab = (int32_t *)take((size_t)bucket_counts * sizeof(int32_t));
-    w.unprotected = off;
-    for (size_t n : {scan_bytes(dtype, N, D, K), small_fit_bytes(D, K)})
-        if (w.unprotected < shared + n) w.unprotected = shared + n;
+    size_t least = off;  // serves all of them but the scan on fp16 pieces
+    for (size_t n : {scan_bytes(dtype, N, D, K, false), small_fit_bytes(D, K)})
+        if (least < shared + n) least = shared + n;
+    w.unprotected = least;
+    if (const size_t n = scan_bytes(dtype, N, D, K, true); w.unprotected < shared + n) w.unprotected = shared + n;
     w.scan = w.small_fit = nullptr;
-    w.room = p && bytes >= w.unprotected;
-    if (w.room) w.scan = w.small_fit = (void *)(p + shared);
+    w.scan_bytes = 0;
+    w.room = p && bytes >= least;
+    if (w.room) {
+        w.scan = w.small_fit = (void *)(p + shared);
+        w.scan_bytes = bytes - shared;
+    }
     return w;
 }
 
@@ -352,6 +367,7 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
     else if (!fast && froute == FAST_OWN && !small && w.scan)
         scan = route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     AssignPlan p;
+    if (scan.ok) scan = fit_scan(scan, w, c.N, c.D);
     if (small || scan.ok) {
         memset(&p, 0, sizeof(p));
     } else if (fast) {
@@ -366,7 +382,7 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
     if (small)
         FTK_TRY(launch_small_assign(c, st));
     else if (scan.ok)
-        FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N), w, st));
+        FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N, c.D), w, st));
     else if (fast)
         FTK_TRY(launch_assign_fast(c, p, w, st));
     else
@@ -589,7 +605,8 @@ ftk_status ftk_kmeans_assign_static(ftk_dtype dtype, const void *X, const void *
     // the assignment's buffers are a prefix of the layout, the scan's follow them here; a problem that fits the
     // array only without those runs on the fp32 / fp64 kernels
     Workspace w = carve_workspace(scratch, 0, dtype, N, D, K);
-    if (need + scan_bytes(dtype, N, D, K) <= FTK_STATIC_SCRATCH_BYTES) w.scan = (char *)scratch + need;
+    w.scan_bytes = FTK_STATIC_SCRATCH_BYTES - need;
+    if (scan_bytes(dtype, N, D, K, false) <= w.scan_bytes) w.scan = (char *)scratch + need;
     AssignCall c{dtype, X, C, N, D, K, labels, mindist, ft, faults, n_faults, stats};
     return assign_impl(c, w, (hipStream_t)hip_stream, false, true);
 }
@@ -736,7 +753,7 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
     AssignPlan pprev = plan_assign(dtype, whole.N, D, K, FTK_FT_OFF, aligned16);
     // the path is chosen for the whole problem, as in the two-call step
     const bool small = route_small(dtype, N, D, K, FTK_FT_OFF, 0);
-    const ScanPlan scan = small || !w.scan ? ScanPlan{} : route_scan(dtype, N, D, K, FTK_FT_OFF, 0);
+    const ScanPlan scan = small || !w.scan ? ScanPlan{} : fit_scan(route_scan(dtype, N, D, K, FTK_FT_OFF, 0), w, N, D);
     if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
     for (int64_t b = 0; b < nbatch; ++b) {
         const int64_t r0 = b * batch_rows;
@@ -750,7 +767,11 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
             if (small)
                 FTK_TRY(launch_small_assign(c, st));
             else
-                FTK_TRY(launch_scan_assign(c, cut_scan(dtype, nb, D, K), carve_scan(w.scan, scan, N), wb, st));
+            {
+                ScanPlan part = cut_scan(dtype, nb, D, K);
+                part.half = part.half && scan.half;
+                FTK_TRY(launch_scan_assign(c, part, carve_scan(w.scan, scan, N, D), wb, st));
+            }
             FTK_TRY(launch_update_batch(dtype, Xb, labels + r0, nb, D, K, x_absmax, w, ub, b == 0, st));
             continue;
         }

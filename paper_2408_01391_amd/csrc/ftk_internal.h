@@ -102,6 +102,7 @@ struct Workspace {
     size_t total;       // bytes that serve every call
     // faster paths of unprotected calls, in the bytes of the label sort and beyond: NULL / unused without room
     void *scan;         // buffers of the scan (ftk_scan.h)
+    size_t scan_bytes;  // room there
     int64_t *bucket_slab;   // [workgroups][clusters of a bucket * D] tables of the bucketed update
     int32_t *bucket_cslab;  // [workgroups][clusters of a bucket]
     void *small_fit;    // tables of the one-launch Lloyd iteration (ftk_small.h)

@@ -18,6 +18,8 @@ struct ScanPlan {
     int64_t pblocks;    // blocks of 256 points
     int64_t batch;      // points of a launch: the rest of this is cut for those
     int64_t rec_reserve;  // records to reserve
+    bool half;          // a scan on fp16 pieces is prepared too, and runs first
+    int half_nb, half_tiles;  // blocks and tiles of its image
     bool resolve;       // listed points are settled by the scan's own third pass (else refine_kernel)
 };
 
@@ -39,10 +41,14 @@ struct ScanBuffers {
     float *norm;        // [tiles_pad][32] ||c|| (scaled)
     float4 *tile_stat;  // [tiles_pad] largest ||c||^2 (scaled), ||c1||^2 / ||c||^2, ||r_c||^2 / ||c||^2 of a tile
     double *scale;      // [2] the power of two both operands are multiplied by; length of the (scaled) reference
+    void *ref;          // [D] the reference, zero where none is taken
     ScanRecord *rec;    // [splits][N]
     ScanListed *list;   // points to resolve: lists of equal capacity ...
-    int32_t *list_count;  // ... and a counter each
+    int32_t *list_count;  // ... and a counter each (then the state of the choice of form, and the counters of `rest`)
     int32_t *tickets;   // [N/32 + 1] workgroups done with a group of listed points
+    uint4 *half_image;  // [half_tiles][half_nb][64] fp16 pieces, and the start values that go with them
+    float *half_start;
+    ScanListed *rest;   // listed points that go on from the fp16 scan's own third pass
     size_t bytes;
 };
 
@@ -51,7 +57,7 @@ ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // the cut alone, for part of a problem that takes this path
 ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // buffers for the whole problem and for any batch of it
-ScanBuffers carve_scan(void *base, const ScanPlan &whole, int64_t N);
+ScanBuffers carve_scan(void *base, const ScanPlan &whole, int64_t N, int D);
 ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,
                               hipStream_t st);
 

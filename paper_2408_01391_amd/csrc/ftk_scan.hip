@@ -44,6 +44,14 @@
 //     A ||c|| + (psi / 2 - lift) ||c||^2 <= A^2 / (4 lift - 2 psi)
 // too low, whatever its norm, and that of the named centroid at most A ||c|| + (psi / 2 + lift) ||c||^2 too high.
 //
+// Large calls try a cheaper form first, FORM_HALF: one fp16 piece of either operand and one product, a third of the
+// matrix work.  Lost are r_x.c and x.r_c, |r| up to 2^-11 |x|: ||r_c|| / ||c|| is measured by the preparation and ||r_x|| by the settle
+// pass, some 0.45 2^-11 each, which makes the bound some 25 times wider than that of two bf16 pieces and leaves 3 to 10 %
+// of the points for the third pass - with two candidates as a rule, so that it costs a tenth of the scan.  An operand below
+// 2^-14 rounds like that value, in the piece and in the instruction (pinned by a test): norms are raised by 2^-14 for every
+// feature.  Data whose points lie far from the origin or in groups would list nearly all, so the scan's first workgroups vote
+// (ScanGate) before the rest of it runs.
+//
 // Both operands are multiplied by one power of two taken from the same rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
 // the same (overflow, NaN) is found by the settle pass, and such a point is compared with every centroid.
@@ -58,6 +66,7 @@
 namespace ftk {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 // rows need no more than element alignment: 16-byte loads from 4- or 8-byte aligned addresses
 typedef float float4e __attribute__((ext_vector_type(4), aligned(4)));
 typedef double double2e __attribute__((ext_vector_type(2), aligned(8)));
@@ -72,16 +81,42 @@ constexpr int SETTLE_ROWS_MAX = 512;  // rows of a workgroup
 constexpr int settle_rows(size_t element) { return element == 8 ? 2 : 4; }  // rows a group of lanes settles at once
 constexpr int SCAN_LISTS = 64;    // lists of points to resolve, a counter in a line of its own each
 constexpr int LIST_STRIDE = 32;
+constexpr int HALF_VOTERS = 128;  // workgroups that decide between the forms
+constexpr float HALF_RANGE = 6e4f;  // of a norm: no feature leaves the range of fp16
+constexpr int HALF_LIMIT = 12;    // percent of their points listed, beyond which two pieces are faster
 constexpr float SCAN_FLOOR = 7.9e-31f;  // 2^-100: below it scores (of centroids near 1) may have lost digits to underflow
 
 // how a block of the contraction is laid out
 enum ScanForm : int {
     FORM_PAIR = 0,    // 16 features, two pieces: fragments c0, c1 against x0, x1; c1x0 + c0x1 + c0x0
     FORM_OCTET = 1,   // 8 features, three pieces: fragments (c0 | c1), (c2 | c0) against (x0 | x0), (x1 | x1), (x0 | x2)
-    FORM_TRIPLE = 2   // 16 features, three pieces: c0, c1, c2 against x0, x1, x2; the six largest products
+    FORM_TRIPLE = 2,  // 16 features, three pieces: c0, c1, c2 against x0, x1, x2; the six largest products
+    FORM_HALF = 3     // 16 features, one fp16 piece: one product
 };
-static constexpr int form_frags(int form) { return form == FORM_TRIPLE ? 3 : 2; }   // centroid fragments per block
-static constexpr int form_pieces(int form) { return form == FORM_PAIR ? 2 : 3; }    // point fragments per block
+// centroid and point fragments per block
+static constexpr int form_frags(int form) { return form == FORM_HALF ? 1 : (form == FORM_TRIPLE ? 3 : 2); }
+static constexpr int form_pieces(int form) { return form == FORM_HALF ? 1 : (form == FORM_PAIR ? 2 : 3); }
+
+// Which of two forms a call takes: the one with fp16 pieces, unless the first workgroups of its scan find too many
+// points that it cannot tell.  The rest of that scan is then left out, and the other form's runs.
+struct ScanGate {
+    int32_t *state;  // [0] waves that have voted << 20 | points these would list, [1] not 0: two pieces; NULL: no choice
+    int votes;       // waves that vote
+    __device__ __forceinline__ bool refused() const { return __hip_atomic_load(state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0; }
+    __device__ __forceinline__ bool half() const { return state && !refused(); }
+    template <int FORM>
+    __device__ __forceinline__ bool closed() const
+    {
+        return state && refused() == (FORM == FORM_HALF);
+    }
+    // one lane of a wave with 64 points; the last to vote decides
+    __device__ __forceinline__ void vote(int listed) const
+    {
+        const int sum = (1 << 20 | listed) + atomicAdd(state, 1 << 20 | listed);
+        if (sum >> 20 == votes && (sum & 0xfffff) > votes * 64 * HALF_LIMIT / 100)
+            __hip_atomic_store(state + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
 
 struct ScanArgs {
     const void *X;
@@ -97,6 +132,9 @@ struct ScanArgs {
     int splits;
     int pblocks;
     ScanRecord *rec;
+    ScanGate gate;
+    const float *norm;  // for the vote: ||c||
+    const float4 *tile_stat;
 };
 
 __device__ __forceinline__ void split_pair(const float (&v)[8], uint4 &hi, uint4 &lo)
@@ -124,6 +162,21 @@ __device__ __forceinline__ void split_triple(const float (&v)[8], uint4 &a, uint
     a = __builtin_bit_cast(uint4, p0);
     b = __builtin_bit_cast(uint4, p1);
     c = __builtin_bit_cast(uint4, p2);
+}
+
+__device__ __forceinline__ uint4 round_half(const float (&v)[8])
+{
+    halfx8 h;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) h[e] = (_Float16)v[e];
+    return __builtin_bit_cast(uint4, h);
+}
+
+// squared norm of what an fp16 piece leaves of a value (the difference is exact)
+__device__ __forceinline__ void add_lost_half(float v, float &n)
+{
+    const float r = v - (float)(_Float16)v;
+    n = fmaf(r, r, n);
 }
 
 // squared norms of what two pieces leave of a value: the second piece, and what neither holds
@@ -232,16 +285,27 @@ __device__ __forceinline__ V wave_max(V v)
 // 16b + 8(l/32) of block b (FORM_OCTET: all 8 features).  Each of them forms the reference r and the scale for
 // itself, from the same rows by the same instructions; r stays in LDS (REF_BYTES; longer rows go without).
 constexpr int REF_ROWS = 8;
+// second image, of fp16 pieces; nb 0: none
+struct HalfImage {
+    uint4 *image;
+    float *start;
+    void *ref;  // the reference goes there
+    int32_t *gate;
+    int nb;
+    float lift, tiny;
+};
 constexpr size_t REF_BYTES = 64 * 1024;
 template <typename T, int FORM>
 __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
                                                               float4 *tile_stat, double *scale, int32_t *list_count, int lists,
-                                                              int has_ref, float *norm, double lift)
+                                                              int has_ref, float *norm, double lift, HalfImage half)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    T *const ref = reinterpret_cast<T *>(lds_raw);  // [16 nb]
+    T *const ref = reinterpret_cast<T *>(lds_raw);  // [16 nb_all]
+    const int nb_all = max(nb, half.nb);
     __shared__ double sh_n[16][32], sh_rc[16][32];
     __shared__ float sh_n1[16][32], sh_nr[16][32];  // squared norms of the second pieces and of the residuals
+    __shared__ float sh_nh[16][32];                 // and of what fp16 pieces leave
     __shared__ T sh_m[16][2];
     __shared__ double sh_s[16][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = (int)blockDim.x >> 6;
@@ -279,7 +343,7 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
         if (has_ref) ref[d] = r;
     }
     if (has_ref)
-        for (int d = D + tid; d < 16 * nb; d += blockDim.x) ref[d] = T(0);
+        for (int d = D + tid; d < 16 * nb_all; d += blockDim.x) ref[d] = T(0);
     m = wave_max(m);
     whole = wave_max(whole);
     gain = group_sum<64>(gain);
@@ -312,16 +376,27 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
         scale[0] = (double)s;
         scale[1] = moved ? sqrt(rr) * (double)s : 0.0;
     }
-    if (blockIdx.x == 0 && tid < lists) list_count[tid * LIST_STRIDE] = 0;
+    if (blockIdx.x == 0) {
+        if (tid < lists) list_count[tid * LIST_STRIDE] = 0;
+        if (tid == 0 && half.nb) {
+            half.gate[0] = 0;
+            // data far from the origin against their spread are not tried: the vote of 2^19 x 32 at 20, spread 1, K = 1024,
+            // comes when half of the scan has run (225 us a call, two pieces alone 163)
+            half.gate[1] = moved && rr > 4.0 * D * (double)m * (double)m;
+        }
+        if (tid < SCAN_LISTS && half.nb) half.gate[(tid + 1) * LIST_STRIDE] = 0;  // of the points left over
+        if (half.nb)
+            for (int d = tid; d < D; d += blockDim.x) static_cast<T *>(half.ref)[d] = moved ? ref[d] : T(0);
+    }
     const int tile = blockIdx.x;
     const int row = lane & 31, g = lane >> 5;
     const int j = 32 * tile + row;
     const T *c = C + (size_t)(j < K ? j : 0) * D;
     const RowReader<T, true> reader(c, D);
     double n = 0.0, rc = 0.0;
-    float n1 = 0.f, nr = 0.f;
+    float n1 = 0.f, nr = 0.f, nh = 0.f;
 #pragma unroll 2
-    for (int b = wave; b < nb; b += nw) {
+    for (int b = wave; b < nb_all; b += nw) {
         const int f0 = FORM == FORM_OCTET ? 0 : 16 * b + 8 * g;
         const Quad<T> q0 = reader.request(f0), q1 = reader.request(f0 + 4);
         const Quad<T> k0 = reader.keep(q0, f0), k1 = reader.keep(q1, f0 + 4);
@@ -347,12 +422,19 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
                 dst[2 * FRAG_UNITS] = a2;
             }
         } else {
-            uint4 a0, a1;
-            split_pair(v, a0, a1);
-            dst[0] = a0;
-            dst[FRAG_UNITS] = a1;
+            if (b < nb) {
+                uint4 a0, a1;
+                split_pair(v, a0, a1);
+                dst[0] = a0;
+                dst[FRAG_UNITS] = a1;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) add_lost(v[e], n1, nr);
+                for (int e = 0; e < 8; ++e) add_lost(v[e], n1, nr);
+            }
+            if (b < half.nb) {
+                half.image[((size_t)tile * half.nb + b) * FRAG_UNITS + lane] = round_half(v);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) add_lost_half(v[e], nh);
+            }
         }
     }
     if (FORM != FORM_OCTET) {
@@ -362,38 +444,47 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     if (FORM == FORM_PAIR) {
         n1 += __shfl_xor(n1, 32, 64);
         nr += __shfl_xor(nr, 32, 64);
+        nh += __shfl_xor(nh, 32, 64);
     }
     if (lane < 32) {
         sh_n[wave][lane] = n;
         sh_rc[wave][lane] = rc;
         sh_n1[wave][lane] = n1;
         sh_nr[wave][lane] = nr;
+        sh_nh[wave][lane] = nh;
     }
     __syncthreads();
     if (tid < 32) {
         n = rc = 0.0;
-        n1 = nr = 0.f;
+        n1 = nr = nh = 0.f;
         for (int i = 0; i < nw; ++i) {
             n += sh_n[i][tid];
             rc += sh_rc[i][tid];
             n1 += sh_n1[i][tid];
             nr += sh_nr[i][tid];
+            nh += sh_nh[i][tid];
         }
         // register r of lane group gg reads row 8(r/4) + 4gg + r%4
         const int gg = (tid >> 2) & 1, r = 4 * (tid >> 3) + (tid & 3);
         start[tile * 32 + gg * 16 + r] =
             32 * tile + tid < K ? (float)((lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
+        if (half.nb)
+            half.start[tile * 32 + gg * 16 + r] =
+                32 * tile + tid < K ? (float)(((double)half.lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
         norm[tile * 32 + tid] = sqrtf((float)n);
         // (a NaN row never wins and does not count)
         float f = n > 0.0 ? (float)n : 0.f;
         float q1 = n > 0.0 ? (float)((double)n1 / n) : 0.f, qr = n > 0.0 ? (float)((double)nr / n) : 0.f;
+        const float full = sqrtf(f) + half.tiny;
+        float qh = half.nb && full > 0.f ? nh / (full * full) : 0.f;
 #pragma unroll
         for (int k = 16; k >= 1; k >>= 1) {
             f = fmaxf(f, __shfl_xor(f, k, 64));
             q1 = fmaxf(q1, __shfl_xor(q1, k, 64));
             qr = fmaxf(qr, __shfl_xor(qr, k, 64));
+            qh = fmaxf(qh, __shfl_xor(qh, k, 64));
         }
-        if (tid == 0) tile_stat[tile] = make_float4(f, q1, qr, 0.f);
+        if (tid == 0) tile_stat[tile] = make_float4(f, q1, qr, qh);
     }
 }
 
@@ -448,15 +539,39 @@ __device__ __forceinline__ void scan_best_finish(const ScanBest &b, int g, float
     if (!(b.m1 == b.m1) || !(om1 == om1)) m2 = __builtin_huge_valf();  // NaN scores: not to be trusted
 }
 
+// whether the scan on fp16 pieces would list the point (about: with the named centroid's norm in place of the point's)
+__device__ __forceinline__ bool half_lists(const ScanArgs &a, float m1, int j1, float m2)
+{
+    const float c = a.norm[min(j1, 32 * a.tiles - 1)];
+    return !(m1 - m2 > 0.9f * 0x1p-11f * (c + (float)a.scale[1]) * c);
+}
+
+// the vote of a wave that found `listed` of its 64 points so; against fp16 pieces where a centroid leaves their range
+__device__ __forceinline__ void half_vote(const ScanArgs &a, int lane, int listed)
+{
+    float m = 0.f;
+    for (int i = lane; i < a.tiles; i += 64) m = fmaxf(m, a.tile_stat[i].x);
+    m = wave_max(m);
+    if (lane == 0) a.gate.vote(m < 0.99f * HALF_RANGE * HALF_RANGE ? listed : 64);
+}
+
 // ---- scan of rows of up to 128 features ---------------------------------------------------------
 // A wave keeps the pieces of its 2 x 32 points in registers for the whole sweep; the centroid image
 // passes through LDS in chunks of 16 or 32 KB, the next chunk copied (global memory to LDS, no
 // registers) while the current one is multiplied.  Fragments are stored lane by lane, so the copy is
 // linear and the reads are free of bank conflicts.  No settlement code: at 128 features 228 registers,
 // two workgroups of four waves per compute unit that wait at their own barriers.
-template <typename T, int NB, int FORM, bool RAG>
-__global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_kernel(ScanArgs a)
+// waves of a SIMD whose registers suffice
+constexpr int resident_waves(int nb, int form, bool wide, bool ragged)
 {
+    if (form != FORM_HALF) return nb <= 4 ? 3 : 2;
+    return wide ? (nb <= 2 ? 4 : (nb <= 4 ? 3 : 2)) : (nb <= 3 ? 4 : (nb <= 6 || !ragged ? 3 : 2));
+}
+// GATED: part of a call that chooses its form (the check alone, ahead of all other requests, is 1 us of 38 at 300007 x 45).
+template <typename T, int NB, int FORM, bool RAG, bool GATED>
+__global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8, RAG)) void scan_resident_kernel(ScanArgs a)
+{
+    if (GATED && a.gate.closed<FORM>()) return;
     constexpr int FR = form_frags(FORM);
     constexpr int TU = NB * FR * FRAG_UNITS;  // units per tile
     extern __shared__ __align__(16) uint4 lds4[];
@@ -506,7 +621,9 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
             }
-            if constexpr (FORM != FORM_PAIR) {
+            if constexpr (FORM == FORM_HALF) {
+                b[pt][k][0] = round_half(v);
+            } else if constexpr (FORM != FORM_PAIR) {
                 uint4 x0, x1, x2;
                 split_triple(v, x0, x1, x2);
                 b[pt][k][0] = x0;
@@ -556,6 +673,13 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
 #pragma unroll
                     for (int i = 0; i < FR; ++i) n[i] = f[((k + 1) * FR + i) * FRAG_UNITS];
                 }
+                if constexpr (FORM == FORM_HALF) {
+#pragma unroll
+                    for (int pt = 0; pt < SC_PT; ++pt)
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                            __builtin_bit_cast(halfx8, af[0]), __builtin_bit_cast(halfx8, b[pt][k][0]), acc[pt], 0, 0, 0);
+                    continue;
+                }
                 // (centroid, point) fragments of the products, smallest first; the chains of the two
                 // point tiles interleave
                 constexpr int NM = FORM == FORM_TRIPLE ? 6 : 3;
@@ -567,11 +691,11 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
 #pragma unroll
                     for (int pt = 0; pt < SC_PT; ++pt)
                         acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            af[PROD[i][0]], __builtin_bit_cast(bf16x8, b[pt][k][PROD[i][1]]), acc[pt], 0, 0, 0);
+                            af[PROD[i][0] % FR], __builtin_bit_cast(bf16x8, b[pt][k][PROD[i][1] % NP]), acc[pt], 0, 0, 0);
             }
             // keep that order through instruction scheduling, which would sink every read to its use
             // (at four blocks the second pair of fragments does not fit the registers of three waves)
-            if constexpr (NB != 4 && FORM != FORM_TRIPLE) {
+            if constexpr (NB != 4 && FORM != FORM_TRIPLE && FORM != FORM_HALF) {
                 __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
                 for (int k = 0; k + 1 < NB; ++k) {
@@ -587,6 +711,7 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
         __syncthreads();
         cur ^= 1;
     }
+    int listed = 0;
 #pragma unroll
     for (int pt = 0; pt < SC_PT; ++pt) {
         float m1, m2;
@@ -596,6 +721,12 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
         if (g == 0 && p < a.N) {
             a.rec[(int64_t)split * a.N + p] = ScanRecord{m1, m2, j1, 0};
         }
+        if constexpr (FORM == FORM_HALF) {
+            if (blockIdx.x < HALF_VOTERS) listed += __popcll(__ballot(g == 0 && half_lists(a, m1, j1, m2)));
+        }
+    }
+    if constexpr (FORM == FORM_HALF) {
+        if (blockIdx.x < HALF_VOTERS) half_vote(a, lane, listed);
     }
 }
 
@@ -605,9 +736,10 @@ __global__ __launch_bounds__(SC_THREADS, (NB <= 4 ? 3 : 2)) void scan_resident_k
 // on the way - requested two stages ahead, split and stored one stage ahead.  Wave w takes point tiles 2(w%4) .. +1 and the centroid tiles of half w/4.  The
 // workgroups that share a block of points run side by side on one XCD, so that X comes from memory
 // once whatever K.
-template <typename T, int CT, bool RAG>
+template <typename T, int CT, bool RAG, bool GATED>
 __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
 {
+    if (GATED && a.gate.closed<FORM_PAIR>()) return;
     constexpr int TPC = 2 * CT;  // centroid tiles per workgroup
     constexpr int AU = TPC * 4 * FRAG_UNITS, BU = 8 * 4 * FRAG_UNITS;  // units per stage: centroids, points
     extern __shared__ __align__(16) uint4 lds4[];
@@ -766,6 +898,177 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
     }
 }
 
+// ---- scan on fp16 pieces of rows of 129 .. 1024 features ---------------------------------------------
+// One piece is a third of the matrix work, and the streaming scan does not follow: it reads and splits X once per 256
+// centroids, a stage at a time between barriers (60000 x 1024, K = 1024: 230-260 us so shaped, 70 us of them matrix
+// instructions).  Here a workgroup rounds the rows of 32 PT points once, into LDS (up to 128 KB), and sweeps all
+// centroids without a barrier: each of its eight waves multiplies every eighth pair of centroid tiles, the
+// image's fragments straight from L2 with RING blocks of 16 features in flight.  Two tiles at a time halve the LDS
+// reads of an instruction, which would be its bound (a fragment of 1 KB per 32 cycles and SIMD), and all 64 (128)
+// points that LDS holds share a read of the image (64 bytes a clock from L2: 2 MB per 64 points of 1024 features).
+// The chain of a tile is long, so its 16 scores are compared one by one: three registers a point.
+constexpr int SP_THREADS = 512, SP_WAVES = SP_THREADS / 64, SP_CT = 2;
+constexpr int sp_ring(int pt) { return pt == 2 ? 8 : 4; }
+template <typename T, int PT, bool RAG>
+__global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, int nb)
+{
+    if (a.gate.closed<FORM_HALF>()) return;
+    constexpr int P = 32 * PT, CT = SP_CT, RING = sp_ring(PT);
+    extern __shared__ __align__(16) uint4 lds4[];  // [nb][PT][64] fragments; then the waves' records
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g = lane >> 5;
+    const int64_t p0 = (int64_t)blockIdx.x * P;
+    const T *X = reinterpret_cast<const T *>(a.X);
+    const T s = (T)a.scale[0];
+    {
+        // wave w rounds point tile w % PT, every (8 / PT)th group of BATCH blocks
+        constexpr int BATCH = sizeof(T) == 4 ? 8 : 4;
+        const int pt = wave % PT;
+        const int64_t pr = min(p0 + pt * 32 + col, a.N - 1);
+        const RowReader<T, RAG> row(X + pr * a.D, a.D);
+        for (int b0 = wave / PT * BATCH; b0 < nb; b0 += SP_WAVES / PT * BATCH) {
+            Quad<T> q[2 * BATCH];
+#pragma unroll
+            for (int u = 0; u < 2 * BATCH; ++u) q[u] = row.request(16 * (b0 + (u >> 1)) + 8 * g + 4 * (u & 1));
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k) {
+                float v[8];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const Quad<T> w = row.keep(q[2 * k + h], 16 * (b0 + k) + 8 * g + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
+                }
+                if (b0 + k < nb) lds4[((b0 + k) * PT + pt) * FRAG_UNITS + lane] = round_half(v);
+            }
+        }
+    }
+    float m1[PT], m2[PT];
+    int j1[PT];
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) {
+        m1[pt] = m2[pt] = Mma<float>::neg_inf();
+        j1[pt] = 0;
+    }
+    __syncthreads();
+    const int pairs = (a.tiles + CT - 1) / CT;
+    const size_t tile_units = (size_t)nb * FRAG_UNITS;
+    const int shift = ((int)blockIdx.x >> 3) % pairs;
+    auto place = [&](int t) {
+        const int q = min(t, pairs - 1) + shift;
+        return q < pairs ? q : q - pairs;
+    };
+    auto fragments = [&](int t) { return a.image + (size_t)place(t) * CT * tile_units + lane; };
+    uint4 ring[RING][CT];
+    const uint4 *f = fragments(wave);
+#pragma unroll
+    for (int u = 0; u < RING; ++u)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) ring[u][c] = f[c * tile_units + u * FRAG_UNITS];
+    floatx16 ci[CT];
+    auto request_start = [&](int t) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const float *hv = a.start + (place(t) * CT + c) * 32 + g * 16;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const floatx4 h = *reinterpret_cast<const floatx4 *>(hv + 4 * i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ci[c][4 * i + e] = h[e];
+            }
+        }
+    };
+    request_start(wave);
+    const uint4 *xf = lds4 + lane;
+    uint4 xn[PT];
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) xn[pt] = xf[pt * FRAG_UNITS];
+    for (int t = wave; t < pairs; t += SP_WAVES) {
+        floatx16 acc[CT][PT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int pt = 0; pt < PT; ++pt) acc[c][pt] = ci[c];
+        const uint4 *const next = fragments(t + SP_WAVES);
+        for (int b = 0; b < nb; b += RING) {
+            f = b + RING < nb ? f + RING * FRAG_UNITS : next;
+#pragma unroll
+            for (int u = 0; u < RING; ++u) {
+                halfx8 ah[CT], xh[PT];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) ah[c] = __builtin_bit_cast(halfx8, ring[u][c]);
+#pragma unroll
+                for (int pt = 0; pt < PT; ++pt) xh[pt] = __builtin_bit_cast(halfx8, xn[pt]);
+#pragma unroll
+                for (int c = 0; c < CT; ++c) ring[u][c] = f[c * tile_units + u * FRAG_UNITS];
+                const int bn = b + u + 1 < nb ? b + u + 1 : 0;
+#pragma unroll
+                for (int pt = 0; pt < PT; ++pt) xn[pt] = xf[(bn * PT + pt) * FRAG_UNITS];
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+                        acc[c][pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[c], xh[pt], acc[c][pt], 0, 0, 0);
+            }
+            // requests stay ahead of the instructions (left alone they all gather at the end of the loop)
+#pragma unroll
+            for (int u = 0; u < RING; ++u) {
+                __builtin_amdgcn_sched_group_barrier(0x020, CT, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, PT, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, CT * PT, 0);
+            }
+        }
+        request_start(t + SP_WAVES);
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int j = 32 * (place(t) * CT + c) + 8 * (r >> 2) + (r & 3);
+#pragma unroll
+                for (int pt = 0; pt < PT; ++pt) {
+                    const float v = acc[c][pt][r];
+                    j1[pt] = v > m1[pt] ? j : j1[pt];
+                    m2[pt] = __builtin_amdgcn_fmed3f(m1[pt], m2[pt], v);
+                    m1[pt] = max2f(m1[pt], v);
+                }
+            }
+    }
+    __syncthreads();  // the fragments are done with
+    float *xm1 = reinterpret_cast<float *>(lds4), *xm2 = xm1 + SP_WAVES * P;
+    int *xj = reinterpret_cast<int *>(xm2 + SP_WAVES * P);
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) {
+        const int j = j1[pt] + 4 * g;
+        const float o1 = __shfl_xor(m1[pt], 32, 64), o2 = __shfl_xor(m2[pt], 32, 64);
+        const int oj = __shfl_xor(j, 32, 64);
+        const bool mine = m1[pt] > o1 || (m1[pt] == o1 && j < oj);
+        if (g == 0) {
+            const int i = wave * P + pt * 32 + col;
+            xm1[i] = mine ? m1[pt] : o1;
+            xm2[i] = fmaxf(fmaxf(m2[pt], o2), mine ? o1 : m1[pt]);
+            xj[i] = mine ? j : oj;
+        }
+    }
+    __syncthreads();
+    if (tid < P) {
+        float b1 = xm1[tid], b2 = xm2[tid];
+        int j = xj[tid];
+        for (int w = 1; w < SP_WAVES; ++w) {
+            const float o1 = xm1[w * P + tid];
+            const bool mine = b1 >= o1;
+            b2 = fmaxf(fmaxf(b2, xm2[w * P + tid]), mine ? o1 : b1);
+            j = mine ? j : xj[w * P + tid];
+            b1 = mine ? b1 : o1;
+        }
+        const int64_t p = p0 + tid;
+        if (p < a.N) a.rec[p] = ScanRecord{b1, b2, j, 0};
+        if (blockIdx.x < HALF_VOTERS) {
+            const int listed = __popcll(__ballot(half_lists(a, b1, j, b2)));
+            half_vote(a, lane, listed);
+        }
+    }
+}
+
 // ---- settle -----------------------------------------------------------------------------------
 // L lanes share a row (row-contiguous 16-byte loads) and take ROWS of them at once: the pass is a
 // chain of latencies - record, then the centroid's row - that only requests in flight can hide.
@@ -782,20 +1085,31 @@ struct SettleArgs {
     float psi, lost;    // rounding of a score; what is lost of ||x|| ||c|| whatever the centroids
     float lift;         // by which multiple of ||c||^2 the scores were raised
     const float *norm;  // ||c||
+    float sums;         // rounding of a sum of squares over a row, halved
     float slack, tiny;  // of the measured norms: their own rounding, and what underflow takes from them
     int32_t *labels;
     ScanListed *list;  // (point, score a candidate needs), or NULL: the points alone go to wl
     int32_t *wl, *list_count;
     int lists, list_cap;
     int32_t *tickets;   // [N/32 + 1] cleared here for the pass that follows
+    // scans on fp16 pieces: their numbers where the gate chooses them
+    ScanGate gate;
+    int half_splits;
+    float half_psi, half_lift, half_tiny;
+    const void *ref;    // [D] the reference r
 };
 
-template <typename T, int L>
+// HALF: the records may come from fp16 pieces
+template <typename T, int L, bool HALF>
 __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T *C, T *mindist, SettleArgs a)
 {
+    const bool half = HALF && a.gate.half();
+    const int splits = half ? a.half_splits : a.splits;
+    const float psi = half ? a.half_psi : a.psi, lift = half ? a.half_lift : a.lift, tiny = half ? a.half_tiny : a.tiny;
     constexpr int ROWS = settle_rows(sizeof(T));
     constexpr int RPB = 256 / L;  // rows side by side
-    __shared__ float sh_max[4][3];
+    constexpr int Q = HALF ? 4 : 3;
+    __shared__ float sh_max[4][Q];
     __shared__ int sh_n, sh_base;
     __shared__ int32_t sh_lab[RPB * ROWS];   // ~label for listed points
     __shared__ T sh_dist[RPB * ROWS];
@@ -804,51 +1118,54 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
     const int sub = tid & (L - 1), grp = tid / L;
     const int Dq = a.D & ~3;
     const int64_t first = (int64_t)blockIdx.x * (ROWS * RPB);
-    int64_t pp[ROWS];
+    int at[ROWS];  // of the rows, from the first one
     float m1[ROWS], m2[ROWS];
     int j[ROWS];
-    const T *x[ROWS], *c[ROWS];
+    const T *c[ROWS];
+    const T *const X0 = X + first * a.D;
+    const ScanRecord *rec = a.rec + first;
     Quad<T> xv[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
-        const int64_t p = first + u * RPB + grp;
-        pp[u] = p < a.N ? p : a.N - 1;
-        x[u] = X + pp[u] * a.D;
-        const ScanRecord r = a.rec[pp[u]];
+        at[u] = (int)min((int64_t)(u * RPB + grp), a.N - 1 - first);
+        const ScanRecord r = rec[at[u]];
         m1[u] = r.m1;
         m2[u] = r.m2;
         j[u] = r.j1;
     }
     // the first piece of every row travels with the records
 #pragma unroll
-    for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(x[u] + min(4 * sub, Dq - 4));
+    for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(X0 + (unsigned)(at[u] * a.D + min(4 * sub, Dq - 4)));
     if (tid == 0) sh_n = 0;
     const int64_t i0 = (int64_t)blockIdx.x * 256 + tid;
     if (i0 * 32 < a.N) a.tickets[i0] = 0;
-    float cm[3] = {0.f, 0.f, 0.f};
+    float cm[Q] = {};
     for (int i = tid; i < a.tiles; i += 256) {
         const float4 t = a.tile_stat[i];
         cm[0] = fmaxf(cm[0], t.x);
         cm[1] = fmaxf(cm[1], t.y);
         cm[2] = fmaxf(cm[2], t.z);
+        if constexpr (HALF) cm[3] = fmaxf(cm[3], t.w);
     }
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < Q; ++q) {
         cm[q] = wave_max(cm[q]);
         if (lane == 0) sh_max[tid >> 6][q] = cm[q];
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 3; ++q) cm[q] = fmaxf(fmaxf(sh_max[0][q], sh_max[1][q]), fmaxf(sh_max[2][q], sh_max[3][q]));
-    const float cmax = 1.000001f * sqrtf(cm[0]) + a.tiny;
+    for (int q = 0; q < Q; ++q) cm[q] = fmaxf(fmaxf(sh_max[0][q], sh_max[1][q]), fmaxf(sh_max[2][q], sh_max[3][q]));
+    const float cmax = 1.000001f * sqrtf(cm[0]) + tiny;
     // a score of centroid c is off by at most A ||c|| + psi ||c||^2 / 2, A = lost ||x|| + psi (||x|| + ||r||); ||x1|| <= 2^-8 ||x||
-    const float lost = a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
+    // (fp16 pieces: lost ||x|| is ||r_x|| + max(||r_c|| / ||c||) ||x||, the first measured below)
+    const float lost = half ? 1.001f * a.slack * sqrtf(cm[Q - 1])
+                            : a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
     const T s = (T)a.scale[0];
-    const float ref = 1.000001f * (float)a.scale[1] + a.tiny;  // ||r||
-    for (int k = 1; k < a.splits; ++k) {
+    const float ref = 1.000001f * (float)a.scale[1] + tiny;  // ||r||
+    for (int k = 1; k < splits; ++k) {
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
-            const ScanRecord o = a.rec[(int64_t)k * a.N + pp[u]];
+            const ScanRecord o = rec[(int64_t)k * a.N + at[u]];
             const bool mine = m1[u] >= o.m1;
             m2[u] = fmaxf(fmaxf(m2[u], o.m2), mine ? o.m1 : m1[u]);
             m1[u] = mine ? m1[u] : o.m1;
@@ -856,52 +1173,72 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
         }
     }
     T d[ROWS];
-    float xn[ROWS], cn[ROWS];
+    float xn[ROWS], yn[ROWS], cn[ROWS], xr[ROWS];  // of x and of x - r, of c, of what an fp16 piece leaves of x
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         j[u] = (unsigned)j[u] < (unsigned)a.K ? j[u] : 0;  // padding rows, when no score was a number
         c[u] = C + (size_t)j[u] * a.D;
         cn[u] = a.norm[j[u]];
         d[u] = T(0);
-        xn[u] = 0.f;
+        xn[u] = yn[u] = xr[u] = 0.f;
     }
-    auto add = [&](int u, T xe, T ce) {
+    const T *const ref_row = (const T *)a.ref;
+    auto add = [&](int u, T xe, T ce, T re) {
         const T t = xe - ce;
         d[u] = fma(t, t, d[u]);
         const float w = (float)(xe * s);
         xn[u] = fmaf(w, w, xn[u]);
+        if constexpr (HALF) {
+            const float y = (float)((xe - re) * s);
+            yn[u] = fmaf(y, y, yn[u]);
+            add_lost_half(w, xr[u]);
+        }
     };
     for (int f = 4 * sub; f < Dq;) {
         Quad<T> cv[ROWS];
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) cv[u] = load_quad<T>(c[u] + f);
+        Quad<T> rv = {};
+        if constexpr (HALF) rv = load_quad<T>(ref_row + f);
 #pragma unroll
         for (int u = 0; u < ROWS; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) add(u, xv[u].v[e], cv[u].v[e]);
+            for (int e = 0; e < 4; ++e) add(u, xv[u].v[e], cv[u].v[e], rv.v[e]);
         f += 4 * L;
         if (f < Dq)
 #pragma unroll
-            for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(x[u] + f);
+            for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(X0 + (unsigned)(at[u] * a.D + f));
     }
     for (int f = Dq + sub; f < a.D; f += L)
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) add(u, x[u][f], c[u][f]);
+        for (int u = 0; u < ROWS; ++u) add(u, X0[(unsigned)(at[u] * a.D + f)], c[u][f], HALF ? ref_row[f] : T(0));
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         const T dist = group_sum<L>(d[u]);
-        const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + a.tiny;
-        const float A = lost * norm + a.psi * (norm + ref), B = a.lift - 0.5f * a.psi;
-        const float c1 = 1.000001f * cn[u] + a.tiny, t = fminf(A / (2.f * B), cmax);  // the norm most too low
-        const float bound = 1.00001f * ((A - B * t) * t + A * a.tiny + (A + (a.lift + 0.5f * a.psi) * c1) * c1) + SCAN_FLOOR;
+        const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + tiny;
+        float A = lost * norm + psi * (norm + ref);
+        const float B = lift - 0.5f * psi;
+        if constexpr (HALF) A += half ? 1.001f * a.slack * sqrtf(group_sum<L>(xr[u])) : 0.f;
+        const float c1 = 1.000001f * cn[u] + tiny, t = fminf(A / (2.f * B), cmax);  // the norm most too low
+        // How much too low the score of any centroid is, at most, and how much too high that of the named one.
+        const float low = 1.00001f * ((A - B * t) * t + (A + psi * cmax) * tiny) + SCAN_FLOOR;
+        const float high = 1.00001f * (A + (lift + 0.5f * psi) * c1) * c1;
+        float least = m1[u] - high;
+        if constexpr (HALF) {
+            // Its true score is also known from the distance, (||x - r||^2 - ||x - c||^2) / 2, to within the rounding of
+            // these sums: of fp16 pieces that halves the bound (2^21 x 32, K = 4096: 68 000 points listed against 105 000).
+            const float y2 = group_sum<L>(yn[u]), d2 = (float)(dist * s * s);
+            least = fmaxf(least, 0.5f * (y2 - d2) - a.sums * (y2 + d2));
+        }
+        least -= low;
         // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on
         // the way to a sum that is not): a threshold that is not a number makes every centroid a candidate.
-        const bool sound = (norm + ref + cmax) * cmax < 1e38f;
-        const bool listed = !sound || !(m1[u] - m2[u] > bound);
+        const bool sound = (norm + ref + cmax) * cmax < 1e38f && (!half || fmaxf(norm, cmax) < HALF_RANGE);
+        const bool listed = !sound || !(least > m2[u]);
         if (sub == 0) {
             sh_lab[u * RPB + grp] = listed ? ~j[u] : j[u];
             sh_dist[u * RPB + grp] = dist;
-            sh_thr[u * RPB + grp] = sound ? m1[u] - bound : __builtin_nanf("");
+            sh_thr[u * RPB + grp] = sound ? least : __builtin_nanf("");
         }
     }
     __syncthreads();
@@ -924,15 +1261,15 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
     const int which = (int)blockIdx.x % a.lists;
     if (tid == 0) sh_base = atomicAdd(a.list_count + which * LIST_STRIDE, sh_n);
     __syncthreads();
-    const int64_t at = (int64_t)which * a.list_cap + sh_base;
+    const int64_t slot0 = (int64_t)which * a.list_cap + sh_base;
 #pragma unroll
     for (int k = 0; k < (RPB * ROWS + 255) / 256; ++k) {
         if (mine[k] < 0) continue;
         const int i = k * 256 + tid;
         if (a.list)
-            a.list[at + mine[k]] = ScanListed{(int32_t)(first + i), sh_thr[i]};
+            a.list[slot0 + mine[k]] = ScanListed{(int32_t)(first + i), sh_thr[i]};
         else
-            a.wl[at + mine[k]] = (int32_t)(first + i);
+            a.wl[slot0 + mine[k]] = (int32_t)(first + i);
     }
 }
 
@@ -960,6 +1297,12 @@ struct ResolveArgs {
     int list_cap;
     int32_t *tickets;
     ftk_ft_stats *stats;
+    ScanGate gate;
+    // Lists of points that the third pass of a scan on fp16 pieces leaves; FORM_HALF writes them, the other form then
+    // settles these instead of its own
+    ScanListed *rest;
+    int32_t *rest_count;
+    int rest_cap;
 };
 
 // result of one workgroup for one point, in the place of its scan record
@@ -1031,6 +1374,7 @@ __device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *c
 #pragma unroll
         for (int r = 0; r < R; ++r) d[i][r] = group_sum<L>(d[i][r]);
 }
+
 
 constexpr int RS_THREADS = 512, RS_WAVES = RS_THREADS / 64, RS_CAP = 8;
 
@@ -1200,8 +1544,9 @@ __device__ __forceinline__ int native_verdict(const NativeShared<T> &sh, int i, 
     return sound && (double)m1 - (double)m2 > band ? j1 : -1;
 }
 
-template <typename T, int FORM, int L>
-__global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, const T *C, T *mindist, ResolveArgs a)
+// GATED: in a call that chooses its form
+template <typename T, int FORM, int L, bool GATED>
+__global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_resolve_kernel(const T *X, const T *C, T *mindist, ResolveArgs a)
 {
     constexpr int NP = form_pieces(FORM), FR = form_frags(FORM);
     constexpr int GROUPS = RS_THREADS / L;
@@ -1221,12 +1566,17 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
     const int sub = tid & (L - 1), grp = tid / L;
+    const bool rest = GATED && FORM != FORM_HALF && a.gate.half();
+    if (FORM == FORM_HALF && a.gate.closed<FORM>()) return;
+    const ScanListed *const list = rest ? a.rest : a.list;
+    const int32_t *const list_count = rest ? a.rest_count : a.list_count;
+    const int list_cap = rest ? a.rest_cap : a.list_cap;
     const T s = (T)a.scale[0];
     __shared__ int sh_pre[SCAN_LISTS + 1];  // listed points before each list
     __shared__ int32_t sh_job[32 * RS_CAP];
     __shared__ int sh_jobs;
     if (wave == 0) {
-        int v = a.list_count[lane * LIST_STRIDE];
+        int v = list_count[lane * LIST_STRIDE];
 #pragma unroll
         for (int k = 1; k < 64; k <<= 1) {
             const int o = __shfl_up(v, k, 64);
@@ -1238,19 +1588,20 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     __syncthreads();
     const int n = sh_pre[SCAN_LISTS];
     // workgroups per group: no more than run side by side
-    const int S = max(1, min(a.splits, a.side / max(1, (n + 31) / 32)));
+    const int nb = rest ? 0 : a.nb;  // (what is left over meets all centroids)
+    const int S = rest ? 1 : max(1, min(a.splits, a.side / max(1, (n + 31) / 32)));
     const int split = (int)blockIdx.x % S, per = (a.tiles + S - 1) / S;
     const int tile_end = min(a.tiles, (split + 1) * per);
     auto listed_point = [&](int i) {  // the i-th of all lists
         int q = 0;
 #pragma unroll
         for (int k = SCAN_LISTS / 2; k >= 1; k >>= 1) q += sh_pre[q + k] <= i ? k : 0;
-        return a.list[(int64_t)q * a.list_cap + (i - sh_pre[q])];
+        return list[(int64_t)q * list_cap + (i - sh_pre[q])];
     };
-    if (a.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&a.stats->refined, (unsigned long long)n);
+    if (a.stats && !rest && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&a.stats->refined, (unsigned long long)n);
     if ((int)blockIdx.x / S >= (int)gridDim.x / S) return;  // a remainder of the grid
     // points per group: 32, or fewer of the rows that meet all centroids right away, while that leaves workgroups idle
-    const int per_group = a.nb ? 32 : max(1, min(32, (n + a.side - 1) / a.side));
+    const int per_group = nb ? 32 : max(1, min(32, (n + a.side - 1) / a.side));
     for (int64_t at = (int64_t)((int)blockIdx.x / S) * per_group; at < n; at += (int64_t)((int)gridDim.x / S) * per_group) {
         const int first = (int)at, np = min(per_group, n - first);
         __syncthreads();  // the previous group is written out
@@ -1258,12 +1609,12 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
             const ScanListed e = listed_point(first + min(tid, np - 1));
             sh_p[tid] = e.point;
             sh_thr[tid] = e.thr;
-            sh_cnt[tid] = a.nb ? 0 : RS_CAP + 1;  // rows too long for that: all centroids
+            sh_cnt[tid] = nb ? 0 : RS_CAP + 1;  // rows too long for that: all centroids
         }
         __syncthreads();
         const RowReader<T, true> row(X + (int64_t)sh_p[col] * a.D, a.D);
-#pragma unroll 2
-        for (int b = wave; b < a.nb; b += RS_THREADS / 64) {
+#pragma unroll(FORM == FORM_HALF ? 4 : 2)
+        for (int b = wave; b < nb; b += RS_THREADS / 64) {
             const int f0 = FORM == FORM_OCTET ? 0 : 16 * b + 8 * g;
             const Quad<T> q0 = row.keep(row.request(f0), f0), q1 = row.keep(row.request(f0 + 4), f0 + 4);
             float v[8];
@@ -1273,7 +1624,9 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
                 v[4 + e] = (float)(q1.v[e] * s);
             }
             uint4 *dst = lds4 + b * NP * FRAG_UNITS + lane;
-            if constexpr (FORM != FORM_PAIR) {
+            if constexpr (FORM == FORM_HALF) {
+                dst[0] = round_half(v);
+            } else if constexpr (FORM != FORM_PAIR) {
                 uint4 x0, x1, x2;
                 split_triple(v, x0, x1, x2);
                 dst[0] = x0;
@@ -1288,10 +1641,11 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
         }
         __syncthreads();
         const float thr = sh_thr[col];
-        // this wave's tiles, block by block, four blocks and the next tile's start values in flight
+        // this wave's tiles, block by block, `RING` blocks and the next tile's start values in flight
         const int t0 = split * per + wave;
-        const int total = t0 < tile_end ? ((tile_end - t0 - 1) / (RS_THREADS / 64) + 1) * a.nb : 0;
-        uint4 ring[4][FR];
+        const int total = t0 < tile_end ? ((tile_end - t0 - 1) / (RS_THREADS / 64) + 1) * nb : 0;
+        constexpr int RING = FORM == FORM_HALF ? 8 : 4;
+        uint4 ring[RING][FR];
         int lt = t0, lb = 0;  // tile and block of the next request
         auto request = [&](uint4 (&r)[FR]) {
             const uint4 *f = a.image + ((size_t)min(lt, a.tiles - 1) * a.nb + lb) * (FR * FRAG_UNITS) + lane;
@@ -1314,34 +1668,40 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
         };
         request_start(t0);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) request(ring[u]);
+        for (int u = 0; u < RING; ++u) request(ring[u]);
         int t = t0, b = 0;
-        for (int i = 0; i < total; i += 4) {
+        for (int i = 0; i < total; i += RING) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < RING; ++u) {
                 if (i + u >= total) break;
                 if (b == 0) {
                     acc = ci;
                     request_start(t + RS_THREADS / 64);
                 }
-                const bf16x8 a0 = __builtin_bit_cast(bf16x8, ring[u][0]);
-                const bf16x8 a1 = __builtin_bit_cast(bf16x8, ring[u][1]);
-                const bf16x8 a2 = __builtin_bit_cast(bf16x8, ring[u][FR - 1]);
-                request(ring[u]);
                 const uint4 *q = lds4 + b * NP * FRAG_UNITS + lane;
-                const bf16x8 x0 = __builtin_bit_cast(bf16x8, q[0]);
-                const bf16x8 x1 = __builtin_bit_cast(bf16x8, q[FRAG_UNITS]);
-                const bf16x8 x2 = __builtin_bit_cast(bf16x8, q[(NP - 1) * FRAG_UNITS]);
-                if constexpr (FORM == FORM_TRIPLE) {
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, x0, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, x1, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x2, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, x0, acc, 0, 0, 0);
+                if constexpr (FORM == FORM_HALF) {
+                    const halfx8 a0 = __builtin_bit_cast(halfx8, ring[u][0]);
+                    request(ring[u]);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, __builtin_bit_cast(halfx8, q[0]), acc, 0, 0, 0);
                 } else {
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, FORM == FORM_OCTET ? x2 : x0, acc, 0, 0, 0);
+                    const bf16x8 a0 = __builtin_bit_cast(bf16x8, ring[u][0]);
+                    const bf16x8 a1 = __builtin_bit_cast(bf16x8, ring[u][1]);
+                    const bf16x8 a2 = __builtin_bit_cast(bf16x8, ring[u][FR - 1]);
+                    request(ring[u]);
+                    const bf16x8 x0 = __builtin_bit_cast(bf16x8, q[0]);
+                    const bf16x8 x1 = __builtin_bit_cast(bf16x8, q[FRAG_UNITS]);
+                    const bf16x8 x2 = __builtin_bit_cast(bf16x8, q[(NP - 1) * FRAG_UNITS]);
+                    if constexpr (FORM == FORM_TRIPLE) {
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, x0, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, x1, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x2, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, x0, acc, 0, 0, 0);
+                    } else {
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, FORM == FORM_OCTET ? x2 : x0, acc, 0, 0, 0);
+                    }
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x1, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x0, acc, 0, 0, 0);
                 }
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x1, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x0, acc, 0, 0, 0);
                 if (++b < a.nb) continue;
                 float tm = fmaxf(acc[0], acc[1]);
 #pragma unroll
@@ -1429,6 +1789,14 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
         if (tid < np && sh_code[tid] >= 0) {
             a.labels[sh_p[tid]] = sh_code[tid];
             if (mindist) mindist[sh_p[tid]] = (T)sh_bd32[tid];
+        }
+        if constexpr (FORM == FORM_HALF) {  // without what follows: half the registers, two workgroups a compute unit
+            if (tid < np && sh_code[tid] < 0) {
+                const int which = first / 32 % SCAN_LISTS;
+                const int slot = atomicAdd(a.rest_count + which * LIST_STRIDE, 1);
+                a.rest[(int64_t)which * a.rest_cap + slot] = ScanListed{sh_p[tid], __builtin_nanf("")};
+            }
+            continue;
         }
         __syncthreads();
         auto collect = [&] {
@@ -1530,6 +1898,187 @@ __global__ __launch_bounds__(RS_THREADS) void scan_resolve_kernel(const T *X, co
     }
 }
 
+// ---- listed points of a scan on fp16 pieces, rows of up to 128 features -------------------------------
+// These are some percent of all points, most with two candidates, so their sweep is shaped like the scan itself: fragments
+// in registers, the image through LDS.  (By scan_resolve_kernel, 32 points a group and a chain of latencies
+// each: 160 us for the 68 000 points of 2^21 x 32, K = 4096.)  The four waves of a workgroup share 64 points
+// and take every fourth tile: 256 points of their own each took 123 us, one workgroup per compute unit.  A lane notes the centroids
+// whose score reaches its point's threshold; then L lanes at a time evaluate them in double.  A point with
+// more of them than are noted goes on to scan_resolve_kernel, to meet all centroids.
+struct RecheckArgs {
+    const ScanListed *list;
+    const int32_t *list_count;
+    int list_cap;
+    ScanListed *rest;
+    int32_t *rest_count;
+    int rest_cap;
+    int K;
+    int32_t *labels;
+    ftk_ft_stats *stats;
+};
+constexpr int RC_CAP = 6, RC_POINTS = SC_PT * 32;
+constexpr int recheck_tiles(int nb) { return nb <= 3 ? 8 : 4; }  // of a chunk: 16 .. 32 KB, a multiple of the waves
+
+template <typename T, int NB, bool RAG, int L>
+__global__ __launch_bounds__(SC_THREADS, resident_waves(NB + 1, FORM_HALF, sizeof(T) == 8, RAG))
+void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, RecheckArgs r)
+{
+    if (a.gate.closed<FORM_HALF>()) return;
+    constexpr int TU = NB * FRAG_UNITS;
+    constexpr int GROUPS = SC_THREADS / L;
+    extern __shared__ __align__(16) uint4 lds4[];
+    __shared__ int sh_pre[SCAN_LISTS + 1];
+    __shared__ int32_t sh_p[RC_POINTS];
+    __shared__ float sh_thr[RC_POINTS];
+    __shared__ int sh_cnt[RC_POINTS];
+    __shared__ int32_t sh_j[RC_POINTS][RC_CAP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g = lane >> 5;
+    const int sub = tid & (L - 1), grp = tid / L;
+    const int cu = a.tpc * TU + ((a.tpc + 1) / 2) * 16;
+    if (wave == 0) {
+        int v = r.list_count[lane * LIST_STRIDE];
+#pragma unroll
+        for (int k = 1; k < 64; k <<= 1) {
+            const int o = __shfl_up(v, k, 64);
+            v += lane >= k ? o : 0;
+        }
+        sh_pre[lane + 1] = v;
+        if (lane == 0) sh_pre[0] = 0;
+    }
+    __syncthreads();
+    const int n = sh_pre[SCAN_LISTS];
+    if (r.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&r.stats->refined, (unsigned long long)n);
+    auto stage = [&](int ch, uint4 *buf) {
+        const int tile0 = ch * a.tpc;
+        const uint4 *src = a.image + (size_t)tile0 * TU;
+        const int m = min(a.tpc, a.tiles - tile0) * NB;
+        for (int i = wave; i < m; i += SC_THREADS / 64) to_lds16(src + i * FRAG_UNITS + lane, buf + i * FRAG_UNITS);
+        const float *sv = a.start + tile0 * 32;
+        float *dst = reinterpret_cast<float *>(buf + a.tpc * TU);
+        for (int i = wave; 2 * i < a.tpc; i += SC_THREADS / 64) to_lds4(sv + i * 64 + lane, dst + i * 64);
+    };
+    const T s = (T)a.scale[0];
+    for (int64_t first = (int64_t)blockIdx.x * RC_POINTS; first < n; first += (int64_t)gridDim.x * RC_POINTS) {
+        __syncthreads();  // the points before these are done
+        stage(0, lds4);
+        if (tid < RC_POINTS) {
+            const int64_t i = first + tid < n ? first + tid : n - 1;
+            int q = 0;
+#pragma unroll
+            for (int k = SCAN_LISTS / 2; k >= 1; k >>= 1) q += sh_pre[q + k] <= i ? k : 0;
+            const ScanListed e = r.list[(int64_t)q * r.list_cap + (i - sh_pre[q])];
+            sh_p[tid] = e.point;
+            sh_thr[tid] = first + tid < n ? e.thr : __builtin_huge_valf();
+            sh_cnt[tid] = 0;
+        }
+        __syncthreads();
+        uint4 b[SC_PT][NB];
+        float thr[SC_PT];
+#pragma unroll
+        for (int pt = 0; pt < SC_PT; ++pt) {
+            const int i = pt * 32 + col;
+            thr[pt] = sh_thr[i];
+            const RowReader<T, RAG> row(X + (int64_t)sh_p[i] * a.D, a.D);
+            Quad<T> q[2 * NB];
+#pragma unroll
+            for (int u = 0; u < 2 * NB; ++u) q[u] = row.request(16 * (u >> 1) + 8 * g + 4 * (u & 1));
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                float v[8];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const Quad<T> w = row.keep(q[2 * k + h], 16 * k + 8 * g + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
+                }
+                b[pt][k] = round_half(v);
+            }
+        }
+        wait_loads<0>();
+        __syncthreads();
+        int cur = 0;
+        for (int ch = 0; ch < a.nch; ++ch) {
+            const uint4 *buf = lds4 + cur * cu;
+            if (ch + 1 < a.nch) stage(ch + 1, lds4 + (cur ^ 1) * cu);
+            const int nt = min(a.tpc, a.tiles - ch * a.tpc);
+            const float *hv = reinterpret_cast<const float *>(buf + a.tpc * TU) + g * 16;
+            for (int t = wave; t < nt; t += SC_THREADS / 64) {
+                const uint4 *f = buf + t * TU + lane;
+                floatx16 acc[SC_PT];
+                floatx16 ci;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const floatx4 h = *reinterpret_cast<const floatx4 *>(hv + t * 32 + 4 * i);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ci[4 * i + e] = h[e];
+                }
+#pragma unroll
+                for (int pt = 0; pt < SC_PT; ++pt) acc[pt] = ci;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const halfx8 af = __builtin_bit_cast(halfx8, f[k * FRAG_UNITS]);
+#pragma unroll
+                    for (int pt = 0; pt < SC_PT; ++pt)
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, __builtin_bit_cast(halfx8, b[pt][k]), acc[pt], 0, 0, 0);
+                }
+#pragma unroll
+                for (int pt = 0; pt < SC_PT; ++pt) {
+                    float tm = fmaxf(acc[pt][0], acc[pt][1]);
+#pragma unroll
+                    for (int i = 2; i < 16; i += 2) tm = max3f(tm, acc[pt][i], acc[pt][i + 1]);
+                    if (__any(tm >= thr[pt])) {
+                        const int at = pt * 32 + col;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            const int j = 32 * (ch * a.tpc + t) + 8 * (i >> 2) + 4 * g + (i & 3);
+                            if (acc[pt][i] >= thr[pt] && j < r.K) {
+                                const int slot = atomicAdd(&sh_cnt[at], 1);
+                                if (slot < RC_CAP) sh_j[at][slot] = j;
+                            }
+                        }
+                    }
+                }
+            }
+            wait_loads<0>();  // the next chunk has arrived
+            __syncthreads();
+            cur ^= 1;
+        }
+        const int np = (int)(n - first < RC_POINTS ? n - first : RC_POINTS);
+        for (int i = grp; i < np; i += GROUPS) {
+            const int m = sh_cnt[i], p = sh_p[i];
+            if (m < 1 || m > RC_CAP) {
+                if (sub == 0) {
+                    const int which = (int)((first / RC_POINTS) % SCAN_LISTS);
+                    const int slot = atomicAdd(r.rest_count + which * LIST_STRIDE, 1);
+                    r.rest[(int64_t)which * r.rest_cap + slot] = ScanListed{p, __builtin_nanf("")};
+                }
+                continue;
+            }
+            const T *const x[1] = {X + (int64_t)p * a.D};
+            double best = __builtin_huge_val();
+            int bj = -1;
+            for (int k = 0; k < m; k += 2) {
+                const int j0 = sh_j[i][k], j1 = sh_j[i][min(k + 1, m - 1)];
+                const T *const c[2] = {C + (size_t)j0 * a.D, C + (size_t)j1 * a.D};
+                double d[1][2];
+                group_sqdists<T, L, 1, 2>(x, c, a.D, sub, d);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int j = q ? j1 : j0;
+                    const bool better = bj < 0 || d[0][q] < best || (d[0][q] == best && j < bj);
+                    best = better ? d[0][q] : best;
+                    bj = better ? j : bj;
+                }
+            }
+            if (sub == 0) {
+                r.labels[p] = bj;
+                if (mindist) mindist[p] = (T)best;
+            }
+        }
+    }
+}
+
 // ---- host ----------------------------------------------------------------------------------------
 static int resident_blocks(int D)
 {
@@ -1591,6 +2140,22 @@ static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
     return K >= scan_from(dtype, N, D);
 }
 
+// Where the scan on fp16 pieces runs first.  It has a third of the matrix work, a settle pass that measures more of
+// each row (fp64: in instructions of half the rate) and some percent of the points in the third pass; three more launches, of
+// which two return at once.  Two pieces / one, whole calls, us, blobs:
+//   fp32  D <= 128  10^6 x 32, K = 300 127 / 139, 600 169 / 161; 2 10^6 x 32, K = 512 288 / 256; 262144 x 128, K = 400 117 / 125;
+//                   65536 x 128, K = 2000 119 / 116; 40000 x 100, K = 4000 149 / 167; 400000 x 32, K = 2000 196 / 160
+//         longer    1872756 x 340, K = 108 1418 / 1569; 131072 x 256, K = 300 129 / 130, 700 191 / 154; 40000 x 1000, K = 512 225 / 179
+//   fp64  D <= 128  262144 x 64, K = 1200 156 / 165; 65536 x 128, K = 2000 143 / 166; 10^6 x 32, K = 2048 424 / 346
+//         longer    200000 x 130, K = 512 210 / 231; 131072 x 256, K = 300 206 / 203; 40000 x 1024, K = 300 372 / 287
+static bool half_pays(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    const double work = (double)N * D * K;
+    if (D <= 16 || D > 1024 || N < HALF_VOTERS * SC_POINTS) return false;
+    if (D <= 128) return K >= 512 && N >= 60000 && work >= (dtype == FTK_F32 ? 1.5e10 : 4e10);
+    return K >= 256 && work >= (dtype == FTK_F32 || D >= 192 ? 1.2e10 : 3e10);
+}
+
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K)
 {
     return scan_pays(dtype, N, D, K) ? cut_scan(dtype, N, D, K) : ScanPlan{};
@@ -1602,16 +2167,24 @@ ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K)
 constexpr int64_t SCAN_RECORDS = (int64_t)1 << 22;  // 64 MB
 constexpr int64_t SCAN_BATCH_STEP = 2048;           // points: whole rounds of the streaming scan's XCD order
 
-static ScanPlan cut_launch(ftk_dtype dtype, int64_t N, int D, int K)
+static ScanPlan cut_launch(ftk_dtype dtype, int64_t N, int D, int K, bool half = false)
 {
     ScanPlan p = {};
     p.ok = true;
     p.batch = N;
-    p.form = D <= 8 ? FORM_OCTET : (D <= 16 ? FORM_TRIPLE : FORM_PAIR);
+    p.form = half ? FORM_HALF : (D <= 8 ? FORM_OCTET : (D <= 16 ? FORM_TRIPLE : FORM_PAIR));
     p.stream = D > 128;
     p.tiles = (int)ceil_div(K, 32);
     p.pblocks = ceil_div(N, SC_POINTS);
-    if (p.stream) {
+    if (p.stream && half) {
+        p.ct = D <= 512 ? 4 : 2;  // point tiles of a workgroup: 128 KB of fragments at most
+        p.nb = (int)ceil_div(D, 16 * sp_ring(p.ct)) * sp_ring(p.ct);
+        p.pblocks = ceil_div(N, 32 * p.ct);
+        p.tpc = SP_CT;
+        p.nch = (int)ceil_div(p.tiles, SP_CT);
+        p.cps = p.nch;
+        p.splits = 1;
+    } else if (p.stream) {
         p.nb = 2 * (int)ceil_div(D, 32);
         // whole chunks of up to eight tiles; smaller ones while the chip is not filled
         int nch = (int)ceil_div(p.tiles, 8);
@@ -1644,6 +2217,18 @@ static ScanPlan cut_launch(ftk_dtype dtype, int64_t N, int D, int K)
     return p;
 }
 
+// the cut of the fp16 form for the points of a launch
+static ScanPlan cut_half(const ScanPlan &p, ftk_dtype dtype, int64_t N, int D, int K)
+{
+    ScanPlan h = cut_launch(dtype, N, D, K, true);
+    // the records of a launch are reserved for the other form's split
+    if (!p.stream && h.splits > p.splits) {
+        h.cps = (int)ceil_div(h.nch, p.splits);
+        h.splits = (int)ceil_div(h.nch, h.cps);
+    }
+    return h;
+}
+
 ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
 {
     ScanPlan p = cut_launch(dtype, N, D, K);
@@ -1654,6 +2239,12 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
         const int64_t n = ceil_div(N, batch_max);
         p = cut_launch(dtype, ceil_div(ceil_div(N, n), SCAN_BATCH_STEP) * SCAN_BATCH_STEP, D, K);
     }
+    p.half = p.form == FORM_PAIR && half_pays(dtype, p.batch, D, K);
+    if (p.half) {
+        const ScanPlan h = cut_half(p, dtype, p.batch, D, K);
+        p.half_nb = h.nb;
+        p.half_tiles = p.stream ? p.tiles + 8 : h.tiles_pad;
+    }
     // What the points or any part of them may need: fewer points may be shared by more workgroups than the whole,
     // but splits <= SCAN_FILL / pblocks + 1 wherever there is more than the whole's.
     const int64_t fill = (int64_t)SCAN_FILL * SC_POINTS;
@@ -1663,7 +2254,7 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     return p;
 }
 
-ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
+ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N, int D)
 {
     ScanBuffers b = {};
     if (!p.ok) return b;
@@ -1675,17 +2266,23 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N)
         return r;
     };
     // whole chunks of whatever size a batch is cut into: at most eight tiles (stream), tpc (resident)
-    const size_t tiles = p.stream ? (size_t)p.tiles + 8 : (size_t)p.tiles_pad;
+    const size_t tiles = p.stream ? (size_t)p.tiles + 8 : (size_t)(p.half && p.half_tiles > p.tiles_pad ? p.half_tiles : p.tiles_pad);
     b.image = (uint4 *)take(tiles * p.nb * form_frags(p.form) * FRAG_UNITS * 16);
     b.start = (float *)take((tiles + 1) * 32 * 4);  // copied two tiles a time
     b.tile_stat = (float4 *)take(tiles * sizeof(float4));
     b.norm = (float *)take(tiles * 32 * 4);
     b.scale = (double *)take(16);
     b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
-    b.list_count = (int32_t *)take((size_t)SCAN_LISTS * LIST_STRIDE * 4);
+    b.list_count = (int32_t *)take((size_t)(p.half ? 2 * SCAN_LISTS + 1 : SCAN_LISTS) * LIST_STRIDE * 4);
     const size_t points = N < SCAN_RECORDS ? N : SCAN_RECORDS;  // of a launch
     b.list = (ScanListed *)take((points + SCAN_LISTS * SETTLE_ROWS_MAX) * sizeof(ScanListed));
     b.tickets = (int32_t *)take((points / 32 + 1) * 4);
+    if (p.half) {
+        b.half_image = (uint4 *)take((size_t)p.half_tiles * p.half_nb * FRAG_UNITS * 16);
+        b.half_start = (float *)take(((size_t)p.half_tiles + 1) * 32 * 4);
+        b.ref = take((size_t)D * 8);
+        b.rest = (ScanListed *)take((points + SCAN_LISTS * SC_POINTS) * sizeof(ScanListed));
+    }
     b.bytes = off;
     return b;
 }
@@ -1695,10 +2292,19 @@ static void launch_resident(const ScanArgs &a, const ScanPlan &p, hipStream_t st
 {
     const dim3 grid((unsigned)(p.pblocks * p.splits)), block(SC_THREADS);
     const size_t lds = 2 * ((size_t)p.tpc * NB * form_frags(FORM) * FRAG_UNITS + (size_t)((p.tpc + 1) / 2) * 16) * 16;
-    if (a.D % 4)
-        hipLaunchKernelGGL((scan_resident_kernel<T, NB, FORM, true>), grid, block, lds, st, a);
-    else
-        hipLaunchKernelGGL((scan_resident_kernel<T, NB, FORM, false>), grid, block, lds, st, a);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a); };
+    const bool ragged = a.D % 4 != 0;
+    if constexpr (FORM == FORM_PAIR || FORM == FORM_HALF) {
+        if (a.gate.state) {
+            if (ragged) launch(scan_resident_kernel<T, NB, FORM, true, true>);
+            else launch(scan_resident_kernel<T, NB, FORM, false, true>);
+            return;
+        }
+    }
+    if constexpr (FORM != FORM_HALF) {
+        if (ragged) launch(scan_resident_kernel<T, NB, FORM, true, false>);
+        else launch(scan_resident_kernel<T, NB, FORM, false, false>);
+    }
 }
 
 template <typename T, int CT>
@@ -1706,37 +2312,176 @@ static void launch_stream(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
 {
     const dim3 grid((unsigned)(ceil_div(p.pblocks, 8) * 8 * p.nch)), block(SS_THREADS);
     const size_t lds = 2 * (size_t)(2 * CT + 8) * 4 * FRAG_UNITS * 16;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a); };
+    if (a.gate.state) {
+        if (a.D % 4) launch(scan_stream_kernel<T, CT, true, true>);
+        else launch(scan_stream_kernel<T, CT, false, true>);
+    } else {
+        if (a.D % 4) launch(scan_stream_kernel<T, CT, true, false>);
+        else launch(scan_stream_kernel<T, CT, false, false>);
+    }
+}
+
+template <typename T, int PT>
+static void launch_points(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
+{
+    const dim3 grid((unsigned)p.pblocks), block(SP_THREADS);
+    const size_t frags = (size_t)p.nb * PT * FRAG_UNITS * 16, records = (size_t)SP_WAVES * 32 * PT * 12;
+    const size_t lds = frags > records ? frags : records;
     if (a.D % 4)
-        hipLaunchKernelGGL((scan_stream_kernel<T, CT, true>), grid, block, lds, st, a);
+        hipLaunchKernelGGL((scan_points_kernel<T, PT, true>), grid, block, lds, st, a, p.nb);
     else
-        hipLaunchKernelGGL((scan_stream_kernel<T, CT, false>), grid, block, lds, st, a);
+        hipLaunchKernelGGL((scan_points_kernel<T, PT, false>), grid, block, lds, st, a, p.nb);
+}
+
+// the scan in form p.form of a call that `a` describes but for the cut
+template <typename T>
+static void launch_scan_form(ScanArgs a, const ScanPlan &p, hipStream_t st)
+{
+    a.tiles = p.tiles;
+    a.tpc = p.tpc;
+    a.nch = p.nch;
+    a.cps = p.cps;
+    a.splits = p.splits;
+    a.pblocks = (int)p.pblocks;
+    if (p.stream) {
+        if (p.form == FORM_HALF) {
+            if (p.ct == 4) launch_points<T, 4>(a, p, st);
+            else launch_points<T, 2>(a, p, st);
+            return;
+        }
+        switch (p.ct) {
+        case 1: launch_stream<T, 1>(a, p, st); break;
+        case 2: launch_stream<T, 2>(a, p, st); break;
+        case 3: launch_stream<T, 3>(a, p, st); break;
+        default: launch_stream<T, 4>(a, p, st); break;
+        }
+    } else if (p.form == FORM_OCTET) {
+        launch_resident<T, 1, FORM_OCTET>(a, p, st);
+    } else if (p.form == FORM_TRIPLE) {
+        launch_resident<T, 1, FORM_TRIPLE>(a, p, st);
+    } else {
+#define FTK_LAUNCH_RESIDENT(NB)                                                   \
+    case NB:                                                                      \
+        if (p.form == FORM_HALF) launch_resident<T, NB, FORM_HALF>(a, p, st);     \
+        else launch_resident<T, NB, FORM_PAIR>(a, p, st);                         \
+        break
+        switch (p.nb) {
+            FTK_LAUNCH_RESIDENT(2);
+            FTK_LAUNCH_RESIDENT(3);
+            FTK_LAUNCH_RESIDENT(4);
+            FTK_LAUNCH_RESIDENT(6);
+            FTK_LAUNCH_RESIDENT(8);
+        }
+#undef FTK_LAUNCH_RESIDENT
+    }
 }
 
 // L lanes per row in both passes
 template <typename T, int L>
-static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, ResolveArgs r, hipStream_t st)
+static void launch_recheck(const AssignCall &c, const ScanPlan &h, const ScanArgs &a, const RecheckArgs &r, hipStream_t st)
+{
+    const int64_t groups = ceil_div(c.N, RC_POINTS);
+    const dim3 grid((unsigned)(groups < 2048 ? groups : 2048)), block(SC_THREADS);
+    const size_t lds = 2 * ((size_t)a.tpc * h.nb * FRAG_UNITS + (size_t)((a.tpc + 1) / 2) * 16) * 16;
+#define FTK_LAUNCH_RECHECK(NB)                                                                                            \
+    case NB:                                                                                                              \
+        if (a.D % 4)                                                                                                      \
+            hipLaunchKernelGGL((scan_recheck_kernel<T, NB, true, L>), grid, block, lds, st, (const T *)c.X, (const T *)c.C, \
+                               (T *)c.mindist, a, r);                                                                     \
+        else                                                                                                              \
+            hipLaunchKernelGGL((scan_recheck_kernel<T, NB, false, L>), grid, block, lds, st, (const T *)c.X,              \
+                               (const T *)c.C, (T *)c.mindist, a, r);                                                     \
+        break
+    if constexpr (L == 4) {
+        switch (h.nb) {
+            FTK_LAUNCH_RECHECK(2);
+        }
+    } else {
+        switch (h.nb) {
+            FTK_LAUNCH_RECHECK(2);
+            FTK_LAUNCH_RECHECK(3);
+            FTK_LAUNCH_RECHECK(4);
+            FTK_LAUNCH_RECHECK(6);
+            FTK_LAUNCH_RECHECK(8);
+        }
+    }
+#undef FTK_LAUNCH_RECHECK
+}
+
+template <typename T, int L>
+static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, ResolveArgs r, const ScanBuffers &b,
+                          const ScanPlan &ph, const ScanArgs &ah, hipStream_t st)
 {
     const int rows = 256 / L * settle_rows(sizeof(T));
     static_assert(256 / L * settle_rows(sizeof(T)) <= SETTLE_ROWS_MAX, "list capacity");
+    // a lane adds up its share, a tree of six the lanes'; 10 u for the differences, their squares and the scale
+    s.sums = 0.5f * (float)((c.D / L + 4 + 6 + 10) * (double)Mma<float>::kEps);
     r.list_cap = s.list_cap = (int)ceil_div(ceil_div(c.N, rows), s.lists) * rows;
-    hipLaunchKernelGGL((scan_settle_kernel<T, L>), dim3((unsigned)ceil_div(c.N, rows)), dim3(256), 0, st, (const T *)c.X,
-                       (const T *)c.C, (T *)c.mindist, s);
+    const dim3 sg((unsigned)ceil_div(c.N, rows)), sb(256);
+    bool half = false;
+    if constexpr (L >= 4) {
+        half = p.half;
+        if (half)
+            hipLaunchKernelGGL((scan_settle_kernel<T, L, true>), sg, sb, 0, st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, s);
+    }
+    if (!half)
+        hipLaunchKernelGGL((scan_settle_kernel<T, L, false>), sg, sb, 0, st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, s);
     if (!p.resolve) return;
+    if (half) {
+        r.rest = b.rest;
+        r.rest_count = b.list_count + (SCAN_LISTS + 1) * LIST_STRIDE;
+        r.rest_cap = (int)ceil_div(ceil_div(c.N, RC_POINTS), SCAN_LISTS) * RC_POINTS;
+    }
+    if constexpr (L == 4 || L == 8) {
+        if (half) {
+            RecheckArgs q = {};
+            q.list = b.list;
+            q.list_count = b.list_count;
+            q.list_cap = s.list_cap;
+            q.rest = r.rest;
+            q.rest_count = r.rest_count;
+            q.rest_cap = r.rest_cap;
+            q.K = c.K;
+            q.labels = c.labels;
+            q.stats = c.stats;
+            ScanArgs whole = ah;
+            whole.tiles = ph.tiles;
+            whole.tpc = recheck_tiles(ph.nb);
+            whole.nch = (int)ceil_div(ph.tiles, whole.tpc);
+            launch_recheck<T, L>(c, ph, whole, q, st);
+        }
+    }
     const int64_t groups = ceil_div(c.N, 32);
     // any share of a group among 1 .. splits workgroups divides the grid's work: see the kernel
     const int64_t most = r.nb ? groups * r.splits : c.N;
     const dim3 grid((unsigned)(most < 1024 ? most : 1024)), block(RS_THREADS);
-#define FTK_LAUNCH_RESOLVE(F)                                                                                        \
-    hipLaunchKernelGGL((scan_resolve_kernel<T, F, L>), grid, block, (size_t)r.nb * form_pieces(F) * FRAG_UNITS * 16, \
-                       st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, r)
+#define FTK_LAUNCH_RESOLVE(F, G)                                                                                     \
+    hipLaunchKernelGGL((scan_resolve_kernel<T, F, L, G>), grid, block,                                               \
+                       (size_t)r.nb * form_pieces(F) * FRAG_UNITS * 16, st, (const T *)c.X, (const T *)c.C,          \
+                       (T *)c.mindist, r)
     if constexpr (L <= 2) {
-        if (p.form == FORM_OCTET) FTK_LAUNCH_RESOLVE(FORM_OCTET);
-        else FTK_LAUNCH_RESOLVE(FORM_TRIPLE);
-    } else if constexpr (L == 4) {
-        if (p.form == FORM_TRIPLE) FTK_LAUNCH_RESOLVE(FORM_TRIPLE);
-        else FTK_LAUNCH_RESOLVE(FORM_PAIR);
+        if (p.form == FORM_OCTET) FTK_LAUNCH_RESOLVE(FORM_OCTET, false);
+        else FTK_LAUNCH_RESOLVE(FORM_TRIPLE, false);
     } else {
-        FTK_LAUNCH_RESOLVE(FORM_PAIR);
+        if constexpr (L > 8) {
+            if (half) {
+                const ResolveArgs own = r;
+                r.image = b.half_image;
+                r.start = b.half_start;
+                r.nb = p.half_nb;
+                r.side = 512;
+                FTK_LAUNCH_RESOLVE(FORM_HALF, true);
+                r = own;
+            }
+        }
+        if (L == 4 && p.form == FORM_TRIPLE) {
+            if constexpr (L == 4) FTK_LAUNCH_RESOLVE(FORM_TRIPLE, false);
+        } else if (half) {
+            FTK_LAUNCH_RESOLVE(FORM_PAIR, true);
+        } else {
+            FTK_LAUNCH_RESOLVE(FORM_PAIR, false);
+        }
     }
 #undef FTK_LAUNCH_RESOLVE
 }
@@ -1756,12 +2501,25 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     const double psi = ((p.form == FORM_TRIPLE ? 42.0 : 21.0) * 1.01 * p.nb + 6.0) * u;
     // half of what A comes to for ||x|| = 1 makes the two parts of the bound smallest where ||c|| = 1 as well
     const double lift = 0.5 * ((p.form == FORM_PAIR ? 280.0 : 2.0) * u + psi) + 0.5 * psi;
-    const size_t ref_bytes = (size_t)p.nb * 16 * sizeof(T);
+    // the same for one fp16 piece: what is left of x is at most 2^-11 of it, of c some 0.4 of that; operands below
+    // 2^-14 count as that in the rounding of an instruction, and round to within 2^-11 of it
+    const double half_psi = (7.0 * 1.01 * p.half_nb + 6.0) * u;
+    HalfImage half = {};
+    if (p.half) {
+        half.gate = b.list_count + SCAN_LISTS * LIST_STRIDE;
+        half.image = b.half_image;
+        half.ref = b.ref;
+        half.start = b.half_start;
+        half.nb = p.half_nb;
+        half.lift = (float)(0.5 * (0.8 * 0x1p-11 + half_psi) + 0.5 * half_psi);
+        half.tiny = (float)(std::sqrt(16.0 * p.half_nb) * 0x1p-14);
+    }
+    const size_t ref_bytes = (size_t)(p.half && p.half_nb > p.nb ? p.half_nb : p.nb) * 16 * sizeof(T);
     const bool has_ref = ref_bytes <= REF_BYTES;
 #define FTK_LAUNCH_CENTROIDS(F)                                                                                       \
     hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, has_ref ? ref_bytes : 0, st, (const T *)c.C, c.D, c.K, p.nb, \
-                       b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref, b.norm, lift)
-    if (tiles == 0) FTK_TRY(launch_zero_ints(counts, (lists - 1) * LIST_STRIDE + 1, st));  // the preparation does that
+                       b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref, b.norm, lift, half)
+    if (tiles == 0) FTK_TRY(launch_zero_ints(counts, (lists - 1) * LIST_STRIDE + 1 + (p.half ? (SCAN_LISTS + 1) * LIST_STRIDE : 0), st));  // the preparation does that
     else if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
     else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE);
     else FTK_LAUNCH_CENTROIDS(FORM_PAIR);
@@ -1773,34 +2531,15 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     a.scale = b.scale;
     a.N = c.N;
     a.D = c.D;
-    a.tiles = p.tiles;
-    a.tpc = p.tpc;
-    a.nch = p.nch;
-    a.cps = p.cps;
-    a.splits = p.splits;
-    a.pblocks = (int)p.pblocks;
     a.rec = b.rec;
-    if (p.stream) {
-        switch (p.ct) {
-        case 1: launch_stream<T, 1>(a, p, st); break;
-        case 2: launch_stream<T, 2>(a, p, st); break;
-        case 3: launch_stream<T, 3>(a, p, st); break;
-        default: launch_stream<T, 4>(a, p, st); break;
-        }
-    } else if (p.form == FORM_OCTET) {
-        launch_resident<T, 1, FORM_OCTET>(a, p, st);
-    } else if (p.form == FORM_TRIPLE) {
-        launch_resident<T, 1, FORM_TRIPLE>(a, p, st);
-    } else {
-        switch (p.nb) {
-        case 2: launch_resident<T, 2, FORM_PAIR>(a, p, st); break;
-        case 3: launch_resident<T, 3, FORM_PAIR>(a, p, st); break;
-        case 4: launch_resident<T, 4, FORM_PAIR>(a, p, st); break;
-        case 6: launch_resident<T, 6, FORM_PAIR>(a, p, st); break;
-        default: launch_resident<T, 8, FORM_PAIR>(a, p, st); break;
-        }
-    }
-    SettleArgs s;
+    ScanArgs ah = a;  // fp16 pieces
+    ah.image = b.half_image;
+    ah.start = b.half_start;
+    const ScanPlan ph = p.half ? cut_half(p, c.dtype, c.N, c.D, c.K) : ScanPlan{};
+    ah.norm = b.norm;
+    ah.tile_stat = b.tile_stat;
+    if (p.half) a.gate = ah.gate = ScanGate{b.list_count + SCAN_LISTS * LIST_STRIDE, HALF_VOTERS * (p.stream ? ph.ct / 2 : SC_THREADS / 64)};
+    SettleArgs s = {};
     s.rec = b.rec;
     s.splits = p.splits;
     s.tile_stat = b.tile_stat;
@@ -1814,6 +2553,7 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     s.norm = b.norm;
     s.lost = (float)(p.form == FORM_PAIR ? 128.0 * u : 2.0 * u);  // ||r_x|| <= 2^-17 ||x||; three pieces hold 24 bits
     s.slack = (float)(1.0001 + c.D * u);
+    s.ref = b.ref;
     s.tiny = (float)(std::sqrt((double)c.D) * 0x1p-73);  // squares below 2^-149 are lost
     s.labels = c.labels;
     s.tickets = b.tickets;
@@ -1821,7 +2561,13 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     s.wl = w.wl;
     s.list_count = counts;
     s.lists = lists;
-    ResolveArgs r;
+    s.gate = a.gate;
+    s.half_splits = ph.splits;
+    s.half_psi = (float)half_psi;
+    s.half_lift = half.lift;
+    s.half_tiny = half.tiny;
+    ResolveArgs r = {};
+    r.gate = a.gate;
     r.image = b.image;
     r.start = b.start;
     r.scale = b.scale;
@@ -1838,11 +2584,16 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     r.list_count = b.list_count;
     r.tickets = b.tickets;
     r.stats = c.stats;
-    if (c.D <= 12) launch_settle<T, 2>(c, p, s, r, st);
-    else if (c.D <= 24) launch_settle<T, 4>(c, p, s, r, st);
-    else if (c.D <= 128) launch_settle<T, 8>(c, p, s, r, st);
-    else if (c.D <= 512) launch_settle<T, 16>(c, p, s, r, st);
-    else launch_settle<T, 64>(c, p, s, r, st);
+    auto settle = [&](const SettleArgs &q) {
+        if (c.D <= 12) launch_settle<T, 2>(c, p, q, r, b, ph, ah, st);
+        else if (c.D <= 24) launch_settle<T, 4>(c, p, q, r, b, ph, ah, st);
+        else if (c.D <= 128) launch_settle<T, 8>(c, p, q, r, b, ph, ah, st);
+        else if (c.D <= 512) launch_settle<T, 16>(c, p, q, r, b, ph, ah, st);
+        else launch_settle<T, 64>(c, p, q, r, b, ph, ah, st);
+    };
+    if (p.half) launch_scan_form<T>(ah, ph, st);
+    launch_scan_form<T>(a, p, st);
+    settle(s);
     FTK_TRY_HIP(hipGetLastError());
     return p.resolve ? FTK_OK : launch_refine(c, w, 0, st);
 }
@@ -1853,6 +2604,8 @@ ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const Scan
     const int64_t rest = c.N % p.batch;
     ScanPlan last = rest ? cut_scan(c.dtype, rest, c.D, c.K) : p;  // fewer points may be cut into smaller chunks
     int tiles = p.tiles_pad > last.tiles_pad ? p.tiles_pad : last.tiles_pad;
+    last.half = last.half && p.half;
+    if (p.half && tiles < p.half_tiles) tiles = p.half_tiles;
     for (int64_t r0 = 0; r0 < c.N; r0 += p.batch) {
         AssignCall part = c;
         part.N = c.N - r0 < p.batch ? c.N - r0 : p.batch;

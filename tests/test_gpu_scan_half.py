@@ -1,0 +1,134 @@
+"""The scan on fp16 pieces, which large unprotected assignments try first: widths and ragged rows of its compiled
+variants, data that make it hand over to the bf16 pieces, points with more candidates than it notes, values beyond the
+range of fp16, a workspace without room for it.  Sampled rows against the CPU oracle; every row against the same call
+in parts that are too small for it."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import cpu as oracle
+from paper_2408_01391_amd import binding as ftk
+from tests.gpu_util import DEV, check_assign, to_dev
+from tests.test_gpu_scan import EPS, NP, run
+
+pytestmark = pytest.mark.gpu
+
+
+def blobs(seed, N, D, K, dtype):
+    rng = np.random.default_rng(seed)
+    centres = (rng.normal(size=(K, D)) * 5).astype(NP[dtype])
+    X = rng.normal(size=(N, D)).astype(NP[dtype])
+    X += centres[rng.integers(0, K, N)]
+    return X, X[rng.permutation(N)[:K]].copy()
+
+
+def in_parts(X, C, parts=6):
+    out = [run(p, C) for p in np.array_split(X, parts)]
+    return np.concatenate([o[0] for o in out]), np.concatenate([o[1] for o in out])
+
+
+def check(X, C, dtype, seed=0):
+    labels, mind = run(X, C)
+    rows = np.sort(np.random.default_rng(seed).permutation(len(X))[:1500])
+    lab_o, d1, d2 = ref = oracle.assign(X, C, rows)
+    check_assign(X, C, labels, mind, rows=rows, ref=ref)
+    # direct differences: D terms of at most 3 roundings each, the oracle's own included
+    tol = 2 * (X.shape[1] + 4) * EPS[dtype]
+    assert np.all(np.abs(mind[rows].astype(np.float64) - d1) <= tol * d1)
+    lab_p, mind_p = in_parts(X, C)
+    assert np.array_equal(labels, lab_p)
+    assert np.all(np.abs(mind.astype(np.float64) - mind_p) <= tol * mind_p)
+    return labels
+
+
+SIZES = [("f32", 300007, 17, 2950), ("f32", 250001, 33, 1900), ("f32", 130003, 64, 1805), ("f32", 100001, 97, 1550),
+         ("f32", 60001, 128, 1960), ("f32", 100003, 129, 931), ("f32", 40001, 255, 1200), ("f32", 33001, 512, 720),
+         ("f32", 32769, 513, 720), ("f32", 33333, 1024, 360), ("f64", 300007, 20, 6700), ("f64", 150001, 128, 2085),
+         ("f64", 130003, 90, 3500), ("f64", 70001, 192, 900), ("f64", 33001, 1021, 357)]
+
+
+@pytest.mark.parametrize("dtype,N,D,K", SIZES)
+def test_labels_and_distances_at_the_edges(dtype, N, D, K):
+    print("half", dtype, N, D, K, flush=True)
+    check(*blobs(N + D, N, D, K, dtype), dtype)
+
+
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 130003, 64, 1805), ("f32", 33001, 512, 720), ("f64", 70001, 192, 900)])
+@pytest.mark.parametrize("data", ["groups", "offset", "last points"])
+def test_data_that_it_cannot_tell(data, dtype, N, D, K):
+    X, C = blobs(D, N, D, K, dtype)
+    rng = np.random.default_rng(1)
+    if data == "groups":  # refused: every point has the centroids of its group within the bound
+        X += np.where(rng.random(N) < 0.5, 300, -300)[:, None].astype(X.dtype)
+        C = X[rng.permutation(N)[:K]].copy()
+    elif data == "offset":
+        X += X.dtype.type(400)
+        C = C + C.dtype.type(400)
+    else:  # not seen by those who vote; more candidates than are noted, equal ones among them
+        C[40:70] = C[5] + (rng.normal(size=(30, D)) * 1e-5).astype(C.dtype)
+        C[50] = C[5]
+        X[-400:] = C[5]
+    labels = check(X, C, dtype)
+    if data == "last points":
+        assert np.all(labels[-400:] == 5)
+
+
+@pytest.mark.parametrize("N,D,K", [(130003, 64, 1805), (33001, 512, 720)])
+def test_values_beyond_fp16_and_values_that_are_not_numbers(N, D, K):
+    X, C = blobs(D + 1, N, D, K, "f32")
+    clean, mind = run(X, C)
+    Xb = X.copy()
+    Xb[7, 3], Xb[600, 0], Xb[N - 3, D - 1], Xb[9000, 5] = np.nan, np.inf, 3e38, 1e7
+    labels, md = run(Xb, C)
+    keep = np.ones(N, bool)
+    keep[[7, 600, N - 3, 9000]] = False
+    assert np.array_equal(labels[keep], clean[keep]) and np.array_equal(md[keep], mind[keep])
+    assert labels.min() >= 0 and labels.max() < K
+    rows = np.array([9000])
+    check_assign(Xb, C, labels, rows=rows, ref=oracle.assign(Xb, C, rows))
+    far = C.copy()
+    far[17] = -1e8  # refused whatever the points' products with it
+    bad = C.copy()
+    bad[17] = np.nan
+    a, b = run(X, far), run(X, bad)
+    assert np.array_equal(a[0], b[0])
+    assert np.all(np.abs(a[1].astype(np.float64) - b[1]) <= 2 * (D + 4) * EPS["f32"] * b[1])  # listed points: in double
+    rows = np.arange(0, N, 97)
+    check_assign(X, far, *a, rows=rows, ref=oracle.assign(X, far, rows))
+
+
+def test_a_workspace_without_room_for_it():
+    X, C = blobs(3, 300007, 20, 6700, "f64")  # nothing else needs more of the workspace
+    Xd, Cd = to_dev(X), to_dev(C)
+    full = ftk.new_workspace(Xd, len(C), ftk.FT_OFF)
+    labels, mind = ftk.kmeans_assign(Xd, Cd, workspace=full)
+    cut = torch.empty(full.numel() - 4096, dtype=full.dtype, device=DEV)
+    lab2, mind2 = ftk.kmeans_assign(Xd, Cd, workspace=cut)
+    assert torch.equal(labels, lab2)
+    assert torch.allclose(mind, mind2, rtol=2 * 24 * EPS["f64"], atol=0)
+
+
+@pytest.mark.parametrize("N,D,K", [(130003, 64, 1805), (33001, 512, 720)])
+def test_a_captured_call_replays_on_new_contents(N, D, K):
+    X, C = blobs(4, N, D, K, "f32")
+    X2, C2 = blobs(5, N, D, K, "f32")
+    X2 += np.float32(400)  # the form is chosen anew by every replay
+    C2 += np.float32(400)
+    Xd, Cd = to_dev(X), to_dev(C)
+    ws = ftk.new_workspace(Xd, K, ftk.FT_OFF)
+    labels = torch.empty(N, dtype=torch.int32, device=DEV)
+    mind = torch.empty(N, dtype=torch.float32, device=DEV)
+    ftk.kmeans_assign(Xd, Cd, labels=labels, mindist=mind, workspace=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ftk.kmeans_assign(Xd, Cd, labels=labels, mindist=mind, workspace=ws)
+    for x, c in ((X2, C2), (X, C), (X2, C2)):
+        want = run(x, c)
+        Xd.copy_(to_dev(x))
+        Cd.copy_(to_dev(c))
+        labels.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(labels.cpu().numpy(), want[0])
+        assert np.allclose(mind.cpu().numpy(), want[1], rtol=2 * (D + 4) * EPS["f32"], atol=0)
