@@ -1900,9 +1900,10 @@ __global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_re
 
 // ---- listed points of a scan on fp16 pieces, rows of up to 128 features -------------------------------
 // These are some percent of all points, most with two candidates, so their sweep is shaped like the scan itself: fragments
-// in registers, the image through LDS.  (By scan_resolve_kernel, 32 points a group and a chain of latencies
+// in registers.  (By scan_resolve_kernel, 32 points a group and a chain of latencies
 // each: 160 us for the 68 000 points of 2^21 x 32, K = 4096.)  The four waves of a workgroup share 64 points
-// and take every fourth tile: 256 points of their own each took 123 us, one workgroup per compute unit.  A lane notes the centroids
+// and take every fourth tile, its fragments straight from L2 while those before are multiplied (256 points of their own
+// each took 123 us, one workgroup per compute unit; the image in chunks through LDS 86 us; so 69).  A lane notes the centroids
 // whose score reaches its point's threshold; then L lanes at a time evaluate them in double.  A point with
 // more of them than are noted goes on to scan_resolve_kernel, to meet all centroids.
 struct RecheckArgs {
@@ -1917,16 +1918,14 @@ struct RecheckArgs {
     ftk_ft_stats *stats;
 };
 constexpr int RC_CAP = 6, RC_POINTS = SC_PT * 32;
-constexpr int recheck_tiles(int nb) { return nb <= 3 ? 8 : 4; }  // of a chunk: 16 .. 32 KB, a multiple of the waves
 
 template <typename T, int NB, bool RAG, int L>
-__global__ __launch_bounds__(SC_THREADS, resident_waves(NB + 1, FORM_HALF, sizeof(T) == 8, RAG))
+__global__ __launch_bounds__(SC_THREADS, (NB <= 2 ? 4 : (NB <= 4 ? 3 : 2)))
 void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, RecheckArgs r)
 {
     if (a.gate.closed<FORM_HALF>()) return;
     constexpr int TU = NB * FRAG_UNITS;
     constexpr int GROUPS = SC_THREADS / L;
-    extern __shared__ __align__(16) uint4 lds4[];
     __shared__ int sh_pre[SCAN_LISTS + 1];
     __shared__ int32_t sh_p[RC_POINTS];
     __shared__ float sh_thr[RC_POINTS];
@@ -1935,7 +1934,6 @@ void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, Recheck
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
     const int sub = tid & (L - 1), grp = tid / L;
-    const int cu = a.tpc * TU + ((a.tpc + 1) / 2) * 16;
     if (wave == 0) {
         int v = r.list_count[lane * LIST_STRIDE];
 #pragma unroll
@@ -1949,19 +1947,9 @@ void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, Recheck
     __syncthreads();
     const int n = sh_pre[SCAN_LISTS];
     if (r.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&r.stats->refined, (unsigned long long)n);
-    auto stage = [&](int ch, uint4 *buf) {
-        const int tile0 = ch * a.tpc;
-        const uint4 *src = a.image + (size_t)tile0 * TU;
-        const int m = min(a.tpc, a.tiles - tile0) * NB;
-        for (int i = wave; i < m; i += SC_THREADS / 64) to_lds16(src + i * FRAG_UNITS + lane, buf + i * FRAG_UNITS);
-        const float *sv = a.start + tile0 * 32;
-        float *dst = reinterpret_cast<float *>(buf + a.tpc * TU);
-        for (int i = wave; 2 * i < a.tpc; i += SC_THREADS / 64) to_lds4(sv + i * 64 + lane, dst + i * 64);
-    };
     const T s = (T)a.scale[0];
     for (int64_t first = (int64_t)blockIdx.x * RC_POINTS; first < n; first += (int64_t)gridDim.x * RC_POINTS) {
         __syncthreads();  // the points before these are done
-        stage(0, lds4);
         if (tid < RC_POINTS) {
             const int64_t i = first + tid < n ? first + tid : n - 1;
             int q = 0;
@@ -1995,55 +1983,52 @@ void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, Recheck
                 b[pt][k] = round_half(v);
             }
         }
-        wait_loads<0>();
-        __syncthreads();
-        int cur = 0;
-        for (int ch = 0; ch < a.nch; ++ch) {
-            const uint4 *buf = lds4 + cur * cu;
-            if (ch + 1 < a.nch) stage(ch + 1, lds4 + (cur ^ 1) * cu);
-            const int nt = min(a.tpc, a.tiles - ch * a.tpc);
-            const float *hv = reinterpret_cast<const float *>(buf + a.tpc * TU) + g * 16;
-            for (int t = wave; t < nt; t += SC_THREADS / 64) {
-                const uint4 *f = buf + t * TU + lane;
-                floatx16 acc[SC_PT];
-                floatx16 ci;
+        // this wave's tiles, fragments and start values of the next one requested ahead
+        uint4 f[NB];
+        floatx4 h[4];
+        auto request = [&](int t) {
+            const uint4 *src = a.image + (size_t)min(t, a.tiles - 1) * TU + lane;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const floatx4 h = *reinterpret_cast<const floatx4 *>(hv + t * 32 + 4 * i);
+            for (int k = 0; k < NB; ++k) f[k] = src[k * FRAG_UNITS];
+            const float *hv = a.start + min(t, a.tiles - 1) * 32 + g * 16;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) ci[4 * i + e] = h[e];
-                }
+            for (int i = 0; i < 4; ++i) h[i] = *reinterpret_cast<const floatx4 *>(hv + 4 * i);
+        };
+        request(wave);
+        for (int t = wave; t < a.tiles; t += SC_THREADS / 64) {
+            floatx16 acc[SC_PT];
+            halfx8 af[NB];
 #pragma unroll
-                for (int pt = 0; pt < SC_PT; ++pt) acc[pt] = ci;
+            for (int k = 0; k < NB; ++k) af[k] = __builtin_bit_cast(halfx8, f[k]);
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const halfx8 af = __builtin_bit_cast(halfx8, f[k * FRAG_UNITS]);
+            for (int i = 0; i < 16; ++i)
 #pragma unroll
-                    for (int pt = 0; pt < SC_PT; ++pt)
-                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, __builtin_bit_cast(halfx8, b[pt][k]), acc[pt], 0, 0, 0);
-                }
+                for (int pt = 0; pt < SC_PT; ++pt) acc[pt][i] = h[i / 4][i % 4];
+            request(t + SC_THREADS / 64);
 #pragma unroll
-                for (int pt = 0; pt < SC_PT; ++pt) {
-                    float tm = fmaxf(acc[pt][0], acc[pt][1]);
+            for (int k = 0; k < NB; ++k)
 #pragma unroll
-                    for (int i = 2; i < 16; i += 2) tm = max3f(tm, acc[pt][i], acc[pt][i + 1]);
-                    if (__any(tm >= thr[pt])) {
-                        const int at = pt * 32 + col;
+                for (int pt = 0; pt < SC_PT; ++pt)
+                    acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[k], __builtin_bit_cast(halfx8, b[pt][k]), acc[pt], 0, 0, 0);
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            const int j = 32 * (ch * a.tpc + t) + 8 * (i >> 2) + 4 * g + (i & 3);
-                            if (acc[pt][i] >= thr[pt] && j < r.K) {
-                                const int slot = atomicAdd(&sh_cnt[at], 1);
-                                if (slot < RC_CAP) sh_j[at][slot] = j;
-                            }
+            for (int pt = 0; pt < SC_PT; ++pt) {
+                float tm = fmaxf(acc[pt][0], acc[pt][1]);
+#pragma unroll
+                for (int i = 2; i < 16; i += 2) tm = max3f(tm, acc[pt][i], acc[pt][i + 1]);
+                if (__any(tm >= thr[pt])) {
+                    const int at = pt * 32 + col;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int j = 32 * t + 8 * (i >> 2) + 4 * g + (i & 3);
+                        if (acc[pt][i] >= thr[pt] && j < r.K) {
+                            const int slot = atomicAdd(&sh_cnt[at], 1);
+                            if (slot < RC_CAP) sh_j[at][slot] = j;
                         }
                     }
                 }
             }
-            wait_loads<0>();  // the next chunk has arrived
-            __syncthreads();
-            cur ^= 1;
         }
+        __syncthreads();
         const int np = (int)(n - first < RC_POINTS ? n - first : RC_POINTS);
         for (int i = grp; i < np; i += GROUPS) {
             const int m = sh_cnt[i], p = sh_p[i];
@@ -2383,14 +2368,13 @@ static void launch_recheck(const AssignCall &c, const ScanPlan &h, const ScanArg
 {
     const int64_t groups = ceil_div(c.N, RC_POINTS);
     const dim3 grid((unsigned)(groups < 2048 ? groups : 2048)), block(SC_THREADS);
-    const size_t lds = 2 * ((size_t)a.tpc * h.nb * FRAG_UNITS + (size_t)((a.tpc + 1) / 2) * 16) * 16;
 #define FTK_LAUNCH_RECHECK(NB)                                                                                            \
     case NB:                                                                                                              \
         if (a.D % 4)                                                                                                      \
-            hipLaunchKernelGGL((scan_recheck_kernel<T, NB, true, L>), grid, block, lds, st, (const T *)c.X, (const T *)c.C, \
+            hipLaunchKernelGGL((scan_recheck_kernel<T, NB, true, L>), grid, block, 0, st, (const T *)c.X, (const T *)c.C,   \
                                (T *)c.mindist, a, r);                                                                     \
         else                                                                                                              \
-            hipLaunchKernelGGL((scan_recheck_kernel<T, NB, false, L>), grid, block, lds, st, (const T *)c.X,              \
+            hipLaunchKernelGGL((scan_recheck_kernel<T, NB, false, L>), grid, block, 0, st,  (const T *)c.X,              \
                                (const T *)c.C, (T *)c.mindist, a, r);                                                     \
         break
     if constexpr (L == 4) {
@@ -2447,8 +2431,6 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
             q.stats = c.stats;
             ScanArgs whole = ah;
             whole.tiles = ph.tiles;
-            whole.tpc = recheck_tiles(ph.nb);
-            whole.nch = (int)ceil_div(ph.tiles, whole.tpc);
             launch_recheck<T, L>(c, ph, whole, q, st);
         }
     }
