@@ -1,4 +1,4 @@
-// Assignment for the unprotected path: a scan on the bf16 matrix instructions names each point's
+// Assignment for the unprotected path: a scan on the 16-bit matrix instructions names each point's
 // nearest centroid, further passes settle it exactly (see ftk_scan.hip).
 #pragma once
 

@@ -1,7 +1,7 @@
 // Assignment without fault tolerance for fp32 and fp64 data, in three passes:
 //
-//   scan    the contraction on the bf16 matrix instructions, both operands split into two bf16 pieces,
-//           fp32 accumulation.  Per point it keeps the best score, its centroid and the second-best
+//   scan    the contraction on the 16-bit matrix instructions, both operands split into two bf16 pieces (large
+//           calls: rounded to one fp16 piece), fp32 accumulation.  Per point it keeps the best score, its centroid and the second-best
 //           score - nothing else;
 //   settle  the distance to the named centroid in direct-difference form, in the data's own type
 //           (Section 3.1.1), and the decision whether the scan could be trusted: where the two best
@@ -104,6 +104,8 @@ struct ScanGate {
     int votes;       // waves that vote
     __device__ __forceinline__ bool refused() const { return __hip_atomic_load(state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0; }
     __device__ __forceinline__ bool half() const { return state && !refused(); }
+    // (While the others vote the waves of one workgroup may read different answers: those that go on then work on fragments
+    // that nobody staged, which is harmless - every record is written again by the other form, and voters started earlier.)
     template <int FORM>
     __device__ __forceinline__ bool closed() const
     {
@@ -295,11 +297,13 @@ struct HalfImage {
     float lift, tiny;
 };
 constexpr size_t REF_BYTES = 64 * 1024;
-template <typename T, int FORM>
+// HALF: the second image too
+template <typename T, int FORM, bool HALF>
 __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
                                                               float4 *tile_stat, double *scale, int32_t *list_count, int lists,
-                                                              int has_ref, float *norm, double lift, HalfImage half)
+                                                              int has_ref, float *norm, double lift, HalfImage half_args)
 {
+    const HalfImage half = HALF ? half_args : HalfImage{};
     extern __shared__ __align__(16) unsigned char lds_raw[];
     T *const ref = reinterpret_cast<T *>(lds_raw);  // [16 nb_all]
     const int nb_all = max(nb, half.nb);
@@ -2498,13 +2502,15 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     }
     const size_t ref_bytes = (size_t)(p.half && p.half_nb > p.nb ? p.half_nb : p.nb) * 16 * sizeof(T);
     const bool has_ref = ref_bytes <= REF_BYTES;
-#define FTK_LAUNCH_CENTROIDS(F)                                                                                       \
-    hipLaunchKernelGGL((scan_centroids_kernel<T, F>), cg, cb, has_ref ? ref_bytes : 0, st, (const T *)c.C, c.D, c.K, p.nb, \
+#define FTK_LAUNCH_CENTROIDS(F, H)                                                                                    \
+    hipLaunchKernelGGL((scan_centroids_kernel<T, F, H>), cg, cb, has_ref ? ref_bytes : 0, st, (const T *)c.C, c.D, c.K, p.nb, \
                        b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref, b.norm, lift, half)
-    if (tiles == 0) FTK_TRY(launch_zero_ints(counts, (lists - 1) * LIST_STRIDE + 1 + (p.half ? (SCAN_LISTS + 1) * LIST_STRIDE : 0), st));  // the preparation does that
-    else if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET);
-    else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE);
-    else FTK_LAUNCH_CENTROIDS(FORM_PAIR);
+    const int zeros = (lists - 1) * LIST_STRIDE + 1 + (p.half ? (SCAN_LISTS + 1) * LIST_STRIDE : 0);
+    if (tiles == 0) FTK_TRY(launch_zero_ints(counts, zeros, st));  // the preparation does that
+    else if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET, false);
+    else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE, false);
+    else if (p.half) FTK_LAUNCH_CENTROIDS(FORM_PAIR, true);
+    else FTK_LAUNCH_CENTROIDS(FORM_PAIR, false);
 #undef FTK_LAUNCH_CENTROIDS
     ScanArgs a = {};
     a.X = c.X;
