@@ -31,9 +31,10 @@ if ROOT not in sys.path:
 
 PEAK = {"f32": 157.3, "f64": 78.6}          # dense MFMA TFLOP/s, MI355X datasheet
 BF16_PEAK = 2500.0
-# unprotected assignments that scan on the bf16 matrix instructions: bf16 products per multiplication
-# (8 features fill half of a block of six products in three instructions, longer rows take two pieces)
-SCAN_PRODUCTS = {"c2": 6, "c3": 3, "c5": 3}
+# unprotected assignments that scan on the 16-bit matrix instructions: products per multiplication (8 features
+# fill half of a block of six products in three instructions, longer rows take two bf16 pieces, and where there
+# is enough matrix work one fp16 piece)
+SCAN_PRODUCTS = {"c2": 6, "c3": 3, "c5": 1}
 HBM_PEAK_GBS = 8000.0
 DEFAULT_STEPS = {"c1": 200, "c2": 100, "c3": 100, "c4": 20, "c5": 10}
 ALL = ["c1", "c2", "c3", "c4", "c5"]
@@ -523,8 +524,8 @@ def main():
             "frac_whole_call": a["frac_mfma_call"] if mfma_bound else None,
             "call_ms": a["call_ms"],
             "frac_hbm_algorithmic": a["frac_hbm_kernel"],
-            "note": "2*N*D*K over what the unit it runs on could do: with FT off c2, c3 and c5 scan on the bf16 matrix "
-                    "instructions, 3 or 6 products a multiplication (kernel_ms = scan with its preparation and "
+            "note": "2*N*D*K over what the unit it runs on could do: with FT off c2, c3 and c5 scan on the 16-bit matrix "
+                    "instructions, 6, 3 and 1 products a multiplication (kernel_ms = scan with its preparation and "
                     "settlement); the others and the checksummed legs run the fp32 / fp64 instructions",
         },
         "configs": configs,
