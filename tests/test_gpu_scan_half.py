@@ -44,7 +44,8 @@ def check(X, C, dtype, seed=0):
 SIZES = [("f32", 300007, 17, 2950), ("f32", 250001, 33, 1900), ("f32", 130003, 64, 1805), ("f32", 100001, 97, 1550),
          ("f32", 60001, 128, 1960), ("f32", 100003, 129, 931), ("f32", 40001, 255, 1200), ("f32", 33001, 512, 720),
          ("f32", 32769, 513, 720), ("f32", 33333, 1024, 360), ("f64", 300007, 20, 6700), ("f64", 150001, 128, 2085),
-         ("f64", 130003, 90, 3500), ("f64", 70001, 192, 900), ("f64", 33001, 1021, 357)]
+         ("f64", 130003, 90, 3500), ("f64", 70001, 192, 900), ("f64", 33001, 1021, 357),
+         ("f32", 530001, 130, 2100)]  # the last one in two launches, the second on the image of the first
 
 
 @pytest.mark.parametrize("dtype,N,D,K", SIZES)
