@@ -125,7 +125,8 @@ ftk_status ftk_ft_thresholds(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, f
  * whole chunks of their own blocking (Section 3.2: several tile shapes per problem), and the
  * prologue writes -||c||^2/2 for every padded row.  Reports the largest padded row count over
  * every kernel variant and fault-tolerance mode that can be dispatched or forced for the problem,
- * and the rows the workspace reserves; planned_max <= reserved must hold. */
+ * and the rows the workspace reserves; planned_max <= reserved must hold.  The scan of unprotected
+ * calls pads and reserves by itself: where it falls short, its figures are reported instead. */
 ftk_status ftk_plan_padded_rows(ftk_dtype dtype, int64_t N, int32_t D, int32_t K,
                                 int64_t *planned_max /* (host) */, int64_t *reserved /* (host) */);
 

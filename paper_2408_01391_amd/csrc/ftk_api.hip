@@ -171,11 +171,17 @@ static FastRoute route_fast(int64_t N, int D, int K, ftk_ft_mode ft, int n_fault
     return fast_rule(N, D, K);
 }
 
+// whether the plain or the reduced-precision entry point may scan
+static bool may_scan(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    return plan_scan(dtype, N, D, K).ok || (fast_supported(dtype, D) && fast_rule(N, D, K) == FAST_SCAN);
+}
+
 // bytes of the scan's buffers for the plain or the reduced-precision entry point, whatever kernel is forced;
 // half: with those of its fp16 pieces, without which it runs as well
 static size_t scan_bytes(ftk_dtype dtype, int64_t N, int D, int K, bool half)
 {
-    if (!plan_scan(dtype, N, D, K).ok && !(fast_supported(dtype, D) && fast_rule(N, D, K) == FAST_SCAN)) return 0;
+    if (!may_scan(dtype, N, D, K)) return 0;
     ScanPlan p = cut_scan(dtype, N, D, K);
     p.half = p.half && half;
     return carve_scan(nullptr, p, N, D).bytes;
@@ -548,6 +554,14 @@ ftk_status ftk_plan_padded_rows(ftk_dtype dtype, int64_t N, int32_t D, int32_t K
     }
     *planned_max = worst;
     *reserved = (int64_t)hcn_entries_max(dtype, N, D, K);
+    if (may_scan(dtype, N, D, K)) {  // its arrays are reserved by themselves
+        int64_t planned = 0, rows = 0;
+        scan_padded_rows(dtype, N, D, K, &planned, &rows);
+        if (planned > rows) {
+            *planned_max = planned;
+            *reserved = rows;
+        }
+    }
     return FTK_OK;
 }
 

@@ -56,6 +56,8 @@ struct ScanBuffers {
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // the cut alone, for part of a problem that takes this path
 ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K);
+// rows that the preparation writes for the points or for any batch of them, and those its images are reserved for
+void scan_padded_rows(ftk_dtype dtype, int64_t N, int D, int K, int64_t *planned, int64_t *reserved);
 // buffers for the whole problem and for any batch of it
 ScanBuffers carve_scan(void *base, const ScanPlan &whole, int64_t N, int D);
 ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,

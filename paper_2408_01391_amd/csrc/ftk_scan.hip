@@ -2232,7 +2232,8 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     if (p.half) {
         const ScanPlan h = cut_half(p, dtype, p.batch, D, K);
         p.half_nb = h.nb;
-        p.half_tiles = p.stream ? p.tiles + 8 : h.tiles_pad;
+        // the preparation writes both images for every tile of its grid, which is padded for the larger chunks
+        p.half_tiles = p.stream ? p.tiles + 8 : (h.tiles_pad > p.tiles_pad ? h.tiles_pad : p.tiles_pad);
     }
     // What the points or any part of them may need: fewer points may be shared by more workgroups than the whole,
     // but splits <= SCAN_FILL / pblocks + 1 wherever there is more than the whole's.
@@ -2241,6 +2242,40 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
     if (p.rec_reserve < fill + (N < fill ? N : fill) + SC_POINTS) p.rec_reserve = fill + (N < fill ? N : fill) + SC_POINTS;
     if (p.rec_reserve > (int64_t)p.tiles * N) p.rec_reserve = (int64_t)p.tiles * N;
     return p;
+}
+
+// Tiles that the preparation of a call writes; `last`: the cut of its last launch, whose chunks may be smaller.
+static int prepared_tiles(const ScanPlan &p, const ScanPlan &last)
+{
+    const int tiles = p.tiles_pad > last.tiles_pad ? p.tiles_pad : last.tiles_pad;
+    return p.half && tiles < p.half_tiles ? p.half_tiles : tiles;
+}
+
+static ScanPlan cut_last(const ScanPlan &p, ftk_dtype dtype, int64_t N, int D, int K)
+{
+    const int64_t rest = N % p.batch;
+    return rest ? cut_scan(dtype, rest, D, K) : p;
+}
+
+void scan_padded_rows(ftk_dtype dtype, int64_t N, int D, int K, int64_t *planned, int64_t *reserved)
+{
+    const ScanPlan whole = cut_scan(dtype, N, D, K);
+    const ScanBuffers b = carve_scan((void *)256, whole, N, D);  // (offsets alone)
+    const size_t tile = FRAG_UNITS * 16;
+    size_t room = ((char *)b.start - (char *)b.image) / ((size_t)whole.nb * form_frags(whole.form) * tile);
+    if (whole.half) {
+        const size_t h = ((char *)b.half_start - (char *)b.half_image) / ((size_t)whole.half_nb * tile);
+        room = h < room ? h : room;
+    }
+    int most = 0;
+    for (int64_t n = N; n >= 1; n /= 2) {  // the points, and batches of them
+        ScanPlan p = cut_scan(dtype, n, D, K);
+        p.half = p.half && whole.half;
+        const int t = prepared_tiles(p, cut_last(p, dtype, n, D, K));
+        most = t > most ? t : most;
+    }
+    *planned = 32 * (int64_t)most;
+    *reserved = 32 * (int64_t)room;
 }
 
 ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N, int D)
@@ -2589,11 +2624,9 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
 ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w, hipStream_t st)
 {
     const size_t esz = c.dtype == FTK_F32 ? 4 : 8;
-    const int64_t rest = c.N % p.batch;
-    ScanPlan last = rest ? cut_scan(c.dtype, rest, c.D, c.K) : p;  // fewer points may be cut into smaller chunks
-    int tiles = p.tiles_pad > last.tiles_pad ? p.tiles_pad : last.tiles_pad;
+    ScanPlan last = cut_last(p, c.dtype, c.N, c.D, c.K);
     last.half = last.half && p.half;
-    if (p.half && tiles < p.half_tiles) tiles = p.half_tiles;
+    int tiles = prepared_tiles(p, last);
     for (int64_t r0 = 0; r0 < c.N; r0 += p.batch) {
         AssignCall part = c;
         part.N = c.N - r0 < p.batch ? c.N - r0 : p.batch;

@@ -54,6 +54,14 @@ def test_labels_and_distances_at_the_edges(dtype, N, D, K):
     check(*blobs(N + D, N, D, K, dtype), dtype)
 
 
+# 25 and 35 tiles of centroids: rows of 3 and 6 blocks, whose bf16 image is padded by a tile more than the fp16 chunks take
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 400001, 48, 800), ("f32", 280001, 47, 1120), ("f32", 200003, 96, 777),
+                                         ("f32", 140003, 91, 1120), ("f64", 530001, 96, 800), ("f64", 750001, 48, 1119)])
+def test_chunks_of_the_two_forms_that_pad_the_centroids_differently(dtype, N, D, K):
+    print("half", dtype, N, D, K, flush=True)
+    check(*blobs(N + D, N, D, K, dtype), dtype)
+
+
 @pytest.mark.parametrize("dtype,N,D,K", [("f32", 130003, 64, 1805), ("f32", 33001, 512, 720), ("f64", 70001, 192, 900)])
 @pytest.mark.parametrize("data", ["groups", "offset", "last points"])
 def test_data_that_it_cannot_tell(data, dtype, N, D, K):

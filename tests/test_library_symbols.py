@@ -55,3 +55,16 @@ def test_workspace_reserves_every_padded_centroid_row():
             for K in ks:
                 planned, reserved = binding.plan_padded_rows(dtype, max(K, 1 << 20), D, K)
                 assert K <= planned <= reserved, (dtype, D, K, planned, reserved)
+
+
+@pytest.mark.parametrize("dtype", [binding.F32, binding.F64])
+def test_scan_reserves_every_tile_that_its_preparation_writes(dtype):
+    """Two forms of the scan pad the centroids to chunks of their own (rows of 3 and 6 blocks of 16 features: 2 tiles and
+    5); one launch prepares both images, for the larger of the two."""
+    if not binding._LIB_PATH.exists():
+        pytest.skip("libftkmeans.so not built")
+    for D in list(range(17, 129, 5)) + [48, 80, 96, 128, 129, 200, 513, 1024]:
+        for K in list(range(520, 8200, 32)) + [800, 1120, 2720]:
+            for N in (60000, 600000):
+                planned, reserved = binding.plan_padded_rows(dtype, N, D, K)
+                assert planned <= reserved, (dtype, N, D, K, planned, reserved)
