@@ -56,6 +56,7 @@
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
 // the same (overflow, NaN) is found by the settle pass, and such a point is compared with every centroid.
 #include <cmath>
+#include <limits>
 #include <type_traits>
 
 #include "ftk_internal.h"
@@ -1166,6 +1167,7 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
                             : a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
     const T s = (T)a.scale[0];
     const float ref = 1.000001f * (float)a.scale[1] + tiny;  // ||r||
+    const float under = (float)((T)(a.D + 16) * std::numeric_limits<T>::min() * s * s);
     for (int k = 1; k < splits; ++k) {
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
@@ -1231,8 +1233,10 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
         if constexpr (HALF) {
             // Its true score is also known from the distance, (||x - r||^2 - ||x - c||^2) / 2, to within the rounding of
             // these sums: of fp16 pieces that halves the bound (2^21 x 32, K = 4096: 68 000 points listed against 105 000).
+            // The distance comes from differences that carry no scale: `under` is what underflow may have taken from it,
+            // infinite (a distance out of range: d2) where these sums say nothing.
             const float y2 = group_sum<L>(yn[u]), d2 = (float)(dist * s * s);
-            least = fmaxf(least, 0.5f * (y2 - d2) - a.sums * (y2 + d2));
+            least = half ? fmaxf(least, 0.5f * (y2 - d2) - a.sums * (y2 + d2) - under) : least;
         }
         least -= low;
         // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on

@@ -106,6 +106,20 @@ def test_values_beyond_fp16_and_values_that_are_not_numbers(N, D, K):
     check_assign(X, far, *a, rows=rows, ref=oracle.assign(X, far, rows))
 
 
+# powers of two, so that the data are the same but for the exponent: squares of differences leave the range of their type
+@pytest.mark.parametrize("dtype,N,D,K,exps", [("f32", 130003, 64, 1805, (-40, -55, -62, -67, -75, -84, 40, 75)),
+                                              ("f32", 33001, 512, 720, (-62, -75, -84, 75))])
+def test_labels_do_not_depend_on_the_scale_of_the_data(dtype, N, D, K, exps):
+    rng = np.random.default_rng(D)
+    X = rng.random((N, D)).astype(NP[dtype])  # nothing stands out: what one fp16 product names is often wrong
+    C = X[rng.permutation(N)[:K]].copy()
+    want = check(X, C, dtype)
+    for e in exps:
+        labels, mind = run(np.ldexp(X, e), np.ldexp(C, e))
+        assert np.array_equal(labels, want), (e, int((labels != want).sum()))
+        assert not np.isnan(mind).any()
+
+
 def test_a_workspace_without_room_for_it():
     X, C = blobs(3, 300007, 20, 6700, "f64")  # nothing else needs more of the workspace
     Xd, Cd = to_dev(X), to_dev(C)
