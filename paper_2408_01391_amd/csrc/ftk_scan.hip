@@ -1321,9 +1321,30 @@ struct ResolveSlot {
 };
 static_assert(sizeof(ResolveSlot) == sizeof(ScanRecord), "layout");
 
+// What differences of fp64 data are multiplied by before they are squared: the scale of the operands where squares of the
+// data as they are would leave the range, so that distances can be compared at any scale; else 1 (fp32 data: always).
+template <typename T>
+struct SquareScale {
+    double s;
+    __device__ __forceinline__ explicit SquareScale(double scale)
+        : s(sizeof(T) == 8 && (scale > 0x1p300 || scale < 0x1p-300) ? scale : 1.0)
+    {
+    }
+    __device__ __forceinline__ double diff(T x, T c) const
+    {
+        if constexpr (sizeof(T) == 8) return (x - c) * s;
+        else return (double)x - (double)c;
+    }
+    __device__ __forceinline__ T result(double d) const  // the distance itself
+    {
+        if constexpr (sizeof(T) == 8) return d / s / s;
+        else return (T)d;
+    }
+};
+
 // direct-difference distance in double by the L lanes of a group (every lane gets it)
 template <typename T, int L>
-__device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, int sub)
+__device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, int sub, const SquareScale<T> &q)
 {
     const int Dq = D & ~3;
     double d = 0.0;
@@ -1332,12 +1353,12 @@ __device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, in
         const Quad<T> xv = load_quad<T>(x + f), cv = load_quad<T>(c + f);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const double t = (double)xv.v[e] - (double)cv.v[e];
+            const double t = q.diff(xv.v[e], cv.v[e]);
             d = fma(t, t, d);
         }
     }
     for (int f = Dq + sub; f < D; f += L) {
-        const double t = (double)x[f] - (double)c[f];
+        const double t = q.diff(x[f], c[f]);
         d = fma(t, t, d);
     }
     return group_sum<L>(d);
@@ -1345,7 +1366,8 @@ __device__ __forceinline__ double group_sqdist(const T *x, const T *c, int D, in
 
 // the same for P points against R centroids, whose elements are read once
 template <typename T, int L, int P, int R>
-__device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *const (&c)[R], int D, int sub, double (&d)[P][R])
+__device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *const (&c)[R], int D, int sub, const SquareScale<T> &q,
+                                              double (&d)[P][R])
 {
     const int Dq = D & ~3;
 #pragma unroll
@@ -1365,7 +1387,7 @@ __device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *c
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const double t = (double)xv[i].v[e] - (double)cv[r].v[e];
+                    const double t = q.diff(xv[i].v[e], cv[r].v[e]);
                     d[i][r] = fma(t, t, d[i][r]);
                 }
     }
@@ -1374,7 +1396,7 @@ __device__ __forceinline__ void group_sqdists(const T *const (&x)[P], const T *c
         for (int i = 0; i < P; ++i)
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const double t = (double)x[i][f] - (double)c[r][f];
+                const double t = q.diff(x[i][f], c[r][f]);
                 d[i][r] = fma(t, t, d[i][r]);
             }
 #pragma unroll
@@ -1548,7 +1570,8 @@ __device__ __forceinline__ int native_verdict(const NativeShared<T> &sh, int i, 
     // the band of the matrix kernels (see ftk_assign_generic.hip): D products and the sum's start, each rounded
     const double big = sqrt(sh.xn[i] * cmax2) + 0.5 * cmax2;
     const double band = 2.0 * (double)(((D + 7) & ~7) + 4) * Mma<T>::kEps * big;
-    const bool sound = big < 0.25 * (sizeof(T) == 4 ? 3e38 : 1e308);
+    // (what underflow takes from the products is below the band)
+    const bool sound = big < 0.25 * (sizeof(T) == 4 ? 3e38 : 1e308) && big > (sizeof(T) == 4 ? 0x1p-96 : 0x1p-960);
     return sound && (double)m1 - (double)m2 > band ? j1 : -1;
 }
 
@@ -1580,6 +1603,7 @@ __global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_re
     const int32_t *const list_count = rest ? a.rest_count : a.list_count;
     const int list_cap = rest ? a.rest_cap : a.list_cap;
     const T s = (T)a.scale[0];
+    const SquareScale<T> sq(a.scale[0]);
     __shared__ int sh_pre[SCAN_LISTS + 1];  // listed points before each list
     __shared__ int32_t sh_job[32 * RS_CAP];
     __shared__ int sh_jobs;
@@ -1744,7 +1768,7 @@ __global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_re
         __syncthreads();
         for (int q = grp; q < sh_jobs; q += GROUPS) {
             const int k = sh_job[q] / RS_CAP, at = sh_job[q] % RS_CAP;
-            const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)sh_j[k][at] * a.D, a.D, sub);
+            const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)sh_j[k][at] * a.D, a.D, sub, sq);
             if (sub == 0) sh_d[k][at] = d;
         }
         __syncthreads();
@@ -1796,7 +1820,7 @@ __global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_re
         }
         if (tid < np && sh_code[tid] >= 0) {
             a.labels[sh_p[tid]] = sh_code[tid];
-            if (mindist) mindist[sh_p[tid]] = (T)sh_bd32[tid];
+            if (mindist) mindist[sh_p[tid]] = sq.result(sh_bd32[tid]);
         }
         if constexpr (FORM == FORM_HALF) {  // without what follows: half the registers, two workgroups a compute unit
             if (tid < np && sh_code[tid] < 0) {
@@ -1834,8 +1858,8 @@ __global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_re
                 for (int q = grp; q < nleft; q += GROUPS) {
                     const int k = sh_left[q], j = sh_code[k];
                     if (j < 0) continue;
-                    const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)j * a.D, a.D, sub);
-                    if (sub == 0) mindist[sh_p[k]] = (T)d;
+                    const double d = group_sqdist<T, L>(X + (int64_t)sh_p[k] * a.D, C + (size_t)j * a.D, a.D, sub, sq);
+                    if (sub == 0) mindist[sh_p[k]] = sq.result(d);
                 }
             __syncthreads();
             collect();
@@ -1857,7 +1881,7 @@ __global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_re
 #pragma unroll
                 for (int r = 0; r < R; ++r) c[r] = C + (size_t)min(j0 + r * GROUPS, a.K - 1) * a.D;
                 double d[P][R];
-                group_sqdists<T, L, P, R>(x, c, a.D, sub, d);
+                group_sqdists<T, L, P, R>(x, c, a.D, sub, sq, d);
 #pragma unroll
                 for (int i = 0; i < P; ++i)
 #pragma unroll
@@ -1896,7 +1920,7 @@ __global__ __launch_bounds__(RS_THREADS, FORM == FORM_HALF ? 4 : 2) void scan_re
                     }
                 const int32_t p = sh_p[sh_left[k0 + tid]];
                 a.labels[p] = j == 0x7fffffff ? 0 : j;
-                if (mindist) mindist[p] = (T)d;
+                if (mindist) mindist[p] = sq.result(d);
             }
         };
         for (int k0 = 0; k0 < sh_nleft; k0 += 4) {
@@ -1956,6 +1980,7 @@ void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, Recheck
     const int n = sh_pre[SCAN_LISTS];
     if (r.stats && blockIdx.x == 0 && tid == 0 && n > 0) atomicAdd((unsigned long long *)&r.stats->refined, (unsigned long long)n);
     const T s = (T)a.scale[0];
+    const SquareScale<T> sq(a.scale[0]);
     for (int64_t first = (int64_t)blockIdx.x * RC_POINTS; first < n; first += (int64_t)gridDim.x * RC_POINTS) {
         __syncthreads();  // the points before these are done
         if (tid < RC_POINTS) {
@@ -2055,7 +2080,7 @@ void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, Recheck
                 const int j0 = sh_j[i][k], j1 = sh_j[i][min(k + 1, m - 1)];
                 const T *const c[2] = {C + (size_t)j0 * a.D, C + (size_t)j1 * a.D};
                 double d[1][2];
-                group_sqdists<T, L, 1, 2>(x, c, a.D, sub, d);
+                group_sqdists<T, L, 1, 2>(x, c, a.D, sub, sq, d);
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     const int j = q ? j1 : j0;
@@ -2066,7 +2091,7 @@ void scan_recheck_kernel(const T *X, const T *C, T *mindist, ScanArgs a, Recheck
             }
             if (sub == 0) {
                 r.labels[p] = bj;
-                if (mindist) mindist[p] = (T)best;
+                if (mindist) mindist[p] = sq.result(best);
             }
         }
     }

@@ -108,7 +108,9 @@ def test_values_beyond_fp16_and_values_that_are_not_numbers(N, D, K):
 
 # powers of two, so that the data are the same but for the exponent: squares of differences leave the range of their type
 @pytest.mark.parametrize("dtype,N,D,K,exps", [("f32", 130003, 64, 1805, (-40, -55, -62, -67, -75, -84, 40, 75)),
-                                              ("f32", 33001, 512, 720, (-62, -75, -84, 75))])
+                                              ("f32", 33001, 512, 720, (-62, -75, -84, 75)),
+                                              ("f64", 150001, 128, 2085, (-515, -550, 505, 550)),
+                                              ("f64", 33001, 1021, 357, (-515, -550, 550))])
 def test_labels_do_not_depend_on_the_scale_of_the_data(dtype, N, D, K, exps):
     rng = np.random.default_rng(D)
     X = rng.random((N, D)).astype(NP[dtype])  # nothing stands out: what one fp16 product names is often wrong
