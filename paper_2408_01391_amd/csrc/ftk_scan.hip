@@ -1236,7 +1236,7 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
             // The distance comes from differences that carry no scale: `under` is what underflow may have taken from it,
             // infinite (a distance out of range: d2) where these sums say nothing.
             const float y2 = group_sum<L>(yn[u]), d2 = (float)(dist * s * s);
-            least = half ? fmaxf(least, 0.5f * (y2 - d2) - a.sums * (y2 + d2) - under) : least;
+            least = fmaxf(least, 0.5f * (y2 - d2) - a.sums * (y2 + d2) - under);
         }
         least -= low;
         // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on
