@@ -388,7 +388,7 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
     if (small)
         FTK_TRY(launch_small_assign(c, st));
     else if (scan.ok)
-        FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N, c.D), w, st));
+        FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N, c.D), w, c, st));
     else if (fast)
         FTK_TRY(launch_assign_fast(c, p, w, st));
     else
@@ -767,6 +767,7 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
     AssignPlan pprev = plan_assign(dtype, whole.N, D, K, FTK_FT_OFF, aligned16);
     // the path is chosen for the whole problem, as in the two-call step
     const bool small = route_small(dtype, N, D, K, FTK_FT_OFF, 0);
+    const AssignCall problem{dtype, X, C, N, D, K, labels, mindist, FTK_FT_OFF, nullptr, 0, nullptr};
     const ScanPlan scan = small || !w.scan ? ScanPlan{} : fit_scan(route_scan(dtype, N, D, K, FTK_FT_OFF, 0), w, N, D);
     if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
     for (int64_t b = 0; b < nbatch; ++b) {
@@ -781,11 +782,7 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
             if (small)
                 FTK_TRY(launch_small_assign(c, st));
             else
-            {
-                ScanPlan part = cut_scan(dtype, nb, D, K);
-                part.half = part.half && scan.half;
-                FTK_TRY(launch_scan_assign(c, part, carve_scan(w.scan, scan, N, D), wb, st));
-            }
+                FTK_TRY(launch_scan_assign(c, cut_part(scan, dtype, nb, D, K), carve_scan(w.scan, scan, N, D), wb, problem, st));
             FTK_TRY(launch_update_batch(dtype, Xb, labels + r0, nb, D, K, x_absmax, w, ub, b == 0, st));
             continue;
         }

@@ -42,9 +42,10 @@ struct ScanBuffers {
     float4 *tile_stat;  // [tiles_pad] largest ||c||^2 (scaled), ||c1||^2 / ||c||^2, ||r_c||^2 / ||c||^2 of a tile
     double *scale;      // [2] the power of two both operands are multiplied by; length of the (scaled) reference
     void *ref;          // [D] the reference, zero where none is taken
+    float4 *sample;     // [tiles][rows] scores of the rows that choose the form
     ScanRecord *rec;    // [splits][N]
     ScanListed *list;   // points to resolve: lists of equal capacity ...
-    int32_t *list_count;  // ... and a counter each (then the state of the choice of form, and the counters of `rest`)
+    int32_t *list_count;  // ... and a counter each (then the counters of `rest`, and which form was chosen)
     int32_t *tickets;   // [N/32 + 1] workgroups done with a group of listed points
     uint4 *half_image;  // [half_tiles][half_nb][64] fp16 pieces, and the start values that go with them
     float *half_start;
@@ -56,11 +57,14 @@ struct ScanBuffers {
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // the cut alone, for part of a problem that takes this path
 ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K);
+// the same for n points of a problem that is cut as `whole`: with fp16 pieces if that has them
+ScanPlan cut_part(const ScanPlan &whole, ftk_dtype dtype, int64_t n, int D, int K);
 // rows that the preparation writes for the points or for any batch of them, and those its images are reserved for
 void scan_padded_rows(ftk_dtype dtype, int64_t N, int D, int K, int64_t *planned, int64_t *reserved);
 // buffers for the whole problem and for any batch of it
 ScanBuffers carve_scan(void *base, const ScanPlan &whole, int64_t N, int D);
+// whole: the problem that c is a part of, whose rows choose the form
 ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,
-                              hipStream_t st);
+                              const AssignCall &whole, hipStream_t st);
 
 }  // namespace ftk

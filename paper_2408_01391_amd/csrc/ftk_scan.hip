@@ -49,8 +49,8 @@
 // pass, some 0.45 2^-11 each, which makes the bound some 25 times wider than that of two bf16 pieces and leaves 3 to 10 %
 // of the points for the third pass - with two candidates as a rule, so that it costs a tenth of the scan.  An operand below
 // 2^-14 rounds like that value, in the piece and in the instruction (pinned by a test): norms are raised by 2^-14 for every
-// feature.  Data whose points lie far from the origin or in groups would list nearly all, so the scan's first workgroups vote
-// (ScanGate) before the rest of it runs.
+// feature.  Data whose points lie far from the origin or in groups would list nearly all, so a sample of the rows chooses
+// (scan_choose_kernel).
 //
 // Both operands are multiplied by one power of two taken from the same rows, so that the scores
 // sit in the middle of the fp32 exponent range whatever the scale of the data; what falls outside all
@@ -82,9 +82,14 @@ constexpr int SETTLE_ROWS_MAX = 512;  // rows of a workgroup
 constexpr int settle_rows(size_t element) { return element == 8 ? 2 : 4; }  // rows a group of lanes settles at once
 constexpr int SCAN_LISTS = 64;    // lists of points to resolve, a counter in a line of its own each
 constexpr int LIST_STRIDE = 32;
-constexpr int HALF_VOTERS = 128;  // workgroups that decide between the forms
 constexpr float HALF_RANGE = 6e4f;  // of a norm: no feature leaves the range of fp16
-constexpr int HALF_LIMIT = 12;    // percent of their points listed, beyond which two pieces are faster
+// The rows that decide between the forms come in shares of 32 that a workgroup compares with a tile of centroids: fewer for many centroids, where this adds up (150 000 x
+// 128, K = 2085 5 us with four shares, 33000 x 256, K = 8192 28).
+static int sample_shares(int tiles) { return tiles <= 64 ? 4 : (tiles <= 128 ? 2 : 1); }
+// Of them listed, from which on two pieces are taken: 14, 19, 22 percent.  They are faster from 10 percent (524288 x 96, K = 800: 11.5
+// percent 289 us, refused 272), 13 (400000 x 32, K = 2000: 10.5 percent 182, 15 percent 234, refused 212), 16 (130003 x 256, K = 1024: 15
+// percent 262, refused 297) or more than 20 (2^21 x 32, K = 4096: 21 percent 1331, refused 1595) on.
+static int sample_limit(int shares) { return shares == 4 ? 18 : (shares == 2 ? 12 : 7); }
 constexpr float SCAN_FLOOR = 7.9e-31f;  // 2^-100: below it scores (of centroids near 1) may have lost digits to underflow
 
 // how a block of the contraction is laid out
@@ -98,26 +103,14 @@ enum ScanForm : int {
 static constexpr int form_frags(int form) { return form == FORM_HALF ? 1 : (form == FORM_TRIPLE ? 3 : 2); }
 static constexpr int form_pieces(int form) { return form == FORM_HALF ? 1 : (form == FORM_PAIR ? 2 : 3); }
 
-// Which of two forms a call takes: the one with fp16 pieces, unless the first workgroups of its scan find too many
-// points that it cannot tell.  The rest of that scan is then left out, and the other form's runs.
+// Which of two forms a call takes: see scan_choose_kernel.
 struct ScanGate {
-    int32_t *state;  // [0] waves that have voted << 20 | points these would list, [1] not 0: two pieces; NULL: no choice
-    int votes;       // waves that vote
-    __device__ __forceinline__ bool refused() const { return __hip_atomic_load(state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0; }
-    __device__ __forceinline__ bool half() const { return state && !refused(); }
-    // (While the others vote the waves of one workgroup may read different answers: those that go on then work on fragments
-    // that nobody staged, which is harmless - every record is written again by the other form, and voters started earlier.)
+    const int32_t *refused;  // not 0: two pieces; NULL: no choice
+    __device__ __forceinline__ bool half() const { return refused && *refused == 0; }
     template <int FORM>
     __device__ __forceinline__ bool closed() const
     {
-        return state && refused() == (FORM == FORM_HALF);
-    }
-    // one lane of a wave with 64 points; the last to vote decides
-    __device__ __forceinline__ void vote(int listed) const
-    {
-        const int sum = (1 << 20 | listed) + atomicAdd(state, 1 << 20 | listed);
-        if (sum >> 20 == votes && (sum & 0xfffff) > votes * 64 * HALF_LIMIT / 100)
-            __hip_atomic_store(state + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return refused && (*refused != 0) == (FORM == FORM_HALF);
     }
 };
 
@@ -136,8 +129,6 @@ struct ScanArgs {
     int pblocks;
     ScanRecord *rec;
     ScanGate gate;
-    const float *norm;  // for the vote: ||c||
-    const float4 *tile_stat;
 };
 
 __device__ __forceinline__ void split_pair(const float (&v)[8], uint4 &hi, uint4 &lo)
@@ -293,27 +284,46 @@ struct HalfImage {
     uint4 *image;
     float *start;
     void *ref;  // the reference goes there
-    int32_t *gate;
+    int32_t *rest_count;
+    float4 *sample;  // [tiles][32 shares] best score of a tile, the second, the bound of the best
+    const void *X;   // the rows are taken from [N] of these
+    int64_t N;
+    int tiles;       // workgroups of the images; the others take a tile and a share of the sample each
+    int shares;
     int nb;
     float lift, tiny;
 };
 constexpr size_t REF_BYTES = 64 * 1024;
-// HALF: the second image too
+// HALF: the second image too, and the scores of sampled rows (fp64: more registers than 16 waves have)
+constexpr int centroid_waves(size_t element, bool half) { return half && element == 8 ? 8 : 16; }
 template <typename T, int FORM, bool HALF>
-__global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
+__global__ __launch_bounds__(64 * centroid_waves(sizeof(T), HALF)) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
                                                               float4 *tile_stat, double *scale, int32_t *list_count, int lists,
                                                               int has_ref, float *norm, double lift, HalfImage half_args)
 {
     const HalfImage half = HALF ? half_args : HalfImage{};
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    T *const ref = reinterpret_cast<T *>(lds_raw);  // [16 nb_all]
     const int nb_all = max(nb, half.nb);
+    T *const ref = reinterpret_cast<T *>(lds_raw);  // [16 nb_all]
+    // sampling: [waves][4][64] sums of the rows over a wave's blocks
+    floatx4 *const part = reinterpret_cast<floatx4 *>(lds_raw + (has_ref ? (size_t)16 * nb_all * sizeof(T) : 0));
+    __shared__ float sh_start[32], sh_norm[32];
     __shared__ double sh_n[16][32], sh_rc[16][32];
     __shared__ float sh_n1[16][32], sh_nr[16][32];  // squared norms of the second pieces and of the residuals
     __shared__ float sh_nh[16][32];                 // and of what fp16 pieces leave
     __shared__ T sh_m[16][2];
     __shared__ double sh_s[16][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = (int)blockDim.x >> 6;
+    // (beside the images, as few of the chip's units are busy: one workgroup for both took 42 us at K = 357, 1021 fp64
+    // features, so 28; 18 and 15 at K = 720, 512 features)
+    const bool sampling = HALF && (int)blockIdx.x >= half.tiles;
+    const int extra = (int)blockIdx.x - half.tiles, tile = sampling ? extra / half.shares : (int)blockIdx.x;
+    const int row = lane & 31, g = lane >> 5;
+    const int j = 32 * tile + row;
+    const RowReader<T, true> reader(C + (size_t)(j < K ? j : 0) * D, D);
+    const int share = extra - tile * half.shares;
+    const int64_t picked = sampling ? half.N * (2 * (32 * share + row) + 1) / (64 * half.shares) : 0;
+    const RowReader<T, true> xr(sampling ? static_cast<const T *>(half.X) + picked * D : C, D);
     T m = T(0), whole = T(0);  // largest magnitude of the rows less the reference, and of the rows
     double gain = 0.0, rr = 0.0;  // half the rows' sum of squares less that of what is left of them, and ||r||^2
     for (int d = tid; d < D; d += blockDim.x) {
@@ -352,7 +362,7 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     m = wave_max(m);
     whole = wave_max(whole);
     gain = group_sum<64>(gain);
-    if (blockIdx.x == 0) rr = group_sum<64>(rr);  // the only one to write it
+    if (HALF || blockIdx.x == 0) rr = group_sum<64>(rr);  // (else the only one to use it)
     if (lane == 0) {
         sh_m[wave][0] = m;
         sh_m[wave][1] = whole;
@@ -383,36 +393,49 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
     }
     if (blockIdx.x == 0) {
         if (tid < lists) list_count[tid * LIST_STRIDE] = 0;
-        if (tid == 0 && half.nb) {
-            half.gate[0] = 0;
-            // data far from the origin against their spread are not tried: the vote of 2^19 x 32 at 20, spread 1, K = 1024,
-            // comes when half of the scan has run (225 us a call, two pieces alone 163)
-            half.gate[1] = moved && rr > 4.0 * D * (double)m * (double)m;
-        }
-        if (tid < SCAN_LISTS && half.nb) half.gate[(tid + 1) * LIST_STRIDE] = 0;  // of the points left over
+        if (tid < SCAN_LISTS && half.nb) half.rest_count[tid * LIST_STRIDE] = 0;
         if (half.nb)
             for (int d = tid; d < D; d += blockDim.x) static_cast<T *>(half.ref)[d] = moved ? ref[d] : T(0);
     }
-    const int tile = blockIdx.x;
-    const int row = lane & 31, g = lane >> 5;
-    const int j = 32 * tile + row;
-    const T *c = C + (size_t)(j < K ? j : 0) * D;
-    const RowReader<T, true> reader(c, D);
     double n = 0.0, rc = 0.0;
     float n1 = 0.f, nr = 0.f, nh = 0.f;
+    float sn = 0.f, src = 0.f;
+    floatx16 sum;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum[r] = 0.f;
 #pragma unroll 2
     for (int b = wave; b < nb_all; b += nw) {
         const int f0 = FORM == FORM_OCTET ? 0 : 16 * b + 8 * g;
         const Quad<T> q0 = reader.request(f0), q1 = reader.request(f0 + 4);
+        Quad<T> x0 = {}, x1 = {};
+        if (sampling) {
+            x0 = xr.request(f0);
+            x1 = xr.request(f0 + 4);
+        }
         const Quad<T> k0 = reader.keep(q0, f0), k1 = reader.keep(q1, f0 + 4);
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const T r = moved ? ref[f0 + e] : T(0);
             const T w = j < K ? ((e < 4 ? k0.v[e & 3] : k1.v[e & 3]) - r) * s : T(0);
-            n = fma((double)w, (double)w, n);
-            rc = fma((double)w, (double)r, rc);
             v[e] = (float)w;
+            if (sampling) {  // (their scores carry the error of fp16 pieces)
+                sn = fmaf(v[e], v[e], sn);
+                src = fmaf(v[e], (float)(r * s), src);
+            } else {
+                n = fma((double)w, (double)w, n);
+                rc = fma((double)w, (double)r, rc);
+            }
+        }
+        if (sampling) {
+            x0 = xr.keep(x0, f0);
+            x1 = xr.keep(x1, f0 + 4);
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = (float)((e < 4 ? x0.v[e & 3] : x1.v[e & 3]) * s);
+            sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, round_half(v)),
+                                                         __builtin_bit_cast(halfx8, round_half(x)), sum, 0, 0, 0);
+            continue;
         }
         uint4 *dst = image + ((size_t)tile * nb + b) * (form_frags(FORM) * FRAG_UNITS) + lane;
         if constexpr (FORM != FORM_PAIR) {
@@ -442,6 +465,10 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
             }
         }
     }
+    if (sampling) {
+        n = (double)sn;
+        rc = (double)src / (double)s;
+    }
     if (FORM != FORM_OCTET) {
         n += __shfl_xor(n, 32, 64);
         rc += __shfl_xor(rc, 32, 64);
@@ -458,6 +485,11 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
         sh_nr[wave][lane] = nr;
         sh_nh[wave][lane] = nh;
     }
+    if (sampling) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            part[(wave * 4 + i) * 64 + lane] = floatx4{sum[4 * i], sum[4 * i + 1], sum[4 * i + 2], sum[4 * i + 3]};
+    }
     __syncthreads();
     if (tid < 32) {
         n = rc = 0.0;
@@ -471,12 +503,16 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
         }
         // register r of lane group gg reads row 8(r/4) + 4gg + r%4
         const int gg = (tid >> 2) & 1, r = 4 * (tid >> 3) + (tid & 3);
-        start[tile * 32 + gg * 16 + r] =
-            32 * tile + tid < K ? (float)((lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
-        if (half.nb)
-            half.start[tile * 32 + gg * 16 + r] =
-                32 * tile + tid < K ? (float)(((double)half.lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
-        norm[tile * 32 + tid] = sqrtf((float)n);
+        const float half_start =
+            32 * tile + tid < K ? (float)(((double)half.lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
+        sh_start[tid] = half_start;
+        sh_norm[tid] = sqrtf((float)n);
+        if (!sampling) {
+            start[tile * 32 + gg * 16 + r] =
+                32 * tile + tid < K ? (float)((lift - 0.5) * n - rc * (double)s) : -__builtin_huge_valf();
+            if (half.nb) half.start[tile * 32 + gg * 16 + r] = half_start;
+            norm[tile * 32 + tid] = sqrtf((float)n);
+        }
         // (a NaN row never wins and does not count)
         float f = n > 0.0 ? (float)n : 0.f;
         float q1 = n > 0.0 ? (float)((double)n1 / n) : 0.f, qr = n > 0.0 ? (float)((double)nr / n) : 0.f;
@@ -489,8 +525,73 @@ __global__ __launch_bounds__(1024) void scan_centroids_kernel(const T *C, int D,
             qr = fmaxf(qr, __shfl_xor(qr, k, 64));
             qh = fmaxf(qh, __shfl_xor(qh, k, 64));
         }
-        if (tid == 0) tile_stat[tile] = make_float4(f, q1, qr, qh);
+        if (tid == 0 && !sampling) tile_stat[tile] = make_float4(f, q1, qr, qh);
     }
+    if (sampling) {
+        __syncthreads();
+        if (wave > 0) return;
+        float m1 = Mma<float>::neg_inf(), m2 = m1;
+        int j1 = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            floatx4 v = part[i * 64 + lane];
+            for (int w = 1; w < nw; ++w) v += part[(w * 4 + i) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int jj = 8 * i + 4 * g + e;
+                const float score = v[e] + sh_start[jj];
+                const bool better = score > m1;
+                m2 = better ? m1 : (score > m2 ? score : m2);
+                m1 = better ? score : m1;
+                j1 = better ? jj : j1;
+            }
+        }
+        const float o1 = __shfl_xor(m1, 32, 64), o2 = __shfl_xor(m2, 32, 64);
+        const int oj = __shfl_xor(j1, 32, 64);
+        const bool mine = m1 >= o1;
+        // about the bound of the settle pass, with the named centroid's norm in place of the point's
+        const float c = sh_norm[mine ? j1 : oj], r = moved ? (float)(sqrt(rr) * (double)s) : 0.f;
+        if (lane < 32)
+            half.sample[(size_t)extra * 32 + lane] =
+                make_float4(mine ? m1 : o1, fmaxf(fmaxf(m2, o2), mine ? o1 : m1), 0.9f * 0x1p-11f * (c + r) * c, 0.f);
+    }
+}
+
+// ---- choice of form ---------------------------------------------------------------------------
+// One fp16 piece leaves nearly all points of some data to the third pass (data far from the origin or in groups, against
+// their spread; a centroid beyond the range of fp16): two pieces scan these.  Rows spread evenly over the whole problem
+// tell, whatever their order, before either scan runs; the choice holds for all launches and batches of the problem.
+// The sample costs one launch, 4 us, beside what it adds to the preparation (2^21 x 32, K = 4096 2 us; 1021 fp64 features, K = 357
+// 11 us).  (A vote of the scan's first workgroups costs none, but all of that scan where all run at
+// once: two groups at +-20, spread 1, in 200000 x 32, K = 2400 206 us against 144 by two pieces alone, 150001 x 128 fp64,
+// K = 2085 475 / 317; a scan of 32 000 rows ahead 24 to 62 us.)
+__global__ __launch_bounds__(1024) void scan_choose_kernel(const float4 *sample, const float4 *tile_stat, int tiles, int rows, int limit,
+                                                           int32_t *refused)
+{
+    __shared__ float sh_m1[1024], sh_m2[1024], sh_bound[1024];
+    const int tid = threadIdx.x, i = tid & (rows - 1);  // rows: a power of two
+    float m1 = Mma<float>::neg_inf(), m2 = m1, bound = 0.f;
+    auto add = [&](float o1, float o2, float ob) {
+        const bool mine = m1 >= o1;
+        m2 = fmaxf(fmaxf(m2, o2), mine ? o1 : m1);
+        m1 = mine ? m1 : o1;
+        bound = mine ? bound : ob;
+    };
+#pragma unroll 4
+    for (int64_t k = tid; k < (int64_t)tiles * rows; k += 1024) {
+        const float4 v = sample[k];
+        add(v.x, v.y, v.z);
+    }
+    bool far = false;
+    for (int t = tid; t < tiles; t += 1024) far = far || !(tile_stat[t].x < 0.99f * HALF_RANGE * HALF_RANGE);
+    sh_m1[tid] = m1;
+    sh_m2[tid] = m2;
+    sh_bound[tid] = bound;
+    far = __syncthreads_or(far);
+    if (tid < rows)
+        for (int k = i + rows; k < 1024; k += rows) add(sh_m1[k], sh_m2[k], sh_bound[k]);
+    const int listed = __syncthreads_count(tid < rows && !(m1 - m2 > bound));
+    if (tid == 0) *refused = far || listed >= limit;
 }
 
 // ---- bookkeeping of the scans -----------------------------------------------------------------
@@ -542,22 +643,6 @@ __device__ __forceinline__ void scan_best_finish(const ScanBest &b, int g, float
     j1 = mine ? j : oj;
     m2 = mine ? (sec > om1 ? sec : om1) : (osec > b.m1 ? osec : b.m1);
     if (!(b.m1 == b.m1) || !(om1 == om1)) m2 = __builtin_huge_valf();  // NaN scores: not to be trusted
-}
-
-// whether the scan on fp16 pieces would list the point (about: with the named centroid's norm in place of the point's)
-__device__ __forceinline__ bool half_lists(const ScanArgs &a, float m1, int j1, float m2)
-{
-    const float c = a.norm[min(j1, 32 * a.tiles - 1)];
-    return !(m1 - m2 > 0.9f * 0x1p-11f * (c + (float)a.scale[1]) * c);
-}
-
-// the vote of a wave that found `listed` of its 64 points so; against fp16 pieces where a centroid leaves their range
-__device__ __forceinline__ void half_vote(const ScanArgs &a, int lane, int listed)
-{
-    float m = 0.f;
-    for (int i = lane; i < a.tiles; i += 64) m = fmaxf(m, a.tile_stat[i].x);
-    m = wave_max(m);
-    if (lane == 0) a.gate.vote(m < 0.99f * HALF_RANGE * HALF_RANGE ? listed : 64);
 }
 
 // ---- scan of rows of up to 128 features ---------------------------------------------------------
@@ -716,7 +801,6 @@ __global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8
         __syncthreads();
         cur ^= 1;
     }
-    int listed = 0;
 #pragma unroll
     for (int pt = 0; pt < SC_PT; ++pt) {
         float m1, m2;
@@ -726,12 +810,6 @@ __global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8
         if (g == 0 && p < a.N) {
             a.rec[(int64_t)split * a.N + p] = ScanRecord{m1, m2, j1, 0};
         }
-        if constexpr (FORM == FORM_HALF) {
-            if (blockIdx.x < HALF_VOTERS) listed += __popcll(__ballot(g == 0 && half_lists(a, m1, j1, m2)));
-        }
-    }
-    if constexpr (FORM == FORM_HALF) {
-        if (blockIdx.x < HALF_VOTERS) half_vote(a, lane, listed);
     }
 }
 
@@ -1067,10 +1145,6 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
         }
         const int64_t p = p0 + tid;
         if (p < a.N) a.rec[p] = ScanRecord{b1, b2, j, 0};
-        if (blockIdx.x < HALF_VOTERS) {
-            const int listed = __popcll(__ballot(half_lists(a, b1, j, b2)));
-            half_vote(a, lane, listed);
-        }
     }
 }
 
@@ -2158,20 +2232,25 @@ static bool scan_pays(ftk_dtype dtype, int64_t N, int D, int K)
     return K >= scan_from(dtype, N, D);
 }
 
-// Where the scan on fp16 pieces runs first.  It has a third of the matrix work, a settle pass that measures more of
-// each row (fp64: in instructions of half the rate) and some percent of the points in the third pass; three more launches, of
-// which two return at once.  Two pieces / one, whole calls, us, blobs:
-//   fp32  D <= 128  10^6 x 32, K = 300 127 / 139, 600 169 / 161; 2 10^6 x 32, K = 512 288 / 256; 262144 x 128, K = 400 117 / 125;
-//                   65536 x 128, K = 2000 119 / 116; 40000 x 100, K = 4000 149 / 167; 400000 x 32, K = 2000 196 / 160
-//         longer    1872756 x 340, K = 108 1418 / 1569; 131072 x 256, K = 300 129 / 130, 700 191 / 154; 40000 x 1000, K = 512 225 / 179
-//   fp64  D <= 128  262144 x 64, K = 1200 156 / 165; 65536 x 128, K = 2000 143 / 166; 10^6 x 32, K = 2048 424 / 346
-//         longer    200000 x 130, K = 512 210 / 231; 131072 x 256, K = 300 206 / 203; 40000 x 1024, K = 300 372 / 287
+// Where the scan on fp16 pieces runs first.  It has a third of the matrix work, a sample of the rows ahead, a settle pass that measures
+// more of each row (fp64: in instructions of half the rate) and some percent of the points in the third pass; four more launches, of
+// which two return at once.  Two pieces / one, whole calls, us, blobs, near the line:
+//   fp32  D <= 128  65536 x 48, K = 4800 117 / 111; 600000 x 48, K = 544 142 / 128; 65536 x 96, K = 2400 117 / 106; 524288 x 96, K = 512
+//                   192 / 165; 300000 x 80, K = 640 143 / 129; 100000 x 72, K = 2100 156 / 131; 800000 x 37, K = 512 168 / 150; 130000 x 40,
+//                   K = 2900 132 / 115; 60000 x 128, K = 2000 129 / 122; 450000 x 64, K = 544 132 / 116; 1600000 x 20, K = 512 199 / 168
+//         longer    400000 x 160, K = 256 195 / 235; 200000 x 192, K = 330 181 / 166; 65536 x 512, K = 360 138 / 137; 40000 x 512, K = 600
+//                   139 / 138; 131072 x 256, K = 512 155 / 146; 33000 x 1024, K = 360 212 / 181; 60000 x 200, K = 1024 132 / 107
+//   fp64  D <= 128  600000 x 128, K = 528 451 / 474; 700000 x 96, K = 600 381 / 392; 1000000 x 64, K = 630 365 / 365; 1600000 x 32, K = 800
+//                   384 / 362; 500000 x 48, K = 1700 283 / 238; 300000 x 80, K = 1700 305 / 271; 70000 x 128, K = 4500 324 / 271
+//         longer    200000 x 130, K = 512 210 / 231; 131072 x 256, K = 360 212 / 211; 40000 x 512, K = 600 193 / 194; 33000 x 1024, K = 360 334 / 277
+// Data that the sample refuses pay the sample and the launches that return: 200000 x 32, K = 2400 145 / 163; 130000 x 256, K = 1024
+// 300 / 304; fp64 150001 x 128, K = 2085 318 / 347.
 static bool half_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     const double work = (double)N * D * K;
-    if (D <= 16 || D > 1024 || N < HALF_VOTERS * SC_POINTS) return false;
-    if (D <= 128) return K >= 512 && N >= 60000 && work >= (dtype == FTK_F32 ? 1.5e10 : 4e10);
-    return K >= 256 && work >= (dtype == FTK_F32 || D >= 192 ? 1.2e10 : 3e10);
+    if (D <= 16 || D > 1024 || N < 32768) return false;
+    if (D <= 128) return K >= (dtype == FTK_F32 ? 512 : 640) && N >= 60000 && work >= (dtype == FTK_F32 ? 1.5e10 : 4e10);
+    return K >= 320 && work >= (dtype == FTK_F32 || D >= 192 ? 1.2e10 : 3e10);
 }
 
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K)
@@ -2280,10 +2359,19 @@ static int prepared_tiles(const ScanPlan &p, const ScanPlan &last)
     return p.half && tiles < p.half_tiles ? p.half_tiles : tiles;
 }
 
+ScanPlan cut_part(const ScanPlan &whole, ftk_dtype dtype, int64_t n, int D, int K)
+{
+    ScanPlan p = cut_scan(dtype, n, D, K);
+    p.half = whole.half;
+    p.half_nb = whole.half_nb;
+    p.half_tiles = whole.half_tiles;
+    return p;
+}
+
 static ScanPlan cut_last(const ScanPlan &p, ftk_dtype dtype, int64_t N, int D, int K)
 {
     const int64_t rest = N % p.batch;
-    return rest ? cut_scan(dtype, rest, D, K) : p;
+    return rest ? cut_part(p, dtype, rest, D, K) : p;
 }
 
 void scan_padded_rows(ftk_dtype dtype, int64_t N, int D, int K, int64_t *planned, int64_t *reserved)
@@ -2298,8 +2386,7 @@ void scan_padded_rows(ftk_dtype dtype, int64_t N, int D, int K, int64_t *planned
     }
     int most = 0;
     for (int64_t n = N; n >= 1; n /= 2) {  // the points, and batches of them
-        ScanPlan p = cut_scan(dtype, n, D, K);
-        p.half = p.half && whole.half;
+        const ScanPlan p = cut_part(whole, dtype, n, D, K);
         const int t = prepared_tiles(p, cut_last(p, dtype, n, D, K));
         most = t > most ? t : most;
     }
@@ -2326,7 +2413,7 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N, int D)
     b.norm = (float *)take(tiles * 32 * 4);
     b.scale = (double *)take(16);
     b.rec = (ScanRecord *)take((size_t)p.rec_reserve * sizeof(ScanRecord));
-    b.list_count = (int32_t *)take((size_t)(p.half ? 2 * SCAN_LISTS + 1 : SCAN_LISTS) * LIST_STRIDE * 4);
+    b.list_count = (int32_t *)take(((size_t)(p.half ? 2 * SCAN_LISTS : SCAN_LISTS) * LIST_STRIDE + 1) * 4);
     const size_t points = N < SCAN_RECORDS ? N : SCAN_RECORDS;  // of a launch
     b.list = (ScanListed *)take((points + SCAN_LISTS * SETTLE_ROWS_MAX) * sizeof(ScanListed));
     b.tickets = (int32_t *)take((points / 32 + 1) * 4);
@@ -2334,6 +2421,7 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N, int D)
         b.half_image = (uint4 *)take((size_t)p.half_tiles * p.half_nb * FRAG_UNITS * 16);
         b.half_start = (float *)take(((size_t)p.half_tiles + 1) * 32 * 4);
         b.ref = take((size_t)D * 8);
+        b.sample = (float4 *)take((size_t)p.tiles * sample_shares(p.tiles) * 32 * sizeof(float4));
         b.rest = (ScanListed *)take((points + SCAN_LISTS * SC_POINTS) * sizeof(ScanListed));
     }
     b.bytes = off;
@@ -2348,7 +2436,7 @@ static void launch_resident(const ScanArgs &a, const ScanPlan &p, hipStream_t st
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a); };
     const bool ragged = a.D % 4 != 0;
     if constexpr (FORM == FORM_PAIR || FORM == FORM_HALF) {
-        if (a.gate.state) {
+        if (a.gate.refused) {
             if (ragged) launch(scan_resident_kernel<T, NB, FORM, true, true>);
             else launch(scan_resident_kernel<T, NB, FORM, false, true>);
             return;
@@ -2366,7 +2454,7 @@ static void launch_stream(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
     const dim3 grid((unsigned)(ceil_div(p.pblocks, 8) * 8 * p.nch)), block(SS_THREADS);
     const size_t lds = 2 * (size_t)(2 * CT + 8) * 4 * FRAG_UNITS * 16;
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a); };
-    if (a.gate.state) {
+    if (a.gate.refused) {
         if (a.D % 4) launch(scan_stream_kernel<T, CT, true, true>);
         else launch(scan_stream_kernel<T, CT, false, true>);
     } else {
@@ -2482,7 +2570,7 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
     if (!p.resolve) return;
     if (half) {
         r.rest = b.rest;
-        r.rest_count = b.list_count + (SCAN_LISTS + 1) * LIST_STRIDE;
+        r.rest_count = b.list_count + SCAN_LISTS * LIST_STRIDE;
         r.rest_cap = (int)ceil_div(ceil_div(c.N, RC_POINTS), SCAN_LISTS) * RC_POINTS;
     }
     if constexpr (L == 4 || L == 8) {
@@ -2536,12 +2624,13 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
 #undef FTK_LAUNCH_RESOLVE
 }
 
-// tiles: those of the image to prepare (0: they are)
+// tiles: those of the image to prepare (0: they are); whole: the problem that c is a part of
 template <typename T>
 static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w, int tiles,
-                                hipStream_t st)
+                                const AssignCall &whole, hipStream_t st)
 {
-    const dim3 cg((unsigned)tiles), cb((unsigned)(p.nb < 16 ? 64 * p.nb : 1024));
+    const int most = centroid_waves(sizeof(T), p.half), waves = p.nb < most ? p.nb : most;
+    const dim3 cg((unsigned)(tiles + (p.half ? sample_shares(p.tiles) * p.tiles : 0))), cb((unsigned)(64 * waves));
     // a contiguous list where refine_kernel takes it over
     int32_t *const counts = p.resolve ? b.list_count : w.wl_count;
     const int lists = p.resolve ? SCAN_LISTS : 1;
@@ -2556,7 +2645,12 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     const double half_psi = (7.0 * 1.01 * p.half_nb + 6.0) * u;
     HalfImage half = {};
     if (p.half) {
-        half.gate = b.list_count + SCAN_LISTS * LIST_STRIDE;
+        half.rest_count = b.list_count + SCAN_LISTS * LIST_STRIDE;
+        half.sample = b.sample;
+        half.X = whole.X;
+        half.N = whole.N;
+        half.tiles = tiles;
+        half.shares = sample_shares(p.tiles);
         half.image = b.half_image;
         half.ref = b.ref;
         half.start = b.half_start;
@@ -2566,16 +2660,21 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     }
     const size_t ref_bytes = (size_t)(p.half && p.half_nb > p.nb ? p.half_nb : p.nb) * 16 * sizeof(T);
     const bool has_ref = ref_bytes <= REF_BYTES;
+    const size_t sums = p.half ? (size_t)waves * 1024 * sizeof(float) : 0;
 #define FTK_LAUNCH_CENTROIDS(F, H)                                                                                    \
-    hipLaunchKernelGGL((scan_centroids_kernel<T, F, H>), cg, cb, has_ref ? ref_bytes : 0, st, (const T *)c.C, c.D, c.K, p.nb, \
+    hipLaunchKernelGGL((scan_centroids_kernel<T, F, H>), cg, cb, (has_ref ? ref_bytes : 0) + sums, st, (const T *)c.C, c.D, c.K, p.nb, \
                        b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref, b.norm, lift, half)
-    const int zeros = (lists - 1) * LIST_STRIDE + 1 + (p.half ? (SCAN_LISTS + 1) * LIST_STRIDE : 0);
+    int32_t *const refused = b.list_count + 2 * SCAN_LISTS * LIST_STRIDE;
+    const int zeros = (lists - 1) * LIST_STRIDE + 1 + (p.half ? SCAN_LISTS * LIST_STRIDE : 0);
     if (tiles == 0) FTK_TRY(launch_zero_ints(counts, zeros, st));  // the preparation does that
     else if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET, false);
     else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE, false);
     else if (p.half) FTK_LAUNCH_CENTROIDS(FORM_PAIR, true);
     else FTK_LAUNCH_CENTROIDS(FORM_PAIR, false);
 #undef FTK_LAUNCH_CENTROIDS
+    if (tiles && p.half)
+        hipLaunchKernelGGL(scan_choose_kernel, dim3(1), dim3(1024), 0, st, b.sample, b.tile_stat, p.tiles, 32 * half.shares,
+                           sample_limit(half.shares), refused);
     ScanArgs a = {};
     a.X = c.X;
     a.image = b.image;
@@ -2588,9 +2687,7 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     ah.image = b.half_image;
     ah.start = b.half_start;
     const ScanPlan ph = p.half ? cut_half(p, c.dtype, c.N, c.D, c.K) : ScanPlan{};
-    ah.norm = b.norm;
-    ah.tile_stat = b.tile_stat;
-    if (p.half) a.gate = ah.gate = ScanGate{b.list_count + SCAN_LISTS * LIST_STRIDE, HALF_VOTERS * (p.stream ? ph.ct / 2 : SC_THREADS / 64)};
+    if (p.half) a.gate = ah.gate = ScanGate{refused};
     SettleArgs s = {};
     s.rec = b.rec;
     s.splits = p.splits;
@@ -2650,11 +2747,11 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     return p.resolve ? FTK_OK : launch_refine(c, w, 0, st);
 }
 
-ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w, hipStream_t st)
+ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const ScanBuffers &b, const Workspace &w,
+                              const AssignCall &whole, hipStream_t st)
 {
     const size_t esz = c.dtype == FTK_F32 ? 4 : 8;
-    ScanPlan last = cut_last(p, c.dtype, c.N, c.D, c.K);
-    last.half = last.half && p.half;
+    const ScanPlan last = cut_last(p, c.dtype, c.N, c.D, c.K);
     int tiles = prepared_tiles(p, last);
     for (int64_t r0 = 0; r0 < c.N; r0 += p.batch) {
         AssignCall part = c;
@@ -2663,8 +2760,8 @@ ftk_status launch_scan_assign(const AssignCall &c, const ScanPlan &p, const Scan
         part.labels = c.labels + r0;
         if (c.mindist) part.mindist = (char *)c.mindist + (size_t)r0 * esz;
         const ScanPlan &cut = part.N < p.batch ? last : p;
-        FTK_TRY(c.dtype == FTK_F32 ? launch_scan_t<float>(part, cut, b, w, tiles, st)
-                                   : launch_scan_t<double>(part, cut, b, w, tiles, st));
+        FTK_TRY(c.dtype == FTK_F32 ? launch_scan_t<float>(part, cut, b, w, tiles, whole, st)
+                                   : launch_scan_t<double>(part, cut, b, w, tiles, whole, st));
         tiles = 0;
     }
     return FTK_OK;

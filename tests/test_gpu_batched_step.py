@@ -46,6 +46,29 @@ def test_batched_step_matches_two_call_step_and_oracle(N, D, K, dtype, batch):
     check_centroids(C_b.cpu().numpy(), C_ref.cpu().numpy())
 
 
+@pytest.mark.parametrize("N,D,K,dtype,batch,offset", [
+    (400000, 32, 2000, "f32", 50000, 0), (400000, 32, 2000, "f32", 130000, 40),   # batches too small for the form
+    (340001, 40, 1120, "f32", 340000, 0), (70001, 256, 1024, "f32", 9999, 0),     # that the whole takes, one row among them
+    (150001, 128, 2085, "f64", 40000, 0), (150001, 128, 2085, "f64", 40000, 40),
+])
+def test_batches_take_the_form_of_the_whole_problem(N, D, K, dtype, batch, offset):
+    """Large unprotected assignments scan on fp16 pieces where their rows allow it: which batch a row is in decides
+    nothing, to the last bit."""
+    rng = np.random.default_rng(N + D)
+    np_t = np.float32 if dtype == "f32" else np.float64
+    X = rng.normal(size=(N, D)).astype(np_t) + (rng.normal(size=(K, D)) * 5).astype(np_t)[rng.integers(0, K, N)]
+    X[N // 2:] += np.where(rng.random(N - N // 2) < 0.5, offset, -offset)[:, None].astype(np_t)
+    C = X[rng.permutation(N)[:K]].copy()
+    print("batched form", N, D, K, dtype, batch, offset, flush=True)
+    Xd, C_b = to_dev(X), to_dev(C)
+    lab_ref, md_ref = ftk.kmeans_assign(Xd, to_dev(C))
+    labels, mind, counts = ftk.kmeans_step_batched(Xd, C_b, batch)
+    torch.cuda.synchronize()
+    assert torch.equal(labels, lab_ref)
+    assert torch.equal(mind, md_ref)
+    assert torch.equal(counts.long(), torch.bincount(lab_ref.long(), minlength=K))
+
+
 def test_batched_step_keeps_empty_clusters_and_rejects_bad_batch_sizes():
     X, C = synth.random_problem(3, 4000, 16, 20, "f32")
     C[7] = 1e6          # nobody is nearest to it

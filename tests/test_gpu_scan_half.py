@@ -1,7 +1,8 @@
 """The scan on fp16 pieces, which large unprotected assignments try first: widths and ragged rows of its compiled
 variants, data that make it hand over to the bf16 pieces, points with more candidates than it notes, values beyond the
 range of fp16, a workspace without room for it.  Sampled rows against the CPU oracle; every row against the same call
-in parts that are too small for it."""
+in parts that are too small for it.  Results are those of the bf16 form by design, so which form ran is told by the
+points listed for the third pass: more than the bf16 form lists where it was fp16, no more where it was not."""
 import numpy as np
 import pytest
 import torch
@@ -22,20 +23,30 @@ def blobs(seed, N, D, K, dtype):
     return X, X[rng.permutation(N)[:K]].copy()
 
 
-def in_parts(X, C, parts=6):
-    out = [run(p, C) for p in np.array_split(X, parts)]
-    return np.concatenate([o[0] for o in out]), np.concatenate([o[1] for o in out])
+def counted(X, C, **kw):
+    stats = ftk.new_stats(DEV)
+    labels, mind = run(X, C, stats=stats, **kw)
+    return labels, mind, ftk.stats_dict(stats)["refined"]
 
 
-def check(X, C, dtype, seed=0):
-    labels, mind = run(X, C)
+def in_parts(X, C):
+    """The same by the bf16 form alone: parts of fewer rows than any call on fp16 pieces has."""
+    out = [counted(p, C) for p in np.array_split(X, -(-len(X) // 32000))]
+    return np.concatenate([o[0] for o in out]), np.concatenate([o[1] for o in out]), sum(o[2] for o in out)
+
+
+def check(X, C, dtype, half, seed=0):
+    """half: whether the call has to stay on fp16 pieces."""
+    labels, mind, listed = counted(X, C)
     rows = np.sort(np.random.default_rng(seed).permutation(len(X))[:1500])
     lab_o, d1, d2 = ref = oracle.assign(X, C, rows)
     check_assign(X, C, labels, mind, rows=rows, ref=ref)
     # direct differences: D terms of at most 3 roundings each, the oracle's own included
     tol = 2 * (X.shape[1] + 4) * EPS[dtype]
     assert np.all(np.abs(mind[rows].astype(np.float64) - d1) <= tol * d1)
-    lab_p, mind_p = in_parts(X, C)
+    lab_p, mind_p, listed_p = in_parts(X, C)
+    print("listed", listed, "by two pieces", listed_p, flush=True)
+    assert (listed > listed_p) == half
     assert np.array_equal(labels, lab_p)
     assert np.all(np.abs(mind.astype(np.float64) - mind_p) <= tol * mind_p)
     return labels
@@ -51,15 +62,15 @@ SIZES = [("f32", 300007, 17, 2950), ("f32", 250001, 33, 1900), ("f32", 130003, 6
 @pytest.mark.parametrize("dtype,N,D,K", SIZES)
 def test_labels_and_distances_at_the_edges(dtype, N, D, K):
     print("half", dtype, N, D, K, flush=True)
-    check(*blobs(N + D, N, D, K, dtype), dtype)
+    check(*blobs(N + D, N, D, K, dtype), dtype, half=True)
 
 
 # 25 and 35 tiles of centroids: rows of 3 and 6 blocks, whose bf16 image is padded by a tile more than the fp16 chunks take
-@pytest.mark.parametrize("dtype,N,D,K", [("f32", 400001, 48, 800), ("f32", 280001, 47, 1120), ("f32", 200003, 96, 777),
-                                         ("f32", 140003, 91, 1120), ("f64", 530001, 96, 800), ("f64", 750001, 48, 1119)])
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 400001, 48, 800), ("f32", 290003, 47, 1120), ("f32", 210011, 96, 777),
+                                         ("f32", 150001, 91, 1120), ("f64", 530001, 96, 800), ("f64", 750001, 48, 1119)])
 def test_chunks_of_the_two_forms_that_pad_the_centroids_differently(dtype, N, D, K):
     print("half", dtype, N, D, K, flush=True)
-    check(*blobs(N + D, N, D, K, dtype), dtype)
+    check(*blobs(N + D, N, D, K, dtype), dtype, half=True)
 
 
 @pytest.mark.parametrize("dtype,N,D,K", [("f32", 130003, 64, 1805), ("f32", 33001, 512, 720), ("f64", 70001, 192, 900)])
@@ -73,11 +84,11 @@ def test_data_that_it_cannot_tell(data, dtype, N, D, K):
     elif data == "offset":
         X += X.dtype.type(400)
         C = C + C.dtype.type(400)
-    else:  # not seen by those who vote; more candidates than are noted, equal ones among them
+    else:  # more candidates than are noted, equal ones among them
         C[40:70] = C[5] + (rng.normal(size=(30, D)) * 1e-5).astype(C.dtype)
         C[50] = C[5]
         X[-400:] = C[5]
-    labels = check(X, C, dtype)
+    labels = check(X, C, dtype, half=data == "last points")
     if data == "last points":
         assert np.all(labels[-400:] == 5)
 
@@ -110,12 +121,12 @@ def test_values_beyond_fp16_and_values_that_are_not_numbers(N, D, K):
 @pytest.mark.parametrize("dtype,N,D,K,exps", [("f32", 130003, 64, 1805, (-40, -55, -62, -67, -75, -84, 40, 75)),
                                               ("f32", 33001, 512, 720, (-62, -75, -84, 75)),
                                               ("f64", 150001, 128, 2085, (-515, -550, 505, 550)),
-                                              ("f64", 33001, 1021, 357, (-515, -550, 550))])
+                                              ("f64", 70001, 192, 900, (-515, -550, 550))])
 def test_labels_do_not_depend_on_the_scale_of_the_data(dtype, N, D, K, exps):
     rng = np.random.default_rng(D)
     X = rng.random((N, D)).astype(NP[dtype])  # nothing stands out: what one fp16 product names is often wrong
     C = X[rng.permutation(N)[:K]].copy()
-    want = check(X, C, dtype)
+    want = check(X, C, dtype, half=True)
     for e in exps:
         labels, mind = run(np.ldexp(X, e), np.ldexp(C, e))
         assert np.array_equal(labels, want), (e, int((labels != want).sum()))
@@ -126,11 +137,30 @@ def test_a_workspace_without_room_for_it():
     X, C = blobs(3, 300007, 20, 6700, "f64")  # nothing else needs more of the workspace
     Xd, Cd = to_dev(X), to_dev(C)
     full = ftk.new_workspace(Xd, len(C), ftk.FT_OFF)
-    labels, mind = ftk.kmeans_assign(Xd, Cd, workspace=full)
-    cut = torch.empty(full.numel() - 4096, dtype=full.dtype, device=DEV)
-    lab2, mind2 = ftk.kmeans_assign(Xd, Cd, workspace=cut)
-    assert torch.equal(labels, lab2)
-    assert torch.allclose(mind, mind2, rtol=2 * 24 * EPS["f64"], atol=0)
+    labels, mind, listed = counted(X, C, workspace=full)
+    lab2, mind2, listed2 = counted(X, C, workspace=torch.empty(full.numel() - 4096, dtype=full.dtype, device=DEV))
+    assert np.array_equal(labels, lab2)
+    assert np.allclose(mind, mind2, rtol=2 * 24 * EPS["f64"], atol=0)
+    _, mind_p, listed_p = in_parts(X, C)
+    assert listed > listed2 == listed_p and np.array_equal(mind2, mind_p)
+
+
+def grouped(X, rows, off=40):
+    """Two groups on either side of the origin, in these rows: the bf16 bound tells them, the fp16 bound does not."""
+    X[rows] += np.where(np.random.default_rng(1).random(len(X[rows])) < 0.5, off, -off)[:, None].astype(X.dtype)
+    return X
+
+
+@pytest.mark.parametrize("dtype,N,D,K,rows", [
+    ("f32", 400000, 32, 2000, slice(120000, None)),  # in order: all that comes first is easy
+    ("f32", 130003, 256, 1024, slice(80000, None)),
+    ("f64", 150001, 128, 2085, slice(0, 90000)),
+    ("f32", 530001, 130, 2100, slice(0, 266240)),    # the first of two launches alone
+])
+def test_rows_in_any_order_choose_the_form_for_all_launches(dtype, N, D, K, rows):
+    X, C = blobs(D, N, D, K, dtype)
+    grouped(X, rows)
+    check(X, X[np.random.default_rng(2).permutation(N)[:K]].copy(), dtype, half=False)
 
 
 @pytest.mark.parametrize("N,D,K", [(130003, 64, 1805), (33001, 512, 720)])
