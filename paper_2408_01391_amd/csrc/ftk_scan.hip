@@ -1036,12 +1036,7 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
     __syncthreads();
     const int pairs = (a.tiles + CT - 1) / CT;
     const size_t tile_units = (size_t)nb * FRAG_UNITS;
-    const int shift = ((int)blockIdx.x >> 3) % pairs;
-    auto place = [&](int t) {
-        const int q = min(t, pairs - 1) + shift;
-        return q < pairs ? q : q - pairs;
-    };
-    auto fragments = [&](int t) { return a.image + (size_t)place(t) * CT * tile_units + lane; };
+    auto fragments = [&](int t) { return a.image + (size_t)min(t, pairs - 1) * CT * tile_units + lane; };
     uint4 ring[RING][CT];
     const uint4 *f = fragments(wave);
 #pragma unroll
@@ -1052,7 +1047,7 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
     auto request_start = [&](int t) {
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            const float *hv = a.start + (place(t) * CT + c) * 32 + g * 16;
+            const float *hv = a.start + (min(t, pairs - 1) * CT + c) * 32 + g * 16;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const floatx4 h = *reinterpret_cast<const floatx4 *>(hv + 4 * i);
@@ -1106,7 +1101,7 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
         for (int c = 0; c < CT; ++c)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int j = 32 * (place(t) * CT + c) + 8 * (r >> 2) + (r & 3);
+                const int j = 32 * (t * CT + c) + 8 * (r >> 2) + (r & 3);
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt) {
                     const float v = acc[c][pt][r];
