@@ -99,7 +99,8 @@ typedef struct {
 
 /* Bytes of workspace sufficient for any of the three calls below on this problem.  FTK_FT_OFF asks for
  * more than the protected modes, for buffers of faster paths that only unprotected calls take; such a
- * call also accepts a workspace of a protected mode's size, and then runs without them. */
+ * call also accepts a workspace of a protected mode's size, and then runs without them (mindist may
+ * differ in the last places). */
 size_t ftk_workspace_bytes(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft);
 
 ftk_status ftk_assign_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K, ftk_ft_mode ft,
@@ -136,8 +137,12 @@ ftk_status ftk_plan_padded_rows(ftk_dtype dtype, int64_t N, int32_t D, int32_t K
  *   mindist [N] (dtype)   out : squared distance to it, >= 0; may be NULL.  Accuracy: points whose
  *                               decision was settled by exact re-evaluation, every point of the
  *                               scan that unprotected calls with enough centroids take (bf16
- *                               matrix instructions on split operands name the centroid, the
- *                               distance is evaluated from the rows), and every point of
+ *                               matrix instructions on split operands, or fp16 ones on rounded
+ *                               operands, name the centroid, the distance is evaluated from the
+ *                               rows: in dtype, or in double and rounded where the point was
+ *                               settled; the two forms settle different points, so that which of
+ *                               them ran - by the sizes, the rows and the room in the workspace -
+ *                               shows in last places), and every point of
  *                               the register-resident fp32 kernels (D <= 32; 32 < D <= 128 where
  *                               that kernel is dispatched), get the direct-difference value
  *                               (relative error of a few units in the last place of the
@@ -166,7 +171,8 @@ ftk_status ftk_kmeans_assign(ftk_dtype dtype, const void *X, const void *C, int6
  * not apply to it).  A problem whose scratch exceeds the array (roughly N > 4 million points, or
  * K*D beyond a few million) is rejected with FTK_EWORKSPACE and nothing is enqueued; one that fits
  * only without the buffers of the scan (16 bytes per point and more) runs on the fp32 / fp64 matrix
- * kernels, whose distances may differ in the last places.  Every call
+ * kernels, one that fits only without those of its fp16 operands scans on bf16: distances may differ
+ * in the last places.  Every call
  * on a GPU shares that GPU's array: calls must be ordered on one stream; calls that overlap on
  * one GPU race.  The buffer keeps the last call's contents; everything that must start at zero
  * is cleared by the call itself. */
