@@ -139,10 +139,9 @@ ftk_status ftk_plan_padded_rows(ftk_dtype dtype, int64_t N, int32_t D, int32_t K
  *                               scan that unprotected calls with enough centroids take (bf16
  *                               matrix instructions on split operands, or fp16 ones on rounded
  *                               operands, name the centroid, the distance is evaluated from the
- *                               rows: in dtype, or in double and rounded where the point was
- *                               settled; the two forms settle different points, so that which of
- *                               them ran - by the sizes, the rows and the room in the workspace -
- *                               shows in last places), and every point of
+ *                               rows: in dtype, where the point was settled in double and rounded;
+ *                               for all points in double where a problem is large enough for fp16
+ *                               operands, whichever of the two forms runs), and every point of
  *                               the register-resident fp32 kernels (D <= 32; 32 < D <= 128 where
  *                               that kernel is dispatched), get the direct-difference value
  *                               (relative error of a few units in the last place of the
@@ -171,8 +170,7 @@ ftk_status ftk_kmeans_assign(ftk_dtype dtype, const void *X, const void *C, int6
  * not apply to it).  A problem whose scratch exceeds the array (roughly N > 4 million points, or
  * K*D beyond a few million) is rejected with FTK_EWORKSPACE and nothing is enqueued; one that fits
  * only without the buffers of the scan (16 bytes per point and more) runs on the fp32 / fp64 matrix
- * kernels, one that fits only without those of its fp16 operands scans on bf16: distances may differ
- * in the last places.  Every call
+ * kernels, whose distances may differ in the last places.  Every call
  * on a GPU shares that GPU's array: calls must be ordered on one stream; calls that overlap on
  * one GPU race.  The buffer keeps the last call's contents; everything that must start at zero
  * is cleared by the call itself. */

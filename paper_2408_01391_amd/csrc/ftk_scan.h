@@ -20,6 +20,7 @@ struct ScanPlan {
     int64_t rec_reserve;  // records to reserve
     bool half;          // a scan on fp16 pieces is prepared too, and runs first
     int half_nb, half_tiles;  // blocks and tiles of its image
+    bool either;        // part of a problem that may take either form, so that neither must show in the distances
     bool resolve;       // listed points are settled by the scan's own third pass (else refine_kernel)
 };
 
@@ -57,7 +58,7 @@ struct ScanBuffers {
 ScanPlan plan_scan(ftk_dtype dtype, int64_t N, int D, int K);
 // the cut alone, for part of a problem that takes this path
 ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K);
-// the same for n points of a problem that is cut as `whole`: with fp16 pieces if that has them
+// the same for n points of a problem that is cut as `whole`
 ScanPlan cut_part(const ScanPlan &whole, ftk_dtype dtype, int64_t n, int D, int K);
 // rows that the preparation writes for the points or for any batch of them, and those its images are reserved for
 void scan_padded_rows(ftk_dtype dtype, int64_t N, int D, int K, int64_t *planned, int64_t *reserved);

@@ -560,7 +560,7 @@ __global__ __launch_bounds__(64 * centroid_waves(sizeof(T), HALF)) void scan_cen
 // ---- choice of form ---------------------------------------------------------------------------
 // One fp16 piece leaves nearly all points of some data to the third pass (data far from the origin or in groups, against
 // their spread; a centroid beyond the range of fp16): two pieces scan these.  Rows spread evenly over the whole problem
-// tell, whatever their order, before either scan runs; the choice holds for all launches and batches of the problem.
+// tell, whatever their order, before either scan runs; the choice holds for all launches of the problem.
 // The sample costs one launch, 4 us, beside what it adds to the preparation (2^21 x 32, K = 4096 2 us; 1021 fp64 features, K = 357
 // 11 us).  (A vote of the scan's first workgroups costs none, but all of that scan where all run at
 // once: two groups at +-20, spread 1, in 200000 x 32, K = 2400 206 us against 144 by two pieces alone, 150001 x 128 fp64,
@@ -1173,10 +1173,18 @@ struct SettleArgs {
     const void *ref;    // [D] the reference r
 };
 
-// HALF: the records may come from fp16 pieces
-template <typename T, int L, bool HALF>
+enum SettleKind : int {
+    SETTLE_PLAIN = 0,   // distances in the data's type
+    SETTLE_DOUBLE = 1,  // in double, added up in the order of group_sqdist(): whatever passes a point goes through, and so
+                        // whichever form scanned it (batches of a step take the one that is faster for their size), its
+                        // distance has the same bits; fp32 2^21 x 32, K = 4096 859 / 860 us a call, 60000 x 1024 343 / 344
+    SETTLE_HALF = 2     // the same, and the records may come from fp16 pieces
+};
+template <typename T, int L, int KIND>
 __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T *C, T *mindist, SettleArgs a)
 {
+    constexpr bool HALF = KIND == SETTLE_HALF;
+    using Acc = std::conditional_t<KIND == SETTLE_PLAIN, T, double>;
     const bool half = HALF && a.gate.half();
     const int splits = half ? a.half_splits : a.splits;
     const float psi = half ? a.half_psi : a.psi, lift = half ? a.half_lift : a.lift, tiny = half ? a.half_tiny : a.tiny;
@@ -1247,19 +1255,19 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
             j[u] = mine ? j[u] : o.j1;
         }
     }
-    T d[ROWS];
+    Acc d[ROWS];
     float xn[ROWS], yn[ROWS], cn[ROWS], xr[ROWS];  // of x and of x - r, of c, of what an fp16 piece leaves of x
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         j[u] = (unsigned)j[u] < (unsigned)a.K ? j[u] : 0;  // padding rows, when no score was a number
         c[u] = C + (size_t)j[u] * a.D;
         cn[u] = a.norm[j[u]];
-        d[u] = T(0);
+        d[u] = Acc(0);
         xn[u] = yn[u] = xr[u] = 0.f;
     }
     const T *const ref_row = (const T *)a.ref;
     auto add = [&](int u, T xe, T ce, T re) {
-        const T t = xe - ce;
+        const Acc t = (Acc)xe - (Acc)ce;
         d[u] = fma(t, t, d[u]);
         const float w = (float)(xe * s);
         xn[u] = fmaf(w, w, xn[u]);
@@ -1289,7 +1297,7 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
         for (int u = 0; u < ROWS; ++u) add(u, X0[(unsigned)(at[u] * a.D + f)], c[u][f], HALF ? ref_row[f] : T(0));
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
-        const T dist = group_sum<L>(d[u]);
+        const T dist = (T)group_sum<L>(d[u]);
         const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + tiny;
         float A = lost * norm + psi * (norm + ref);
         const float B = lift - 0.5f * psi;
@@ -2331,7 +2339,7 @@ ScanPlan cut_scan(ftk_dtype dtype, int64_t N, int D, int K)
         const int64_t n = ceil_div(N, batch_max);
         p = cut_launch(dtype, ceil_div(ceil_div(N, n), SCAN_BATCH_STEP) * SCAN_BATCH_STEP, D, K);
     }
-    p.half = p.form == FORM_PAIR && half_pays(dtype, p.batch, D, K);
+    p.half = p.either = p.form == FORM_PAIR && half_pays(dtype, p.batch, D, K);
     if (p.half) {
         const ScanPlan h = cut_half(p, dtype, p.batch, D, K);
         p.half_nb = h.nb;
@@ -2357,9 +2365,8 @@ static int prepared_tiles(const ScanPlan &p, const ScanPlan &last)
 ScanPlan cut_part(const ScanPlan &whole, ftk_dtype dtype, int64_t n, int D, int K)
 {
     ScanPlan p = cut_scan(dtype, n, D, K);
-    p.half = whole.half;
-    p.half_nb = whole.half_nb;
-    p.half_tiles = whole.half_tiles;
+    p.half = p.half && whole.half;
+    p.either = whole.either;
     return p;
 }
 
@@ -2554,14 +2561,15 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
     s.sums = 0.5f * (float)((c.D / L + 4 + 6 + 10) * (double)Mma<float>::kEps);
     r.list_cap = s.list_cap = (int)ceil_div(ceil_div(c.N, rows), s.lists) * rows;
     const dim3 sg((unsigned)ceil_div(c.N, rows)), sb(256);
-    bool half = false;
+    const bool half = L >= 4 && p.half;
+    auto settle = [&](auto kernel) { hipLaunchKernelGGL(kernel, sg, sb, 0, st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, s); };
     if constexpr (L >= 4) {
-        half = p.half;
-        if (half)
-            hipLaunchKernelGGL((scan_settle_kernel<T, L, true>), sg, sb, 0, st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, s);
+        if (half) settle(scan_settle_kernel<T, L, SETTLE_HALF>);
+        else if (sizeof(T) == 4 && p.either) settle(scan_settle_kernel<T, L, SETTLE_DOUBLE>);
+        else settle(scan_settle_kernel<T, L, SETTLE_PLAIN>);
+    } else {
+        settle(scan_settle_kernel<T, L, SETTLE_PLAIN>);
     }
-    if (!half)
-        hipLaunchKernelGGL((scan_settle_kernel<T, L, false>), sg, sb, 0, st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, s);
     if (!p.resolve) return;
     if (half) {
         r.rest = b.rest;

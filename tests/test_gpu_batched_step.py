@@ -47,13 +47,14 @@ def test_batched_step_matches_two_call_step_and_oracle(N, D, K, dtype, batch):
 
 
 @pytest.mark.parametrize("N,D,K,dtype,batch,offset", [
-    (400000, 32, 2000, "f32", 50000, 0), (400000, 32, 2000, "f32", 130000, 40),   # batches too small for the form
-    (340001, 40, 1120, "f32", 340000, 0), (70001, 256, 1024, "f32", 9999, 0),     # that the whole takes, one row among them
-    (150001, 128, 2085, "f64", 40000, 0), (150001, 128, 2085, "f64", 40000, 40),
+    (400000, 32, 2000, "f32", 50000, 0), (400000, 32, 2000, "f32", 250000, 40),   # batches too small for the form
+    (340001, 40, 1120, "f32", 340000, 0), (70001, 256, 1024, "f32", 9999, 0),     # that the whole takes, or not;
+    (70001, 256, 1024, "f32", 50000, 0), (150001, 128, 2085, "f64", 40000, 0),    # one row among them
+    (150001, 128, 2085, "f64", 150000, 40),
 ])
-def test_batches_take_the_form_of_the_whole_problem(N, D, K, dtype, batch, offset):
-    """Large unprotected assignments scan on fp16 pieces where their rows allow it: which batch a row is in decides
-    nothing, to the last bit."""
+def test_the_form_of_the_scan_does_not_show_in_a_batched_step(N, D, K, dtype, batch, offset):
+    """Large unprotected assignments scan on fp16 pieces where size and rows allow it, batch by batch: labels, distances
+    and counts are those of the whole problem to the last bit."""
     rng = np.random.default_rng(N + D)
     np_t = np.float32 if dtype == "f32" else np.float64
     X = rng.normal(size=(N, D)).astype(np_t) + (rng.normal(size=(K, D)) * 5).astype(np_t)[rng.integers(0, K, N)]

@@ -133,16 +133,16 @@ def test_labels_do_not_depend_on_the_scale_of_the_data(dtype, N, D, K, exps):
         assert not np.isnan(mind).any()
 
 
-def test_a_workspace_without_room_for_it():
-    X, C = blobs(3, 300007, 20, 6700, "f64")  # nothing else needs more of the workspace
+@pytest.mark.parametrize("dtype,N,D,K", [("f64", 300007, 20, 6700), ("f32", 100003, 129, 931), ("f32", 33333, 1024, 360)])
+def test_a_workspace_without_room_for_it(dtype, N, D, K):
+    X, C = blobs(3, N, D, K, dtype)  # nothing else needs more of the workspace
     Xd, Cd = to_dev(X), to_dev(C)
     full = ftk.new_workspace(Xd, len(C), ftk.FT_OFF)
     labels, mind, listed = counted(X, C, workspace=full)
     lab2, mind2, listed2 = counted(X, C, workspace=torch.empty(full.numel() - 4096, dtype=full.dtype, device=DEV))
-    assert np.array_equal(labels, lab2)
-    assert np.allclose(mind, mind2, rtol=2 * 24 * EPS["f64"], atol=0)
-    _, mind_p, listed_p = in_parts(X, C)
-    assert listed > listed2 == listed_p and np.array_equal(mind2, mind_p)
+    assert np.array_equal(labels, lab2) and np.array_equal(mind, mind2)  # the form does not show
+    _, _, listed_p = in_parts(X, C)
+    assert listed > listed2 and abs(listed2 - listed_p) <= 0.01 * listed_p
 
 
 def grouped(X, rows, off=40):
