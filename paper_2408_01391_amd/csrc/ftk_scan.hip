@@ -296,7 +296,8 @@ struct HalfImage {
 constexpr size_t REF_BYTES = 64 * 1024;
 // HALF: the second image too, and the scores of sampled rows (fp64: more registers than 16 waves have)
 constexpr int centroid_waves(size_t element, bool half) { return half && element == 8 ? 8 : 16; }
-template <typename T, int FORM, bool HALF>
+// RAG: rows that are not whole quads (only HALF asks)
+template <typename T, int FORM, bool HALF, bool RAG = true>
 __global__ __launch_bounds__(64 * centroid_waves(sizeof(T), HALF)) void scan_centroids_kernel(const T *C, int D, int K, int nb, uint4 *image, float *start,
                                                               float4 *tile_stat, double *scale, int32_t *list_count, int lists,
                                                               int has_ref, float *norm, double lift, HalfImage half_args)
@@ -320,10 +321,10 @@ __global__ __launch_bounds__(64 * centroid_waves(sizeof(T), HALF)) void scan_cen
     const int extra = (int)blockIdx.x - half.tiles, tile = sampling ? extra / half.shares : (int)blockIdx.x;
     const int row = lane & 31, g = lane >> 5;
     const int j = 32 * tile + row;
-    const RowReader<T, true> reader(C + (size_t)(j < K ? j : 0) * D, D);
+    const RowReader<T, RAG> reader(C + (size_t)(j < K ? j : 0) * D, D);
     const int share = extra - tile * half.shares;
     const int64_t picked = sampling ? half.N * (2 * (32 * share + row) + 1) / (64 * half.shares) : 0;
-    const RowReader<T, true> xr(sampling ? static_cast<const T *>(half.X) + picked * D : C, D);
+    const RowReader<T, RAG> xr(sampling ? static_cast<const T *>(half.X) + picked * D : C, D);
     T m = T(0), whole = T(0);  // largest magnitude of the rows less the reference, and of the rows
     double gain = 0.0, rr = 0.0;  // half the rows' sum of squares less that of what is left of them, and ||r||^2
     for (int d = tid; d < D; d += blockDim.x) {
@@ -2664,15 +2665,16 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     const size_t ref_bytes = (size_t)(p.half && p.half_nb > p.nb ? p.half_nb : p.nb) * 16 * sizeof(T);
     const bool has_ref = ref_bytes <= REF_BYTES;
     const size_t sums = p.half ? (size_t)waves * 1024 * sizeof(float) : 0;
-#define FTK_LAUNCH_CENTROIDS(F, H)                                                                                    \
-    hipLaunchKernelGGL((scan_centroids_kernel<T, F, H>), cg, cb, (has_ref ? ref_bytes : 0) + sums, st, (const T *)c.C, c.D, c.K, p.nb, \
+#define FTK_LAUNCH_CENTROIDS(...)                                                                                     \
+    hipLaunchKernelGGL((scan_centroids_kernel<T, __VA_ARGS__>), cg, cb, (has_ref ? ref_bytes : 0) + sums, st, (const T *)c.C, c.D, c.K, p.nb, \
                        b.image, b.start, b.tile_stat, b.scale, counts, lists, (int)has_ref, b.norm, lift, half)
     int32_t *const refused = b.list_count + 2 * SCAN_LISTS * LIST_STRIDE;
     const int zeros = (lists - 1) * LIST_STRIDE + 1 + (p.half ? SCAN_LISTS * LIST_STRIDE : 0);
     if (tiles == 0) FTK_TRY(launch_zero_ints(counts, zeros, st));  // the preparation does that
     else if (p.form == FORM_OCTET) FTK_LAUNCH_CENTROIDS(FORM_OCTET, false);
     else if (p.form == FORM_TRIPLE) FTK_LAUNCH_CENTROIDS(FORM_TRIPLE, false);
-    else if (p.half) FTK_LAUNCH_CENTROIDS(FORM_PAIR, true);
+    else if (p.half && c.D % 4) FTK_LAUNCH_CENTROIDS(FORM_PAIR, true, true);
+    else if (p.half) FTK_LAUNCH_CENTROIDS(FORM_PAIR, true, false);
     else FTK_LAUNCH_CENTROIDS(FORM_PAIR, false);
 #undef FTK_LAUNCH_CENTROIDS
     if (tiles && p.half)
