@@ -46,7 +46,7 @@
 //
 // Large calls try a cheaper form first, FORM_HALF: one fp16 piece of either operand and one product, a third of the
 // matrix work.  Lost are r_x.c and x.r_c, |r| up to 2^-11 |x|: ||r_c|| / ||c|| is measured by the preparation and ||r_x|| by the settle
-// pass, some 0.45 2^-11 each, which makes the bound some 25 times wider than that of two bf16 pieces and leaves 3 to 10 %
+// pass, some 0.45 2^-11 each, which makes the bound some 25 times wider than that of two bf16 pieces and leaves 1 to 10 %
 // of the points for the third pass - with two candidates as a rule, so that it costs a tenth of the scan.  An operand below
 // 2^-14 rounds like that value, in the piece and in the instruction (pinned by a test): norms are raised by 2^-14 for every
 // feature.  Data whose points lie far from the origin or in groups would list nearly all, so a sample of the rows chooses
