@@ -18,7 +18,7 @@ struct ScanPlan {
     int64_t pblocks;    // blocks of 256 points
     int64_t batch;      // points of a launch: the rest of this is cut for those
     int64_t rec_reserve;  // records to reserve
-    bool half;          // a scan on fp16 pieces is prepared too, and runs first
+    bool half;          // a scan on fp16 pieces is prepared too, and runs instead where a sample of the rows says so
     int half_nb, half_tiles;  // blocks and tiles of its image
     bool either;        // part of a problem that may take either form, so that neither must show in the distances
     bool resolve;       // listed points are settled by the scan's own third pass (else refine_kernel)

@@ -4,7 +4,7 @@
 //           calls: rounded to one fp16 piece), fp32 accumulation.  Per point it keeps the best score, its centroid and the second-best
 //           score - nothing else;
 //   settle  the distance to the named centroid in direct-difference form, in the data's own type
-//           (Section 3.1.1), and the decision whether the scan could be trusted: where the two best
+//           (Section 3.1.1; in double where either form may run), and the decision whether the scan could be trusted: where the two best
 //           scores are closer than the scan's error bound the point is listed;
 //   resolve the listed points: every centroid whose score lies within the bound of the best is
 //           evaluated in double; where there are many of those, all centroids on the matrix instructions
@@ -44,7 +44,7 @@
 //     A ||c|| + (psi / 2 - lift) ||c||^2 <= A^2 / (4 lift - 2 psi)
 // too low, whatever its norm, and that of the named centroid at most A ||c|| + (psi / 2 + lift) ||c||^2 too high.
 //
-// Large calls try a cheaper form first, FORM_HALF: one fp16 piece of either operand and one product, a third of the
+// Large calls take a cheaper form where their rows allow it, FORM_HALF: one fp16 piece of either operand and one product, a third of the
 // matrix work.  Lost are r_x.c and x.r_c, |r| up to 2^-11 |x|: ||r_c|| / ||c|| is measured by the preparation and ||r_x|| by the settle
 // pass, some 0.45 2^-11 each, which makes the bound some 25 times wider than that of two bf16 pieces and leaves 1 to 10 %
 // of the points for the third pass - with two candidates as a rule, so that it costs a tenth of the scan.  An operand below

@@ -1,4 +1,4 @@
-"""The scan on fp16 pieces, which large unprotected assignments try first: widths and ragged rows of its compiled
+"""The scan on fp16 pieces, which large unprotected assignments take where their rows allow it: widths and ragged rows of its compiled
 variants, data that make it hand over to the bf16 pieces, points with more candidates than it notes, values beyond the
 range of fp16, a workspace without room for it.  Sampled rows against the CPU oracle; every row against the same call
 in parts that are too small for it.  Results are those of the bf16 form by design, so which form ran is told by the
