@@ -61,6 +61,7 @@
 
 #include "ftk_internal.h"
 #include "ftk_mma.h"
+#include "ftk_quads.h"
 #include "ftk_scan.h"
 #include "ftk_smalld.h"
 
@@ -68,10 +69,6 @@ namespace ftk {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-// rows need no more than element alignment: 16-byte loads from 4- or 8-byte aligned addresses
-typedef float float4e __attribute__((ext_vector_type(4), aligned(4)));
-typedef double double2e __attribute__((ext_vector_type(2), aligned(8)));
-
 constexpr int SC_THREADS = 256;  // resident scan: four waves of two point tiles
 constexpr int SC_PT = 2;
 constexpr int SC_POINTS = 256;   // points per workgroup (both scans)
@@ -189,28 +186,6 @@ __device__ __forceinline__ uint4 select_units(bool c, const uint4 &a, const uint
 
 // Four features from `off`, without branches: whole quads by one access clamped into the row, the
 // quad that holds the row's end (RAG: D not a multiple of 4) from `tail`, zero beyond.
-template <typename T>
-struct Quad {
-    T v[4];
-};
-template <typename T>
-__device__ __forceinline__ Quad<T> load_quad(const T *p)
-{
-    Quad<T> q;
-    if constexpr (sizeof(T) == 4) {
-        const float4e f = *reinterpret_cast<const float4e *>(p);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) q.v[e] = f[e];
-    } else {
-        const double2e f = *reinterpret_cast<const double2e *>(p);
-        const double2e h = *reinterpret_cast<const double2e *>(p + 2);
-        q.v[0] = f[0];
-        q.v[1] = f[1];
-        q.v[2] = h[0];
-        q.v[3] = h[1];
-    }
-    return q;
-}
 template <typename T, bool RAG>
 struct RowReader {
     const T *row;
@@ -238,30 +213,6 @@ struct RowReader {
     }
 };
 
-// Sum over the L lanes of a group (every lane gets it; the same additions whatever the values).
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-template <int L, typename V>
-__device__ __forceinline__ V group_sum(V v)
-{
-    v += dpp_move<0xB1>(v);                            // lane ^ 1
-    if constexpr (L >= 4) v += dpp_move<0x4E>(v);      // lane ^ 2
-    if constexpr (L >= 8) v += dpp_move<0x141>(v);     // the other four of eight
-    if constexpr (L >= 16) v += dpp_move<0x140>(v);    // the other eight of sixteen
-    if constexpr (L >= 32) v += __shfl_xor(v, 16, 64);
-    if constexpr (L >= 64) v += __shfl_xor(v, 32, 64);
-    return v;
-}
 // the largest of 64 lanes, but for those that are not numbers
 template <typename V>
 __device__ __forceinline__ V wave_max(V v)
@@ -597,7 +548,9 @@ __global__ __launch_bounds__(1024) void scan_choose_kernel(const float4 *sample,
 
 // ---- bookkeeping of the scans -----------------------------------------------------------------
 // Tile maximum, runner-up tile maximum and the 16 scores of the best tile of one lane: two scores
-// share a v_max3; the copy of the scores is skipped unless some lane of the wave found a better tile.
+// share a v_max3; the copy of the scores is skipped unless some lane of the wave found a better tile, and runs as moves
+// under the lane mask: a v_mov_b64 takes the issue time of one v_cndmask_b32 and moves two scores (2^20 x 8, K = 1024
+// 152 us a call with selects, 140 with moves; 2^21 x 32, K = 4096 850 / 785; 300007 x 45, K = 333 69.7 / 67.7).
 struct ScanBest {
     float m1, m2;
     int t1;
@@ -620,10 +573,11 @@ __device__ __forceinline__ void scan_best_add(ScanBest &b, const floatx16 &acc, 
     const bool c = tm > b.m1;
     b.m2 = __builtin_amdgcn_fmed3f(b.m1, b.m2, tm);
     b.m1 = max2f(b.m1, tm);
-    if (__any(c)) {
-        b.t1 = c ? T : b.t1;
+    if (c) {
+        asm volatile("");  // (keeps the branch: the compiler would turn it into selects)
+        b.t1 = T;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) b.s[r] = c ? acc[r] : b.s[r];
+        for (int r = 0; r < 16; ++r) b.s[r] = acc[r];
     }
 }
 

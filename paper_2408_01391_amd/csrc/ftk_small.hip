@@ -8,6 +8,7 @@
 // nothing has to be prepared, certified or settled afterwards.
 #include "ftk_internal.h"
 #include "ftk_mma.h"
+#include "ftk_quads.h"
 #include "ftk_small.h"
 
 namespace ftk {
@@ -19,9 +20,6 @@ constexpr int SM_GRID = 512;
 constexpr int SM_FILL = 256;          // workgroups to aim at: more lanes per point than that fills cost time (20000 x 24,
                                       // K = 100: 13.4 us; aiming at 1024: 15.4)
 constexpr int SM_LIMB_BITS = 24;
-
-typedef float float4e __attribute__((ext_vector_type(4), aligned(4)));
-typedef double double2e __attribute__((ext_vector_type(2), aligned(8)));
 
 // the update's fixed point (see ftk_update.hip): the same scale and rounding, so the same sums
 __device__ __forceinline__ double small_scale(double absmax, int64_t rows)
