@@ -207,8 +207,8 @@ __global__ __launch_bounds__(fast_waves(NQ) * 64, fast_waves_per_simd(NQ)) void 
             float s = 0.f;
 #pragma unroll
             for (int b = 0; b < NQ; ++b) {
-                const floatx4 lo = load_frag<float, true>(xrow, 8 * b, D);
-                const floatx4 hi = load_frag<float, true>(xrow, 8 * b + 4, D);
+                const floatx4 lo = load_frag<float, ROWS_ALIGNED>(xrow, 8 * b, D);
+                const floatx4 hi = load_frag<float, ROWS_ALIGNED>(xrow, 8 * b + 4, D);
                 bf16x8 q0, q1, q2;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(fast_waves(NQ) * 64, fast_waves_per_simd(NQ)) void 
                             float ref2 = -a.chk_s[(T * 2 + g) * 2 + 1];
 #pragma unroll
                             for (int q = 0; q < 2 * NQ; ++q) {
-                                const floatx4 xv = load_frag<float, true>(xrow, 4 * q, D);
+                                const floatx4 xv = load_frag<float, ROWS_ALIGNED>(xrow, 4 * q, D);
                                 const floatx4 vv = *reinterpret_cast<const floatx4 *>(v2 + 4 * q);
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) ref2 = fmaf(xv[e], vv[e], ref2);
@@ -414,8 +414,8 @@ __global__ __launch_bounds__(fast_waves(NQ) * 64, fast_waves_per_simd(NQ)) void 
             floatx4 xlo[NQ], xhi[NQ];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                xlo[q] = load_frag<float, true>(xrow, 8 * q, D);
-                xhi[q] = load_frag<float, true>(xrow, 8 * q + 4, D);
+                xlo[q] = load_frag<float, ROWS_ALIGNED>(xrow, 8 * q, D);
+                xhi[q] = load_frag<float, ROWS_ALIGNED>(xrow, 8 * q + 4, D);
             }
             float bound = (float)a.band_coef * (sqrtf(xn[pt]) * cmax + 0.5f * cmax2);
             // strict FT: an error that stayed below the detection threshold left its mark in the

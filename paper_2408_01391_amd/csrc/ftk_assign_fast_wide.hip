@@ -128,8 +128,8 @@ __global__ __launch_bounds__(256) void split2_centroids_kernel(const float *C, i
         const int j = j0 + i;
         if (j >= K) break;
         const float *src = C + (size_t)j * D;
-        const floatx4 lo = load_frag<float, true>(src, 8 * u, D);
-        const floatx4 hi = load_frag<float, true>(src, 8 * u + 4, D);
+        const floatx4 lo = load_frag<float, ROWS_ALIGNED>(src, 8 * u, D);
+        const floatx4 hi = load_frag<float, ROWS_ALIGNED>(src, 8 * u + 4, D);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             float v = e < 4 ? lo[e] : hi[e - 4];
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(FW_WAVES * 64, FW_WAVES / 4) void assign_fast_wide_
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 const int off = 16 * (u >> 1) + 8 * g + 4 * (u & 1);
-                const floatx4 v = load_frag_clamped<float, true>(row, off, D);
+                const floatx4 v = load_frag_clamped<float, ROWS_ALIGNED>(row, off, D);
                 const bool keep = off < D;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) raw[u][e] = keep ? v[e] : 0.f;

@@ -98,10 +98,10 @@ constexpr int generic_kt(int K) { return K <= Mma<T>::TM ? 1 : (K <= 2 * Mma<T>:
 // real centroids only (K a multiple of the chunk) - the stage loop is then compiled without its
 // per-quad, per-tile and per-element conditions: one straight run of matrix instructions per stage
 // instead of a branch every KT of them, and no masking selects on the point fragments.
-template <typename T, int KTV, bool ALIGNED, bool FT, bool FULL>
+template <typename T, int KTV, int AL, bool FT, bool FULL>
 __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void assign_generic_kernel(GenericArgs<T> a)
 {
-    static_assert(ALIGNED || !FULL, "the condition-free stage loop is compiled for aligned rows only");
+    static_assert(AL == ROWS_ALIGNED || !FULL, "the condition-free stage loop is compiled for aligned rows only");
     using M = Mma<T>;
     using Cfg = GenericCfg<T, KTV>;
     using frag_t = typename M::frag_t;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
         if constexpr (FULL)
             return *reinterpret_cast<const frag_t *>(xbase + (xoff[pt] + (unsigned)(quad * 8 * (int)sizeof(T))));
         else
-            return load_frag_clamped<T, ALIGNED>(xrow[pt], quad * 8 + E * g, D);
+            return load_frag_clamped<T, AL>(xrow[pt], quad * 8 + E * g, D);
     };
 
     // Epilogue state per point tile: best tile maximum, runner-up maximum over the OTHER tiles and
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
             } else {
                 const int j = kc * KC + st_row[i];
                 const int d0 = q0 * 8 + st_pc[i] * E;
-                pf[i] = load_frag_clamped<T, ALIGNED>(a.C + (int64_t)min(j, a.K - 1) * D, d0, D);
+                pf[i] = load_frag_clamped<T, AL>(a.C + (int64_t)min(j, a.K - 1) * D, d0, D);
             }
         }
 #pragma unroll
@@ -242,6 +242,9 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
     auto commit = [&](int kc, int dc, int buf) {
         unsigned char *const base = lds_raw + buf * STAGE_BYTES;
         const int q0 = dc * DQ;
+        if (AL == ROWS_PIECES && (q0 + DQ) * 8 > D)
+#pragma unroll
+            for (int i = 0; i < NP; ++i) pf[i] = frag_place<T>(pf[i], q0 * 8 + st_pc[i] * E, D);
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int idx = tid + 256 * i;
@@ -273,9 +276,17 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
     for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
         for (int q = 0; q < DQ; ++q) xs[pt][q] = load_x(pt, q);
+    auto place_x = [&](int q0) {  // the stage that starts at quad q0
+        if (AL == ROWS_PIECES && (q0 + DQ) * 8 > D)
+#pragma unroll
+            for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                for (int q = 0; q < DQ; ++q) xs[pt][q] = frag_place<T>(xs[pt][q], (q0 + q) * 8 + E * g, D);
+    };
 
     fetch(0, 0);
     commit(0, 0, 0);
+    place_x(0);
     __syncthreads();
     int buf = 0;
 
@@ -367,6 +378,7 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
             for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
                 for (int q = 0; q < DQ; ++q) xs[pt][q] = xnx[pt][q];
+            place_x(chunk_end ? 0 : q0 + DQ);
             if (more) commit(kc_n, dc_n, buf ^ 1);
             __syncthreads();
             buf ^= 1;
@@ -452,7 +464,7 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
                         // weighted reference on demand: x . v2 over this lane's features
                         double r2 = 0.0;
                         for (int qq = 0; qq < nq; ++qq) {
-                            const frag_t xv = load_frag<T, ALIGNED>(xrow[pt], qq * 8 + E * g, D);
+                            const frag_t xv = load_frag<T, AL>(xrow[pt], qq * 8 + E * g, D);
                             const frag_t vv = *reinterpret_cast<const frag_t *>(a.chk_v2 + (size_t)kc * a.D8 + qq * 8 + E * g);
 #pragma unroll
                             for (int e = 0; e < E; ++e) r2 = fma((double)xv[e], (double)vv[e], r2);
@@ -585,7 +597,7 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
             // two candidates: lane groups 0/1 each evaluate one of them exactly
             const int ja = min(i1, i2), jb = max(i1, i2);
             const int mine = (g & 1) ? jb : ja;
-            const double dm = exact_sqdist<T, ALIGNED>(xrow[pt], a.C + (int64_t)mine * D, D);
+            const double dm = exact_sqdist<T, AL>(xrow[pt], a.C + (int64_t)mine * D, D);
             const double dother = shfl_xor_t(dm, TN);
             const double da = (g & 1) ? dother : dm;
             const double db = (g & 1) ? dm : dother;
@@ -687,7 +699,7 @@ __device__ __forceinline__ void refine_settle(double (&best)[P], int (&bj)[P], c
 // widely as possible), up to P = 8 beyond.  Point rows are read with wave-uniform addresses (one
 // cache line broadcast per load).  Every (point, centroid) sum adds the features in index order
 // into one accumulator, so identical centroids tie exactly whatever the batch size.
-template <typename T, bool ALIGNED, int JU, int P>
+template <typename T, int AL, int JU, int P>
 __device__ __forceinline__ void refine_batch(const T *__restrict__ X, const T *__restrict__ C, int D, int K,
                                              const int32_t *__restrict__ wl, int first, int np,
                                              int32_t *labels, T *mindist, double (*sh_best)[8], int (*sh_j)[8])
@@ -728,19 +740,27 @@ __device__ __forceinline__ void refine_batch(const T *__restrict__ X, const T *_
 #pragma unroll
             for (int r = 0; r < JU; ++r)
 #pragma unroll
-                for (int v = 0; v < DU; ++v) cf[r][v] = load_frag_clamped<T, ALIGNED>(c[r], d0 + v * E, D);
+                for (int v = 0; v < DU; ++v) cf[r][v] = load_frag_clamped<T, AL>(c[r], d0 + v * E, D);
 #pragma unroll
             for (int u = 0; u < P; ++u)
 #pragma unroll
-                for (int v = 0; v < DU; ++v) xf[u][v] = load_frag_clamped<T, ALIGNED>(x[u], d0 + v * E, D);
+                for (int v = 0; v < DU; ++v) xf[u][v] = load_frag_clamped<T, AL>(x[u], d0 + v * E, D);
+            if (AL == ROWS_PIECES && d0 + E * DU > D)
+#pragma unroll
+                for (int v = 0; v < DU; ++v) {
+#pragma unroll
+                    for (int r = 0; r < JU; ++r) cf[r][v] = frag_place<T>(cf[r][v], d0 + v * E, D);
+#pragma unroll
+                    for (int u = 0; u < P; ++u) xf[u][v] = frag_place<T>(xf[u][v], d0 + v * E, D);
+                }
 #pragma unroll
             for (int v = 0; v < DU; ++v) {
                 // aligned rows hold whole fragments: a fragment is inside the row or (clamped copy)
                 // skipped as a whole, a wave-uniform decision; otherwise elements are masked one by one
-                if (ALIGNED && d0 + v * E >= D) continue;
+                if (AL == ROWS_ALIGNED && d0 + v * E >= D) continue;
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    const bool keep = ALIGNED || d0 + v * E + e < D;
+                    const bool keep = AL == ROWS_ALIGNED || d0 + v * E + e < D;
                     double cd[JU];
 #pragma unroll
                     for (int r = 0; r < JU; ++r) cd[r] = (double)cf[r][v][e];
@@ -770,13 +790,13 @@ __device__ __forceinline__ void refine_batch(const T *__restrict__ X, const T *_
     refine_settle<T, P>(best, bj, wl, first, np, labels, mindist, sh_best, sh_j);
 }
 
-// The same for aligned rows of 16 fragments and more: L lanes share a centroid row (8, or the whole
+// The same for rows of 16 fragments and more: L lanes share a centroid row (8, or the whole
 // wave from 128 fragments on), each taking every L-th 16-byte fragment.  With a thread per row a
 // load instruction touches 64 different rows - 64 requests to the vector cache, a whole line read
 // for each 16 bytes used - and the kernel's time was those requests (2^18 x 128, K = 256: 12 us
 // for a few hundred points); here an instruction reads runs of 128 bytes and more.  The L partial
 // sums of a row are added by the same tree for every row, so identical centroids still tie exactly.
-template <typename T, int L, int P>
+template <typename T, int AL, int L, int P>
 __device__ __forceinline__ void refine_batch_wide(const T *__restrict__ X, const T *__restrict__ C, int D, int K,
                                                   const int32_t *__restrict__ wl, int first, int np,
                                                   int32_t *labels, T *mindist, double (*sh_best)[8], int (*sh_j)[8])
@@ -816,9 +836,9 @@ __device__ __forceinline__ void refine_batch_wide(const T *__restrict__ X, const
             for (int v = 0; v < DU; ++v) {
                 const int off = min(f0 + L * v, nfrag - 1) * E;
 #pragma unroll
-                for (int r = 0; r < JU; ++r) cf[r][v] = *reinterpret_cast<const F *>(c[r] + off);
+                for (int r = 0; r < JU; ++r) cf[r][v] = load_piece(c[r] + off);
 #pragma unroll
-                for (int u = 0; u < P; ++u) xf[u][v] = *reinterpret_cast<const F *>(x[u] + off);
+                for (int u = 0; u < P; ++u) xf[u][v] = load_piece(x[u] + off);
             }
 #pragma unroll
             for (int v = 0; v < DU; ++v) {
@@ -837,6 +857,17 @@ __device__ __forceinline__ void refine_batch_wide(const T *__restrict__ X, const
                 }
             }
         }
+        if (AL == ROWS_PIECES)  // the rest of the row: fewer features than a fragment
+            for (int d = nfrag * E + sub; d < D; d += L)
+#pragma unroll
+                for (int u = 0; u < P; ++u) {
+                    const double xd = (double)x[u][d];
+#pragma unroll
+                    for (int r = 0; r < JU; ++r) {
+                        const double diff = xd - (double)c[r][d];
+                        s[r][u] = fma(diff, diff, s[r][u]);
+                    }
+                }
 #pragma unroll
         for (int r = 0; r < JU; ++r) {  // j increases within a thread: first minimum kept
             const int j = j0 + ROWS * r;
@@ -854,7 +885,7 @@ __device__ __forceinline__ void refine_batch_wide(const T *__restrict__ X, const
     refine_settle<T, P>(best, bj, wl, first, np, labels, mindist, sh_best, sh_j);
 }
 
-template <typename T, bool ALIGNED, int JU, int L>
+template <typename T, int AL, int JU, int L>
 __global__ __launch_bounds__(256) void refine_kernel(const T *__restrict__ X, const T *__restrict__ C, int D, int K,
                                                      const int32_t *__restrict__ wl, const int32_t *__restrict__ wl_count,
                                                      int32_t *labels, T *mindist, ftk_ft_stats *stats,
@@ -872,22 +903,22 @@ __global__ __launch_bounds__(256) void refine_kernel(const T *__restrict__ X, co
         const int np = min(bs, count - first);
         if constexpr (L > 1) {
             if (bs == 1)
-                refine_batch_wide<T, L, 1>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch_wide<T, AL, L, 1>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
             else if (bs == 2)
-                refine_batch_wide<T, L, 2>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch_wide<T, AL, L, 2>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
             else if (bs == 4)
-                refine_batch_wide<T, L, 4>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch_wide<T, AL, L, 4>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
             else
-                refine_batch_wide<T, L, 8>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch_wide<T, AL, L, 8>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
         } else {
             if (bs == 1)
-                refine_batch<T, ALIGNED, JU, 1>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch<T, AL, JU, 1>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
             else if (bs == 2)
-                refine_batch<T, ALIGNED, (JU > 4 ? 4 : JU), 2>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch<T, AL, (JU > 4 ? 4 : JU), 2>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
             else if (bs == 4)
-                refine_batch<T, ALIGNED, (JU > 2 ? 2 : JU), 4>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch<T, AL, (JU > 2 ? 2 : JU), 4>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
             else
-                refine_batch<T, ALIGNED, (JU > 2 ? 2 : JU), 8>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
+                refine_batch<T, AL, (JU > 2 ? 2 : JU), 8>(X, C, D, K, wl, first, np, labels, mindist, sh_best, sh_j);
         }
     }
     if (stats && blockIdx.x == 0) {
@@ -943,23 +974,25 @@ static ftk_status launch_generic_t(const AssignCall &c, const AssignPlan &p, con
     a.ft_mode = (int)c.ft;
     a.ft_coef = p.ft_coef;
     a.widen_coef = c.ft == FTK_FT_STRICT ? 0.5 * a.ft_coef : 0.0;
-    const bool aligned = (c.D % Mma<T>::E == 0) && ((uintptr_t)c.X % 16 == 0) && ((uintptr_t)c.C % 16 == 0);
+    const int rows = row_access(c.X, c.C, c.D, sizeof(T));
     const bool ft = c.ft != FTK_FT_OFF;
     dim3 grid((unsigned)p.workgroups), block(256);
     // whole stages and whole chunks: the condition-free stage loop
     // (and 32-bit byte offsets inside C and inside a workgroup's block of rows)
-    const bool full = aligned && c.D % (8 * p.DQ) == 0 && c.K % p.KC == 0 &&
+    const bool full = rows == ROWS_ALIGNED && c.D % (8 * p.DQ) == 0 && c.K % p.KC == 0 &&
                       (double)c.K * c.D * sizeof(T) < 4.0e9 && (double)p.points_per_wg * c.D * sizeof(T) < 4.0e9;
 #define FTK_LAUNCH_GEN(KV, AL, F, FU) \
     hipLaunchKernelGGL((assign_generic_kernel<T, KV, AL, F, FU>), grid, block, p.lds_bytes, st, a)
 #define FTK_LAUNCH_GEN_K(KV)                          \
     do {                                              \
-        if (full && ft) FTK_LAUNCH_GEN(KV, true, true, true);          \
-        else if (full) FTK_LAUNCH_GEN(KV, true, false, true);          \
-        else if (aligned && ft) FTK_LAUNCH_GEN(KV, true, true, false); \
-        else if (aligned) FTK_LAUNCH_GEN(KV, true, false, false);      \
-        else if (ft) FTK_LAUNCH_GEN(KV, false, true, false);           \
-        else FTK_LAUNCH_GEN(KV, false, false, false);                  \
+        if (full && ft) FTK_LAUNCH_GEN(KV, ROWS_ALIGNED, true, true);                          \
+        else if (full) FTK_LAUNCH_GEN(KV, ROWS_ALIGNED, false, true);                          \
+        else if (rows == ROWS_ALIGNED && ft) FTK_LAUNCH_GEN(KV, ROWS_ALIGNED, true, false);    \
+        else if (rows == ROWS_ALIGNED) FTK_LAUNCH_GEN(KV, ROWS_ALIGNED, false, false);         \
+        else if (rows == ROWS_PIECES && ft) FTK_LAUNCH_GEN(KV, ROWS_PIECES, true, false);      \
+        else if (rows == ROWS_PIECES) FTK_LAUNCH_GEN(KV, ROWS_PIECES, false, false);           \
+        else if (ft) FTK_LAUNCH_GEN(KV, ROWS_ELEMENTS, true, false);                           \
+        else FTK_LAUNCH_GEN(KV, ROWS_ELEMENTS, false, false);                                  \
     } while (0)
     if (p.KT == 8) FTK_LAUNCH_GEN_K(8);
     else if (p.KT == 4) FTK_LAUNCH_GEN_K(4);
@@ -981,21 +1014,24 @@ ftk_status launch_assign_generic(const AssignCall &c, const AssignPlan &p, const
 template <typename T>
 static void launch_refine_t(const AssignCall &c, const Workspace &w, int n_wg, hipStream_t st)
 {
-    const bool aligned = (c.D % Mma<T>::E == 0) && ((uintptr_t)c.X % 16 == 0) && ((uintptr_t)c.C % 16 == 0);
+    const int rows = row_access(c.X, c.C, c.D, sizeof(T));
     dim3 grid(1024), block(256);
 #define FTK_LAUNCH_REFINE(AL, JU, LV)                                                                      \
     hipLaunchKernelGGL((refine_kernel<T, AL, JU, LV>), grid, block, 0, st, (const T *)c.X, (const T *)c.C, \
                        c.D, c.K, w.wl, w.wl_count, c.labels, (T *)c.mindist, c.stats, w.wg_refined, n_wg)
 #define FTK_LAUNCH_REFINE_J(JU)                   \
     do {                                          \
-        if (aligned) FTK_LAUNCH_REFINE(true, JU, 1); \
-        else FTK_LAUNCH_REFINE(false, JU, 1);        \
+        if (rows == ROWS_ALIGNED) FTK_LAUNCH_REFINE(ROWS_ALIGNED, JU, 1); \
+        else if (rows == ROWS_PIECES) FTK_LAUNCH_REFINE(ROWS_PIECES, JU, 1);        \
+        else FTK_LAUNCH_REFINE(ROWS_ELEMENTS, JU, 1);        \
     } while (0)
     // sixteen 16-byte loads in flight per thread: short rows leave room for more rows at once
     const int nfrag = (int)ceil_div(c.D, Mma<T>::E);
-    // long aligned rows: lanes share a row (see refine_batch_wide)
-    if (aligned && nfrag >= 128) FTK_LAUNCH_REFINE(true, 1, 64);
-    else if (aligned && nfrag >= 16) FTK_LAUNCH_REFINE(true, 1, 8);
+    // long rows: lanes share a row (see refine_batch_wide)
+    if (rows == ROWS_ALIGNED && nfrag >= 128) FTK_LAUNCH_REFINE(ROWS_ALIGNED, 1, 64);
+    else if (rows == ROWS_ALIGNED && nfrag >= 16) FTK_LAUNCH_REFINE(ROWS_ALIGNED, 1, 8);
+    else if (nfrag >= 128) FTK_LAUNCH_REFINE(ROWS_PIECES, 1, 64);
+    else if (nfrag >= 16) FTK_LAUNCH_REFINE(ROWS_PIECES, 1, 8);
     else if (nfrag <= 2) FTK_LAUNCH_REFINE_J(8);
     else if (nfrag <= 4) FTK_LAUNCH_REFINE_J(4);
     else if (nfrag <= 8) FTK_LAUNCH_REFINE_J(2);

@@ -176,7 +176,7 @@ __global__ __launch_bounds__(MIDD_WAVES * 64, 2) void assign_midd_kernel(MidArgs
                 if (p >= a.N) p = a.N - 1;
                 const float *xrow = a.X + p * D;
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) xf[pt][q] = load_frag<float, true>(xrow, 8 * q + 4 * g, D);
+                for (int q = 0; q < NQ; ++q) xf[pt][q] = load_frag<float, ROWS_ALIGNED>(xrow, 8 * q + 4 * g, D);
             }
         };
         auto start_points = [&]() {  // norms, thresholds, empty records
@@ -437,7 +437,7 @@ __global__ __launch_bounds__(MIDD_WAVES * 64, 2) void assign_midd_kernel(MidArgs
                     const float *c = a.C + (size_t)jr * D;
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
-                        const floatx4 cv = load_frag<float, true>(c, 8 * q + 4 * g, D);
+                        const floatx4 cv = load_frag<float, ROWS_ALIGNED>(c, 8 * q + 4 * g, D);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float t = xf[pt][q][e] - cv[e];

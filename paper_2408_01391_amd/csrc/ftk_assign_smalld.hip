@@ -231,7 +231,7 @@ __global__ __launch_bounds__(smalld_waves(NQ, FT) * 64, smalld_min_wgs(NQ, FT)) 
             float s = 0.f;
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                xf[pt][q] = load_frag<float, true>(xrow, 8 * q + 4 * g, D);
+                xf[pt][q] = load_frag<float, ROWS_ALIGNED>(xrow, 8 * q + 4 * g, D);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) s = fmaf(xf[pt][q][e], xf[pt][q][e], s);
             }

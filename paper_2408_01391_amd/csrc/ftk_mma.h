@@ -76,22 +76,39 @@ struct Mma<double> {
     static __device__ __forceinline__ double huge() { return __builtin_huge_val(); }
 };
 
+// How rows are read: 16-byte pieces where rows and base are aligned to them; pieces at element alignment (global memory
+// takes those at the same rate), the last one of a row moved back into the row; element by element where a row is
+// shorter than a piece.  Pieces against elements, whole calls: 155948 x 209, K = 21, strict 70 / 167 us; 102957 x 102, K = 7
+// 26 / 53; 426483 x 126, K = 2 81 / 98.
+enum RowAccess : int { ROWS_ELEMENTS = 0, ROWS_ALIGNED = 1, ROWS_PIECES = 2 };
+typedef float floatx4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef double doublex2e __attribute__((ext_vector_type(2), aligned(8)));
+template <typename T>
+__device__ __forceinline__ typename Mma<T>::frag_t load_piece(const T *p)
+{
+    if constexpr (sizeof(T) == 4) return *reinterpret_cast<const floatx4e *>(p);
+    else return *reinterpret_cast<const doublex2e *>(p);
+}
+static inline int row_access(const void *a, const void *b, int D, size_t element)
+{
+    const int E = (int)(16 / element);
+    if (D % E == 0 && (uintptr_t)a % 16 == 0 && (uintptr_t)b % 16 == 0) return ROWS_ALIGNED;
+    return D >= E ? ROWS_PIECES : ROWS_ELEMENTS;
+}
+
 // E consecutive elements of a row starting at feature d0, zero beyond D.
-template <typename T, bool ALIGNED>
+template <typename T, int AL>
 __device__ __forceinline__ typename Mma<T>::frag_t load_frag(const T *row, int d0, int D)
 {
     using F = typename Mma<T>::frag_t;
+    constexpr int E = Mma<T>::E;
     F f;
-    if constexpr (ALIGNED) {
-        if (d0 < D) {
-            f = *reinterpret_cast<const F *>(row + d0);
-        } else {
-#pragma unroll
-            for (int e = 0; e < Mma<T>::E; ++e) f[e] = T(0);
-        }
+    if (AL == ROWS_ALIGNED ? d0 < D : (AL == ROWS_PIECES && d0 + E <= D)) {
+        if constexpr (AL == ROWS_ALIGNED) f = *reinterpret_cast<const F *>(row + d0);
+        else f = load_piece(row + d0);
     } else {
 #pragma unroll
-        for (int e = 0; e < Mma<T>::E; ++e) f[e] = (d0 + e < D) ? row[d0 + e] : T(0);
+        for (int e = 0; e < E; ++e) f[e] = (AL != ROWS_ALIGNED && d0 + e < D) ? row[d0 + e] : T(0);
     }
     return f;
 }
@@ -100,19 +117,38 @@ __device__ __forceinline__ typename Mma<T>::frag_t load_frag(const T *row, int d
 // beyond D come back as copies of valid elements of the same row (finite whenever the row is).
 // A load inside a branch would force the compiler to wait for every outstanding load at the next
 // use; callers either multiply the surplus elements by zero or clear them with frag_keep().
-template <typename T, bool ALIGNED>
+// ROWS_PIECES: a piece that was moved back goes to its place in frag_place(), once it has arrived.
+template <typename T, int AL>
 __device__ __forceinline__ typename Mma<T>::frag_t load_frag_clamped(const T *row, int d0, int D)
 {
     using F = typename Mma<T>::frag_t;
     constexpr int E = Mma<T>::E;
-    if constexpr (ALIGNED) {
+    if constexpr (AL == ROWS_ALIGNED) {
         return *reinterpret_cast<const F *>(row + min(d0, D - E));
+    } else if constexpr (AL == ROWS_PIECES) {
+        return load_piece(row + min(d0, D - E));
     } else {
         F f;
 #pragma unroll
         for (int e = 0; e < E; ++e) f[e] = row[min(d0 + e, D - 1)];
         return f;
     }
+}
+template <typename T>
+__device__ __forceinline__ typename Mma<T>::frag_t frag_place(typename Mma<T>::frag_t f, int d0, int D)
+{
+    const int back = d0 - (D - Mma<T>::E);  // elements it was moved back by, if positive
+    if constexpr (sizeof(T) == 4) {
+        const int s = back < 0 ? 0 : (back < 3 ? back : 3);
+        const bool one = (s & 1) != 0, two = (s & 2) != 0;
+        const float t0 = one ? f[1] : f[0], t1 = one ? f[2] : f[1], t2 = one ? f[3] : f[2];
+        f[0] = two ? t2 : t0;
+        f[1] = two ? f[3] : t1;
+        f[2] = t2;
+    } else {
+        f[0] = back > 0 ? f[1] : f[0];
+    }
+    return f;
 }
 
 // Keeps element e of a fragment fetched at feature d0 if `keep` and d0 + e < D, else zero.
@@ -130,21 +166,25 @@ __device__ __forceinline__ typename Mma<T>::frag_t frag_keep(typename Mma<T>::fr
 // Features are added in index order into one accumulator (so two candidates evaluated here
 // always compare consistently, and identical centroids tie exactly); the loads are issued
 // several fragments ahead, since their latency - not the arithmetic - is what a lane waits for.
-template <typename T, bool ALIGNED>
+template <typename T, int AL>
 __device__ __forceinline__ double exact_sqdist(const T *x, const T *c, int D)
 {
     constexpr int E = Mma<T>::E;
     double s = 0.0;
-#pragma unroll 4
-    for (int d0 = 0; d0 < D; d0 += E) {
-        const typename Mma<T>::frag_t xf = load_frag<T, ALIGNED>(x, d0, D);
-        const typename Mma<T>::frag_t cf = load_frag<T, ALIGNED>(c, d0, D);
+    auto add = [&](const typename Mma<T>::frag_t &xf, const typename Mma<T>::frag_t &cf) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const double diff = (double)xf[e] - (double)cf[e];
             s = fma(diff, diff, s);
         }
+    };
+    const int whole = AL == ROWS_PIECES ? D - D % E : D;
+#pragma unroll 4
+    for (int d0 = 0; d0 < whole; d0 += E) {
+        if constexpr (AL == ROWS_PIECES) add(load_piece(x + d0), load_piece(c + d0));
+        else add(load_frag<T, AL>(x, d0, D), load_frag<T, AL>(c, d0, D));
     }
+    if (AL == ROWS_PIECES && whole < D) add(load_frag<T, AL>(x, whole, D), load_frag<T, AL>(c, whole, D));
     return s;
 }
 
