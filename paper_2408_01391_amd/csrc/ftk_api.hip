@@ -755,7 +755,7 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
     hipStream_t st = (hipStream_t)hip_stream;
     // whole rows of 16 bytes keep every batch as aligned as X itself
     const bool aligned16 = ((uintptr_t)X % 16 == 0) && ((uintptr_t)C % 16 == 0) && ((size_t)D * esz) % 16 == 0;
-    const BatchedUpdatePlan ub = plan_update_batched(dtype, aligned16 ? X : (const void *)1, N, batch_rows, D, K);
+    const BatchedUpdatePlan ub = plan_update_batched(dtype, N, batch_rows, D, K);
     if (!ub.ok) {
         set_error("internal: update tables of a batch exceed the workspace bound (chunks %d)", ub.chunks);
         return FTK_EINVAL;
@@ -809,7 +809,8 @@ ftk_status ftk_update_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K,
         set_error("out is NULL");
         return FTK_EINVAL;
     }
-    update_geometry(dtype, rows_aligned16 != 0, N, D, K, out);
+    (void)rows_aligned16;  // both take the same kernel
+    update_geometry(dtype, N, D, K, out);
     return FTK_OK;
 }
 

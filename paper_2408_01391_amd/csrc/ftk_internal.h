@@ -161,10 +161,10 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
 // update accumulated over several launches (batches of rows), finished by one averaging pass
 struct BatchedUpdatePlan {
     int Ks, Ds, nks, nds, tx_log2, chunks;
-    bool aligned, ok;
+    bool pieces, ok;
     int64_t scale_rows;
 };
-BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, const void *X, int64_t N, int64_t batch_rows, int D, int K);
+BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, int64_t N, int64_t batch_rows, int D, int K);
 ftk_status launch_update_batch(ftk_dtype dtype, const void *Xb, const int32_t *labels_b, int64_t nb, int D, int K,
                                const double *absmax, const Workspace &w, const BatchedUpdatePlan &b, bool first,
                                hipStream_t st);
@@ -172,7 +172,7 @@ ftk_status launch_update_batched_finalize(ftk_dtype dtype, int D, int K, const d
                                           int32_t *counts, const Workspace &w, const BatchedUpdatePlan &b,
                                           hipStream_t st);
 ftk_status launch_zero_ints(int32_t *p, int n, hipStream_t st);
-void update_geometry(ftk_dtype dtype, bool aligned16, int64_t N, int D, int K, ftk_geometry *out);
+void update_geometry(ftk_dtype dtype, int64_t N, int D, int K, ftk_geometry *out);
 ftk_status launch_gather_rows(ftk_dtype dtype, const void *X, int D, const int64_t *idx_dev, int K,
                               void *C, hipStream_t st);
 ftk_status launch_sum_to_double(ftk_dtype dtype, const void *v, int64_t n, double *partials,

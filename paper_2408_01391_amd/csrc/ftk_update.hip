@@ -32,7 +32,7 @@ struct UpdatePlan {
     int Ks, Ds, nks, nds, tx_log2;
     int64_t rows_per_chunk;
     int chunks;
-    bool aligned;
+    bool pieces;  // rows hold 16-byte pieces (at element alignment, the last one moved back into the row)
 };
 
 // Row chunks of the LDS path never exceed UPD_TARGET_WGS or one per 64 rows; with S
@@ -43,8 +43,11 @@ int64_t update_slab_chunks_max(int64_t N)
     const int64_t by_rows = ceil_div(N, 64);
     return by_rows < UPD_TARGET_WGS ? (by_rows < 1 ? 1 : by_rows) : UPD_TARGET_WGS;
 }
-// walkers of the label-sorted path: one per RED_ROWS_PER_LANE_MIN rows at most
-int64_t update_walkers_max(int64_t N) { return ceil_div(N, 64) + 1; }
+// rows of a walker of the label-sorted path: few points in rows of few pieces leave too few waves otherwise (100000 x 33,
+// K = 2000, strict 57 us with 64 rows)
+constexpr int RED_ROWS_PER_LANE_MAX = 256;
+static int red_rows_min(int64_t N) { return N < 262144 ? 32 : 64; }
+int64_t update_walkers_max(int64_t N) { return ceil_div(N, red_rows_min(N)) + 1; }
 int64_t update_slab_cells_max(int64_t N, int D, int K)
 {
     const int64_t cells = (int64_t)K * D;
@@ -54,11 +57,11 @@ int64_t update_slab_cells_max(int64_t N, int D, int K)
     return v > cells ? v : cells;
 }
 
-static UpdatePlan plan_update(ftk_dtype dtype, const void *X, int64_t N, int D, int K)
+static UpdatePlan plan_update(ftk_dtype dtype, int64_t N, int D, int K)
 {
     UpdatePlan u;
     const int E = dtype == FTK_F32 ? 4 : 2;
-    u.aligned = (D % E == 0) && ((uintptr_t)X % 16 == 0);
+    u.pieces = D >= E;
     const int line = dtype == FTK_F32 ? 32 : 16;  // features per 128-byte line
     if ((int64_t)K * D <= UPD_CELLS && upd_lds(K, D) <= UPD_LDS) {
         u.Ks = K;
@@ -67,7 +70,7 @@ static UpdatePlan plan_update(ftk_dtype dtype, const void *X, int64_t N, int D, 
         int ds = UPD_CELLS / K;          // widest feature slice with all clusters resident
         if (ds < line) ds = line;        // never read less than one line per row
         if (ds > D) ds = D;
-        if (u.aligned) ds = ds / E * E;
+        if (u.pieces && ds < D) ds = ds / E * E;
         if (ds < 1) ds = 1;
         u.Ds = ds;
         int ks = UPD_CELLS / ds;
@@ -78,7 +81,7 @@ static UpdatePlan plan_update(ftk_dtype dtype, const void *X, int64_t N, int D, 
     u.nds = (int)ceil_div(D, u.Ds);
     u.nks = (int)ceil_div(K, u.Ks);
     const int slices = u.nds * u.nks;
-    const int ppr = u.aligned ? (u.Ds + E - 1) / E : u.Ds;  // pieces per row slice
+    const int ppr = u.pieces ? (u.Ds + E - 1) / E : u.Ds;  // pieces per row slice
     int l2 = 0;
     while ((1 << l2) < ppr && l2 < 8) ++l2;
     u.tx_log2 = l2;
@@ -185,14 +188,14 @@ __device__ __forceinline__ void add_stat(ftk_ft_stats *stats, int field, int n)
 }
 enum { STAT_INJECTED = 1, STAT_DETECTED = 2, STAT_CORRECTED = 3, STAT_RECOMPUTED = 4, STAT_UNCORRECTABLE = 5 };
 
-template <typename T, bool ALIGNED, bool DMR>
+template <typename T, int AL, bool DMR>
 __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
     const T *X, const int32_t *labels, int64_t N, int D, int K, const double *absmax_p,
     long long *slabs, int32_t *cslabs, int Ks, int Ds, int nds, int tx_log2,
     int64_t rows_per_chunk, int64_t scale_rows, int accumulate, UpdateFtArgs ft)
 {
     using F = typename Mma<T>::frag_t;
-    constexpr int E = ALIGNED ? Mma<T>::E : 1;
+    constexpr int E = AL != ROWS_ELEMENTS ? Mma<T>::E : 1;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     unsigned long long *cell = reinterpret_cast<unsigned long long *>(lds_raw);
     // table rows are padded by one cell: a row of Ds 8-byte cells is a whole number of LDS bank
@@ -220,6 +223,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
     const int TX = 1 << tx_log2, TY = UPD_THREADS >> tx_log2;
     const int tx = tid & (TX - 1), ty = tid >> tx_log2;
     const int ppr = (dn + E - 1) / E;
+    const bool ragged = AL == ROWS_PIECES && dn % E != 0;  // the last piece of a row holds fewer features
     const int64_t r0 = (int64_t)blockIdx.x * rows_per_chunk;
     const int64_t r1 = r0 + rows_per_chunk < N ? r0 + rows_per_chunk : N;
     const int nf = stage_faults(ft, (int)blockIdx.x, sh_faults, &sh_nf, UPD_THREADS);
@@ -245,17 +249,49 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
         // before any LDS atomic, so several HBM requests per thread are in flight
         constexpr int UNR = 4;
         // When the slice holds every cluster the point loads do not depend on the labels and go out
-        // together with them (ALLK); otherwise only rows whose label falls into the slice are read,
-        // one memory latency after their labels.
+        // together with them (ALLK).  Otherwise only rows whose label falls into the slice are read: those of a step are
+        // requested while the rows of the step before are added, their labels one step earlier still (10^6 x 11, K = 4000
+        // 105 us a call without, 95 with; of ALLK slices, which the LDS atomics bound, 2^18 x 128, K = 256 42 without, 44 with; rows of
+        // up to three features 38 without, 41 with).
         auto pass = [&](auto allk_tag) {
         constexpr bool ALLK = decltype(allk_tag)::value;
-        for (int64_t row0 = r0 + ty; row0 < r1; row0 += (int64_t)TY * UNR, ++step) {
-            int lab[UNR];
-            bool ok[UNR];
+        constexpr bool AHEAD = !ALLK && AL != ROWS_ELEMENTS;
+        const int64_t stride = (int64_t)TY * UNR;
+        auto fetch_labels = [&](int64_t row0, int (&lab)[UNR]) {
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
                 const int64_t row = row0 + (int64_t)u * TY;
                 lab[u] = row < r1 ? labels[row] - k0 : -1;
+            }
+        };
+        auto fetch_rows = [&](int64_t row0, const int (&lab)[UNR], int pc, F (&f)[UNR]) {
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const int64_t row = row0 + (int64_t)u * TY;
+                if (ALLK ? row < r1 : (unsigned)lab[u] < (unsigned)kn) {
+                    if constexpr (AL == ROWS_ALIGNED) f[u] = *reinterpret_cast<const F *>(X + row * D + d0 + pc * E);
+                    else if constexpr (AL == ROWS_PIECES) f[u] = load_piece(X + (row * D + min(d0 + pc * E, D - E)));
+                    else f[u][0] = X[row * D + d0 + pc];
+                }
+            }
+        };
+        const int p0 = min(tx, ppr - 1);  // (lanes beyond the row's pieces request its last one)
+        int lab[UNR], lab_n[UNR];
+        F f[UNR], f_n[UNR];
+        if constexpr (AHEAD) {
+            fetch_labels(r0 + ty, lab);
+            fetch_rows(r0 + ty, lab, p0, f);
+            fetch_labels(r0 + ty + stride, lab_n);
+        }
+        for (int64_t row0 = r0 + ty; row0 < r1; row0 += stride, ++step) {
+            bool ok[UNR];
+            int lab_2[UNR];
+            if constexpr (!AHEAD) {
+                fetch_labels(row0, lab);
+                fetch_rows(row0, lab, p0, f);
+            } else {
+                fetch_rows(row0 + stride, lab_n, p0, f_n);
+                fetch_labels(row0 + 2 * stride, lab_2);
             }
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
@@ -273,31 +309,27 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
             int flip_e = -1;
             if (nf > 0 && attempt == 0) {
                 for (int i = 0; i < nf; ++i) {
-                    const ftk_fault f = sh_faults[i];
+                    const ftk_fault flt = sh_faults[i];
                     // the addressed thread, moved onto the lane of its row that owns a piece
-                    const int ft_id = (int)(f.wave % (UPD_THREADS / 64)) * 64 + (int)(f.lane & 63);
-                    if ((ft_id >> tx_log2) == ty && ((ft_id & (TX - 1)) % ppr) == tx && (int)f.tile == step) {
-                        flip[f.reg % UNR] = 1ull << (f.bit & 63);
-                        flip_e = (int)((f.reg / UNR) % E);
+                    const int ft_id = (int)(flt.wave % (UPD_THREADS / 64)) * 64 + (int)(flt.lane & 63);
+                    if ((ft_id >> tx_log2) == ty && ((ft_id & (TX - 1)) % ppr) == tx && (int)flt.tile == step) {
+                        flip[flt.reg % UNR] = 1ull << (flt.bit & 63);
+                        flip_e = (int)((flt.reg / UNR) % E);
                     }
                 }
             }
             for (int pc = tx; pc < ppr; pc += TX) {
-                F f[UNR];
+                if (pc != tx) fetch_rows(row0, lab, pc, f);
+                if (AL == ROWS_PIECES && ragged)
 #pragma unroll
-                for (int u = 0; u < UNR; ++u) {
-                    const int64_t row = row0 + (int64_t)u * TY;
-                    if (ALLK ? row < r1 : ok[u]) {
-                        if constexpr (ALIGNED) f[u] = *reinterpret_cast<const F *>(X + row * D + d0 + pc * E);
-                        else f[u][0] = X[row * D + d0 + pc];
-                    }
-                }
+                    for (int u = 0; u < UNR; ++u) f[u] = frag_place<T>(f[u], d0 + pc * E, D);
 #pragma unroll
                 for (int u = 0; u < UNR; ++u) {
                     if (ok[u]) {
-                        unsigned long long *dst = cell + (size_t)lab[u] * Dp + pc * E;
+                        unsigned long long *dst = cell + lab[u] * Dp + pc * E;
 #pragma unroll
                         for (int e = 0; e < E; ++e) {
+                            if (AL == ROWS_PIECES && ragged && pc * E + e >= dn) break;
                             const double x = (double)f[u][e];
                             long long v = to_fixed(x, scale);
                             if constexpr (DMR) {
@@ -318,6 +350,13 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
                     }
                 }
             }
+            if constexpr (AHEAD)
+#pragma unroll
+                for (int u = 0; u < UNR; ++u) {
+                    lab[u] = lab_n[u];
+                    lab_n[u] = lab_2[u];
+                    f[u] = f_n[u];
+                }
         }
         };
         if (kn == K)
@@ -376,35 +415,38 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
 
 // Sum of the per-chunk tables and averaging pass ("the last kernel", Section 3.1.1) in one:
 // C_j = sum_j / count_j, rounded once; a cluster without points keeps its previous centroid.
-// A workgroup owns RF_CELLS consecutive cells; its RF_GROUPS thread groups each add every
-// RF_GROUPS-th table (coalesced reads, several in flight), the partial sums meet in LDS.
+// A workgroup owns consecutive cells; each of its thread groups adds every (number of groups)-th
+// table (coalesced reads, several in flight), the partial sums meet in LDS.
 // fp64 data: the tables were scaled for one chunk's rows, so the sum over chunks is carried in
 // two limbs.
-constexpr int RF_CELLS = 32, RF_GROUPS = 32;
+// 32 groups, or fewer where there are fewer tables (8117 x 680, K = 1335: one table of 907 800 cells, 112 us with 32 groups).
+constexpr int RF_THREADS = 1024;
+static int reduce_groups(int chunks) { return chunks <= 1 ? 1 : (chunks <= 2 ? 2 : (chunks <= 4 ? 4 : (chunks <= 8 ? 8 : 32))); }
 // DMR: two sets of table sums are kept and compared before the partial sums are combined; a
 // mismatch is settled by a third pass.
-template <typename T, bool DMR>
-__global__ __launch_bounds__(RF_CELLS * RF_GROUPS) void update_reduce_finalize_kernel(
+template <typename T, bool DMR, int GROUPS>
+__global__ __launch_bounds__(RF_THREADS) void update_reduce_finalize_kernel(
     const long long *slabs, const int32_t *cslabs, int chunks, int64_t scale_rows, int D,
     int K, const double *absmax_p, T *C, int32_t *counts, ftk_ft_stats *stats)
 {
     constexpr bool TWO_LIMB = sizeof(T) == 8;
-    __shared__ long long sh_hi[RF_GROUPS][RF_CELLS], sh_lo[RF_GROUPS][RF_CELLS];
-    __shared__ int sh_cnt[RF_GROUPS][RF_CELLS];
-    const int ci = threadIdx.x % RF_CELLS, grp = threadIdx.x / RF_CELLS;
-    const int64_t cells = (int64_t)K * D;
-    const int64_t cell0 = (int64_t)blockIdx.x * RF_CELLS;
+    __shared__ long long sh_hi[RF_THREADS], sh_lo[RF_THREADS];
+    __shared__ int sh_cnt[RF_THREADS];
+    constexpr int wg_cells = RF_THREADS / GROUPS;
+    const int ci = threadIdx.x % wg_cells, grp = threadIdx.x / wg_cells;
+    const int64_t cells = (int64_t)K * D;  // at most 2^31
+    const int64_t cell0 = (int64_t)blockIdx.x * wg_cells;
     const int64_t cell = cell0 + ci;
-    // member counts of the rows this workgroup touches (at most RF_CELLS): thread ci <-> row
-    const int row0 = (int)(cell0 / D);
-    const int64_t last_cell = cell0 + RF_CELLS - 1 < cells ? cell0 + RF_CELLS - 1 : cells - 1;
-    const int nrows = (int)(last_cell / D) - row0 + 1;
+    // member counts of the rows this workgroup touches (at most wg_cells): thread ci <-> row
+    const int row0 = (int)((unsigned)cell0 / (unsigned)D);
+    const int64_t last_cell = cell0 + wg_cells - 1 < cells ? cell0 + wg_cells - 1 : cells - 1;
+    const int nrows = (int)((unsigned)last_cell / (unsigned)D) - row0 + 1;
     // one pass over the tables; under DMR every value loaded is added into two sets of sums (the
     // second through an opaque copy), which are compared before the partial sums are combined
     int c = 0, c2 = 0, detected = 0;
     long long hi = 0, lo = 0, hi2 = 0, lo2 = 0;
 #pragma unroll 4
-    for (int ch = grp; ch < chunks; ch += RF_GROUPS) {
+    for (int ch = grp; ch < chunks; ch += GROUPS) {
         if (ci < nrows) {
             int n = cslabs[(int64_t)ch * K + row0 + ci];
             c += n;
@@ -436,7 +478,7 @@ __global__ __launch_bounds__(RF_CELLS * RF_GROUPS) void update_reduce_finalize_k
         if (hi != hi2 || lo != lo2 || c != c2) {  // settle by a third, separate pass
             long long hi3 = 0, lo3 = 0;
             int c3 = 0;
-            for (int ch = grp; ch < chunks; ch += RF_GROUPS) {
+            for (int ch = grp; ch < chunks; ch += GROUPS) {
                 if (ci < nrows) c3 += cslabs[(int64_t)ch * K + row0 + ci];
                 if (cell < cells) {
                     const long long v = slabs[(int64_t)ch * cells + cell];
@@ -454,17 +496,18 @@ __global__ __launch_bounds__(RF_CELLS * RF_GROUPS) void update_reduce_finalize_k
             detected += 1;
         }
     }
-    sh_hi[grp][ci] = hi;
-    sh_lo[grp][ci] = lo;
-    sh_cnt[grp][ci] = c;
+    sh_hi[threadIdx.x] = hi;
+    sh_lo[threadIdx.x] = lo;
+    sh_cnt[threadIdx.x] = c;
     __syncthreads();
     if (grp == 0) {
-        for (int g2 = 1; g2 < RF_GROUPS; ++g2) {
-            hi += sh_hi[g2][ci];
-            lo += sh_lo[g2][ci];
-            c += sh_cnt[g2][ci];
+#pragma unroll
+        for (int g2 = 1; g2 < GROUPS; ++g2) {
+            hi += sh_hi[g2 * wg_cells + ci];
+            lo += sh_lo[g2 * wg_cells + ci];
+            c += sh_cnt[g2 * wg_cells + ci];
         }
-        sh_cnt[0][ci] = c;  // row totals, read back below by the threads of other cells
+        sh_cnt[ci] = c;  // row totals, read back below by the threads of other cells
     }
     __syncthreads();
     if (grp == 0) {
@@ -474,7 +517,7 @@ __global__ __launch_bounds__(RF_CELLS * RF_GROUPS) void update_reduce_finalize_k
             if (first >= cell0 && first <= last_cell) counts[row0 + ci] = c;
         }
         if (cell < cells) {
-            const int n = sh_cnt[0][(int)(cell / D) - row0];
+            const int n = sh_cnt[(int)((unsigned)cell / (unsigned)D) - row0];
             if (n > 0) {
                 const double inv = 1.0 / fixed_point_scale(*absmax_p, scale_rows);
                 C[cell] = fixed_point_mean<T, DMR>(hi, lo, inv, n, &detected);
@@ -596,8 +639,6 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(const int32_t *labels
     }
 }
 
-constexpr int RED_ROWS_PER_LANE_MAX = 256;  // most sorted positions one walker covers
-constexpr int RED_ROWS_PER_LANE_MIN = 64;
 
 // Walk the sorted order.  lpr_log2: lanes per row (power of two); a wave holds 64/lpr "walkers"
 // (row groups), each covering rows_per_lane consecutive sorted positions; blockIdx.y selects the
@@ -610,7 +651,7 @@ constexpr int RED_ROWS_PER_LANE_MIN = 64;
 //     after it (then it is the last): the partial sum goes to the walker's slot 0 resp. 1,
 //     tagged with the label, and the averaging kernel adds the slots of the walkers a segment
 //     touches.  (cursor[k] is the end of segment k after the scatter, cursor[K] their total.)
-template <typename T, bool ALIGNED, bool DMR, bool NT = false>
+template <typename T, int AL, bool DMR, bool NT = false>
 __global__ __launch_bounds__(256) void sorted_reduce_kernel(const T *X, const int32_t *sorted_idx,
                                                             const int32_t *sorted_lab, const int32_t *cursor,
                                                             int K, int64_t N, int D, int lpr_log2, int rows_per_lane,
@@ -619,7 +660,8 @@ __global__ __launch_bounds__(256) void sorted_reduce_kernel(const T *X, const in
                                                             int32_t *slot_lab, UpdateFtArgs ft)
 {
     using F = typename Mma<T>::frag_t;
-    constexpr int E = ALIGNED ? Mma<T>::E : 1;
+    using FE = std::conditional_t<sizeof(T) == 4, floatx4e, doublex2e>;
+    constexpr int E = AL != ROWS_ELEMENTS ? Mma<T>::E : 1;
     constexpr bool TWO_LIMB = sizeof(T) == 8;
     constexpr int UNR = 8;
     __shared__ int sh_nf;
@@ -630,6 +672,8 @@ __global__ __launch_bounds__(256) void sorted_reduce_kernel(const T *X, const in
     const int group = lane >> lpr_log2, piece = lane & (lpr - 1);
     const int d0 = (blockIdx.y * 64 + piece) * E;  // first feature of this lane
     const bool lane_on = d0 < D;
+    const int off = AL == ROWS_PIECES ? min(d0, D - E) : d0;
+    const bool ragged = AL == ROWS_PIECES && D % E != 0 && blockIdx.y + 1 == gridDim.y;  // the last piece of a row is moved back
     // fp32: one limb scaled for the whole of N; fp64: scaled for one walker's rows, two limbs later
     const double scale = fixed_point_scale(*absmax_p, TWO_LIMB ? RED_ROWS_PER_LANE_MAX : N);
     const double scale2 = dmr_copy(scale);
@@ -739,12 +783,17 @@ __global__ __launch_bounds__(256) void sorted_reduce_kernel(const T *X, const in
                 // NT: X far larger than the 256 MB memory-side cache and read exactly once - streaming
                 // (non-temporal) loads then sustain 12-15 % more than ordinary ones on this device;
                 // for an X that the preceding assignment left in that cache they are slower
-                if constexpr (ALIGNED && NT) f[u] = __builtin_nontemporal_load(reinterpret_cast<const F *>(X + row_n[u] * D + d0));
-                else if constexpr (ALIGNED) f[u] = *reinterpret_cast<const F *>(X + row_n[u] * D + d0);
+                if constexpr (AL == ROWS_ALIGNED && NT) f[u] = __builtin_nontemporal_load(reinterpret_cast<const F *>(X + row_n[u] * D + d0));
+                else if constexpr (AL == ROWS_ALIGNED) f[u] = *reinterpret_cast<const F *>(X + row_n[u] * D + d0);
+                else if constexpr (AL == ROWS_PIECES && NT) f[u] = __builtin_nontemporal_load(reinterpret_cast<const FE *>(X + (row_n[u] * D + off)));
+                else if constexpr (AL == ROWS_PIECES) f[u] = load_piece(X + (row_n[u] * D + off));
                 else f[u][0] = X[row_n[u] * D + d0];
             }
         }
         fetch_keys(s0 + UNR);
+        if (AL == ROWS_PIECES && ragged)  // (what is beyond D is a copy of other elements, and not stored)
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) f[u] = frag_place<T>(f[u], d0, D);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             if (lab[u] >= 0) {
@@ -1015,6 +1064,7 @@ __device__ __forceinline__ BucketShare bucket_share(const int32_t *totals, const
 
 // One workgroup's part of a bucket: table in LDS, then slot `blockIdx.x` of the slabs.  TX lanes share a
 // row; UNR rows per thread in flight, the entries of the next ones on their way.
+template <int AL>
 __global__ __launch_bounds__(BK_THREADS) void bucket_accumulate_kernel(
     const float *X, const uint32_t *entries, const int32_t *bounds, const int32_t *totals, int64_t N, int D, int K,
     BucketPlan b, const double *absmax_p, long long *slabs, int32_t *cslabs)
@@ -1054,7 +1104,12 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_accumulate_kernel(
     const double scale = fixed_point_scale(*absmax_p, N);
     const int TX = 1 << b.tx_log2, TY = BK_THREADS >> b.tx_log2;
     const int tx = tid & (TX - 1), ty = tid >> b.tx_log2;
-    const int ppr = D / E;
+    const int ppr = (D + E - 1) / E;
+    const bool ragged = AL == ROWS_PIECES && D % E != 0;
+    auto piece = [&](const float *r, int pc) -> floatx4 {
+        if constexpr (AL == ROWS_ALIGNED) return *reinterpret_cast<const floatx4 *>(r + pc * E);
+        else return load_piece(r + min(pc * E, D - E));
+    };
     // the sources this workgroup's points come from: the last whose points begin at or before i
     auto source_of = [&](int i, int q, int span) {
         int top = 1;
@@ -1088,7 +1143,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_accumulate_kernel(
         floatx4 f[UNR];
         const int p0 = min(tx, ppr - 1);
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) f[u] = *reinterpret_cast<const floatx4 *>(row[u] + p0 * E);
+        for (int u = 0; u < UNR; ++u) f[u] = piece(row[u], p0);
         if (i0 + TY * UNR < hi) fetch(i0 + TY * UNR, e, q);
 #pragma unroll
         for (int u = 0; u < UNR; ++u)
@@ -1096,14 +1151,20 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_accumulate_kernel(
         for (int pc = tx; pc < ppr; pc += TX) {
             if (pc != tx) {
 #pragma unroll
-                for (int u = 0; u < UNR; ++u) f[u] = *reinterpret_cast<const floatx4 *>(row[u] + pc * E);
+                for (int u = 0; u < UNR; ++u) f[u] = piece(row[u], pc);
             }
+            if (AL == ROWS_PIECES && ragged)
+#pragma unroll
+                for (int u = 0; u < UNR; ++u) f[u] = frag_place<float>(f[u], pc * E, D);
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
                 if (lab[u] < 0) continue;
                 unsigned long long *dst = cell + (size_t)lab[u] * Dp + pc * E;
 #pragma unroll
-                for (int k = 0; k < E; ++k) atomicAdd(dst + k, (unsigned long long)to_fixed((double)f[u][k], scale));
+                for (int k = 0; k < E; ++k) {
+                    if (AL == ROWS_PIECES && ragged && pc * E + k >= D) break;
+                    atomicAdd(dst + k, (unsigned long long)to_fixed((double)f[u][k], scale));
+                }
             }
         }
     }
@@ -1160,14 +1221,15 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finalize_kernel(
     }
 }
 
-// Rows of whole quads (read by 16-byte pieces) that the other paths do not serve as well (whole calls,
-// before / here): D = 32, K = 4096: N = 2^21 174 / 98 us, labels crowded into few clusters 199 / 120, all in one
+// Rows that the other paths do not serve as well (whole calls, before / here): D = 32, K = 4096: N = 2^21 174 / 98 us, labels crowded into few clusters 199 / 120, all in one
 // 398 / 133; D = 64, K = 1000, N = 70000 46 / 38; D = 128, K = 512, N = 500000 91 / 88.  Longer rows hide the sort
 // once X leaves the memory-side cache: D = 256: 10^5, K = 4000 101 / 80, 10^6, K = 300 233 / 283.  Against the
-// LDS tables with many slices: D = 12, K = 3000, N = 10^6 76 / 56, but D = 8, K = 4096 41 / 49.
+// LDS tables with many slices, which read X once each: D = 12, K = 3000, N = 10^6 76 / 56; of 9 to 11 features where there are
+// enough points and slices: D = 9, K = 6635, N = 947578 107 / 65, D = 10, K = 8000, N = 300000 60 / 48, but D = 9, K = 3800,
+// N = 300000 39 / 50; D = 8, K = 4096, N = 10^6 39 / 49.
 static bool bucket_pays(int64_t N, int D)
 {
-    return D % 4 == 0 && D >= 12 && (D <= 128 || (D <= 256 && (double)N * D * 4 < 268435456.0));
+    return D >= 9 && (D <= 128 || (D <= 256 && (double)N * D * 4 < 268435456.0));
 }
 
 static BucketPlan plan_bucket(ftk_dtype dtype, int64_t N, int D, int K)
@@ -1180,7 +1242,7 @@ static BucketPlan plan_bucket(ftk_dtype dtype, int64_t N, int D, int K)
     if (b.buckets >= BK_MAX || sources > BK_SOURCES) return b;
     b.sources = (int)sources;
     b.wgs = BK_WGS;  // shares; rounding up adds at most one workgroup per bucket
-    while ((1 << b.tx_log2) < D / 4 && b.tx_log2 < 6) ++b.tx_log2;
+    while ((1 << b.tx_log2) < (D + 3) / 4 && b.tx_log2 < 6) ++b.tx_log2;
     b.ok = sources * (b.buckets + 1) <= N;  // the boundaries take the place of the sorted labels
     return b;
 }
@@ -1202,10 +1264,10 @@ struct UpdateLaunch {
     int64_t n_walkers;
     dim3 rgrid;
 };
-static UpdateLaunch plan_update_launch(ftk_dtype dtype, const void *X, int64_t N, int D, int K)
+static UpdateLaunch plan_update_launch(ftk_dtype dtype, int64_t N, int D, int K)
 {
     UpdateLaunch L;
-    L.u = plan_update(dtype, X, N, D, K);
+    L.u = plan_update(dtype, N, D, K);
     const size_t esz = dtype == FTK_F32 ? 4 : 8;
     // Rows of at least half a cache line gather efficiently, and the label-sorted path streams
     // them at nearly the HBM rate - but it is six kernels with a fixed cost of about 45 us, and the
@@ -1221,14 +1283,14 @@ static UpdateLaunch plan_update_launch(ftk_dtype dtype, const void *X, int64_t N
                              ((int64_t)K * D <= 4 * UPD_CELLS && x_bytes < 268435456.0);
     L.sorted_path = (size_t)D * esz >= 64 && N >= 65536 && !small_table;
     if (g_tuning.update_path >= 0) L.sorted_path = g_tuning.update_path == 1;
-    L.E = L.u.aligned ? (dtype == FTK_F32 ? 4 : 2) : 1;
+    L.E = L.u.pieces ? (dtype == FTK_F32 ? 4 : 2) : 1;
     L.pieces = (int)ceil_div(D, L.E);
     L.lpr_log2 = 0;
     while ((1 << L.lpr_log2) < L.pieces && L.lpr_log2 < 6) ++L.lpr_log2;
     const int gpw = 64 >> L.lpr_log2;
     // about 2048 waves where N allows (run ends cost only plain stores, so parallelism is free)
     int64_t rpl = N / ((int64_t)gpw * 2048);
-    if (rpl < RED_ROWS_PER_LANE_MIN) rpl = RED_ROWS_PER_LANE_MIN;
+    if (rpl < red_rows_min(N)) rpl = red_rows_min(N);
     if (rpl > RED_ROWS_PER_LANE_MAX) rpl = RED_ROWS_PER_LANE_MAX;
     L.rows_per_lane = (int)rpl;
     L.n_walkers = ceil_div(N, L.rows_per_lane);
@@ -1237,9 +1299,9 @@ static UpdateLaunch plan_update_launch(ftk_dtype dtype, const void *X, int64_t N
     return L;
 }
 
-void update_geometry(ftk_dtype dtype, bool aligned16, int64_t N, int D, int K, ftk_geometry *out)
+void update_geometry(ftk_dtype dtype, int64_t N, int D, int K, ftk_geometry *out)
 {
-    const UpdateLaunch L = plan_update_launch(dtype, aligned16 ? nullptr : (const void *)1, N, D, K);
+    const UpdateLaunch L = plan_update_launch(dtype, N, D, K);
     if (L.sorted_path) {
         out->workgroups = L.rgrid.x;
         out->waves_per_workgroup = 4;
@@ -1256,13 +1318,42 @@ void update_geometry(ftk_dtype dtype, bool aligned16, int64_t N, int D, int K, f
     out->bits = 64;
 }
 
+static void launch_reduce_finalize(ftk_dtype dtype, bool dmr, const long long *slabs, const int32_t *cslabs, int chunks,
+                                   int64_t scale_rows, int D, int K, const double *absmax, void *C, int32_t *counts,
+                                   ftk_ft_stats *stats, hipStream_t st)
+{
+    const int groups = reduce_groups(chunks);
+    const dim3 grid((unsigned)ceil_div((int64_t)K * D, RF_THREADS / groups)), block(RF_THREADS);
+#define FTK_LAUNCH_RF(T, DM, G)                                                                                     \
+    hipLaunchKernelGGL((update_reduce_finalize_kernel<T, DM, G>), grid, block, 0, st, slabs, cslabs, chunks, scale_rows, D, \
+                       K, absmax, (T *)C, counts, stats)
+#define FTK_LAUNCH_RF_G(T, DM)                           \
+    do {                                                 \
+        if (groups == 1) FTK_LAUNCH_RF(T, DM, 1);        \
+        else if (groups == 2) FTK_LAUNCH_RF(T, DM, 2);   \
+        else if (groups == 4) FTK_LAUNCH_RF(T, DM, 4);   \
+        else if (groups == 8) FTK_LAUNCH_RF(T, DM, 8);   \
+        else FTK_LAUNCH_RF(T, DM, 32);                   \
+    } while (0)
+    if (dtype == FTK_F32) {
+        if (dmr) FTK_LAUNCH_RF_G(float, true);
+        else FTK_LAUNCH_RF_G(float, false);
+    } else {
+        if (dmr) FTK_LAUNCH_RF_G(double, true);
+        else FTK_LAUNCH_RF_G(double, false);
+    }
+#undef FTK_LAUNCH_RF_G
+#undef FTK_LAUNCH_RF
+}
+
 ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, int64_t N, int D,
                          int K, void *C, int32_t *counts, const double *absmax, const Workspace &w,
                          ftk_ft_mode ft_mode, const ftk_fault *faults, int n_faults, ftk_ft_stats *stats,
                          hipStream_t st)
 {
-    const UpdateLaunch L = plan_update_launch(dtype, X, N, D, K);
+    const UpdateLaunch L = plan_update_launch(dtype, N, D, K);
     const UpdatePlan &u = L.u;
+    const int rows = row_access(X, X, D, dtype == FTK_F32 ? 4 : 8);
     const int64_t cells = (int64_t)K * D;
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(w.fx_sums);
     const bool dmr = ft_mode != FTK_FT_OFF;
@@ -1272,8 +1363,8 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
     fa.mode = (int)ft_mode;
     fa.stats = stats;
     const BucketPlan bp = plan_bucket(dtype, N, D, K);
-    if (bp.ok && w.room && u.aligned && !dmr && n_faults == 0 && g_tuning.update_path < 0 &&
-        (L.sorted_path || (u.nks >= 4 && N >= 65536))) {
+    if (bp.ok && w.room && !dmr && n_faults == 0 && g_tuning.update_path < 0 &&
+        (L.sorted_path || (u.nks >= 4 && N >= 65536 && (D >= 12 || (double)N * u.nks >= 2.4e6)))) {
         uint32_t *entries = reinterpret_cast<uint32_t *>(w.sort_idx);
         long long *slabs = reinterpret_cast<long long *>(w.bucket_slab);
         int32_t *bounds = w.sort_lab, *totals = w.sort_cursor;
@@ -1281,8 +1372,12 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
         hipLaunchKernelGGL(bucket_split_kernel, dim3(bp.sources), dim3(BK_THREADS), 0, st, labels, N, K, bp.Kb, bp.buckets,
                            entries, bounds, totals);
         const size_t lds = (size_t)bp.Kb * (D + 1) * 8 + ((size_t)bp.Kb + 2 * bp.sources + 1) * 4;
-        hipLaunchKernelGGL(bucket_accumulate_kernel, dim3(bp.wgs + bp.buckets), dim3(BK_THREADS), lds, st, (const float *)X, entries,
-                           bounds, totals, N, D, K, bp, absmax, slabs, w.bucket_cslab);
+        auto add_up = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(bp.wgs + bp.buckets), dim3(BK_THREADS), lds, st, (const float *)X, entries,
+                               bounds, totals, N, D, K, bp, absmax, slabs, w.bucket_cslab);
+        };
+        if (rows == ROWS_ALIGNED) add_up(bucket_accumulate_kernel<ROWS_ALIGNED>);
+        else add_up(bucket_accumulate_kernel<ROWS_PIECES>);
         hipLaunchKernelGGL(bucket_finalize_kernel, dim3(bp.buckets, (unsigned)ceil_div(bp.Kb * D, BF_CELLS)),
                            dim3(BK_THREADS), 0, st, slabs, w.bucket_cslab, totals, N, D, K, bp, absmax, (float *)C,
                            counts);
@@ -1309,18 +1404,24 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
     hipLaunchKernelGGL((sorted_reduce_kernel<T, AL, DM, ##__VA_ARGS__>), L.rgrid, rblock, 0, st, (const T *)X, w.sort_idx, \
                        w.sort_lab, w.sort_cursor, K, N, D, L.lpr_log2, L.rows_per_lane, L.n_walkers, absmax, \
                        reinterpret_cast<long long *>(sums), slot_val, slot_lab, fa)
+#define FTK_LAUNCH_RED_AL(T, AL)                           \
+    do {                                                   \
+        if (dmr && stream_x) FTK_LAUNCH_RED(T, AL, true, true);  \
+        else if (stream_x) FTK_LAUNCH_RED(T, AL, false, true);   \
+        else if (dmr) FTK_LAUNCH_RED(T, AL, true);         \
+        else FTK_LAUNCH_RED(T, AL, false);                 \
+    } while (0)
 #define FTK_LAUNCH_RED_T(T)                                \
     do {                                                   \
-        if (u.aligned && dmr && stream_x) FTK_LAUNCH_RED(T, true, true, true);   \
-        else if (u.aligned && stream_x) FTK_LAUNCH_RED(T, true, false, true);    \
-        else if (u.aligned && dmr) FTK_LAUNCH_RED(T, true, true);  \
-        else if (u.aligned) FTK_LAUNCH_RED(T, true, false);        \
-        else if (dmr) FTK_LAUNCH_RED(T, false, true);              \
-        else FTK_LAUNCH_RED(T, false, false);                      \
+        if (rows == ROWS_ALIGNED) FTK_LAUNCH_RED_AL(T, ROWS_ALIGNED);     \
+        else if (rows == ROWS_PIECES) FTK_LAUNCH_RED_AL(T, ROWS_PIECES);  \
+        else if (dmr) FTK_LAUNCH_RED(T, ROWS_ELEMENTS, true);             \
+        else FTK_LAUNCH_RED(T, ROWS_ELEMENTS, false);                     \
     } while (0)
         if (dtype == FTK_F32) FTK_LAUNCH_RED_T(float);
         else FTK_LAUNCH_RED_T(double);
 #undef FTK_LAUNCH_RED_T
+#undef FTK_LAUNCH_RED_AL
 #undef FTK_LAUNCH_RED
         {
             const int blocks = (int)ceil_div(cells, SF_CELLS);
@@ -1352,27 +1453,18 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
                        scale_rows, 0, fa)
 #define FTK_LAUNCH_ACC_T(T)                                \
     do {                                                   \
-        if (u.aligned && dmr) FTK_LAUNCH_ACC(T, true, true);       \
-        else if (u.aligned) FTK_LAUNCH_ACC(T, true, false);        \
-        else if (dmr) FTK_LAUNCH_ACC(T, false, true);              \
-        else FTK_LAUNCH_ACC(T, false, false);                      \
+        if (rows == ROWS_ALIGNED && dmr) FTK_LAUNCH_ACC(T, ROWS_ALIGNED, true);      \
+        else if (rows == ROWS_ALIGNED) FTK_LAUNCH_ACC(T, ROWS_ALIGNED, false);       \
+        else if (rows == ROWS_PIECES && dmr) FTK_LAUNCH_ACC(T, ROWS_PIECES, true);   \
+        else if (rows == ROWS_PIECES) FTK_LAUNCH_ACC(T, ROWS_PIECES, false);         \
+        else if (dmr) FTK_LAUNCH_ACC(T, ROWS_ELEMENTS, true);                        \
+        else FTK_LAUNCH_ACC(T, ROWS_ELEMENTS, false);                                \
     } while (0)
         if (dtype == FTK_F32) FTK_LAUNCH_ACC_T(float);
         else FTK_LAUNCH_ACC_T(double);
 #undef FTK_LAUNCH_ACC_T
 #undef FTK_LAUNCH_ACC
-        const int blocks = (int)ceil_div(cells, RF_CELLS);
-#define FTK_LAUNCH_RF(T, DM)                                                                                  \
-    hipLaunchKernelGGL((update_reduce_finalize_kernel<T, DM>), dim3(blocks), dim3(RF_CELLS * RF_GROUPS), 0, st, \
-                       slabs, w.upd_cslab, u.chunks, scale_rows, D, K, absmax, (T *)C, counts, stats)
-        if (dtype == FTK_F32) {
-            if (dmr) FTK_LAUNCH_RF(float, true);
-            else FTK_LAUNCH_RF(float, false);
-        } else {
-            if (dmr) FTK_LAUNCH_RF(double, true);
-            else FTK_LAUNCH_RF(double, false);
-        }
-#undef FTK_LAUNCH_RF
+        launch_reduce_finalize(dtype, dmr, slabs, w.upd_cslab, u.chunks, scale_rows, D, K, absmax, C, counts, stats, st);
     }
     FTK_TRY_HIP(hipGetLastError());
     return FTK_OK;
@@ -1383,9 +1475,9 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
 // predecessors left (plain read-modify-write: a table belongs to one workgroup), and the
 // reduce-and-average kernel runs once after the last batch.  The plan is the one of a full batch;
 // a shorter last batch only changes the rows per workgroup.
-BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, const void *X, int64_t N, int64_t batch_rows, int D, int K)
+BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, int64_t N, int64_t batch_rows, int D, int K)
 {
-    const UpdatePlan u = plan_update(dtype, X, batch_rows < N ? batch_rows : N, D, K);
+    const UpdatePlan u = plan_update(dtype, batch_rows < N ? batch_rows : N, D, K);
     BatchedUpdatePlan b;
     b.Ks = u.Ks;
     b.Ds = u.Ds;
@@ -1393,7 +1485,7 @@ BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, const void *X, int64_t N,
     b.nds = u.nds;
     b.tx_log2 = u.tx_log2;
     b.chunks = u.chunks;
-    b.aligned = u.aligned;
+    b.pieces = u.pieces;
     const int64_t nbatch = ceil_div(N, batch_rows);
     b.scale_rows = dtype == FTK_F64 ? u.rows_per_chunk * nbatch : N;
     b.ok = u.chunks <= update_slab_chunks_max(N) && (int64_t)u.chunks * K * D <= update_slab_cells_max(N, D, K);
@@ -1417,12 +1509,15 @@ ftk_status launch_update_batch(ftk_dtype dtype, const void *Xb, const int32_t *l
     hipLaunchKernelGGL((update_accumulate_kernel<T, AL, false>), grid, block, lds, st, (const T *)Xb, labels_b, \
                        nb, D, K, absmax, slabs, w.upd_cslab, b.Ks, b.Ds, b.nds, b.tx_log2, rows_per_chunk,  \
                        b.scale_rows, first ? 0 : 1, fa)
+    const int rows = row_access(Xb, Xb, D, dtype == FTK_F32 ? 4 : 8);
     if (dtype == FTK_F32) {
-        if (b.aligned) FTK_LAUNCH_ACC(float, true);
-        else FTK_LAUNCH_ACC(float, false);
+        if (rows == ROWS_ALIGNED) FTK_LAUNCH_ACC(float, ROWS_ALIGNED);
+        else if (rows == ROWS_PIECES) FTK_LAUNCH_ACC(float, ROWS_PIECES);
+        else FTK_LAUNCH_ACC(float, ROWS_ELEMENTS);
     } else {
-        if (b.aligned) FTK_LAUNCH_ACC(double, true);
-        else FTK_LAUNCH_ACC(double, false);
+        if (rows == ROWS_ALIGNED) FTK_LAUNCH_ACC(double, ROWS_ALIGNED);
+        else if (rows == ROWS_PIECES) FTK_LAUNCH_ACC(double, ROWS_PIECES);
+        else FTK_LAUNCH_ACC(double, ROWS_ELEMENTS);
     }
 #undef FTK_LAUNCH_ACC
     FTK_TRY_HIP(hipGetLastError());
@@ -1433,15 +1528,8 @@ ftk_status launch_update_batched_finalize(ftk_dtype dtype, int D, int K, const d
                                           int32_t *counts, const Workspace &w, const BatchedUpdatePlan &b,
                                           hipStream_t st)
 {
-    const int64_t cells = (int64_t)K * D;
-    const int blocks = (int)ceil_div(cells, RF_CELLS);
-    const long long *slabs = reinterpret_cast<const long long *>(w.upd_slab);
-    if (dtype == FTK_F32)
-        hipLaunchKernelGGL((update_reduce_finalize_kernel<float, false>), dim3(blocks), dim3(RF_CELLS * RF_GROUPS), 0, st,
-                           slabs, w.upd_cslab, b.chunks, b.scale_rows, D, K, absmax, (float *)C, counts, nullptr);
-    else
-        hipLaunchKernelGGL((update_reduce_finalize_kernel<double, false>), dim3(blocks), dim3(RF_CELLS * RF_GROUPS), 0, st,
-                           slabs, w.upd_cslab, b.chunks, b.scale_rows, D, K, absmax, (double *)C, counts, nullptr);
+    launch_reduce_finalize(dtype, false, reinterpret_cast<const long long *>(w.upd_slab), w.upd_cslab, b.chunks, b.scale_rows, D, K,
+                           absmax, C, counts, nullptr, st);
     FTK_TRY_HIP(hipGetLastError());
     return FTK_OK;
 }

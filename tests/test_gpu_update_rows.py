@@ -1,0 +1,57 @@
+"""Updates of rows of any length and alignment on every path (tables with one to many slices and one to many row blocks,
+buckets, label-sorted gather), protected and not, against the CPU oracle; fp32 sums are the same integers on all of them."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import cpu as oracle
+from paper_2408_01391_amd import binding as ftk
+from tests.gpu_util import DEV, check_centroids, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _restore_rules():
+    yield
+    ftk.tuning_override(-1, -1, -1)
+
+
+def _update(x, lab, C, mode):
+    Cd, stats = to_dev(C.copy()), ftk.new_stats(DEV)
+    _, counts = ftk.kmeans_update(x, lab, Cd, ft_mode=mode, stats=stats)
+    torch.cuda.synchronize()
+    assert ftk.stats_dict(stats)["detected"] == 0
+    return Cd.cpu().numpy(), counts.cpu().numpy()
+
+
+# N, D, K: rows shorter than a piece, every remainder, one table of many slices and few row blocks, buckets, sorted rows
+SIZES = [(900, 1, 5), (900, 3, 500), (3000, 5, 40), (3000, 6, 300), (3000, 7, 2000), (2500, 33, 50), (2500, 34, 400), (1500, 131, 700),
+         (4000, 257, 90), (700, 1030, 40), (400, 1100, 200), (70001, 13, 900), (70001, 35, 600), (66001, 130, 270), (66001, 5, 3000)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("N,D,K", SIZES)
+def test_update_of_rows_of_any_length(N, D, K, dtype):
+    print("update rows", N, D, K, dtype, flush=True)
+    rng = np.random.default_rng(N + D + K)
+    X = rng.normal(size=(N, D)).astype(np.float32 if dtype == "f32" else np.float64)
+    C = rng.normal(size=(K, D)).astype(X.dtype)
+    labels = rng.integers(0, K, N).astype(np.int32)
+    labels[: N // 3] = K // 2  # one large cluster, and some empty ones
+    labels[labels == K - 1] = 0
+    ref, counts = oracle.update(X, labels, C)
+    lab = to_dev(labels)
+    flat = torch.empty(X.size + 1, dtype=torch.float32 if dtype == "f32" else torch.float64, device=DEV)
+    flat[1:] = to_dev(X).flatten()
+    first = None
+    for path in (-1, 0, 1):
+        ftk.tuning_override(-1, -1, path)
+        for x in (to_dev(X), flat[1:].view(N, D)):
+            for mode in (ftk.FT_OFF, ftk.FT_STRICT):
+                out, n = _update(x, lab, C, mode)
+                assert np.array_equal(n, counts)
+                check_centroids(out, ref)
+                if dtype == "f32":
+                    first = out if first is None else first
+                    assert np.array_equal(out, first)
