@@ -692,7 +692,7 @@ ftk_status ftk_absmax(ftk_dtype dtype, const void *X, int64_t count, double *out
     FTK_TRY(check_ptr(X, dtype == FTK_F32 ? 4 : 8, "X"));
     FTK_TRY(check_ptr(out_absmax, 8, "out_absmax"));
     FTK_TRY(check_device());
-    return launch_absmax(dtype, X, count, out_absmax, (hipStream_t)hip_stream);
+    return launch_absmax(dtype, X, count, out_absmax, nullptr, 0, (hipStream_t)hip_stream);
 }
 
 ftk_status ftk_kmeans_update_ft(ftk_dtype dtype, const void *X, const int32_t *labels, int64_t N,
@@ -718,7 +718,7 @@ ftk_status ftk_kmeans_update_ft(ftk_dtype dtype, const void *X, const int32_t *l
     FTK_TRY(check_device());
     hipStream_t st = (hipStream_t)hip_stream;
     if (!x_absmax) {
-        FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, w.absmax, st));
+        FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, w.absmax, nullptr, 0, st));
         x_absmax = w.absmax;
     }
     return launch_update(dtype, X, labels, N, D, K, C, counts, x_absmax, w, ft, faults, n_faults, stats, st);
@@ -871,30 +871,36 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
     FTK_TRY(check_device());
     hipStream_t st = (hipStream_t)hip_stream;
 
-    if (C_init) {
-        FTK_TRY_HIP(hipMemcpyAsync(w.C_cur, C_init, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
-    } else {
+    const bool small = !fast && w.small_fit && iters > 0 && ft == FTK_FT_OFF && g_tuning.assign_variant == -1 &&
+                       g_tuning.update_path == -1 && small_fit_pays(dtype, N, D, K);
+    // the centroids live where they are asked for, if whole pieces may be read from there
+    void *const C = (uintptr_t)C_out % 16 == 0 ? C_out : w.C_cur;
+    const void *C_first = C_init;  // (a small fit reads the first ones where they are)
+    if (!C_init) {
         std::vector<int64_t> idx((size_t)K);
         FTK_TRY(ftk_seeded_indices(seed, N, K, idx.data()));
         FTK_TRY_HIP(hipMemcpyAsync(w.idx, idx.data(), (size_t)K * sizeof(int64_t), hipMemcpyHostToDevice, st));
         FTK_TRY_HIP(hipStreamSynchronize(st));  // idx lives on this stack frame
-        FTK_TRY(launch_gather_rows(dtype, X, D, w.idx, K, w.C_cur, st));
+        C_first = small ? w.C_cur : C;
+        FTK_TRY(launch_gather_rows(dtype, X, D, w.idx, K, const_cast<void *>(C_first), st));
     }
-    FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, w.absmax, st));
-    const bool small = !fast && w.small_fit && iters > 0 && ft == FTK_FT_OFF && g_tuning.assign_variant == -1 &&
-                       g_tuning.update_path == -1 && small_fit_pays(dtype, N, D, K);
-    if (small)
-        FTK_TRY(launch_small_fit(dtype, X, N, D, K, iters, w.C_cur, C_out, labels_out, counts_out, w.absmax, w.inertia,
+    if (!small && C_first != C) FTK_TRY_HIP(hipMemcpyAsync(C, C_first, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
+    int32_t *const ticket = reinterpret_cast<int32_t *>(w.absmax + 1);
+    if (small) {
+        FTK_TRY(launch_small_fit(dtype, X, N, D, K, iters, C_first, w.C_cur, C_out, labels_out, counts_out, w.absmax, w.inertia,
                                  w.partials, w.small_fit, st));
+    } else {
+        FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, w.absmax, ticket, 1, st));
+    }
     for (int t = 0; !small && t < iters; ++t) {
-        AssignCall c{dtype, X, w.C_cur, N, D, K, labels_out, w.mindist, ft, nullptr, 0, stats};
+        AssignCall c{dtype, X, C, N, D, K, labels_out, w.mindist, ft, nullptr, 0, stats};
         FTK_TRY(assign_impl(c, w, st, fast));
         if (inertia_per_iter)
-            FTK_TRY(launch_sum_to_double(dtype, w.mindist, N, w.partials, w.inertia + t, st));
-        FTK_TRY(launch_update(dtype, X, labels_out, N, D, K, w.C_cur, counts_out, w.absmax, w, ft, nullptr, 0,
+            FTK_TRY(launch_sum_to_double(dtype, w.mindist, N, w.partials, ticket, w.inertia + t, st));
+        FTK_TRY(launch_update(dtype, X, labels_out, N, D, K, C, counts_out, w.absmax, w, ft, nullptr, 0,
                               stats, st));
     }
-    if (!small) FTK_TRY_HIP(hipMemcpyAsync(C_out, w.C_cur, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
+    if (!small && C != C_out) FTK_TRY_HIP(hipMemcpyAsync(C_out, C, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
     if (inertia_per_iter && iters > 0) {
         FTK_TRY_HIP(hipMemcpyAsync(inertia_per_iter, w.inertia, (size_t)iters * sizeof(double),
                                    hipMemcpyDeviceToHost, st));

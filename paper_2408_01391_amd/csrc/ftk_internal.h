@@ -153,7 +153,8 @@ size_t fast_split_bytes(ftk_dtype dtype, int D, int K);
 void plan_fast(int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p);
 ftk_status launch_assign_fast(const AssignCall &c, const AssignPlan &p, const Workspace &w, hipStream_t st);
 
-ftk_status launch_absmax(ftk_dtype dtype, const void *X, int64_t count, double *out, hipStream_t st);
+// `zero`: words cleared on the way
+ftk_status launch_absmax(ftk_dtype dtype, const void *X, int64_t count, double *out, int32_t *zero, int n_zero, hipStream_t st);
 ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, int64_t N, int D,
                          int K, void *C, int32_t *counts, const double *absmax, const Workspace &w,
                          ftk_ft_mode ft_mode, const ftk_fault *faults, int n_faults, ftk_ft_stats *stats,
@@ -175,7 +176,8 @@ ftk_status launch_zero_ints(int32_t *p, int n, hipStream_t st);
 void update_geometry(ftk_dtype dtype, int64_t N, int D, int K, ftk_geometry *out);
 ftk_status launch_gather_rows(ftk_dtype dtype, const void *X, int D, const int64_t *idx_dev, int K,
                               void *C, hipStream_t st);
-ftk_status launch_sum_to_double(ftk_dtype dtype, const void *v, int64_t n, double *partials,
-                                double *out, hipStream_t st);
+// ticket: one word, zero before the first call
+ftk_status launch_sum_to_double(ftk_dtype dtype, const void *v, int64_t n, double *partials, int32_t *ticket, double *out,
+                                hipStream_t st);
 
 }  // namespace ftk

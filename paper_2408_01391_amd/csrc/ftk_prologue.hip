@@ -192,17 +192,22 @@ ftk_status launch_zero_ints(int32_t *p, int n, hipStream_t st)
 }
 
 // ---- |x| maximum ---------------------------------------------------------------------------
-__global__ void reset_double_kernel(double *p)
+// ... and clears `n` words that the kernels behind need
+__global__ void reset_double_kernel(double *p, int32_t *zero, int n)
 {
-    if (threadIdx.x == 0) p[0] = 0.0;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) p[0] = 0.0;
+    for (int k = i; k < n; k += gridDim.x * blockDim.x) zero[k] = 0;
 }
 
 // The workgroup's maximum goes to `out` by one atomic, and only if it is larger than what stands there:
-// atomics on one word follow one another at about 10 ns (one per wave, 8192 of them, made this pass over
-// 2^18 x 128 floats 109 us; the read itself takes a quarter of that).
+// atomics on one word follow one another at about 10 ns, and workgroups that run side by side all find the word
+// empty.  So few and large workgroups: 2^18 x 128 floats 109 us with an atomic a wave, 35 with 2048 workgroups of four
+// waves, 23 with 512 of eight; 15521 x 148 19 and 5.8.
+constexpr int AM_THREADS = 512, AM_GRID = 512;
 __device__ __forceinline__ void absmax_publish(double m, double *out)
 {
-    __shared__ double sh[4];
+    __shared__ double sh[AM_THREADS / 64];
 #pragma unroll
     for (int mask = 32; mask >= 1; mask >>= 1) {
         const double o = __shfl_xor(m, mask, 64);
@@ -211,14 +216,14 @@ __device__ __forceinline__ void absmax_publish(double m, double *out)
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) m = sh[i] > m ? sh[i] : m;
+        for (int i = 1; i < AM_THREADS / 64; ++i) m = sh[i] > m ? sh[i] : m;
         if (m > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             atomicMax((unsigned long long *)out, (unsigned long long)__double_as_longlong(m));
     }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void absmax_kernel(const T *X, int64_t count, double *out)
+__global__ __launch_bounds__(AM_THREADS) void absmax_kernel(const T *X, int64_t count, double *out)
 {
     double m = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -231,7 +236,7 @@ __global__ __launch_bounds__(256) void absmax_kernel(const T *X, int64_t count, 
 
 // 16-byte vectorised variant for aligned, large inputs, four loads in flight
 template <typename T>
-__global__ __launch_bounds__(256) void absmax_vec_kernel(const T *X, int64_t nvec, double *out)
+__global__ __launch_bounds__(AM_THREADS) void absmax_vec_kernel(const T *X, int64_t nvec, int64_t count, double *out)
 {
     using F = typename Mma<T>::frag_t;
     constexpr int E = Mma<T>::E;
@@ -247,35 +252,32 @@ __global__ __launch_bounds__(256) void absmax_vec_kernel(const T *X, int64_t nve
             m = (v > m && v < Mma<T>::huge()) ? v : m;  // NaN and Inf never raise the maximum
         }
     }
+    if (const int64_t i = nvec * E + threadIdx.x; blockIdx.x == 0 && i < count) {  // what is left: fewer than a piece
+        const T v = fabs(X[i]);
+        m = (v > m && v < Mma<T>::huge()) ? v : m;
+    }
     absmax_publish((double)m, out);
 }
 
-ftk_status launch_absmax(ftk_dtype dtype, const void *X, int64_t count, double *out, hipStream_t st)
+ftk_status launch_absmax(ftk_dtype dtype, const void *X, int64_t count, double *out, int32_t *zero, int n_zero, hipStream_t st)
 {
-    hipLaunchKernelGGL(reset_double_kernel, dim3(1), dim3(64), 0, st, out);
+    const int64_t zb = ceil_div(n_zero, 256);
+    hipLaunchKernelGGL(reset_double_kernel, dim3((unsigned)(zb < 1 ? 1 : (zb < 1024 ? zb : 1024))), dim3(n_zero ? 256 : 64), 0, st, out, zero,
+                       n_zero);
     const int E = dtype == FTK_F32 ? 4 : 2;
-    const size_t esz = dtype == FTK_F32 ? 4 : 8;
-    int64_t nvec = ((uintptr_t)X % 16 == 0) ? count / E : 0;
+    const int64_t nvec = ((uintptr_t)X % 16 == 0) ? count / E : 0;
+    const dim3 block(AM_THREADS);
+    auto grid = [](int64_t n) { return dim3((unsigned)(ceil_div(n, AM_THREADS) < AM_GRID ? ceil_div(n, AM_THREADS) : AM_GRID)); };
     if (nvec > 0) {
-        const int blocks = (int)(ceil_div(nvec, 256) < 2048 ? ceil_div(nvec, 256) : 2048);
         if (dtype == FTK_F32)
-            hipLaunchKernelGGL((absmax_vec_kernel<float>), dim3(blocks), dim3(256), 0, st,
-                               (const float *)X, nvec, out);
+            hipLaunchKernelGGL((absmax_vec_kernel<float>), grid(nvec), block, 0, st, (const float *)X, nvec, count, out);
         else
-            hipLaunchKernelGGL((absmax_vec_kernel<double>), dim3(blocks), dim3(256), 0, st,
-                               (const double *)X, nvec, out);
-    }
-    const int64_t done = nvec * E;
-    if (done < count) {
-        const int64_t rest = count - done;
-        const int blocks = (int)(ceil_div(rest, 256) < 1024 ? ceil_div(rest, 256) : 1024);
-        const char *tail = (const char *)X + done * esz;
+            hipLaunchKernelGGL((absmax_vec_kernel<double>), grid(nvec), block, 0, st, (const double *)X, nvec, count, out);
+    } else {
         if (dtype == FTK_F32)
-            hipLaunchKernelGGL((absmax_kernel<float>), dim3(blocks), dim3(256), 0, st,
-                               (const float *)tail, rest, out);
+            hipLaunchKernelGGL((absmax_kernel<float>), grid(count), block, 0, st, (const float *)X, count, out);
         else
-            hipLaunchKernelGGL((absmax_kernel<double>), dim3(blocks), dim3(256), 0, st,
-                               (const double *)tail, rest, out);
+            hipLaunchKernelGGL((absmax_kernel<double>), grid(count), block, 0, st, (const double *)X, count, out);
     }
     FTK_TRY_HIP(hipGetLastError());
     return FTK_OK;
@@ -304,51 +306,61 @@ ftk_status launch_gather_rows(ftk_dtype dtype, const void *X, int D, const int64
     return FTK_OK;
 }
 
-// ---- objective: sum of a vector in double, fixed order (block partials, then one block) ----
-constexpr int SUM_BLOCKS = 512;
+// ---- objective: sum of a vector in double, fixed order: block partials, added up by the block that ends last ----
+// (few blocks: their tickets follow one another at about 10 ns, 512 of them cost what the second launch did)
+static int sum_blocks(int64_t n) { return (int)(ceil_div(n, 2048) < 128 ? ceil_div(n, 2048) : 128); }
+
+// sum of one value a thread in a fixed order (thread 0 gets it)
+__device__ __forceinline__ double block_sum(double s, double (&sh)[256])
+{
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w >= 1; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    return sh[0];
+}
 
 template <typename T>
-__global__ __launch_bounds__(256) void sum_partials_kernel(const T *v, int64_t n, double *partials)
+__global__ __launch_bounds__(256) void sum_kernel(const T *v, int64_t n, double *partials, int32_t *ticket, double *out)
 {
     __shared__ double sh[256];
+    __shared__ int sh_last;
     const int64_t per = (n + gridDim.x - 1) / gridDim.x;
     const int64_t lo = per * blockIdx.x;
     const int64_t hi = lo + per < n ? lo + per : n;
     double s = 0.0;
+#pragma unroll 8
     for (int64_t i = lo + threadIdx.x; i < hi; i += 256) s += (double)v[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
+    s = block_sum(s, sh);
+    if (threadIdx.x == 0) {
+        // written and read past the caches that other XCDs do not see; the ticket follows the value
+        __hip_atomic_store(partials + blockIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0);
+        sh_last = atomicAdd(ticket, 1) == (int)gridDim.x - 1;
     }
-    if (threadIdx.x == 0) partials[blockIdx.x] = sh[0];
+    __syncthreads();
+    if (!sh_last) return;
+    s = 0.0;
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += 256)
+        s += __hip_atomic_load(partials + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    s = block_sum(s, sh);
+    if (threadIdx.x == 0) {
+        out[0] = s;
+        *ticket = 0;  // for the next launch
+    }
 }
 
-__global__ __launch_bounds__(256) void sum_final_kernel(const double *partials, int n, double *out)
-{
-    __shared__ double sh[256];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) s += partials[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = sh[0];
-}
-
-ftk_status launch_sum_to_double(ftk_dtype dtype, const void *v, int64_t n, double *partials,
-                                double *out, hipStream_t st)
+// `ticket`: zero before the first call
+ftk_status launch_sum_to_double(ftk_dtype dtype, const void *v, int64_t n, double *partials, int32_t *ticket, double *out,
+                                hipStream_t st)
 {
     if (dtype == FTK_F32)
-        hipLaunchKernelGGL((sum_partials_kernel<float>), dim3(SUM_BLOCKS), dim3(256), 0, st,
-                           (const float *)v, n, partials);
+        hipLaunchKernelGGL((sum_kernel<float>), dim3((unsigned)sum_blocks(n)), dim3(256), 0, st, (const float *)v, n, partials, ticket, out);
     else
-        hipLaunchKernelGGL((sum_partials_kernel<double>), dim3(SUM_BLOCKS), dim3(256), 0, st,
-                           (const double *)v, n, partials);
-    hipLaunchKernelGGL(sum_final_kernel, dim3(1), dim3(256), 0, st, partials, SUM_BLOCKS, out);
+        hipLaunchKernelGGL((sum_kernel<double>), dim3((unsigned)sum_blocks(n)), dim3(256), 0, st, (const double *)v, n, partials, ticket, out);
     FTK_TRY_HIP(hipGetLastError());
     return FTK_OK;
 }

@@ -75,6 +75,30 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
     const T *X = reinterpret_cast<const T *>(a.X), *C = reinterpret_cast<const T *>(a.C);
     T *C_out = reinterpret_cast<T *>(a.C_out);
 
+    // The first rows are on their way while the centroids are formed (their means wait for the sums, then for divisions), and
+    // those of the next round while distances are taken: 20000 x 24, K = 100 13.2 us a call, 12.2 so; with the one launch
+    // ahead of the first iteration a fit of 4096 x 16, K = 8, ten iterations 143, 130.
+    const int per_wg = (SM_THREADS >> a.p_log2) * PT;  // points per workgroup and round
+    T raw[PT][4 * NQ];
+    auto request = [&](int64_t p0) {
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const int64_t p = p0 + (int64_t)t * (SM_THREADS >> a.p_log2) + (tid >> a.p_log2);
+            const T *row = X + (p < a.N ? p : a.N - 1) * D;
+            if (D % 4 == 0) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const Quad<T> f = load_quad<T>(row + min(4 * q, D - 4));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) raw[t][4 * q + e] = f.v[e];
+                }
+            } else {
+#pragma unroll
+                for (int d = 0; d < 4 * NQ; ++d) raw[t][d] = row[min(d, D - 1)];
+            }
+        }
+    };
+    request((int64_t)blockIdx.x * per_wg);
     double scale = 1.0;
     if constexpr (FIT) scale = small_scale(*a.absmax, a.scale_rows);
     const double inv = 1.0 / scale;
@@ -108,7 +132,6 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
     }
     __syncthreads();
 
-    const int per_wg = (SM_THREADS >> a.p_log2) * PT;  // points per workgroup and round
     double inertia = 0.0;
     for (int64_t p0 = (int64_t)blockIdx.x * per_wg; p0 < a.N; p0 += (int64_t)gridDim.x * per_wg) {
         double x[PT][4 * NQ];
@@ -120,35 +143,12 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
         for (int t = 0; t < PT; ++t) {
             p[t] = p0 + (int64_t)t * (SM_THREADS >> a.p_log2) + (tid >> a.p_log2);
             live[t] = p[t] < a.N;
-            const T *row = X + (live[t] ? p[t] : a.N - 1) * D;
-            if (D % 4 == 0) {
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    const int off = min(4 * q, D - 4);
-                    if constexpr (sizeof(T) == 4) {
-                        const float4e f = *reinterpret_cast<const float4e *>(row + off);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) x[t][4 * q + e] = 4 * q < D ? (double)f[e] : 0.0;
-                    } else {
-                        const double2e f = *reinterpret_cast<const double2e *>(row + off);
-                        const double2e h = *reinterpret_cast<const double2e *>(row + off + 2);
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            x[t][4 * q + e] = 4 * q < D ? f[e] : 0.0;
-                            x[t][4 * q + 2 + e] = 4 * q < D ? h[e] : 0.0;
-                        }
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int d = 0; d < 4 * NQ; ++d) {
-                    const double v = (double)row[min(d, D - 1)];
-                    x[t][d] = d < D ? v : 0.0;
-                }
-            }
+            for (int d = 0; d < 4 * NQ; ++d) x[t][d] = d < D ? (double)raw[t][d] : 0.0;
             best[t] = __builtin_huge_val();
             bj[t] = 0x7fffffff;
         }
+        if (p0 + (int64_t)gridDim.x * per_wg < a.N) request(p0 + (int64_t)gridDim.x * per_wg);
         for (int j = sub; j < K; j += P) {
             const T *c = ldsC + j * (SU * E);
             double d[PT];
@@ -224,6 +224,39 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
         int *cur_cnt = reinterpret_cast<int *>(a.cur + 2 * (size_t)cells);
         for (int i = tid; i < K; i += SM_THREADS)
             if (cnt[i]) atomicAdd(cur_cnt + i, cnt[i]);
+    }
+}
+
+// What the first iteration needs of a few points, in one workgroup: the largest |x| (as absmax_kernel finds it), a cleared
+// table.  4096 x 16: 4.6 us against three launches and the gaps between them.
+constexpr int SM_PREPARE = 131072;  // elements
+template <typename T>
+__global__ __launch_bounds__(1024) void small_prepare_kernel(const T *X, int count, double *absmax, int32_t *table, int words)
+{
+    __shared__ double sh[16];
+    const int tid = threadIdx.x;
+    T m = T(0);
+    auto add = [&](T x) {
+        const T v = fabs(x);
+        m = (v > m && v < Mma<T>::huge()) ? v : m;  // NaN and Inf never raise the maximum
+    };
+    const int quads = count / 4;
+#pragma unroll 8
+    for (int i = tid; i < quads; i += 1024) {
+        const Quad<T> q = load_quad<T>(X + 4 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) add(q.v[e]);
+    }
+    if (4 * quads + tid < count) add(X[4 * quads + tid]);
+    for (int i = tid; i < words; i += 1024) table[i] = 0;
+    double d = (double)m;
+#pragma unroll
+    for (int k = 32; k >= 1; k >>= 1) d = fmax(d, __shfl_xor(d, k, 64));
+    if ((tid & 63) == 0) sh[tid >> 6] = d;
+    __syncthreads();
+    if (tid == 0) {
+        for (int i = 1; i < 16; ++i) d = fmax(d, sh[i]);
+        *absmax = d;
     }
 }
 
@@ -329,8 +362,8 @@ ftk_status launch_small_assign(const AssignCall &c, hipStream_t st)
 
 // Iteration t adds into table t % 3 and clears the next one; the centroids of iteration t + 1 are formed
 // from it by every workgroup for itself, in the launch that uses them.
-ftk_status launch_small_fit(ftk_dtype dtype, const void *X, int64_t N, int D, int K, int iters, void *C_cur, void *C_out,
-                            int32_t *labels, int32_t *counts, const double *absmax, double *inertia, double *partials,
+ftk_status launch_small_fit(ftk_dtype dtype, const void *X, int64_t N, int D, int K, int iters, const void *C_first, void *C_cur,
+                            void *C_out, int32_t *labels, int32_t *counts, double *absmax, double *inertia, double *partials,
                             void *scratch, hipStream_t st)
 {
     const size_t cells = (size_t)K * D;
@@ -349,11 +382,20 @@ ftk_status launch_small_fit(ftk_dtype dtype, const void *X, int64_t N, int D, in
     const int64_t per_wg = (int64_t)(SM_THREADS >> a.p_log2) * pt;
     a.scale_rows = dtype == FTK_F32 ? N : ceil_div(ceil_div(N, per_wg), grid) * per_wg;
     a.absmax = absmax;
-    FTK_TRY(launch_zero_ints(reinterpret_cast<int32_t *>(tab(0)), (int)(4 * cells + K), st));
+    const int words = (int)(4 * cells + K);
+    int32_t *const first = reinterpret_cast<int32_t *>(tab(0));
+    if (N * D <= SM_PREPARE && words <= SM_PREPARE) {
+        if (dtype == FTK_F32)
+            hipLaunchKernelGGL(small_prepare_kernel<float>, dim3(1), dim3(1024), 0, st, (const float *)X, (int)(N * D), absmax, first, words);
+        else
+            hipLaunchKernelGGL(small_prepare_kernel<double>, dim3(1), dim3(1024), 0, st, (const double *)X, (int)(N * D), absmax, first, words);
+    } else {
+        FTK_TRY(launch_absmax(dtype, X, N * (int64_t)D, absmax, first, words, st));
+    }
     void *C_buf[2] = {C_cur, C_alt};
     for (int t = 0; t < iters; ++t) {
         // centroids before the update of iteration t - 1 are in C_buf[(t - 1) & 1]; those after go to the other
-        a.C = t == 0 ? C_buf[0] : C_buf[(t - 1) & 1];
+        a.C = t <= 1 ? C_first : C_buf[(t - 1) & 1];
         a.C_out = C_buf[t & 1];
         a.prev = t == 0 ? nullptr : tab(t - 1);
         a.cur = tab(t);
@@ -370,12 +412,13 @@ ftk_status launch_small_fit(ftk_dtype dtype, const void *X, int64_t N, int D, in
     }
     const dim3 g((unsigned)ceil_div((int64_t)cells > K ? (int64_t)cells : K, 256));
     const int last = iters - 1;
+    const void *const C_prev = last == 0 ? C_first : C_buf[last & 1];
     if (dtype == FTK_F32)
-        hipLaunchKernelGGL((small_finish_kernel<float>), g, dim3(256), 0, st, tab(last), (const float *)C_buf[last & 1],
+        hipLaunchKernelGGL((small_finish_kernel<float>), g, dim3(256), 0, st, tab(last), (const float *)C_prev,
                            (float *)C_out, counts, D, K, absmax, a.scale_rows, partials + (last & 1) * SM_GRID, grid,
                            inertia + last);
     else
-        hipLaunchKernelGGL((small_finish_kernel<double>), g, dim3(256), 0, st, tab(last), (const double *)C_buf[last & 1],
+        hipLaunchKernelGGL((small_finish_kernel<double>), g, dim3(256), 0, st, tab(last), (const double *)C_prev,
                            (double *)C_out, counts, D, K, absmax, a.scale_rows, partials + (last & 1) * SM_GRID, grid,
                            inertia + last);
     FTK_TRY_HIP(hipGetLastError());
