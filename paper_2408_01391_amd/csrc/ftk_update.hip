@@ -86,8 +86,9 @@ static UpdatePlan plan_update(ftk_dtype dtype, int64_t N, int D, int K)
     while ((1 << l2) < ppr && l2 < 8) ++l2;
     u.tx_log2 = l2;
     // a workgroup takes UPD_THREADS >> tx_log2 rows per pass; at least 16 passes (and 64 rows) per
-    // chunk, so that long rows of a mid-sized problem still spread over all CUs
-    int64_t min_rows = (int64_t)16 * (UPD_THREADS >> l2);
+    // chunk, so that long rows of a mid-sized problem still spread over all CUs; four where a table more is soon written and
+    // read (36311 x 63, K = 5 18.9 us with 16, 13.0 with four; 36000 x 64, K = 5 17.4 / 12.4)
+    int64_t min_rows = (int64_t)((int64_t)K * D <= 2048 ? 4 : 16) * (UPD_THREADS >> l2);
     if (min_rows > UPD_THREADS) min_rows = UPD_THREADS;
     if (min_rows < 64) min_rows = 64;
     int chunks = UPD_TARGET_WGS / slices;
@@ -252,10 +253,10 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
         // together with them (ALLK).  Otherwise only rows whose label falls into the slice are read: those of a step are
         // requested while the rows of the step before are added, their labels one step earlier still (10^6 x 11, K = 4000
         // 105 us a call without, 95 with; of ALLK slices, which the LDS atomics bound, 2^18 x 128, K = 256 42 without, 44 with; rows of
-        // up to three features 38 without, 41 with).
+        // up to three features 38 without, 41 with; under DMR the registers cost the other slices 3 %).
         auto pass = [&](auto allk_tag) {
         constexpr bool ALLK = decltype(allk_tag)::value;
-        constexpr bool AHEAD = !ALLK && AL != ROWS_ELEMENTS;
+        constexpr bool AHEAD = !ALLK && AL != ROWS_ELEMENTS && !DMR;
         const int64_t stride = (int64_t)TY * UNR;
         auto fetch_labels = [&](int64_t row0, int (&lab)[UNR]) {
 #pragma unroll
@@ -276,20 +277,25 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
             }
         };
         const int p0 = min(tx, ppr - 1);  // (lanes beyond the row's pieces request its last one)
-        int lab[UNR], lab_n[UNR];
-        F f[UNR], f_n[UNR];
+        int lab_c[UNR], lab_n[UNR];
+        F f_c[UNR], f_n[UNR];
         if constexpr (AHEAD) {
-            fetch_labels(r0 + ty, lab);
-            fetch_rows(r0 + ty, lab, p0, f);
+            fetch_labels(r0 + ty, lab_c);
+            fetch_rows(r0 + ty, lab_c, p0, f_c);
             fetch_labels(r0 + ty + stride, lab_n);
         }
         for (int64_t row0 = r0 + ty; row0 < r1; row0 += stride, ++step) {
             bool ok[UNR];
-            int lab_2[UNR];
+            int lab[UNR], lab_2[UNR];
+            F f[UNR];
             if constexpr (!AHEAD) {
                 fetch_labels(row0, lab);
-                fetch_rows(row0, lab, p0, f);
             } else {
+#pragma unroll
+                for (int u = 0; u < UNR; ++u) {
+                    lab[u] = lab_c[u];
+                    f[u] = f_c[u];
+                }
                 fetch_rows(row0 + stride, lab_n, p0, f_n);
                 fetch_labels(row0 + 2 * stride, lab_2);
             }
@@ -319,7 +325,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
                 }
             }
             for (int pc = tx; pc < ppr; pc += TX) {
-                if (pc != tx) fetch_rows(row0, lab, pc, f);
+                if (!AHEAD || pc != tx) fetch_rows(row0, lab, pc, f);
                 if (AL == ROWS_PIECES && ragged)
 #pragma unroll
                     for (int u = 0; u < UNR; ++u) f[u] = frag_place<T>(f[u], d0 + pc * E, D);
@@ -353,9 +359,9 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
             if constexpr (AHEAD)
 #pragma unroll
                 for (int u = 0; u < UNR; ++u) {
-                    lab[u] = lab_n[u];
+                    lab_c[u] = lab_n[u];
                     lab_n[u] = lab_2[u];
-                    f[u] = f_n[u];
+                    f_c[u] = f_n[u];
                 }
         }
         };
@@ -1229,7 +1235,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finalize_kernel(
 // N = 300000 39 / 50; D = 8, K = 4096, N = 10^6 39 / 49.
 static bool bucket_pays(int64_t N, int D)
 {
-    return D >= 9 && (D <= 128 || (D <= 256 && (double)N * D * 4 < 268435456.0));
+    return D >= 9 && (D <= 128 || (D <= 256 && D % 4 == 0 && (double)N * D * 4 < 268435456.0));
 }
 
 static BucketPlan plan_bucket(ftk_dtype dtype, int64_t N, int D, int K)
