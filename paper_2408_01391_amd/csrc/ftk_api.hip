@@ -8,6 +8,7 @@
 #include <utility>
 #include <vector>
 
+#include "ftk_direct.h"
 #include "ftk_internal.h"
 #include "ftk_scan.h"
 #include "ftk_small.h"
@@ -135,9 +136,9 @@ size_t hcn_entries_max(ftk_dtype dtype, int64_t N, int D, int K)
     return (size_t)ceil_div((int64_t)need, 512) * 512 + 512;
 }
 
-// Assignments that carry neither checksums nor listed faults: the one-launch kernel (ftk_small.hip) takes
-// the small ones, the scan (ftk_scan.hip) the large ones with enough centroids.  A forced kernel choice
-// goes to the kernel it names.
+// Assignments that carry neither checksums nor listed faults: the one-launch kernels (ftk_small.hip for short rows,
+// ftk_direct.hip) take the small ones and those with few centroids, the scan (ftk_scan.hip) the large ones with enough
+// centroids.  A forced kernel choice goes to the kernel it names.
 static ScanPlan route_scan(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
 {
     if (ft != FTK_FT_OFF || n_faults > 0 || g_tuning.assign_variant != -1) return ScanPlan{};
@@ -149,16 +150,32 @@ static bool route_small(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft
     return ft == FTK_FT_OFF && n_faults == 0 && g_tuning.assign_variant == -1 && small_assign_pays(dtype, N, D, K);
 }
 
+// Of what the scan takes, fp32 problems go on up to 8 * 10^7 multiplications, 10^8 with up to 100 centroids (scan / direct kernel, 397
+// random shapes: 1.4 .. 3.9 below, 0.6 .. 1.0 above; 1286 x 73, K = 110 22.7 / 9.1 us, 1500 x 20, K = 700 22.4 / 12, 1316 x 432,
+// K = 135 35 / 25); fp64 ones stay: the scan compares distances of data at any scale, where squares leave the range.
+static bool direct_rule(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    const double work = (double)N * D * K;
+    if (plan_scan(dtype, N, D, K).ok) return dtype == FTK_F32 && work <= (K <= 100 ? 1e8 : 8e7);
+    return direct_pays(dtype, N, D, K);
+}
+static bool route_direct(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)
+{
+    return ft == FTK_FT_OFF && n_faults == 0 && g_tuning.assign_variant == -1 && !small_assign_pays(dtype, N, D, K) &&
+           direct_rule(dtype, N, D, K);
+}
+
 // The reduced-precision entry point without checksums or faults: its own kernels where nothing else that
 // returns direct-difference distances is faster (whole calls, its own kernel / the other): rows of 9 .. 32
 // features scan at any K (1.5 * 10^6 x 32, K = 64 330 / 95 us, K = 512 516 / 194), wider ones from K = 512 (2 * 10^5 x
 // 128 217 / 125; K = 192 92 / 80, but 64 features 42 / 46 at K = 96).  Rows of up to 8: the fp32 kernel up to 512
 // centroids (2 * 10^5 x 8, K = 64 31 / 19), beyond that, while there are few points, the scan where it is faster than that
 // kernel (20000, K = 4096 106 / 45; 97801 x 4, K = 758: own 30.7, scan 35.0, fp32 28.4; 1.5 * 10^6, K = 1024 163 / 195).
-enum FastRoute { FAST_OWN, FAST_SMALL, FAST_FP32, FAST_SCAN };
+enum FastRoute { FAST_OWN, FAST_SMALL, FAST_DIRECT, FAST_FP32, FAST_SCAN };
 static FastRoute fast_rule(int64_t N, int D, int K)
 {
     if (small_assign_pays(FTK_F32, N, D, K)) return FAST_SMALL;
+    if (direct_rule(FTK_F32, N, D, K)) return FAST_DIRECT;
     if (D <= 8) {
         if (K <= 512) return FAST_FP32;
         return N >= 100000 ? FAST_OWN : (plan_scan(FTK_F32, N, D, K).ok ? FAST_SCAN : FAST_FP32);
@@ -251,18 +268,20 @@ Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, 
     const int64_t bucket_cells = update_bucket_cells(dtype, N, D, K, &bucket_counts);
     w.bucket_slab = (int64_t *)take((size_t)bucket_cells * sizeof(int64_t));
     w.bucket_cslab = (int32_t *)take((size_t)bucket_counts * sizeof(int32_t));
-    size_t least = off;  // serves all of them but the scan on fp16 pieces
-    for (size_t n : {scan_bytes(dtype, N, D, K, false), small_fit_bytes(D, K)})
-        if (least < shared + n) least = shared + n;
-    w.unprotected = least;
-    if (const size_t n = scan_bytes(dtype, N, D, K, true); w.unprotected < shared + n) w.unprotected = shared + n;
+    w.unprotected = off;
+    const size_t least = scan_bytes(dtype, N, D, K, false), small = small_fit_bytes(D, K);  // (the scan without its fp16 pieces)
+    for (size_t n : {scan_bytes(dtype, N, D, K, true), small})
+        if (w.unprotected < shared + n) w.unprotected = shared + n;
     w.scan = w.small_fit = nullptr;
     w.scan_bytes = 0;
-    w.room = p && bytes >= least;
-    if (w.room) {
-        w.scan = w.small_fit = (void *)(p + shared);
+    // each takes what room there is beyond the size of a protected mode
+    const bool more = p && (bytes > w.total || w.unprotected == w.total);
+    w.room = more && bytes >= off;
+    if (more && least && bytes >= shared + least) {
+        w.scan = (void *)(p + shared);
         w.scan_bytes = bytes - shared;
     }
+    if (more && small && bytes >= shared + small) w.small_fit = (void *)(p + shared);
     return w;
 }
 
@@ -367,14 +386,15 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
         if (froute == FAST_FP32) fast = false;  // the register-resident kernel of short rows
     }
     const bool small = fast ? froute == FAST_SMALL : froute == FAST_OWN && route_small(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
+    const bool direct = fast ? froute == FAST_DIRECT : froute == FAST_OWN && route_direct(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     ScanPlan scan = {};
     if (froute == FAST_SCAN)
         scan = cut_scan(c.dtype, c.N, c.D, c.K);
-    else if (!fast && froute == FAST_OWN && !small && w.scan)
+    else if (!fast && froute == FAST_OWN && !small && !direct && w.scan)
         scan = route_scan(c.dtype, c.N, c.D, c.K, c.ft, c.n_faults);
     AssignPlan p;
     if (scan.ok) scan = fit_scan(scan, w, c.N, c.D);
-    if (small || scan.ok) {
+    if (small || direct || scan.ok) {
         memset(&p, 0, sizeof(p));
     } else if (fast) {
         memset(&p, 0, sizeof(p));
@@ -382,11 +402,13 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
     } else {
         p = plan_assign(c.dtype, c.N, c.D, c.K, c.ft, aligned16);
     }
-    if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(c, p, w, st));
+    if (!small && !direct && !scan.ok) FTK_TRY(launch_centroid_prologue(c, p, w, st));
     ProfileMark mark = {};
     if (!own_scratch) FTK_TRY(profile_begin(mark, st));
     if (small)
         FTK_TRY(launch_small_assign(c, st));
+    else if (direct)
+        FTK_TRY(launch_direct_assign(c, cut_direct(c.N, c.D, c.K), st));
     else if (scan.ok)
         FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N, c.D), w, c, st));
     else if (fast)
@@ -394,7 +416,7 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
     else
         FTK_TRY(launch_assign(c, p, w, st));
     FTK_TRY(profile_end(mark, st));
-    if (small || scan.ok) return FTK_OK;  // no list is left
+    if (small || direct || scan.ok) return FTK_OK;  // no list is left
     const int n_wg = (!fast && c.stats && p.variant == VAR_GENERIC) ? (int)p.workgroups : 0;
     FTK_TRY(launch_refine(c, w, n_wg, st));
     return FTK_OK;
@@ -767,20 +789,23 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
     AssignPlan pprev = plan_assign(dtype, whole.N, D, K, FTK_FT_OFF, aligned16);
     // the path is chosen for the whole problem, as in the two-call step
     const bool small = route_small(dtype, N, D, K, FTK_FT_OFF, 0);
+    const bool direct = route_direct(dtype, N, D, K, FTK_FT_OFF, 0);
     const AssignCall problem{dtype, X, C, N, D, K, labels, mindist, FTK_FT_OFF, nullptr, 0, nullptr};
-    const ScanPlan scan = small || !w.scan ? ScanPlan{} : fit_scan(route_scan(dtype, N, D, K, FTK_FT_OFF, 0), w, N, D);
-    if (!small && !scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
+    const ScanPlan scan = small || direct || !w.scan ? ScanPlan{} : fit_scan(route_scan(dtype, N, D, K, FTK_FT_OFF, 0), w, N, D);
+    if (!small && !direct && !scan.ok) FTK_TRY(launch_centroid_prologue(whole, pprev, w, st));
     for (int64_t b = 0; b < nbatch; ++b) {
         const int64_t r0 = b * batch_rows;
         const int64_t nb = N - r0 < batch_rows ? N - r0 : batch_rows;
         const char *Xb = (const char *)X + (size_t)r0 * D * esz;
         AssignCall c{dtype, Xb, C, nb, D, K, labels + r0, mindist ? (void *)((char *)mindist + (size_t)r0 * esz) : nullptr,
                      FTK_FT_OFF, nullptr, 0, nullptr};
-        if (small || scan.ok) {
+        if (small || direct || scan.ok) {
             Workspace wb = w;
             wb.wl_count = w.batch_counters + 4 * b;
             if (small)
                 FTK_TRY(launch_small_assign(c, st));
+            else if (direct)
+                FTK_TRY(launch_direct_assign(c, cut_direct(N, D, K), st));
             else
                 FTK_TRY(launch_scan_assign(c, cut_part(scan, dtype, nb, D, K), carve_scan(w.scan, scan, N, D), wb, problem, st));
             FTK_TRY(launch_update_batch(dtype, Xb, labels + r0, nb, D, K, x_absmax, w, ub, b == 0, st));
