@@ -600,12 +600,305 @@ __device__ __forceinline__ void scan_best_finish(const ScanBest &b, int g, float
     if (!(b.m1 == b.m1) || !(om1 == om1)) m2 = __builtin_huge_valf();  // NaN scores: not to be trusted
 }
 
+// ---- settle -----------------------------------------------------------------------------------
+// L lanes share a row (row-contiguous 16-byte loads) and take ROWS of them at once: the pass is a
+// chain of latencies - record, then the centroid's row - that only requests in flight can hide.
+// A workgroup hands its listed points over with one atomic, to one of 64 lists: atomics on one word
+// follow one another at about 10 ns (2^21 x 32, K = 4096: 9 000 workgroups with something to list).
+struct SettleArgs {
+    ScanRecord *rec;
+    int splits;
+    const float4 *tile_stat;
+    int tiles;
+    const double *scale;
+    int64_t N;
+    int D, K;
+    float psi, lost;    // rounding of a score; what is lost of ||x|| ||c|| whatever the centroids
+    float lift;         // by which multiple of ||c||^2 the scores were raised
+    const float *norm;  // ||c||
+    float sums;         // rounding of a sum of squares over a row, halved
+    float slack, tiny;  // of the measured norms: their own rounding, and what underflow takes from them
+    int32_t *labels;
+    ScanListed *list;  // (point, score a candidate needs), or NULL: the points alone go to wl
+    int32_t *wl, *list_count;
+    int lists, list_cap;
+    int32_t *tickets;   // [N/32 + 1] cleared here for the pass that follows
+    // scans on fp16 pieces: their numbers where the gate chooses them
+    ScanGate gate;
+    int half_splits;
+    float half_psi, half_lift, half_tiny;
+    const void *ref;    // [D] the reference r
+};
+
+enum SettleKind : int {
+    SETTLE_PLAIN = 0,   // distances in the data's type
+    SETTLE_DOUBLE = 1,  // in double, added up in the order of group_sqdist(): whatever passes a point goes through, and so
+                        // whichever form scanned it (batches of a step take the one that is faster for their size), its
+                        // distance has the same bits; fp32 2^21 x 32, K = 4096 859 / 860 us a call, 60000 x 1024 343 / 344
+    SETTLE_HALF = 2     // the same, and the records may come from fp16 pieces
+};
+// lanes of a row
+constexpr int settle_lanes(int D) { return D <= 12 ? 2 : (D <= 24 ? 4 : (D <= 128 ? 8 : (D <= 512 ? 16 : 64))); }
+
+// of a row: squared norms of x, of x - r and of what an fp16 piece leaves of x; its record and ||c||
+struct SettleSums {
+    float x2, y2, xr2, m1, m2, cn;
+    int32_t j;
+};
+template <typename T, int L, int ROWS>
+struct SettleShared {
+    static constexpr int N = 256 / L * ROWS;  // rows of a block
+    float max[4][4];
+    int n, base;
+    SettleSums sums[N];
+    T dist[N];
+};
+
+// Block `block` of N rows.  own: their records where the workgroup that scanned the points settles them itself, else NULL;
+// half: the records come from fp16 pieces; again: a block after another one.
+template <typename T, int L, int ROWS, int KIND>
+__device__ __forceinline__ void settle_block(const T *X, const T *C, T *mindist, const SettleArgs &a, const int64_t block,
+                                             const ScanRecord *own, const bool half, const bool again,
+                                             SettleShared<T, L, ROWS> &sh)
+{
+    constexpr bool HALF = KIND == SETTLE_HALF;
+    using Acc = std::conditional_t<KIND == SETTLE_PLAIN, T, double>;
+    const int splits = own ? 1 : (half ? a.half_splits : a.splits);
+    const float psi = half ? a.half_psi : a.psi, lift = half ? a.half_lift : a.lift, tiny = half ? a.half_tiny : a.tiny;
+    constexpr int RPB = 256 / L;  // rows side by side
+    constexpr int Q = HALF ? 4 : 3;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int sub = tid & (L - 1), grp = tid / L;
+    const int Dq = a.D & ~3;
+    const int64_t first = block * (ROWS * RPB);
+    int at[ROWS];  // of the rows, from the first one
+    float m1[ROWS], m2[ROWS];
+    int j[ROWS];
+    const T *c[ROWS];
+    const T *const X0 = X + first * a.D;
+    const ScanRecord *rec = own ? own : a.rec + first;
+    Quad<T> xv[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        at[u] = (int)min((int64_t)(u * RPB + grp), a.N - 1 - first);
+        const ScanRecord r = rec[at[u]];
+        m1[u] = r.m1;
+        m2[u] = r.m2;
+        j[u] = r.j1;
+    }
+    // the first piece of every row travels with the records
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(X0 + (unsigned)(at[u] * a.D + min(4 * sub, Dq - 4)));
+    if (tid == 0) sh.n = 0;
+    const int64_t i0 = block * 256 + tid;
+    if (i0 * 32 < a.N) a.tickets[i0] = 0;
+    float cm[Q] = {};
+    for (int i = again ? a.tiles : tid; i < a.tiles; i += 256) {
+        const float4 t = a.tile_stat[i];
+        cm[0] = fmaxf(cm[0], t.x);
+        cm[1] = fmaxf(cm[1], t.y);
+        cm[2] = fmaxf(cm[2], t.z);
+        if constexpr (HALF) cm[3] = fmaxf(cm[3], t.w);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        cm[q] = wave_max(cm[q]);
+        if (lane == 0 && !again) sh.max[tid >> 6][q] = cm[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cm[q] = fmaxf(fmaxf(sh.max[0][q], sh.max[1][q]), fmaxf(sh.max[2][q], sh.max[3][q]));
+    const float cmax = 1.000001f * sqrtf(cm[0]) + tiny;
+    // a score of centroid c is off by at most A ||c|| + psi ||c||^2 / 2, A = lost ||x|| + psi (||x|| + ||r||); ||x1|| <= 2^-8 ||x||
+    // (fp16 pieces: lost ||x|| is ||r_x|| + max(||r_c|| / ||c||) ||x||, the first measured below)
+    const float lost = half ? 1.001f * a.slack * sqrtf(cm[Q - 1])
+                            : a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
+    const T s = (T)a.scale[0];
+    const float ref = 1.000001f * (float)a.scale[1] + tiny;  // ||r||
+    const float under = (float)((T)(a.D + 16) * std::numeric_limits<T>::min() * s * s);
+    for (int k = 1; k < splits; ++k) {
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const ScanRecord o = rec[(int64_t)k * a.N + at[u]];
+            const bool mine = m1[u] >= o.m1;
+            m2[u] = fmaxf(fmaxf(m2[u], o.m2), mine ? o.m1 : m1[u]);
+            m1[u] = mine ? m1[u] : o.m1;
+            j[u] = mine ? j[u] : o.j1;
+        }
+    }
+    Acc d[ROWS];
+    float xn[ROWS], yn[ROWS], cn[ROWS], xr[ROWS];  // of x and of x - r, of c, of what an fp16 piece leaves of x
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        j[u] = (unsigned)j[u] < (unsigned)a.K ? j[u] : 0;  // padding rows, when no score was a number
+        c[u] = C + (size_t)j[u] * a.D;
+        cn[u] = a.norm[j[u]];
+        if (sub == 0) {
+            SettleSums &q = sh.sums[u * RPB + grp];
+            q.m1 = m1[u];
+            q.m2 = m2[u];
+            q.j = j[u];
+        }
+        d[u] = Acc(0);
+        xn[u] = yn[u] = xr[u] = 0.f;
+    }
+    const T *const ref_row = (const T *)a.ref;
+    auto add = [&](int u, T xe, T ce, T re) {
+        const Acc t = (Acc)xe - (Acc)ce;
+        d[u] = fma(t, t, d[u]);
+        const float w = (float)(xe * s);
+        xn[u] = fmaf(w, w, xn[u]);
+        if constexpr (HALF) {
+            const float y = (float)((xe - re) * s);
+            yn[u] = fmaf(y, y, yn[u]);
+            add_lost_half(w, xr[u]);
+        }
+    };
+    for (int f = 4 * sub; f < Dq;) {
+        Quad<T> cv[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) cv[u] = load_quad<T>(c[u] + f);
+        Quad<T> rv = {};
+        if constexpr (HALF) rv = load_quad<T>(ref_row + f);
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) add(u, xv[u].v[e], cv[u].v[e], rv.v[e]);
+        f += 4 * L;
+        if (f < Dq)
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(X0 + (unsigned)(at[u] * a.D + f));
+    }
+    for (int f = Dq + sub; f < a.D; f += L)
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) add(u, X0[(unsigned)(at[u] * a.D + f)], c[u][f], HALF ? ref_row[f] : T(0));
+    // a row's bound is some hundred instructions: a thread takes one instead of its L lanes the same one
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        const T dist = (T)group_sum<L>(d[u]);
+        const float x2 = group_sum<L>(xn[u]);
+        float y2 = 0.f, xr2 = 0.f;
+        if constexpr (HALF) {
+            y2 = group_sum<L>(yn[u]);
+            if (half) xr2 = group_sum<L>(xr[u]);
+        }
+        if (sub == 0) {
+            SettleSums &q = sh.sums[u * RPB + grp];
+            q.x2 = x2;
+            q.y2 = y2;
+            q.xr2 = xr2;
+            q.cn = cn[u];
+            sh.dist[u * RPB + grp] = dist;
+        }
+    }
+    __syncthreads();
+    // whether score bounds say who is nearest; the score a candidate needs
+    auto bound = [&](const SettleSums &q, T dist, float &thr) {
+        const float norm = a.slack * sqrtf(q.x2) + tiny;
+        float A = lost * norm + psi * (norm + ref);
+        const float B = lift - 0.5f * psi;
+        if constexpr (HALF) A += half ? 1.001f * a.slack * sqrtf(q.xr2) : 0.f;
+        const float c1 = 1.000001f * q.cn + tiny, t = fminf(A / (2.f * B), cmax);  // the norm most too low
+        // How much too low the score of any centroid is, at most, and how much too high that of the named one.
+        const float low = 1.00001f * ((A - B * t) * t + (A + psi * cmax) * tiny) + SCAN_FLOOR;
+        const float high = 1.00001f * (A + (lift + 0.5f * psi) * c1) * c1;
+        float least = q.m1 - high;
+        if constexpr (HALF) {
+            // Its true score is also known from the distance, (||x - r||^2 - ||x - c||^2) / 2, to within the rounding of
+            // these sums: of fp16 pieces that halves the bound (2^21 x 32, K = 4096: 68 000 points listed against 105 000).
+            // The distance comes from differences that carry no scale: `under` is what underflow may have taken from it,
+            // infinite (a distance out of range: d2) where these sums say nothing.
+            const float d2 = (float)(dist * s * s);
+            least = fmaxf(least, 0.5f * (q.y2 - d2) - a.sums * (q.y2 + d2) - under);
+        }
+        least -= low;
+        // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on
+        // the way to a sum that is not): a threshold that is not a number makes every centroid a candidate.
+        const bool sound = (norm + ref + cmax) * cmax < 1e38f && (!half || fmaxf(norm, cmax) < HALF_RANGE);
+        thr = sound ? least : __builtin_nanf("");
+        return sound && least > q.m2;
+    };
+    // results and the list leave in whole lines
+    int mine[(RPB * ROWS + 255) / 256];
+    float thr[(RPB * ROWS + 255) / 256];
+#pragma unroll
+    for (int k = 0; k < (RPB * ROWS + 255) / 256; ++k) {
+        const int i = k * 256 + tid;
+        const int64_t p = first + i;
+        mine[k] = -1;
+        if (i < RPB * ROWS && p < a.N) {
+            const SettleSums q = sh.sums[i];
+            const T dist = sh.dist[i];
+            a.labels[p] = q.j;
+            if (mindist) mindist[p] = dist;
+            if (!bound(q, dist, thr[k])) mine[k] = atomicAdd(&sh.n, 1);
+        }
+    }
+    __syncthreads();
+    if (sh.n == 0) return;
+    const int which = (int)(block % a.lists);
+    if (tid == 0) sh.base = atomicAdd(a.list_count + which * LIST_STRIDE, sh.n);
+    __syncthreads();
+    const int64_t slot0 = (int64_t)which * a.list_cap + sh.base;
+#pragma unroll
+    for (int k = 0; k < (RPB * ROWS + 255) / 256; ++k) {
+        if (mine[k] < 0) continue;
+        const int i = k * 256 + tid;
+        if (a.list)
+            a.list[slot0 + mine[k]] = ScanListed{(int32_t)(first + i), thr[k]};
+        else
+            a.wl[slot0 + mine[k]] = (int32_t)(first + i);
+    }
+}
+
+template <typename T, int L, int KIND>
+__global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T *C, T *mindist, SettleArgs a)
+{
+    __shared__ SettleShared<T, L, settle_rows(sizeof(T))> sh;
+    settle_block<T, L, settle_rows(sizeof(T)), KIND>(X, C, mindist, a, blockIdx.x, nullptr,
+                                                     KIND == SETTLE_HALF && a.gate.half(), false, sh);
+}
+
+// The points of a scan's workgroup, settled by it where no other one shares them: their records stay in LDS, and its
+// requests travel while other workgroups multiply; a pass of its own waits for them with nothing else to do, after a launch
+// and a read of what the scan has just written.  Passes apart / as one, whole calls, us:
+//   2 lanes a row  2^20 x 8, K = 1024 136.9 / 130.1; 10^6 x 12, K = 700 150 / 140; fp64 2^20 x 6, K = 300 80 / 72
+//   4              1.5 * 10^6 x 16, K = 300 116 / 106; 700000 x 24, K = 1000 120 / 109; fp64 500000 x 20, K = 1000 121 / 115
+//   8              2^21 x 32, K = 4096 762 / 733; 971508 x 27, K = 781 153 / 153.  Two pieces alone, where half_pays() is not
+//                  met (fewer workgroups a unit, fewer centroids): 1864205 x 29, K = 89 133 / 162; 749932 x 29, K = 417 106 / 112
+//   33 features or more: 10^6 x 40, K = 700 178 / 186; 10^6 x 33, K = 50 87 / 91; 300000 x 96, K = 2000 206 / 209
+struct SettleOwn {
+    const void *C;   // NULL: scan_settle_kernel follows
+    void *mindist;
+    SettleArgs s;
+};
+constexpr int OWN_D = 32;  // features of a row, at most
+// Rows a group of lanes settles at once, within the registers of the scan: eight lanes, four rows of fp32 spill 128 bytes of
+// the fp16 form (2^21 x 32, K = 4096 758 us against 750), four lanes do better with them (700000 x 24, K = 1000 112, 118).
+constexpr int own_rows(size_t element, int lanes) { return element == 4 && lanes == 4 ? 4 : 2; }
+template <typename T, int L>
+struct OwnShared {
+    ScanRecord rec[SC_POINTS];
+    SettleShared<T, L, own_rows(sizeof(T), L)> sh;
+};
+template <typename T, int L, int KIND>
+__device__ __forceinline__ void settle_own(const void *X, const SettleOwn &o, int pb, const bool half, OwnShared<T, L> &sh)
+{
+    constexpr int ROWS = own_rows(sizeof(T), L), N = 256 / L * ROWS, BLOCKS = SC_POINTS / N;
+    for (int i = 0; i < BLOCKS; ++i) {
+        const int64_t block = (int64_t)pb * BLOCKS + i;
+        if (block * N >= o.s.N) break;
+        if (i) __syncthreads();
+        settle_block<T, L, ROWS, KIND>((const T *)X, (const T *)o.C, (T *)o.mindist, o.s, block, sh.rec + i * N, half, i > 0, sh.sh);
+    }
+}
+
 // ---- scan of rows of up to 128 features ---------------------------------------------------------
 // A wave keeps the pieces of its 2 x 32 points in registers for the whole sweep; the centroid image
 // passes through LDS in chunks of 16 or 32 KB, the next chunk copied (global memory to LDS, no
 // registers) while the current one is multiplied.  Fragments are stored lane by lane, so the copy is
-// linear and the reads are free of bank conflicts.  No settlement code: at 128 features 228 registers,
-// two workgroups of four waves per compute unit that wait at their own barriers.
+// linear and the reads are free of bank conflicts.  Rows of up to 32 features are settled here too (SettleOwn); longer
+// ones are not: at 128 features 228 registers, two workgroups of four waves per compute unit that wait at their own barriers.
 // waves of a SIMD whose registers suffice
 constexpr int resident_waves(int nb, int form, bool wide, bool ragged)
 {
@@ -614,7 +907,7 @@ constexpr int resident_waves(int nb, int form, bool wide, bool ragged)
 }
 // GATED: part of a call that chooses its form (the check alone, ahead of all other requests, is 1 us of 38 at 300007 x 45).
 template <typename T, int NB, int FORM, bool RAG, bool GATED>
-__global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8, RAG)) void scan_resident_kernel(ScanArgs a)
+__global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8, RAG)) void scan_resident_kernel(ScanArgs a, SettleOwn own)
 {
     if (GATED && a.gate.closed<FORM>()) return;
     constexpr int FR = form_frags(FORM);
@@ -762,8 +1055,31 @@ __global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8
         int j1;
         scan_best_finish(best[pt], g, m1, j1, m2);
         const int64_t p = p0 + pt * 32 + col;
-        if (g == 0 && p < a.N) {
+        if (NB <= 2 && own.C) {
+            // the chunks are done with: every wave has passed the barrier behind the last one
+            ScanRecord *const rec = reinterpret_cast<ScanRecord *>(lds4) + (wave * SC_PT + pt) * 32 + col;
+            if (g == 0) *rec = ScanRecord{m1, m2, j1, 0};
+        } else if (g == 0 && p < a.N) {
             a.rec[(int64_t)split * a.N + p] = ScanRecord{m1, m2, j1, 0};
+        }
+    }
+    if constexpr (NB <= 2) {
+        if (!own.C) return;
+        __syncthreads();
+        constexpr int KIND = GATED ? SETTLE_HALF : SETTLE_PLAIN;
+        auto settle = [&](auto lanes) {
+            constexpr int L = decltype(lanes)::value;
+            settle_own<T, L, KIND>(a.X, own, pb, FORM == FORM_HALF, *reinterpret_cast<OwnShared<T, L> *>(lds4));
+        };
+        // an octet's rows go to two lanes, a triple's to two or four, those of two blocks to four or eight
+        if constexpr (FORM == FORM_OCTET) {
+            settle(std::integral_constant<int, 2>{});
+        } else if constexpr (FORM == FORM_TRIPLE) {
+            if (settle_lanes(a.D) == 2) settle(std::integral_constant<int, 2>{});
+            else settle(std::integral_constant<int, 4>{});
+        } else {
+            if (settle_lanes(a.D) == 4) settle(std::integral_constant<int, 4>{});
+            else settle(std::integral_constant<int, 8>{});
         }
     }
 }
@@ -1095,221 +1411,6 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
         }
         const int64_t p = p0 + tid;
         if (p < a.N) a.rec[p] = ScanRecord{b1, b2, j, 0};
-    }
-}
-
-// ---- settle -----------------------------------------------------------------------------------
-// L lanes share a row (row-contiguous 16-byte loads) and take ROWS of them at once: the pass is a
-// chain of latencies - record, then the centroid's row - that only requests in flight can hide.
-// A workgroup hands its listed points over with one atomic, to one of 64 lists: atomics on one word
-// follow one another at about 10 ns (2^21 x 32, K = 4096: 9 000 workgroups with something to list).
-struct SettleArgs {
-    ScanRecord *rec;
-    int splits;
-    const float4 *tile_stat;
-    int tiles;
-    const double *scale;
-    int64_t N;
-    int D, K;
-    float psi, lost;    // rounding of a score; what is lost of ||x|| ||c|| whatever the centroids
-    float lift;         // by which multiple of ||c||^2 the scores were raised
-    const float *norm;  // ||c||
-    float sums;         // rounding of a sum of squares over a row, halved
-    float slack, tiny;  // of the measured norms: their own rounding, and what underflow takes from them
-    int32_t *labels;
-    ScanListed *list;  // (point, score a candidate needs), or NULL: the points alone go to wl
-    int32_t *wl, *list_count;
-    int lists, list_cap;
-    int32_t *tickets;   // [N/32 + 1] cleared here for the pass that follows
-    // scans on fp16 pieces: their numbers where the gate chooses them
-    ScanGate gate;
-    int half_splits;
-    float half_psi, half_lift, half_tiny;
-    const void *ref;    // [D] the reference r
-};
-
-enum SettleKind : int {
-    SETTLE_PLAIN = 0,   // distances in the data's type
-    SETTLE_DOUBLE = 1,  // in double, added up in the order of group_sqdist(): whatever passes a point goes through, and so
-                        // whichever form scanned it (batches of a step take the one that is faster for their size), its
-                        // distance has the same bits; fp32 2^21 x 32, K = 4096 859 / 860 us a call, 60000 x 1024 343 / 344
-    SETTLE_HALF = 2     // the same, and the records may come from fp16 pieces
-};
-template <typename T, int L, int KIND>
-__global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T *C, T *mindist, SettleArgs a)
-{
-    constexpr bool HALF = KIND == SETTLE_HALF;
-    using Acc = std::conditional_t<KIND == SETTLE_PLAIN, T, double>;
-    const bool half = HALF && a.gate.half();
-    const int splits = half ? a.half_splits : a.splits;
-    const float psi = half ? a.half_psi : a.psi, lift = half ? a.half_lift : a.lift, tiny = half ? a.half_tiny : a.tiny;
-    constexpr int ROWS = settle_rows(sizeof(T));
-    constexpr int RPB = 256 / L;  // rows side by side
-    constexpr int Q = HALF ? 4 : 3;
-    __shared__ float sh_max[4][Q];
-    __shared__ int sh_n, sh_base;
-    __shared__ int32_t sh_lab[RPB * ROWS];   // ~label for listed points
-    __shared__ T sh_dist[RPB * ROWS];
-    __shared__ float sh_thr[RPB * ROWS];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int sub = tid & (L - 1), grp = tid / L;
-    const int Dq = a.D & ~3;
-    const int64_t first = (int64_t)blockIdx.x * (ROWS * RPB);
-    int at[ROWS];  // of the rows, from the first one
-    float m1[ROWS], m2[ROWS];
-    int j[ROWS];
-    const T *c[ROWS];
-    const T *const X0 = X + first * a.D;
-    const ScanRecord *rec = a.rec + first;
-    Quad<T> xv[ROWS];
-#pragma unroll
-    for (int u = 0; u < ROWS; ++u) {
-        at[u] = (int)min((int64_t)(u * RPB + grp), a.N - 1 - first);
-        const ScanRecord r = rec[at[u]];
-        m1[u] = r.m1;
-        m2[u] = r.m2;
-        j[u] = r.j1;
-    }
-    // the first piece of every row travels with the records
-#pragma unroll
-    for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(X0 + (unsigned)(at[u] * a.D + min(4 * sub, Dq - 4)));
-    if (tid == 0) sh_n = 0;
-    const int64_t i0 = (int64_t)blockIdx.x * 256 + tid;
-    if (i0 * 32 < a.N) a.tickets[i0] = 0;
-    float cm[Q] = {};
-    for (int i = tid; i < a.tiles; i += 256) {
-        const float4 t = a.tile_stat[i];
-        cm[0] = fmaxf(cm[0], t.x);
-        cm[1] = fmaxf(cm[1], t.y);
-        cm[2] = fmaxf(cm[2], t.z);
-        if constexpr (HALF) cm[3] = fmaxf(cm[3], t.w);
-    }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        cm[q] = wave_max(cm[q]);
-        if (lane == 0) sh_max[tid >> 6][q] = cm[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < Q; ++q) cm[q] = fmaxf(fmaxf(sh_max[0][q], sh_max[1][q]), fmaxf(sh_max[2][q], sh_max[3][q]));
-    const float cmax = 1.000001f * sqrtf(cm[0]) + tiny;
-    // a score of centroid c is off by at most A ||c|| + psi ||c||^2 / 2, A = lost ||x|| + psi (||x|| + ||r||); ||x1|| <= 2^-8 ||x||
-    // (fp16 pieces: lost ||x|| is ||r_x|| + max(||r_c|| / ||c||) ||x||, the first measured below)
-    const float lost = half ? 1.001f * a.slack * sqrtf(cm[Q - 1])
-                            : a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
-    const T s = (T)a.scale[0];
-    const float ref = 1.000001f * (float)a.scale[1] + tiny;  // ||r||
-    const float under = (float)((T)(a.D + 16) * std::numeric_limits<T>::min() * s * s);
-    for (int k = 1; k < splits; ++k) {
-#pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-            const ScanRecord o = rec[(int64_t)k * a.N + at[u]];
-            const bool mine = m1[u] >= o.m1;
-            m2[u] = fmaxf(fmaxf(m2[u], o.m2), mine ? o.m1 : m1[u]);
-            m1[u] = mine ? m1[u] : o.m1;
-            j[u] = mine ? j[u] : o.j1;
-        }
-    }
-    Acc d[ROWS];
-    float xn[ROWS], yn[ROWS], cn[ROWS], xr[ROWS];  // of x and of x - r, of c, of what an fp16 piece leaves of x
-#pragma unroll
-    for (int u = 0; u < ROWS; ++u) {
-        j[u] = (unsigned)j[u] < (unsigned)a.K ? j[u] : 0;  // padding rows, when no score was a number
-        c[u] = C + (size_t)j[u] * a.D;
-        cn[u] = a.norm[j[u]];
-        d[u] = Acc(0);
-        xn[u] = yn[u] = xr[u] = 0.f;
-    }
-    const T *const ref_row = (const T *)a.ref;
-    auto add = [&](int u, T xe, T ce, T re) {
-        const Acc t = (Acc)xe - (Acc)ce;
-        d[u] = fma(t, t, d[u]);
-        const float w = (float)(xe * s);
-        xn[u] = fmaf(w, w, xn[u]);
-        if constexpr (HALF) {
-            const float y = (float)((xe - re) * s);
-            yn[u] = fmaf(y, y, yn[u]);
-            add_lost_half(w, xr[u]);
-        }
-    };
-    for (int f = 4 * sub; f < Dq;) {
-        Quad<T> cv[ROWS];
-#pragma unroll
-        for (int u = 0; u < ROWS; ++u) cv[u] = load_quad<T>(c[u] + f);
-        Quad<T> rv = {};
-        if constexpr (HALF) rv = load_quad<T>(ref_row + f);
-#pragma unroll
-        for (int u = 0; u < ROWS; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) add(u, xv[u].v[e], cv[u].v[e], rv.v[e]);
-        f += 4 * L;
-        if (f < Dq)
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) xv[u] = load_quad<T>(X0 + (unsigned)(at[u] * a.D + f));
-    }
-    for (int f = Dq + sub; f < a.D; f += L)
-#pragma unroll
-        for (int u = 0; u < ROWS; ++u) add(u, X0[(unsigned)(at[u] * a.D + f)], c[u][f], HALF ? ref_row[f] : T(0));
-#pragma unroll
-    for (int u = 0; u < ROWS; ++u) {
-        const T dist = (T)group_sum<L>(d[u]);
-        const float norm = a.slack * sqrtf(group_sum<L>(xn[u])) + tiny;
-        float A = lost * norm + psi * (norm + ref);
-        const float B = lift - 0.5f * psi;
-        if constexpr (HALF) A += half ? 1.001f * a.slack * sqrtf(group_sum<L>(xr[u])) : 0.f;
-        const float c1 = 1.000001f * cn[u] + tiny, t = fminf(A / (2.f * B), cmax);  // the norm most too low
-        // How much too low the score of any centroid is, at most, and how much too high that of the named one.
-        const float low = 1.00001f * ((A - B * t) * t + (A + psi * cmax) * tiny) + SCAN_FLOOR;
-        const float high = 1.00001f * (A + (lift + 0.5f * psi) * c1) * c1;
-        float least = m1[u] - high;
-        if constexpr (HALF) {
-            // Its true score is also known from the distance, (||x - r||^2 - ||x - c||^2) / 2, to within the rounding of
-            // these sums: of fp16 pieces that halves the bound (2^21 x 32, K = 4096: 68 000 points listed against 105 000).
-            // The distance comes from differences that carry no scale: `under` is what underflow may have taken from it,
-            // infinite (a distance out of range: d2) where these sums say nothing.
-            const float y2 = group_sum<L>(yn[u]), d2 = (float)(dist * s * s);
-            least = fmaxf(least, 0.5f * (y2 - d2) - a.sums * (y2 + d2) - under);
-        }
-        least -= low;
-        // No score means anything where one may have left the fp32 range (||c||^2 or a product infinite, also on
-        // the way to a sum that is not): a threshold that is not a number makes every centroid a candidate.
-        const bool sound = (norm + ref + cmax) * cmax < 1e38f && (!half || fmaxf(norm, cmax) < HALF_RANGE);
-        const bool listed = !sound || !(least > m2[u]);
-        if (sub == 0) {
-            sh_lab[u * RPB + grp] = listed ? ~j[u] : j[u];
-            sh_dist[u * RPB + grp] = dist;
-            sh_thr[u * RPB + grp] = sound ? least : __builtin_nanf("");
-        }
-    }
-    __syncthreads();
-    // results and the list leave in whole lines
-    int mine[(RPB * ROWS + 255) / 256];
-#pragma unroll
-    for (int k = 0; k < (RPB * ROWS + 255) / 256; ++k) {
-        const int i = k * 256 + tid;
-        const int64_t p = first + i;
-        mine[k] = -1;
-        if (i < RPB * ROWS && p < a.N) {
-            const int v = sh_lab[i];
-            a.labels[p] = v < 0 ? ~v : v;
-            if (mindist) mindist[p] = sh_dist[i];
-            if (v < 0) mine[k] = atomicAdd(&sh_n, 1);
-        }
-    }
-    __syncthreads();
-    if (sh_n == 0) return;
-    const int which = (int)blockIdx.x % a.lists;
-    if (tid == 0) sh_base = atomicAdd(a.list_count + which * LIST_STRIDE, sh_n);
-    __syncthreads();
-    const int64_t slot0 = (int64_t)which * a.list_cap + sh_base;
-#pragma unroll
-    for (int k = 0; k < (RPB * ROWS + 255) / 256; ++k) {
-        if (mine[k] < 0) continue;
-        const int i = k * 256 + tid;
-        if (a.list)
-            a.list[slot0 + mine[k]] = ScanListed{(int32_t)(first + i), sh_thr[i]};
-        else
-            a.wl[slot0 + mine[k]] = (int32_t)(first + i);
     }
 }
 
@@ -2386,11 +2487,12 @@ ScanBuffers carve_scan(void *base, const ScanPlan &p, int64_t N, int D)
 }
 
 template <typename T, int NB, int FORM>
-static void launch_resident(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
+static void launch_resident(const ScanArgs &a, const ScanPlan &p, const SettleOwn &own, hipStream_t st)
 {
     const dim3 grid((unsigned)(p.pblocks * p.splits)), block(SC_THREADS);
-    const size_t lds = 2 * ((size_t)p.tpc * NB * form_frags(FORM) * FRAG_UNITS + (size_t)((p.tpc + 1) / 2) * 16) * 16;
-    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a); };
+    size_t lds = 2 * ((size_t)p.tpc * NB * form_frags(FORM) * FRAG_UNITS + (size_t)((p.tpc + 1) / 2) * 16) * 16;
+    if (own.C && lds < sizeof(OwnShared<T, 2>)) lds = sizeof(OwnShared<T, 2>);  // that of fewest lanes is the largest
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a, own); };
     const bool ragged = a.D % 4 != 0;
     if constexpr (FORM == FORM_PAIR || FORM == FORM_HALF) {
         if (a.gate.refused) {
@@ -2434,7 +2536,7 @@ static void launch_points(const ScanArgs &a, const ScanPlan &p, hipStream_t st)
 
 // the scan in form p.form of a call that `a` describes but for the cut
 template <typename T>
-static void launch_scan_form(ScanArgs a, const ScanPlan &p, hipStream_t st)
+static void launch_scan_form(ScanArgs a, const ScanPlan &p, const SettleOwn &own, hipStream_t st)
 {
     a.tiles = p.tiles;
     a.tpc = p.tpc;
@@ -2455,14 +2557,14 @@ static void launch_scan_form(ScanArgs a, const ScanPlan &p, hipStream_t st)
         default: launch_stream<T, 4>(a, p, st); break;
         }
     } else if (p.form == FORM_OCTET) {
-        launch_resident<T, 1, FORM_OCTET>(a, p, st);
+        launch_resident<T, 1, FORM_OCTET>(a, p, own, st);
     } else if (p.form == FORM_TRIPLE) {
-        launch_resident<T, 1, FORM_TRIPLE>(a, p, st);
+        launch_resident<T, 1, FORM_TRIPLE>(a, p, own, st);
     } else {
 #define FTK_LAUNCH_RESIDENT(NB)                                                   \
     case NB:                                                                      \
-        if (p.form == FORM_HALF) launch_resident<T, NB, FORM_HALF>(a, p, st);     \
-        else launch_resident<T, NB, FORM_PAIR>(a, p, st);                         \
+        if (p.form == FORM_HALF) launch_resident<T, NB, FORM_HALF>(a, p, own, st);     \
+        else launch_resident<T, NB, FORM_PAIR>(a, p, own, st);                         \
         break
         switch (p.nb) {
             FTK_LAUNCH_RESIDENT(2);
@@ -2507,18 +2609,18 @@ static void launch_recheck(const AssignCall &c, const ScanPlan &h, const ScanArg
 }
 
 template <typename T, int L>
-static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, ResolveArgs r, const ScanBuffers &b,
-                          const ScanPlan &ph, const ScanArgs &ah, hipStream_t st)
+static void launch_settle(const AssignCall &c, const ScanPlan &p, const SettleArgs &s, bool own, ResolveArgs r,
+                          const ScanBuffers &b, const ScanPlan &ph, const ScanArgs &ah, hipStream_t st)
 {
     const int rows = 256 / L * settle_rows(sizeof(T));
     static_assert(256 / L * settle_rows(sizeof(T)) <= SETTLE_ROWS_MAX, "list capacity");
-    // a lane adds up its share, a tree of six the lanes'; 10 u for the differences, their squares and the scale
-    s.sums = 0.5f * (float)((c.D / L + 4 + 6 + 10) * (double)Mma<float>::kEps);
-    r.list_cap = s.list_cap = (int)ceil_div(ceil_div(c.N, rows), s.lists) * rows;
+    r.list_cap = s.list_cap;
     const dim3 sg((unsigned)ceil_div(c.N, rows)), sb(256);
     const bool half = L >= 4 && p.half;
     auto settle = [&](auto kernel) { hipLaunchKernelGGL(kernel, sg, sb, 0, st, (const T *)c.X, (const T *)c.C, (T *)c.mindist, s); };
-    if constexpr (L >= 4) {
+    if (own) {
+        // the scan's workgroups have done it
+    } else if constexpr (L >= 4) {
         if (half) settle(scan_settle_kernel<T, L, SETTLE_HALF>);
         else if (sizeof(T) == 4 && p.either) settle(scan_settle_kernel<T, L, SETTLE_DOUBLE>);
         else settle(scan_settle_kernel<T, L, SETTLE_PLAIN>);
@@ -2580,6 +2682,14 @@ static void launch_settle(const AssignCall &c, const ScanPlan &p, SettleArgs s, 
         }
     }
 #undef FTK_LAUNCH_RESOLVE
+}
+
+// Where the workgroups of the scan settle their points themselves: see SettleOwn for where the lines lie.  Of two pieces
+// alone in fp32 only the sums in the data's type are built; a part of a call that chooses its form takes those in double.
+static bool settles_own(const ScanPlan &p, const ScanPlan &ph, ftk_dtype dtype, int D)
+{
+    if (D > OWN_D || p.splits != 1 || (!p.half && settle_lanes(D) > 4)) return false;
+    return p.half ? ph.splits == 1 : !(dtype == FTK_F32 && p.either);
 }
 
 // tiles: those of the image to prepare (0: they are); whole: the problem that c is a part of
@@ -2692,16 +2802,27 @@ static ftk_status launch_scan_t(const AssignCall &c, const ScanPlan &p, const Sc
     r.list_count = b.list_count;
     r.tickets = b.tickets;
     r.stats = c.stats;
-    auto settle = [&](const SettleArgs &q) {
-        if (c.D <= 12) launch_settle<T, 2>(c, p, q, r, b, ph, ah, st);
-        else if (c.D <= 24) launch_settle<T, 4>(c, p, q, r, b, ph, ah, st);
-        else if (c.D <= 128) launch_settle<T, 8>(c, p, q, r, b, ph, ah, st);
-        else if (c.D <= 512) launch_settle<T, 16>(c, p, q, r, b, ph, ah, st);
-        else launch_settle<T, 64>(c, p, q, r, b, ph, ah, st);
-    };
-    if (p.half) launch_scan_form<T>(ah, ph, st);
-    launch_scan_form<T>(a, p, st);
-    settle(s);
+    const int lanes = settle_lanes(c.D);
+    // a lane adds up its share, a tree of six the lanes'; 10 u for the differences, their squares and the scale
+    s.sums = 0.5f * (float)((c.D / lanes + 4 + 6 + 10) * u);
+    SettleOwn own = {};
+    if (settles_own(p, ph, c.dtype, c.D)) {
+        own.C = c.C;
+        own.mindist = c.mindist;
+    }
+    const int rows = 256 / lanes * (own.C ? own_rows(sizeof(T), lanes) : settle_rows(sizeof(T)));
+    s.list_cap = (int)ceil_div(ceil_div(c.N, rows), s.lists) * rows;
+    own.s = s;
+    if (p.half) launch_scan_form<T>(ah, ph, own, st);
+    launch_scan_form<T>(a, p, own, st);
+    auto settle = [&](auto l) { launch_settle<T, decltype(l)::value>(c, p, s, own.C != nullptr, r, b, ph, ah, st); };
+    switch (lanes) {
+    case 2: settle(std::integral_constant<int, 2>{}); break;
+    case 4: settle(std::integral_constant<int, 4>{}); break;
+    case 8: settle(std::integral_constant<int, 8>{}); break;
+    case 16: settle(std::integral_constant<int, 16>{}); break;
+    default: settle(std::integral_constant<int, 64>{}); break;
+    }
     FTK_TRY_HIP(hipGetLastError());
     return p.resolve ? FTK_OK : launch_refine(c, w, 0, st);
 }
