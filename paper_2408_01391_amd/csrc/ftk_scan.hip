@@ -1275,25 +1275,32 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
     const T *X = reinterpret_cast<const T *>(a.X);
     const T s = (T)a.scale[0];
     {
-        // wave w rounds point tile w % PT, every (8 / PT)th group of BATCH blocks
+        // Wave w rounds point tile w % PT, every (8 / PT)th group of BATCH blocks.  Eight lanes take 32 features of a row, whole
+        // lines of memory, and eight rows at a time: with a lane to a row a request names 64 places, one after the other (whole
+        // calls 60000 x 1024, K = 1024 325 / 320 us, 131072 x 512, K = 1000 287 / 279, 150000 x 200, K = 700 154 / 154).
         constexpr int BATCH = sizeof(T) == 4 ? 8 : 4;
-        const int pt = wave % PT;
-        const int64_t pr = min(p0 + pt * 32 + col, a.N - 1);
-        const RowReader<T, RAG> row(X + pr * a.D, a.D);
+        const int pt = wave % PT, q8 = lane & 7, r8 = lane >> 3;
+        auto reader = [&](int i) { return RowReader<T, RAG>(X + min(p0 + pt * 32 + 8 * i + r8, a.N - 1) * a.D, a.D); };
+        const RowReader<T, RAG> rows[4] = {reader(0), reader(1), reader(2), reader(3)};
+        uint2 *const to = reinterpret_cast<uint2 *>(lds4 + pt * FRAG_UNITS + (q8 >> 1 & 1) * 32 + r8) + (q8 & 1);
         for (int b0 = wave / PT * BATCH; b0 < nb; b0 += SP_WAVES / PT * BATCH) {
-            Quad<T> q[2 * BATCH];
+            Quad<T> q[BATCH / 2][4];
 #pragma unroll
-            for (int u = 0; u < 2 * BATCH; ++u) q[u] = row.request(16 * (b0 + (u >> 1)) + 8 * g + 4 * (u & 1));
+            for (int k = 0; k < BATCH / 2; ++k)
 #pragma unroll
-            for (int k = 0; k < BATCH; ++k) {
-                float v[8];
+                for (int i = 0; i < 4; ++i) q[k][i] = rows[i].request(16 * (b0 + 2 * k) + 4 * q8);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const Quad<T> w = row.keep(q[2 * k + h], 16 * (b0 + k) + 8 * g + 4 * h);
+            for (int k = 0; k < BATCH / 2; ++k) {
+                const int b = b0 + 2 * k + (q8 >> 2);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
+                for (int i = 0; i < 4; ++i) {
+                    const Quad<T> w = rows[i].keep(q[k][i], 16 * (b0 + 2 * k) + 4 * q8);
+                    typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
+                    halfx4 h;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) h[e] = (_Float16)(float)(w.v[e] * s);
+                    if (b < nb) to[2 * (b * PT * FRAG_UNITS + 8 * i)] = __builtin_bit_cast(uint2, h);
                 }
-                if (b0 + k < nb) lds4[((b0 + k) * PT + pt) * FRAG_UNITS + lane] = round_half(v);
             }
         }
     }

@@ -65,6 +65,14 @@ def test_labels_and_distances_at_the_edges(dtype, N, D, K):
     check(*blobs(N + D, N, D, K, dtype), dtype, half=True)
 
 
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 75001, 131, 1300), ("f32", 66017, 150, 1300), ("f32", 60007, 160, 1300), ("f32", 35009, 511, 700),
+                                         ("f32", 33031, 1019, 400), ("f64", 70023, 203, 900), ("f64", 48001, 529, 480)])
+def test_rows_that_end_anywhere_in_a_line(dtype, N, D, K):
+    """Long rows are rounded 32 features of eight rows at a time: every place of a row's end among them, partial blocks of rows."""
+    print("half", dtype, N, D, K, flush=True)
+    check(*blobs(N + D, N, D, K, dtype), dtype, half=True)
+
+
 # 25 and 35 tiles of centroids: rows of 3 and 6 blocks, whose bf16 image is padded by a tile more than the fp16 chunks take
 @pytest.mark.parametrize("dtype,N,D,K", [("f32", 400001, 48, 800), ("f32", 290003, 47, 1120), ("f32", 210011, 96, 777),
                                          ("f32", 150001, 91, 1120), ("f64", 530001, 96, 800), ("f64", 750001, 48, 1119)])
