@@ -68,6 +68,8 @@
 namespace ftk {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 constexpr int SC_THREADS = 256;  // resident scan: four waves of two point tiles
 constexpr int SC_PT = 2;
@@ -1109,17 +1111,20 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
     const int nb = 2 * ns;  // blocks per tile of the image
     const int wp = wave & 3, wc = wave >> 2;
 
-    // the features this thread brings in: 16 of block kb of row `wave * 32 + lane % 32`
-    const int kb = g;
-    int64_t pr = (int64_t)pb * SC_POINTS + wave * 32 + col;
-    if (pr >= a.N) pr = a.N - 1;
+    // The features this thread brings in: four of each of four rows; eight lanes take a row's 32, whole lines of memory.  (16
+    // features of one row a lane, 64 places a request, whole calls: 500000 x 130, K = 64 149 us against 130, 131072 x 512, K = 100
+    // 139 / 131, 100000 x 301, K = 300 153 / 144, 9000 x 640, K = 1000 116 / 107; fp64 40000 x 900, K = 310 339 / 257.)
+    const int q8 = lane & 7, r8 = lane >> 3;
     const T *X = reinterpret_cast<const T *>(a.X);
-    const RowReader<T, RAG> row(X + pr * D, D);
+    auto reader = [&](int i) {
+        return RowReader<T, RAG>(X + min((int64_t)pb * SC_POINTS + wave * 32 + 8 * i + r8, a.N - 1) * D, D);
+    };
+    const RowReader<T, RAG> rows[4] = {reader(0), reader(1), reader(2), reader(3)};
     const T s = (T)a.scale[0];
     Quad<T> xq[4];
     auto request = [&](int st) {
 #pragma unroll
-        for (int h = 0; h < 4; ++h) xq[h] = row.request(32 * st + 16 * kb + 4 * h);
+        for (int i = 0; i < 4; ++i) xq[i] = rows[i].request(32 * st + 4 * q8);
     };
     auto stage_centroids = [&](int st, uint4 *buf) {
         if (TPC == 8 || wave < TPC) {
@@ -1128,19 +1133,21 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
             for (int i = 0; i < 4; ++i) to_lds16(src + i * FRAG_UNITS, buf + (wave * 4 + i) * FRAG_UNITS);
         }
     };
-    auto store_half = [&](int st, uint4 *buf, int gg) {  // features 8gg .. 8gg + 7 of the block
-        float v[8];
+    auto store = [&](int st, uint4 *buf) {
+        uint2 *const dst = reinterpret_cast<uint2 *>(buf + AU + (wave * 4 + 2 * (q8 >> 2)) * FRAG_UNITS + (q8 >> 1 & 1) * 32 + r8) + (q8 & 1);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const Quad<T> w = row.keep(xq[2 * gg + h], 32 * st + 16 * kb + 8 * gg + 4 * h);
+        for (int i = 0; i < 4; ++i) {
+            const Quad<T> w = rows[i].keep(xq[i], 32 * st + 4 * q8);
+            bf16x4 hi, lo;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * h + e] = (float)(w.v[e] * s);
+            for (int e = 0; e < 4; ++e) {
+                const float v = (float)(w.v[e] * s);
+                hi[e] = (__bf16)v;
+                lo[e] = (__bf16)(v - (float)hi[e]);  // the difference is exact
+            }
+            dst[16 * i] = __builtin_bit_cast(uint2, hi);
+            dst[16 * i + 2 * FRAG_UNITS] = __builtin_bit_cast(uint2, lo);
         }
-        uint4 hi, lo;
-        split_pair(v, hi, lo);
-        uint4 *dst = buf + AU + (wave * 4 + 2 * kb) * FRAG_UNITS + gg * 32 + col;
-        dst[0] = hi;
-        dst[FRAG_UNITS] = lo;
     };
 
     floatx16 acc[CT][SC_PT];
@@ -1157,8 +1164,7 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
     }
     request(0);
     stage_centroids(0, lds4);
-    store_half(0, lds4, 0);
-    store_half(0, lds4, 1);
+    store(0, lds4);
     request(min(1, ns - 1));
     wait_loads<0>();
     __syncthreads();
@@ -1197,8 +1203,7 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
                     acc[c][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, x0[pt], acc[c][pt], 0, 0, 0);
             }
         }
-        store_half(min(st + 1, ns - 1), nxt, 0);
-        store_half(min(st + 1, ns - 1), nxt, 1);
+        store(min(st + 1, ns - 1), nxt);
         // fp32: reads two fragments ahead of the matrix instructions, the split after them - the rows requested
         // at the end of the last stage are then there, and the other wave of the SIMD fills its time.  (Spread
         // between the second block's instructions it waited for the rows: 60000 x 1024, K = 1024 461 us a call
@@ -1295,7 +1300,6 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const Quad<T> w = rows[i].keep(q[k][i], 16 * (b0 + 2 * k) + 4 * q8);
-                    typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
                     halfx4 h;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) h[e] = (_Float16)(float)(w.v[e] * s);
