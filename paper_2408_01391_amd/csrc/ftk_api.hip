@@ -32,7 +32,7 @@ ftk_status hip_failed(hipError_t e, const char *what)
     return FTK_EDEVICE;
 }
 
-void plan_generic(ftk_dtype dtype, int64_t N, int D, int K, AssignPlan &p);
+void plan_generic(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p);
 void plan_smalld(int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p);
 bool smalld_supported(ftk_dtype dtype, int D, int K);
 void plan_midd(int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p);
@@ -93,7 +93,7 @@ AssignPlan plan_assign(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft,
     else if (aligned16 && midd_supported(dtype, D, K) && want_midd)
         plan_midd(N, D, K, ft, p);
     else
-        plan_generic(dtype, N, D, K, p);
+        plan_generic(dtype, N, D, K, ft, p);
     return p;
 }
 

@@ -73,7 +73,7 @@ static double generic_ft_coef(int n, int D)
 }
 
 // Blocking per wave: PT = 2 point tiles by KT centroid tiles of accumulators (KT = 8: one point
-// tile by eight centroid tiles, fp64 only), DQ quads per LDS
+// tile by eight centroid tiles, fp64 only; LINES: one point tile, see plan_generic()), DQ quads per LDS
 // stage, and the waves per SIMD the register budget is sized for.  KT = 4 is the workhorse (fp64
 // tiles are 16x16, so it leaves room for a third resident wave).  For K of at most one or two
 // tiles the stages hold little matrix work and the kernel is bound by the latency of the point
@@ -84,10 +84,12 @@ static double generic_ft_coef(int n, int D)
 // (c3: 170 against 158 us; with checksums 211 against 168 us).
 constexpr int generic_dq(bool f32, int kt) { return (f32 && kt == 4) ? GENERIC_DQ_F32_KT4 : 2; }
 
-template <typename T, int KT_>
+constexpr int LINES_DQ = 4;  // of a stage whose rows pass through LDS (fp32): 128 bytes
+
+template <typename T, int KT_, bool LINES = false>
 struct GenericCfg {
-    static constexpr int PT = KT_ == 8 ? 1 : 2, KT = KT_, WAVES = 4;
-    static constexpr int DQ = generic_dq(sizeof(T) == 4, KT_);
+    static constexpr int PT = KT_ == 8 || LINES ? 1 : 2, KT = KT_, WAVES = 4;
+    static constexpr int DQ = LINES ? LINES_DQ : generic_dq(sizeof(T) == 4, KT_);
     static constexpr int WAVES_PER_SIMD = KT_ == 8 ? 2 : (KT_ == 4 ? (sizeof(T) == 4 ? 2 : 3) : (KT_ == 2 ? 3 : 4));
 };
 // number of accumulator tiles used for a problem with K centroids
@@ -98,12 +100,16 @@ constexpr int generic_kt(int K) { return K <= Mma<T>::TM ? 1 : (K <= 2 * Mma<T>:
 // real centroids only (K a multiple of the chunk) - the stage loop is then compiled without its
 // per-quad, per-tile and per-element conditions: one straight run of matrix instructions per stage
 // instead of a branch every KT of them, and no masking selects on the point fragments.
-template <typename T, int KTV, int AL, bool FT, bool FULL>
-__global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void assign_generic_kernel(GenericArgs<T> a)
+//
+// LINES: the rows pass through LDS (plan_generic() tells when).
+template <typename T, int KTV, int AL, bool FT, bool FULL, bool LINES = false>
+__global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD))
+void assign_generic_kernel(GenericArgs<T> a)
 {
+    static_assert(!LINES || (sizeof(T) == 4 && KTV <= 2 && AL != ROWS_ELEMENTS), "rows of whole pieces, one chunk");
     static_assert(AL == ROWS_ALIGNED || !FULL, "the condition-free stage loop is compiled for aligned rows only");
     using M = Mma<T>;
-    using Cfg = GenericCfg<T, KTV>;
+    using Cfg = GenericCfg<T, KTV, LINES>;
     using frag_t = typename M::frag_t;
     using acc_t = typename M::acc_t;
     constexpr int TM = M::TM, TN = M::TN, R = M::R, E = M::E;
@@ -271,11 +277,55 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
     // instead of coming back for its second half a thousand cycles later.
     // Features beyond D hold copies of valid ones: the staged centroid rows are zero there, so they
     // add nothing to the scores; the norm masks them explicitly.
-    frag_t xs[PT][DQ];
+    frag_t xs[PT][LINES ? 1 : DQ];
+    // LINES: eight lanes take the 128 bytes of a stage of one row, eight rows at a time; the wave's share of LDS hands them to
+    // the lanes that multiply them.  Slot of a piece: its number, turned by the row's, so that neither side meets a bank twice.
+    // The best tile's slots take the same place: they are written once the last stage has been read.
+    constexpr int XR = LINES ? PT * TN / 8 : 1;
+    const int q8 = lane & 7, r8 = lane >> 3;
+    unsigned char *const lds_x = lds_best + wave * (PT * TN * 128);
+    frag_t xl[XR];
+    unsigned xo[XR];
+    if constexpr (LINES) {
+        static_assert(DQ * 8 == 8 * E && TN * 128 == R * (int)sizeof(T) * 64, "128 bytes a row; one place for both");
+        const int64_t row0 = (int64_t)blockIdx.x * (Cfg::WAVES * PT * TN);
+        const int last = (int)min((int64_t)(Cfg::WAVES * PT * TN), a.N - row0) - 1;
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt)
+        for (int i = 0; i < XR; ++i) xo[i] = (unsigned)min(wave * (PT * TN) + 8 * i + r8, last) * (unsigned)D;
+    }
+    auto request_x = [&](int q0) {
 #pragma unroll
-        for (int q = 0; q < DQ; ++q) xs[pt][q] = load_x(pt, q);
+        for (int i = 0; i < XR; ++i) {
+            if constexpr (FULL)
+                xl[i] = *reinterpret_cast<const frag_t *>(xbase + (xo[i] + (unsigned)(q0 * 8 + q8 * E)) * (unsigned)sizeof(T));
+            else
+                xl[i] = load_frag_clamped<T, AL>(reinterpret_cast<const T *>(xbase) + xo[i], q0 * 8 + q8 * E, D);
+        }
+    };
+    auto turn_x = [&](int q0) {
+#pragma unroll
+        for (int i = 0; i < XR; ++i) {
+            frag_t v = xl[i];
+            if (AL == ROWS_PIECES && (q0 + DQ) * 8 > D) v = frag_place<T>(v, q0 * 8 + q8 * E, D);
+            const int row = 8 * i + r8;
+            *reinterpret_cast<frag_t *>(lds_x + row * 128 + (q8 ^ (row >> 1 & 7)) * 16) = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // by this wave's other lanes
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto turned_x = [&](int pt, int q) {
+        const int row = pt * TN + col;
+        return *reinterpret_cast<const frag_t *>(lds_x + row * 128 + ((q * (8 / E) + g) ^ (row >> 1 & 7)) * 16);
+    };
+    if constexpr (LINES) {
+        request_x(0);
+    } else {
+#pragma unroll
+        for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+            for (int q = 0; q < DQ; ++q) xs[pt][q] = load_x(pt, q);
+    }
     auto place_x = [&](int q0) {  // the stage that starts at quad q0
         if (AL == ROWS_PIECES && (q0 + DQ) * 8 > D)
 #pragma unroll
@@ -286,7 +336,8 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
 
     fetch(0, 0);
     commit(0, 0, 0);
-    place_x(0);
+    if constexpr (LINES) turn_x(0);
+    else place_x(0);
     __syncthreads();
     int buf = 0;
 
@@ -322,8 +373,10 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
             const bool more = kc_n < a.nkc;
             if (more) fetch(kc_n, dc_n);
             const unsigned char *const sbuf = lds_raw + buf * STAGE_BYTES;
-            frag_t xnx[PT][DQ];
-            {
+            frag_t xnx[LINES ? 1 : PT][DQ];
+            if constexpr (LINES) {
+                if (more) request_x(q0 + DQ);
+            } else {
                 const int qn0 = chunk_end ? 0 : q0 + DQ;
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt)
@@ -334,11 +387,17 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
 #pragma unroll
             for (int q = 0; q < DQ; ++q) {
                 if (FULL || q0 + q < nq) {
+                    frag_t xq[PT];
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt) {
+                        if constexpr (LINES) xq[pt] = turned_x(pt, q);
+                        else xq[pt] = xs[pt][q];
+                    }
                     if (kc == 0) {
                         const int d0 = (q0 + q) * 8 + E * g;
 #pragma unroll
                         for (int pt = 0; pt < PT; ++pt) {
-                            const frag_t xm = FULL ? xs[pt][q] : frag_keep<T>(xs[pt][q], d0, D, true);
+                            const frag_t xm = FULL ? xq[pt] : frag_keep<T>(xq[pt], d0, D, true);
 #pragma unroll
                             for (int e = 0; e < E; ++e) xn[pt] = fma(xm[e], xm[e], xn[pt]);
                         }
@@ -349,9 +408,9 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
                             sbuf + KC * SB + q * (8 * (int)sizeof(T)) + g * 16);
 #pragma unroll
                         for (int pt = 0; pt < PT; ++pt) {
-                            T part = xs[pt][q][0] * v[0];
+                            T part = xq[pt][0] * v[0];
 #pragma unroll
-                            for (int e = 1; e < E; ++e) part = fma(xs[pt][q][e], v[e], part);
+                            for (int e = 1; e < E; ++e) part = fma(xq[pt][e], v[e], part);
                             ref1[pt] += (double)part;
                         }
                     }
@@ -369,16 +428,20 @@ __global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD)) void ass
                             for (int e = 0; e < E; ++e)
 #pragma unroll
                                 for (int pt = 0; pt < PT; ++pt)
-                                    acc[pt][t] = M::mma(av[t][e], xs[pt][q][e], acc[pt][t]);
+                                    acc[pt][t] = M::mma(av[t][e], xq[pt][e], acc[pt][t]);
                         }
                     }
                 }
             }
+            if constexpr (LINES) {
+                if (more) turn_x(q0 + DQ);
+            } else {
 #pragma unroll
-            for (int pt = 0; pt < PT; ++pt)
+                for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-                for (int q = 0; q < DQ; ++q) xs[pt][q] = xnx[pt][q];
-            place_x(chunk_end ? 0 : q0 + DQ);
+                    for (int q = 0; q < DQ; ++q) xs[pt][q] = xnx[pt][q];
+                place_x(chunk_end ? 0 : q0 + DQ);
+            }
             if (more) commit(kc_n, dc_n, buf ^ 1);
             __syncthreads();
             buf ^= 1;
@@ -983,6 +1046,8 @@ static ftk_status launch_generic_t(const AssignCall &c, const AssignPlan &p, con
                       (double)c.K * c.D * sizeof(T) < 4.0e9 && (double)p.points_per_wg * c.D * sizeof(T) < 4.0e9;
 #define FTK_LAUNCH_GEN(KV, AL, F, FU) \
     hipLaunchKernelGGL((assign_generic_kernel<T, KV, AL, F, FU>), grid, block, p.lds_bytes, st, a)
+#define FTK_LAUNCH_LINES(KV, AL, F, FU) \
+    hipLaunchKernelGGL((assign_generic_kernel<T, KV, AL, F, FU, true>), grid, block, p.lds_bytes, st, a)
 #define FTK_LAUNCH_GEN_K(KV)                          \
     do {                                              \
         if (full && ft) FTK_LAUNCH_GEN(KV, ROWS_ALIGNED, true, true);                          \
@@ -994,12 +1059,27 @@ static ftk_status launch_generic_t(const AssignCall &c, const AssignPlan &p, con
         else if (ft) FTK_LAUNCH_GEN(KV, ROWS_ELEMENTS, true, false);                           \
         else FTK_LAUNCH_GEN(KV, ROWS_ELEMENTS, false, false);                                  \
     } while (0)
-    if (p.KT == 8) FTK_LAUNCH_GEN_K(8);
+    auto launch_lines = [&](auto kt) {
+        constexpr int KV = decltype(kt)::value;
+        if (full && ft) FTK_LAUNCH_LINES(KV, ROWS_ALIGNED, true, true);
+        else if (full) FTK_LAUNCH_LINES(KV, ROWS_ALIGNED, false, true);
+        else if (rows == ROWS_ALIGNED && ft) FTK_LAUNCH_LINES(KV, ROWS_ALIGNED, true, false);
+        else if (rows == ROWS_ALIGNED) FTK_LAUNCH_LINES(KV, ROWS_ALIGNED, false, false);
+        else if (ft) FTK_LAUNCH_LINES(KV, ROWS_PIECES, true, false);
+        else FTK_LAUNCH_LINES(KV, ROWS_PIECES, false, false);
+    };
+    if (p.lines) {
+        if constexpr (sizeof(T) == 4) {
+            if (p.KT == 1) launch_lines(std::integral_constant<int, 1>{});
+            else launch_lines(std::integral_constant<int, 2>{});
+        }
+    } else if (p.KT == 8) FTK_LAUNCH_GEN_K(8);
     else if (p.KT == 4) FTK_LAUNCH_GEN_K(4);
     else if (p.KT == 2) FTK_LAUNCH_GEN_K(2);
     else FTK_LAUNCH_GEN_K(1);
 #undef FTK_LAUNCH_GEN_K
 #undef FTK_LAUNCH_GEN
+#undef FTK_LAUNCH_LINES
     FTK_TRY_HIP(hipGetLastError());
     return FTK_OK;
 }
@@ -1050,7 +1130,7 @@ ftk_status launch_refine(const AssignCall &c, const Workspace &w, int n_wg, hipS
     return FTK_OK;
 }
 
-void plan_generic(ftk_dtype dtype, int64_t N, int D, int K, AssignPlan &p)
+void plan_generic(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p)
 {
     const bool f32 = dtype == FTK_F32;
     p.variant = VAR_GENERIC;
@@ -1064,12 +1144,22 @@ void plan_generic(ftk_dtype dtype, int64_t N, int D, int K, AssignPlan &p)
     // the same layout measured slower there.
     if (!f32 && D >= 512 && K > 4 * Mma<double>::TM) p.KT = 8;
     if (g_tuning.kt > 0) p.KT = g_tuning.kt;
-    p.PT = p.KT == 8 ? 1 : 2;
+    // Rows through LDS, line by line, where one chunk holds all centroids and the rows are what a call waits for: each lane of the
+    // other loop reads a row of its own, 64 places a request.  32 instead of 64 points a wave: twice the workgroups, which a
+    // pass over long rows has too few of (20000 x 900: 79 for 256 units).  Whole calls, us, its own rows / lines:
+    //   without checksums  2^20 x 128, K = 32 154 / 143; 2^20 x 100, K = 5 149 / 130; 500000 x 256, K = 20 162 / 150; 200000 x 1000,
+    //                      K = 12 374 / 270; 20000 x 900, K = 10 114 / 77; 300000 x 256, K = 64 132 / 123; 2^20 x 64, K = 28 80 / 76;
+    //                      below: 2^20 x 48, K = 28 63 / 66, 2^20 x 17, K = 10 46 / 50
+    //   with               2^20 x 128, K = 32 182 / 161; 300000 x 40, K = 28 39 / 32; 300000 x 24, K = 10 30 / 26; 5000 x 700, K = 64
+    //                      126 / 90; 200000 x 1000, K = 12 390 / 297; below: 40000 x 17, K = 10 18 / 19
+    // fp64 reads four lanes to a row as it is: 300000 x 512, K = 7 295 / 273, with checksums 300000 x 200, K = 7 124 / 146.
+    p.lines = f32 && p.KT <= 2 && K <= p.KT * p.TM && D >= (ft == FTK_FT_OFF ? 64 : 24) && D < (1 << 22);
+    p.PT = p.KT == 8 || p.lines ? 1 : 2;
     p.waves = 4;
     p.KC = p.KT * p.TM;
     p.nkc = (int)ceil_div(K, p.KC);
     p.D8 = (int)ceil_div(D, 8) * 8;
-    p.DQ = generic_dq(f32, p.KT);
+    p.DQ = p.lines ? LINES_DQ : generic_dq(f32, p.KT);
     p.points_per_wg = p.waves * p.PT * p.TN;
     p.workgroups = ceil_div(N, p.points_per_wg);
     p.tiles_per_wave = p.nkc * p.PT * p.KT;

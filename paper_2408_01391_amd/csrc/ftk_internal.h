@@ -52,6 +52,7 @@ struct AssignPlan {
     int nkc;                    // number of K-chunks
     int D8;                     // D rounded up to a multiple of 8
     int DQ;                     // quads (8 features) per LDS stage
+    bool lines;                 // generic: rows pass through LDS
     int points_per_wg;
     int64_t workgroups;
     int tiles_per_wave;         // output tiles a wave finishes (fault addressing)
