@@ -141,8 +141,9 @@ ftk_status ftk_plan_padded_rows(ftk_dtype dtype, int64_t N, int32_t D, int32_t K
  *                               operands, name the centroid, the distance is evaluated from the
  *                               rows: in dtype, where the point was settled in double and rounded;
  *                               for all points in double where a problem is large enough for fp16
- *                               operands, whichever of the two forms runs), and every point of
- *                               the register-resident fp32 kernels (D <= 32; 32 < D <= 128 where
+ *                               operands, whichever of the two forms runs), every point of the
+ *                               one-launch kernels that small unprotected calls take (in double,
+ *                               rounded once), and every point of the register-resident fp32 kernels (D <= 32; 32 < D <= 128 where
  *                               that kernel is dispatched), get the direct-difference value
  *                               (relative error of a few units in the last place of the
  *                               distance).  Otherwise the value comes from the expanded form of
@@ -284,8 +285,8 @@ ftk_status ftk_kmeans_update_ft(ftk_dtype dtype, const void *X, const int32_t *l
                                 int32_t n_faults, ftk_ft_stats *stats, void *workspace,
                                 size_t workspace_bytes, void *hip_stream);
 
-/* Extents of the fault coordinates of ftk_kmeans_update_ft (rows_aligned16: whether X rows are
- * 16-byte aligned, i.e. X % 16 == 0 and D * element size % 16 == 0). */
+/* Extents of the fault coordinates of ftk_kmeans_update_ft.  rows_aligned16 (whether X % 16 == 0 and
+ * D * element size % 16 == 0) has no influence: all rows take the same path. */
 ftk_status ftk_update_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K,
                                int32_t rows_aligned16, ftk_geometry *out /* (host) */);
 

@@ -2283,9 +2283,10 @@ static int scan_from(ftk_dtype dtype, int64_t N, int D)
     const int d = D < 8 ? 0 : (D == 8 ? 1 : (D <= 16 ? 2 : (D <= 48 ? 3 : (D <= 128 ? 4 : 5))));
     const int n = N < 9000 ? 0 : (N < 36000 ? 1 : (N < 110000 ? 2 : (N < 450000 ? 3 : 4)));
     int k = from[dtype == FTK_F32 ? 0 : 1][n][d];
-    // fp32 rows that are not whole 16-byte pieces, which the matrix kernels load element by element: 60000 x 867, K = 20
-    // 424 / 119; 60000 x 111, K = 8 35 / 33; 6000 x 337, K = 8 150 / 41; 4 * 10^5 x 45, K = 50 70 / 52; 200000 x 45, K = 48
-    // 38.5 / 34.5; 200000 x 6, K = 192 33.1 / 28.3; 60000 x 45, K = 192 31.0 / 28.3
+    // fp32 rows that are not whole 16-byte pieces.  The lines lie where matrix kernels that load these rows element by element
+    // lose (60000 x 867, K = 20 424 / 119; 6000 x 337, K = 8 150 / 41; 4 * 10^5 x 45, K = 50 70 / 52; 200000 x 45, K = 48 38.5 / 34.5;
+    // 200000 x 6, K = 192 33.1 / 28.3).  Those read 16-byte pieces now and would win some of these calls back, with the distances
+    // of the expanded form: the lines stay for the direct ones that such calls get here.
     if (dtype == FTK_F32 && D % 4 != 0) {
         if (D >= 96) k = 8;
         else if (n >= 3) k = d == 0 ? 192 : (d == 2 ? 96 : (N >= 300000 ? 32 : 48));
