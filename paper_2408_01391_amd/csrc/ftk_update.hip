@@ -87,8 +87,13 @@ static UpdatePlan plan_update(ftk_dtype dtype, int64_t N, int D, int K)
     u.tx_log2 = l2;
     // a workgroup takes UPD_THREADS >> tx_log2 rows per pass; at least 16 passes (and 64 rows) per
     // chunk, so that long rows of a mid-sized problem still spread over all CUs; four where a table more is soon written and
-    // read (36311 x 63, K = 5 18.9 us with 16, 13.0 with four; 36000 x 64, K = 5 17.4 / 12.4)
-    int64_t min_rows = (int64_t)((int64_t)K * D <= 2048 ? 4 : 16) * (UPD_THREADS >> l2);
+    // read (36311 x 63, K = 5 18.9 us with 16, 13.0 with four; 36000 x 64, K = 5 17.4 / 12.4), and down to four where a launch has
+    // fewer than 64 workgroups otherwise (2123 x 72, K = 82 15.3 / 11.3; 30000 x 50, K = 100 19.4 / 15.5; 12000 x 128, K = 64 19.2 /
+    // 15.8; with redundancy 5000 x 100, K = 60 22.5 / 15.8), 24 if the tables outweigh the rows (50000 x 20, K = 350 14.9 / 15.5)
+    int passes = (int64_t)K * D <= 2048 ? 4 : 16;
+    const int pass_rows = UPD_THREADS >> l2;
+    while (passes > 4 && ceil_div(N, (int64_t)passes * pass_rows) * slices < (passes / 2 * pass_rows >= 2 * K ? 64 : 24)) passes /= 2;
+    int64_t min_rows = (int64_t)passes * pass_rows;
     if (min_rows > UPD_THREADS) min_rows = UPD_THREADS;
     if (min_rows < 64) min_rows = 64;
     int chunks = UPD_TARGET_WGS / slices;
