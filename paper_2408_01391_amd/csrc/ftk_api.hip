@@ -152,11 +152,13 @@ static bool route_small(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft
 
 // Of what the scan takes, fp32 problems go on up to 8 * 10^7 multiplications, 10^8 with up to 100 centroids (scan / direct kernel, 397
 // random shapes: 1.4 .. 3.9 below, 0.6 .. 1.0 above; 1286 x 73, K = 110 22.7 / 9.1 us, 1500 x 20, K = 700 22.4 / 12, 1316 x 432,
-// K = 135 35 / 25); fp64 ones stay: the scan compares distances of data at any scale, where squares leave the range.
+// K = 135 35 / 25).  Of fp64 ones only those that are small by the other kernel's measure go on (6267 x 22, K = 169 27 / 13): the scan
+// compares distances of data at any scale, where squares leave the range.
 static bool direct_rule(ftk_dtype dtype, int64_t N, int D, int K)
 {
     const double work = (double)N * D * K;
-    if (plan_scan(dtype, N, D, K).ok) return dtype == FTK_F32 && work <= (K <= 100 ? 1e8 : 8e7);
+    if (plan_scan(dtype, N, D, K).ok)
+        return dtype == FTK_F32 ? work <= (K <= 100 ? 1e8 : 8e7) : small_assign_fits(dtype, N, D, K);
     return direct_pays(dtype, N, D, K);
 }
 static bool route_direct(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, int n_faults)

@@ -6,6 +6,8 @@
 namespace ftk {
 
 bool small_assign_pays(ftk_dtype dtype, int64_t N, int D, int K);
+// what it can take at all
+bool small_assign_fits(ftk_dtype dtype, int64_t N, int D, int K);
 ftk_status launch_small_assign(const AssignCall &c, hipStream_t st);
 
 bool small_fit_pays(ftk_dtype dtype, int64_t N, int D, int K);

@@ -301,10 +301,14 @@ static bool small_work(ftk_dtype dtype, int64_t N, int D, int K)
 
 // (an assignment of longer rows is faster with several lanes a row, see ftk_direct.hip: fp32 6521 x 57, K = 95 15.8 / 12.2 us,
 // 58896 x 52, K = 12 12.9 / 10.9; fp64 4278 x 25, K = 91 18.2 / 9.4, 28555 x 19, K = 17 9.4 / 7.9, but 185114 x 23, K = 10 17 / 29)
+bool small_assign_fits(ftk_dtype dtype, int64_t N, int D, int K)
+{
+    return D <= 64 && (int64_t)K * small_quads(D) * 4 <= SM_CELLS && small_work(dtype, N, D, K);
+}
 bool small_assign_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     const int most = dtype == FTK_F32 ? 32 : (N < 60000 ? 16 : 24);
-    return D <= most && (int64_t)K * small_quads(D) * 4 <= SM_CELLS && small_work(dtype, N, D, K);
+    return D <= most && small_assign_fits(dtype, N, D, K);
 }
 
 bool small_fit_pays(ftk_dtype dtype, int64_t N, int D, int K)

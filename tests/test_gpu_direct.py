@@ -41,6 +41,15 @@ def test_direct_assign_matches_oracle(N, D, K, dtype):
     assert ftk.stats_dict(stats)["refined"] == 0
 
 
+@pytest.mark.parametrize("N,D,K", [(6267, 22, 169), (5000, 30, 200), (3001, 64, 128), (8000, 17, 341)])
+def test_small_problems_in_double_that_the_scan_would_take(N, D, K):
+    X, C = synth.random_problem(N, N, D, K, "f64")
+    stats = ftk.new_stats(DEV)
+    labels, mind = ftk.kmeans_assign(to_dev(X), to_dev(C), stats=stats)
+    check(X, C, "f64", labels.cpu().numpy(), mind.cpu().numpy())
+    assert ftk.stats_dict(stats)["refined"] == 0  # nothing listed: one launch
+
+
 @pytest.mark.parametrize("N,D,K,dtype", [(3000, 100, 40, "f32"), (2000, 300, 20, "f64"), (900, 37, 66, "f32")])
 def test_direct_assign_ties_and_values_that_are_not_numbers(N, D, K, dtype):
     X, C = synth.random_problem(D, N, D, K, dtype)
