@@ -171,12 +171,16 @@ DirectPlan cut_direct(int64_t N, int D, int K)
 //         K = 16 18 / 17; 641930 x 2, K = 110 53 / 38; 416968 x 4, K = 54 23 / 21
 //   fp64  393442 x 86, K = 2 70 / 81; 54801 x 136, K = 8 20.6 / 21.3; 353114 x 136, K = 3 83 / 83; 2627 x 635, K = 84 69 / 50;
 //         300000 x 100, K = 20 67 / 162
+// Two lanes to rows of almost their eight quads ask for too little at once where there are many (10^6 x 32, K = 2 47 / 61, but 300000
+// 12.3 / 11.5, 10^6 x 20 19 / 18 and x 33 80 / 30); rows of two or three features have nothing to share out among many
+// centroids' groups (333333 x 2, K = 150 46 / 35, 166666 x 2, K = 600 55 / 70; fp64 277777 x 3, K = 300 66 / 90).
 bool direct_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     const double work = (double)N * D * K;
+    if (dtype == FTK_F32 && D > 24 && D <= 32 && N > 500000) return false;
     if (dtype == FTK_F32)
-        return work <= 7e7 || (K <= 4 && work <= 1e9) || (K <= 8 && work <= 1.5e8) || (N <= 8000 && work <= 1e8) || (D < 4 && work <= 2e8);
-    return work <= 5e7 || (K <= 4 && work <= 4e8) || (K <= 8 && work <= 7e7) || (N <= 8000 && work <= 1.5e8) || (D < 4 && work <= 2.5e8);
+        return work <= 7e7 || (K <= 4 && work <= 1e9) || (K <= 8 && work <= 1.5e8) || (N <= 8000 && work <= 1e8) || (D < 4 && K <= 200 && work <= 2e8);
+    return work <= 5e7 || (K <= 4 && work <= 4e8) || (K <= 8 && work <= 7e7) || (N <= 8000 && work <= 1.5e8) || (D < 4 && K <= 200 && work <= 2.5e8);
 }
 
 template <typename T>

@@ -1301,7 +1301,8 @@ static UpdateLaunch plan_update_launch(ftk_dtype dtype, int64_t N, int D, int K)
     const int gpw = 64 >> L.lpr_log2;
     // about 2048 waves where N allows (run ends cost only plain stores, so parallelism is free)
     int64_t rpl = N / ((int64_t)gpw * 2048);
-    if (rpl < red_rows_min(N)) rpl = red_rows_min(N);
+    const int least = gpw == 1 ? 64 : red_rows_min(N);  // long rows: 84285 x 264, K = 1152 67 us with 64 rows, 75 with 41
+    if (rpl < least) rpl = least;
     if (rpl > RED_ROWS_PER_LANE_MAX) rpl = RED_ROWS_PER_LANE_MAX;
     L.rows_per_lane = (int)rpl;
     L.n_walkers = ceil_div(N, L.rows_per_lane);
