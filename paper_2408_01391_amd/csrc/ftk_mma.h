@@ -93,9 +93,7 @@ static inline int row_access(const void *a, const void *b, int D, size_t element
 {
     const int E = (int)(16 / element);
     if (D % E == 0 && (uintptr_t)a % 16 == 0 && (uintptr_t)b % 16 == 0) return ROWS_ALIGNED;
-    // short rows of doubles: two elements a piece save little, and pieces at odd places take longer (1600000 x 9, K = 30 90 us by
-    // elements, 99 by pieces, 21 features 122 / 126; 400000 x 25, K = 100 58 / 59)
-    return D >= (element == 8 ? 32 : E) ? ROWS_PIECES : ROWS_ELEMENTS;
+    return D >= E ? ROWS_PIECES : ROWS_ELEMENTS;
 }
 
 // E consecutive elements of a row starting at feature d0, zero beyond D.
