@@ -246,7 +246,7 @@ Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, 
     w.assign = off;
     {   // shared by the update paths: per-workgroup tables, or two tagged slots per walker
         const size_t slab_cells = (size_t)update_slab_cells_max(N, D, K);
-        const size_t slot_cells = (size_t)update_walkers_max(N) * 2 * (size_t)D;
+        const size_t slot_cells = (size_t)update_slot_cells_max(dtype, N, D);
         w.upd_slab = (int64_t *)take((slab_cells > slot_cells ? slab_cells : slot_cells) * sizeof(int64_t));
         const size_t slab_counts = (size_t)update_slab_chunks_max(N) * K;
         const size_t slot_tags = (size_t)update_walkers_max(N) * 2;

@@ -119,6 +119,7 @@ Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, 
 int64_t update_slab_chunks_max(int64_t N);
 int64_t update_slab_cells_max(int64_t N, int D, int K);
 int64_t update_walkers_max(int64_t N);
+int64_t update_slot_cells_max(ftk_dtype dtype, int64_t N, int D);
 int64_t update_bucket_cells(ftk_dtype dtype, int64_t N, int D, int K, int64_t *counts);
 
 // Events around the kernels that ftk_profile_read sums up (null while profiling is off).

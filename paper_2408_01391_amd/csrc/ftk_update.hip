@@ -43,11 +43,30 @@ int64_t update_slab_chunks_max(int64_t N)
     const int64_t by_rows = ceil_div(N, 64);
     return by_rows < UPD_TARGET_WGS ? (by_rows < 1 ? 1 : by_rows) : UPD_TARGET_WGS;
 }
-// rows of a walker of the label-sorted path: few points in rows of few pieces leave too few waves otherwise (100000 x 33,
-// K = 2000, strict 57 us with 64 rows)
-constexpr int RED_ROWS_PER_LANE_MAX = 256;
-static int red_rows_min(int64_t N) { return N < 262144 ? 32 : 64; }
-int64_t update_walkers_max(int64_t N) { return ceil_div(N, red_rows_min(N)) + 1; }
+// Rows of a walker of the label-sorted path, at least: where a wave holds several walkers, few points leave too few waves
+// with 64 (100000 x 33, K = 2000, strict 57 us); where a row takes the whole wave they do not (84285 x 264, K = 1152
+// 67 us with 64 rows, 75 with 41).
+constexpr int RED_ROWS_PER_LANE_MAX = 256, RED_ROWS_PER_LANE_MIN = 64, RED_ROWS_PER_LANE_FEW = 32;
+constexpr int64_t RED_FEW_POINTS = 262144;
+static int red_rows_min(int64_t N, int walkers_per_wave)
+{
+    return walkers_per_wave > 1 && N < RED_FEW_POINTS ? RED_ROWS_PER_LANE_FEW : RED_ROWS_PER_LANE_MIN;
+}
+// The most walkers of any row length, and the cells of their slots.  Neither falls as N or D grows, so that a workspace
+// made for the largest of several problems serves the smaller ones: points below the line keep what they have above it,
+// long rows what the longest of several walkers a wave have.
+int64_t update_walkers_max(int64_t N)
+{
+    const int64_t few = N < RED_FEW_POINTS ? N : RED_FEW_POINTS - 1;
+    const int64_t a = ceil_div(few, RED_ROWS_PER_LANE_FEW), b = ceil_div(N, RED_ROWS_PER_LANE_MIN);
+    return (a > b ? a : b) + 1;
+}
+int64_t update_slot_cells_max(ftk_dtype dtype, int64_t N, int D)
+{
+    const int shared = 32 * (dtype == FTK_F32 ? 4 : 2);  // features of the longest rows that share a wave
+    const int64_t a = update_walkers_max(N) * (D < shared ? D : shared), b = (ceil_div(N, RED_ROWS_PER_LANE_MIN) + 1) * D;
+    return 2 * (a > b ? a : b);
+}
 int64_t update_slab_cells_max(int64_t N, int D, int K)
 {
     const int64_t cells = (int64_t)K * D;
@@ -1301,7 +1320,7 @@ static UpdateLaunch plan_update_launch(ftk_dtype dtype, int64_t N, int D, int K)
     const int gpw = 64 >> L.lpr_log2;
     // about 2048 waves where N allows (run ends cost only plain stores, so parallelism is free)
     int64_t rpl = N / ((int64_t)gpw * 2048);
-    const int least = gpw == 1 ? 64 : red_rows_min(N);  // long rows: 84285 x 264, K = 1152 67 us with 64 rows, 75 with 41
+    const int least = red_rows_min(N, gpw);
     if (rpl < least) rpl = least;
     if (rpl > RED_ROWS_PER_LANE_MAX) rpl = RED_ROWS_PER_LANE_MAX;
     L.rows_per_lane = (int)rpl;
@@ -1407,7 +1426,7 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
         dim3 rblock(256);
         long long *slot_val = reinterpret_cast<long long *>(w.upd_slab);
         int32_t *slot_lab = w.upd_cslab;
-        if (L.n_walkers > update_walkers_max(N)) {
+        if (L.n_walkers > update_walkers_max(N) || 2 * L.n_walkers * D > update_slot_cells_max(dtype, N, D)) {
             set_error("internal: %lld walkers exceed the workspace bound", (long long)L.n_walkers);
             return FTK_EINVAL;
         }

@@ -35,6 +35,23 @@ def test_size_does_not_depend_on_a_forced_kernel(dtype, N, D, K):
             assert ftk.workspace_bytes(dtype, N, D, K, mode) == size
 
 
+@pytest.mark.parametrize("dtype", [ftk.F32, ftk.F64])
+@pytest.mark.parametrize("D,K", [(1, 8), (17, 300), (64, 64), (65, 1000), (128, 256), (129, 4), (512, 64), (1024, 71)])
+def test_a_workspace_for_the_most_points_serves_fewer(dtype, D, K):
+    """A batch of fewer rows is accepted wherever a larger one is."""
+    N = sorted({int(64 * 1.07 ** i) for i in range(150)} | {e + d for e in (65536, 131072, 262144, 524288) for d in (-1, 0, 1)})
+    size = [ftk.workspace_bytes(dtype, n, D, K, ftk.FT_STRICT) for n in N]
+    assert size == sorted(size)
+
+
+@pytest.mark.parametrize("dtype,D", [(ftk.F32, 512), (ftk.F32, 1024), (ftk.F64, 256)])
+def test_long_rows_reserve_a_walker_per_64_rows(dtype, D):
+    """Two slots of 64-bit sums a walker, the rest as for a problem whose tables are larger than them."""
+    N, K = 200000, 64
+    more = ftk.workspace_bytes(dtype, N, D, K, ftk.FT_STRICT) - ftk.workspace_bytes(dtype, N // 2, D, K, ftk.FT_STRICT)
+    assert more <= (N // 2 // 64 + 1) * 2 * D * 8 + N * 16
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,N,D,K", [("f32", 70000, 32, 3000), ("f64", 5000, 40, 800), ("f32", 4096, 16, 8), ("f32", 3000, 200, 800)])
 def test_unprotected_calls_in_a_workspace_of_a_protected_mode(dtype, N, D, K):
