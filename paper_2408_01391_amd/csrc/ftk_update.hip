@@ -340,11 +340,12 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
             if (nf > 0 && attempt == 0) {
                 for (int i = 0; i < nf; ++i) {
                     const ftk_fault flt = sh_faults[i];
-                    // the addressed thread, moved onto the lane of its row that owns a piece
+                    // the addressed thread, moved onto the lane of its row that owns a piece, and the element onto
+                    // one that the piece has
                     const int ft_id = (int)(flt.wave % (UPD_THREADS / 64)) * 64 + (int)(flt.lane & 63);
                     if ((ft_id >> tx_log2) == ty && ((ft_id & (TX - 1)) % ppr) == tx && (int)flt.tile == step) {
                         flip[flt.reg % UNR] = 1ull << (flt.bit & 63);
-                        flip_e = (int)((flt.reg / UNR) % E);
+                        flip_e = (int)((flt.reg / UNR) % (unsigned)min(E, dn - tx * E));
                     }
                 }
             }
@@ -848,14 +849,15 @@ __global__ __launch_bounds__(256) void sorted_reduce_kernel(const T *X, const in
             for (int i = 0; i < nf; ++i) {
                 const ftk_fault fl = sh_faults[i];
                 if ((int)(fl.wave & 3) == (int)(threadIdx.x >> 6) && (int)fl.tile == step) {
-                    // the addressed lane, moved onto a lane of its row group that owns features
+                    // the addressed lane, moved onto a lane of its row group that owns features, and the sum onto one of them
                     const int fl_lane = (int)(fl.lane & 63);
                     const int pa = min(lpr, (D + E - 1) / E);
                     const bool me = group == (fl_lane >> lpr_log2) && piece == (fl_lane & (lpr - 1)) % pa &&
                                     lane_on && cur >= 0;
+                    const int at = (int)(fl.reg % (unsigned)max(1, min(E, D - d0)));
 #pragma unroll
                     for (int e = 0; e < E; ++e)
-                        if (me && (int)(fl.reg % E) == e)
+                        if (me && at == e)
                             acc[e] = (long long)((unsigned long long)acc[e] ^ (1ull << (fl.bit & 63)));
                     n_injected += me ? 1 : 0;
                 }

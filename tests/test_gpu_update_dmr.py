@@ -94,6 +94,26 @@ def test_high_bit_flips_corrupt_centroids_without_dmr(name, N, D, K, dtype):
     assert np.array_equal(C_dmr, C_clean) and st2["detected"] == st2["injected"] >= 1
 
 
+@pytest.mark.parametrize("N,D,K,dtype", [(3000, 33, 50, "f32"), (3000, 34, 50, "f32"), (5000, 15, 100, "f32"), (3000, 7, 40, "f64"),
+                                         (70000, 33, 1000, "f32"), (70000, 35, 600, "f32"), (66000, 17, 2100, "f64"),
+                                         (66000, 35, 900, "f64")])
+def test_a_flip_in_any_register_of_a_rows_last_piece_lands(N, D, K, dtype):
+    """The last 16 bytes of a ragged row hold fewer features than registers are listed for.  (A workgroup's slices, of
+    which each takes the flip, are several where the table is large.)"""
+    X, C, labels = _problem(N, D, K, dtype)
+    geom = ftk.update_geometry(ftk.F32 if dtype == "f32" else ftk.F64, N, D, K, False)
+    tables = geom.waves_per_workgroup == 16
+    pieces = -(-D // (geom.regs_per_tile // 4 if tables else geom.regs_per_tile))
+    lane = (pieces - 1) % (1 << (pieces - 1).bit_length())
+    clean, _, _ = _update(X, C, labels, ftk.FT_OFF)
+    for reg in range(geom.regs_per_tile):
+        faults = ftk.make_faults([(0, 0, 0, reg, lane, 55)], DEV)
+        bad, _, st = _update(X, C, labels, ftk.FT_OFF, faults)
+        assert st["injected"] >= 1 and not np.array_equal(bad, clean), reg
+        good, _, st = _update(X, C, labels, ftk.FT_CORRECT, faults)
+        assert st["injected"] == st["detected"] == st["recomputed"] >= 1 and np.array_equal(good, clean), reg
+
+
 def test_detect_mode_only_counts():
     name, N, D, K, dtype = SHAPES[5]
     X, C, labels = _problem(N, D, K, dtype)
