@@ -270,20 +270,20 @@ Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, 
     const int64_t bucket_cells = update_bucket_cells(dtype, N, D, K, &bucket_counts);
     w.bucket_slab = (int64_t *)take((size_t)bucket_cells * sizeof(int64_t));
     w.bucket_cslab = (int32_t *)take((size_t)bucket_counts * sizeof(int32_t));
-    w.unprotected = off;
-    const size_t least = scan_bytes(dtype, N, D, K, false), small = small_fit_bytes(D, K);  // (the scan without its fp16 pieces)
-    for (size_t n : {scan_bytes(dtype, N, D, K, true), small})
-        if (w.unprotected < shared + n) w.unprotected = shared + n;
+    // one line for all of them, at what the scan without its fp16 pieces needs: below it a call runs as in a workspace of a
+    // protected mode's size, whatever is left over
+    size_t least = off;
+    for (size_t n : {scan_bytes(dtype, N, D, K, false), small_fit_bytes(D, K)})
+        if (least < shared + n) least = shared + n;
+    w.unprotected = least;
+    if (const size_t n = scan_bytes(dtype, N, D, K, true); w.unprotected < shared + n) w.unprotected = shared + n;
     w.scan = w.small_fit = nullptr;
     w.scan_bytes = 0;
-    // each takes what room there is beyond the size of a protected mode
-    const bool more = p && (bytes > w.total || w.unprotected == w.total);
-    w.room = more && bytes >= off;
-    if (more && least && bytes >= shared + least) {
-        w.scan = (void *)(p + shared);
+    w.room = p && bytes >= least;
+    if (w.room) {
+        w.scan = w.small_fit = (void *)(p + shared);
         w.scan_bytes = bytes - shared;
     }
-    if (more && small && bytes >= shared + small) w.small_fit = (void *)(p + shared);
     return w;
 }
 

@@ -78,6 +78,23 @@ def test_unprotected_calls_in_a_workspace_of_a_protected_mode(dtype, N, D, K):
     assert bool((whole[start + size:] == 0x5a).all()) and bool((whole[:start] == 0x5a).all())
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 3000, 200, 800), ("f32", 9000, 129, 931), ("f64", 5000, 300, 900), ("f32", 20000, 33, 2000)])
+def test_a_few_bytes_beyond_a_protected_mode_change_nothing(dtype, N, D, K):
+    """What is left of an allocation after its alignment does not choose the path."""
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    t = torch.float32 if dtype == "f32" else torch.float64
+    C = torch.randn(K, D, generator=gen, device="cuda", dtype=t) * 5
+    X = C[torch.randint(K, (N,), generator=gen, device="cuda")] + torch.randn(N, D, generator=gen, device="cuda", dtype=t)
+    size = ftk.workspace_bytes(ftk.F32 if dtype == "f32" else ftk.F64, N, D, K, ftk.FT_STRICT)
+    ws = torch.empty(size + 512, dtype=torch.uint8, device="cuda")
+    ws = ws[-ws.data_ptr() % 256:]
+    labels, mind = ftk.kmeans_assign(X, C, workspace=ws[:size])
+    for more in (1, 255):
+        lab2, mind2 = ftk.kmeans_assign(X, C, workspace=ws[:size + more])
+        assert torch.equal(labels, lab2) and torch.equal(mind, mind2)
+
+
 @pytest.mark.parametrize("dtype,N,D,K", [(ftk.F32, 1 << 21, 256, 16384), (ftk.F64, 1 << 20, 512, 8192), (ftk.F32, 1 << 24, 132, 33000)])
 def test_records_of_the_scan_do_not_grow_with_points_times_centroids(dtype, N, D, K):
     """64 MB of records, 8 bytes a listed point, a copy of the centroids, the tables of the bucketed update."""
