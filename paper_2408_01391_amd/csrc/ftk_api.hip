@@ -900,9 +900,17 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
 
     const bool small = !fast && w.small_fit && iters > 0 && ft == FTK_FT_OFF && g_tuning.assign_variant == -1 &&
                        g_tuning.update_path == -1 && small_fit_pays(dtype, N, D, K);
-    // the centroids live where they are asked for, if whole pieces may be read from there
-    void *const C = (uintptr_t)C_out % 16 == 0 ? C_out : w.C_cur;
-    const void *C_first = C_init;  // (a small fit reads the first ones where they are)
+    const size_t c_bytes = (size_t)K * D * esz, l_bytes = (size_t)N * 4, n_bytes = (size_t)K * 4;
+    auto apart = [](const void *a, size_t na, const void *b, size_t nb) {
+        return (uintptr_t)a + na <= (uintptr_t)b || (uintptr_t)b + nb <= (uintptr_t)a;
+    };
+    // The centroids live where they are asked for, if whole pieces may be read from there and nothing else is: outputs may
+    // lie over inputs, which the copies of the other way have read before the first iteration or leave until after the last.
+    const bool in_place = (uintptr_t)C_out % 16 == 0 && apart(C_out, c_bytes, X, (size_t)N * D * esz) &&
+                          apart(C_out, c_bytes, labels_out, l_bytes) && apart(C_out, c_bytes, counts_out, n_bytes) &&
+                          (C_init == C_out || !C_init || apart(C_init, c_bytes, C_out, c_bytes));
+    void *const C = in_place ? C_out : w.C_cur;
+    const void *C_first = C_init;  // (a small fit reads the first ones where they are, if they stay there)
     if (!C_init) {
         std::vector<int64_t> idx((size_t)K);
         FTK_TRY(ftk_seeded_indices(seed, N, K, idx.data()));
@@ -911,7 +919,13 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
         C_first = small ? w.C_cur : C;
         FTK_TRY(launch_gather_rows(dtype, X, D, w.idx, K, const_cast<void *>(C_first), st));
     }
-    if (!small && C_first != C) FTK_TRY_HIP(hipMemcpyAsync(C, C_first, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
+    if (!small) {
+        if (C_first != C) FTK_TRY_HIP(hipMemcpyAsync(C, C_first, c_bytes, hipMemcpyDeviceToDevice, st));
+    } else if (C_init && !(apart(C_init, c_bytes, C_out, c_bytes) && apart(C_init, c_bytes, labels_out, l_bytes) &&
+                           apart(C_init, c_bytes, counts_out, n_bytes))) {
+        FTK_TRY_HIP(hipMemcpyAsync(w.C_cur, C_init, c_bytes, hipMemcpyDeviceToDevice, st));
+        C_first = w.C_cur;
+    }
     int32_t *const ticket = reinterpret_cast<int32_t *>(w.absmax + 1);
     if (small) {
         FTK_TRY(launch_small_fit(dtype, X, N, D, K, iters, C_first, w.C_cur, C_out, labels_out, counts_out, w.absmax, w.inertia,
@@ -927,7 +941,7 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
         FTK_TRY(launch_update(dtype, X, labels_out, N, D, K, C, counts_out, w.absmax, w, ft, nullptr, 0,
                               stats, st));
     }
-    if (!small && C != C_out) FTK_TRY_HIP(hipMemcpyAsync(C_out, C, (size_t)K * D * esz, hipMemcpyDeviceToDevice, st));
+    if (!small && C != C_out) FTK_TRY_HIP(hipMemcpyAsync(C_out, C, c_bytes, hipMemcpyDeviceToDevice, st));
     if (inertia_per_iter && iters > 0) {
         FTK_TRY_HIP(hipMemcpyAsync(inertia_per_iter, w.inertia, (size_t)iters * sizeof(double),
                                    hipMemcpyDeviceToHost, st));
