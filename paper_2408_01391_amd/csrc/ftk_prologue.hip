@@ -335,10 +335,9 @@ __global__ __launch_bounds__(256) void sum_kernel(const T *v, int64_t n, double 
     for (int64_t i = lo + threadIdx.x; i < hi; i += 256) s += (double)v[i];
     s = block_sum(s, sh);
     if (threadIdx.x == 0) {
-        // written and read past the caches that other XCDs do not see; the ticket follows the value
+        // the ticket releases the value, the last block's acquires the others'
         __hip_atomic_store(partials + blockIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_s_waitcnt(0);
-        sh_last = atomicAdd(ticket, 1) == (int)gridDim.x - 1;
+        sh_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
     }
     __syncthreads();
     if (!sh_last) return;

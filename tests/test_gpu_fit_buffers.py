@@ -1,5 +1,7 @@
 """Fits whose outputs lie over their inputs: centroids that replace the initial ones, in place or some elements further on,
-and centroids that take the place of the first points."""
+and centroids that take the place of the first points.  The objective of every iteration, whose partial sums the block
+that ends last adds up."""
+import numpy as np
 import pytest
 import torch
 
@@ -50,3 +52,21 @@ def test_outputs_over_inputs(N, D, K, dtype, mode, iters):
         assert torch.equal(got[0], want[0]) and torch.equal(over[K:], X[K:])
         if iters:
             assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("N", [1, 255, 2048, 2049, 100003, 262144, 700001])
+def test_objective_of_every_iteration(N, dtype):
+    """One block, two, all 128; the ticket starts over for each of 12 iterations, and each fit gives the same bits."""
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    X = torch.randn(N, 5, generator=gen, device=DEV, dtype=dtype)
+    C0 = torch.randn(3, 5, generator=gen, device=DEV, dtype=dtype)
+    runs = [ftk.kmeans_fit(X, 3, 12, C_init=C0, ft_mode=ftk.FT_STRICT)["inertia"] for _ in range(3)]
+    assert np.array_equal(runs[0], runs[1]) and np.array_equal(runs[0], runs[2])
+    want, C = [], C0
+    for _ in range(12):
+        labels, mind = ftk.kmeans_assign(X, C, ft_mode=ftk.FT_STRICT)
+        want.append(float(mind.double().sum()))
+        C, _ = ftk.kmeans_update(X, labels, C.clone(), ft_mode=ftk.FT_STRICT)
+    # N terms of one sign in double, added up in two orders
+    assert np.all(np.abs(runs[0] - want) <= 2 * N * 2.0 ** -53 * np.abs(want))
