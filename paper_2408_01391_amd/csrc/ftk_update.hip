@@ -274,13 +274,15 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
         // before any LDS atomic, so several HBM requests per thread are in flight
         constexpr int UNR = 4;
         // When the slice holds every cluster the point loads do not depend on the labels and go out
-        // together with them (ALLK).  Otherwise only rows whose label falls into the slice are read: those of a step are
-        // requested while the rows of the step before are added, their labels one step earlier still (10^6 x 11, K = 4000
-        // 105 us a call without, 95 with; of ALLK slices, which the LDS atomics bound, 2^18 x 128, K = 256 42 without, 44 with; rows of
-        // up to three features 38 without, 41 with; under DMR the registers cost the other slices 3 %).
-        auto pass = [&](auto allk_tag) {
+        // together with them (ALLK).  Otherwise only rows whose label falls into the slice are read: over more than four
+        // steps those of one are requested while the rows of the step before are added, their labels one step earlier
+        // still (AHEAD; without / with: 400000 x 100, K = 300 88 / 76 us, 10^6 x 15, K = 1600 61 / 57, fp64 500000 x 16,
+        // K = 900 35 / 32; four steps 500000 x 15, K = 1000 29.3 / 29.2, fp64 300000 x 7, K = 3000 28.1 / 28.6; two or one
+        // 20000 x 32, K = 1000 18.8 / 19.3).  The LDS atomics bound ALLK slices (2^18 x 128, K = 256 42 / 44); rows of up to
+        // three features 38 / 41; under DMR the registers cost the other slices 3 %.
+        auto pass = [&](auto allk_tag, auto ahead_tag) {
         constexpr bool ALLK = decltype(allk_tag)::value;
-        constexpr bool AHEAD = !ALLK && AL != ROWS_ELEMENTS && !DMR;
+        constexpr bool AHEAD = decltype(ahead_tag)::value;
         const int64_t stride = (int64_t)TY * UNR;
         auto fetch_labels = [&](int64_t row0, int (&lab)[UNR]) {
 #pragma unroll
@@ -391,9 +393,11 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
         }
         };
         if (kn == K)
-            pass(std::true_type{});
+            pass(std::true_type{}, std::false_type{});
+        else if (AL != ROWS_ELEMENTS && !DMR && rows_per_chunk > (int64_t)4 * TY * UNR)
+            pass(std::false_type{}, std::bool_constant<AL != ROWS_ELEMENTS && !DMR>{});
         else
-            pass(std::false_type{});
+            pass(std::false_type{}, std::false_type{});
         __syncthreads();
         if constexpr (DMR) {
             unsigned long long tsum = 0ull, csum = 0ull;
