@@ -235,7 +235,21 @@ void assign_generic_kernel(GenericArgs<T> a)
     // fetch only issues the loads (clamped into the matrix, so always valid); rows beyond K and
     // features beyond D are cleared when the stage is committed to LDS, i.e. after the matrix work
     // of the stage in between - a select right behind the load would make the wave wait for it here
+    // the pieces beside the rows: half-norms of the chunk (padded with zeros to nkc*KC entries), checksum row
+    auto fetch_extra = [&](int kc, int dc) {
+        const int q0 = dc * DQ;
+#pragma unroll
+        for (int e = 0; e < E; ++e) pfx[e] = T(0);
+        if (dc == 0 && tid < KC / E)
+            pfx = *reinterpret_cast<const frag_t *>(a.hcn + (size_t)kc * KC + tid * E);
+        if (FT && tid >= 64 && tid < 64 + PPR && (q0 * 8 + (tid - 64) * E) < a.D8)
+            pfx = *reinterpret_cast<const frag_t *>(a.chk_v1 + (size_t)kc * a.D8 + q0 * 8 + (tid - 64) * E);
+    };
+    // They go first: where the allocator gave their address a register of a row in flight, they waited for all rows (fp64
+    // 10000 x 1024, K = 300, strict 328 us behind the rows, 300 ahead of them; 30000 x 300, K = 100 98 / 92).  With one tile
+    // the pieces of points in flight are few: 120000 x 128, K = 12 37.5 / 39.2.
     auto fetch = [&](int kc, int dc) {
+        if constexpr (KTV > 1) fetch_extra(kc, dc);
         const int q0 = dc * DQ;
         const unsigned stage_off = (unsigned)(kc * KC * D + q0 * 8) * (unsigned)sizeof(T);  // wave-uniform
 #pragma unroll
@@ -248,12 +262,7 @@ void assign_generic_kernel(GenericArgs<T> a)
                 pf[i] = load_frag_clamped<T, AL>(a.C + (int64_t)min(j, a.K - 1) * D, d0, D);
             }
         }
-#pragma unroll
-        for (int e = 0; e < E; ++e) pfx[e] = T(0);
-        if (dc == 0 && tid < KC / E)  // half-norms of the chunk (padded with zeros to nkc*KC entries)
-            pfx = *reinterpret_cast<const frag_t *>(a.hcn + (size_t)kc * KC + tid * E);
-        if (FT && tid >= 64 && tid < 64 + PPR && (q0 * 8 + (tid - 64) * E) < a.D8)
-            pfx = *reinterpret_cast<const frag_t *>(a.chk_v1 + (size_t)kc * a.D8 + q0 * 8 + (tid - 64) * E);
+        if constexpr (KTV == 1) fetch_extra(kc, dc);
     };
     auto commit = [&](int kc, int dc, int buf) {
         unsigned char *const base = lds_raw + buf * STAGE_BYTES;
