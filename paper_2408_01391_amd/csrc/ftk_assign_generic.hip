@@ -246,10 +246,11 @@ void assign_generic_kernel(GenericArgs<T> a)
             pfx = *reinterpret_cast<const frag_t *>(a.chk_v1 + (size_t)kc * a.D8 + q0 * 8 + (tid - 64) * E);
     };
     // They go first: where the allocator gave their address a register of a row in flight, they waited for all rows (fp64
-    // 10000 x 1024, K = 300, strict 328 us behind the rows, 300 ahead of them; 30000 x 300, K = 100 98 / 92).  With one tile
-    // the pieces of points in flight are few: 120000 x 128, K = 12 37.5 / 39.2.
+    // 10000 x 1024, K = 300, strict 328 us behind the rows, 300 ahead of them; 30000 x 300, K = 100 98 / 92).  Not
+    // with one tile or rows through LDS, which have few rows in flight: 120000 x 128, K = 12 37.5 / 39.2, fp32 280000 x 128,
+    // K = 32, strict 50.0 / 51.8.
     auto fetch = [&](int kc, int dc) {
-        if constexpr (KTV > 1) fetch_extra(kc, dc);
+        if constexpr (KTV > 1 && !LINES) fetch_extra(kc, dc);
         const int q0 = dc * DQ;
         const unsigned stage_off = (unsigned)(kc * KC * D + q0 * 8) * (unsigned)sizeof(T);  // wave-uniform
 #pragma unroll
@@ -262,7 +263,7 @@ void assign_generic_kernel(GenericArgs<T> a)
                 pf[i] = load_frag_clamped<T, AL>(a.C + (int64_t)min(j, a.K - 1) * D, d0, D);
             }
         }
-        if constexpr (KTV == 1) fetch_extra(kc, dc);
+        if constexpr (KTV == 1 || LINES) fetch_extra(kc, dc);
     };
     auto commit = [&](int kc, int dc, int buf) {
         unsigned char *const base = lds_raw + buf * STAGE_BYTES;
@@ -1149,6 +1150,31 @@ ftk_status launch_refine(const AssignCall &c, const Workspace &w, int n_wg, hipS
     return FTK_OK;
 }
 
+// Rows through LDS, line by line, where one chunk holds all centroids and the rows are what a call waits for: each lane of
+// the other loop reads a row of its own, 64 places a request.  32 instead of 64 points a wave: twice the workgroups, which
+// a pass over long rows has too few of (20000 x 900: 79 for 256 units).  Whole calls, us, its own rows / lines:
+//   without checksums  2^20 x 128, K = 32 154 / 143; 2^20 x 100, K = 5 149 / 130; 200000 x 1000, K = 12 374 / 270;
+//                      20000 x 900, K = 10 114 / 77; below 64 features 2^20 x 48, K = 28 63 / 66, 2^20 x 17, K = 10 46 / 50
+//   with               2^20 x 128, K = 32 182 / 161; 300000 x 24, K = 10 30 / 26; 5000 x 700, K = 64 126 / 90; 200000 x 1000,
+//                      K = 12 390 / 297; below 24 features 40000 x 17, K = 10 18 / 19
+// fp64 reads four lanes to a row as it is: 300000 x 512, K = 7 295 / 273, with checksums 300000 x 200, K = 7 124 / 146.
+static bool lines_pay(int64_t N, int D, int K, int KT, bool ft)
+{
+    if (D < (ft ? 24 : 64) || D >= (1 << 22)) return false;
+    // The other loop, with stages half as long, runs without conditions where this one has half a stage left over:
+    // 400000 x 240, K = 64 144 / 153, with checksums 161 / 181, 100000 x 112 32 / 33, 39 / 42; few points and the checksums
+    // of one tile still do better here: 60000 x 240, K = 64 44 / 42, 100000 x 112, K = 32, with checksums 31 / 29.
+    if (D % 32 == 16 && K == 32 * KT && N > 65536 && (KT == 2 || (!ft && D < 160))) return false;
+    // As many points a unit of the chip either way, the larger workgroups side by side, the smaller ones with a second
+    // round of few: 190000 x 256, K = 64 77 / 86, 180000 x 112, K = 12 33 / 35, with checksums 120000 x 300, K = 40 88 / 100;
+    // but 135000 x 256, K = 64 (five a unit instead of two times three) 74 / 66, 200000 93 / 87, and whole stages of one
+    // tile, or rows soon done with under two, 180000 x 256, K = 32 59 / 54, with checksums 110000 x 64, K = 64 30.2 / 28.5.
+    if (KT == 2 ? D <= 64 : (ft || (D % 32 == 0 && D >= 128))) return true;
+    const int64_t many = ceil_div(ceil_div(N, 128), 256), few = ceil_div(ceil_div(N, 256), 256);
+    const int at_once = KT == 1 ? 5 : (ft ? 3 : 4), rest = (int)(many % at_once);  // of 128 points
+    return !(many == 2 * few && few <= (KT == 1 ? 4 : 3) && many > at_once && rest && 2 * rest <= at_once);
+}
+
 void plan_generic(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, AssignPlan &p)
 {
     const bool f32 = dtype == FTK_F32;
@@ -1163,16 +1189,7 @@ void plan_generic(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft, Assi
     // the same layout measured slower there.
     if (!f32 && D >= 512 && K > 4 * Mma<double>::TM) p.KT = 8;
     if (g_tuning.kt > 0) p.KT = g_tuning.kt;
-    // Rows through LDS, line by line, where one chunk holds all centroids and the rows are what a call waits for: each lane of the
-    // other loop reads a row of its own, 64 places a request.  32 instead of 64 points a wave: twice the workgroups, which a
-    // pass over long rows has too few of (20000 x 900: 79 for 256 units).  Whole calls, us, its own rows / lines:
-    //   without checksums  2^20 x 128, K = 32 154 / 143; 2^20 x 100, K = 5 149 / 130; 500000 x 256, K = 20 162 / 150; 200000 x 1000,
-    //                      K = 12 374 / 270; 20000 x 900, K = 10 114 / 77; 300000 x 256, K = 64 132 / 123; 2^20 x 64, K = 28 80 / 76;
-    //                      below: 2^20 x 48, K = 28 63 / 66, 2^20 x 17, K = 10 46 / 50
-    //   with               2^20 x 128, K = 32 182 / 161; 300000 x 40, K = 28 39 / 32; 300000 x 24, K = 10 30 / 26; 5000 x 700, K = 64
-    //                      126 / 90; 200000 x 1000, K = 12 390 / 297; below: 40000 x 17, K = 10 18 / 19
-    // fp64 reads four lanes to a row as it is: 300000 x 512, K = 7 295 / 273, with checksums 300000 x 200, K = 7 124 / 146.
-    p.lines = f32 && p.KT <= 2 && K <= p.KT * p.TM && D >= (ft == FTK_FT_OFF ? 64 : 24) && D < (1 << 22);
+    p.lines = f32 && p.KT <= 2 && K <= p.KT * p.TM && lines_pay(N, D, K, p.KT, ft != FTK_FT_OFF);
     p.PT = p.KT == 8 || p.lines ? 1 : 2;
     p.waves = 4;
     p.KC = p.KT * p.TM;

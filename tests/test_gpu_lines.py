@@ -32,6 +32,19 @@ def test_every_end_of_a_row_and_of_the_points(D, N, K, mode):
         check_assign(X, C, labels.cpu().numpy(), mind.cpu().numpy(), ref=ref)
 
 
+@pytest.mark.parametrize("N,D,K,points", [(65536, 112, 64, 128), (65537, 112, 64, 256), (65537, 128, 64, 128), (65537, 112, 63, 128),
+                                          (65537, 112, 32, 128), (98304, 300, 40, 128), (98305, 300, 40, 256), (131072, 300, 40, 256),
+                                          (131073, 300, 40, 128), (163841, 300, 40, 128), (60001, 240, 64, 128), (70001, 240, 64, 256)])
+def test_either_workgroup_on_both_sides_of_its_lines(N, D, K, points):
+    """Protected calls, whose workgroups the geometry reports: the same labels as the oracle's on sampled rows."""
+    print("lines", N, D, K, flush=True)
+    assert ftk.assign_geometry(0, N, D, K, ftk.FT_STRICT).workgroups == -(-N // points)
+    X, C = synth.random_problem(D + K, N, D, K, "f32", spread=3.0)
+    labels, mind = ftk.kmeans_assign(to_dev(X), to_dev(C), ft_mode=ftk.FT_STRICT)
+    rows = np.unique(np.concatenate([np.arange(0, N, 97), np.arange(N - 300, N)]))
+    check_assign(X[rows], C, labels.cpu().numpy()[rows], mind.cpu().numpy()[rows], ref=oracle.assign(X[rows], C))
+
+
 @pytest.mark.parametrize("D,K", [(24, 9), (33, 50), (128, 32), (300, 64)])
 def test_flips_are_repaired(D, K):
     N = 2000
