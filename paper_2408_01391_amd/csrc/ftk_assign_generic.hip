@@ -112,8 +112,11 @@ constexpr int generic_kt(int K) { return K <= Mma<T>::TM ? 1 : (K <= 2 * Mma<T>:
 // instead of a branch every KT of them, and no masking selects on the point fragments.
 //
 // LINES: the rows pass through LDS (plan_generic() tells when).
+//
+// fp64, two tiles, no checksums: asked for a fourth wave, since a few registers more cost it (900000 x 48, K = 32 106 us with
+// three, 92 with four; 400000 x 128, K = 32 99 / 92).
 template <typename T, int KTV, int AL, bool FT, bool FULL, bool LINES = false>
-__global__ __launch_bounds__(256, (GenericCfg<T, KTV>::WAVES_PER_SIMD))
+__global__ __launch_bounds__(256, (sizeof(T) == 8 && KTV == 2 && !FT ? 4 : GenericCfg<T, KTV>::WAVES_PER_SIMD))
 void assign_generic_kernel(GenericArgs<T> a)
 {
     static_assert(!LINES || (sizeof(T) == 4 && KTV <= 2 && AL != ROWS_ELEMENTS), "rows of whole pieces, one chunk");
