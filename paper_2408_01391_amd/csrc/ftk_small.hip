@@ -59,8 +59,10 @@ __device__ __forceinline__ T small_mean(const unsigned long long *sums, int cell
     return (T)((total * inv) / (double)n);
 }
 
-// NQ quads of features, PT points per thread; whole = rows are whole quads
-template <typename T, int NQ, int PT, bool FIT>
+// NQ quads of features, PT points per thread.
+// AHEAD: the first rows are on their way while the centroids are formed (in a fit their means wait for the sums, then for
+// divisions), and those of the next round while distances are taken (launch_small_t() tells when).
+template <typename T, int NQ, int PT, bool FIT, bool AHEAD>
 __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
 {
     constexpr int E = 16 / sizeof(T);              // elements per LDS read
@@ -75,12 +77,9 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
     const T *X = reinterpret_cast<const T *>(a.X), *C = reinterpret_cast<const T *>(a.C);
     T *C_out = reinterpret_cast<T *>(a.C_out);
 
-    // The first rows are on their way while the centroids are formed (their means wait for the sums, then for divisions), and
-    // those of the next round while distances are taken: 20000 x 24, K = 100 13.2 us a call, 12.2 so; with the one launch
-    // ahead of the first iteration a fit of 4096 x 16, K = 8, ten iterations 143, 130.
     const int per_wg = (SM_THREADS >> a.p_log2) * PT;  // points per workgroup and round
-    T raw[PT][4 * NQ];
-    auto request = [&](int64_t p0) {
+    // element d of point t goes to put(t, d, value, whether the row has it)
+    auto read_rows = [&](int64_t p0, auto put) {
 #pragma unroll
         for (int t = 0; t < PT; ++t) {
             const int64_t p = p0 + (int64_t)t * (SM_THREADS >> a.p_log2) + (tid >> a.p_log2);
@@ -90,15 +89,19 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
                 for (int q = 0; q < NQ; ++q) {
                     const Quad<T> f = load_quad<T>(row + min(4 * q, D - 4));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) raw[t][4 * q + e] = f.v[e];
+                    for (int e = 0; e < 4; ++e) put(t, 4 * q + e, f.v[e], 4 * q < D);
                 }
             } else {
 #pragma unroll
-                for (int d = 0; d < 4 * NQ; ++d) raw[t][d] = row[min(d, D - 1)];
+                for (int d = 0; d < 4 * NQ; ++d) put(t, d, row[min(d, D - 1)], d < D);
             }
         }
     };
-    request((int64_t)blockIdx.x * per_wg);
+    T raw[PT][AHEAD ? 4 * NQ : 1];
+    auto request = [&](int64_t p0) {
+        read_rows(p0, [&](int t, int d, T v, bool) { raw[t][d] = v; });
+    };
+    if constexpr (AHEAD) request((int64_t)blockIdx.x * per_wg);
     double scale = 1.0;
     if constexpr (FIT) scale = small_scale(*a.absmax, a.scale_rows);
     const double inv = 1.0 / scale;
@@ -143,12 +146,17 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
         for (int t = 0; t < PT; ++t) {
             p[t] = p0 + (int64_t)t * (SM_THREADS >> a.p_log2) + (tid >> a.p_log2);
             live[t] = p[t] < a.N;
+            if constexpr (AHEAD)
 #pragma unroll
-            for (int d = 0; d < 4 * NQ; ++d) x[t][d] = d < D ? (double)raw[t][d] : 0.0;
+                for (int d = 0; d < 4 * NQ; ++d) x[t][d] = d < D ? (double)raw[t][d] : 0.0;
             best[t] = __builtin_huge_val();
             bj[t] = 0x7fffffff;
         }
-        if (p0 + (int64_t)gridDim.x * per_wg < a.N) request(p0 + (int64_t)gridDim.x * per_wg);
+        if constexpr (AHEAD) {
+            if (p0 + (int64_t)gridDim.x * per_wg < a.N) request(p0 + (int64_t)gridDim.x * per_wg);
+        } else {
+            read_rows(p0, [&](int t, int d, T v, bool there) { x[t][d] = there ? (double)v : 0.0; });
+        }
         for (int j = sub; j < K; j += P) {
             const T *c = ldsC + j * (SU * E);
             double d[PT];
@@ -332,6 +340,10 @@ static int small_lanes_log2(int64_t N, int K, int pt, int *grid)
     return l;
 }
 
+// Rows ahead, us without / with: fp32 20000 x 24, K = 100 13.9 / 13.1, 700000 x 20, K = 3 16.6 / 14.6, fit of 4096 x 16, K = 8, ten
+// iterations 139 / 136; doubles that are read one by one 200000 x 15, K = 9 12.3 / 9.9.  Longer rows and other doubles pay
+// for the registers with a wave: 60000 x 32, K = 26 10.6 / 12.0; fp64 60000 x 20, K = 26 9.7 / 10.3, 700000 x 16, K = 3 19.0 / 21.5, fit
+// of 20000 x 32, K = 20, five iterations 159 / 206.
 template <typename T, bool FIT>
 static void launch_small_t(const SmallArgs &a, int grid, hipStream_t st)
 {
@@ -339,13 +351,16 @@ static void launch_small_t(const SmallArgs &a, int grid, hipStream_t st)
     const size_t row = (size_t)((4 * nq * sizeof(T) / 16) | 1) * 16;
     const size_t lds = (size_t)a.K * row + (FIT ? (size_t)a.K * a.D * 8 + (size_t)a.K * 4 : 0);
     const dim3 g((unsigned)grid), b(SM_THREADS);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, st, a); };
+    constexpr bool F32 = sizeof(T) == 4;
+    const bool ahead = F32 || (!FIT && a.D % 4 != 0);
     switch (nq) {
-    case 2: hipLaunchKernelGGL((small_kernel<T, 2, 2, FIT>), g, b, lds, st, a); break;
-    case 4: hipLaunchKernelGGL((small_kernel<T, 4, 2, FIT>), g, b, lds, st, a); break;
-    case 6: hipLaunchKernelGGL((small_kernel<T, 6, 2, FIT>), g, b, lds, st, a); break;
-    case 8: hipLaunchKernelGGL((small_kernel<T, 8, 2, FIT>), g, b, lds, st, a); break;
-    case 12: hipLaunchKernelGGL((small_kernel<T, 12, 1, FIT>), g, b, lds, st, a); break;
-    default: hipLaunchKernelGGL((small_kernel<T, 16, 1, FIT>), g, b, lds, st, a); break;
+    case 2: launch(ahead ? small_kernel<T, 2, 2, FIT, F32 || !FIT> : small_kernel<T, 2, 2, FIT, F32>); break;
+    case 4: launch(ahead ? small_kernel<T, 4, 2, FIT, F32 || !FIT> : small_kernel<T, 4, 2, FIT, F32>); break;
+    case 6: launch(small_kernel<T, 6, 2, FIT, F32>); break;
+    case 8: launch(small_kernel<T, 8, 2, FIT, false>); break;
+    case 12: launch(small_kernel<T, 12, 1, FIT, false>); break;
+    default: launch(small_kernel<T, 16, 1, FIT, false>); break;
     }
 }
 
