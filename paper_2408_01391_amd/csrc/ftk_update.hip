@@ -1257,15 +1257,35 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finalize_kernel(
     }
 }
 
-// Rows that the other paths do not serve as well (whole calls, before / here): D = 32, K = 4096: N = 2^21 174 / 98 us, labels crowded into few clusters 199 / 120, all in one
-// 398 / 133; D = 64, K = 1000, N = 70000 46 / 38; D = 128, K = 512, N = 500000 91 / 88.  Longer rows hide the sort
-// once X leaves the memory-side cache: D = 256: 10^5, K = 4000 101 / 80, 10^6, K = 300 233 / 283.  Against the
-// LDS tables with many slices, which read X once each: D = 12, K = 3000, N = 10^6 76 / 56; of 9 to 11 features where there are
-// enough points and slices: D = 9, K = 6635, N = 947578 107 / 65, D = 10, K = 8000, N = 300000 60 / 48, but D = 9, K = 3800,
-// N = 300000 39 / 50; D = 8, K = 4096, N = 10^6 39 / 49.
+// Rows that the other paths may not serve as well.  Longer ones hide the sort once X leaves the memory-side cache: D = 256,
+// sort / buckets, whole calls, us: 10^5, K = 4000 101 / 80, 10^6, K = 300 233 / 283.
 static bool bucket_pays(int64_t N, int D)
 {
     return D >= 9 && (D <= 128 || (D <= 256 && D % 4 == 0 && (double)N * D * 4 < 268435456.0));
+}
+
+// Where the buckets take over from tables in `nks` slices of clusters: a slice reads all labels and its rows, a bucket
+// costs 40 us whatever the points.  Tables / buckets: D = 12, K = 4000 200000 points 33 / 38 us, 600000 55 / 45, K = 8000 70000
+// 39 / 36; D = 13, K = 2000 70000 24 / 45, 600000 46 / 61, 1500000 88 / 85, K = 4000 300000 47 / 48, K = 8000 150000 50 / 44; D = 9, K = 8000
+// 300000 56 / 49, K = 4000 300000 39 / 50; rows of half a line, whose slices hold few clusters: D = 20, K = 1600 200000 35 / 41,
+// 500000 53 / 49, D = 27, K = 1000 150000 35 / 48, 500000 65 / 62.
+static bool buckets_beat_tables(int64_t N, int D, int nks)
+{
+    if (N < 65536 || nks < 4) return false;
+    const double least = D >= 16 ? 0.85e6 : (D % 4 == 0 ? 2.1e6 - 0.13e6 * nks : 2.6e6 - 0.14e6 * nks);
+    return (double)N * (nks - 2) >= least;
+}
+
+// ... and from the label sort, whose cost grows with the clusters; it reads each row by one wave instruction, which
+// ragged rows of several lines gain from.  Whole quads, sort / buckets: 2^21 x 32, K = 4096 174 / 98, 70000 x 64, K = 1000 46 / 38,
+// 500000 x 128, K = 512 91 / 88.  Others: 400000 x 17, K = 2500 62 / 57; 400000 x 33, K = 1000 56 / 67, 150000 x 33, K = 2500 51 / 47;
+// 150000 x 66, K = 1000 48 / 58, 70000 x 66, K = 2500 52 / 47, 400000 x 66, K = 2500 86 / 94; 10^6 x 66, K = 1000 142 / 187; 400000 x 97, K =
+// 8000 135 / 124, 70000 x 126, K = 300 40 / 47.
+static bool buckets_beat_sort(int64_t N, int D, int K)
+{
+    if (D % 4 == 0) return true;
+    const double per_point = D <= 32 ? -8e-6 : (D <= 64 ? 3e-6 : 45e-6);  // us that a bucket's row takes more
+    return 7e-3 * K - 14 > N * per_point;
 }
 
 static BucketPlan plan_bucket(ftk_dtype dtype, int64_t N, int D, int K)
@@ -1401,7 +1421,7 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
     fa.stats = stats;
     const BucketPlan bp = plan_bucket(dtype, N, D, K);
     if (bp.ok && w.room && !dmr && n_faults == 0 && g_tuning.update_path < 0 &&
-        (L.sorted_path || (u.nks >= 4 && N >= 65536 && (D >= 12 || (double)N * u.nks >= 2.4e6)))) {
+        (L.sorted_path ? buckets_beat_sort(N, D, K) : buckets_beat_tables(N, D, u.nks))) {
         uint32_t *entries = reinterpret_cast<uint32_t *>(w.sort_idx);
         long long *slabs = reinterpret_cast<long long *>(w.bucket_slab);
         int32_t *bounds = w.sort_lab, *totals = w.sort_cursor;

@@ -27,7 +27,8 @@ def _update(x, lab, C, mode):
 
 # N, D, K: rows shorter than a piece, every remainder, one table of many slices and few row blocks, buckets, sorted rows
 SIZES = [(900, 1, 5), (900, 3, 500), (3000, 5, 40), (3000, 6, 300), (3000, 7, 2000), (2500, 33, 50), (2500, 34, 400), (1500, 131, 700),
-         (4000, 257, 90), (700, 1030, 40), (400, 1100, 200), (70001, 13, 900), (70001, 35, 600), (66001, 130, 270), (66001, 5, 3000)]
+         (4000, 257, 90), (700, 1030, 40), (400, 1100, 200), (70001, 13, 900), (70001, 35, 600), (66001, 130, 270), (66001, 5, 3000),
+         (70001, 17, 2500), (70003, 67, 5000), (180001, 13, 8000), (66002, 127, 4001)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
