@@ -285,8 +285,9 @@ ftk_status ftk_kmeans_update_ft(ftk_dtype dtype, const void *X, const int32_t *l
                                 int32_t n_faults, ftk_ft_stats *stats, void *workspace,
                                 size_t workspace_bytes, void *hip_stream);
 
-/* Extents of the fault coordinates of ftk_kmeans_update_ft.  rows_aligned16 (whether X % 16 == 0 and
- * D * element size % 16 == 0) has no influence: all rows take the same path. */
+/* Extents of the fault coordinates of ftk_kmeans_update_ft (rows_aligned16: whether X rows are
+ * 16-byte aligned, i.e. X % 16 == 0 and D * element size % 16 == 0).  A register beyond what the last
+ * 16 bytes of a row hold names one that they do. */
 ftk_status ftk_update_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K,
                                int32_t rows_aligned16, ftk_geometry *out /* (host) */);
 

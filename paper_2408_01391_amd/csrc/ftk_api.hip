@@ -836,8 +836,7 @@ ftk_status ftk_update_geometry(ftk_dtype dtype, int64_t N, int32_t D, int32_t K,
         set_error("out is NULL");
         return FTK_EINVAL;
     }
-    (void)rows_aligned16;  // both take the same kernel
-    update_geometry(dtype, N, D, K, out);
+    update_geometry(dtype, rows_aligned16 != 0, N, D, K, out);
     return FTK_OK;
 }
 

@@ -175,7 +175,7 @@ ftk_status launch_update_batched_finalize(ftk_dtype dtype, int D, int K, const d
                                           int32_t *counts, const Workspace &w, const BatchedUpdatePlan &b,
                                           hipStream_t st);
 ftk_status launch_zero_ints(int32_t *p, int n, hipStream_t st);
-void update_geometry(ftk_dtype dtype, int64_t N, int D, int K, ftk_geometry *out);
+void update_geometry(ftk_dtype dtype, bool aligned16, int64_t N, int D, int K, ftk_geometry *out);
 ftk_status launch_gather_rows(ftk_dtype dtype, const void *X, int D, const int64_t *idx_dev, int K,
                               void *C, hipStream_t st);
 // ticket: one word, zero before the first call

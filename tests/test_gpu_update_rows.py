@@ -56,3 +56,22 @@ def test_update_of_rows_of_any_length(N, D, K, dtype):
                 if dtype == "f32":
                     first = out if first is None else first
                     assert np.array_equal(out, first)
+
+
+@pytest.mark.parametrize("D", [30, 31])
+def test_short_rows_of_doubles_beyond_the_cache(D):
+    """Label-sorted: by elements where rows begin at odd places, by pieces where they do not."""
+    N, K = 1000003, 2500
+    gen = torch.Generator(device=DEV).manual_seed(D)
+    flat = torch.randn(N * D + 1, generator=gen, device=DEV, dtype=torch.float64)
+    labels = torch.randint(K, (N,), generator=gen, device=DEV, dtype=torch.int32)
+    C = np.zeros((K, D))
+    for x in (flat[:-1].view(N, D), flat[1:].view(N, D)):
+        aligned = x.data_ptr() % 16 == 0 and D % 2 == 0
+        assert ftk.update_geometry(ftk.F64, N, D, K, aligned).regs_per_tile == (2 if aligned else 1)
+        sums = torch.zeros(K, D, device=DEV, dtype=torch.float64).index_add_(0, labels.long(), x)
+        want = torch.bincount(labels, minlength=K)
+        for mode in (ftk.FT_OFF, ftk.FT_STRICT):
+            out, n = _update(x, labels, C, mode)
+            assert np.array_equal(n, want.cpu().numpy())
+            check_centroids(out, (sums / want.unsqueeze(1)).cpu().numpy())
