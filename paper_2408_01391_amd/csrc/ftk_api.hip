@@ -410,7 +410,7 @@ static ftk_status assign_impl(const AssignCall &c, const Workspace &w, hipStream
     if (small)
         FTK_TRY(launch_small_assign(c, st));
     else if (direct)
-        FTK_TRY(launch_direct_assign(c, cut_direct(c.N, c.D, c.K), st));
+        FTK_TRY(launch_direct_assign(c, cut_direct(c.dtype, c.N, c.D, c.K), st));
     else if (scan.ok)
         FTK_TRY(launch_scan_assign(c, scan, carve_scan(w.scan, scan, c.N, c.D), w, c, st));
     else if (fast)
@@ -807,7 +807,7 @@ ftk_status ftk_kmeans_step_batched(ftk_dtype dtype, const void *X, int64_t N, in
             if (small)
                 FTK_TRY(launch_small_assign(c, st));
             else if (direct)
-                FTK_TRY(launch_direct_assign(c, cut_direct(N, D, K), st));
+                FTK_TRY(launch_direct_assign(c, cut_direct(dtype, N, D, K), st));
             else
                 FTK_TRY(launch_scan_assign(c, cut_part(scan, dtype, nb, D, K), carve_scan(w.scan, scan, N, D), wb, problem, st));
             FTK_TRY(launch_update_batch(dtype, Xb, labels + r0, nb, D, K, x_absmax, w, ub, b == 0, st));

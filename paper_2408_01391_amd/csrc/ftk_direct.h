@@ -12,7 +12,7 @@ struct DirectPlan {
 };
 bool direct_pays(ftk_dtype dtype, int64_t N, int D, int K);
 // the cut: distances depend on it in the last place (fp64), so parts of a problem take that of the whole
-DirectPlan cut_direct(int64_t N, int D, int K);
+DirectPlan cut_direct(ftk_dtype dtype, int64_t N, int D, int K);
 ftk_status launch_direct_assign(const AssignCall &c, const DirectPlan &p, hipStream_t st);
 
 }  // namespace ftk

@@ -1,15 +1,15 @@
 // Unprotected assignment in one launch: every distance in direct-difference form (Section 3.1.1), in double.
 //
-// The matrix kernels need norms ahead and a settlement behind, and cut the points into blocks of 256: three launches, and
-// too few workgroups where points are few (14665 x 520, K = 2: 58 of them, 65 us a call; 1278 x 639, K = 43: five, 63 us).
-// With few centroids they are far from the memory's rate too (426483 x 126, K = 2: 98 us, X read at 2.2 TB/s).  Here
+// The matrix kernels need norms ahead and a settlement behind, and cut the points into blocks of 128 or 256: three launches,
+// and too few workgroups where points are few (14665 x 520, K = 2: 115 of them, 33 us a call; 1278 x 639, K = 43: ten).
+// With few centroids they stay below the memory's rate too (426483 x 126, K = 2: 62 us, X read at 3.5 TB/s).  Here
 // fp64 arithmetic runs on the vector units at the fp32 rate, two instructions a multiplication, and nothing has to be
 // prepared, certified or settled: what a call below some 10^8 .. 10^9 multiplications spends on launches is more.
 //
 // L lanes share the features of a row (row-contiguous 16-byte pieces), each of them for R points against KG centroids at
 // a time: R + KG loads for 4 R KG differences, so that the vector units and not the caches set the pace.  TC such groups
 // take different centroids of the same points, the rest of the workgroup other points.  How L and TC are chosen: see
-// plan_direct().
+// cut_direct().
 #include <type_traits>
 
 #include "ftk_internal.h"
@@ -20,6 +20,7 @@ namespace ftk {
 
 constexpr int DR_THREADS = 256;
 constexpr int DR_R = 4;  // points of a lane
+static int direct_group(int K) { return K <= 2 ? 2 : (K <= 4 ? 4 : 8); }  // centroids of a lane at a time
 
 struct DirectArgs {
     int64_t N;
@@ -150,37 +151,55 @@ __global__ __launch_bounds__(DR_THREADS) void direct_kernel(const T *X, const T 
 // lanes of a row have is added up once per centroid).  Groups of lanes on other centroids of the same points: until 65536 threads
 // are busy (and while four of them take all centroids of long rows: one read of X); where that does not do, more lanes per
 // row.  Of 41 shapes timed with every choice (10^3 .. 10^6 points, 4 .. 1000 features, 2 .. 700 centroids, both types) this one is
-// near the best: 1286 x 73, K = 110 9.1 / 9.1 us, 1278 x 639, K = 43 15.7 / 14.1, 14665 x 520, K = 2 8.9 / 7.2, 426483 x 126, K = 2 45.4 / 44.3.
-DirectPlan cut_direct(int64_t N, int D, int K)
+// near the best: 1286 x 73, K = 110 9.1 / 9.1 us, 1278 x 639, K = 43 15.7 / 14.1, 14665 x 520, K = 2 8.9 / 7.2.
+// Up to four centroids the rows are all that a call waits for: twice the lanes ask for twice as much of a row at once (such lanes
+// / twice as many: 480049 x 60, K = 2 34 / 25, 46418 x 316, K = 3 18.5 / 14.5, fp64 1585025 x 70, K = 2 250 / 187, 1592522 x 32, K = 1 114 /
+// 80, fp32 1800000 x 14, K = 1 57 / 25, fp64 x 15, K = 3 170 / 81; four or eight lanes: 700000 x 52, K = 1 41 / 30, 44 31 / 28, 36 24 / 25, fp64 700000 x 34, K = 1 47 / 33, 1200000 x 48, K = 4 98 / 113),
+// but for fp32 data that the memory-side cache holds anyway (121474 x 108, K = 2 12.2 / 13.4, 54590 x 256 11.2 / 13.3).  So do few
+// doubles, whose rows are as long as those of twice as many floats (50000 x 29, K = 8 11.3 / 9.5, 4000 x 56, K = 50 11.5 / 9.3), until
+// the vector units set the pace (20000 x 17, K = 40 10.0 / 11.5, 20000 x 25, K = 60 12.0 / 15.2).
+DirectPlan cut_direct(ftk_dtype dtype, int64_t N, int D, int K)
 {
     DirectPlan p = {};
-    p.kg = K <= 2 ? 2 : (K <= 4 ? 4 : 8);
-    p.lanes = D <= 15 ? 1 : (D <= 32 ? 2 : (D <= 112 ? 4 : (D <= 448 ? 8 : 16)));
+    p.kg = direct_group(K);
+    const bool f64 = dtype == FTK_F64;
+    const bool twice = f64 ? K <= 4 || (double)N * D * K < (D > 32 ? 2e7 : 1.2e7)
+                           : K <= 4 && (D <= 112 ? (double)N * D >= (D < 16 ? 1e7 : 1.6e7) : N < 50000);
+    const int four = K > 4 ? 56 : (K > 2 ? 48 : (f64 ? 32 : 42));  // most features of four lanes, twice as many as usual
+    if (twice) p.lanes = D <= 8 ? 1 : (D <= 16 ? 2 : (D <= four ? 4 : (D <= 224 ? 8 : 16)));
+    else p.lanes = D <= 15 ? 1 : (D <= 32 ? 2 : (D <= 112 ? 4 : (D <= 448 ? 8 : 16)));
     const int64_t groups = ceil_div(K, p.kg), quads = ceil_div(N, DR_R);
     auto threads = [&] { return (quads * p.lanes) << p.tc_log2; };
     while ((1 << p.tc_log2) < groups && (p.lanes << p.tc_log2) < DR_THREADS && (threads() < 65536 || (groups <= 4 && D >= 64))) ++p.tc_log2;
-    while (p.lanes < 32 && 16 * p.lanes <= D && (p.lanes << p.tc_log2) < DR_THREADS && threads() < 40000) p.lanes *= 2;
+    while (p.lanes < 32 && (f64 ? 8 : 16) * p.lanes <= D && (p.lanes << p.tc_log2) < DR_THREADS && threads() < 40000) p.lanes *= 2;
     return p;
 }
 
 // Where one launch of double arithmetic beats the matrix kernels behind their norms and ahead of their refine kernel: 1400
-// random shapes of 500 .. 2 * 10^6 points, 2 .. 1024 features, 2 .. 1000 centroids and up to 10^9 multiplications timed with both
-// (matrix / this, whole calls, geometric means): fp32 up to 5 * 10^7 multiplications 2.6, to 7 * 10^7 1.9, beyond that with up to 4
-// centroids 1.4, 8 1.0, 16 0.7; fp64 2.1, 1.9, 1.2, 0.8, 0.6.  Near the lines, us:
-//   fp32  433961 x 64, K = 5 40 / 43; 16438 x 672, K = 13 51 / 62; 159477 x 576, K = 3 108 / 80; 35681 x 216, K = 12 31 / 39; 50387 x 128,
-//         K = 16 18 / 17; 641930 x 2, K = 110 53 / 38; 416968 x 4, K = 54 23 / 21
-//   fp64  393442 x 86, K = 2 70 / 81; 54801 x 136, K = 8 20.6 / 21.3; 353114 x 136, K = 3 83 / 83; 2627 x 635, K = 84 69 / 50;
-//         300000 x 100, K = 20 67 / 162
-// Two lanes to rows of almost their eight quads ask for too little at once where there are many (10^6 x 32, K = 2 47 / 61, but 300000
-// 12.3 / 11.5, 10^6 x 20 19 / 18 and x 33 80 / 30); rows of two or three features have nothing to share out among many
-// centroids' groups (333333 x 2, K = 150 46 / 35, 166666 x 2, K = 600 55 / 70; fp64 277777 x 3, K = 300 66 / 90).
+// random shapes of 500 .. 2 * 10^6 points, 2 .. 1024 features, 2 .. 1000 centroids and up to 10^9 multiplications timed with both, and
+// 900 again with the matrix kernels' rows by lines (matrix / this, whole calls, geometric means of the second lot): fp32 up to 7 * 10^7
+// multiplications 2.0, with up to 4 centroids 1.4 at any size, fp64 1.9 and 1.2; centroids that fill up the last group count like
+// others.  Near the lines, us:
+//   fp32  16438 x 672, K = 13 45 / 47; 159477 x 576, K = 3 80 / 75; 35681 x 216, K = 12 31 / 30; 50387 x 128, K = 16 18 / 17; 132339 x 41,
+//         K = 9 18 / 25; 33607 x 7, K = 278 20 / 27; 146809 x 124, K = 8 32 / 34; 478244 x 51, K = 5 49 / 41; 641930 x 2, K = 110 53 / 38
+//   fp64  393442 x 86, K = 2 70 / 58; 54801 x 136, K = 8 20.6 / 21.3; 333471 x 36, K = 5 33 / 36; 95490 x 56, K = 9 17.6 / 27.6; 2627 x 635,
+//         K = 84 69 / 50; 300000 x 100, K = 20 67 / 162
+// Two lanes to rows of almost their eight quads ask for too little at once where there are many (10^6 x 32, K = 8 47 / 60); rows
+// of two or three features have nothing to share out among many centroids' groups (333333 x 2, K = 150 46 / 35, 166666 x 2,
+// K = 600 55 / 70; fp64 277777 x 3, K = 300 66 / 90).
 bool direct_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     const double work = (double)N * D * K;
-    if (dtype == FTK_F32 && D > 24 && D <= 32 && N > 500000) return false;
-    if (dtype == FTK_F32)
-        return work <= 7e7 || (K <= 4 && work <= 1e9) || (K <= 8 && work <= 1.5e8) || (N <= 8000 && work <= 1e8) || (D < 4 && K <= 200 && work <= 2e8);
-    return work <= 5e7 || (K <= 4 && work <= 4e8) || (K <= 8 && work <= 7e7) || (N <= 8000 && work <= 1.5e8) || (D < 4 && K <= 200 && work <= 2.5e8);
+    if (K <= 4) return work <= (dtype == FTK_F32 ? 1e9 : 4e8);
+    const int KG = direct_group(K);
+    const double filled = D < 16 ? work : (double)N * D * (ceil_div(K, KG) * KG);
+    if (dtype == FTK_F32) {
+        if (D > 24 && D <= 32 && N > 500000) return false;
+        if (K <= 8) return work <= (D < 64 ? 1.5e8 : 1.1e8);
+        return filled <= (D < 16 && K > 100 ? 5e7 : 7e7) || (N <= 8000 && work <= 1e8) || (D < 4 && K <= 200 && work <= 2e8);
+    }
+    if (K <= 8) return filled <= 7e7 || (N <= 8000 && work <= 1.5e8) || (D < 4 && work <= 2.5e8);
+    return filled <= 5e7 || (N <= 8000 && work <= 1.5e8) || (D < 4 && K <= 200 && work <= 2.5e8);
 }
 
 template <typename T>

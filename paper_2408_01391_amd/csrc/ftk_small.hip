@@ -307,16 +307,25 @@ static bool small_work(ftk_dtype dtype, int64_t N, int D, int K)
     return work <= 5e7;
 }
 
-// (an assignment of longer rows is faster with several lanes a row, see ftk_direct.hip: fp32 6521 x 57, K = 95 15.8 / 12.2 us,
-// 58896 x 52, K = 12 12.9 / 10.9; fp64 4278 x 25, K = 91 18.2 / 9.4, 28555 x 19, K = 17 9.4 / 7.9, but 185114 x 23, K = 10 17 / 29)
 bool small_assign_fits(ftk_dtype dtype, int64_t N, int D, int K)
 {
     return D <= 64 && (int64_t)K * small_quads(D) * 4 <= SM_CELLS && small_work(dtype, N, D, K);
 }
+// An assignment of longer rows is faster with several lanes a row, see ftk_direct.hip (this kernel / that one): fp32 6521 x
+// 57, K = 95 15.8 / 12.2 us, 58896 x 52, K = 12 12.9 / 10.9, but 32803 x 48, K = 17 11.2 / 14.9, where a third of its last group of
+// centroids is padding; ragged ones with few centroids 600000 x 10, K = 4 13.7 / 9.2, 600000 x 25 49 / 27, but 600000 x 15 14.6 / 15.4;
+// fp64 4278 x 25, K = 91 18.2 / 9.4, 28555 x 19, K = 17 9.4 / 7.9, but 185114 x 23, K = 10 17 / 29, 20000 x 20, K = 100 14.3 / 18.9,
+// 60000 x 28, K = 26 11.7 / 13.6 (ragged 60000 x 25, K = 26 13.5 / 11.8, x 31 13.1 / 13.9).
 bool small_assign_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
-    const int most = dtype == FTK_F32 ? 32 : (N < 60000 ? 16 : 24);
-    return D <= most && small_assign_fits(dtype, N, D, K);
+    if (!small_assign_fits(dtype, N, D, K)) return false;
+    if (dtype == FTK_F32) {
+        if (K <= 4 && D > 8 && D < 32 && D != 15 && D % 4 != 0) return false;
+        return D <= 32 || (D % 4 == 0 && K > 8 && 5 * ceil_div(K, 8) * 8 >= 7 * (int64_t)K);
+    }
+    const double work = (double)N * D * K;
+    if (D > 24) return D <= 32 && (D % 4 == 0 || D >= 30) && work >= 2.5e7;
+    return D <= 16 || N >= 60000 || work >= (D > 20 ? 1.5e7 : 2.5e7);
 }
 
 bool small_fit_pays(ftk_dtype dtype, int64_t N, int D, int K)

@@ -41,6 +41,24 @@ def test_direct_assign_matches_oracle(N, D, K, dtype):
     assert ftk.stats_dict(stats)["refined"] == 0
 
 
+# the lanes and groups that the list above leaves out: few centroids, and doubles with one or two lanes
+@pytest.mark.parametrize("N,D,K,dtype", [
+    (3001, 9, 1, "f32"), (3001, 9, 3, "f32"), (3001, 17, 2, "f32"), (3001, 17, 4, "f32"), (3001, 64, 3, "f32"),
+    (100003, 20, 30, "f32"), (2001, 150, 3, "f32"), (70, 1500, 1, "f32"), (70, 1500, 3, "f32"), (700001, 20, 4, "f32"),
+    (3600001, 7, 2, "f64"), (1700001, 8, 4, "f64"), (1700001, 16, 2, "f64"), (1100001, 16, 4, "f64"), (30001, 18, 40, "f64"),
+    (3001, 17, 2, "f64"), (70, 1500, 1, "f64"), (70, 1500, 3, "f64"), (14665, 520, 3, "f64")])
+def test_every_cut_of_the_lanes(N, D, K, dtype):
+    print("cut", N, D, K, dtype, flush=True)
+    X, C = synth.random_problem(N + D + K, N, D, K, dtype)
+    stats = ftk.new_stats(DEV)
+    labels, mind = ftk.kmeans_assign(to_dev(X), to_dev(C), stats=stats)
+    check(X, C, dtype, labels.cpu().numpy(), mind.cpu().numpy())
+    flat = torch.empty(X.size + 1, dtype=mind.dtype, device=DEV)
+    flat[1:] = to_dev(X).flatten()
+    off, _ = ftk.kmeans_assign(flat[1:].view(N, D), to_dev(C), want_mindist=False)
+    assert torch.equal(off, labels) and ftk.stats_dict(stats)["refined"] == 0
+
+
 @pytest.mark.parametrize("N,D,K", [(6267, 22, 169), (5000, 30, 200), (3001, 64, 128), (8000, 17, 341)])
 def test_small_problems_in_double_that_the_scan_would_take(N, D, K):
     X, C = synth.random_problem(N, N, D, K, "f64")
