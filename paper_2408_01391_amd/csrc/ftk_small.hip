@@ -350,9 +350,9 @@ static int small_lanes_log2(int64_t N, int K, int pt, int *grid)
 }
 
 // Rows ahead, us without / with: fp32 20000 x 24, K = 100 13.9 / 13.1, 700000 x 20, K = 3 16.6 / 14.6, fit of 4096 x 16, K = 8, ten
-// iterations 139 / 136; 14 or 15 doubles, which are read one by one, 200000 x 15, K = 9 12.3 / 9.9.  Longer rows and other doubles
-// pay for the registers with a wave: 60000 x 32, K = 26 10.6 / 12.0; fp64 700000 x 9, K = 3 14.7 / 16.0, 700000 x 16, K = 3 19.0 /
-// 21.5, 60000 x 20, K = 26 9.7 / 10.3, fit of 20000 x 32, K = 20, five iterations 159 / 206.
+// iterations 139 / 136; 14 doubles and more that are read one by one, 200000 x 15, K = 9 12.3 / 9.9, 700000 x 22, K = 3 51 / 36.
+// Longer rows and other doubles pay for the registers with a wave: 60000 x 32, K = 26 10.6 / 12.0; fp64 700000 x 9, K = 3 14.7 / 16.0,
+// 700000 x 16, K = 3 19.0 / 21.5, 60000 x 20, K = 26 9.7 / 10.3, fit of 20000 x 32, K = 20, five iterations 159 / 206.
 template <typename T, bool FIT>
 static void launch_small_t(const SmallArgs &a, int grid, hipStream_t st)
 {
@@ -362,11 +362,11 @@ static void launch_small_t(const SmallArgs &a, int grid, hipStream_t st)
     const dim3 g((unsigned)grid), b(SM_THREADS);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, st, a); };
     constexpr bool F32 = sizeof(T) == 4;
-    const bool ahead = F32 || (!FIT && (a.D == 14 || a.D == 15));
+    const bool ahead = F32 || (!FIT && a.D > 13 && a.D % 4 != 0);
     switch (nq) {
     case 2: launch(small_kernel<T, 2, 2, FIT, F32>); break;
     case 4: launch(ahead ? small_kernel<T, 4, 2, FIT, F32 || !FIT> : small_kernel<T, 4, 2, FIT, F32>); break;
-    case 6: launch(small_kernel<T, 6, 2, FIT, F32>); break;
+    case 6: launch(ahead ? small_kernel<T, 6, 2, FIT, F32 || !FIT> : small_kernel<T, 6, 2, FIT, F32>); break;
     case 8: launch(small_kernel<T, 8, 2, FIT, false>); break;
     case 12: launch(small_kernel<T, 12, 1, FIT, false>); break;
     default: launch(small_kernel<T, 16, 1, FIT, false>); break;
