@@ -19,6 +19,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "ftk_quads.h"
+
 namespace ftk {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -81,13 +83,11 @@ struct Mma<double> {
 // shorter than a piece.  Pieces against elements, whole calls: 155948 x 209, K = 21, strict 70 / 167 us; 102957 x 102, K = 7
 // 26 / 53; 426483 x 126, K = 2 81 / 98.
 enum RowAccess : int { ROWS_ELEMENTS = 0, ROWS_ALIGNED = 1, ROWS_PIECES = 2 };
-typedef float floatx4e __attribute__((ext_vector_type(4), aligned(4)));
-typedef double doublex2e __attribute__((ext_vector_type(2), aligned(8)));
 template <typename T>
 __device__ __forceinline__ typename Mma<T>::frag_t load_piece(const T *p)
 {
-    if constexpr (sizeof(T) == 4) return *reinterpret_cast<const floatx4e *>(p);
-    else return *reinterpret_cast<const doublex2e *>(p);
+    if constexpr (sizeof(T) == 4) return *reinterpret_cast<const float4e *>(p);
+    else return *reinterpret_cast<const double2e *>(p);
 }
 static inline int row_access(const void *a, const void *b, int D, size_t element)
 {

@@ -1073,14 +1073,15 @@ __global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8
             constexpr int L = decltype(lanes)::value;
             settle_own<T, L, KIND>(a.X, own, pb, FORM == FORM_HALF, *reinterpret_cast<OwnShared<T, L> *>(lds4));
         };
-        // an octet's rows go to two lanes, a triple's to two or four, those of two blocks to four or eight
+        // an octet's rows go to two lanes, a triple's to two or four, those of two blocks to four or, of calls that choose
+        // their form, eight: settles_own()
         if constexpr (FORM == FORM_OCTET) {
             settle(std::integral_constant<int, 2>{});
         } else if constexpr (FORM == FORM_TRIPLE) {
             if (settle_lanes(a.D) == 2) settle(std::integral_constant<int, 2>{});
             else settle(std::integral_constant<int, 4>{});
         } else {
-            if (settle_lanes(a.D) == 4) settle(std::integral_constant<int, 4>{});
+            if (!GATED || settle_lanes(a.D) == 4) settle(std::integral_constant<int, 4>{});
             else settle(std::integral_constant<int, 8>{});
         }
     }

@@ -695,7 +695,7 @@ __global__ __launch_bounds__(256) void sorted_reduce_kernel(const T *X, const in
                                                             int32_t *slot_lab, UpdateFtArgs ft)
 {
     using F = typename Mma<T>::frag_t;
-    using FE = std::conditional_t<sizeof(T) == 4, floatx4e, doublex2e>;
+    using FE = std::conditional_t<sizeof(T) == 4, float4e, double2e>;
     constexpr int E = AL != ROWS_ELEMENTS ? Mma<T>::E : 1;
     constexpr bool TWO_LIMB = sizeof(T) == 8;
     constexpr int UNR = 8;
@@ -1546,7 +1546,6 @@ BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, int64_t N, int64_t batch_
     b.nds = u.nds;
     b.tx_log2 = u.tx_log2;
     b.chunks = u.chunks;
-    b.pieces = u.pieces;
     const int64_t nbatch = ceil_div(N, batch_rows);
     b.scale_rows = dtype == FTK_F64 ? u.rows_per_chunk * nbatch : N;
     b.ok = u.chunks <= update_slab_chunks_max(N) && (int64_t)u.chunks * K * D <= update_slab_cells_max(N, D, K);
