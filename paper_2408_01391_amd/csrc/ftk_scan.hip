@@ -2266,28 +2266,36 @@ static int resident_blocks(int D)
 //         D = 4    N = 60000 K = 512 22.8 / 28.4, 1024 33.4 / 32.2; N = 10^6 K = 256 61.1 / 62.2, 512 96.1 / 88.0
 //   fp64  D = 32   N = 20000 K = 192 21.2 / 22.0, 384 33.4 / 23.1; N = 60000 K = 128 22.3 / 23.2, 256 34.5 / 27.3; N = 200000 K = 64 34.0 / 37.6,
 //                  96 47.1 / 38.7
-//         D = 256  N = 6000 K = 128 52.9 / 44.9, 256 96.3 / 46.7; N = 60000 K = 96 76.7 / 83.0, 192 119.2 / 95.1
+// Rows beyond 128 features again with the matrix kernels that read them by lines (3000 .. 10^6 points, 132 .. 1600 features, 8 .. 224
+// centroids, some 2300 calls):
+//   fp32  N = 20000 D = 256 K = 48 32 / 39, 66 52 / 43; D = 512 K = 48 62 / 58; N = 60000 D = 132 K = 80 36 / 45; D = 320 K = 50 55 / 54, 80
+//         73 / 64; D = 1024 K = 50 155 / 133; N = 200000 D = 256 K = 64 89 / 97, 80 141 / 112; D = 1000 K = 64 392 / 400; N = 500000
+//         D = 256 K = 50 199 / 224, 80 276 / 257
+//   fp64  N = 20000 D = 256 K = 100 54 / 53, 130 71 / 54; D = 1024 K = 115 176 / 140; N = 60000 D = 256 K = 80 70 / 75, 115 92 / 76;
+//         N = 200000 D = 320 K = 50 184 / 233, 100 316 / 253; N = 500000 D = 256 K = 66 451 / 420, 100 553 / 425
 static int scan_from(ftk_dtype dtype, int64_t N, int D)
 {
-    static const int from[2][5][6] = {
-        // D < 8, 8, .. 16, .. 48, .. 128, beyond
-        {{768, 512, 256, 160, 96, 48},       // fp32: N < 9 000
-         {768, 512, 320, 176, 160, 80},      //       N < 36 000
-         {1024, 640, 448, 256, 224, 144},    //       N < 110 000
-         {768, 640, 160, 96, 96, 96},        //       N < 450 000
-         {384, 384, 96, 72, 72, 96}},        //       more
-        {{512, 512, 384, 160, 160, 144},     // fp64
-         {512, 512, 384, 288, 272, 160},
-         {512, 512, 320, 192, 224, 160},
-         {96, 96, 96, 96, 96, 144},
-         {48, 48, 48, 72, 80, 144}}};
-    const int d = D < 8 ? 0 : (D == 8 ? 1 : (D <= 16 ? 2 : (D <= 48 ? 3 : (D <= 128 ? 4 : 5))));
+    static const int from[2][5][9] = {
+        // D < 8, 8, .. 16, .. 48, .. 128, .. 160, .. 384, .. 1024, beyond
+        {{768, 512, 256, 160, 96, 48, 48, 48, 48},       // fp32: N < 9 000
+         {768, 512, 320, 176, 160, 80, 65, 48, 48},      //       N < 36 000
+         {1024, 640, 448, 256, 224, 113, 80, 48, 65},    //       N < 110 000
+         {768, 640, 160, 96, 96, 96, 65, 65, 96},        //       N < 450 000
+         {384, 384, 96, 72, 72, 96, 65, 65, 96}},        //       more
+        {{512, 512, 384, 160, 160, 144, 144, 144, 144},  // fp64
+         {512, 512, 384, 288, 272, 129, 112, 129, 129},
+         {512, 512, 320, 192, 224, 112, 96, 96, 113},
+         {96, 96, 96, 96, 96, 81, 81, 65, 96},
+         {48, 48, 48, 72, 80, 81, 81, 81, 96}}};
+    const int beyond[] = {160, 384, 1024};
+    int d = D < 8 ? 0 : (D == 8 ? 1 : (D <= 16 ? 2 : (D <= 48 ? 3 : (D <= 128 ? 4 : 5))));
+    for (int w : beyond) d += D > w;
     const int n = N < 9000 ? 0 : (N < 36000 ? 1 : (N < 110000 ? 2 : (N < 450000 ? 3 : 4)));
     int k = from[dtype == FTK_F32 ? 0 : 1][n][d];
-    // fp32 rows that are not whole 16-byte pieces.  The lines lie where matrix kernels that load these rows element by element
-    // lose (60000 x 867, K = 20 424 / 119; 6000 x 337, K = 8 150 / 41; 4 * 10^5 x 45, K = 50 70 / 52; 200000 x 45, K = 48 38.5 / 34.5;
-    // 200000 x 6, K = 192 33.1 / 28.3).  Those read 16-byte pieces now and would win some of these calls back, with the distances
-    // of the expanded form: the lines stay for the direct ones that such calls get here.
+    // fp32 rows that are not whole 16-byte pieces: lines by precision, not by speed.  They were drawn against matrix kernels that
+    // read such rows element by element; by pieces those are the faster ones again for few centroids (200000 x 131, K = 32 44 / 74,
+    // 60000 x 337, K = 20 47 / 59, 350000 x 27, K = 32 25 / 39), level from 80 or so of long rows (200000 x 131, K = 80 90 / 91), 48 of
+    // short ones.  But these calls return distances in direct-difference form, and the matrix kernels' are of the expanded one.
     if (dtype == FTK_F32 && D % 4 != 0) {
         if (D >= 96) k = 8;
         else if (n >= 3) k = d == 0 ? 192 : (d == 2 ? 96 : (N >= 300000 ? 32 : 48));

@@ -148,3 +148,19 @@ def test_scan_on_both_sides_of_its_rule(N, D, K, dtype):
         labels, mind = run(X, C)
         rows = np.arange(0, n, max(1, n // 4000))
         check_assign(X, C, labels, mind, rows=rows)
+
+
+@pytest.mark.parametrize("dtype,N,D,K", [("f32", 20001, 160, 85), ("f32", 9001, 161, 66), ("f32", 36001, 384, 90), ("f32", 3001, 1024, 49),
+                                         ("f32", 110003, 164, 66), ("f32", 60001, 1028, 66), ("f64", 9001, 161, 113),
+                                         ("f64", 110003, 130, 82), ("f64", 36001, 385, 97), ("f64", 20001, 1025, 130)])
+def test_lines_of_rows_beyond_128_features(dtype, N, D, K):
+    """On the near side of a line distances may be of the expanded form; on the far side they are differences' squares."""
+    print("line", dtype, N, D, K, flush=True)
+    for k in (K - 4, K):
+        X, C = offset_blobs(N + D, N, D, k, 3.0, dtype)
+        labels, mind = run(X, C)
+        rows = np.arange(0, N, max(1, N // 3000))
+        check_assign(X, C, labels, mind, rows=rows)
+    ref = ((X[rows].astype(np.float64) - C[labels[rows]].astype(np.float64)) ** 2).sum(1)
+    eps = 2.0 ** -24 if dtype == "f32" else 2.0 ** -53
+    assert np.all(np.abs(mind[rows].astype(np.float64) - ref) <= 2 * (D + 4) * eps * ref)
