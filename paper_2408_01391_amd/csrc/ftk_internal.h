@@ -164,7 +164,7 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
 // update accumulated over several launches (batches of rows), finished by one averaging pass
 struct BatchedUpdatePlan {
     int Ks, Ds, nks, nds, tx_log2, chunks;
-    bool ok;
+    bool pieces, ok;
     int64_t scale_rows;
 };
 BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, int64_t N, int64_t batch_rows, int D, int K);

@@ -32,7 +32,7 @@ struct UpdatePlan {
     int Ks, Ds, nks, nds, tx_log2;
     int64_t rows_per_chunk;
     int chunks;
-    bool pieces;  // rows hold 16-byte pieces (at element alignment, the last one moved back into the row)
+    bool pieces;  // the tables take rows by 16-byte pieces (at element alignment, the last one moved back into the row)
 };
 
 // Row chunks of the LDS path never exceed UPD_TARGET_WGS or one per 64 rows; with S
@@ -104,6 +104,15 @@ static UpdatePlan plan_update(ftk_dtype dtype, int64_t N, int D, int K)
     int l2 = 0;
     while ((1 << l2) < ppr && l2 < 8) ++l2;
     u.tx_log2 = l2;
+    // Pieces of ragged rows that leave a quarter of a pass's lanes idle lose to elements, which fill them and add to a table
+    // without bank conflicts, where few clusters share the adds and the rows come from the memory-side cache (pieces /
+    // elements: 425 x 1063, K = 4 23.9 / 18.4 us, 883 x 631, K = 7 18.4 / 15.7, 77632 x 530, K = 7 strict 86 / 79, 2347 x 1418, K = 11
+    // 22.5 / 20.1; fp64 43353 x 665, K = 3 57 / 50; but 60314 x 490, K = 6 38 / 47, 23191 x 518, K = 16 30 / 38, 13251 x 1803, K = 3
+    // 34 / 37, and beyond that cache 206658 x 742, K = 13 315 / 396, 42297 x 1561, K = 7 112 / 122; fp64 49042 x 771, K = 5 71 / 77).
+    const int width = 256, full = (int)ceil_div(ppr, width) * width;
+    if (D % E != 0 && K < 16 && ppr > (dtype == FTK_F32 ? width / 2 : width) && 32 * ppr <= 25 * full &&
+        (double)N * D * (16 / E) < 2.4e8)
+        u.pieces = false;
     // a workgroup takes UPD_THREADS >> tx_log2 rows per pass; at least 16 passes (and 64 rows) per
     // chunk, so that long rows of a mid-sized problem still spread over all CUs; four where a table more is soon written and
     // read (36311 x 63, K = 5 18.9 us with 16, 13.0 with four; 36000 x 64, K = 5 17.4 / 12.4), and down to four where a launch has
@@ -1339,7 +1348,8 @@ static UpdateLaunch plan_update_launch(ftk_dtype dtype, bool aligned16, int64_t 
                              ((int64_t)K * D <= 4 * UPD_CELLS && x_bytes < 268435456.0);
     L.sorted_path = (size_t)D * esz >= 64 && N >= 65536 && !small_table;
     if (g_tuning.update_path >= 0) L.sorted_path = g_tuning.update_path == 1;
-    L.E = L.u.pieces ? (dtype == FTK_F32 ? 4 : 2) : 1;
+    L.E = dtype == FTK_F32 ? 4 : 2;
+    if (D < L.E || (!L.sorted_path && !L.u.pieces)) L.E = 1;
     // Short rows of doubles at odd places, gathered from beyond the memory-side cache: by elements, whose requests end where
     // lines do (pieces / elements: 2081309 x 19, K = 1213 214 / 195 us, 1600000 x 27, K = 2500 206 / 193; 900000 x 31 117 / 130,
     // 1000000 x 33, K = 2500 132 / 132).
@@ -1415,6 +1425,7 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
     const UpdateLaunch L = plan_update_launch(dtype, (uintptr_t)X % 16 == 0, N, D, K);
     const UpdatePlan &u = L.u;
     const int rows = row_access(X, X, D, dtype == FTK_F32 ? 4 : 8);
+    const int table_rows = u.pieces ? rows : (int)ROWS_ELEMENTS;
     const int64_t cells = (int64_t)K * D;
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(w.fx_sums);
     const bool dmr = ft_mode != FTK_FT_OFF;
@@ -1514,10 +1525,10 @@ ftk_status launch_update(ftk_dtype dtype, const void *X, const int32_t *labels, 
                        scale_rows, 0, fa)
 #define FTK_LAUNCH_ACC_T(T)                                \
     do {                                                   \
-        if (rows == ROWS_ALIGNED && dmr) FTK_LAUNCH_ACC(T, ROWS_ALIGNED, true);      \
-        else if (rows == ROWS_ALIGNED) FTK_LAUNCH_ACC(T, ROWS_ALIGNED, false);       \
-        else if (rows == ROWS_PIECES && dmr) FTK_LAUNCH_ACC(T, ROWS_PIECES, true);   \
-        else if (rows == ROWS_PIECES) FTK_LAUNCH_ACC(T, ROWS_PIECES, false);         \
+        if (table_rows == ROWS_ALIGNED && dmr) FTK_LAUNCH_ACC(T, ROWS_ALIGNED, true);      \
+        else if (table_rows == ROWS_ALIGNED) FTK_LAUNCH_ACC(T, ROWS_ALIGNED, false);       \
+        else if (table_rows == ROWS_PIECES && dmr) FTK_LAUNCH_ACC(T, ROWS_PIECES, true);   \
+        else if (table_rows == ROWS_PIECES) FTK_LAUNCH_ACC(T, ROWS_PIECES, false);         \
         else if (dmr) FTK_LAUNCH_ACC(T, ROWS_ELEMENTS, true);                        \
         else FTK_LAUNCH_ACC(T, ROWS_ELEMENTS, false);                                \
     } while (0)
@@ -1544,6 +1555,7 @@ BatchedUpdatePlan plan_update_batched(ftk_dtype dtype, int64_t N, int64_t batch_
     b.Ds = u.Ds;
     b.nks = u.nks;
     b.nds = u.nds;
+    b.pieces = u.pieces;
     b.tx_log2 = u.tx_log2;
     b.chunks = u.chunks;
     const int64_t nbatch = ceil_div(N, batch_rows);
@@ -1569,7 +1581,7 @@ ftk_status launch_update_batch(ftk_dtype dtype, const void *Xb, const int32_t *l
     hipLaunchKernelGGL((update_accumulate_kernel<T, AL, false>), grid, block, lds, st, (const T *)Xb, labels_b, \
                        nb, D, K, absmax, slabs, w.upd_cslab, b.Ks, b.Ds, b.nds, b.tx_log2, rows_per_chunk,  \
                        b.scale_rows, first ? 0 : 1, fa)
-    const int rows = row_access(Xb, Xb, D, dtype == FTK_F32 ? 4 : 8);
+    const int rows = b.pieces ? row_access(Xb, Xb, D, dtype == FTK_F32 ? 4 : 8) : (int)ROWS_ELEMENTS;
     if (dtype == FTK_F32) {
         if (rows == ROWS_ALIGNED) FTK_LAUNCH_ACC(float, ROWS_ALIGNED);
         else if (rows == ROWS_PIECES) FTK_LAUNCH_ACC(float, ROWS_PIECES);

@@ -75,3 +75,37 @@ def test_short_rows_of_doubles_beyond_the_cache(D):
             out, n = _update(x, labels, C, mode)
             assert np.array_equal(n, want.cpu().numpy())
             check_centroids(out, (sums / want.unsqueeze(1)).cpu().numpy())
+
+
+@pytest.mark.parametrize("N,D,K,dtype,elements", [(700, 529, 4, "f32", True), (403, 1261, 5, "f32", True), (900, 631, 13, "f32", True),
+                                                  (300, 1418, 11, "f32", True), (500, 727, 2, "f64", True), (301, 1027, 3, "f64", True),
+                                                  (700, 529, 16, "f32", False), (700, 511, 4, "f32", False), (500, 509, 2, "f64", False)])
+def test_long_ragged_rows_of_few_clusters(N, D, K, dtype, elements):
+    """By elements where pieces would leave much of a pass idle, with every flip that the geometry names."""
+    per_lane = ftk.update_geometry(ftk.F32 if dtype == "f32" else ftk.F64, N, D, K, False).regs_per_tile // 4
+    assert per_lane == (1 if elements else 4 if dtype == "f32" else 2)
+    rng = np.random.default_rng(D)
+    X = rng.normal(size=(N, D)).astype(np.float32 if dtype == "f32" else np.float64)
+    labels = rng.integers(0, K, N).astype(np.int32)
+    ref, counts = oracle.update(X, labels, X[:K])
+    flat = torch.empty(X.size + 1, dtype=torch.float32 if dtype == "f32" else torch.float64, device=DEV)
+    flat[1:] = to_dev(X).flatten()
+    clean = {}
+    for x in (to_dev(X), flat[1:].view(N, D)):
+        for mode in (ftk.FT_OFF, ftk.FT_STRICT):
+            out, n = _update(x, to_dev(labels), X[:K], mode)
+            check_centroids(out, ref)
+            assert np.array_equal(n, counts) and np.array_equal(out, clean.setdefault(dtype, out))
+    for lane, reg in ((0, 0), (63, 1), (17, 4 * per_lane - 1)):
+        C, stats, faults = to_dev(X[:K].copy()), ftk.new_stats(DEV), ftk.make_faults([(0, 1, 0, reg, lane, 54)], DEV)
+        ftk.kmeans_update(to_dev(X), to_dev(labels), C, ft_mode=ftk.FT_CORRECT, faults=faults, stats=stats)
+        torch.cuda.synchronize()
+        st = ftk.stats_dict(stats)
+        assert st["injected"] == st["detected"] == st["recomputed"] >= 1 and np.array_equal(C.cpu().numpy(), clean[dtype])
+    if dtype == "f32":
+        C0 = to_dev(X[:K].copy())
+        lab, _, n = ftk.kmeans_step_batched(to_dev(X), C0, 257)
+        C1 = to_dev(X[:K].copy())
+        lab1, _ = ftk.kmeans_assign(to_dev(X), C1)
+        ftk.kmeans_update(to_dev(X), lab1, C1)
+        assert torch.equal(lab, lab1) and torch.equal(C0, C1)
