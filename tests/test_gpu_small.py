@@ -31,6 +31,21 @@ def test_small_assign_matches_oracle(N, D, K, dtype):
     assert np.all(np.abs(mind.astype(np.float64) - ref[1]) <= tol * ref[1] * 1.01)
 
 
+@pytest.mark.parametrize("N,D,K", [(9429, 39, 70), (20165, 39, 38), (13186, 54, 67), (32803, 48, 17), (11000, 64, 35), (20001, 33, 35)])
+def test_small_assign_of_longer_rows(N, D, K):
+    """Rows of 33 .. 64 floats where lanes that share a row would have little to do in their last round."""
+    print("small, longer rows", N, D, K, flush=True)
+    X, C = synth.random_problem(N + D + K, N, D, K, "f32")
+    flat = torch.empty(X.size + 1, dtype=torch.float32, device=DEV)
+    flat[1:] = to_dev(X).flatten()
+    ref = oracle.assign(X, C)
+    for x in (to_dev(X), flat[1:].view(N, D)):
+        labels, mind = ftk.kmeans_assign(x, to_dev(C))
+        labels, mind = labels.cpu().numpy(), mind.cpu().numpy()
+        check_assign(X, C, labels, mind, ref=ref)
+        assert np.all(np.abs(mind.astype(np.float64) - ref[1]) <= EPS["f32"] * ref[1] * 1.01)
+
+
 def test_small_assign_ties_offsets_and_values_that_are_not_numbers():
     X, C = synth.random_problem(4, 900, 12, 40, "f32")
     C[20:] = C[:20]
