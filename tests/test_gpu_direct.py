@@ -44,7 +44,7 @@ def test_direct_assign_matches_oracle(N, D, K, dtype):
 # the lanes and groups that the list above leaves out: few centroids, and doubles with one or two lanes
 @pytest.mark.parametrize("N,D,K,dtype", [
     (3001, 9, 1, "f32"), (3001, 9, 3, "f32"), (3001, 17, 2, "f32"), (3001, 17, 4, "f32"), (3001, 64, 3, "f32"),
-    (100003, 20, 30, "f32"), (2001, 150, 3, "f32"), (70, 1500, 1, "f32"), (70, 1500, 3, "f32"), (700001, 20, 4, "f32"),
+    (85003, 20, 30, "f32"), (2001, 150, 3, "f32"), (70, 1500, 1, "f32"), (70, 1500, 3, "f32"), (700001, 20, 4, "f32"),
     (3600001, 7, 2, "f64"), (1700001, 8, 4, "f64"), (1700001, 16, 2, "f64"), (1100001, 16, 4, "f64"), (30001, 18, 40, "f64"),
     (3001, 17, 2, "f64"), (70, 1500, 1, "f64"), (70, 1500, 3, "f64"), (14665, 520, 3, "f64")])
 def test_every_cut_of_the_lanes(N, D, K, dtype):
