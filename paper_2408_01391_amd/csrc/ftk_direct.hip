@@ -187,7 +187,7 @@ DirectPlan cut_direct(ftk_dtype dtype, int64_t N, int D, int K)
 // Rows of up to 64 features fill a few rounds of their lanes, and few groups of centroids a few rounds: where there are many points
 // the line lies by what the rounds hold (47873 x 52, K = 22 17.0 / 18.8, 74775 x 36, K = 21 15.3 / 22.3, 58280 x 51, K = 15 15.3 / 10.0;
 // 34278 x 20, K = 91 16.4 / 21.2, 69142 x 12, K = 79 17.1 / 22.9, 51448 x 31, K = 37 14.7 / 20.9, 26719 x 16, K = 127 15.7 / 13.0; fp64
-// 33958 x 58, K = 20 16.8 / 21.9, 16727 x 58, K = 48 16.1 / 22.1, 66468 x 38, K = 10 14.4 / 18.3, 50704 x 59, K = 10 15.5 / 14.0).
+// 33958 x 58, K = 20 16.8 / 21.9, 16727 x 58, K = 48 16.1 / 22.1, 10630 x 54, K = 77 18.8 / 22.8, 66468 x 38, K = 10 14.4 / 18.3, 50704 x 59, K = 10 15.5 / 14.0).
 // Two lanes to rows of almost their eight quads ask for too little at once where there are many (10^6 x 32, K = 8 47 / 60); rows
 // of two or three features have nothing to share out among many centroids' groups (333333 x 2, K = 150 46 / 35, 166666 x 2,
 // K = 600 55 / 70; fp64 277777 x 3, K = 300 66 / 90).
@@ -197,11 +197,11 @@ bool direct_pays(ftk_dtype dtype, int64_t N, int D, int K)
     if (K <= 4) return work <= (dtype == FTK_F32 ? 1e9 : 4e8);
     const int KG = direct_group(K);
     const double filled = D < 16 ? work : (double)N * D * (ceil_div(K, KG) * KG);
-    if (K > 8 && D > (dtype == FTK_F32 ? 8 : 32) && D <= 64 && N >= (dtype == FTK_F32 && D > 32 ? 30000 : 16000)) {
+    if (K > 8 && D > (dtype == FTK_F32 ? 8 : 32) && D <= 64 && N >= (dtype == FTK_F64 ? 8000 : (D > 32 ? 30000 : 16000))) {
         const DirectPlan p = cut_direct(dtype, N, D, K);
         const int64_t centroids = (int64_t)KG << p.tc_log2, features = 4 * p.lanes;  // of a round
         const double rounds = (double)ceil_div(K, centroids) * centroids * (ceil_div(D / 4, p.lanes) * features + D % 4);
-        if ((double)N * rounds > (dtype == FTK_F32 ? (D > 32 ? 7.2e7 : 7.6e7) : 5.2e7)) return false;
+        if ((double)N * rounds > (dtype == FTK_F32 ? (D > 32 ? 7.2e7 : 7.6e7) : (N < 16000 ? 8.2e7 : 5.1e7))) return false;
     }
     if (dtype == FTK_F32) {
         if (D > 24 && D <= 32 && N > 500000) return false;

@@ -314,8 +314,9 @@ bool small_assign_fits(ftk_dtype dtype, int64_t N, int D, int K)
 }
 // An assignment of longer rows is faster with several lanes a row, see ftk_direct.hip (this kernel / that one): fp32 6521 x
 // 57, K = 95 15.8 / 12.2 us, 58896 x 52, K = 12 12.9 / 10.9, but 32803 x 48, K = 17 11.2 / 14.9, where a third of its last group of
-// centroids is padding, and 9429 x 39, K = 70 14.0 / 17.4, 20165 x 39, K = 38 13.6 / 16.5, 13186 x 54, K = 67 17.0 / 20.1, where lanes
-// and groups are half empty in their last round (6303 x 62, K = 69 13.5 / 12.1, 91489 x 58, K = 9 23.8 / 19.1); ragged ones with few centroids 600000 x 10, K = 4 13.7 / 9.2, 600000 x 25 49 / 27, but 600000 x 15 14.6 / 15.4;
+// centroids is padding, and 9429 x 39, K = 70 14.0 / 17.4, 13186 x 54, K = 67 17.0 / 20.1, 22036 x 48, K = 44 13.8 / 15.9, 17320 x 39,
+// K = 67 19.0 / 22.6, where the last of several rounds of centroids or features is nearly empty (one round 6303 x 62, K = 69
+// 13.5 / 12.1, 15822 x 53, K = 46 13.9 / 12.0; no features left over 42028 x 51, K = 17 19.8 / 16.4); ragged ones with few centroids 600000 x 10, K = 4 13.7 / 9.2, 600000 x 25 49 / 27, but 600000 x 15 14.6 / 15.4;
 // fp64 4278 x 25, K = 91 18.2 / 9.4, 28555 x 19, K = 17 9.4 / 7.9, but 185114 x 23, K = 10 17 / 29, 20000 x 20, K = 100 14.3 / 18.9,
 // 60000 x 28, K = 26 11.7 / 13.6 (ragged 60000 x 25, K = 26 13.5 / 11.8, x 31 13.1 / 13.9).
 bool small_assign_pays(ftk_dtype dtype, int64_t N, int D, int K)
@@ -325,8 +326,10 @@ bool small_assign_pays(ftk_dtype dtype, int64_t N, int D, int K)
         if (K <= 4 && D > 8 && D < 32 && D != 15 && D % 4 != 0) return false;
         if (D <= 32 || (D % 4 == 0 && K > 8 && 5 * ceil_div(K, 8) * 8 >= 7 * (int64_t)K)) return true;
         const DirectPlan p = cut_direct(dtype, N, D, K);
-        const int64_t centroids = ceil_div(K, p.kg << p.tc_log2) * (p.kg << p.tc_log2), features = ceil_div(D / 4, p.lanes) * p.lanes * 4;
-        return K > 16 && N >= 8000 && (double)N * D * K >= 2.2e7 && 10 * centroids * features >= 17 * (int64_t)K * D;
+        const int round = p.kg << p.tc_log2;  // centroids of one
+        if (K <= 16 || K <= round) return false;
+        const double centroids = (double)ceil_div(K, round) * round / K, features = (double)ceil_div(D / 4, p.lanes) * p.lanes * 4 / D;
+        return features >= 1 && (centroids >= 1.42 || centroids * features >= 1.58);
     }
     const double work = (double)N * D * K;
     if (D > 24) return D <= 32 && (D % 4 == 0 || D >= 30) && work >= 2.5e7;
