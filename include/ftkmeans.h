@@ -143,8 +143,9 @@ ftk_status ftk_plan_padded_rows(ftk_dtype dtype, int64_t N, int32_t D, int32_t K
  *                               for all points in double where a problem is large enough for fp16
  *                               operands, whichever of the two forms runs), every point of the
  *                               one-launch kernels that small unprotected calls take (in double,
- *                               rounded once), and every point of the register-resident fp32 kernels (D <= 32; 32 < D <= 128 where
- *                               that kernel is dispatched), get the direct-difference value
+ *                               rounded once), and every point of the register-resident fp32
+ *                               kernels (D <= 32; 32 < D <= 128 where that kernel is
+ *                               dispatched), get the direct-difference value
  *                               (relative error of a few units in the last place of the
  *                               distance).  Otherwise the value comes from the expanded form of
  *                               Section 3.1.2, whose cancellation leaves an ABSOLUTE error of up

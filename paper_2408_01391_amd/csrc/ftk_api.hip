@@ -150,10 +150,11 @@ static bool route_small(ftk_dtype dtype, int64_t N, int D, int K, ftk_ft_mode ft
     return ft == FTK_FT_OFF && n_faults == 0 && g_tuning.assign_variant == -1 && small_assign_pays(dtype, N, D, K);
 }
 
-// Of what the scan takes, fp32 problems go on up to 8 * 10^7 multiplications, 10^8 with up to 100 centroids (scan / direct kernel, 397
-// random shapes: 1.4 .. 3.9 below, 0.6 .. 1.0 above; 1286 x 73, K = 110 22.7 / 9.1 us, 1500 x 20, K = 700 22.4 / 12, 1316 x 432,
-// K = 135 35 / 25).  Of fp64 ones only those that are small by the other kernel's measure go on (6267 x 22, K = 169 27 / 13): the scan
-// compares distances of data at any scale, where squares leave the range.
+// Of what the scan takes, fp32 problems go on up to 8 * 10^7 multiplications, 10^8 with up to 100 centroids (scan /
+// direct kernel, 397 random shapes: 1.4 .. 3.9 below, 0.6 .. 1.0 above; 1286 x 73, K = 110 22.7 / 9.1 us, 1500 x 20,
+// K = 700 22.4 / 12, 1316 x 432, K = 135 35 / 25).  Of fp64 ones only those that are small by the other kernel's
+// measure go on (6267 x 22, K = 169 27 / 13): the scan compares distances of data at any scale, where squares leave
+// the range.
 static bool direct_rule(ftk_dtype dtype, int64_t N, int D, int K)
 {
     const double work = (double)N * D * K;
@@ -270,8 +271,8 @@ Workspace carve_workspace(void *base, size_t bytes, ftk_dtype dtype, int64_t N, 
     const int64_t bucket_cells = update_bucket_cells(dtype, N, D, K, &bucket_counts);
     w.bucket_slab = (int64_t *)take((size_t)bucket_cells * sizeof(int64_t));
     w.bucket_cslab = (int32_t *)take((size_t)bucket_counts * sizeof(int32_t));
-    // one line for all of them, at what the scan without its fp16 pieces needs: below it a call runs as in a workspace of a
-    // protected mode's size, whatever is left over
+    // one line for all of them, at what the scan without its fp16 pieces needs: below it a call runs as in a
+    // workspace of a protected mode's size, whatever is left over
     size_t least = off;
     for (size_t n : {scan_bytes(dtype, N, D, K, false), small_fit_bytes(D, K)})
         if (least < shared + n) least = shared + n;
@@ -903,8 +904,9 @@ static ftk_status fit_impl(ftk_dtype dtype, const void *X, int64_t N, int32_t D,
     auto apart = [](const void *a, size_t na, const void *b, size_t nb) {
         return (uintptr_t)a + na <= (uintptr_t)b || (uintptr_t)b + nb <= (uintptr_t)a;
     };
-    // The centroids live where they are asked for, if whole pieces may be read from there and nothing else is: outputs may
-    // lie over inputs, which the copies of the other way have read before the first iteration or leave until after the last.
+    // The centroids live where they are asked for, if whole pieces may be read from there and nothing else is:
+    // outputs may lie over inputs, which the copies of the other way have read before the first iteration or leave
+    // until after the last.
     const bool in_place = (uintptr_t)C_out % 16 == 0 && apart(C_out, c_bytes, X, (size_t)N * D * esz) &&
                           apart(C_out, c_bytes, labels_out, l_bytes) && apart(C_out, c_bytes, counts_out, n_bytes) &&
                           (C_init == C_out || !C_init || apart(C_init, c_bytes, C_out, c_bytes));

@@ -49,8 +49,8 @@ struct GenericArgs {
 
 constexpr int GENERIC_MAX_FAULTS = 4;
 
-// Short rows of doubles by elements: two of them a piece save little, and pieces at odd places take longer (1600000 x 9, K = 30 90
-// us by elements, 99 by pieces, 21 features 122 / 126; 400000 x 25, K = 100 58 / 59).
+// Short rows of doubles by elements: two of them a piece save little, and pieces at odd places take longer
+// (1600000 x 9, K = 30 90 us by elements, 99 by pieces, 21 features 122 / 126; 400000 x 25, K = 100 58 / 59).
 template <typename T>
 static int matrix_row_access(const AssignCall &c)
 {
@@ -113,8 +113,8 @@ constexpr int generic_kt(int K) { return K <= Mma<T>::TM ? 1 : (K <= 2 * Mma<T>:
 //
 // LINES: the rows pass through LDS (plan_generic() tells when).
 //
-// fp64, two tiles, no checksums: asked for a fourth wave, since a few registers more cost it (900000 x 48, K = 32 106 us with
-// three, 92 with four; 400000 x 128, K = 32 99 / 92).
+// fp64, two tiles, no checksums: asked for a fourth wave, since a few registers more cost it (900000 x 48, K = 32 106
+// us with three, 92 with four; 400000 x 128, K = 32 99 / 92).
 template <typename T, int KTV, int AL, bool FT, bool FULL, bool LINES = false>
 __global__ __launch_bounds__(256, (sizeof(T) == 8 && KTV == 2 && !FT ? 4 : GenericCfg<T, KTV>::WAVES_PER_SIMD))
 void assign_generic_kernel(GenericArgs<T> a)
@@ -248,10 +248,10 @@ void assign_generic_kernel(GenericArgs<T> a)
         if (FT && tid >= 64 && tid < 64 + PPR && (q0 * 8 + (tid - 64) * E) < a.D8)
             pfx = *reinterpret_cast<const frag_t *>(a.chk_v1 + (size_t)kc * a.D8 + q0 * 8 + (tid - 64) * E);
     };
-    // They go first: where the allocator gave their address a register of a row in flight, they waited for all rows (fp64
-    // 10000 x 1024, K = 300, strict 328 us behind the rows, 300 ahead of them; 30000 x 300, K = 100 98 / 92).  Not
-    // with one tile or rows through LDS, which have few rows in flight: 120000 x 128, K = 12 37.5 / 39.2, fp32 280000 x 128,
-    // K = 32, strict 50.0 / 51.8.
+    // They go first: where the allocator gave their address a register of a row in flight, they waited for all rows
+    // (fp64 10000 x 1024, K = 300, strict 328 us behind the rows, 300 ahead of them; 30000 x 300, K = 100
+    // 98 / 92).  Not with one tile or rows through LDS, which have few rows in flight: 120000 x 128, K = 12
+    // 37.5 / 39.2, fp32 280000 x 128, K = 32, strict 50.0 / 51.8.
     auto fetch = [&](int kc, int dc) {
         if constexpr (KTV > 1 && !LINES) fetch_extra(kc, dc);
         const int q0 = dc * DQ;
@@ -301,9 +301,10 @@ void assign_generic_kernel(GenericArgs<T> a)
     // Features beyond D hold copies of valid ones: the staged centroid rows are zero there, so they
     // add nothing to the scores; the norm masks them explicitly.
     frag_t xs[PT][LINES ? 1 : DQ];
-    // LINES: eight lanes take the 128 bytes of a stage of one row, eight rows at a time; the wave's share of LDS hands them to
-    // the lanes that multiply them.  Slot of a piece: its number, turned by the row's, so that neither side meets a bank twice.
-    // The best tile's slots take the same place: they are written once the last stage has been read.
+    // LINES: eight lanes take the 128 bytes of a stage of one row, eight rows at a time; the wave's share of LDS
+    // hands them to the lanes that multiply them.  Slot of a piece: its number, turned by the row's, so that neither
+    // side meets a bank twice. The best tile's slots take the same place: they are written once the last stage has
+    // been read.
     constexpr int XR = LINES ? PT * TN / 8 : 1;
     const int q8 = lane & 7, r8 = lane >> 3;
     unsigned char *const lds_x = lds_best + wave * (PT * TN * 128);
@@ -1153,9 +1154,10 @@ ftk_status launch_refine(const AssignCall &c, const Workspace &w, int n_wg, hipS
     return FTK_OK;
 }
 
-// Rows through LDS, line by line, where one chunk holds all centroids and the rows are what a call waits for: each lane of
-// the other loop reads a row of its own, 64 places a request.  32 instead of 64 points a wave: twice the workgroups, which
-// a pass over long rows has too few of (20000 x 900: 79 for 256 units).  Whole calls, us, its own rows / lines:
+// Rows through LDS, line by line, where one chunk holds all centroids and the rows are what a call waits for: each
+// lane of the other loop reads a row of its own, 64 places a request.  32 instead of 64 points a wave: twice the
+// workgroups, which a pass over long rows has too few of (20000 x 900: 79 for 256 units).  Whole calls, us, its own
+// rows / lines:
 //   without checksums  2^20 x 128, K = 32 154 / 143; 2^20 x 100, K = 5 149 / 130; 200000 x 1000, K = 12 374 / 270;
 //                      20000 x 900, K = 10 114 / 77; below 64 features 2^20 x 48, K = 28 63 / 66, 2^20 x 17, K = 10 46 / 50
 //   with               2^20 x 128, K = 32 182 / 161; 300000 x 24, K = 10 30 / 26; 5000 x 700, K = 64 126 / 90; 200000 x 1000,
@@ -1165,13 +1167,15 @@ static bool lines_pay(int64_t N, int D, int K, int KT, bool ft)
 {
     if (D < (ft ? 24 : 64) || D >= (1 << 22)) return false;
     // The other loop, with stages half as long, runs without conditions where this one has half a stage left over:
-    // 400000 x 240, K = 64 144 / 153, with checksums 161 / 181, 100000 x 112 32 / 33, 39 / 42; few points and the checksums
-    // of one tile still do better here: 60000 x 240, K = 64 44 / 42, 100000 x 112, K = 32, with checksums 31 / 29.
+    // 400000 x 240, K = 64 144 / 153, with checksums 161 / 181, 100000 x 112 32 / 33, 39 / 42; few points and the
+    // checksums of one tile still do better here: 60000 x 240, K = 64 44 / 42, 100000 x 112, K = 32, with checksums
+    // 31 / 29.
     if (D % 32 == 16 && K == 32 * KT && N > 65536 && (KT == 2 || (!ft && D < 160))) return false;
-    // As many points a unit of the chip either way, the larger workgroups side by side, the smaller ones with a second
-    // round of few: 190000 x 256, K = 64 77 / 86, 180000 x 112, K = 12 33 / 35, with checksums 120000 x 300, K = 40 88 / 100;
-    // but 135000 x 256, K = 64 (five a unit instead of two times three) 74 / 66, 200000 93 / 87, and whole stages of one
-    // tile, or rows soon done with under two, 180000 x 256, K = 32 59 / 54, with checksums 110000 x 64, K = 64 30.2 / 28.5.
+    // As many points a unit of the chip either way, the larger workgroups side by side, the smaller ones with a
+    // second round of few: 190000 x 256, K = 64 77 / 86, 180000 x 112, K = 12 33 / 35, with checksums 120000 x 300,
+    // K = 40 88 / 100; but 135000 x 256, K = 64 (five a unit instead of two times three) 74 / 66, 200000 93 / 87, and
+    // whole stages of one tile, or rows soon done with under two, 180000 x 256, K = 32 59 / 54, with checksums
+    // 110000 x 64, K = 64 30.2 / 28.5.
     if (KT == 2 ? D <= 64 : (ft || (D % 32 == 0 && D >= 128))) return true;
     const int64_t many = ceil_div(ceil_div(N, 128), 256), few = ceil_div(ceil_div(N, 256), 256);
     const int at_once = KT == 1 ? 5 : (ft ? 3 : 4), rest = (int)(many % at_once);  // of 128 points

@@ -1,10 +1,11 @@
 // Unprotected assignment in one launch: every distance in direct-difference form (Section 3.1.1), in double.
 //
-// The matrix kernels need norms ahead and a settlement behind, and cut the points into blocks of 128 or 256: three launches,
-// and too few workgroups where points are few (14665 x 520, K = 2: 115 of them, 33 us a call; 1278 x 639, K = 43: ten).
-// With few centroids they stay below the memory's rate too (426483 x 126, K = 2: 62 us, X read at 3.5 TB/s).  Here
-// fp64 arithmetic runs on the vector units at the fp32 rate, two instructions a multiplication, and nothing has to be
-// prepared, certified or settled: what a call below some 10^8 .. 10^9 multiplications spends on launches is more.
+// The matrix kernels need norms ahead and a settlement behind, and cut the points into blocks of 128 or 256: three
+// launches, and too few workgroups where points are few (14665 x 520, K = 2: 115 of them, 33 us a call; 1278 x 639,
+// K = 43: ten). With few centroids they stay below the memory's rate too (426483 x 126, K = 2: 62 us, X read at 3.5
+// TB/s).  Here fp64 arithmetic runs on the vector units at the fp32 rate, two instructions a multiplication, and
+// nothing has to be prepared, certified or settled: what a call below some 10^8 .. 10^9 multiplications spends on
+// launches is more.
 //
 // L lanes share the features of a row (row-contiguous 16-byte pieces), each of them for R points against KG centroids at
 // a time: R + KG loads for 4 R KG differences, so that the vector units and not the caches set the pace.  TC such groups
@@ -148,16 +149,19 @@ __global__ __launch_bounds__(DR_THREADS) void direct_kernel(const T *X, const T 
 
 // ---- host ----------------------------------------------------------------------------------------
 // Lanes that share a row: enough that they read whole lines of it, few enough that each has several pieces (what the
-// lanes of a row have is added up once per centroid).  Groups of lanes on other centroids of the same points: until 65536 threads
-// are busy (and while four of them take all centroids of long rows: one read of X); where that does not do, more lanes per
-// row.  Of 41 shapes timed with every choice (10^3 .. 10^6 points, 4 .. 1000 features, 2 .. 700 centroids, both types) this one is
-// near the best: 1286 x 73, K = 110 9.1 / 9.1 us, 1278 x 639, K = 43 15.7 / 14.1, 14665 x 520, K = 2 8.9 / 7.2.
-// Up to four centroids the rows are all that a call waits for: twice the lanes ask for twice as much of a row at once (such lanes
-// / twice as many: 480049 x 60, K = 2 34 / 25, 46418 x 316, K = 3 18.5 / 14.5, fp64 1585025 x 70, K = 2 250 / 187, 1592522 x 32, K = 1 114 /
-// 80, fp32 1800000 x 14, K = 1 57 / 25, fp64 x 15, K = 3 170 / 81; four or eight lanes: 700000 x 52, K = 1 41 / 30, 44 31 / 28, 36 24 / 25, fp64 700000 x 34, K = 1 47 / 33, 1200000 x 48, K = 4 98 / 113),
-// but for fp32 data that the memory-side cache holds anyway (121474 x 108, K = 2 12.2 / 13.4, 54590 x 256 11.2 / 13.3).  So do few
-// doubles, whose rows are as long as those of twice as many floats (50000 x 29, K = 8 11.3 / 9.5, 4000 x 56, K = 50 11.5 / 9.3), until
-// the vector units set the pace (20000 x 17, K = 40 10.0 / 11.5, 20000 x 25, K = 60 12.0 / 15.2).
+// lanes of a row have is added up once per centroid).  Groups of lanes on other centroids of the same points: until
+// 65536 threads are busy (and while four of them take all centroids of long rows: one read of X); where that does not
+// do, more lanes per row.  Of 41 shapes timed with every choice (10^3 .. 10^6 points, 4 .. 1000 features, 2 .. 700
+// centroids, both types) this one is near the best: 1286 x 73, K = 110 9.1 / 9.1 us, 1278 x 639, K = 43 15.7 / 14.1,
+// 14665 x 520, K = 2 8.9 / 7.2.
+// Up to four centroids the rows are all that a call waits for: twice the lanes ask for twice as much of a row at once
+// (such lanes / twice as many: 480049 x 60, K = 2 34 / 25, 46418 x 316, K = 3 18.5 / 14.5, fp64 1585025 x 70, K = 2
+// 250 / 187, 1592522 x 32, K = 1 114 / 80, fp32 1800000 x 14, K = 1 57 / 25, fp64 x 15, K = 3 170 / 81; four or eight
+// lanes: 700000 x 52, K = 1 41 / 30, 44 31 / 28, 36 24 / 25, fp64 700000 x 34, K = 1 47 / 33, 1200000 x 48, K = 4
+// 98 / 113), but for fp32 data that the memory-side cache holds anyway (121474 x 108, K = 2 12.2 / 13.4, 54590 x 256
+// 11.2 / 13.3).  So do few doubles, whose rows are as long as those of twice as many floats (50000 x 29, K = 8
+// 11.3 / 9.5, 4000 x 56, K = 50 11.5 / 9.3), until the vector units set the pace (20000 x 17, K = 40 10.0 / 11.5,
+// 20000 x 25, K = 60 12.0 / 15.2).
 DirectPlan cut_direct(ftk_dtype dtype, int64_t N, int D, int K)
 {
     DirectPlan p = {};
@@ -175,22 +179,24 @@ DirectPlan cut_direct(ftk_dtype dtype, int64_t N, int D, int K)
     return p;
 }
 
-// Where one launch of double arithmetic beats the matrix kernels behind their norms and ahead of their refine kernel: 1400
-// random shapes of 500 .. 2 * 10^6 points, 2 .. 1024 features, 2 .. 1000 centroids and up to 10^9 multiplications timed with both, and
-// 900 again with the matrix kernels' rows by lines (matrix / this, whole calls, geometric means of the second lot): fp32 up to 7 * 10^7
-// multiplications 2.0, with up to 4 centroids 1.4 at any size, fp64 1.9 and 1.2; centroids that fill up the last group count like
-// others.  Near the lines, us:
+// Where one launch of double arithmetic beats the matrix kernels behind their norms and ahead of their refine kernel:
+// 1400 random shapes of 500 .. 2 * 10^6 points, 2 .. 1024 features, 2 .. 1000 centroids and up to 10^9
+// multiplications timed with both, and 900 again with the matrix kernels' rows by lines (matrix / this, whole calls,
+// geometric means of the second lot): fp32 up to 7 * 10^7 multiplications 2.0, with up to 4 centroids 1.4 at any
+// size, fp64 1.9 and 1.2; centroids that fill up the last group count like others.  Near the lines, us:
 //   fp32  16438 x 672, K = 13 45 / 47; 159477 x 576, K = 3 80 / 75; 35681 x 216, K = 12 31 / 30; 50387 x 128, K = 16 18 / 17; 132339 x 41,
 //         K = 9 18 / 25; 33607 x 7, K = 278 20 / 27; 146809 x 124, K = 8 32 / 34; 478244 x 51, K = 5 49 / 41; 641930 x 2, K = 110 53 / 38
 //   fp64  393442 x 86, K = 2 70 / 58; 54801 x 136, K = 8 20.6 / 21.3; 333471 x 36, K = 5 33 / 36; 95490 x 56, K = 9 17.6 / 27.6; 2627 x 635,
 //         K = 84 69 / 50; 300000 x 100, K = 20 67 / 162
-// Rows of up to 64 features fill a few rounds of their lanes, and few groups of centroids a few rounds: where there are many points
-// the line lies by what the rounds hold (47873 x 52, K = 22 17.0 / 18.8, 74775 x 36, K = 21 15.3 / 22.3, 58280 x 51, K = 15 15.3 / 10.0;
-// 34278 x 20, K = 91 16.4 / 21.2, 69142 x 12, K = 79 17.1 / 22.9, 51448 x 31, K = 37 14.7 / 20.9, 26719 x 16, K = 127 15.7 / 13.0; fp64
-// 33958 x 58, K = 20 16.8 / 21.9, 16727 x 58, K = 48 16.1 / 22.1, 10630 x 54, K = 77 18.8 / 22.8, 66468 x 38, K = 10 14.4 / 18.3, 50704 x 59, K = 10 15.5 / 14.0).
-// Two lanes to rows of almost their eight quads ask for too little at once where there are many (10^6 x 32, K = 8 47 / 60); rows
-// of two or three features have nothing to share out among many centroids' groups (333333 x 2, K = 150 46 / 35, 166666 x 2,
-// K = 600 55 / 70; fp64 277777 x 3, K = 300 66 / 90).
+// Rows of up to 64 features fill a few rounds of their lanes, and few groups of centroids a few rounds: where there
+// are many points the line lies by what the rounds hold (47873 x 52, K = 22 17.0 / 18.8, 74775 x 36, K = 21
+// 15.3 / 22.3, 58280 x 51, K = 15 15.3 / 10.0; 34278 x 20, K = 91 16.4 / 21.2, 69142 x 12, K = 79 17.1 / 22.9,
+// 51448 x 31, K = 37 14.7 / 20.9, 26719 x 16, K = 127 15.7 / 13.0; fp64 33958 x 58, K = 20 16.8 / 21.9, 16727 x 58,
+// K = 48 16.1 / 22.1, 10630 x 54, K = 77 18.8 / 22.8, 66468 x 38, K = 10 14.4 / 18.3, 50704 x 59, K = 10
+// 15.5 / 14.0).
+// Two lanes to rows of almost their eight quads ask for too little at once where there are many
+// (10^6 x 32, K = 8 47 / 60); rows of two or three features have nothing to share out among many centroids' groups
+// (333333 x 2, K = 150 46 / 35, 166666 x 2, K = 600 55 / 70; fp64 277777 x 3, K = 300 66 / 90).
 bool direct_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     const double work = (double)N * D * K;

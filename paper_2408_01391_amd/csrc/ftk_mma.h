@@ -78,10 +78,10 @@ struct Mma<double> {
     static __device__ __forceinline__ double huge() { return __builtin_huge_val(); }
 };
 
-// How rows are read: 16-byte pieces where rows and base are aligned to them; pieces at element alignment (global memory
-// takes those at the same rate), the last one of a row moved back into the row; element by element where a row is
-// shorter than a piece.  Pieces against elements, whole calls: 155948 x 209, K = 21, strict 70 / 167 us; 102957 x 102, K = 7
-// 26 / 53; 426483 x 126, K = 2 81 / 98.
+// How rows are read: 16-byte pieces where rows and base are aligned to them; pieces at element alignment (global
+// memory takes those at the same rate), the last one of a row moved back into the row; element by element where a row
+// is shorter than a piece.  Pieces against elements, whole calls: 155948 x 209, K = 21, strict 70 / 167 us;
+// 102957 x 102, K = 7 26 / 53; 426483 x 126, K = 2 81 / 98 (62 by lines, see ftk_assign_generic.hip).
 enum RowAccess : int { ROWS_ELEMENTS = 0, ROWS_ALIGNED = 1, ROWS_PIECES = 2 };
 template <typename T>
 __device__ __forceinline__ typename Mma<T>::frag_t load_piece(const T *p)

@@ -82,12 +82,14 @@ constexpr int settle_rows(size_t element) { return element == 8 ? 2 : 4; }  // r
 constexpr int SCAN_LISTS = 64;    // lists of points to resolve, a counter in a line of its own each
 constexpr int LIST_STRIDE = 32;
 constexpr float HALF_RANGE = 6e4f;  // of a norm: no feature leaves the range of fp16
-// The rows that decide between the forms come in shares of 32 that a workgroup compares with a tile of centroids: fewer for many centroids, where this adds up (150 000 x
-// 128, K = 2085 5 us with four shares, 33000 x 256, K = 8192 28).
+// The rows that decide between the forms come in shares of 32 that a workgroup compares with a tile of centroids:
+// fewer for many centroids, where this adds up (150 000 x 128, K = 2085 5 us with four shares, 33000 x 256, K = 8192
+// 28).
 static int sample_shares(int tiles) { return tiles <= 64 ? 4 : (tiles <= 128 ? 2 : 1); }
-// Of them listed, from which on two pieces are taken: 14, 19, 22 percent.  They are faster from 10 percent (524288 x 96, K = 800: 11.5
-// percent 289 us, refused 272), 13 (400000 x 32, K = 2000: 10.5 percent 182, 15 percent 234, refused 212), 16 (130003 x 256, K = 1024: 15
-// percent 262, refused 297) or more than 20 (2^21 x 32, K = 4096: 21 percent 1331, refused 1595) on.
+// Of them listed, from which on two pieces are taken: 14, 19, 22 percent.  They are faster from 10 percent
+// (524288 x 96, K = 800: 11.5 percent 289 us, refused 272), 13 (400000 x 32, K = 2000: 10.5 percent 182, 15 percent
+// 234, refused 212), 16 (130003 x 256, K = 1024: 15 percent 262, refused 297) or more than 20 (2^21 x 32, K = 4096:
+// 21 percent 1331, refused 1595) on.
 static int sample_limit(int shares) { return shares == 4 ? 18 : (shares == 2 ? 12 : 7); }
 constexpr float SCAN_FLOOR = 7.9e-31f;  // 2^-100: below it scores (of centroids near 1) may have lost digits to underflow
 
@@ -635,8 +637,9 @@ struct SettleArgs {
 enum SettleKind : int {
     SETTLE_PLAIN = 0,   // distances in the data's type
     SETTLE_DOUBLE = 1,  // in double, added up in the order of group_sqdist(): whatever passes a point goes through, and so
-                        // whichever form scanned it (batches of a step take the one that is faster for their size), its
-                        // distance has the same bits; fp32 2^21 x 32, K = 4096 859 / 860 us a call, 60000 x 1024 343 / 344
+                        // whichever form scanned it (batches of a step take the one that is faster for their size),
+                        // its distance has the same bits; fp32 2^21 x 32, K = 4096 859 / 860 us a call, 60000 x 1024
+                        // 343 / 344
     SETTLE_HALF = 2     // the same, and the records may come from fp16 pieces
 };
 // lanes of a row
@@ -656,8 +659,8 @@ struct SettleShared {
     T dist[N];
 };
 
-// Block `block` of N rows.  own: their records where the workgroup that scanned the points settles them itself, else NULL;
-// half: the records come from fp16 pieces; again: a block after another one.
+// Block `block` of N rows.  own: their records where the workgroup that scanned the points settles them itself, else
+// NULL; half: the records come from fp16 pieces; again: a block after another one.
 template <typename T, int L, int ROWS, int KIND>
 __device__ __forceinline__ void settle_block(const T *X, const T *C, T *mindist, const SettleArgs &a, const int64_t block,
                                              const ScanRecord *own, const bool half, const bool again,
@@ -711,8 +714,8 @@ __device__ __forceinline__ void settle_block(const T *X, const T *C, T *mindist,
 #pragma unroll
     for (int q = 0; q < Q; ++q) cm[q] = fmaxf(fmaxf(sh.max[0][q], sh.max[1][q]), fmaxf(sh.max[2][q], sh.max[3][q]));
     const float cmax = 1.000001f * sqrtf(cm[0]) + tiny;
-    // a score of centroid c is off by at most A ||c|| + psi ||c||^2 / 2, A = lost ||x|| + psi (||x|| + ||r||); ||x1|| <= 2^-8 ||x||
-    // (fp16 pieces: lost ||x|| is ||r_x|| + max(||r_c|| / ||c||) ||x||, the first measured below)
+    // a score of centroid c is off by at most A ||c|| + psi ||c||^2 / 2, A = lost ||x|| + psi (||x|| + ||r||); ||x1||
+    // <= 2^-8 ||x|| (fp16 pieces: lost ||x|| is ||r_x|| + max(||r_c|| / ||c||) ||x||, the first measured below)
     const float lost = half ? 1.001f * a.slack * sqrtf(cm[Q - 1])
                             : a.lost + 1.001f * a.slack * (0x1p-8f * sqrtf(cm[1]) + sqrtf(cm[2]));
     const T s = (T)a.scale[0];
@@ -806,10 +809,10 @@ __device__ __forceinline__ void settle_block(const T *X, const T *C, T *mindist,
         const float high = 1.00001f * (A + (lift + 0.5f * psi) * c1) * c1;
         float least = q.m1 - high;
         if constexpr (HALF) {
-            // Its true score is also known from the distance, (||x - r||^2 - ||x - c||^2) / 2, to within the rounding of
-            // these sums: of fp16 pieces that halves the bound (2^21 x 32, K = 4096: 68 000 points listed against 105 000).
-            // The distance comes from differences that carry no scale: `under` is what underflow may have taken from it,
-            // infinite (a distance out of range: d2) where these sums say nothing.
+            // Its true score is also known from the distance, (||x - r||^2 - ||x - c||^2) / 2, to within the rounding
+            // of these sums: of fp16 pieces that halves the bound (2^21 x 32, K = 4096: 68 000 points listed against
+            // 105 000). The distance comes from differences that carry no scale: `under` is what underflow may have
+            // taken from it, infinite (a distance out of range: d2) where these sums say nothing.
             const float d2 = (float)(dist * s * s);
             least = fmaxf(least, 0.5f * (q.y2 - d2) - a.sums * (q.y2 + d2) - under);
         }
@@ -862,8 +865,8 @@ __global__ __launch_bounds__(256, 4) void scan_settle_kernel(const T *X, const T
 }
 
 // The points of a scan's workgroup, settled by it where no other one shares them: their records stay in LDS, and its
-// requests travel while other workgroups multiply; a pass of its own waits for them with nothing else to do, after a launch
-// and a read of what the scan has just written.  Passes apart / as one, whole calls, us:
+// requests travel while other workgroups multiply; a pass of its own waits for them with nothing else to do, after a
+// launch and a read of what the scan has just written.  Passes apart / as one, whole calls, us:
 //   2 lanes a row  2^20 x 8, K = 1024 136.9 / 130.1; 10^6 x 12, K = 700 150 / 140; fp64 2^20 x 6, K = 300 80 / 72
 //   4              1.5 * 10^6 x 16, K = 300 116 / 106; 700000 x 24, K = 1000 120 / 109; fp64 500000 x 20, K = 1000 121 / 115
 //   8              2^21 x 32, K = 4096 762 / 733; 971508 x 27, K = 781 153 / 153.  Two pieces alone, where half_pays() is not
@@ -875,8 +878,9 @@ struct SettleOwn {
     SettleArgs s;
 };
 constexpr int OWN_D = 32;  // features of a row, at most
-// Rows a group of lanes settles at once, within the registers of the scan: eight lanes, four rows of fp32 spill 128 bytes of
-// the fp16 form (2^21 x 32, K = 4096 758 us against 750), four lanes do better with them (700000 x 24, K = 1000 112, 118).
+// Rows a group of lanes settles at once, within the registers of the scan: eight lanes, four rows of fp32 spill 128
+// bytes of the fp16 form (2^21 x 32, K = 4096 758 us against 750), four lanes do better with them (700000 x 24,
+// K = 1000 112, 118).
 constexpr int own_rows(size_t element, int lanes) { return element == 4 && lanes == 4 ? 4 : 2; }
 template <typename T, int L>
 struct OwnShared {
@@ -900,7 +904,8 @@ __device__ __forceinline__ void settle_own(const void *X, const SettleOwn &o, in
 // passes through LDS in chunks of 16 or 32 KB, the next chunk copied (global memory to LDS, no
 // registers) while the current one is multiplied.  Fragments are stored lane by lane, so the copy is
 // linear and the reads are free of bank conflicts.  Rows of up to 32 features are settled here too (SettleOwn); longer
-// ones are not: at 128 features 228 registers, two workgroups of four waves per compute unit that wait at their own barriers.
+// ones are not: at 128 features 228 registers, two workgroups of four waves per compute unit that wait at their own
+// barriers.
 // waves of a SIMD whose registers suffice
 constexpr int resident_waves(int nb, int form, bool wide, bool ragged)
 {
@@ -1073,8 +1078,8 @@ __global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8
             constexpr int L = decltype(lanes)::value;
             settle_own<T, L, KIND>(a.X, own, pb, FORM == FORM_HALF, *reinterpret_cast<OwnShared<T, L> *>(lds4));
         };
-        // an octet's rows go to two lanes, a triple's to two or four, those of two blocks to four or, of calls that choose
-        // their form, eight: settles_own()
+        // an octet's rows go to two lanes, a triple's to two or four, those of two blocks to four or, of calls that
+        // choose their form, eight: settles_own()
         if constexpr (FORM == FORM_OCTET) {
             settle(std::integral_constant<int, 2>{});
         } else if constexpr (FORM == FORM_TRIPLE) {
@@ -1088,10 +1093,10 @@ __global__ __launch_bounds__(SC_THREADS, resident_waves(NB, FORM, sizeof(T) == 8
 }
 
 // ---- scan of longer rows --------------------------------------------------------------------------
-// A workgroup multiplies 256 points by 64 * CT centroids, 32 features at a time through LDS (double
-// buffered, up to 128 KB): the centroid fragments are copied from the image, the rows of X are split
-// on the way - requested two stages ahead, split and stored one stage ahead.  Wave w takes point tiles 2(w%4) .. +1 and the centroid tiles of half w/4.  The
-// workgroups that share a block of points run side by side on one XCD, so that X comes from memory
+// A workgroup multiplies 256 points by 64 * CT centroids, 32 features at a time through LDS (double buffered, up to
+// 128 KB): the centroid fragments are copied from the image, the rows of X are split on the way - requested two
+// stages ahead, split and stored one stage ahead.  Wave w takes point tiles 2(w%4) .. +1 and the centroid tiles of
+// half w/4.  The workgroups that share a block of points run side by side on one XCD, so that X comes from memory
 // once whatever K.
 template <typename T, int CT, bool RAG, bool GATED>
 __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
@@ -1112,9 +1117,10 @@ __global__ __launch_bounds__(SS_THREADS, 2) void scan_stream_kernel(ScanArgs a)
     const int nb = 2 * ns;  // blocks per tile of the image
     const int wp = wave & 3, wc = wave >> 2;
 
-    // The features this thread brings in: four of each of four rows; eight lanes take a row's 32, whole lines of memory.  (16
-    // features of one row a lane, 64 places a request, whole calls: 500000 x 130, K = 64 149 us against 130, 131072 x 512, K = 100
-    // 139 / 131, 100000 x 301, K = 300 153 / 144, 9000 x 640, K = 1000 116 / 107; fp64 40000 x 900, K = 310 339 / 257.)
+    // The features this thread brings in: four of each of four rows; eight lanes take a row's 32, whole lines of
+    // memory.  (16 features of one row a lane, 64 places a request, whole calls: 500000 x 130, K = 64 149 us against
+    // 130, 131072 x 512, K = 100 139 / 131, 100000 x 301, K = 300 153 / 144, 9000 x 640, K = 1000 116 / 107; fp64
+    // 40000 x 900, K = 310 339 / 257.)
     const int q8 = lane & 7, r8 = lane >> 3;
     const T *X = reinterpret_cast<const T *>(a.X);
     auto reader = [&](int i) {
@@ -1281,9 +1287,10 @@ __global__ __launch_bounds__(SP_THREADS, 2) void scan_points_kernel(ScanArgs a, 
     const T *X = reinterpret_cast<const T *>(a.X);
     const T s = (T)a.scale[0];
     {
-        // Wave w rounds point tile w % PT, every (8 / PT)th group of BATCH blocks.  Eight lanes take 32 features of a row, whole
-        // lines of memory, and eight rows at a time: with a lane to a row a request names 64 places, one after the other (whole
-        // calls 60000 x 1024, K = 1024 325 / 320 us, 131072 x 512, K = 1000 287 / 279, 150000 x 200, K = 700 154 / 154).
+        // Wave w rounds point tile w % PT, every (8 / PT)th group of BATCH blocks.  Eight lanes take 32 features of a
+        // row, whole lines of memory, and eight rows at a time: with a lane to a row a request names 64 places, one
+        // after the other (whole calls 60000 x 1024, K = 1024 325 / 320 us, 131072 x 512, K = 1000 287 / 279,
+        // 150000 x 200, K = 700 154 / 154).
         constexpr int BATCH = sizeof(T) == 4 ? 8 : 4;
         const int pt = wave % PT, q8 = lane & 7, r8 = lane >> 3;
         auto reader = [&](int i) { return RowReader<T, RAG>(X + min(p0 + pt * 32 + 8 * i + r8, a.N - 1) * a.D, a.D); };
@@ -2266,8 +2273,8 @@ static int resident_blocks(int D)
 //         D = 4    N = 60000 K = 512 22.8 / 28.4, 1024 33.4 / 32.2; N = 10^6 K = 256 61.1 / 62.2, 512 96.1 / 88.0
 //   fp64  D = 32   N = 20000 K = 192 21.2 / 22.0, 384 33.4 / 23.1; N = 60000 K = 128 22.3 / 23.2, 256 34.5 / 27.3; N = 200000 K = 64 34.0 / 37.6,
 //                  96 47.1 / 38.7
-// Rows beyond 128 features again with the matrix kernels that read them by lines (3000 .. 10^6 points, 132 .. 1600 features, 8 .. 224
-// centroids, some 2300 calls):
+// Rows beyond 128 features again with the matrix kernels that read them by lines (3000 .. 10^6 points, 132 .. 1600
+// features, 8 .. 224 centroids, some 2300 calls):
 //   fp32  N = 20000 D = 256 K = 48 32 / 39, 66 52 / 43; D = 512 K = 48 62 / 58; N = 60000 D = 132 K = 80 36 / 45; D = 320 K = 50 55 / 54, 80
 //         73 / 64; D = 1024 K = 50 155 / 133; N = 200000 D = 256 K = 64 89 / 97, 80 141 / 112; D = 1000 K = 64 392 / 400; N = 500000
 //         D = 256 K = 50 199 / 224, 80 276 / 257
@@ -2292,10 +2299,11 @@ static int scan_from(ftk_dtype dtype, int64_t N, int D)
     for (int w : beyond) d += D > w;
     const int n = N < 9000 ? 0 : (N < 36000 ? 1 : (N < 110000 ? 2 : (N < 450000 ? 3 : 4)));
     int k = from[dtype == FTK_F32 ? 0 : 1][n][d];
-    // fp32 rows that are not whole 16-byte pieces: lines by precision, not by speed.  They were drawn against matrix kernels that
-    // read such rows element by element; by pieces those are the faster ones again for few centroids (200000 x 131, K = 32 44 / 74,
-    // 60000 x 337, K = 20 47 / 59, 350000 x 27, K = 32 25 / 39), level from 80 or so of long rows (200000 x 131, K = 80 90 / 91), 48 of
-    // short ones.  But these calls return distances in direct-difference form, and the matrix kernels' are of the expanded one.
+    // fp32 rows that are not whole 16-byte pieces: lines by precision, not by speed.  They were drawn against matrix
+    // kernels that read such rows element by element; by pieces those are the faster ones again for few centroids
+    // (200000 x 131, K = 32 44 / 74, 60000 x 337, K = 20 47 / 59, 350000 x 27, K = 32 25 / 39), level from 80 or so
+    // of long rows (200000 x 131, K = 80 90 / 91), 48 of short ones.  But these calls return distances in
+    // direct-difference form, and the matrix kernels' are of the expanded one.
     if (dtype == FTK_F32 && D % 4 != 0) {
         if (D >= 96) k = 8;
         else if (n >= 3) k = d == 0 ? 192 : (d == 2 ? 96 : (N >= 300000 ? 32 : 48));

@@ -236,8 +236,8 @@ __global__ __launch_bounds__(SM_THREADS) void small_kernel(SmallArgs a)
     }
 }
 
-// What the first iteration needs of a few points, in one workgroup: the largest |x| (as absmax_kernel finds it), a cleared
-// table.  4096 x 16: 4.6 us against three launches and the gaps between them.
+// What the first iteration needs of a few points, in one workgroup: the largest |x| (as absmax_kernel finds it), a
+// cleared table.  4096 x 16: 4.6 us against three launches and the gaps between them.
 constexpr int SM_PREPARE = 131072;  // elements
 template <typename T>
 __global__ __launch_bounds__(1024) void small_prepare_kernel(const T *X, int count, double *absmax, int32_t *table, int words)
@@ -312,13 +312,15 @@ bool small_assign_fits(ftk_dtype dtype, int64_t N, int D, int K)
 {
     return D <= 64 && (int64_t)K * small_quads(D) * 4 <= SM_CELLS && small_work(dtype, N, D, K);
 }
-// An assignment of longer rows is faster with several lanes a row, see ftk_direct.hip (this kernel / that one): fp32 6521 x
-// 57, K = 95 15.8 / 12.2 us, 58896 x 52, K = 12 12.9 / 10.9, but 32803 x 48, K = 17 11.2 / 14.9, where a third of its last group of
-// centroids is padding, and 9429 x 39, K = 70 14.0 / 17.4, 13186 x 54, K = 67 17.0 / 20.1, 22036 x 48, K = 44 13.8 / 15.9, 17320 x 39,
-// K = 67 19.0 / 22.6, where the last of several rounds of centroids or features is nearly empty (one round 6303 x 62, K = 69
-// 13.5 / 12.1, 15822 x 53, K = 46 13.9 / 12.0; no features left over 42028 x 51, K = 17 19.8 / 16.4); ragged ones with few centroids 600000 x 10, K = 4 13.7 / 9.2, 600000 x 25 49 / 27, but 600000 x 15 14.6 / 15.4;
-// fp64 4278 x 25, K = 91 18.2 / 9.4, 28555 x 19, K = 17 9.4 / 7.9, but 185114 x 23, K = 10 17 / 29, 20000 x 20, K = 100 14.3 / 18.9,
-// 60000 x 28, K = 26 11.7 / 13.6 (ragged 60000 x 25, K = 26 13.5 / 11.8, x 31 13.1 / 13.9).
+// An assignment of longer rows is faster with several lanes a row, see ftk_direct.hip (this kernel / that one): fp32
+// 6521 x 57, K = 95 15.8 / 12.2 us, 58896 x 52, K = 12 12.9 / 10.9, but 32803 x 48, K = 17 11.2 / 14.9, where a third
+// of its last group of centroids is padding, and 9429 x 39, K = 70 14.0 / 17.4, 13186 x 54, K = 67 17.0 / 20.1,
+// 22036 x 48, K = 44 13.8 / 15.9, 17320 x 39, K = 67 19.0 / 22.6, where the last of several rounds of centroids or
+// features is nearly empty (one round 6303 x 62, K = 69 13.5 / 12.1, 15822 x 53, K = 46 13.9 / 12.0; no features left
+// over 42028 x 51, K = 17 19.8 / 16.4); ragged ones with few centroids 600000 x 10, K = 4 13.7 / 9.2, 600000 x 25
+// 49 / 27, but 600000 x 15 14.6 / 15.4; fp64 4278 x 25, K = 91 18.2 / 9.4, 28555 x 19, K = 17 9.4 / 7.9, but
+// 185114 x 23, K = 10 17 / 29, 20000 x 20, K = 100 14.3 / 18.9, 60000 x 28, K = 26 11.7 / 13.6 (ragged 60000 x 25,
+// K = 26 13.5 / 11.8, x 31 13.1 / 13.9).
 bool small_assign_pays(ftk_dtype dtype, int64_t N, int D, int K)
 {
     if (!small_assign_fits(dtype, N, D, K)) return false;
@@ -357,10 +359,11 @@ static int small_lanes_log2(int64_t N, int K, int pt, int *grid)
     return l;
 }
 
-// Rows ahead, us without / with: fp32 20000 x 24, K = 100 13.9 / 13.1, 700000 x 20, K = 3 16.6 / 14.6, fit of 4096 x 16, K = 8, ten
-// iterations 139 / 136; 14 doubles and more that are read one by one, 200000 x 15, K = 9 12.3 / 9.9, 700000 x 22, K = 3 51 / 36.
-// Longer rows and other doubles pay for the registers with a wave: 60000 x 32, K = 26 10.6 / 12.0; fp64 700000 x 9, K = 3 14.7 / 16.0,
-// 700000 x 16, K = 3 19.0 / 21.5, 60000 x 20, K = 26 9.7 / 10.3, fit of 20000 x 32, K = 20, five iterations 159 / 206.
+// Rows ahead, us without / with: fp32 20000 x 24, K = 100 13.9 / 13.1, 700000 x 20, K = 3 16.6 / 14.6, fit of
+// 4096 x 16, K = 8, ten iterations 139 / 136; 14 doubles and more that are read one by one, 200000 x 15, K = 9
+// 12.3 / 9.9, 700000 x 22, K = 3 51 / 36. Longer rows and other doubles pay for the registers with a wave:
+// 60000 x 32, K = 26 10.6 / 12.0; fp64 700000 x 9, K = 3 14.7 / 16.0, 700000 x 16, K = 3 19.0 / 21.5, 60000 x 20,
+// K = 26 9.7 / 10.3, fit of 20000 x 32, K = 20, five iterations 159 / 206.
 template <typename T, bool FIT>
 static void launch_small_t(const SmallArgs &a, int grid, hipStream_t st)
 {

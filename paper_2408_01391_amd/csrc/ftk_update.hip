@@ -104,20 +104,22 @@ static UpdatePlan plan_update(ftk_dtype dtype, int64_t N, int D, int K)
     int l2 = 0;
     while ((1 << l2) < ppr && l2 < 8) ++l2;
     u.tx_log2 = l2;
-    // Pieces of ragged rows that leave a quarter of a pass's lanes idle lose to elements, which fill them and add to a table
-    // without bank conflicts, where few clusters share the adds and the rows come from the memory-side cache (pieces /
-    // elements: 425 x 1063, K = 4 23.9 / 18.4 us, 883 x 631, K = 7 18.4 / 15.7, 77632 x 530, K = 7 strict 86 / 79, 2347 x 1418, K = 11
-    // 22.5 / 20.1; fp64 43353 x 665, K = 3 57 / 50; but 60314 x 490, K = 6 38 / 47, 23191 x 518, K = 16 30 / 38, 13251 x 1803, K = 3
-    // 34 / 37, and beyond that cache 206658 x 742, K = 13 315 / 396, 42297 x 1561, K = 7 112 / 122; fp64 49042 x 771, K = 5 71 / 77).
+    // Pieces of ragged rows that leave a quarter of a pass's lanes idle lose to elements, which fill them and add to
+    // a table without bank conflicts, where few clusters share the adds and the rows come from the memory-side cache
+    // (pieces / elements: 425 x 1063, K = 4 23.9 / 18.4 us, 883 x 631, K = 7 18.4 / 15.7, 77632 x 530, K = 7 strict
+    // 86 / 79, 2347 x 1418, K = 11 22.5 / 20.1; fp64 43353 x 665, K = 3 57 / 50; but 60314 x 490, K = 6 38 / 47,
+    // 23191 x 518, K = 16 30 / 38, 13251 x 1803, K = 3 34 / 37, and beyond that cache 206658 x 742, K = 13 315 / 396,
+    // 42297 x 1561, K = 7 112 / 122; fp64 49042 x 771, K = 5 71 / 77).
     const int width = 256, full = (int)ceil_div(ppr, width) * width;
     if (D % E != 0 && K < 16 && ppr > (dtype == FTK_F32 ? width / 2 : width) && 32 * ppr <= 25 * full &&
         (double)N * D * (16 / E) < 2.4e8)
         u.pieces = false;
-    // a workgroup takes UPD_THREADS >> tx_log2 rows per pass; at least 16 passes (and 64 rows) per
-    // chunk, so that long rows of a mid-sized problem still spread over all CUs; four where a table more is soon written and
-    // read (36311 x 63, K = 5 18.9 us with 16, 13.0 with four; 36000 x 64, K = 5 17.4 / 12.4), and down to four where a launch has
-    // fewer than 64 workgroups otherwise (2123 x 72, K = 82 15.3 / 11.3; 30000 x 50, K = 100 19.4 / 15.5; 12000 x 128, K = 64 19.2 /
-    // 15.8; with redundancy 5000 x 100, K = 60 22.5 / 15.8), 24 if the tables outweigh the rows (50000 x 20, K = 350 14.9 / 15.5)
+    // a workgroup takes UPD_THREADS >> tx_log2 rows per pass; at least 16 passes (and 64 rows) per chunk, so that
+    // long rows of a mid-sized problem still spread over all CUs; four where a table more is soon written and read
+    // (36311 x 63, K = 5 18.9 us with 16, 13.0 with four; 36000 x 64, K = 5 17.4 / 12.4), and down to four where a
+    // launch has fewer than 64 workgroups otherwise (2123 x 72, K = 82 15.3 / 11.3; 30000 x 50, K = 100 19.4 / 15.5;
+    // 12000 x 128, K = 64 19.2 / 15.8; with redundancy 5000 x 100, K = 60 22.5 / 15.8), 24 if the tables outweigh the
+    // rows (50000 x 20, K = 350 14.9 / 15.5)
     int passes = (int64_t)K * D <= 2048 ? 4 : 16;
     const int pass_rows = UPD_THREADS >> l2;
     while (passes > 4 && ceil_div(N, (int64_t)passes * pass_rows) * slices < (passes / 2 * pass_rows >= 2 * K ? 64 : 24)) passes /= 2;
@@ -282,13 +284,13 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
         // UNR rows per thread and step: the label loads, then the point loads, are issued together
         // before any LDS atomic, so several HBM requests per thread are in flight
         constexpr int UNR = 4;
-        // When the slice holds every cluster the point loads do not depend on the labels and go out
-        // together with them (ALLK).  Otherwise only rows whose label falls into the slice are read: over more than four
-        // steps those of one are requested while the rows of the step before are added, their labels one step earlier
-        // still (AHEAD; without / with: 400000 x 100, K = 300 88 / 76 us, 10^6 x 15, K = 1600 61 / 57, fp64 500000 x 16,
-        // K = 900 35 / 32; four steps 500000 x 15, K = 1000 29.3 / 29.2, fp64 300000 x 7, K = 3000 28.1 / 28.6; two or one
-        // 20000 x 32, K = 1000 18.8 / 19.3).  The LDS atomics bound ALLK slices (2^18 x 128, K = 256 42 / 44); rows of up to
-        // three features 38 / 41; under DMR the registers cost the other slices 3 %.
+        // When the slice holds every cluster the point loads do not depend on the labels and go out together with
+        // them (ALLK).  Otherwise only rows whose label falls into the slice are read: over more than four steps
+        // those of one are requested while the rows of the step before are added, their labels one step earlier still
+        // (AHEAD; without / with: 400000 x 100, K = 300 88 / 76 us, 10^6 x 15, K = 1600 61 / 57, fp64 500000 x 16,
+        // K = 900 35 / 32; four steps 500000 x 15, K = 1000 29.3 / 29.2, fp64 300000 x 7, K = 3000 28.1 / 28.6; two
+        // or one 20000 x 32, K = 1000 18.8 / 19.3).  The LDS atomics bound ALLK slices (2^18 x 128, K = 256 42 / 44);
+        // rows of up to three features 38 / 41; under DMR the registers cost the other slices 3 %.
         auto pass = [&](auto allk_tag, auto ahead_tag) {
         constexpr bool ALLK = decltype(allk_tag)::value;
         constexpr bool AHEAD = decltype(ahead_tag)::value;
@@ -463,7 +465,8 @@ __global__ __launch_bounds__(UPD_THREADS) void update_accumulate_kernel(
 // table (coalesced reads, several in flight), the partial sums meet in LDS.
 // fp64 data: the tables were scaled for one chunk's rows, so the sum over chunks is carried in
 // two limbs.
-// 32 groups, or fewer where there are fewer tables (8117 x 680, K = 1335: one table of 907 800 cells, 112 us with 32 groups).
+// 32 groups, or fewer where there are fewer tables (8117 x 680, K = 1335: one table of 907 800 cells, 112 us with 32
+// groups).
 constexpr int RF_THREADS = 1024;
 static int reduce_groups(int chunks) { return chunks <= 1 ? 1 : (chunks <= 2 ? 2 : (chunks <= 4 ? 4 : (chunks <= 8 ? 8 : 32))); }
 // DMR: two sets of table sums are kept and compared before the partial sums are combined; a
@@ -862,7 +865,8 @@ __global__ __launch_bounds__(256) void sorted_reduce_kernel(const T *X, const in
             for (int i = 0; i < nf; ++i) {
                 const ftk_fault fl = sh_faults[i];
                 if ((int)(fl.wave & 3) == (int)(threadIdx.x >> 6) && (int)fl.tile == step) {
-                    // the addressed lane, moved onto a lane of its row group that owns features, and the sum onto one of them
+                    // the addressed lane, moved onto a lane of its row group that owns features, and the sum onto one
+                    // of them
                     const int fl_lane = (int)(fl.lane & 63);
                     const int pa = min(lpr, (D + E - 1) / E);
                     const bool me = group == (fl_lane >> lpr_log2) && piece == (fl_lane & (lpr - 1)) % pa &&
@@ -1266,18 +1270,19 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finalize_kernel(
     }
 }
 
-// Rows that the other paths may not serve as well.  Longer ones hide the sort once X leaves the memory-side cache: D = 256,
-// sort / buckets, whole calls, us: 10^5, K = 4000 101 / 80, 10^6, K = 300 233 / 283.
+// Rows that the other paths may not serve as well.  Longer ones hide the sort once X leaves the memory-side cache:
+// D = 256, sort / buckets, whole calls, us: 10^5, K = 4000 101 / 80, 10^6, K = 300 233 / 283.
 static bool bucket_pays(int64_t N, int D)
 {
     return D >= 9 && (D <= 128 || (D <= 256 && D % 4 == 0 && (double)N * D * 4 < 268435456.0));
 }
 
-// Where the buckets take over from tables in `nks` slices of clusters: a slice reads all labels and its rows, a bucket
-// costs 40 us whatever the points.  Tables / buckets: D = 12, K = 4000 200000 points 33 / 38 us, 600000 55 / 45, K = 8000 70000
-// 39 / 36; D = 13, K = 2000 70000 24 / 45, 600000 46 / 61, 1500000 88 / 85, K = 4000 300000 47 / 48, K = 8000 150000 50 / 44; D = 9, K = 8000
-// 300000 56 / 49, K = 4000 300000 39 / 50; rows of half a line, whose slices hold few clusters: D = 20, K = 1600 200000 35 / 41,
-// 500000 53 / 49, D = 27, K = 1000 150000 35 / 48, 500000 65 / 62.
+// Where the buckets take over from tables in `nks` slices of clusters: a slice reads all labels and its rows, a
+// bucket costs 40 us whatever the points.  Tables / buckets: D = 12, K = 4000 200000 points 33 / 38 us, 600000
+// 55 / 45, K = 8000 70000 39 / 36; D = 13, K = 2000 70000 24 / 45, 600000 46 / 61, 1500000 88 / 85, K = 4000 300000
+// 47 / 48, K = 8000 150000 50 / 44; D = 9, K = 8000 300000 56 / 49, K = 4000 300000 39 / 50; rows of half a line,
+// whose slices hold few clusters: D = 20, K = 1600 200000 35 / 41, 500000 53 / 49, D = 27, K = 1000 150000 35 / 48,
+// 500000 65 / 62.
 static bool buckets_beat_tables(int64_t N, int D, int nks)
 {
     if (N < 65536 || nks < 4) return false;
@@ -1286,10 +1291,10 @@ static bool buckets_beat_tables(int64_t N, int D, int nks)
 }
 
 // ... and from the label sort, whose cost grows with the clusters; it reads each row by one wave instruction, which
-// ragged rows of several lines gain from.  Whole quads, sort / buckets: 2^21 x 32, K = 4096 174 / 98, 70000 x 64, K = 1000 46 / 38,
-// 500000 x 128, K = 512 91 / 88.  Others: 400000 x 17, K = 2500 62 / 57; 400000 x 33, K = 1000 56 / 67, 150000 x 33, K = 2500 51 / 47;
-// 150000 x 66, K = 1000 48 / 58, 70000 x 66, K = 2500 52 / 47, 400000 x 66, K = 2500 86 / 94; 10^6 x 66, K = 1000 142 / 187; 400000 x 97, K =
-// 8000 135 / 124, 70000 x 126, K = 300 40 / 47.
+// ragged rows of several lines gain from.  Whole quads, sort / buckets: 2^21 x 32, K = 4096 174 / 98, 70000 x 64,
+// K = 1000 46 / 38, 500000 x 128, K = 512 91 / 88.  Others: 400000 x 17, K = 2500 62 / 57; 400000 x 33, K = 1000
+// 56 / 67, 150000 x 33, K = 2500 51 / 47; 150000 x 66, K = 1000 48 / 58, 70000 x 66, K = 2500 52 / 47, 400000 x 66,
+// K = 2500 86 / 94; 10^6 x 66, K = 1000 142 / 187; 400000 x 97, K = 8000 135 / 124, 70000 x 126, K = 300 40 / 47.
 static bool buckets_beat_sort(int64_t N, int D, int K)
 {
     if (D % 4 == 0) return true;
@@ -1350,9 +1355,9 @@ static UpdateLaunch plan_update_launch(ftk_dtype dtype, bool aligned16, int64_t 
     if (g_tuning.update_path >= 0) L.sorted_path = g_tuning.update_path == 1;
     L.E = dtype == FTK_F32 ? 4 : 2;
     if (D < L.E || (!L.sorted_path && !L.u.pieces)) L.E = 1;
-    // Short rows of doubles at odd places, gathered from beyond the memory-side cache: by elements, whose requests end where
-    // lines do (pieces / elements: 2081309 x 19, K = 1213 214 / 195 us, 1600000 x 27, K = 2500 206 / 193; 900000 x 31 117 / 130,
-    // 1000000 x 33, K = 2500 132 / 132).
+    // Short rows of doubles at odd places, gathered from beyond the memory-side cache: by elements, whose requests
+    // end where lines do (pieces / elements: 2081309 x 19, K = 1213 214 / 195 us, 1600000 x 27, K = 2500 206 / 193;
+    // 900000 x 31 117 / 130, 1000000 x 33, K = 2500 132 / 132).
     if (L.sorted_path && dtype == FTK_F64 && !(aligned16 && D % 2 == 0) && D < 32 && x_bytes >= 2.4e8) L.E = 1;
     L.pieces = (int)ceil_div(D, L.E);
     L.lpr_log2 = 0;
